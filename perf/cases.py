@@ -19,7 +19,6 @@ Fields of a case
 """
 import math
 
-import numpy as np
 import torch
 
 import paper_2110_02781_amd as P
@@ -169,6 +168,27 @@ def _init_vector(unit, gen):
     return torch.cat(parts)
 
 
+def _draw_inputs(case, gen, in_shape, out_shape):
+    """({unit: its parameter vector}, the batches, their labels or None, the gradients of their outputs or None)"""
+    units = _units(case)
+    a, b, n = _range(case)
+    tdt = torch.float32 if case["dtype"] == "f32" else torch.bfloat16
+    steps = range(case["steps"])
+    vectors = {u: _init_vector(units[u], gen) for u in range(a, b) if P.models.unit_param_layout(units[u])}
+    xs, labels, dys = [], None, None
+    for _ in steps:
+        x = torch.randn(in_shape, generator=gen, device="cuda")
+        if a > 0 and units[a - 1]["kind"] == B.UNIT_CONV:
+            x = x.clamp_(0.0, 6.0)           # behind an activation; a block's output is a linear bottleneck
+        xs.append(x.to(tdt))
+    if b == n:
+        labels = [torch.randint(0, case["classes"], (case["batch"],), generator=gen, device="cuda", dtype=torch.int32)
+                  for _ in steps]
+    else:
+        dys = [(torch.randn(out_shape, generator=gen, device="cuda") * (0.02 / case["batch"])).to(tdt) for _ in steps]
+    return vectors, xs, labels, dys
+
+
 def prepare(case, seed):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
@@ -181,25 +201,16 @@ def prepare(case, seed):
                     dlogits=torch.empty(b, n, dtype=tdt, device="cuda"), loss=torch.zeros(1, device="cuda"),
                     stream=torch.cuda.current_stream().cuda_stream)
     st = Stage(case)
-    for u, _ in st.n_param:
-        P.stage_import_weights(st.handle, u, _init_vector(st.units[u], gen).cpu().numpy())
     s = dict(case=case, stage=st)
-    steps = case["steps"]
-    s["x"] = []
-    for _ in range(steps):
-        x = torch.randn(st.in_shape, generator=gen, device="cuda")
-        if case["first"] > 0 and st.units[case["first"] - 1]["kind"] == B.UNIT_CONV:
-            x = x.clamp_(0.0, 6.0)           # behind an activation; a block's output is a linear bottleneck
-        s["x"].append(x.to(tdt))
+    vectors, s["x"], s["labels"], s["dy"] = _draw_inputs(case, gen, st.in_shape, st.out_shape)
+    for u, v in vectors.items():
+        P.stage_import_weights(st.handle, u, v.cpu().numpy())
     if st.has_loss:
-        s["labels"] = [torch.randint(0, case["classes"], (case["batch"],), generator=gen, device="cuda", dtype=torch.int32)
-                       for _ in range(steps)]
-        s["loss"] = torch.zeros(steps, device="cuda")
+        s["loss"] = torch.zeros(case["steps"], device="cuda")
     else:
-        s["dy"] = [(torch.randn(st.out_shape, generator=gen, device="cuda") * (0.02 / case["batch"])).to(tdt) for _ in range(steps)]
-        s["y"] = torch.empty((steps,) + st.out_shape, dtype=tdt, device="cuda")
+        s["y"] = torch.empty((case["steps"],) + st.out_shape, dtype=tdt, device="cuda")
     if case["first"] > 0:
-        s["dx"] = torch.empty((steps,) + st.in_shape, dtype=tdt, device="cuda")
+        s["dx"] = torch.empty((case["steps"],) + st.in_shape, dtype=tdt, device="cuda")
     stream = torch.cuda.Stream()
     stream.wait_stream(torch.cuda.current_stream())
     s["stream_object"], s["stream"] = stream, stream.cuda_stream
@@ -329,6 +340,134 @@ def work(case):
     if case["work"] == "pipeline":
         total += steps * n_param * 8.0
     return dict(bytes=total, flops=steps * flops * (1 + (again - 1) / 3))
+
+
+# ---- the same pass in 64 bits ------------------------------------------------------------------------------------
+def _conv(x, w, kh, kw, stride, ph, pw):
+    """[N, H, W, C] by [cout, kh * kw * C], zero padding."""
+    if kh * kw > 1:
+        x = torch.nn.functional.pad(x, (0, 0, pw, pw, ph, ph))
+        Ho, Wo = (x.shape[1] - kh) // stride + 1, (x.shape[2] - kw) // stride + 1
+        x = torch.cat([x[:, i:i + (Ho - 1) * stride + 1:stride, j:j + (Wo - 1) * stride + 1:stride]
+                       for i in range(kh) for j in range(kw)], dim=3)
+    return x @ w.t()
+
+
+def _depthwise(x, w, stride):
+    x = torch.nn.functional.pad(x, (0, 0, 1, 1, 1, 1))
+    Ho, Wo = (x.shape[1] - 3) // stride + 1, (x.shape[2] - 3) // stride + 1
+    return sum(x[:, i:i + (Ho - 1) * stride + 1:stride, j:j + (Wo - 1) * stride + 1:stride] * w[:, 3 * i + j]
+               for i in range(3) for j in range(3))
+
+
+def _norm(z, gamma, beta):
+    var, mean = torch.var_mean(z, (0, 1, 2), correction=0)
+    return (z - mean) * torch.rsqrt(var + 1e-5) * gamma + beta
+
+
+def _unit64(u, x, vector):
+    parts = list(torch.split(vector, [n for _, n, _ in P.models.unit_param_layout(u)])) if vector is not None else []
+    kind = u["kind"]
+    if kind == B.UNIT_CONV:
+        y = _norm(_conv(x, parts[0].view(u["cout"], -1), u["kh"], u["kw"], u["stride"], u.get("pad_h", 0), u.get("pad_w", 0)), *parts[1:])
+        return y.clamp(0.0, 6.0) if u["act"] == B.ACT_RELU6 else y.relu() if u["act"] == B.ACT_RELU else y
+    if kind == B.UNIT_INVRES:
+        h = x
+        if u["expand"] != 1:
+            h = _norm(_conv(h, parts[0].view(-1, u["cin"]), 1, 1, 1, 0, 0), *parts[1:3]).clamp(0.0, 6.0)
+            parts = parts[3:]
+        h = _norm(_depthwise(h, parts[0].view(-1, 9), u["stride"]), *parts[1:3]).clamp(0.0, 6.0)
+        h = _norm(_conv(h, parts[3].view(u["cout"], -1), 1, 1, 1, 0, 0), *parts[4:])
+        return x + h if u["stride"] == 1 and u["cin"] == u["cout"] else h
+    if kind == B.UNIT_GAP:
+        return x.mean((1, 2), keepdim=True)
+    if kind == B.UNIT_FC:
+        return x @ parts[0].view(u["cout"], -1).t() + parts[1]
+    return x
+
+
+def exact(case, seed):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    if case["work"] == "loss":
+        s = prepare(case, seed)
+        logits = s["logits"].double().requires_grad_()
+        loss = torch.nn.functional.cross_entropy(logits, s["labels"].long())
+        return dict(loss=loss.detach()[None], dlogits=torch.autograd.grad(loss, logits)[0])
+    units, (a, b, n) = _units(case), _range(case)
+    H, W, C = case["h"], case["w"], case["cin"]
+    shapes = [(case["batch"], H, W, C)]
+    for u in units:
+        s = u.get("stride", 1)
+        if u["kind"] == B.UNIT_CONV:
+            H, W = (H + 2 * u.get("pad_h", 0) - u["kh"]) // s + 1, (W + 2 * u.get("pad_w", 0) - u["kw"]) // s + 1
+        elif u["kind"] == B.UNIT_INVRES:
+            H, W = (H - 1) // s + 1, (W - 1) // s + 1
+        elif u["kind"] == B.UNIT_GAP:
+            H = W = 1
+        shapes.append((case["batch"], H, W, u["cout"]))
+    vectors, xs, labels, dys = _draw_inputs(case, gen, shapes[a], shapes[b])
+    w = {u: v.double() for u, v in vectors.items()}
+    v = {u: torch.zeros_like(t) for u, t in w.items()}
+    g = {u: torch.zeros_like(t) for u, t in w.items()}
+    out = dict(y=[], loss=[], dx=[None] * len(xs))
+
+    def forward(k):
+        x = xs[k].double().requires_grad_(a > 0)
+        p = {u: t.detach().requires_grad_() for u, t in w.items()}      # an update makes new tensors: this is the version
+        h = x
+        for u in range(a, b):
+            h = _unit64(units[u], h, p.get(u))
+        if b == n:
+            h = torch.nn.functional.cross_entropy(h.reshape(case["batch"], -1), labels[k].long())
+        out["loss" if b == n else "y"].append(h.detach())
+        return x, p, h
+
+    def backward(k, run):
+        x, p, h = run
+        got = torch.autograd.grad(h, list(p.values()) + ([x] if a > 0 else []), None if b == n else dys[k].double())
+        for u, t in zip(p, got):
+            g[u] += t
+        if a > 0:
+            out["dx"][k] = got[-1]
+
+    def update(lr=LR):
+        for u in w:
+            v[u] = MOMENTUM * v[u] + g[u] + DECAY * w[u]
+            w[u] = w[u] - lr * v[u]
+            g[u].zero_()
+
+    n_steps, d = case["steps"], case["depth"]
+    if case["work"] == "gpipe":
+        for k0 in range(0, n_steps, d):
+            for k in range(k0, k0 + d):
+                backward(k, forward(k))
+            update(LR / d)
+    else:
+        flight = {k: forward(k) for k in range(min(d, n_steps))}
+        for k in range(n_steps):
+            backward(k, flight.pop(k))
+            update()
+            if k + d < n_steps:
+                flight[k + d] = forward(k + d)
+                if case["work"] == "pipeline" and (k + 1) % d == 0:
+                    for u in w:
+                        w[u] = sum(run[1][u].detach() for run in flight.values()) / len(flight)
+            elif case["work"] == "train" and k + 1 < n_steps:
+                flight[k + 1] = forward(k + 1)
+    # What one activation decision, taken either way by two correct roundings, moves by more than the rounding itself has no
+    # value to hold a run against: the few losses of a deep network (seen: their error moves by up to 4 times when the inputs
+    # move by a unit in the last place, that of the weights by 1.3 times) and what several blocks in single precision, where
+    # the rounding is small, give out (3 times).
+    res = dict(weights=[t.cpu().numpy() for t in w.values()])
+    deep, jumps = case["net"] == "mbv2", case["dtype"] == "f32" and b - a > 1
+    if b == n:
+        res["loss"] = None if deep else torch.stack(out["loss"])
+    else:
+        res["y"] = None if jumps else torch.stack(out["y"])
+    if a > 0 and (case["dtype"] == "f32" or b - a == 1):
+        res["dx"] = None if jumps else torch.stack(out["dx"])
+    return res
 
 
 def tolerance(case):
