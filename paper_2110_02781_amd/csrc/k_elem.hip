@@ -577,8 +577,9 @@ __device__ __forceinline__ float block_reduce_256(float v, bool is_max, float* s
   return r;
 }
 
+// Rows too wide for a wavefront's registers: block = row, three passes over it.
 template <typename T>
-__global__ void softmax_ce_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B,
+__global__ __launch_bounds__(256) void softmax_ce_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B,
                              int classes, float* __restrict__ row_loss, T* __restrict__ dlogits) {
   __shared__ float smem[256];
   int b = blockIdx.x;
@@ -599,20 +600,187 @@ __global__ void softmax_ce_k(const T* __restrict__ logits, const int32_t* __rest
   if (threadIdx.x == 0) row_loss[b] = lab_ok ? -(to_f32(row[lab]) - mx - logf(s)) : NAN;
 }
 
-__global__ void mean_rows_k(const float* __restrict__ row_loss, int B, float* __restrict__ loss) {
-  __shared__ float smem[256];
+// G lanes (a power of two up to 64) own a row and hold it in registers, E elements each, VEC adjacent ones at a time:
+// the logits are read once and the exponentials taken once.  Element e of lane l is column
+// (l + G * (e / VEC)) * VEC + e % VEC; AL: every row starts on 16 bytes (without it the same columns are read one by
+// one, so the sums and their results do not depend on where the caller's buffers lie).
+// op over the G lanes of a group, the same result in all of them: data-parallel-primitive moves inside a row of 16 lanes
+// (wave_sum), the rows through readlane or one exchange
+template <int G, typename F>
+__device__ __forceinline__ float group_all(float x, F op) {
+  x = op(x, dpp_move<0xB1>(x));
+  x = op(x, dpp_move<0x4E>(x));
+  if (G > 4) x = op(x, dpp_move<0x141>(x));
+  if (G > 8) x = op(x, dpp_move<0x140>(x));
+  if (G == 32) x = op(x, __shfl_xor(x, 16, 64));
+  if (G == 64) {
+    const int xi = __builtin_bit_cast(int, x);
+    const float r0 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 0)), r1 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 16));
+    const float r2 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 32)), r3 = __builtin_bit_cast(float, __builtin_amdgcn_readlane(xi, 48));
+    x = op(op(r0, r1), op(r2, r3));
+  }
+  return x;
+}
+template <int G> __device__ __forceinline__ float group_max(float x) { return group_all<G>(x, [](float a, float b) { return fmaxf(a, b); }); }
+template <int G> __device__ __forceinline__ float group_sum(float x) { return group_all<G>(x, [](float a, float b) { return a + b; }); }
+
+template <typename T, int G, int E, int VEC, bool AL>
+struct CeRow {
+  float v[E];
+  int lab;
+  __device__ __forceinline__ void fetch(const T* __restrict__ row, const int32_t* __restrict__ label, int classes, int l) {
+    lab = *label;
+#pragma unroll
+    for (int q = 0; q < E / VEC; ++q) {
+      const int c = (l + G * q) * VEC;
+      const T* src = row + (c < classes ? c : 0);       // classes % VEC == 0: a vector is in or out
+      if constexpr (VEC == 8 && AL) load8(src, v + q * 8);
+      else
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[q * VEC + e] = to_f32(src[e]);
+    }
+  }
+  // the row's loss, the same in all its lanes
+  __device__ __forceinline__ float finish(T* __restrict__ drow, int classes, int l, float invB) {
+    float mx = -INFINITY, z = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int c = (l + G * (e / VEC)) * VEC + e % VEC;
+      mx = fmaxf(mx, c < classes ? v[e] : -INFINITY);
+    }
+    mx = group_max<G>(mx);
+    float s = 0.f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      const int c = (l + G * (e / VEC)) * VEC + e % VEC;
+      z += c == lab ? v[e] - mx : 0.f;
+      v[e] = c < classes ? expf(v[e] - mx) : 0.f;
+      s += v[e];
+    }
+    s = group_sum<G>(s);
+    z = group_sum<G>(z);
+    const float invs = 1.f / s;
+#pragma unroll
+    for (int q = 0; q < E / VEC; ++q) {
+      const int c = (l + G * q) * VEC;
+      if (c >= classes) continue;
+      float d[VEC];
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) d[e] = (v[q * VEC + e] * invs - (c + e == lab ? 1.f : 0.f)) * invB;
+      if constexpr (VEC == 8 && AL) store8(drow + c, d);
+      else
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) drow[c + e] = from_f32<T>(d[e]);
+    }
+    return lab >= 0 && lab < classes ? -(z - logf(s)) : NAN;    // an invalid label yields a NaN loss, never a stray read
+  }
+};
+
+// Wavefront = row.  Bound by memory: 4096 x 1000 bfloat16 moves 16 MB; a block per row, which goes over its row three
+// times with six block-wide reductions between, took 14 us.
+template <typename T, int E, int VEC, bool AL>
+__global__ __launch_bounds__(256) void softmax_ce_wave_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B,
+                                                         int classes, float* __restrict__ row_loss, T* __restrict__ dlogits) {
+  const int l = threadIdx.x & 63, b = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (b >= B) return;
+  CeRow<T, 64, E, VEC, AL> r;
+  r.fetch(logits + (size_t)b * classes, labels + b, classes, l);
+  const float loss = r.finish(dlogits + (size_t)b * classes, classes, l, 1.f / (float)B);
+  if (l == 0) row_loss[b] = loss;
+}
+
+// Few elements: one block does all rows and their mean.  Latency only, and a second dependent launch is half of it.
+template <typename T, int G, int E>
+__global__ __launch_bounds__(1024) void softmax_ce_one_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B,
+                                                         int classes, T* __restrict__ dlogits, float* __restrict__ loss) {
+  enum { ROWS = 1024 / G };
+  __shared__ float part[16];
+  const int l = threadIdx.x % G, g = threadIdx.x / G;
+  const float invB = 1.f / (float)B;
+  float sum = 0.f;
+  CeRow<T, G, E, 1, false> r, next;
+  int b = g;
+  const int b0 = b < B ? b : 0;
+  r.fetch(logits + (size_t)b0 * classes, labels + b0, classes, l);
+  for (; b < B; b += ROWS) {
+    const int bn = b + ROWS < B ? b + ROWS : b;
+    next.fetch(logits + (size_t)bn * classes, labels + bn, classes, l);     // in flight while this row is worked on
+    sum += r.finish(dlogits + (size_t)b * classes, classes, l, invB);
+    r = next;
+  }
+  sum = wave_sum(l == 0 ? sum : 0.f);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sum;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) t += part[w];
+    *loss = t / (float)B;
+  }
+}
+
+__global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ row_loss, int B, float* __restrict__ loss) {
+  __shared__ float part[16];
+  const int nt = blockDim.x;
   float s = 0.f;
-  for (int i = threadIdx.x; i < B; i += 256) s += row_loss[i];
-  s = block_reduce_256(s, false, smem);
-  if (threadIdx.x == 0) *loss = s / (float)B;
+  for (int i0 = threadIdx.x; i0 < B; i0 += 8 * nt) {        // eight loads per trip to memory
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = row_loss[i0 + nt * u < B ? i0 + nt * u : 0];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += i0 + nt * u < B ? x[u] : 0.f;
+  }
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float t = 0.f;
+    for (int w = 0; w < nt / 64; ++w) t += part[w];
+    *loss = t / (float)B;
+  }
+}
+
+// One block for everything where its lane groups need at most two rounds of short rows (or one of longer ones), two
+// launches otherwise.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean
+// kernel): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4,
+// 4096 x 10 11.4 / 24 / 6.4, 4096 x 1000 bfloat16 16.8 / - / 7.8, 16384 x 1000 bfloat16 62 / - / 19.
+template <typename T>
+static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* labels, int B, int classes, float* row_loss, T* dlogits,
+                              float* loss) {
+  const int G = classes <= 16 ? 8 : classes <= 64 ? 16 : classes <= 128 ? 32 : 64;      // lanes of a row in the one-block kernel
+  if (classes <= 1024 && B <= (classes <= 256 ? 2 : 1) * (1024 / G)) {
+#define FTP_CE_ONE(G, E) hipLaunchKernelGGL((softmax_ce_one_k<T, G, E>), dim3(1), dim3(1024), 0, st, logits, labels, B, classes, dlogits, loss)
+    if (classes <= 16) FTP_CE_ONE(8, 2);
+    else if (classes <= 32) FTP_CE_ONE(16, 2);
+    else if (classes <= 64) FTP_CE_ONE(16, 4);
+    else if (classes <= 128) FTP_CE_ONE(32, 4);
+    else if (classes <= 256) FTP_CE_ONE(64, 4);
+    else if (classes <= 512) FTP_CE_ONE(64, 8);
+    else FTP_CE_ONE(64, 16);
+#undef FTP_CE_ONE
+    return;
+  }
+  const dim3 rows((unsigned)((B + 3) / 4));
+  const bool al = ((uintptr_t)logits | (uintptr_t)dlogits) % 16 == 0;      // the buffers are the caller's
+#define FTP_CE_WAVE(E, VEC, AL)   hipLaunchKernelGGL((softmax_ce_wave_k<T, E, VEC, AL>), rows, dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits)
+#define FTP_CE_WAVE8(E) do { if (al) FTP_CE_WAVE(E, 8, true); else FTP_CE_WAVE(E, 8, false); } while (0)
+  if (classes > 1024)
+    hipLaunchKernelGGL(softmax_ce_k<T>, dim3(B), dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits);
+  else if (classes % 8 == 0 && classes > 256) { if (classes <= 512) FTP_CE_WAVE8(8); else FTP_CE_WAVE8(16); }
+  else if (classes <= 64) FTP_CE_WAVE(1, 1, false);
+  else if (classes <= 128) FTP_CE_WAVE(2, 1, false);
+  else if (classes <= 256) FTP_CE_WAVE(4, 1, false);
+  else if (classes <= 512) FTP_CE_WAVE(8, 1, false);
+  else FTP_CE_WAVE(16, 1, false);
+#undef FTP_CE_WAVE8
+#undef FTP_CE_WAVE
+  hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(B <= 2048 ? 256 : 1024), 0, st, row_loss, B, loss);
 }
 
 void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* labels, int B, int classes,
                 float* row_loss, void* dlogits, float* loss) {
   KScope ks(st, "softmax_ce", 2.0 * B * classes * (dt == 0 ? 4.0 : 2.0), 8.0 * B * classes);
-  FTP_DISPATCH(dt, hipLaunchKernelGGL(softmax_ce_k<T>, dim3(B), dim3(256), 0, st, (const T*)logits, labels, B,
-                                      classes, row_loss, (T*)dlogits));
-  hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(256), 0, st, row_loss, B, loss);
+  FTP_DISPATCH(dt, softmax_ce_launch<T>(st, (const T*)logits, labels, B, classes, row_loss, (T*)dlogits, loss));
 }
 
 // block = 16 output columns x 16 row lanes; the row lanes' sums meet in LDS in a fixed order
