@@ -16,6 +16,7 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-
 SOURCES = [
     ("k_elem.hip", ["-x", "hip"]),
     ("k_conv.hip", ["-x", "hip"]),
+    ("k_conv1d.hip", ["-x", "hip"]),
     ("k_gemm.hip", ["-x", "hip"]),
     ("k_fused.hip", ["-x", "hip"]),
     ("k_gemm_deep.hip", ["-x", "hip"]),

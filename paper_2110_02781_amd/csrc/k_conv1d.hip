@@ -1,0 +1,668 @@
+// Convolutions along one axis (1 x kw, stride 1, same length out as in), at most 64 channels on either side, as
+// implicit GEMMs: row m of the patch matrix is kw neighbouring rows of the input, so the matrix is never written.  A tile
+// of rows with its halo goes into LDS once (through the producer's BatchNorm + activation) and every tap reads it
+// there at a row offset; rows are the flattened (window, position) index, so a tile may span windows of any length, and a tap
+// that leaves its own window reads zero.  All products run on the fp32 MFMA (products of bfloat16 values are exact in it).
+// What bounds them is that unit, 256 FLOP a cycle and CU (157 TFLOP/s): 64 -> 64 channels, 5 taps, 32768 rows is 8.5 us a pass.
+#include "dev_common.h"
+#include "kernels.h"
+
+namespace ftp {
+
+#define FTP_DISPATCH(dt, ...)                   \
+  do {                                          \
+    if ((dt) == 0) { typedef float T; __VA_ARGS__; } \
+    else { typedef bf16_t T; __VA_ARGS__; }     \
+  } while (0)
+
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+struct Conv1dArgs {
+  const void* x;      // the tensor read at row offsets: A (forward, weight gradient), dZ (data gradient)
+  const void* w;      // [Cout][kw][Cin] (forward, data gradient); dZ (weight gradient)
+  View view;          // of x: forward and weight gradient
+  View prev;          // data gradient with sums: the BatchNorm + activation whose dA this is
+  void* out;
+  float* stats;       // [nranges][2][NC] or nullptr
+  int M, W;           // rows, window length
+  int C, NC;          // channels of x, output columns
+  int Cin, Cout, kw, pad;   // pad: rows in front of the output row at tap 0
+  int CP;             // C rounded up to 8: reduction index k = tap * CP + channel
+  int itiles, jtiles, tiles_per_range;
+};
+
+enum { kC1Chan = 64, kC1Taps = 9, kC1Small = 2048 };
+
+// ---- row tiles: forward and data gradient ---------------------------------------------------------------------
+// 4 wavefronts of 32 x 32 results: 64 rows x 64 columns (WC 2), or 64 x 32 with two wavefronts on each half of the reduction
+// (WC 1).  Weights pass through LDS 64 reduction elements per wavefront at a time, the next chunk on its way in registers
+// while one is multiplied.  64-row tiles leave two blocks per CU at 32768 rows (two wavefronts per SIMD hide each other's
+// LDS reads and barriers); 64 -> 64 channels, 5 taps there: 20 us forward, 25 us data
+// gradient; patch matrix + GEMM took 63 and 51.
+template <typename T, bool DGRAD, int WC>
+__global__ __launch_bounds__(256) void conv1d_rows_k(Conv1dArgs p) {
+  constexpr int TI = 64, BC = 32 * WC, KS = 64, KC = KS * 2 / WC, WLD = KC + 4;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int LDR = (p.CP / 4) % 2 ? p.CP : p.CP + 4;       // an odd number of 16-byte units: rows fall into different banks
+  const int prow = TI + p.kw - 1;                         // row prow is the zero row
+  float* xs = smem;
+  float* wsm = smem + (prow + 1) * LDR;                   // [2][BC][WLD]
+  __shared__ float red[2][BC][2];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+  const int wr = wave & 1, wc = WC == 2 ? wave >> 1 : 0, ks = WC == 2 ? 0 : wave >> 1;
+  const int lb = xcd_logical_block();
+  const int jt = lb % p.jtiles, range = lb / p.jtiles;
+  const int j0 = jt * BC;
+  const int KP = p.kw * p.CP, nchunk = (KP + KC - 1) / KC;
+  const T* X = reinterpret_cast<const T*>(p.x);
+  const T* Wt = reinterpret_cast<const T*>(p.w);
+  const bool vec = p.C % 8 == 0;
+  const bool view = !DGRAD && p.view.scale != nullptr;
+  const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
+  const int it_beg = range * p.tiles_per_range, it_end = min(it_beg + p.tiles_per_range, p.itiles);
+  const unsigned cp_magic = 65536u / (unsigned)p.CP + 1u;     // k / CP for k < 9 * 64: exact (k * CP < 65536)
+
+  // weight chunk kc into registers / from there into LDS (column-major: a column's chunk is contiguous)
+  constexpr int WE = BC * KC / 256;
+  float wreg[WE];
+  auto fetch_w = [&](int kc) {
+    if (!DGRAD && vec) {
+#pragma unroll
+      for (int s = 0; s < WE / 8; ++s) {
+        const int v = tid + 256 * s, col = v / (KC / 8), k = kc * KC + (v % (KC / 8)) * 8;
+        const bool in = j0 + col < p.NC && k < KP;            // CP == C: k is the offset in a weight row
+        load8(Wt + (in ? (size_t)(j0 + col) * KP + k : 0), wreg + 8 * s);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) wreg[8 * s + e] = in ? wreg[8 * s + e] : 0.f;
+      }
+    } else if (DGRAD && p.NC % 4 == 0) {                      // CP == C here too: k / C is the tap, k % C the channel of dZ
+#pragma unroll
+      for (int s = 0; s < WE / 4; ++s) {
+        const int v = tid + 256 * s, col = v % (BC / 4) * 4, k = kc * KC + v / (BC / 4);
+        const int tap = (int)(((unsigned)k * cp_magic) >> 16), c = k - tap * p.CP;
+        const bool in = j0 + col < p.NC && k < KP;
+        const float4 x = load4(Wt + (in ? ((size_t)c * p.kw + (p.kw - 1 - tap)) * p.Cin + j0 + col : 0));
+        wreg[4 * s] = in ? x.x : 0.f; wreg[4 * s + 1] = in ? x.y : 0.f; wreg[4 * s + 2] = in ? x.z : 0.f; wreg[4 * s + 3] = in ? x.w : 0.f;
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < WE; ++s) {
+        const int e = tid + 256 * s;
+        const int col = DGRAD ? e % BC : e / KC, kk = DGRAD ? e / BC : e % KC;
+        const int k = kc * KC + kk, tap = (int)(((unsigned)k * cp_magic) >> 16), c = k - tap * p.CP;
+        const bool in = j0 + col < p.NC && k < KP && c < p.C;
+        const size_t at = DGRAD ? ((size_t)c * p.kw + (p.kw - 1 - tap)) * p.Cin + j0 + col : ((size_t)(j0 + col) * p.kw + tap) * p.Cin + c;
+        const float x = to_f32(Wt[in ? at : 0]);
+        wreg[s] = in ? x : 0.f;
+      }
+    }
+  };
+  auto commit_w = [&](int buf) {
+    float* dst = wsm + buf * BC * WLD;
+    if (!DGRAD && vec) {
+#pragma unroll
+      for (int s = 0; s < WE / 8; ++s) {
+        const int v = tid + 256 * s;
+        store8(dst + v / (KC / 8) * WLD + v % (KC / 8) * 8, wreg + 8 * s);
+      }
+    } else if (DGRAD && p.NC % 4 == 0) {
+#pragma unroll
+      for (int s = 0; s < WE / 4; ++s) {
+        const int v = tid + 256 * s;
+#pragma unroll
+        for (int f = 0; f < 4; ++f) dst[(v % (BC / 4) * 4 + f) * WLD + v / (BC / 4)] = wreg[4 * s + f];
+      }
+    } else {
+#pragma unroll
+      for (int s = 0; s < WE; ++s) {
+        const int e = tid + 256 * s;
+        const int col = DGRAD ? e % BC : e / KC, kk = DGRAD ? e / BC : e % KC;
+        dst[col * WLD + kk] = wreg[s];
+      }
+    }
+  };
+
+  for (int c = tid; c < LDR; c += 256) xs[prow * LDR + c] = 0.f;
+  float s1 = 0.f, s2 = 0.f;
+  const int col = j0 + wc * 32 + l32;
+  const bool col_ok = col < p.NC;
+  float psc = 0.f, psh = 0.f;
+  const bool sums = DGRAD && p.stats != nullptr;
+  if (sums && col_ok) { psc = p.prev.scale[col]; psh = p.prev.shift[col]; }
+  for (int it = it_beg; it < it_end; ++it) {
+    const int m0 = it * TI;
+    fetch_w(0);
+    const int mb = m0 + wr * 32 + 4 * h;                // rows of this lane's results, see below
+    float zp[16];
+    if (sums) {
+      const T* Z = reinterpret_cast<const T*>(p.prev.z);
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int m = mb + 8 * (r >> 2) + (r & 3);
+        zp[r] = to_f32(Z[col_ok && m < p.M ? (size_t)m * p.NC + col : 0]);
+      }
+    }
+    __syncthreads();                                    // the tile before has been read
+    if (vec) {
+      const int CG = p.CP / 8, nv = prow * CG;
+      for (int v0 = tid; v0 < nv; v0 += 4 * 256) {
+        float val[4][8];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int v = v0 + 256 * s, r = v / CG, m = m0 - p.pad + r;
+          load8(X + (v < nv && m >= 0 && m < p.M ? (size_t)m * p.C + (v - r * CG) * 8 : 0), val[s]);
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int v = v0 + 256 * s, r = v / CG, cg = v - r * CG, m = m0 - p.pad + r;
+          if (v >= nv) break;
+          const bool in = m >= 0 && m < p.M;
+          if (view) {
+            float sc[8], sh[8];
+            load8(p.view.scale + cg * 8, sc);
+            load8(p.view.shift + cg * 8, sh);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) val[s][e] = round_to<T>(clamp_act(fmaf(val[s][e], sc[e], sh[e]), lo, hi));
+          }
+#pragma unroll
+          for (int e = 0; e < 8; ++e) val[s][e] = in ? val[s][e] : 0.f;
+          store8(xs + r * LDR + cg * 8, val[s]);
+        }
+      }
+    } else {
+      const int n = prow * p.CP;
+      for (int i0 = tid; i0 < n; i0 += 4 * 256) {
+        float val[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int i = i0 + 256 * s, r = i / p.CP, c = i - r * p.CP, m = m0 - p.pad + r;
+          const bool in = i < n && m >= 0 && m < p.M && c < p.C;
+          val[s] = to_f32(X[in ? (size_t)m * p.C + c : 0]);
+          if (view) val[s] = round_to<T>(clamp_act(fmaf(val[s], p.view.scale[in ? c : 0], p.view.shift[in ? c : 0]), lo, hi));
+          val[s] = in ? val[s] : 0.f;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int i = i0 + 256 * s, r = i / p.CP;
+          if (i < n) xs[r * LDR + i - r * p.CP] = val[s];
+        }
+      }
+    }
+    commit_w(0);
+    __syncthreads();
+    const int mrow = m0 + wr * 32 + l32;
+    const int t = mrow < p.M ? (int)((unsigned)mrow % (unsigned)p.W) : -(1 << 20);   // a row past the end is outside every window
+    f16v acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    auto tap_row = [&](int tp) { return xs + ((unsigned)(t + tp - p.pad) < (unsigned)p.W ? wr * 32 + l32 + tp : prow) * LDR + 4 * h; };
+    for (int kc = 0; kc < nchunk; ++kc) {
+      if (kc + 1 < nchunk) fetch_w(kc + 1);
+      const float* brow = wsm + (kc & 1) * BC * WLD + (wc * 32 + l32) * WLD + ks * KS + 4 * h;
+      const int k0 = kc * KC + ks * KS, nq = min(KS, KP - k0) / 8;      // KP is a multiple of 8; may be past the end
+      int tap = (int)(((unsigned)k0 * cp_magic) >> 16), c0 = k0 - tap * p.CP;
+      if (tap > p.kw) tap = p.kw;
+      const float* arow = tap_row(tap);
+      float4 a = ld4(arow + c0), b = ld4(brow);
+      for (int q = 0; q < nq; ++q) {                    // the next operands are on their way while four products run
+        c0 += 8;
+        if (c0 == p.CP) { c0 = 0; ++tap; arow = tap_row(tap); }       // behind the last tap: at most the zero row, not used
+        const float4 an = ld4(arow + c0), bn = ld4(brow + 8 * (q + 1 < nq ? q + 1 : q));
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
+        a = an; b = bn;
+      }
+      if (kc + 1 < nchunk) {
+        commit_w((kc + 1) & 1);                         // the buffer read before this chunk: all have passed the barrier behind it
+        __syncthreads();
+      }
+    }
+    if constexpr (WC == 1) {                            // the two halves of the reduction meet
+      __syncthreads();
+      float* half = wsm + wr * 16 * 64 + lane;
+      if (ks == 1)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) half[r * 64] = acc[r];
+      __syncthreads();
+      if (ks == 1) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] += half[r * 64];
+    }
+    // register r: row 8 * (r / 4) + 4 * h + r % 4, column l32
+    T* out = reinterpret_cast<T*>(p.out);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int m = mb + 8 * (r >> 2) + (r & 3);
+      const bool ok = col_ok && m < p.M;
+      if (ok) out[(size_t)m * p.NC + col] = from_f32<T>(acc[r]);
+      const float v = round_to<T>(acc[r]);              // sums are those of the values as stored
+      if (sums) {
+        const float dy = ok ? v * act_mask(fmaf(zp[r], psc, psh), p.prev.act) : 0.f;
+        s1 += dy;
+        s2 += ok ? dy * zp[r] : 0.f;
+      } else {
+        s1 += ok ? v : 0.f;
+        s2 += ok ? v * v : 0.f;
+      }
+    }
+  }
+  if (p.stats) {
+    s1 += __shfl_xor(s1, 32, 64);
+    s2 += __shfl_xor(s2, 32, 64);
+    if (h == 0 && ks == 0) { red[0][wc * 32 + l32][wr] = s1; red[1][wc * 32 + l32][wr] = s2; }
+    __syncthreads();
+    if (tid < 2 * BC) {
+      const int sq = tid / BC, c = tid % BC;
+      if (j0 + c < p.NC) p.stats[((size_t)range * 2 + sq) * p.NC + j0 + c] = red[sq][c][0] + red[sq][c][1];
+    }
+  }
+}
+
+// ---- weight gradient over row tiles ---------------------------------------------------------------------------
+// A block takes a range of 64-row tiles (dZ and the input with its halo in LDS) and a set of 32 x 80 pieces of
+// g_w [Cout][kw * Cin]: a wavefront keeps 2 x 5 tiles of 16 x 16 in accumulators over all its rows and reads seven LDS words for
+// ten MFMAs.  Pieces that leave wavefronts over share their rows among them.  One partial per block and row share.  64 -> 64
+// channels, 32768 rows: 28 us (patch matrix + GEMM 73); the next tile in registers while one is multiplied, or four row groups'
+// LDS reads together, measured no faster.
+struct Conv1dWgArgs {
+  Conv1dArgs c;
+  int nco, nkg;            // pieces along Cout (32 each) and along kw * Cin (80 each)
+  int gpb, rs;             // pieces per block, wavefronts that share a piece's rows: gpb * rs <= 4
+  int ngrp;                // blocks per row range
+};
+enum { kC1WgRows = 64, kC1RT = 2, kC1CT = 5 };
+
+template <typename T>
+__global__ __launch_bounds__(256) void conv1d_wgrad_k(Conv1dWgArgs a) {
+  const Conv1dArgs& p = a.c;
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  // 16 or 48 banks between rows: the four rows of an MFMA operand fall into different banks
+  const int LDR = (p.Cin + 31) / 32 * 32 + 16, LDZ = (p.Cout + 31) / 32 * 32 + 16;
+  const int prow = kC1WgRows + p.kw - 1;
+  float* xs = smem;
+  float* ds = smem + prow * LDR;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, rg = lane >> 4;
+  const int grp = blockIdx.x % a.ngrp, range = blockIdx.x / a.ngrp;
+  const int piece = grp * a.gpb + wave % a.gpb, rsub = wave / a.gpb;
+  const bool live = piece < a.nco * a.nkg && rsub < a.rs;
+  const int pco = piece % a.nco, pkg = piece / a.nco;
+  const int K = p.kw * p.Cin;
+  const T* X = reinterpret_cast<const T*>(p.x);
+  const T* D = reinterpret_cast<const T*>(p.w);
+  const bool view = p.view.scale != nullptr;
+  const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
+  int off[kC1CT], tj[kC1CT], doff[kC1RT];
+#pragma unroll
+  for (int q = 0; q < kC1CT; ++q) {
+    const int k = (pkg * kC1CT + q) * 16 + l16;
+    const int tap = k / p.Cin;
+    off[q] = k < K ? tap * LDR + (k - tap * p.Cin) : 0;
+    tj[q] = k < K ? tap - p.pad : -(1 << 20);           // a column past the end is outside every window
+  }
+#pragma unroll
+  for (int q = 0; q < kC1RT; ++q) {
+    const int co = (pco * kC1RT + q) * 16 + l16;
+    doff[q] = co < p.Cout ? co : 0;                     // its results are not written
+  }
+  f4v acc[kC1RT][kC1CT];
+#pragma unroll
+  for (int i = 0; i < kC1RT; ++i)
+#pragma unroll
+    for (int q = 0; q < kC1CT; ++q) acc[i][q] = f4v{0.f, 0.f, 0.f, 0.f};
+
+  const int it_end = min((range + 1) * p.tiles_per_range, p.itiles);
+  for (int it = range * p.tiles_per_range; it < it_end; ++it) {
+    const int m0 = it * kC1WgRows;
+    __syncthreads();
+    {
+      const int CG = p.Cout / 8, nv = kC1WgRows * CG;
+      for (int v = tid; v < nv; v += 256) {
+        const int r = v / CG, cg = v - r * CG, m = m0 + r;
+        const bool in = m < p.M;
+        float val[8];
+        load8(D + (in ? (size_t)m * p.Cout + cg * 8 : 0), val);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[e] = in ? val[e] : 0.f;
+        store8(ds + r * LDZ + cg * 8, val);
+      }
+    }
+    if (p.Cin % 8 == 0) {
+      const int CG = p.Cin / 8, nv = prow * CG;
+      for (int v = tid; v < nv; v += 256) {
+        const int r = v / CG, cg = v - r * CG, m = m0 - p.pad + r;
+        const bool in = m >= 0 && m < p.M;
+        float val[8];
+        load8(X + (in ? (size_t)m * p.Cin + cg * 8 : 0), val);
+        if (view) {
+          float sc[8], sh[8];
+          load8(p.view.scale + cg * 8, sc);
+          load8(p.view.shift + cg * 8, sh);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) val[e] = round_to<T>(clamp_act(fmaf(val[e], sc[e], sh[e]), lo, hi));
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[e] = in ? val[e] : 0.f;
+        store8(xs + r * LDR + cg * 8, val);
+      }
+    } else {
+      for (int i = tid; i < prow * p.Cin; i += 256) {
+        const int r = i / p.Cin, c = i - r * p.Cin, m = m0 - p.pad + r;
+        const bool in = m >= 0 && m < p.M;
+        float x = to_f32(X[in ? (size_t)m * p.Cin + c : 0]);
+        if (view) x = round_to<T>(clamp_act(fmaf(x, p.view.scale[c], p.view.shift[c]), lo, hi));
+        xs[r * LDR + c] = in ? x : 0.f;
+      }
+    }
+    __syncthreads();
+    if (live) {
+      const int r_step = 4 * a.rs;
+      int t = (int)((unsigned)(m0 + 4 * rsub + rg) % (unsigned)p.W);
+      for (int r = 4 * rsub + rg; r < kC1WgRows; r += r_step) {
+        const bool row_ok = m0 + r < p.M;
+        float d[kC1RT], x[kC1CT];
+#pragma unroll
+        for (int q = 0; q < kC1RT; ++q) d[q] = ds[r * LDZ + doff[q]];
+#pragma unroll
+        for (int q = 0; q < kC1CT; ++q) x[q] = xs[r * LDR + off[q]];
+#pragma unroll
+        for (int q = 0; q < kC1CT; ++q) x[q] = row_ok && (unsigned)(t + tj[q]) < (unsigned)p.W ? x[q] : 0.f;
+#pragma unroll
+        for (int q = 0; q < kC1CT; ++q)
+#pragma unroll
+          for (int i = 0; i < kC1RT; ++i) acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[i], x[q], acc[i][q], 0, 0, 0);
+        t += r_step;                                    // at most 16, and a window has at least 16 rows
+        t -= t >= p.W ? p.W : 0;
+      }
+    }
+  }
+  if (!live) return;
+  float* out = reinterpret_cast<float*>(p.out) + (size_t)(range * a.rs + rsub) * p.Cout * K;
+#pragma unroll
+  for (int i = 0; i < kC1RT; ++i)
+#pragma unroll
+    for (int q = 0; q < kC1CT; ++q) {
+      const int k = (pkg * kC1CT + q) * 16 + l16;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int co = (pco * kC1RT + i) * 16 + 4 * rg + r;
+        if (co < p.Cout && k < K) out[(size_t)co * K + k] = acc[i][q][r];
+      }
+    }
+}
+
+// ---- few rows: latency only ----------------------------------------------------------------------------------
+// 16 x 16 results of forward or data gradient by four wavefronts that split the reduction, fragments straight from global
+// memory (1024 rows, 64 -> 64 channels: 4.9 us; patch matrix, padded weights and GEMM were three launches of 11) with up to five steps in flight (64 channels x 5 taps: one trip), wavefronts meet in LDS.  CV: channels of x are
+// a multiple of 4, so a lane's four reduction elements lie in one tap and in one vector.
+template <typename T, bool DGRAD, bool CV, int NW>
+__device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) {
+  constexpr int U = 5, GROUPS = NW / 4;
+  __shared__ float red[GROUPS][4][16][17];
+  __shared__ float sred[GROUPS][2][16][17];
+  const int grp = threadIdx.x >> 8, wave = (threadIdx.x >> 6) & 3, lane = threadIdx.x & 63;
+  const int tile = bid * GROUPS + grp;
+  const bool tile_ok = tile < p.itiles * p.jtiles;
+  const int jt = tile % p.jtiles, it = tile / p.jtiles;
+  const int m0 = it * 16, j0 = jt * 16, l16 = lane & 15, kg = (lane >> 4) * 4;
+  const int K = p.kw * p.C, nst = (K + 15) / 16, sb = wave * nst / 4, se = (wave + 1) * nst / 4;
+  const int row = m0 + l16, col = j0 + l16;
+  const bool row_ok = tile_ok && row < p.M, col_ok = tile_ok && col < p.NC;
+  const int t = (int)((unsigned)row % (unsigned)p.W);
+  const T* X = reinterpret_cast<const T*>(p.x);
+  const T* Wt = reinterpret_cast<const T*>(p.w);
+  const bool view = !DGRAD && p.view.scale != nullptr;
+  const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
+  f4v acc = {0.f, 0.f, 0.f, 0.f};
+  for (int s0 = sb; s0 < se; s0 += U) {
+    float a[U][4], b[U][4], sc[U][4], sh[U][4];
+    bool ok[U][4], kin[U][4];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+#pragma unroll
+      for (int e = 0; e < 4; e += CV ? 4 : 1) {
+        const int k = (s0 + u) * 16 + kg + e;
+        kin[u][e] = s0 + u < se && k < K;
+        const int kc = kin[u][e] ? k : 0, tap = kc / p.C, c = kc - tap * p.C;
+        ok[u][e] = kin[u][e] && row_ok && (unsigned)(t + tap - p.pad) < (unsigned)p.W;
+        const size_t xa = ok[u][e] ? (size_t)(row + tap - p.pad) * p.C + c : 0;
+        const int cc = col_ok ? col : 0;
+        if constexpr (CV) {
+          *reinterpret_cast<float4*>(a[u]) = load4(X + xa);
+          if (view) { *reinterpret_cast<float4*>(sc[u]) = ld4(p.view.scale + c); *reinterpret_cast<float4*>(sh[u]) = ld4(p.view.shift + c); }
+          if constexpr (!DGRAD) *reinterpret_cast<float4*>(b[u]) = load4(Wt + (size_t)cc * K + kc);
+          else
+#pragma unroll
+            for (int f = 0; f < 4; ++f) b[u][f] = to_f32(Wt[((size_t)(c + f) * p.kw + (p.kw - 1 - tap)) * p.Cin + cc]);
+        } else {
+          a[u][e] = to_f32(X[xa]);
+          if (view) { sc[u][e] = p.view.scale[c]; sh[u][e] = p.view.shift[c]; }
+          b[u][e] = to_f32(Wt[DGRAD ? ((size_t)c * p.kw + (p.kw - 1 - tap)) * p.Cin + cc : (size_t)cc * K + kc]);
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool in = ok[u][CV ? 0 : e], kn = kin[u][CV ? 0 : e];
+        float x = a[u][e];
+        if (view) x = round_to<T>(clamp_act(fmaf(x, sc[u][e], sh[u][e]), lo, hi));
+        acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? x : 0.f, kn ? b[u][e] : 0.f, acc, 0, 0, 0);
+      }
+  }
+  // (a row or column outside the tensor, or a step past the end, contributed 0 x 0; a column outside is not written)
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[grp][wave][4 * (lane >> 4) + r][l16] = acc[r];
+  __syncthreads();
+  const int orow = (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
+  const bool in = tile_ok && m0 + orow < p.M && j0 + ocol < p.NC;
+  const float v = red[grp][0][orow][ocol] + red[grp][1][orow][ocol] + red[grp][2][orow][ocol] + red[grp][3][orow][ocol];
+  if (in) reinterpret_cast<T*>(p.out)[(size_t)(m0 + orow) * p.NC + j0 + ocol] = from_f32<T>(v);
+  if (!DGRAD && p.stats) {
+    const float sv = in ? round_to<T>(v) : 0.f;
+    sred[grp][0][orow][ocol] = sv;
+    sred[grp][1][orow][ocol] = sv * sv;
+    __syncthreads();
+    if ((threadIdx.x & 255) < 32 && tile_ok) {
+      const int sq = (threadIdx.x >> 4) & 1, c = threadIdx.x & 15;
+      float tot = 0.f;
+#pragma unroll
+      for (int rr = 0; rr < 16; ++rr) tot += sred[grp][sq][rr][c];
+      if (j0 + c < p.NC) p.stats[((size_t)it * 2 + sq) * p.NC + j0 + c] = tot;
+    }
+  }
+}
+
+template <typename T, bool CV>
+__global__ __launch_bounds__(256) void conv1d_fwd_small_k(Conv1dArgs p) { conv1d_tile<T, false, CV, 4>(p, xcd_logical_block()); }
+
+// 16 x 16 of g_w by 16 wavefronts that split the rows: no partial buffers, at most two rounds of eight row groups at 1024 rows
+template <typename T>
+__device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __restrict__ g_w, const int bid) {
+  constexpr int U = 8, NW = 16;
+  __shared__ float red[NW][16][17];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, mg = lane >> 4;
+  const int K = p.kw * p.Cin, jt_n = (K + 15) / 16;
+  const int jt = bid % jt_n, it = bid / jt_n;
+  const int co = it * 16 + l16, k = jt * 16 + l16;
+  const bool co_ok = co < p.Cout, k_ok = k < K;
+  const int tap = k_ok ? k / p.Cin : 0, ci = k_ok ? k - tap * p.Cin : 0, dt = tap - p.pad;
+  const T* D = reinterpret_cast<const T*>(p.w) + (co_ok ? co : 0);
+  const T* X = reinterpret_cast<const T*>(p.x) + ci;
+  const bool view = p.view.scale != nullptr;
+  const float sc = view ? p.view.scale[ci] : 1.f, sh = view ? p.view.shift[ci] : 0.f;
+  const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
+  // the gradient element this thread adds to, requested now
+  const int orow = (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
+  const bool writer = threadIdx.x < 256 && it * 16 + orow < p.Cout && jt * 16 + ocol < K;
+  float* dst = g_w + (writer ? (size_t)(it * 16 + orow) * K + jt * 16 + ocol : 0);
+  float g_old = writer ? *dst : 0.f;
+  const int per = (p.M + 4 * NW - 1) / (4 * NW) * 4, mb = wave * per, me = min(mb + per, p.M);
+  f4v acc = {0.f, 0.f, 0.f, 0.f};
+  int t = (int)((unsigned)(mb + mg) % (unsigned)p.W);
+  for (int m = mb; m < me; m += 4 * U) {
+    T dr[U], xr[U];
+    bool xin[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int mm = m + 4 * u + mg;
+      xin[u] = mm < me && k_ok && (unsigned)(t + dt) < (unsigned)p.W;
+      dr[u] = D[(size_t)(mm < me ? mm : mb) * p.Cout];
+      xr[u] = X[xin[u] ? (size_t)(mm + dt) * p.Cin : 0];
+      t += 4;
+      t -= t >= p.W ? p.W : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      float x = to_f32(xr[u]);
+      if (view) x = round_to<T>(clamp_act(fmaf(x, sc, sh), lo, hi));
+      const bool din = m + 4 * u + mg < me && co_ok;
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(din ? to_f32(dr[u]) : 0.f, xin[u] ? x : 0.f, acc, 0, 0, 0);
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][4 * mg + r][l16] = acc[r];
+  __syncthreads();
+  asm volatile("" : "+v"(g_old));
+  if (writer) {
+    float v = 0.f;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) v += red[q][orow][ocol];
+    *dst = g_old + v;
+  }
+}
+
+// both gradients of a layer in one launch: blocks [0, n_dgrad) hold four data-gradient tiles each
+template <typename T, bool CV>
+__global__ __launch_bounds__(1024) void conv1d_bwd_small_k(Conv1dArgs d, Conv1dArgs g, float* g_w, int n_dgrad) {
+  if ((int)blockIdx.x < n_dgrad) conv1d_tile<T, true, CV, 16>(d, blockIdx.x);
+  else conv1d_wgrad_tile<T>(g, g_w, blockIdx.x - n_dgrad);
+}
+
+// ---- host ---------------------------------------------------------------------------------------------------
+int conv1d_ok(const ConvGeom& g) {
+  // windows of 16 and more: the row counters wrap at most once a step; 32-bit row and element indexes
+  return g.kh == 1 && g.Hin == 1 && g.Hout == 1 && g.ph == 0 && g.stride == 1 && g.kw >= 2 && g.kw <= kC1Taps && g.kw % 2 == 1 &&
+         2 * g.pw == g.kw - 1 && g.Win >= 16 && g.Cin <= kC1Chan && g.Cout <= kC1Chan && g.Cout % 8 == 0 &&
+         (size_t)g.N * g.Win * kC1Chan < ((size_t)1 << 31);
+}
+
+static bool conv1d_small(const ConvGeom& g) { return (size_t)g.N * g.Win <= kC1Small; }
+
+static Conv1dArgs conv1d_args(const ConvGeom& g, bool dgrad) {
+  Conv1dArgs a{};
+  a.M = g.N * g.Win; a.W = g.Win; a.Cin = g.Cin; a.Cout = g.Cout; a.kw = g.kw;
+  a.pad = dgrad ? g.kw - 1 - g.pw : g.pw;
+  a.C = dgrad ? g.Cout : g.Cin;
+  a.NC = dgrad ? g.Cin : g.Cout;
+  a.CP = (a.C + 7) / 8 * 8;
+  return a;
+}
+
+static void conv1d_plan_tiles(Conv1dArgs* a) {
+  a->itiles = (a->M + 15) / 16; a->jtiles = (a->NC + 15) / 16; a->tiles_per_range = 1;
+}
+
+// tile shape by the columns (a 64-wide tile over 32 columns or fewer would be half padding); at most kBnPartials row
+// ranges, since each leaves one partial
+template <typename T, bool DGRAD>
+static void conv1d_rows(hipStream_t st, Conv1dArgs& a, int* P_out) {
+  const int WC = a.NC <= 32 ? 1 : 2, TI = 64;
+  a.itiles = (a.M + TI - 1) / TI;
+  a.jtiles = (a.NC + 32 * WC - 1) / (32 * WC);
+  a.tiles_per_range = (a.itiles + kBnPartials - 1) / kBnPartials;
+  const int nr = (a.itiles + a.tiles_per_range - 1) / a.tiles_per_range;
+  const int LDR = (a.CP / 4) % 2 ? a.CP : a.CP + 4;
+  const size_t lds = ((size_t)(TI + a.kw) * LDR + (size_t)2 * 32 * WC * (128 / WC + 4)) * sizeof(float);
+  if (lds > 65536 - 1024) { launch_plan_failed("conv1d: tile does not fit LDS"); return; }
+  if (P_out) *P_out = nr;
+  if (WC == 1) hipLaunchKernelGGL((conv1d_rows_k<T, DGRAD, 1>), dim3(nr * a.jtiles), dim3(256), lds, st, a);
+  else hipLaunchKernelGGL((conv1d_rows_k<T, DGRAD, 2>), dim3(nr * a.jtiles), dim3(256), lds, st, a);
+}
+
+void conv1d_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, void* z, float* stats, int* P_out) {
+  Conv1dArgs a = conv1d_args(g, false);
+  a.x = in.z; a.w = w; a.view = View{in.z, in.scale, in.shift, in.act}; a.out = z; a.stats = stats;
+  KScope ks(st, "conv1d_fwd", ((double)a.M * (g.Cin + g.Cout) + (double)g.Cout * g.kw * g.Cin) * (dt == 0 ? 4.0 : 2.0),
+            2.0 * a.M * g.Cout * g.kw * g.Cin, a.M, g.kw * g.Cin, g.Cout);
+  if (conv1d_small(g)) {
+    conv1d_plan_tiles(&a);
+    *P_out = a.itiles;
+    const dim3 grid(a.itiles * a.jtiles);
+    if (g.Cin % 4 == 0) FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_fwd_small_k<T, true>), grid, dim3(256), 0, st, a));
+    else FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_fwd_small_k<T, false>), grid, dim3(256), 0, st, a));
+    return;
+  }
+  FTP_DISPATCH(dt, (conv1d_rows<T, false>(st, a, P_out)));
+}
+
+void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out) {
+  Conv1dArgs a = conv1d_args(g, true);
+  a.x = dz; a.w = w; a.out = dIn; a.stats = sums; a.prev = View{prev.z, prev.scale, prev.shift, prev.act};
+  KScope ks(st, "conv1d_dgrad", ((double)a.M * (g.Cin + g.Cout) + (double)g.Cout * g.kw * g.Cin) * (dt == 0 ? 4.0 : 2.0),
+            2.0 * a.M * g.Cout * g.kw * g.Cin, a.M, g.kw * g.Cout, g.Cin);
+  FTP_DISPATCH(dt, (conv1d_rows<T, true>(st, a, P_out)));
+}
+
+static Conv1dWgArgs conv1d_wgrad_plan(const ConvGeom& g, int* P) {
+  Conv1dWgArgs a{};
+  a.c = conv1d_args(g, false);
+  a.nco = (g.Cout + 16 * kC1RT - 1) / (16 * kC1RT);
+  a.nkg = (g.kw * g.Cin + 16 * kC1CT - 1) / (16 * kC1CT);
+  const int pieces = a.nco * a.nkg;
+  a.gpb = pieces >= 4 ? 4 : pieces >= 2 ? 2 : 1;
+  a.rs = 4 / a.gpb;
+  a.ngrp = (pieces + a.gpb - 1) / a.gpb;
+  a.c.itiles = (a.c.M + kC1WgRows - 1) / kC1WgRows;
+  // two blocks per CU; every row share leaves a partial of the whole gradient.  One block per CU halves the partials, but
+  // its single wavefront per SIMD waits for every LDS read (64 -> 64 channels, 32768 rows: 37 us against 28)
+  const int want = 512 / a.ngrp > 0 ? 512 / a.ngrp : 1;
+  a.c.tiles_per_range = (a.c.itiles + want - 1) / want;
+  *P = (a.c.itiles + a.c.tiles_per_range - 1) / a.c.tiles_per_range * a.rs;
+  return a;
+}
+
+size_t conv1d_wgrad_ws(const ConvGeom& g) {
+  int P;
+  conv1d_wgrad_plan(g, &P);
+  return (size_t)P * g.Cout * g.kw * g.Cin;
+}
+
+void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w) {
+  int P;
+  Conv1dWgArgs a = conv1d_wgrad_plan(g, &P);
+  const int K = g.kw * g.Cin;
+  a.c.x = in.z; a.c.w = dz; a.c.view = View{in.z, in.scale, in.shift, in.act};
+  if (conv1d_small(g)) {
+    KScope ks(st, "conv1d_wgrad", (double)a.c.M * (g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)g.Cout * K * 8, 2.0 * a.c.M * g.Cout * K,
+              a.c.M, K, g.Cout);
+    FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_bwd_small_k<T, true>), dim3((K + 15) / 16 * ((g.Cout + 15) / 16)), dim3(1024), 0, st, a.c, a.c, g_w, 0));
+    return;
+  }
+  {
+    KScope ks(st, "conv1d_wgrad", (double)a.c.M * (g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)P * g.Cout * K * 4, 2.0 * a.c.M * g.Cout * K,
+              a.c.M, K, g.Cout);
+    a.c.out = ws;
+    const int LDR = (g.Cin + 31) / 32 * 32 + 16, LDZ = (g.Cout + 31) / 32 * 32 + 16;
+    const size_t lds = ((size_t)(kC1WgRows + g.kw - 1) * LDR + (size_t)kC1WgRows * LDZ) * sizeof(float);
+    FTP_DISPATCH(dt, hipLaunchKernelGGL(conv1d_wgrad_k<T>, dim3(P / a.rs * a.ngrp), dim3(256), lds, st, a));
+  }
+  reduce_partials(st, ws, P, (size_t)g.Cout * K, K, (size_t)K, 1, g_w);
+}
+
+int conv1d_bwd_small_ok(const ConvGeom& g) { return conv1d_small(g); }
+void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn) {
+  Conv1dArgs d = conv1d_args(g, true), a = conv1d_args(g, false);
+  d.x = dz; d.w = w; d.out = dIn;
+  conv1d_plan_tiles(&d);
+  a.x = in.z; a.w = dz; a.view = View{in.z, in.scale, in.shift, in.act};
+  const int K = g.kw * g.Cin, nd = (d.itiles * d.jtiles + 3) / 4, nw = (K + 15) / 16 * ((g.Cout + 15) / 16);
+  KScope ks(st, "conv1d_bwd", (double)d.M * (2.0 * g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)g.Cout * K * 8, 4.0 * d.M * g.Cout * K,
+            d.M, K, g.Cout);
+  FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_bwd_small_k<T, true>), dim3(nd + nw), dim3(1024), 0, st, d, a, g_w, nd));
+}
+
+}  // namespace ftp

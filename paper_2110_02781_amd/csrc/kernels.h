@@ -141,6 +141,17 @@ void conv_direct_wgrad(int dt, hipStream_t st, const void* dz, HView in, const C
 void reduce_partials(hipStream_t st, const float* ws, int P, size_t QC, int C, size_t stride_q, size_t stride_c,
                      float* g, int valid_c = -1);
 
+// ---- 1 x kw convolutions, stride 1, same length, at most 64 channels (conv1d_ok): implicit GEMMs, no scratch but ws ----
+int conv1d_ok(const ConvGeom& g);
+void conv1d_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, void* z, float* stats, int* P_out);
+// sums != nullptr (prev is a view): also the partial sums bn_bwd_reduce would compute for the BatchNorm + activation `prev`
+void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out);
+size_t conv1d_wgrad_ws(const ConvGeom& g);
+void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w);
+// few rows (conv1d_bwd_small_ok): weight and data gradient in one launch
+int conv1d_bwd_small_ok(const ConvGeom& g);
+void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn);
+
 // ---- depthwise 3x3 ----------------------------------------------------------------
 // stats != nullptr (only if dw_fwd_stats_ok): the kernel also writes the BatchNorm partial sums [*P_out][2][C] of z
 int dw_fwd_stats_ok(int dt, const ConvGeom& g);

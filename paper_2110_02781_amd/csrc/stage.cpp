@@ -386,16 +386,17 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       if (sb.g.Cout > max_c) max_c = sb.g.Cout;
       ConvGeom g = sb.g; g.N = batch;
       size_t M = (size_t)batch * g.Hout * g.Wout;
-      size_t need = sb.type == SUB_DIRECT ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_wgrad_ws(g) : pw_wgrad_ws(M, g.Cin, g.Cout);
+      const bool c1 = sb.type == SUB_DIRECT && conv1d_ok(g), patches = sb.type == SUB_DIRECT && !c1;
+      size_t need = c1 ? conv1d_wgrad_ws(g) : patches ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_wgrad_ws(g) : pw_wgrad_ws(M, g.Cin, g.Cout);
       if (need > ws_floats) ws_floats = need;
       if (i == a && &sb == &u.subs[0]) s->ws_tail_floats = need;
       if (sb.type == SUB_PW && m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > s->ws_fused_floats)
         s->ws_fused_floats = pw_bwd_fused_ws(M, g.Cin, g.Cout);
-      if (sb.type == SUB_DIRECT) ++s->n_direct;
-      if (sb.type == SUB_DIRECT && conv_direct_gemm_ok(g) && conv_direct_gemm_wpad_elems(g) > ws_floats)
+      if (patches) ++s->n_direct;
+      if (patches && conv_direct_gemm_ok(g) && conv_direct_gemm_wpad_elems(g) > ws_floats)
         ws_floats = conv_direct_gemm_wpad_elems(g);      // padded weight copy of the GEMM forward (at most 4 bytes each)
-      if (sb.type == SUB_DIRECT && conv_direct_im2col_elems(g) > s->im2col_elems) s->im2col_elems = conv_direct_im2col_elems(g);
-      if (sb.type == SUB_DIRECT && conv_direct_dgrad_gemm_ok(g)) {
+      if (patches && conv_direct_im2col_elems(g) > s->im2col_elems) s->im2col_elems = conv_direct_im2col_elems(g);
+      if (patches && conv_direct_dgrad_gemm_ok(g)) {
         if (conv_direct_dgrad_gemm_im2col_elems(g) > s->im2col_elems) s->im2col_elems = conv_direct_dgrad_gemm_im2col_elems(g);
         if (conv_direct_dgrad_gemm_w_elems(g) > ws_floats) ws_floats = conv_direct_dgrad_gemm_w_elems(g);
       }
@@ -657,6 +658,8 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
       *pend = BnPending{s->bn_part, P, M, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv};
       return;
     }
+  } else if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
+    conv1d_fwd(s->dt, st, in, w, g, z, s->bn_part, &P);
   } else if (sb.type == SUB_DIRECT && conv_direct_gemm_ok(g) && s->im2col &&
              conv_direct_gemm_wpad_elems(g) * s->es <= s->ws_floats * sizeof(float)) {
     // the float workspace is free during a forward: the padded weight copy lives there
@@ -999,7 +1002,11 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     pw_bwd(s->dt, st, dz, w, res, in, M, g.Cin, g.Cout, s->ws, gw, dIn);
     return FTP_OK;
   }
-  if (sb.type == SUB_DIRECT) {
+  if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
+    if (!overlap && dIn && conv1d_bwd_small_ok(g)) { conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn); return FTP_OK; }
+    conv1d_wgrad(s->dt, ws, dz, in, g, wsp, gw);
+  }
+  else if (sb.type == SUB_DIRECT) {
     conv_direct_wgrad(s->dt, ws, dz, in, g, s->im2col, wsp, gw, s->im2col_of == out.z);
     s->im2col_of = nullptr;      // one weight gradient per forward: nobody else can want these patches
   }
@@ -1010,7 +1017,13 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     s->join_pending[b] = true;
   }
   if (dIn) {
-    if (sb.type == SUB_DIRECT) {
+    if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
+      // behind another convolution of the stage: this is the dA of that one's BatchNorm + activation
+      const bool sums = in.scale != nullptr && !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cin);
+      conv1d_dgrad(s->dt, st, dz, w, g, dIn, in, sums ? s->bn_part : nullptr, &s->bwd_sums_P);
+      if (sums) s->bwd_sums_of = dIn;
+    }
+    else if (sb.type == SUB_DIRECT) {
       // the scratch buffers are shared with the weight gradients: fine on one stream, but a stage that runs them on
       // the side stream keeps the direct kernel
       if (conv_direct_dgrad_gemm_ok(g) && !stage_forks(s) && s->im2col) {

@@ -122,7 +122,7 @@ def test_config1_cnn1d_train_steps():
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_cnn1d_at_a_larger_batch(dtype):
     """The 1-D CNN at batch 40 (5120 positions per layer): the convolutions leave the short-problem kernels and
-    run as patch matrix + row-streaming MFMA GEMM (forward, data gradient, weight gradient)."""
+    run on row tiles (forward, data gradient, weight gradient)."""
     print(f"cnn1d batch 40 {dtype}", flush=True)
     o, h = OM.cnn1d(), hip_models().cnn1d_units()
     if dtype == "f32":
