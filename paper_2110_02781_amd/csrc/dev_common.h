@@ -124,6 +124,15 @@ __device__ __forceinline__ int xcd_logical(const int b, const int nb) {    // b 
   const int x = b & 7, idx = b >> 3, q = nb >> 3, rem = nb & 7;
   return x * q + (x < rem ? x : rem) + idx;
 }
+// Several jobs in one launch: job j's blocks start at blk0[j], a multiple of 8 (so that each job is dealt evenly over the XCDs
+// whatever its blocks cost), and are numbered per XCD.  Returns the job and sets lb to the block's number in it (may be
+// past the job's last block: the padding to 8).
+__device__ __forceinline__ int group_job(const int* __restrict__ blk0, const int n, int& lb) {      // blk0[n] is the end
+  const int ln = threadIdx.x & 63, b = blockIdx.x;
+  const int j = __builtin_amdgcn_readfirstlane(__popcll(__ballot(ln < n && blk0[ln < n ? ln : 0] <= b)) - 1);
+  lb = xcd_logical(b - blk0[j], blk0[j + 1] - blk0[j]);
+  return j;
+}
 __device__ __forceinline__ int xcd_logical_block() { return xcd_logical(blockIdx.x, gridDim.x); }
 
 // four consecutive channels as a float4

@@ -75,6 +75,75 @@ void reduce_partials(hipStream_t st, const float* ws, int P, size_t QC, int C, s
                        stride_q, stride_c, valid_c, g);
 }
 
+// Several tensors' partials in one launch: a block takes 16 outputs with 16 lanes each (many partials) or 256 outputs (up to
+// 16 partials).  A launch per tensor was 3-10 us, most of it ramp, a trip or two to memory and tail.
+enum { kReduceJobs = 64 };
+struct ReduceGroup { ReduceJob job[kReduceJobs]; int blk0[kReduceJobs + 1]; int n; };
+__global__ __launch_bounds__(256) void reduce_group_k(ReduceGroup a) {
+  __shared__ double sm[16][17];
+  int b0;
+  const ReduceJob r = a.job[group_job(a.blk0, a.n, b0)];
+  const size_t QC = r.QC;
+  if (r.P <= 16) {
+    const int j = b0 * 256 + threadIdx.x;
+    if (j >= r.QC) return;
+    float v[16];
+#pragma unroll
+    for (int p = 0; p < 16; ++p) v[p] = r.ws[(p < r.P ? (size_t)p * QC : 0) + j];
+    const int q = j / r.C, c = j - q * r.C;
+    if (c >= r.valid_c) return;
+    float* dst = r.g + (size_t)c * r.stride_c + (size_t)q * r.stride_q;
+    const float old = *dst;
+    double s = 0.0;
+#pragma unroll
+    for (int p = 0; p < 16; ++p) s += p < r.P ? (double)v[p] : 0.0;
+    *dst = old + (float)s;
+    return;
+  }
+  const int jl = threadIdx.x & 15, lane = threadIdx.x >> 4, j = b0 * 16 + jl;
+  double s = 0.0;
+  if (j < r.QC) {
+    for (int p0 = lane; p0 < r.P; p0 += 128) {          // eight loads a trip, past the end the first one again (not added)
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = r.ws[(size_t)(p0 + 16 * u < r.P ? p0 + 16 * u : lane) * QC + j];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += p0 + 16 * u < r.P ? (double)v[u] : 0.0;
+    }
+  }
+  sm[lane][jl] = s;
+  __syncthreads();
+  if (lane == 0 && j < r.QC) {
+    const int q = j / r.C, c = j - q * r.C;
+    if (c < r.valid_c) {
+      double t = 0.0;
+#pragma unroll
+      for (int l = 0; l < 16; ++l) t += sm[l][jl];
+      r.g[(size_t)c * r.stride_c + (size_t)q * r.stride_q] += (float)t;
+    }
+  }
+}
+
+void reduce_group(hipStream_t st, const ReduceJob* jobs, int n) {
+  while (n > 0) {
+    ReduceGroup a{};
+    double bytes = 0, flops = 0;
+    int blocks = 0;
+    for (a.n = 0; a.n < n && a.n < kReduceJobs; ++a.n) {
+      const ReduceJob& r = jobs[a.n];
+      a.job[a.n] = r;
+      a.blk0[a.n] = blocks;
+      blocks += ((r.P <= 16 ? (r.QC + 255) / 256 : (r.QC + 15) / 16) + 7) / 8 * 8;
+      bytes += (r.P + 2.0) * r.QC * 4;
+      flops += (double)r.P * r.QC;
+    }
+    a.blk0[a.n] = blocks;
+    KScope ks(st, "reduce_partials", bytes, flops);
+    hipLaunchKernelGGL(reduce_group_k, dim3(blocks), dim3(256), 0, st, a);
+    jobs += a.n; n -= a.n;
+  }
+}
+
 // ======================================================== generic direct conv
 static const int kWChunkFloats = 8192;  // LDS weight chunk: 32 KB
 
@@ -1279,14 +1348,13 @@ __device__ __forceinline__ float2 round2(float2 v, bf16_t) {
 }
 
 template <typename T, int S, bool VIEW>
-__global__ __launch_bounds__(256) void dw_wgrad_march_k(DwMarchArgs a) {
+__device__ __forceinline__ void dw_wgrad_march_body(const DwMarchArgs& a, const int lb) {
   constexpr int R = S == 1 ? 2 : 1;
   constexpr int NCOL = (R - 1) * S + 3;
   __shared__ float2 red[4][9][64];
   // Every slab has blocks in proportion to its work (a narrow tail slab takes many strips per wavefront and needs
   // few): with the same number for all, half the resident blocks of a layer with a tail slab had nothing to do and the
   // wide slabs' blocks took a second round.
-  const int lb = xcd_logical_block();
   int si = 0;
   while (si + 1 < a.nslab && lb >= a.slab[si + 1].blk0) ++si;
   const DwMarchSlab sl = a.slab[si];
@@ -1430,6 +1498,19 @@ __global__ __launch_bounds__(256) void dw_wgrad_march_k(DwMarchArgs a) {
     for (int pz = sl.nblk + p; pz < a.P; pz += sl.nblk)
       *reinterpret_cast<float2*>(a.ws + ((size_t)pz * 9 + t) * a.C + sl.ch0 + kDwMarchCpl * gg) = zero2;
   }
+}
+
+template <typename T, int S, bool VIEW>
+__global__ __launch_bounds__(256) void dw_wgrad_march_k(DwMarchArgs a) { dw_wgrad_march_body<T, S, VIEW>(a, xcd_logical_block()); }
+
+// several layers in one launch, the layers' blocks one behind the other
+enum { kDwMarchJobs = 8 };
+struct DwMarchGroup { DwMarchArgs job[kDwMarchJobs]; int blk0[kDwMarchJobs + 1]; int n; };
+template <typename T, int S, bool VIEW>
+__global__ __launch_bounds__(256) void dw_wgrad_march_group_k(DwMarchGroup a) {
+  int lb;
+  const int ji = group_job(a.blk0, a.n, lb);
+  if (lb < a.job[ji].nblocks) dw_wgrad_march_body<T, S, VIEW>(a.job[ji], lb);
 }
 
 // slabs (powers of two, widest first) and the number of blocks; false if the layer needs more slabs than the kernel takes
@@ -1763,17 +1844,22 @@ size_t dw_wgrad_ws(const ConvGeom& g) {
   return n * 9 * g.Cout;
 }
 
+// Where the row kernel pays (measured, all layer shapes of the two MobileNetV2 widths): images of 112 x 112 and more whose
+// channel count the marching kernel has to cut into a wide slab and a narrow tail.  Power-of-two channel counts, and the
+// smaller images (too few rows per block to hide the step's barrier behind), stay with the marching kernel.
+static bool dw_rows_pays(int dt, const ConvGeom& g) {
+  DwMarchArgs m{};
+  DwRowsArgs r{};
+  size_t lds;
+  return dt == 1 && (size_t)g.Hin * g.Win >= (size_t)112 * 112 && dw_march_plan(g, &m) && m.nslab > 1 && dw_rows_plan(g, &r, &lds);
+}
+
 void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w) {
   const int es = dt == 0 ? 4 : 2;
   {
     DwRowsArgs r{};
     size_t lds;
-    // Where it pays (measured, all layer shapes of the two MobileNetV2 widths): images of 112 x 112 and more whose channel
-    // count the marching kernel has to cut into a wide slab and a narrow tail.  Power-of-two channel counts, and the
-    // smaller images (too few rows per block to hide the step's barrier behind), stay with the marching kernel.
-    DwMarchArgs mm{};
-    const bool tail = dw_march_plan(g, &mm) && mm.nslab > 1;
-    if (dt == 1 && tail && (size_t)g.Hin * g.Win >= (size_t)112 * 112 && dw_rows_plan(g, &r, &lds)) {
+    if (dw_rows_pays(dt, g) && dw_rows_plan(g, &r, &lds)) {
       r.dz = (const bf16_t*)dz; r.in = (const bf16_t*)in.z; r.scale = in.scale; r.shift = in.shift; r.act = in.act; r.ws = ws;
       {
         KScope ks(st, "dw_wgrad", ((double)g.N * g.Hin * g.Win * g.Cout + (double)g.N * g.Hout * g.Wout * g.Cout) * es + (double)r.P * 9 * g.Cout * 4,
@@ -1827,6 +1913,43 @@ void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& 
     }
   }
   reduce_partials(st, ws, d.nblocks, (size_t)9 * g.Cout, g.Cout, 1, 9, g_w);
+}
+
+void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::vector<ReduceJob>* left) {
+  const int es = dt == 0 ? 4 : 2;
+  for (int kind = 0; kind < 4; ++kind) {
+    const int stride = 1 + (kind & 1);
+    const bool vw = (kind & 2) != 0;
+    DwMarchGroup a{};
+    int blocks = 0;
+    double bytes = 0, flops = 0;
+    auto launch = [&]() {
+      if (a.n == 0) return;
+      a.blk0[a.n] = blocks;
+      KScope ks(st, "dw_wgrad", bytes, flops);
+#define FTP_MARCH(S, V) FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_group_k<T, S, V>), dim3(blocks), dim3(256), 0, st, a))
+      if (stride == 1) { if (vw) FTP_MARCH(1, true); else FTP_MARCH(1, false); }
+      else { if (vw) FTP_MARCH(2, true); else FTP_MARCH(2, false); }
+#undef FTP_MARCH
+      a.n = 0; blocks = 0; bytes = flops = 0;
+    };
+    for (int i = 0; i < n; ++i) {
+      const DwWgradJob& w = jobs[i];
+      if (w.g.stride != stride || (w.in.scale != nullptr) != vw) continue;
+      DwMarchArgs m{};
+      // what another kernel serves (a layer the marching kernel cannot cut into its slabs, the large images) goes by itself
+      if (dw_rows_pays(dt, w.g) || !dw_march_plan(w.g, &m)) { dw_wgrad(dt, st, w.dz, w.in, w.g, w.ws, w.g_w); continue; }
+      m.dz = w.dz; m.in = View{w.in.z, w.in.scale, w.in.shift, w.in.act}; m.ws = w.ws;
+      a.blk0[a.n] = blocks;
+      a.job[a.n++] = m;
+      blocks += (m.nblocks + 7) / 8 * 8;
+      bytes += ((double)w.g.N * w.g.Hin * w.g.Win * w.g.Cout + (double)w.g.N * w.g.Hout * w.g.Wout * w.g.Cout) * es + (double)m.P * 9 * w.g.Cout * 4;
+      flops += 18.0 * w.g.N * w.g.Hout * w.g.Wout * w.g.Cout;
+      left->push_back(ReduceJob{w.ws, w.g_w, m.P, 9 * w.g.Cout, w.g.Cout, 1, 9, w.g.Cout});
+      if (a.n == kDwMarchJobs) launch();
+    }
+    launch();
+  }
 }
 
 }  // namespace ftp

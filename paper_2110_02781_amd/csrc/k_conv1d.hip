@@ -631,7 +631,8 @@ size_t conv1d_wgrad_ws(const ConvGeom& g) {
   return (size_t)P * g.Cout * g.kw * g.Cin;
 }
 
-void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w) {
+void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w,
+                  std::vector<ReduceJob>* left) {
   int P;
   Conv1dWgArgs a = conv1d_wgrad_plan(g, &P);
   const int K = g.kw * g.Cin;
@@ -650,7 +651,7 @@ void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGe
     const size_t lds = ((size_t)(kC1WgRows + g.kw - 1) * LDR + (size_t)kC1WgRows * LDZ) * sizeof(float);
     FTP_DISPATCH(dt, hipLaunchKernelGGL(conv1d_wgrad_k<T>, dim3(P / a.rs * a.ngrp), dim3(256), lds, st, a));
   }
-  reduce_partials(st, ws, P, (size_t)g.Cout * K, K, (size_t)K, 1, g_w);
+  left->push_back(ReduceJob{ws, g_w, P, g.Cout * K, K, K, 1, K});
 }
 
 int conv1d_bwd_small_ok(const ConvGeom& g) { return conv1d_small(g); }

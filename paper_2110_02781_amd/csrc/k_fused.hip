@@ -287,7 +287,7 @@ static void fused_launch_shape(hipStream_t st, const FusedArgs& a, const FusedPl
 
 void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, const void* w, const void* a_in,
                   const void* res, size_t M, int K, int N, float* ws, float* g_w, void* dIn, hipStream_t st_sum,
-                  hipEvent_t ev_sum) {
+                  hipEvent_t ev_sum, std::vector<ReduceJob>* left) {
   FusedPlan f;
   if (!fused_plan(M, K, N, &f)) { launch_plan_failed("fused pointwise backward called for a shape it does not take"); return; }
   FusedArgs a{};
@@ -307,7 +307,8 @@ void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, 
       return;
     }
   }
-  reduce_partials(st_sum, ws, f.P, (size_t)N * K, K, (size_t)K, 1, g_w, K);
+  if (left) left->push_back(ReduceJob{ws, g_w, f.P, N * K, K, K, 1, K});
+  else reduce_partials(st_sum, ws, f.P, (size_t)N * K, K, (size_t)K, 1, g_w, K);
 }
 
 }  // namespace ftp
@@ -335,12 +336,11 @@ struct WgTrArgs {
 };
 
 template <bool VIEW>
-__global__ __launch_bounds__(256) void pw_wgrad_tr_k(WgTrArgs p) {
+__device__ __forceinline__ void pw_wgrad_tr_body(const WgTrArgs& p, const int lb) {
   constexpr int LDN = kWgN + 8, LDK = kWgK + 8;
   __shared__ __attribute__((aligned(16))) bf16_t sZ[2][kWgRows * LDN];
   __shared__ __attribute__((aligned(16))) bf16_t sA[2][kWgRows * LDK];
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, G = lane >> 4;
-  const int lb = xcd_logical_block();
   const int jt = lb % p.jtiles, rest = lb / p.jtiles, it = rest % p.itiles, split = rest / p.itiles;
   const int n0 = it * kWgN, k0 = jt * kWgK;
   const size_t mb = (size_t)split * p.mchunk, me = mb + p.mchunk < p.M ? mb + p.mchunk : p.M;
@@ -435,14 +435,30 @@ __global__ __launch_bounds__(256) void pw_wgrad_tr_k(WgTrArgs p) {
     }
 }
 
-static bool wg_tr_plan(size_t M, int K, int N, WgTrArgs* a, int* S) {
+template <bool VIEW>
+__global__ __launch_bounds__(256) void pw_wgrad_tr_k(WgTrArgs p) { pw_wgrad_tr_body<VIEW>(p, xcd_logical_block()); }
+
+// several layers in one launch, the layers' blocks one behind the other
+enum { kWgTrJobs = 24 };
+struct WgTrGroup { WgTrArgs job[kWgTrJobs]; int blk0[kWgTrJobs + 1]; int n; };
+template <bool VIEW>
+__global__ __launch_bounds__(256) void pw_wgrad_tr_group_k(WgTrGroup a) {
+  int lb;
+  const int ji = group_job(a.blk0, a.n, lb);
+  const WgTrArgs& p = a.job[ji];
+  if ((size_t)(lb / (p.itiles * p.jtiles)) * p.mchunk < p.M) pw_wgrad_tr_body<VIEW>(p, lb);
+}
+
+// share: how many layers share the launch (pw_wgrad_tr_group): together they need no more blocks than one alone
+static bool wg_tr_plan(size_t M, int K, int N, WgTrArgs* a, int* S, int share = 1) {
   if (K % 8 || N % 8 || M <= 2048 || N < 48) return false;     // a 128-column strip of a narrower dZ is mostly padding: measured slower
   a->itiles = (N + kWgN - 1) / kWgN;
   a->jtiles = (K + kWgK - 1) / kWgK;
   const size_t tiles = (size_t)a->itiles * a->jtiles;
   // about 512 blocks: with 1024 the kernel itself takes the same time, but twice the partial tiles are written and
   // summed afterwards (more than the operands themselves for the layers with large weight matrices)
-  size_t s = (512 + tiles - 1) / tiles;
+  const size_t want = share <= 2 ? 512 : share >= 10 ? 96 : 1024 / share;
+  size_t s = (want + tiles - 1) / tiles;
   const size_t smax = (M + 2 * kWgRows - 1) / (2 * kWgRows);
   if (s > smax) s = smax;
   if (s > (size_t)kMaxPartials) s = kMaxPartials;
@@ -459,10 +475,10 @@ int pw_wgrad_tr_ok(int dt, size_t M, int K, int N) {
   int S;
   return dt == 1 && wg_tr_plan(M, K, N, &a, &S);
 }
-size_t pw_wgrad_tr_ws(size_t M, int K, int N) {
+size_t pw_wgrad_tr_ws(size_t M, int K, int N, int share) {
   WgTrArgs a{};
   int S;
-  if (!wg_tr_plan(M, K, N, &a, &S)) return 0;
+  if (!wg_tr_plan(M, K, N, &a, &S, share)) return 0;
   return (size_t)S * N * K;
 }
 void pw_wgrad_tr(hipStream_t st, const void* dz, HView av, size_t M, int K, int N, float* ws, float* g_w, int K_out) {
@@ -479,6 +495,38 @@ void pw_wgrad_tr(hipStream_t st, const void* dz, HView av, size_t M, int K, int 
   }
   if (K_out < 0) K_out = K;
   reduce_partials(st, ws, S, (size_t)N * K, K, (size_t)K_out, 1, g_w, K_out);
+}
+
+void pw_wgrad_tr_group(hipStream_t st, const PwWgradJob* jobs, int n, int share, std::vector<ReduceJob>* left) {
+  for (int view = 0; view < 2; ++view) {
+    WgTrGroup a{};
+    int blocks = 0;
+    double bytes = 0, flops = 0;
+    auto launch = [&]() {
+      if (a.n == 0) return;
+      a.blk0[a.n] = blocks;
+      KScope ks(st, "pw_wgrad", bytes, flops);
+      if (view) hipLaunchKernelGGL(pw_wgrad_tr_group_k<true>, dim3(blocks), dim3(256), 0, st, a);
+      else hipLaunchKernelGGL(pw_wgrad_tr_group_k<false>, dim3(blocks), dim3(256), 0, st, a);
+      a.n = 0; blocks = 0; bytes = flops = 0;
+    };
+    for (int i = 0; i < n; ++i) {
+      const PwWgradJob& w = jobs[i];
+      WgTrArgs t{};
+      int S = 1;
+      if ((w.a.scale != nullptr) != (view != 0) || !wg_tr_plan(w.M, w.K, w.N, &t, &S, share)) continue;
+      t.dz = (const bf16_t*)w.dz; t.a = (const bf16_t*)w.a.z; t.scale = w.a.scale; t.shift = w.a.shift; t.act = w.a.act;
+      t.ws = w.ws; t.M = w.M; t.K = w.K; t.N = w.N;
+      a.blk0[a.n] = blocks;
+      a.job[a.n++] = t;
+      blocks += (t.itiles * t.jtiles * S + 7) / 8 * 8;
+      bytes += ((double)w.M * w.K + (double)w.M * w.N) * 2.0 + (double)S * w.N * w.K * 4;
+      flops += 2.0 * w.M * w.K * w.N;
+      left->push_back(ReduceJob{w.ws, w.g_w, S, w.N * w.K, w.K, w.K, 1, w.K});
+      if (a.n == kWgTrJobs) launch();
+    }
+    launch();
+  }
 }
 
 }  // namespace ftp

@@ -7,6 +7,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <vector>
+
 namespace ftp {
 
 // Optional per-launch timing (diagnostics for benchmarks): when tracing is on, a
@@ -140,6 +142,9 @@ void conv_direct_wgrad(int dt, hipStream_t st, const void* dz, HView in, const C
 // g[(j % C) * stride_c + (j / C) * stride_q] += sum_p ws[p * QC + j]; columns j % C >= valid_c skipped (-1: none)
 void reduce_partials(hipStream_t st, const float* ws, int P, size_t QC, int C, size_t stride_q, size_t stride_c,
                      float* g, int valid_c = -1);
+// the same for several tensors in one launch (P >= 1 each)
+struct ReduceJob { const float* ws; float* g; int P, QC, C, stride_q, stride_c, valid_c; };
+void reduce_group(hipStream_t st, const ReduceJob* jobs, int n);
 
 // ---- 1 x kw convolutions, stride 1, same length, at most 64 channels (conv1d_ok): implicit GEMMs, no scratch but ws ----
 int conv1d_ok(const ConvGeom& g);
@@ -147,7 +152,8 @@ void conv1d_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom&
 // sums != nullptr (prev is a view): also the partial sums bn_bwd_reduce would compute for the BatchNorm + activation `prev`
 void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out);
 size_t conv1d_wgrad_ws(const ConvGeom& g);
-void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w);
+// partial sums, if any, are left in ws and appended to `left`
+void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left);
 // few rows (conv1d_bwd_small_ok): weight and data gradient in one launch
 int conv1d_bwd_small_ok(const ConvGeom& g);
 void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn);
@@ -177,6 +183,10 @@ void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, con
 int dw_dgrad_sums_ok(int dt, const ConvGeom& g);
 void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev = HView{},
               float* sums = nullptr, int* P_out = nullptr);
+// Weight gradients of several depthwise layers together: the kernels leave partial sums in each job's ws (dw_wgrad_ws
+// floats of its own) and append what is left to sum
+struct DwWgradJob { const void* dz; HView in; ConvGeom g; float* ws; float* g_w; };
+void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::vector<ReduceJob>* left);
 size_t dw_wgrad_ws(const ConvGeom& g);
 void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w);
 
@@ -194,15 +204,23 @@ size_t pw_wgrad_ws(size_t M, int K, int N);
 void pw_wgrad(int dt, hipStream_t st, const void* dz, HView a, size_t M, int K, int N, float* ws,
               float* g_w, int K_out = -1);
 
+// Weight gradients of several pointwise layers together (K and N multiples of 8); short ones are added to g_w at once, the
+// others leave partial sums in their ws (pw_wgrad_group_ws floats of its own) and append what is left to sum
+struct PwWgradJob { const void* dz; HView a; size_t M; int K, N; float* ws; float* g_w; };
+// share: how many layers such a group holds when it is complete (the same number in both calls)
+size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, int share);
+void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int share, std::vector<ReduceJob>* left);
+
 // Narrow-to-wide pointwise layer (K inputs, N >= 2K outputs, bfloat16, input stored activated), whole backward behind
 // the BatchNorm reductions in one pass: dz = k1*dA*act'(out) + k2*z + k3 formed per row tile on chip,
 // dIn = dz * W (+ res), g_w += dz^T * A.  coef: [3][N] from bn_bwd_finalize.  ws: pw_bwd_fused_ws(M, K, N) floats.
 // The kernel's partial weight gradients are summed on st_sum; if that is not st, ev_sum orders the sum behind the kernel.
+// left != nullptr: they are not summed here, the sum is appended there.
 int pw_bwd_fused_ok(int dt, size_t M, int K, int N, HView a);
 size_t pw_bwd_fused_ws(size_t M, int K, int N);
 void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, const void* w, const void* a_in,
                   const void* res, size_t M, int K, int N, float* ws, float* g_w, void* dIn, hipStream_t st_sum,
-                  hipEvent_t ev_sum);
+                  hipEvent_t ev_sum, std::vector<ReduceJob>* left = nullptr);
 
 
 // bfloat16 pointwise layers with a long reduction (>= 192) and 2 K - 64 K rows: forward (A' * W^T, BatchNorm partial sums
@@ -214,8 +232,9 @@ void pw_dgrad_deep(hipStream_t st, const void* dz, const void* w, const void* re
 // the weight gradient for bfloat16 layers with more than 2048 rows: operands staged untransposed, transposed on the
 // way out of LDS (pw_wgrad dispatches to it; ws: pw_wgrad_tr_ws floats)
 int pw_wgrad_tr_ok(int dt, size_t M, int K, int N);
-size_t pw_wgrad_tr_ws(size_t M, int K, int N);
+size_t pw_wgrad_tr_ws(size_t M, int K, int N, int share = 1);
 void pw_wgrad_tr(hipStream_t st, const void* dz, HView a, size_t M, int K, int N, float* ws, float* g_w, int K_out);
+void pw_wgrad_tr_group(hipStream_t st, const PwWgradJob* jobs, int n, int share, std::vector<ReduceJob>* left);   // skips what is not pw_wgrad_tr_ok
 
 // wgrad (g_w +=) then dgrad (dA =) of one layer on one stream; one launch for short problems
 void pw_bwd(int dt, hipStream_t st, const void* dz, const void* w, const void* res, HView a, size_t M, int K, int N,

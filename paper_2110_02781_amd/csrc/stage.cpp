@@ -208,6 +208,8 @@ struct UnitPlan {
   size_t bn_off;                   // channel offset in the running-stat arrays
   std::vector<size_t> z_off;       // per sub: byte offset of z in the slot stash
   std::vector<size_t> st_off;      // per sub: float offset of mean|invstd|scale|shift in the slot stats
+  std::vector<size_t> dz_off;      // per sub: byte offset of its dz in the stage's dz store (stages that defer weight gradients)
+  std::vector<size_t> part_off;    // per sub: float offset of its partial weight gradients (likewise)
   size_t out_off;                  // byte offset of the materialised unit output (if any)
   bool out_virtual;                // CONV unit whose output stays a view
   size_t in_mat_off;               // residual block fed by a view: materialised copy of its input
@@ -249,7 +251,7 @@ struct ftp_stage {
   void* w_lp = nullptr;
   size_t stash_bytes = 0, stats_floats = 0, xin_bytes = 0, max_act_bytes = 0;
   std::vector<Slot> slots;
-  char *gbuf[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // boundary A/B, dz (even), dA, dz (odd)
+  char *gbuf[5] = {nullptr, nullptr, nullptr, nullptr, nullptr};   // boundary A/B, dz (even), dA, dz (odd); no dz ones in a stage that defers
   // Weight gradients depend on nothing downstream, so in backward they run on a second stream next to the
   // data-gradient chain: fork after dz is formed, join before that dz buffer is overwritten / at the end.
   hipStream_t side = nullptr;
@@ -270,6 +272,16 @@ struct ftp_stage {
   bool bjoin_pending[2] = {false, false};
   int bset = 0;
   bool bset_open = false;      // a layer of the current unit has written into the set
+  // A stage too small to run weight gradients on a second stream (a chain of short launches) notes them instead: every
+  // layer's dz and partial sums have a place of their own, and the weight gradients of all layers run together at the end
+  // of the backward call, a few launches for all of them.
+  bool defers = false;
+  char* dz_store = nullptr;
+  float* parts = nullptr;
+  int n_tr = 0;                // layers that share the launch of the transposing weight gradient (pw_wgrad_group's share)
+  std::vector<PwWgradJob> q_pw;
+  std::vector<DwWgradJob> q_dw;
+  std::vector<ReduceJob> q_red;
   unsigned n_sub_bwd = 0;
   float *bn_part = nullptr, *coef = nullptr, *ws = nullptr, *row_loss = nullptr;
   // A second partial-sum workspace for the weight gradient of the stage's very first layer when the stage forks
@@ -326,6 +338,7 @@ static void stage_free(ftp_stage* s) {
   }
   for (int i = 0; i < 6; ++i) dfree(s->dzring[i]);
   dfree(s->bn_part); dfree(s->coef); dfree(s->ws); dfree(s->ws_tail); dfree(s->ws_fused); dfree(s->row_loss); dfree(s->im2col);
+  dfree(s->dz_store); dfree(s->parts);
   if (s->timer) {
     if (s->timer->created)
       for (auto& q : s->timer->ev)
@@ -363,13 +376,18 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   s->es = m->dtype == FTP_F32 ? 4 : 2;
   if (hipGetDevice(&s->device) != hipSuccess) { ftp_set_error("stage_create: no HIP device"); delete s; return FTP_ERR_HIP; }
 
-  size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024;
+  size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, dz_bytes = 0, part_floats = 0, n_subs = 0;
   int max_c = 8;
   auto act_bytes = [&](int H, int W, int C) { return align_up((size_t)batch * H * W * C * s->es, 256); };
   const UnitInfo& first = m->units[a];
   s->xin_bytes = act_bytes(first.inH, first.inW, first.inC);
   stash += s->xin_bytes;
   max_act = s->xin_bytes;
+  for (int i = a; i < b; ++i)
+    for (const Sub& sb : m->units[i].subs) {
+      const size_t M = (size_t)batch * sb.g.Hout * sb.g.Wout;
+      if (sb.type == SUB_PW && pw_wgrad_tr_ok(m->dtype, M, sb.g.Cin, sb.g.Cout) && pw_bwd_fused_ws(M, sb.g.Cin, sb.g.Cout) == 0) ++s->n_tr;
+    }
   for (int i = a; i < b; ++i) {
     const UnitInfo& u = m->units[i];
     UnitPlan p;
@@ -390,6 +408,13 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       size_t need = c1 ? conv1d_wgrad_ws(g) : patches ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_wgrad_ws(g) : pw_wgrad_ws(M, g.Cin, g.Cout);
       if (need > ws_floats) ws_floats = need;
       if (i == a && &sb == &u.subs[0]) s->ws_tail_floats = need;
+      size_t part = need;
+      if (sb.type == SUB_PW) {
+        part = pw_wgrad_group_ws(m->dtype, M, g.Cin, g.Cout, s->n_tr);
+        if (m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > part) part = pw_bwd_fused_ws(M, g.Cin, g.Cout);
+      }
+      p.dz_off.push_back(dz_bytes); dz_bytes += zb;
+      p.part_off.push_back(part_floats); part_floats += patches ? 0 : align_up(part, 64);
       if (sb.type == SUB_PW && m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > s->ws_fused_floats)
         s->ws_fused_floats = pw_bwd_fused_ws(M, g.Cin, g.Cout);
       if (patches) ++s->n_direct;
@@ -401,6 +426,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
         if (conv_direct_dgrad_gemm_w_elems(g) > ws_floats) ws_floats = conv_direct_dgrad_gemm_w_elems(g);
       }
     }
+    n_subs += u.subs.size();
     p.out_virtual = (u.d.kind == FTP_UNIT_CONV);
     p.out_off = 0;
     if (!p.out_virtual && u.d.kind != FTP_UNIT_LOSS) {
@@ -418,8 +444,13 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     if (u.d.kind == FTP_UNIT_LOSS) { s->has_loss = true; s->classes = u.inC; }
     s->plan.push_back(p);
   }
+  // Two ways to keep weight gradients off the data-gradient chain: a second stream (forks and joins are event calls per layer:
+  // pays only when the kernels are long; a 32x32-input stage, largest activation 12 MB, was 10 % faster on one stream, a
+  // 224x224 one 15 % slower), or all of them at the end of the call (a dz buffer per layer, full launches only if the layers are many and small)
+  s->defers = max_act < ((size_t)32 << 20);
   s->stash_bytes = stash; s->stats_floats = stats; s->max_act_bytes = max_act; s->ws_floats = ws_floats; s->max_c = max_c;
 
+  s->q_pw.reserve(n_subs); s->q_dw.reserve(n_subs); s->q_red.reserve(n_subs);      // a layer leaves at most one of each
   int rc = FTP_OK;
   size_t np = s->n_param ? s->n_param : 8;
   size_t nb = s->n_bn ? s->n_bn : 8;
@@ -439,7 +470,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     if (s->has_loss && (rc = dev_alloc(&sl.dlogits, (size_t)batch * s->classes * s->es))) { stage_free(s); return rc; }
   }
   for (int i = 0; i < 5; ++i)
-    if ((rc = dev_alloc(&s->gbuf[i], max_act))) { stage_free(s); return rc; }
+    if (!(s->defers && (i == 2 || i == 4)) && (rc = dev_alloc(&s->gbuf[i], max_act))) { stage_free(s); return rc; }
   {
     hipError_t e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking);     // default priority
     for (int i = 0; i < 3 && e == hipSuccess; ++i) {
@@ -452,7 +483,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     }
     if (e != hipSuccess) { ftp_set_error("stage_create: stream/event creation failed: %s", hipGetErrorString(e)); stage_free(s); return FTP_ERR_HIP; }
   }
-  if (s->max_act_bytes >= ((size_t)32 << 20)) {        // a stage that forks (stage_forks)
+  if (!s->defers) {
     s->dzring_bytes = max_act < ((size_t)64 << 20) ? max_act : ((size_t)64 << 20);
     for (int i = 0; i < 6; ++i)
       if ((rc = dev_alloc(&s->dzring[i], s->dzring_bytes))) { stage_free(s); return rc; }
@@ -460,8 +491,9 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   if ((rc = dev_alloc(&s->bn_part, (size_t)kBnPartials * 2 * max_c * 4)) || (rc = dev_alloc(&s->coef, (size_t)3 * max_c * 4)) ||
       (rc = dev_alloc(&s->ws, ws_floats * 4)) || (rc = dev_alloc(&s->row_loss, (size_t)batch * 4))) { stage_free(s); return rc; }
   if (s->im2col_elems && (rc = dev_alloc(&s->im2col, s->im2col_elems * s->es))) { stage_free(s); return rc; }
-  if (s->ws_fused_floats && (rc = dev_alloc(&s->ws_fused, s->ws_fused_floats * 4))) { stage_free(s); return rc; }
-  if (s->max_act_bytes >= ((size_t)32 << 20) && s->ws_tail_floats && s->n_direct <= 1 &&
+  if (s->defers && ((rc = dev_alloc(&s->dz_store, dz_bytes)) || (rc = dev_alloc(&s->parts, part_floats * 4)))) { stage_free(s); return rc; }
+  if (!s->defers && s->ws_fused_floats && (rc = dev_alloc(&s->ws_fused, s->ws_fused_floats * 4))) { stage_free(s); return rc; }
+  if (!s->defers && s->ws_tail_floats && s->n_direct <= 1 &&
       (rc = dev_alloc(&s->ws_tail, s->ws_tail_floats * 4))) { stage_free(s); return rc; }
 
   // initial state: zero weights / momentum / gradients, running mean 0, running variance 1
@@ -877,7 +909,7 @@ extern "C" int ftp_stage_aggregate_weights(ftp_stage* s, const int* slots, int n
 enum { BWD_FULL = 0, BWD_FROM_DZ = 1 };
 // stage_forks: the stage is large enough to run weight gradients on its second stream (decides which kernels a
 // layer uses); stage_overlaps: it does so now (not while per-unit profiling needs everything on one stream)
-static bool stage_forks(const ftp_stage* s) { return s->max_act_bytes >= ((size_t)32 << 20); }
+static bool stage_forks(const ftp_stage* s) { return !s->defers; }
 static bool stage_overlaps(const ftp_stage* s) { return s->prof == nullptr && stage_forks(s); }
 
 static int join_side(ftp_stage* s, hipStream_t st);
@@ -902,8 +934,8 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
                        M * (size_t)C * s->es <= s->dzring_bytes;
   // An expand layer in bfloat16: behind the BatchNorm reductions the rest of its backward (dz, data gradient,
   // weight gradient) is one pass on this stream; dz never reaches memory.
-  if (mode == BWD_FULL && sb.type == SUB_PW && dIn && s->ws_fused && !bn_bwd_small_ok(M, C) &&
-      pw_bwd_fused_ok(s->dt, M, g.Cin, g.Cout, in) && pw_bwd_fused_ws(M, g.Cin, g.Cout) <= s->ws_fused_floats) {
+  if (mode == BWD_FULL && sb.type == SUB_PW && dIn && !bn_bwd_small_ok(M, C) && pw_bwd_fused_ok(s->dt, M, g.Cin, g.Cout, in) &&
+      (s->defers || (s->ws_fused && pw_bwd_fused_ws(M, g.Cin, g.Cout) <= s->ws_fused_floats))) {
     int P = 0;
     if (s->bwd_sums_of == dA) P = s->bwd_sums_P;
     else bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, s->bn_part, &P);
@@ -917,16 +949,20 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       HIP_TRY(hipStreamWaitEvent(st, s->ev_join[2], 0));
       s->join_pending[2] = false;
     }
-    pw_bwd_fused(st, dA, out, s->coef, conv_w(s, W, p.p_off + sb.w_off), in.z, res, M, g.Cin, g.Cout, s->ws_fused,
-                 s->grads + p.p_off + sb.w_off, dIn, aside ? s->side : st, aside ? s->ev_fork[2] : nullptr);
+    pw_bwd_fused(st, dA, out, s->coef, conv_w(s, W, p.p_off + sb.w_off), in.z, res, M, g.Cin, g.Cout,
+                 s->defers ? s->parts + p.part_off[k] : s->ws_fused, s->grads + p.p_off + sb.w_off, dIn, aside ? s->side : st,
+                 aside ? s->ev_fork[2] : nullptr, s->defers ? &s->q_red : nullptr);
     if (aside) {
       HIP_TRY(hipEventRecord(s->ev_join[2], s->side));
       s->join_pending[2] = true;
     }
     return FTP_OK;
   }
+  // noted for the end of the backward call: dz stays where it is written until then
+  const bool noted = s->defers && (sb.type != SUB_DIRECT || conv1d_ok(g));
   if (mode != BWD_FROM_DZ) {
     if (batched) dz = s->dzring[s->bset * 3 + (int)k];
+    else if (s->defers) dz = s->dz_store + p.dz_off[k];
     else {
       b = (int)(s->n_sub_bwd++ & 1u);
       dz = s->gbuf[b ? 4 : 2];
@@ -975,6 +1011,12 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       dw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn);
     }
   };
+  auto run_conv1d_dgrad = [&]() {
+    // behind another convolution of the stage: this is the dA of that one's BatchNorm + activation
+    const bool sums = in.scale != nullptr && !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cin);
+    conv1d_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, sums ? s->bn_part : nullptr, &s->bwd_sums_P);
+    if (sums) s->bwd_sums_of = dIn;
+  };
   if (dgrad_first) run_dw_dgrad();
   if (batched && mode == BWD_FULL) {
     // noted for the unit's fork; the data gradient goes on as it would behind a forked weight gradient
@@ -982,6 +1024,24 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     s->pend[s->n_pend++] = ftp_stage::PendingWgrad{sb.type, dz, in, g, M, s->grads + p.p_off + sb.w_off};
     if (sb.type == SUB_PW) pw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), res, M, g.Cin, g.Cout, dIn);
     else if (!dgrad_first) run_dw_dgrad();
+    return FTP_OK;
+  }
+  if (noted) {
+    float* gw = s->grads + p.p_off + sb.w_off;
+    float* part = s->parts + p.part_off[k];
+    const void* w = conv_w(s, W, p.p_off + sb.w_off);
+    if (sb.type == SUB_PW) {
+      s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
+      if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);
+    } else if (sb.type == SUB_DW) {
+      s->q_dw.push_back(DwWgradJob{dz, in, g, part, gw});
+      if (dIn) run_dw_dgrad();
+    } else if (dIn && conv1d_bwd_small_ok(g)) {
+      conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn);
+    } else {
+      conv1d_wgrad(s->dt, st, dz, in, g, part, gw, &s->q_red);
+      if (dIn) run_conv1d_dgrad();
+    }
     return FTP_OK;
   }
   // the first layer of the stage, last in this pass and without a data gradient: its weight gradient is all that is
@@ -1004,7 +1064,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   }
   if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
     if (!overlap && dIn && conv1d_bwd_small_ok(g)) { conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn); return FTP_OK; }
-    conv1d_wgrad(s->dt, ws, dz, in, g, wsp, gw);
+    conv1d_wgrad(s->dt, ws, dz, in, g, wsp, gw, &s->q_red);
+    reduce_group(ws, s->q_red.data(), (int)s->q_red.size());
+    s->q_red.clear();
   }
   else if (sb.type == SUB_DIRECT) {
     conv_direct_wgrad(s->dt, ws, dz, in, g, s->im2col, wsp, gw, s->im2col_of == out.z);
@@ -1017,12 +1079,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     s->join_pending[b] = true;
   }
   if (dIn) {
-    if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
-      // behind another convolution of the stage: this is the dA of that one's BatchNorm + activation
-      const bool sums = in.scale != nullptr && !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cin);
-      conv1d_dgrad(s->dt, st, dz, w, g, dIn, in, sums ? s->bn_part : nullptr, &s->bwd_sums_P);
-      if (sums) s->bwd_sums_of = dIn;
-    }
+    if (sb.type == SUB_DIRECT && conv1d_ok(g)) run_conv1d_dgrad();
     else if (sb.type == SUB_DIRECT) {
       // the scratch buffers are shared with the weight gradients: fine on one stream, but a stage that runs them on
       // the side stream keeps the direct kernel
@@ -1036,6 +1093,14 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     else if (!dgrad_first) run_dw_dgrad();
   }
   return FTP_OK;
+}
+
+// every weight gradient noted so far, and the sums of what the kernels left
+static void run_noted(ftp_stage* s, hipStream_t st) {
+  pw_wgrad_group(s->dt, st, s->q_pw.data(), (int)s->q_pw.size(), s->n_tr, &s->q_red);
+  dw_wgrad_group(s->dt, st, s->q_dw.data(), (int)s->q_dw.size(), &s->q_red);
+  reduce_group(st, s->q_red.data(), (int)s->q_red.size());
+  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
 }
 
 // the weight gradients a unit has noted: one fork behind everything the unit has enqueued, all of them on the side
@@ -1098,6 +1163,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
     if (rc) return rc;
     s->stash_owner = slot;
   }
+  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
   const void* d = dy_dev ? dy_dev : sl.dlogits;     // gradient of the current unit's output (read only)
   int flip = 0;
@@ -1138,12 +1204,12 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
         if ((rc = sub_backward(s, sl, p, ns - 1, d, v.sub_out[i][ns - 2], v.sub_out[i][ns - 1], tmp, nullptr, W, st, BWD_FULL, uf))) return rc;
         ConvGeom gd = ns == 3 ? u.subs[1].g : ConvGeom{};
         gd.N = s->batch;
-        if (ns == 3 && !stage_forks(s) && dw_bwd_small_ok(gd)) {
+        if (ns == 3 && s->defers && dw_bwd_small_ok(gd)) {
           // short tensors: depthwise dgrad + wgrad and the expand layer's BatchNorm backward in one launch
           const Sub& s0 = u.subs[0];
           const Sub& s1 = u.subs[1];
           // the depthwise layer's own BatchNorm backward happens inside too: its dz never reaches memory
-          void* dz1 = s->gbuf[(s->n_sub_bwd++ & 1u) ? 4 : 2];
+          void* dz1 = s->dz_store + p.dz_off[0];
           float* st0 = sl.stats + p.st_off[0];
           float* st1 = sl.stats + p.st_off[1];
           BnBwdIn bo{tmp, v.sub_out[i][1], W.w32 + p.p_off + s1.gamma_off, st1, st1 + s1.g.Cout,
@@ -1169,9 +1235,13 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
       default:
         break;
     }
-    if (s->prof) HIP_TRY(hipEventRecord(s->prof->b1[i], st));
+    if (s->prof) {                                    // a unit's time includes its weight gradients
+      run_noted(s, st);
+      HIP_TRY(hipEventRecord(s->prof->b1[i], st));
+    }
     if (produced && next) { d = next; if (i > 0) flip ^= 1; }
   }
+  run_noted(s, st);
   if ((rc = join_side(s, st))) return rc;
   if (s->timer && sl.timer_idx >= 0) {
     HIP_TRY(hipEventRecord(s->timer->ev[sl.timer_idx][3], st));
