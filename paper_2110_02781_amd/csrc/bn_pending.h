@@ -30,12 +30,20 @@ __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, in
     pre[lane][v] = t;
   }
   __syncthreads();
+  // the first wavefront: eight lanes a value with four sums each, then across lanes (the same tree for every call)
+  double s0 = 0.0, s1 = 0.0;
+  if (tid < 64) {
+    const double* f = &pre[0][0] + tid;
+    double t = (f[0] + f[64]) + (f[128] + f[192]);
+#pragma unroll
+    for (int o = 8; o < 64; o <<= 1) t += __shfl_xor(t, o, 64);
+    s0 = t;
+    s1 = __shfl_xor(t, 4, 64);                       // lanes 0..3 hold the sums, 4..7 the second sums
+  }
   // first use of the four values requested at the top: their conversions must not move up to the loads
   asm volatile("" : "+v"(p_g), "+v"(p_b), "+v"(p_rm), "+v"(p_rv));
   if (tid < 4) {
     const int c = c0 + tid;
-    double s0 = 0.0, s1 = 0.0;
-    for (int l = 0; l < 32; ++l) { s0 += pre[l][tid]; s1 += pre[l][4 + tid]; }
     const double Md = (double)pend.M, mu = s0 / Md;
     double var = s1 / Md - mu * mu;
     if (var < 0.0) var = 0.0;

@@ -707,7 +707,9 @@ void dw_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, 
 // For tensors of a few hundred KB the separate kernels are all launch latency.  Here a block owns 4 channels
 // over every pixel: the tensor that is gathered from (input in forward, dz in backward) is staged once in LDS
 // as one float4 per pixel (the view applied once per element), so the nine taps are LDS reads and the
-// per-channel sums never leave the block.
+// per-channel sums never leave the block.  A pixel's row and column come from two 32-bit multiplications and a tap outside the
+// image reads a zero slot, so the nine reads go out together: with 64-bit divisions and a branch per tap the backward of
+// 1859 pixels x 384 channels took 19.5 us instead of 16.5 (bfloat16), the forward 10 instead of 8.1.
 __device__ __forceinline__ float4 view4(float4 v, const float* sc, const float* sh, float lo, float hi) {
   return make_float4(clamp_act(fmaf(v.x, sc[0], sh[0]), lo, hi), clamp_act(fmaf(v.y, sc[1], sh[1]), lo, hi),
                      clamp_act(fmaf(v.z, sc[2], sh[2]), lo, hi), clamp_act(fmaf(v.w, sc[3], sh[3]), lo, hi));
@@ -731,13 +733,13 @@ __device__ __forceinline__ float4 raw4_unpack(const Raw4<bf16_t>& r) {
 // Depthwise convolution + BatchNorm statistics + their finalisation (and, when the producer left them pending,
 // the finalisation of the input's BatchNorm too).
 template <typename T>
-__global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pend, const T* __restrict__ w, ConvGeom g, size_t M,
-                                                          size_t Min, const float* __restrict__ gamma, const float* __restrict__ beta,
+__global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pend, const T* __restrict__ w, ConvGeom g, FastDiv dW,
+                                                          FastDiv dH, int M, int Min, const float* __restrict__ gamma, const float* __restrict__ beta,
                                                           float* mean, float* invstd, float* scale, float* shift,
                                                           float* run_mean, float* run_var, float eps, float momentum,
                                                           T* __restrict__ z) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  float4* tile = reinterpret_cast<float4*>(smem_raw);           // [Min]
+  float4* tile = reinterpret_cast<float4*>(smem_raw);           // [Min + 1], the last one zero
   __shared__ float wl[9][4];
   __shared__ float red[16][8];
   __shared__ double pre[32][8];
@@ -751,8 +753,8 @@ __global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pen
   Raw4<T> rv[3];
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const size_t m = (size_t)tid + (size_t)q * nt;
-    raw4_load(rv[q], src + (m < Min ? m : 0) * C + c0);
+    const int m = tid + q * nt;
+    raw4_load(rv[q], src + (size_t)(m < Min ? m : 0) * C + c0);
   }
   float bn_g = 0.f, bn_b = 0.f, bn_rm = 0.f, bn_rv = 0.f;
   if (tid < 4) { bn_g = gamma[c0 + tid]; bn_b = beta[c0 + tid]; bn_rm = run_mean[c0 + tid]; bn_rv = run_var[c0 + tid]; }
@@ -769,32 +771,36 @@ __global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pen
   const float lo = view ? act_lo(in.act) : -INFINITY, hi = view ? act_hi(in.act) : INFINITY;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
-    const size_t m = (size_t)tid + (size_t)q * nt;
+    const int m = tid + q * nt;
     if (m >= Min) break;
     float4 v = raw4_unpack(rv[q]);
     if (view) v = round4<T>(view4(v, sc, sh, lo, hi));
     tile[m] = v;
   }
+  if (tid == 0) tile[Min] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
   float4 wr[9];
 #pragma unroll
   for (int t = 0; t < 9; ++t) wr[t] = make_float4(wl[t][0], wl[t][1], wl[t][2], wl[t][3]);
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (size_t m = tid; m < M; m += nt) {
-    const int wo = (int)(m % g.Wout), ho = (int)((m / g.Wout) % g.Hout), n = (int)(m / ((size_t)g.Wout * g.Hout));
-    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int m = tid; m < M; m += nt) {
+    const int r = (int)dW.div(m), wo = m - r * g.Wout, n = (int)dH.div(r), ho = r - n * g.Hout;
+    // the nine values first, from the zero slot where a tap leaves the image: no branches between the reads
+    float4 t[9];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
       const int h = ho * s - 1 + i;
-      if (h < 0 || h >= g.Hin) continue;
+      const int row = (unsigned)h < (unsigned)g.Hin ? (n * g.Hin + h) * g.Win : -1;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
         const int ww = wo * s - 1 + j;
-        if (ww < 0 || ww >= g.Win) continue;
-        o = fma4(tile[((size_t)n * g.Hin + h) * g.Win + ww], wr[i * 3 + j], o);
+        t[i * 3 + j] = tile[row >= 0 && (unsigned)ww < (unsigned)g.Win ? row + ww : Min];
       }
     }
-    store4(z + m * C + c0, o);
+    float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) o = fma4(t[k], wr[k], o);
+    store4(z + (size_t)m * C + c0, o);
     const float4 sv = round4<T>(o);               // statistics of the values as stored
     acc[0] += sv.x; acc[1] += sv.y; acc[2] += sv.z; acc[3] += sv.w;
     acc[4] = fmaf(sv.x, sv.x, acc[4]); acc[5] = fmaf(sv.y, sv.y, acc[5]);
@@ -841,7 +847,8 @@ void dw_fwd_bn_small(int dt, hipStream_t st, HView in, const BnPending& pend, co
   View v{in.z, in.scale, in.shift, in.act};
   KScope ks(st, "dw_fwd_bn_small", ((double)Min * g.Cout + (double)M * g.Cout) * es, 21.0 * M * g.Cout, (long)M, g.Cout, g.stride);
   const int nt = Min > 512 ? 1024 : (Min > 256 ? 512 : 256);
-  FTP_DISPATCH(dt, hipLaunchKernelGGL(dw_fwd_bn_small_k<T>, dim3(g.Cout / 4), dim3(nt), Min * 16, st, v, pend, (const T*)w, g, M, Min,
+  FTP_DISPATCH(dt, hipLaunchKernelGGL(dw_fwd_bn_small_k<T>, dim3(g.Cout / 4), dim3(nt), (Min + 1) * 16, st, v, pend, (const T*)w, g,
+                                      FastDiv::of(g.Wout), FastDiv::of(g.Hout), (int)M, (int)Min,
                                       gamma, beta, mean, invstd, scale, shift, run_mean, run_var, eps, momentum, (T*)z));
 }
 
@@ -854,11 +861,11 @@ void dw_fwd_bn_small(int dt, hipStream_t st, HView in, const BnPending& pend, co
 // BatchNorm backward.
 template <typename T, int RPT>
 __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, BnBwdIn bo, const T* __restrict__ w, View in,
-                                                      ConvGeom g, size_t M, size_t Mout, const float* __restrict__ gamma,
+                                                      ConvGeom g, FastDiv dW, FastDiv dH, int M, int Mout, const float* __restrict__ gamma,
                                                       const float* __restrict__ mean, const float* __restrict__ invstd, float* g_w,
                                                       float* g_gamma, float* g_beta, T* __restrict__ dz_prev) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  float4* tile = reinterpret_cast<float4*>(smem_raw);           // dz, [Mout]
+  float4* tile = reinterpret_cast<float4*>(smem_raw);           // dz, [Mout + 1], the last one zero
   __shared__ float wl[9][4];
   __shared__ float red[8][44];    // [wave][value]
   __builtin_amdgcn_s_setprio(3);             // data-gradient chain: ahead of the weight-gradient stream's waves
@@ -872,8 +879,8 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
   float4 zv[RPT];
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
-    const size_t m = tid + (size_t)q * nt;
-    zv[q] = load4(zin + (m < M ? m : 0) * C + c0);
+    const int m = tid + q * nt;
+    zv[q] = load4(zin + (size_t)(m < M ? m : 0) * C + c0);
   }
   float gw_old = 0.f, f_mu = 0.f, f_is = 0.f, f_g = 0.f, f_gg = 0.f, f_gb = 0.f;
   float f2_mu = 0.f, f2_is = 0.f, f2_g = 0.f, f2_gg = 0.f, f2_gb = 0.f;
@@ -907,13 +914,14 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
     float4 d2r[RPT];
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
-      const size_t m = tid + (size_t)q * nt, mc = m < Mout ? m : 0;
+      const int m = tid + q * nt;
+      const size_t mc = m < Mout ? m : 0;
       d2r[q] = load4(dA2 + mc * C + c0);
       z2v[q] = load4(z2 + mc * C + c0);
     }
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
-      const size_t m = tid + (size_t)q * nt;
+      const int m = tid + q * nt;
       dy2[q] = make_float4(0.f, 0.f, 0.f, 0.f);
       if (m >= Mout) { z2v[q] = dy2[q]; continue; }
       const float4 d = d2r[q];
@@ -954,12 +962,13 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
     const float4 k3 = make_float4(coef2[2][0], coef2[2][1], coef2[2][2], coef2[2][3]);
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
-      const size_t m = tid + (size_t)q * nt;
+      const int m = tid + q * nt;
       if (m < Mout) tile[m] = round4<T>(fma4(k1, dy2[q], fma4(k2, z2v[q], k3)));   // as a stored dz would read back
     }
   } else {
-    for (size_t m = tid; m < Mout; m += nt) tile[m] = load4(dz + m * C + c0);
+    for (int m = tid; m < Mout; m += nt) tile[m] = load4(dz + (size_t)m * C + c0);
   }
+  if (tid == 0) tile[Mout] = make_float4(0.f, 0.f, 0.f, 0.f);
   __syncthreads();
   float4 wr[9], accw[9], dy[RPT];
 #pragma unroll
@@ -970,31 +979,30 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
   float bsum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
-    const size_t m = tid + (size_t)q * nt;
+    const int m = tid + q * nt;
     dy[q] = make_float4(0.f, 0.f, 0.f, 0.f);
     if (m >= M) { zv[q] = dy[q]; continue; }
-    const int ww = (int)(m % g.Win), h = (int)((m / g.Win) % g.Hin), n = (int)(m / ((size_t)g.Win * g.Hin));
+    const int r = (int)dW.div(m), ww = m - r * g.Win, n = (int)dH.div(r), h = r - n * g.Hin;
     const float4 y = make_float4(fmaf(zv[q].x, sc[0], sh[0]), fmaf(zv[q].y, sc[1], sh[1]), fmaf(zv[q].z, sc[2], sh[2]),
                                  fmaf(zv[q].w, sc[3], sh[3]));
     const float4 a = round4<T>(make_float4(clamp_act(y.x, lo, hi), clamp_act(y.y, lo, hi), clamp_act(y.z, lo, hi),
                                            clamp_act(y.w, lo, hi)));
-    float4 dA = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 dA = make_float4(0.f, 0.f, 0.f, 0.f), t[9];
+    // the nine values first, from the zero slot where no output pixel lies: no branches between the reads
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      const int hn = h + 1 - i;
-      if (hn < 0 || (s == 2 && (hn & 1))) continue;
-      const int ho = s == 2 ? hn >> 1 : hn;
-      if (ho >= g.Hout) continue;
+      const int hn = h + 1 - i, ho = s == 2 ? hn >> 1 : hn;
+      const int row = (unsigned)ho < (unsigned)g.Hout && !(s == 2 && (hn & 1)) ? (n * g.Hout + ho) * g.Wout : -1;
 #pragma unroll
       for (int j = 0; j < 3; ++j) {
-        const int wn = ww + 1 - j;
-        if (wn < 0 || (s == 2 && (wn & 1))) continue;
-        const int wo = s == 2 ? wn >> 1 : wn;
-        if (wo >= g.Wout) continue;
-        const float4 d = tile[((size_t)n * g.Hout + ho) * g.Wout + wo];
-        dA = fma4(d, wr[i * 3 + j], dA);
-        accw[i * 3 + j] = fma4(d, a, accw[i * 3 + j]);
+        const int wn = ww + 1 - j, wo = s == 2 ? wn >> 1 : wn;
+        t[i * 3 + j] = tile[row >= 0 && (unsigned)wo < (unsigned)g.Wout && !(s == 2 && (wn & 1)) ? row + wo : Mout];
       }
+    }
+#pragma unroll
+    for (int k = 0; k < 9; ++k) {
+      dA = fma4(t[k], wr[k], dA);
+      accw[k] = fma4(t[k], a, accw[k]);
     }
     dA = round4<T>(dA);                    // the data gradient as the separate kernels would store it
     float4 v;
@@ -1043,9 +1051,9 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
   const float4 k3 = make_float4(coef[2][0], coef[2][1], coef[2][2], coef[2][3]);
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
-    const size_t m = tid + (size_t)q * nt;
+    const int m = tid + q * nt;
     if (m >= M) continue;
-    store4(dz_prev + m * C + c0, fma4(k1, dy[q], fma4(k2, zv[q], k3)));
+    store4(dz_prev + (size_t)m * C + c0, fma4(k1, dy[q], fma4(k2, zv[q], k3)));
   }
 }
 
@@ -1061,15 +1069,16 @@ void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, con
   View v{in.z, in.scale, in.shift, in.act};
   KScope ks(st, "dw_bwd_small", ((double)M * g.Cout * 2 + (double)Mout * g.Cout) * es, 42.0 * M * g.Cout, (long)M, g.Cout, g.stride);
   const dim3 grid(g.Cout / 4);
-  const size_t lds = Mout * 16;
+  const size_t lds = (Mout + 1) * 16;
+  const FastDiv dW = FastDiv::of(g.Win), dH = FastDiv::of(g.Hin);
   if (M > 1024) {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 4>), grid, dim3(512), lds, st, (const T*)dz, bo, (const T*)w, v, g, M, Mout,
+    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 4>), grid, dim3(512), lds, st, (const T*)dz, bo, (const T*)w, v, g, dW, dH, (int)M, (int)Mout,
                                         gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
   } else if (M > 256) {
     FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 2>), grid, dim3(M > 512 ? 512 : 256), lds, st, (const T*)dz, bo, (const T*)w,
-                                        v, g, M, Mout, gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
+                                        v, g, dW, dH, (int)M, (int)Mout, gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
   } else {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 1>), grid, dim3(256), lds, st, (const T*)dz, bo, (const T*)w, v, g, M, Mout,
+    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 1>), grid, dim3(256), lds, st, (const T*)dz, bo, (const T*)w, v, g, dW, dH, (int)M, (int)Mout,
                                         gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
   }
 }

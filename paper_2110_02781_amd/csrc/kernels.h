@@ -52,6 +52,15 @@ struct BnBwdIn {
   float *g_gamma, *g_beta;
 };
 
+// n / d as a multiplication, for n * d < 2^32 (a 32-bit division is some 25 instructions, a 64-bit one more than 100)
+struct FastDiv {
+  uint32_t d, mul;
+  static FastDiv of(int d) { return FastDiv{(uint32_t)d, d > 1 ? (uint32_t)((0x100000000ull + (uint32_t)d - 1) / (uint32_t)d) : 0u}; }
+#ifdef __HIPCC__
+  __device__ __forceinline__ uint32_t div(uint32_t n) const { return d == 1 ? n : __umulhi(n, mul); }
+#endif
+};
+
 struct ConvGeom {
   int N, Hin, Win, Cin, Hout, Wout, Cout, kh, kw, stride, ph, pw;
 };
