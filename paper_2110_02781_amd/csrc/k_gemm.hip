@@ -979,15 +979,15 @@ __device__ __forceinline__ f4v tiny_mma(const float* a, const float* b, f4v acc,
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa), __builtin_bit_cast(bf16x8, pb), acc, 0, 0, 0);
 }
 
-template <typename T, int MODE, int NW>
+// WT wavefronts share a tile's reduction (launch_tiny picks the number), a block of NW wavefronts works on NW / WT tiles
+template <typename T, int MODE, int WT, int NW>
 __device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int bid) {
   constexpr int G = TinyStep<T>::G, KS = TinyStep<T>::KS, U = 4;
-  // a block of NW wavefronts works on NW / 4 tiles, four wavefronts each
-  constexpr int GROUPS = NW / 4;
-  __shared__ float red[GROUPS][4][16][17];
-  __shared__ float sred[GROUPS][2][16][17];
+  constexpr int GROUPS = NW / WT;
+  __shared__ float red[WT > 1 ? GROUPS : 1][WT][16][17];
+  __shared__ float sred[WT > 1 ? GROUPS : 1][2][16][17];
   if (MODE == MODE_DGRAD) __builtin_amdgcn_s_setprio(3);   // data-gradient chain: ahead of the weight-gradient stream's waves
-  const int grp = (threadIdx.x >> 8), wave = (threadIdx.x >> 6) & 3, lane = threadIdx.x & 63;
+  const int grp = (threadIdx.x >> 6) / WT, wave = (threadIdx.x >> 6) % WT, lane = threadIdx.x & 63;
   const int tile = bid * GROUPS + grp;
   const bool tile_ok = tile < p.jtiles * p.itiles;
   const int jt = tile % p.jtiles, it = tile / p.jtiles;
@@ -996,7 +996,7 @@ __device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int b
   const int R = MODE == MODE_FWD ? p.K : p.N;       // reduction extent (a multiple of G)
   const int nj = MODE == MODE_FWD ? p.N : p.K;      // output columns
   const int nst = (R + KS - 1) / KS;
-  const int sb = wave * nst / 4, se = (wave + 1) * nst / 4;
+  const int sb = wave * nst / WT, se = (wave + 1) * nst / WT;
   const int l16 = lane & 15, kg = (lane >> 4) * G;
   const size_t row = i0 + l16;
   const int col = j0 + l16;
@@ -1005,15 +1005,22 @@ __device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int b
   const T* W = reinterpret_cast<const T*>(p.y);
   const bool view = MODE == MODE_FWD && p.view.scale != nullptr;
   const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
-  // the output element this thread writes after the reduction; what is added to it there (residual, bias) is
-  // requested now: a load at the end of the kernel would be one more round trip on the launch-latency path
-  const int orow = (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
+  // the output elements this thread writes after the reduction (WT == 1: its four accumulators, else one); what is added
+  // to them there (residual, bias) is requested now: a load at the end of the kernel would be one more round trip on the
+  // launch-latency path
+  constexpr int NO = WT == 1 ? 4 : 1;
+  const int orow = WT == 1 ? 4 * (lane >> 4) : (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
   const size_t ig = i0 + orow;
   const int jg = j0 + ocol;
-  const bool in = tile_ok && ig < p.M && jg < nj;
-  float addend = 0.f;
-  if (MODE == MODE_FWD) { if (p.bias && tile_ok && jg < nj) addend = p.bias[jg]; }
-  else if (p.res && in) addend = to_f32(reinterpret_cast<const T*>(p.res)[ig * p.K + jg]);
+  bool in[NO];
+  float addend[NO];
+#pragma unroll
+  for (int o = 0; o < NO; ++o) {
+    in[o] = tile_ok && ig + o < p.M && jg < nj && (WT <= 4 || wave < 4);
+    addend[o] = 0.f;
+    if (MODE == MODE_FWD) { if (p.bias && in[o]) addend[o] = p.bias[jg]; }
+    else if (p.res && in[o]) addend[o] = to_f32(reinterpret_cast<const T*>(p.res)[(ig + o) * p.K + jg]);
+  }
 
   f4v acc = {0.f, 0.f, 0.f, 0.f};
   for (int s = sb; s < se; s += U) {
@@ -1070,30 +1077,49 @@ __device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int b
   }
 
   // register r of lane l is C[4*(l/16) + r][l%16]
+  if constexpr (WT == 1) {
+    float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float v = acc[r] + addend[r];
+      if (in[r]) reinterpret_cast<T*>(p.out)[(ig + r) * nj + jg] = from_f32<T>(v);
+      const float sv = in[r] ? round_to<T>(v) : 0.f;      // statistics of the values as stored
+      s1 += sv;
+      s2 += sv * sv;
+    }
+    if (MODE == MODE_FWD && p.stats) {
+      s1 += __shfl_xor(s1, 16, 64); s2 += __shfl_xor(s2, 16, 64);
+      s1 += __shfl_xor(s1, 32, 64); s2 += __shfl_xor(s2, 32, 64);
+      if (lane < 32 && tile_ok && jg < nj) p.stats[((size_t)it * 2 + (lane >> 4)) * p.N + jg] = lane < 16 ? s1 : s2;
+    }
+    return;
+  }
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[grp][wave][4 * (lane >> 4) + r][l16] = acc[r];
   __syncthreads();
-  asm volatile("" : "+v"(addend));          // first use: its conversion stays here
-  const float v0 = red[grp][0][orow][ocol] + red[grp][1][orow][ocol] + red[grp][2][orow][ocol] + red[grp][3][orow][ocol];
-  float v = v0;
-  if (MODE == MODE_FWD) {
-    v += addend;
-    if (in) reinterpret_cast<T*>(p.out)[ig * p.N + jg] = from_f32<T>(v);
-    if (p.stats) {
-      const float sv = in ? round_to<T>(v) : 0.f;     // statistics of the values as stored
+  asm volatile("" : "+v"(addend[0]));       // first use: its conversion stays here
+  const bool writer = WT <= 4 || wave < 4;  // 256 threads of a tile hold its elements
+  float v = 0.f;
+  if (writer) {
+#pragma unroll
+    for (int q = 0; q < WT; ++q) v += red[grp][q][orow][ocol];
+    v += addend[0];
+    if (in[0]) reinterpret_cast<T*>(p.out)[ig * nj + jg] = from_f32<T>(v);
+  }
+  if (MODE == MODE_FWD && p.stats) {
+    const float sv = in[0] ? round_to<T>(v) : 0.f;        // statistics of the values as stored
+    if (writer) {
       sred[grp][0][orow][ocol] = sv;
       sred[grp][1][orow][ocol] = sv * sv;
-      __syncthreads();
-      if ((threadIdx.x & 255) < 32 && tile_ok) {
-        const int sq = (threadIdx.x >> 4) & 1, c = threadIdx.x & 15;
-        float tot = 0.f;
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) tot += sred[grp][sq][rr][c];
-        if (j0 + c < p.N) p.stats[((size_t)it * 2 + sq) * p.N + j0 + c] = tot;
-      }
     }
-  } else {
-    if (in) reinterpret_cast<T*>(p.out)[ig * p.K + jg] = from_f32<T>(v + addend);
+    __syncthreads();
+    if (wave == 0 && lane < 32 && tile_ok) {
+      const int sq = lane >> 4, c = lane & 15;
+      float tot = 0.f;
+#pragma unroll
+      for (int rr = 0; rr < 16; ++rr) tot += sred[grp][sq][rr][c];
+      if (j0 + c < p.N) p.stats[((size_t)it * 2 + sq) * p.N + j0 + c] = tot;
+    }
   }
 }
 
@@ -1165,8 +1191,8 @@ __device__ __forceinline__ void pw_wgrad_tiny_body(const GemmArgs& p, const int 
   }
 }
 
-template <typename T, int MODE>
-__global__ __launch_bounds__(256) void pw_gemm_tiny_k(GemmArgs p) { pw_gemm_tiny_body<T, MODE, 4>(p, xcd_logical_block()); }   // the column tiles of a row panel share an L2
+template <typename T, int MODE, int WT, int NW>
+__global__ __launch_bounds__(64 * NW) void pw_gemm_tiny_k(GemmArgs p) { pw_gemm_tiny_body<T, MODE, WT, NW>(p, xcd_logical_block()); }   // the column tiles of a row panel share an L2
 template <typename T>
 __global__ __launch_bounds__(256) void pw_wgrad_tiny_k(GemmArgs p, int K_out) { pw_wgrad_tiny_body<T, 4>(p, K_out, blockIdx.x); }
 // data gradient and weight gradient of one short layer in one launch: both read the same dZ, their tiles are
@@ -1174,7 +1200,7 @@ __global__ __launch_bounds__(256) void pw_wgrad_tiny_k(GemmArgs p, int K_out) { 
 // pixels the weight-gradient tiles are few and each walks all pixels, so 16 wavefronts share that walk.
 template <typename T, int NW>
 __global__ __launch_bounds__(64 * NW) void pw_bwd_tiny_k(GemmArgs pd, GemmArgs pw, int K_out, int n_dgrad) {
-  if ((int)blockIdx.x < n_dgrad) pw_gemm_tiny_body<T, MODE_DGRAD, NW>(pd, blockIdx.x);
+  if ((int)blockIdx.x < n_dgrad) pw_gemm_tiny_body<T, MODE_DGRAD, 4, NW>(pd, blockIdx.x);
   else pw_wgrad_tiny_body<T, NW>(pw, K_out, blockIdx.x - n_dgrad);
 }
 
@@ -1194,9 +1220,22 @@ static void launch_tiny(int dt, hipStream_t st, GemmArgs& a, int ncols) {
   a.itiles = (int)((a.M + 15) / 16);
   a.nranges = a.itiles;
   a.tiles_per_range = 1;
-  unsigned grid = (unsigned)((size_t)a.jtiles * a.itiles);
-  if (dt == 0) hipLaunchKernelGGL((pw_gemm_tiny_k<float, MODE>), dim3(grid), dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((pw_gemm_tiny_k<bf16_t, MODE>), dim3(grid), dim3(256), 0, st, a);
+  // Four steps of a wavefront's reduction travel together, one trip to memory: enough wavefronts per tile to make it one trip
+  // or two.  MobileNetV2 at 32x32, batch 32, fp32: 57 launches a step, 303 us with four wavefronts per tile for all.  Up to four
+  // steps a tile to itself (no LDS, no barrier, a quarter of the blocks; 14 launches, 59 us); above sixteen steps eight
+  // wavefronts (24 launches: 134 us, with four 150, with sixteen 139).
+  const int R = MODE == MODE_FWD ? a.K : a.N, nst = (R + (dt == 0 ? 15 : 31)) / (dt == 0 ? 16 : 32);
+  const unsigned tiles = (unsigned)((size_t)a.jtiles * a.itiles);
+#define FTP_TINY(WT, NW)                                                                                                              \
+  do {                                                                                                                                \
+    const dim3 grid((tiles + (NW) / (WT) - 1) / ((NW) / (WT)));                                                                       \
+    if (dt == 0) hipLaunchKernelGGL((pw_gemm_tiny_k<float, MODE, WT, NW>), grid, dim3(64 * (NW)), 0, st, a);                          \
+    else hipLaunchKernelGGL((pw_gemm_tiny_k<bf16_t, MODE, WT, NW>), grid, dim3(64 * (NW)), 0, st, a);                                 \
+  } while (0)
+  if (nst <= 4) FTP_TINY(1, 4);
+  else if (nst <= 16) FTP_TINY(4, 4);
+  else FTP_TINY(8, 8);
+#undef FTP_TINY
 }
 
 template <typename T, int MODE, bool VEC>
