@@ -6,6 +6,56 @@
 
 namespace ftp {
 
+// one channel from its sum and second sum; write: also the vectors and running statistics in memory
+__device__ __forceinline__ void finish_channel(const BnPending& pend, int c, double s0, double s1, float p_g, float p_b, float p_rm,
+                                               float p_rv, float eps, float momentum, bool write, float& scv, float& shv) {
+  const double Md = (double)pend.M, mu = s0 / Md;
+  double var = s1 / Md - mu * mu;
+  if (var < 0.0) var = 0.0;
+  const double is = 1.0 / sqrt(var + (double)eps);
+  scv = (float)((double)p_g * is);
+  shv = (float)((double)p_b - mu * (double)scv);
+  if (!write) return;
+  pend.mean[c] = (float)mu;
+  pend.invstd[c] = (float)is;
+  pend.scale[c] = scv;
+  pend.shift[c] = shv;
+  const double unb = pend.M > 1 ? var * (Md / (Md - 1.0)) : var;
+  pend.run_mean[c] = (float)((1.0 - momentum) * p_rm + momentum * mu);
+  pend.run_var[c] = (float)((1.0 - momentum) * p_rv + momentum * unb);
+}
+
+// The same for nc channels from c0 (2 * nc <= nt threads of the block), by every block that reads the tensor: a few dozen
+// partials, which cost each of them one trip to memory where a launch of its own costs three (64 partials x 64 channels: 1.4 us
+// more per consumer, the launch was 4.1 and the gap in front of it 1.5).  red: nt doubles, sc / sh: [nc].
+// One block per channel (write) leaves the vectors and running statistics in memory; the others only use them.
+__device__ __forceinline__ void finish_pending_n(const BnPending& pend, int C, int c0, int nc, float eps, float momentum, bool write, int nt,
+                                                 double* red, float* sc, float* sh) {
+  const int tid = threadIdx.x, nv = 2 * nc, L = nt / nv, v = tid % nv, lane = tid / nv;
+  float p_g = 0.f, p_b = 0.f, p_rm = 0.f, p_rv = 0.f;
+  if (tid < nc) { p_g = pend.gamma[c0 + tid]; p_b = pend.beta[c0 + tid]; p_rm = pend.run_mean[c0 + tid]; p_rv = pend.run_var[c0 + tid]; }
+  double t = 0.0;
+  if (lane < L) {
+    const float* src = pend.partial + (size_t)(v >= nc ? C : 0) + c0 + (v >= nc ? v - nc : v);
+    for (int q0 = lane; q0 < pend.P; q0 += 16 * L) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = src[(size_t)(q0 + u * L < pend.P ? q0 + u * L : lane) * 2 * C];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) t += q0 + u * L < pend.P ? (double)x[u] : 0.0;
+    }
+    red[lane * nv + v] = t;
+  }
+  __syncthreads();
+  asm volatile("" : "+v"(p_g), "+v"(p_b), "+v"(p_rm), "+v"(p_rv));       // see finish_pending4
+  if (tid < nc) {
+    double s0 = 0.0, s1 = 0.0;
+    for (int l = 0; l < L; ++l) { s0 += red[l * nv + tid]; s1 += red[l * nv + nc + tid]; }
+    finish_channel(pend, c0 + tid, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, write, sc[tid], sh[tid]);
+  }
+  __syncthreads();
+}
+
 // finish pending BatchNorm statistics for channels c0..c0+3 (first 256 threads), result in insc[2][4]
 __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, int c0, float eps, float momentum, double (*pre)[8],
                                                 float (*insc)[4]) {
@@ -44,21 +94,7 @@ __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, in
   asm volatile("" : "+v"(p_g), "+v"(p_b), "+v"(p_rm), "+v"(p_rv));
   if (tid < 4) {
     const int c = c0 + tid;
-    const double Md = (double)pend.M, mu = s0 / Md;
-    double var = s1 / Md - mu * mu;
-    if (var < 0.0) var = 0.0;
-    const double is = 1.0 / sqrt(var + (double)eps);
-    const float scv = (float)((double)p_g * is);
-    const float shv = (float)((double)p_b - mu * (double)scv);
-    pend.mean[c] = (float)mu;
-    pend.invstd[c] = (float)is;
-    pend.scale[c] = scv;
-    pend.shift[c] = shv;
-    const double unb = pend.M > 1 ? var * (Md / (Md - 1.0)) : var;
-    pend.run_mean[c] = (float)((1.0 - momentum) * p_rm + momentum * mu);
-    pend.run_var[c] = (float)((1.0 - momentum) * p_rv + momentum * unb);
-    insc[0][tid] = scv;
-    insc[1][tid] = shv;
+    finish_channel(pend, c, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, true, insc[0][tid], insc[1][tid]);
   }
   __syncthreads();
 }

@@ -6,6 +6,7 @@
 // What bounds them is that unit, 256 FLOP a cycle and CU (157 TFLOP/s): 64 -> 64 channels, 5 taps, 32768 rows is 8.5 us a pass.
 #include "dev_common.h"
 #include "kernels.h"
+#include "bn_pending.h"
 
 namespace ftp {
 
@@ -30,6 +31,9 @@ struct Conv1dArgs {
   int Cin, Cout, kw, pad;   // pad: rows in front of the output row at tap 0
   int CP;             // C rounded up to 8: reduction index k = tap * CP + channel
   int itiles, jtiles, tiles_per_range;
+  BnPending pend;     // few rows, forward: the BatchNorm of x is still partial sums
+  float eps, momentum;
+  FastDiv dC, dW;     // few rows: by C and by W
 };
 
 enum { kC1Chan = 64, kC1Taps = 9, kC1Small = 2048 };
@@ -410,48 +414,64 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
   const int K = p.kw * p.C, nst = (K + 15) / 16, sb = wave * nst / 4, se = (wave + 1) * nst / 4;
   const int row = m0 + l16, col = j0 + l16;
   const bool row_ok = tile_ok && row < p.M, col_ok = tile_ok && col < p.NC;
-  const int t = (int)((unsigned)row % (unsigned)p.W);
+  const int t = row - (int)p.dW.div(row) * p.W;
   const T* X = reinterpret_cast<const T*>(p.x);
   const T* Wt = reinterpret_cast<const T*>(p.w);
-  const bool view = !DGRAD && p.view.scale != nullptr;
+  const bool view = !DGRAD && p.view.scale != nullptr, pending = !DGRAD && p.pend.partial != nullptr;
+  __shared__ double fin[DGRAD ? 1 : 256];
+  __shared__ float vec[DGRAD ? 1 : 2][kC1Chan];
   const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
   f4v acc = {0.f, 0.f, 0.f, 0.f};
-  for (int s0 = sb; s0 < se; s0 += U) {
-    float a[U][4], b[U][4], sc[U][4], sh[U][4];
-    bool ok[U][4], kin[U][4];
+  float a[U][4], b[U][4], sc[U][4], sh[U][4];
+  bool ok[U][4], kin[U][4];
+  int ch[U][4];
+  auto request = [&](const int s0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
 #pragma unroll
+      for (int e = 0; e < 4; ++e) kin[u][e] = ok[u][e] = false;
+      if (s0 + u >= se) continue;                       // the wavefront as a whole
+#pragma unroll
       for (int e = 0; e < 4; e += CV ? 4 : 1) {
         const int k = (s0 + u) * 16 + kg + e;
-        kin[u][e] = s0 + u < se && k < K;
-        const int kc = kin[u][e] ? k : 0, tap = kc / p.C, c = kc - tap * p.C;
+        kin[u][e] = k < K;
+        const int kc = kin[u][e] ? k : 0, tap = (int)p.dC.div(kc), c = kc - tap * p.C;
+        ch[u][e] = c;
         ok[u][e] = kin[u][e] && row_ok && (unsigned)(t + tap - p.pad) < (unsigned)p.W;
         const size_t xa = ok[u][e] ? (size_t)(row + tap - p.pad) * p.C + c : 0;
         const int cc = col_ok ? col : 0;
         if constexpr (CV) {
           *reinterpret_cast<float4*>(a[u]) = load4(X + xa);
-          if (view) { *reinterpret_cast<float4*>(sc[u]) = ld4(p.view.scale + c); *reinterpret_cast<float4*>(sh[u]) = ld4(p.view.shift + c); }
+          if (view && !pending) { *reinterpret_cast<float4*>(sc[u]) = ld4(p.view.scale + c); *reinterpret_cast<float4*>(sh[u]) = ld4(p.view.shift + c); }
           if constexpr (!DGRAD) *reinterpret_cast<float4*>(b[u]) = load4(Wt + (size_t)cc * K + kc);
           else
 #pragma unroll
             for (int f = 0; f < 4; ++f) b[u][f] = to_f32(Wt[((size_t)(c + f) * p.kw + (p.kw - 1 - tap)) * p.Cin + cc]);
         } else {
           a[u][e] = to_f32(X[xa]);
-          if (view) { sc[u][e] = p.view.scale[c]; sh[u][e] = p.view.shift[c]; }
+          if (view && !pending) { sc[u][e] = p.view.scale[c]; sh[u][e] = p.view.shift[c]; }
           b[u][e] = to_f32(Wt[DGRAD ? ((size_t)c * p.kw + (p.kw - 1 - tap)) * p.Cin + cc : (size_t)cc * K + kc]);
         }
       }
     }
+  };
+  // the first round's fragments travel while the statistics are finished
+  request(sb);
+  if (pending) finish_pending_n(p.pend, p.C, 0, p.C, p.eps, p.momentum, bid == 0, 256, fin, vec[0], vec[DGRAD ? 0 : 1]);
+  for (int s0 = sb; s0 < se; s0 += U) {
+    if (s0 != sb) request(s0);
 #pragma unroll
-    for (int u = 0; u < U; ++u)
+    for (int u = 0; u < U; ++u) {
+      if (s0 + u >= se) break;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
+        if (pending) { const int c = CV ? ch[u][0] + e : ch[u][e]; sc[u][e] = vec[0][c]; sh[u][e] = vec[DGRAD ? 0 : 1][c]; }
         const bool in = ok[u][CV ? 0 : e], kn = kin[u][CV ? 0 : e];
         float x = a[u][e];
         if (view) x = round_to<T>(clamp_act(fmaf(x, sc[u][e], sh[u][e]), lo, hi));
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? x : 0.f, kn ? b[u][e] : 0.f, acc, 0, 0, 0);
       }
+    }
   }
   // (a row or column outside the tensor, or a step past the end, contributed 0 x 0; a column outside is not written)
 #pragma unroll
@@ -479,10 +499,10 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
 template <typename T, bool CV>
 __global__ __launch_bounds__(256) void conv1d_fwd_small_k(Conv1dArgs p) { conv1d_tile<T, false, CV, 4>(p, xcd_logical_block()); }
 
-// 16 x 16 of g_w by 16 wavefronts that split the rows: no partial buffers, at most two rounds of eight row groups at 1024 rows
+// 16 x 16 of g_w by 16 wavefronts that split the rows: no partial buffers, one round of sixteen row groups up to 1024 rows, two at 2048
 template <typename T>
 __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __restrict__ g_w, const int bid) {
-  constexpr int U = 8, NW = 16;
+  constexpr int U = 16, NW = 16;
   __shared__ float red[NW][16][17];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, mg = lane >> 4;
   const int K = p.kw * p.Cin, jt_n = (K + 15) / 16;
@@ -502,7 +522,7 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
   float g_old = writer ? *dst : 0.f;
   const int per = (p.M + 4 * NW - 1) / (4 * NW) * 4, mb = wave * per, me = min(mb + per, p.M);
   f4v acc = {0.f, 0.f, 0.f, 0.f};
-  int t = (int)((unsigned)(mb + mg) % (unsigned)p.W);
+  int t = mb + mg - (int)p.dW.div(mb + mg) * p.W;
   for (int m = mb; m < me; m += 4 * U) {
     T dr[U], xr[U];
     bool xin[U];
@@ -559,6 +579,7 @@ static Conv1dArgs conv1d_args(const ConvGeom& g, bool dgrad) {
   a.C = dgrad ? g.Cout : g.Cin;
   a.NC = dgrad ? g.Cin : g.Cout;
   a.CP = (a.C + 7) / 8 * 8;
+  a.dC = FastDiv::of(a.C); a.dW = FastDiv::of(a.W);
   return a;
 }
 
@@ -583,8 +604,12 @@ static void conv1d_rows(hipStream_t st, Conv1dArgs& a, int* P_out) {
   else hipLaunchKernelGGL((conv1d_rows_k<T, DGRAD, 2>), dim3(nr * a.jtiles), dim3(256), lds, st, a);
 }
 
-void conv1d_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, void* z, float* stats, int* P_out) {
+int conv1d_small_ok(const ConvGeom& g) { return conv1d_ok(g) && conv1d_small(g); }
+
+void conv1d_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, const void* w, const ConvGeom& g, void* z,
+                float* stats, int* P_out) {
   Conv1dArgs a = conv1d_args(g, false);
+  a.pend = pend; a.eps = eps; a.momentum = momentum;
   a.x = in.z; a.w = w; a.view = View{in.z, in.scale, in.shift, in.act}; a.out = z; a.stats = stats;
   KScope ks(st, "conv1d_fwd", ((double)a.M * (g.Cin + g.Cout) + (double)g.Cout * g.kw * g.Cin) * (dt == 0 ? 4.0 : 2.0),
             2.0 * a.M * g.Cout * g.kw * g.Cin, a.M, g.kw * g.Cin, g.Cout);
@@ -654,7 +679,6 @@ void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGe
   left->push_back(ReduceJob{ws, g_w, P, g.Cout * K, K, K, 1, K});
 }
 
-int conv1d_bwd_small_ok(const ConvGeom& g) { return conv1d_small(g); }
 void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn) {
   Conv1dArgs d = conv1d_args(g, true), a = conv1d_args(g, false);
   d.x = dz; d.w = w; d.out = dIn;

@@ -514,15 +514,41 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
 // ------------------------------------------------------------------ pooling
 // block = (image n, group of 8 channels); 64 lanes walk the positions, fixed-order sum through LDS
 template <typename T>
-__global__ __launch_bounds__(64) void gap_fwd_k(View in, int N, int HW, int CG, T* __restrict__ out) {
+__global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float eps, float momentum, int N, int HW, int CG, T* __restrict__ out) {
   __shared__ float red[64][8];
+  __shared__ double fin[64];
+  __shared__ float vec[2][8];
   const int i = blockIdx.x, n = i / CG, cg = i % CG, lane = threadIdx.x;
+  const T* src = reinterpret_cast<const T*>(in.z) + (size_t)n * HW * CG * 8 + cg * 8;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int p = lane; p < HW; p += 64) {
-    float v[8];
-    view_load8<T>(in, ((size_t)n * HW + p) * CG * 8 + cg * 8, cg * 8, v);
+  float sc[8], sh[8];
+  const bool view = in.scale != nullptr;
+  constexpr int U = 4;                                  // positions of a lane on their way together
+  Raw<T> r[U];
+  auto request = [&](const int p0) __attribute__((always_inline)) {
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] += v[e];
+    for (int u = 0; u < U; ++u) raw_load(r[u], src + (size_t)(p0 + 64 * u < HW ? p0 + 64 * u : 0) * CG * 8);
+  };
+  request(lane);
+  if (pend.partial) {
+    finish_pending_n(pend, CG * 8, cg * 8, 8, eps, momentum, n == 0, 64, fin, vec[0], vec[1]);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { sc[e] = vec[0][e]; sh[e] = vec[1][e]; }
+  } else if (view) {
+    load8(in.scale + cg * 8, sc);
+    load8(in.shift + cg * 8, sh);
+  }
+  const float lo = act_lo(in.act), hi = act_hi(in.act);
+  for (int p0 = lane; p0 < HW; p0 += 64 * U) {
+    if (p0 != lane) request(p0);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (p0 + 64 * u >= HW) break;
+      float v[8];
+      raw_unpack(r[u], v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) acc[e] += view ? round_to<T>(clamp_act(fmaf(v[e], sc[e], sh[e]), lo, hi)) : v[e];
+    }
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) red[lane][e] = acc[e];
@@ -535,11 +561,11 @@ __global__ __launch_bounds__(64) void gap_fwd_k(View in, int N, int HW, int CG, 
   }
 }
 
-void gap_fwd(int dt, hipStream_t st, HView in, int N, int HW, int C, void* out) {
+void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out) {
   View v{in.z, in.scale, in.shift, in.act};
   int n = N * (C / 8);
   KScope ks(st, "gap_fwd", ((double)N * HW * C + (double)N * C) * (dt == 0 ? 4.0 : 2.0), 3.0 * N * HW * C);
-  FTP_DISPATCH(dt, hipLaunchKernelGGL(gap_fwd_k<T>, dim3(n), dim3(64), 0, st, v, N, HW, C / 8, (T*)out));
+  FTP_DISPATCH(dt, hipLaunchKernelGGL(gap_fwd_k<T>, dim3(n), dim3(64), 0, st, v, pend, eps, momentum, N, HW, C / 8, (T*)out));
 }
 
 template <typename T>

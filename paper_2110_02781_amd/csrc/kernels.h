@@ -109,13 +109,20 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
                              float momentum, const void* res, void* out);
 
 // ---- pooling, loss, optimiser ---------------------------------------------------
-void gap_fwd(int dt, hipStream_t st, HView in, int N, int HW, int C, void* out);
+// pend.partial != nullptr: the BatchNorm of the input is still partial sums; finished here
+void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out);
 void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn);
 // per-row loss into row_loss[B], dlogits[B][classes] = (softmax - onehot)/B, then mean into *loss
 void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* labels, int B, int classes,
                 float* row_loss, void* dlogits, float* loss);
 // g_bias[j] += sum_b d[b][j]
 void bias_grad(int dt, hipStream_t st, const void* d, int B, int Nout, float* g_bias);
+// the whole backward of a fully connected layer d[B][N] -> in[B][K] in one launch: g_w += d^T in, g_b += column sums of d,
+// and unless dIn is nullptr dIn = d W.  HW >= 1: the layer stands behind an average over HW positions and dIn [B][HW][K] is
+// that one's input gradient.  fc_bwd_ok: few enough rows that the tiles' walks over them stay short.
+int fc_bwd_ok(int B, int N, int K);
+int fc_bwd_gap_ok(int B, int HW, int K);
+void fc_bwd(int dt, hipStream_t st, const void* d, HView in, const void* w, int B, int N, int K, float* g_w, float* g_b, void* dIn, int HW);
 // g += wd*w; v = mu*v+g; w -= lr*v; g = 0; optional working copy w_lp (bfloat16)
 void sgd_update(hipStream_t st, float* w, float* g, float* v, void* w_lp, size_t n, float lr, float mu,
                 float wd);
@@ -157,14 +164,16 @@ void reduce_group(hipStream_t st, const ReduceJob* jobs, int n);
 
 // ---- 1 x kw convolutions, stride 1, same length, at most 64 channels (conv1d_ok): implicit GEMMs, no scratch but ws ----
 int conv1d_ok(const ConvGeom& g);
-void conv1d_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, void* z, float* stats, int* P_out);
+int conv1d_small_ok(const ConvGeom& g);     // few rows
+// pend.partial != nullptr (few rows only): the BatchNorm of the input is still partial sums, not those in `stats`; finished here
+void conv1d_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, const void* w, const ConvGeom& g, void* z,
+                float* stats, int* P_out);
 // sums != nullptr (prev is a view): also the partial sums bn_bwd_reduce would compute for the BatchNorm + activation `prev`
 void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out);
 size_t conv1d_wgrad_ws(const ConvGeom& g);
 // partial sums, if any, are left in ws and appended to `left`
 void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left);
-// few rows (conv1d_bwd_small_ok): weight and data gradient in one launch
-int conv1d_bwd_small_ok(const ConvGeom& g);
+// few rows (conv1d_small_ok): weight and data gradient in one launch
 void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn);
 
 // ---- depthwise 3x3 ----------------------------------------------------------------

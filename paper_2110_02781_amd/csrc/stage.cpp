@@ -691,7 +691,18 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
       return;
     }
   } else if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
-    conv1d_fwd(s->dt, st, in, w, g, z, s->bn_part, &P);
+    // the partials of the input's BatchNorm, if it is pending, are read by every block: this layer's go to the other half
+    float* part = s->bn_part;
+    if (pend && pend->partial == part) part += (size_t)kBnPartials / 2 * 2 * s->max_c;
+    const BnPending none{};
+    conv1d_fwd(s->dt, st, in, pend ? *pend : none, kBnEps, s->bn_mom, w, g, z, part, &P);
+    if (pend) pend->partial = nullptr;
+    if (defer && pend) {
+      *pend = BnPending{part, P, M, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv};
+      return;
+    }
+    bn_finalize(st, part, P, M, C, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv, kBnEps, s->bn_mom);
+    return;
   } else if (sb.type == SUB_DIRECT && conv_direct_gemm_ok(g) && s->im2col &&
              conv_direct_gemm_wpad_elems(g) * s->es <= s->ws_floats * sizeof(float)) {
     // the float workspace is free during a forward: the padded weight copy lives there
@@ -711,6 +722,7 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
 
 // every unit of the stage over the input at offset 0 of the slot's stash, with the weights W
 static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet& W, hipStream_t st) {
+  BnPending carry{};       // a short 1-D convolution leaves its statistics to the short 1-D convolution or the average behind it
   for (size_t i = 0; i < s->plan.size(); ++i) {
     const UnitPlan& p = s->plan[i];
     const UnitInfo& u = *p.info;
@@ -723,8 +735,17 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
     HView in = v.unit_in[i];
     switch (u.d.kind) {
       case FTP_UNIT_CONV:
-        sub_forward(s, sl, p, 0, in, W, st);
+      {
+        auto small1d = [&](const UnitInfo& x) {
+          if (x.d.kind != FTP_UNIT_CONV || x.subs[0].type != SUB_DIRECT) return false;
+          ConvGeom g = x.subs[0].g; g.N = s->batch;
+          return conv1d_small_ok(g) != 0;
+        };
+        const bool defer = small1d(u) && i + 1 < s->plan.size() &&
+                           (s->plan[i + 1].info->d.kind == FTP_UNIT_GAP || small1d(*s->plan[i + 1].info));
+        sub_forward(s, sl, p, 0, in, W, st, &carry, defer);
         break;
+      }
       case FTP_UNIT_INVRES: {
         HView h = in;
         BnPending pend{};
@@ -751,7 +772,8 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
         break;
       }
       case FTP_UNIT_GAP:
-        gap_fwd(s->dt, st, in, s->batch, u.inH * u.inW, u.inC, sl.stash + p.out_off);
+        gap_fwd(s->dt, st, in, carry, kBnEps, s->bn_mom, s->batch, u.inH * u.inW, u.inC, sl.stash + p.out_off);
+        carry.partial = nullptr;
         break;
       case FTP_UNIT_FC:
         pw_fwd(s->dt, st, in, conv_w(s, W, p.p_off), W.w32 + p.p_off + (size_t)u.outC * u.inC, (size_t)s->batch, u.inC,
@@ -1036,7 +1058,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     } else if (sb.type == SUB_DW) {
       s->q_dw.push_back(DwWgradJob{dz, in, g, part, gw});
       if (dIn) run_dw_dgrad();
-    } else if (dIn && conv1d_bwd_small_ok(g)) {
+    } else if (dIn && conv1d_small_ok(g)) {
       conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn);
     } else {
       conv1d_wgrad(s->dt, st, dz, in, g, part, gw, &s->q_red);
@@ -1063,7 +1085,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     return FTP_OK;
   }
   if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
-    if (!overlap && dIn && conv1d_bwd_small_ok(g)) { conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn); return FTP_OK; }
+    if (!overlap && dIn && conv1d_small_ok(g)) { conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn); return FTP_OK; }
     conv1d_wgrad(s->dt, ws, dz, in, g, wsp, gw, &s->q_red);
     reduce_group(ws, s->q_red.data(), (int)s->q_red.size());
     s->q_red.clear();
@@ -1167,6 +1189,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
   const void* d = dy_dev ? dy_dev : sl.dlogits;     // gradient of the current unit's output (read only)
   int flip = 0;
+  bool gap_done = false;
   for (int i = (int)s->plan.size() - 1; i >= 0; --i) {
     const UnitPlan& p = s->plan[i];
     const UnitInfo& u = *p.info;
@@ -1182,13 +1205,23 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
         break;
       case FTP_UNIT_FC: {
         size_t woff = p.p_off;
+        if (fc_bwd_ok(s->batch, u.outC, u.inC)) {
+          // behind an average (not the stage's first unit): its backward is part of the data gradient's last step
+          const UnitInfo* pu = i > 1 ? s->plan[i - 1].info : nullptr;
+          const int HW = pu && pu->d.kind == FTP_UNIT_GAP && s->prof == nullptr && fc_bwd_gap_ok(s->batch, pu->inH * pu->inW, u.inC)
+                             ? pu->inH * pu->inW : 0;
+          fc_bwd(s->dt, st, d, in, conv_w(s, W, woff), s->batch, u.outC, u.inC, s->grads + woff, s->grads + woff + (size_t)u.outC * u.inC, next, HW);
+          gap_done = HW > 0;
+          break;
+        }
         pw_wgrad(s->dt, st, d, in, (size_t)s->batch, u.inC, u.outC, s->ws, s->grads + woff);
         bias_grad(s->dt, st, d, s->batch, u.outC, s->grads + woff + (size_t)u.outC * u.inC);
         if (next) pw_dgrad(s->dt, st, d, conv_w(s, W, woff), nullptr, (size_t)s->batch, u.inC, u.outC, next);
         break;
       }
       case FTP_UNIT_GAP:
-        if (next) gap_bwd(s->dt, st, d, s->batch, u.inH * u.inW, u.inC, next);
+        if (gap_done) { produced = false; gap_done = false; }         // d is its input's gradient already
+        else if (next) gap_bwd(s->dt, st, d, s->batch, u.inH * u.inW, u.inC, next);
         break;
       case FTP_UNIT_CONV:
         if ((rc = sub_backward(s, sl, p, 0, d, in, v.sub_out[i][0], next, nullptr, W, st))) return rc;
