@@ -1863,7 +1863,11 @@ static bool dw_rows_pays(int dt, const ConvGeom& g) {
   return dt == 1 && (size_t)g.Hin * g.Win >= (size_t)112 * 112 && dw_march_plan(g, &m) && m.nslab > 1 && dw_rows_plan(g, &r, &lds);
 }
 
-void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w) {
+void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left) {
+  auto sum = [&](int P) {
+    if (left) left->push_back(ReduceJob{ws, g_w, P, 9 * g.Cout, g.Cout, 1, 9, g.Cout});
+    else reduce_partials(st, ws, P, (size_t)9 * g.Cout, g.Cout, 1, 9, g_w);
+  };
   const int es = dt == 0 ? 4 : 2;
   {
     DwRowsArgs r{};
@@ -1882,7 +1886,7 @@ void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& 
           else hipLaunchKernelGGL((dw_wgrad_rows_k<2, false>), grid, block, lds, st, r);
         }
       }
-      reduce_partials(st, ws, r.P, (size_t)9 * g.Cout, g.Cout, 1, 9, g_w);
+      sum(r.P);
       return;
     }
   }
@@ -1902,7 +1906,7 @@ void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& 
         else { FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_k<T, 2, false>), dim3(grid), dim3(256), 0, st, m)); }
       }
     }
-    reduce_partials(st, ws, m.P, (size_t)9 * g.Cout, g.Cout, 1, 9, g_w);
+    sum(m.P);
     return;
   }
   size_t lds;
@@ -1921,7 +1925,7 @@ void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& 
                                           g.Hout, g.Wout, g.Cout, ws));
     }
   }
-  reduce_partials(st, ws, d.nblocks, (size_t)9 * g.Cout, g.Cout, 1, 9, g_w);
+  sum(d.nblocks);
 }
 
 void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::vector<ReduceJob>* left) {
@@ -1947,7 +1951,7 @@ void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::
       if (w.g.stride != stride || (w.in.scale != nullptr) != vw) continue;
       DwMarchArgs m{};
       // what another kernel serves (a layer the marching kernel cannot cut into its slabs, the large images) goes by itself
-      if (dw_rows_pays(dt, w.g) || !dw_march_plan(w.g, &m)) { dw_wgrad(dt, st, w.dz, w.in, w.g, w.ws, w.g_w); continue; }
+      if (dw_rows_pays(dt, w.g) || !dw_march_plan(w.g, &m)) { dw_wgrad(dt, st, w.dz, w.in, w.g, w.ws, w.g_w, left); continue; }
       m.dz = w.dz; m.in = View{w.in.z, w.in.scale, w.in.shift, w.in.act}; m.ws = w.ws;
       a.blk0[a.n] = blocks;
       a.job[a.n++] = m;

@@ -1390,7 +1390,7 @@ struct PwWgGroupJob {
   const void* x; const void* y;       // dZ [M][N], A [M][K]
   const float* scale; const float* shift;
   float* out;                         // g_w, or partials [S][N][K]
-  int M, K, N, act;
+  int M, K, N, act, rows;             // rows per block
   int wtiles, ntiles;                 // tiles along the wider / narrower of N and K
   int nblk, add;
 };
@@ -1411,7 +1411,7 @@ __global__ __launch_bounds__(256) void pw_wgrad_group_k(PwWgGroup a) {
   const int w0 = tile % p.wtiles * kGrpWide, n0 = tile / p.wtiles * kGrpNarrow;
   const T* W = reinterpret_cast<const T*>(wide_n ? p.x : p.y);
   const T* Nn = reinterpret_cast<const T*>(wide_n ? p.y : p.x);
-  const int mb = split * kGrpRows, me = min(mb + kGrpRows, p.M);
+  const int mb = split * p.rows, me = min(mb + p.rows, p.M);
   const bool view_w = p.scale != nullptr && !wide_n, view_n = p.scale != nullptr && wide_n;
   const float lo = act_lo(p.act), hi = act_hi(p.act);
 
@@ -1503,9 +1503,13 @@ __global__ __launch_bounds__(256) void pw_wgrad_group_k(PwWgGroup a) {
 }
 
 // bfloat16 layers the transposing kernel takes (long ones) run there; both leave partials
+// more rows per block where they are many: at most 512 partials per layer
+static int grp_rows(size_t M) { return kGrpRows * (int)((M + 512 * kGrpRows - 1) / (512 * kGrpRows)); }
+
 size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, int share) {
   if (pw_wgrad_tr_ok(dt, M, K, N)) return pw_wgrad_tr_ws(M, K, N, share);
-  return M > kGrpRows ? (M + kGrpRows - 1) / kGrpRows * (size_t)N * K : 0;
+  const int R = grp_rows(M);
+  return M > (size_t)R ? (M + R - 1) / R * (size_t)N * K : 0;
 }
 
 void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int share, std::vector<ReduceJob>* left) {
@@ -1524,8 +1528,8 @@ void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int s
   for (int i = 0; i < n; ++i) {
     const PwWgradJob& w = jobs[i];
     if (pw_wgrad_tr_ok(dt, w.M, w.K, w.N)) continue;
-    const int S = (int)((w.M + kGrpRows - 1) / kGrpRows), wide = w.N >= w.K ? w.N : w.K, narrow = w.N >= w.K ? w.K : w.N;
-    PwWgGroupJob j{w.dz, w.a.z, w.a.scale, w.a.shift, S == 1 ? w.g_w : w.ws, (int)w.M, w.K, w.N, w.a.act,
+    const int R = grp_rows(w.M), S = (int)((w.M + R - 1) / R), wide = w.N >= w.K ? w.N : w.K, narrow = w.N >= w.K ? w.K : w.N;
+    PwWgGroupJob j{w.dz, w.a.z, w.a.scale, w.a.shift, S == 1 ? w.g_w : w.ws, (int)w.M, w.K, w.N, w.a.act, R,
                    (wide + kGrpWide - 1) / kGrpWide, (narrow + kGrpNarrow - 1) / kGrpNarrow, 0, S == 1};
     j.nblk = j.wtiles * j.ntiles * S;
     a.blk0[a.n] = blocks;

@@ -206,7 +206,8 @@ void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvG
 struct DwWgradJob { const void* dz; HView in; ConvGeom g; float* ws; float* g_w; };
 void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::vector<ReduceJob>* left);
 size_t dw_wgrad_ws(const ConvGeom& g);
-void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w);
+// left != nullptr: the sum over the partials is appended there instead of done
+void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left = nullptr);
 
 // ---- pointwise / fully connected GEMMs (MFMA) ---------------------------------------
 // Z[M][N] = A'[M][K] * W[N][K]^T (+ bias[N]); when stats != nullptr also writes the per-column

@@ -272,7 +272,7 @@ struct ftp_stage {
   bool bjoin_pending[2] = {false, false};
   int bset = 0;
   bool bset_open = false;      // a layer of the current unit has written into the set
-  // A stage too small to run weight gradients on a second stream (a chain of short launches) notes them instead: every
+  // A stage that does not run weight gradients on a second stream (ftp_stage_create_ex says when) notes them instead: every
   // layer's dz and partial sums have a place of their own, and the weight gradients of all layers run together at the end
   // of the backward call, a few launches for all of them.
   bool defers = false;
@@ -376,7 +376,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   s->es = m->dtype == FTP_F32 ? 4 : 2;
   if (hipGetDevice(&s->device) != hipSuccess) { ftp_set_error("stage_create: no HIP device"); delete s; return FTP_ERR_HIP; }
 
-  size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, dz_bytes = 0, part_floats = 0, n_subs = 0;
+  size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, dz_bytes = 0, part_floats = 0, n_convs = 0, z_values = 0;
   int max_c = 8;
   auto act_bytes = [&](int H, int W, int C) { return align_up((size_t)batch * H * W * C * s->es, 256); };
   const UnitInfo& first = m->units[a];
@@ -414,6 +414,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
         if (m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > part) part = pw_bwd_fused_ws(M, g.Cin, g.Cout);
       }
       p.dz_off.push_back(dz_bytes); dz_bytes += zb;
+      z_values += M * g.Cout;
       p.part_off.push_back(part_floats); part_floats += patches ? 0 : align_up(part, 64);
       if (sb.type == SUB_PW && m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > s->ws_fused_floats)
         s->ws_fused_floats = pw_bwd_fused_ws(M, g.Cin, g.Cout);
@@ -426,7 +427,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
         if (conv_direct_dgrad_gemm_w_elems(g) > ws_floats) ws_floats = conv_direct_dgrad_gemm_w_elems(g);
       }
     }
-    n_subs += u.subs.size();
+    n_convs += u.subs.size();
     p.out_virtual = (u.d.kind == FTP_UNIT_CONV);
     p.out_off = 0;
     if (!p.out_virtual && u.d.kind != FTP_UNIT_LOSS) {
@@ -444,13 +445,16 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     if (u.d.kind == FTP_UNIT_LOSS) { s->has_loss = true; s->classes = u.inC; }
     s->plan.push_back(p);
   }
-  // Two ways to keep weight gradients off the data-gradient chain: a second stream (forks and joins are event calls per layer:
-  // pays only when the kernels are long; a 32x32-input stage, largest activation 12 MB, was 10 % faster on one stream, a
-  // 224x224 one 15 % slower), or all of them at the end of the call (a dz buffer per layer, full launches only if the layers are many and small)
-  s->defers = max_act < ((size_t)32 << 20);
+  // Two ways to keep weight gradients off the data-gradient chain: all of them at the end of the call, or each on a second
+  // stream as soon as its dz is there.  The second costs event calls and a division of the memory bandwidth, and pays only where
+  // single layers fill the GPU for long: from about 20 M values per convolution output on average.  A step at 224x224, ms,
+  // second stream / end of the call: whole network batch 32 fp32 4.9 / 4.0, 128 fp32 11.6 / 11.3, 32 bfloat16 (width 1.4) 4.0 / 3.2,
+  // 128 bfloat16 5.8 / 5.6 (16.5 M values); block 2 alone bfloat16 batch 16 0.25 / 0.20, 32 (16.8 M) 0.295 / 0.289, 64 (34 M)
+  // 0.490 / 0.509; units 1-4 bfloat16 batch 32 1.03 / 0.88, 64 (22 M) 1.42 / 1.45; width 1.4 batch 128 bfloat16 (26 M) 7.4 / 7.5.
+  s->defers = n_convs == 0 || z_values / n_convs < ((size_t)20 << 20);
   s->stash_bytes = stash; s->stats_floats = stats; s->max_act_bytes = max_act; s->ws_floats = ws_floats; s->max_c = max_c;
 
-  s->q_pw.reserve(n_subs); s->q_dw.reserve(n_subs); s->q_red.reserve(n_subs);      // a layer leaves at most one of each
+  s->q_pw.reserve(n_convs); s->q_dw.reserve(n_convs); s->q_red.reserve(n_convs);      // a layer leaves at most one of each
   int rc = FTP_OK;
   size_t np = s->n_param ? s->n_param : 8;
   size_t nb = s->n_bn ? s->n_bn : 8;
@@ -929,7 +933,7 @@ extern "C" int ftp_stage_aggregate_weights(ftp_stage* s, const int* slots, int n
 // gradient runs on the stage's side stream unless per-unit profiling is on.
 // mode: the whole layer, or from a dz that the caller formed (passed as dA)
 enum { BWD_FULL = 0, BWD_FROM_DZ = 1 };
-// stage_forks: the stage is large enough to run weight gradients on its second stream (decides which kernels a
+// stage_forks: the stage runs weight gradients on its second stream (decides which kernels a
 // layer uses); stage_overlaps: it does so now (not while per-unit profiling needs everything on one stream)
 static bool stage_forks(const ftp_stage* s) { return !s->defers; }
 static bool stage_overlaps(const ftp_stage* s) { return s->prof == nullptr && stage_forks(s); }
@@ -945,9 +949,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   int C = g.Cout;
   size_t M = (size_t)s->batch * g.Hout * g.Wout;
   float* stt = sl.stats + p.st_off[k];
-  // The fork/join costs four event calls per layer on the host and a cross-stream dependency on the device:
-  // it pays only when the kernels are long.  Measured: a 32x32-input stage (largest activation 12 MB) is
-  // 10 % faster on one stream, a 224x224 one 15 % slower.
+  // the fork and join cost four event calls per layer and a cross-stream dependency: long kernels only
   const bool overlap = mode == BWD_FULL && stage_overlaps(s) && M * (size_t)C >= ((size_t)1 << 20);
   int b = 0, rc_join = 0;
   void* dz = const_cast<void*>(dA);
