@@ -7,12 +7,12 @@
 namespace ftp {
 
 // one channel from its sum and second sum; write: also the vectors and running statistics in memory
-__device__ __forceinline__ void finish_channel(const BnPending& pend, int c, double s0, double s1, float p_g, float p_b, float p_rm,
+__device__ __forceinline__ void finish_channel(const BnPending& pend, double inv_M, int c, double s0, double s1, float p_g, float p_b, float p_rm,
                                                float p_rv, float eps, float momentum, bool write, float& scv, float& shv) {
-  const double Md = (double)pend.M, mu = s0 / Md;
-  double var = s1 / Md - mu * mu;
+  const double mu = s0 * inv_M;
+  double var = s1 * inv_M - mu * mu;
   if (var < 0.0) var = 0.0;
-  const double is = 1.0 / sqrt(var + (double)eps);
+  const double is = rsqrt(var + (double)eps);
   scv = (float)((double)p_g * is);
   shv = (float)((double)p_b - mu * (double)scv);
   if (!write) return;
@@ -20,7 +20,7 @@ __device__ __forceinline__ void finish_channel(const BnPending& pend, int c, dou
   pend.invstd[c] = (float)is;
   pend.scale[c] = scv;
   pend.shift[c] = shv;
-  const double unb = pend.M > 1 ? var * (Md / (Md - 1.0)) : var;
+  const double unb = pend.M > 1 ? var / (1.0 - inv_M) : var;
   pend.run_mean[c] = (float)((1.0 - momentum) * p_rm + momentum * mu);
   pend.run_var[c] = (float)((1.0 - momentum) * p_rv + momentum * unb);
 }
@@ -33,6 +33,7 @@ __device__ __forceinline__ void finish_pending_n(const BnPending& pend, int C, i
                                                  double* red, float* sc, float* sh) {
   const int tid = threadIdx.x, nv = 2 * nc, L = nt / nv, v = tid % nv, lane = tid / nv;
   float p_g = 0.f, p_b = 0.f, p_rm = 0.f, p_rv = 0.f;
+  const double inv_M = early_inverse((double)pend.M);
   if (tid < nc) { p_g = pend.gamma[c0 + tid]; p_b = pend.beta[c0 + tid]; p_rm = pend.run_mean[c0 + tid]; p_rv = pend.run_var[c0 + tid]; }
   double t = 0.0;
   if (lane < L) {
@@ -51,7 +52,7 @@ __device__ __forceinline__ void finish_pending_n(const BnPending& pend, int C, i
   if (tid < nc) {
     double s0 = 0.0, s1 = 0.0;
     for (int l = 0; l < L; ++l) { s0 += red[l * nv + tid]; s1 += red[l * nv + nc + tid]; }
-    finish_channel(pend, c0 + tid, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, write, sc[tid], sh[tid]);
+    finish_channel(pend, inv_M, c0 + tid, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, write, sc[tid], sh[tid]);
   }
   __syncthreads();
 }
@@ -63,6 +64,7 @@ __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, in
   // what the last four threads need at the end is requested now, and the partials four at a time from clamped
   // addresses: this runs at the head of kernels that are a chain of memory round trips and little else
   float p_g = 0.f, p_b = 0.f, p_rm = 0.f, p_rv = 0.f;
+  const double inv_M = early_inverse((double)pend.M);
   if (tid < 4) { p_g = pend.gamma[c0 + tid]; p_b = pend.beta[c0 + tid]; p_rm = pend.run_mean[c0 + tid]; p_rv = pend.run_var[c0 + tid]; }
   if (tid < 256) {
     const int v = tid & 7, lane = tid >> 3;           // 4 sums, 4 second sums; 32 lanes each
@@ -94,7 +96,7 @@ __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, in
   asm volatile("" : "+v"(p_g), "+v"(p_b), "+v"(p_rm), "+v"(p_rv));
   if (tid < 4) {
     const int c = c0 + tid;
-    finish_channel(pend, c, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, true, insc[0][tid], insc[1][tid]);
+    finish_channel(pend, inv_M, c, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, true, insc[0][tid], insc[1][tid]);
   }
   __syncthreads();
 }

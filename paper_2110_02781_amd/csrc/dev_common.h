@@ -174,4 +174,12 @@ __device__ __forceinline__ float wave_sum(float x) {
   return ((r0 + r1) + r2) + r3;
 }
 
+// 1 / x computed here, not behind the reductions it is used after (a float64 division is some forty instructions, and there
+// a few threads would do it while all others wait)
+__device__ __forceinline__ double early_inverse(double x) {
+  double r = 1.0 / x;
+  asm volatile("" : "+v"(r));
+  return r;
+}
+
 }  // namespace ftp

@@ -757,6 +757,7 @@ __global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pen
     raw4_load(rv[q], src + (size_t)(m < Min ? m : 0) * C + c0);
   }
   float bn_g = 0.f, bn_b = 0.f, bn_rm = 0.f, bn_rv = 0.f;
+  const double inv_M = early_inverse((double)M);
   if (tid < 4) { bn_g = gamma[c0 + tid]; bn_b = beta[c0 + tid]; bn_rm = run_mean[c0 + tid]; bn_rv = run_var[c0 + tid]; }
   if (tid < 36) wl[tid / 4][tid % 4] = to_f32(w[(size_t)(c0 + tid % 4) * 9 + tid / 4]);
   const bool view = in.scale != nullptr;
@@ -820,16 +821,16 @@ __global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pen
     const int c = c0 + tid;
     double s0 = 0.0, s1 = 0.0;
     for (int q = 0; q < nw; ++q) { s0 += red[q][tid]; s1 += red[q][4 + tid]; }
-    const double Md = (double)M, mu = s0 / Md;
-    double var = s1 / Md - mu * mu;
+    const double mu = s0 * inv_M;
+    double var = s1 * inv_M - mu * mu;
     if (var < 0.0) var = 0.0;
-    const double is = 1.0 / sqrt(var + (double)eps);
+    const double is = rsqrt(var + (double)eps);
     const float scv = (float)((double)bn_g * is);
     mean[c] = (float)mu;
     invstd[c] = (float)is;
     scale[c] = scv;
     shift[c] = (float)((double)bn_b - mu * (double)scv);
-    const double unb = M > 1 ? var * (Md / (Md - 1.0)) : var;
+    const double unb = M > 1 ? var / (1.0 - inv_M) : var;
     run_mean[c] = (float)((1.0 - momentum) * bn_rm + momentum * mu);
     run_var[c] = (float)((1.0 - momentum) * bn_rv + momentum * unb);
   }
@@ -882,6 +883,7 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
     const int m = tid + q * nt;
     zv[q] = load4(zin + (size_t)(m < M ? m : 0) * C + c0);
   }
+  const double inv_M = early_inverse((double)M), inv_Mo = early_inverse((double)Mout);
   float gw_old = 0.f, f_mu = 0.f, f_is = 0.f, f_g = 0.f, f_gg = 0.f, f_gb = 0.f;
   float f2_mu = 0.f, f2_is = 0.f, f2_g = 0.f, f2_gg = 0.f, f2_gb = 0.f;
   if (tid < 36) gw_old = g_w[(size_t)(c0 + tid % 4) * 9 + tid / 4];
@@ -949,11 +951,11 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
       const int c = c0 + tid;
       double s0 = 0.0, s1 = 0.0;
       for (int q = 0; q < (nt >> 6); ++q) { s0 += red2[q][tid]; s1 += red2[q][4 + tid]; }
-      const double mu = f2_mu, is = f2_is, gm = f2_g, Md = (double)Mout;
+      const double mu = f2_mu, is = f2_is, gm = f2_g;
       const double dbeta = s0, dgamma = is * (s1 - mu * s0);
       bo.g_gamma[c] = f2_gg + (float)dgamma;
       bo.g_beta[c] = f2_gb + (float)dbeta;
-      const double k1 = gm * is, k2 = -k1 * is * dgamma / Md, k3 = -k1 * dbeta / Md - k2 * mu;
+      const double k1 = gm * is, k2 = -k1 * is * dgamma * inv_Mo, k3 = -k1 * dbeta * inv_Mo - k2 * mu;
       coef2[0][tid] = (float)k1; coef2[1][tid] = (float)k2; coef2[2][tid] = (float)k3;
     }
     __syncthreads();
@@ -1038,11 +1040,11 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
     const int e = tid - 64, c = c0 + e;
     double s0 = 0.0, s1 = 0.0;
     for (int q = 0; q < nw; ++q) { s0 += red[q][36 + e]; s1 += red[q][40 + e]; }
-    const double mu = f_mu, is = f_is, gm = f_g, Md = (double)M;
+    const double mu = f_mu, is = f_is, gm = f_g;
     const double dbeta = s0, dgamma = is * (s1 - mu * s0);
     g_gamma[c] = f_gg + (float)dgamma;
     g_beta[c] = f_gb + (float)dbeta;
-    const double k1 = gm * is, k2 = -k1 * is * dgamma / Md, k3 = -k1 * dbeta / Md - k2 * mu;
+    const double k1 = gm * is, k2 = -k1 * is * dgamma * inv_M, k3 = -k1 * dbeta * inv_M - k2 * mu;
     coef[0][e] = (float)k1; coef[1][e] = (float)k2; coef[2][e] = (float)k3;
   }
   __syncthreads();

@@ -106,73 +106,71 @@ void bn_stats(int dt, hipStream_t st, const void* z, size_t M, int C, float* par
   *P_out = t.P;
 }
 
-// Sum partial[p][q][c] over p in float64; kFinCh channels per block, kFinLanes lanes per channel
-// (few channels per block: a layer has only C / kFinCh blocks and the partial walk is pure latency).
+// Sums of partial[p][2][C] over p in float64; kFinCh channels per block, kFinLanes lanes per channel (few channels per
+// block: a layer has only C / kFinCh blocks and the partial walk is pure latency).  Threads 0 .. kFinCh - 1 return the
+// sum and the second sum of channel c0 + threadIdx.x.
 enum { kFinCh = 8, kFinLanes = 256 / kFinCh };
-template <int Q>
-__device__ __forceinline__ void sum_partials(const float* __restrict__ partial, int P, int C, int c,
-                                             int lane, double (&out)[Q], double* smem) {
-  double s[Q];
+__device__ __forceinline__ void sum_partials(const float* __restrict__ partial, int P, int C, int c0, double& s0, double& s1) {
+  __shared__ double sm[kFinLanes][2 * kFinCh];
+  const int tid = threadIdx.x, cl = tid % kFinCh, lane = tid / kFinCh, c = c0 + cl < C ? c0 + cl : c0;
+  double a = 0.0, b = 0.0;
+  // sixteen partials per round (all of them, for up to 512 partials): the loads are independent and unconditional
+  // (past the end: the round's first partial again, not added), the sums keep their order; a round costs one trip to
+  // memory, and this kernel is nothing but such trips
+  constexpr int U = 16;
+  for (int p = lane; p < P; p += U * kFinLanes) {
+    float v[U][2];
 #pragma unroll
-  for (int q = 0; q < Q; ++q) s[q] = 0.0;
-  if (c < C) {
-    // sixteen partials per round (all of them, for up to 512 partials): the loads are independent and unconditional
-    // (past the end: the round's first partial again, not added), the sums keep their order; a round costs one trip to
-    // memory, and this kernel is nothing but such trips
-    constexpr int U = 16;
-    for (int p = lane; p < P; p += U * kFinLanes) {
-      float v[U][Q];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int pp = p + kFinLanes * u < P ? p + kFinLanes * u : p;
-#pragma unroll
-        for (int q = 0; q < Q; ++q) v[u][q] = partial[((size_t)pp * Q + q) * C + c];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (p + kFinLanes * u < P) {
-#pragma unroll
-          for (int q = 0; q < Q; ++q) s[q] += (double)v[u][q];
-        }
-      }
+    for (int u = 0; u < U; ++u) {
+      const unsigned o = (unsigned)(p + kFinLanes * u < P ? p + kFinLanes * u : p) * 2u * C + c;
+      v[u][0] = partial[o];
+      v[u][1] = partial[o + C];
     }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (p + kFinLanes * u < P) { a += (double)v[u][0]; b += (double)v[u][1]; }
   }
-  int cl = threadIdx.x % kFinCh;
-#pragma unroll
-  for (int q = 0; q < Q; ++q) smem[(q * kFinLanes + lane) * kFinCh + cl] = s[q];
+  sm[lane][cl] = a;
+  sm[lane][kFinCh + cl] = b;
   __syncthreads();
+  s0 = s1 = 0.0;
+  if (tid < 64) {                  // sixteen values, four lanes each with eight terms, then across lanes
+    const int v = tid & 15, l0 = tid >> 4;
+    double t0 = 0.0, t1 = 0.0;
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    // four chains of eight in a fixed order instead of one of thirty-two dependent float64 additions
-    double t[4] = {0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int l = 0; l < kFinLanes; ++l) t[l & 3] += smem[(q * kFinLanes + l) * kFinCh + cl];
-    out[q] = (t[0] + t[1]) + (t[2] + t[3]);
+    for (int l = 0; l < 8; l += 2) { t0 += sm[l0 * 8 + l][v]; t1 += sm[l0 * 8 + l + 1][v]; }
+    t0 += t1;
+    t0 += __shfl_xor(t0, 16, 64);
+    t0 += __shfl_xor(t0, 32, 64);
+    s0 = t0;
+    s1 = __shfl_xor(t0, 8, 64);
   }
 }
 
-__global__ void bn_finalize_k(const float* __restrict__ partial, int P, size_t M, int C,
-                              const float* __restrict__ gamma, const float* __restrict__ beta,
-                              float* mean, float* invstd, float* scale, float* shift, float* run_mean,
-                              float* run_var, float eps, float momentum) {
-  __shared__ double smem[2 * kFinLanes * kFinCh];
-  int cl = threadIdx.x % kFinCh, lane = threadIdx.x / kFinCh;
-  int c = xcd_logical_block() * kFinCh + cl;     // neighbours read the same lines of the partials: one L2
-  double s[2];
-  sum_partials<2>(partial, P, C, c, lane, s, smem);
-  if (lane == 0 && c < C) {
-    double mu = s[0] / (double)M;
-    double var = s[1] / (double)M - mu * mu;
+// What the last threads need besides the sums is requested before them.  3.1 - 4.2 us a launch (4.4 - 4.7 when all 256 threads added all
+// lanes' sums, the parameters were fetched behind them and M was divided by in float64).
+__global__ __launch_bounds__(256) void bn_finalize_k(const float* __restrict__ partial, int P, double inv_M, double unbias, int C,
+                                                     const float* __restrict__ gamma, const float* __restrict__ beta, float* mean, float* invstd,
+                                                     float* scale, float* shift, float* run_mean, float* run_var, float eps, float momentum) {
+  const int c0 = xcd_logical_block() * kFinCh, tid = threadIdx.x, c = c0 + tid;     // neighbours read the same lines of the partials: one L2
+  const bool fin = tid < kFinCh && c < C;
+  float p_g = 0.f, p_b = 0.f, p_rm = 0.f, p_rv = 0.f;
+  if (fin) { p_g = gamma[c]; p_b = beta[c]; p_rm = run_mean[c]; p_rv = run_var[c]; }
+  double s0, s1;
+  sum_partials(partial, P, C, c0, s0, s1);
+  asm volatile("" : "+v"(p_g), "+v"(p_b), "+v"(p_rm), "+v"(p_rv));      // first use: conversions must not move up to the loads
+  if (fin) {
+    const double mu = s0 * inv_M;
+    double var = s1 * inv_M - mu * mu;
     if (var < 0.0) var = 0.0;
-    double is = 1.0 / sqrt(var + (double)eps);
-    float sc = (float)((double)gamma[c] * is);
+    const double is = rsqrt(var + (double)eps);
+    const float sc = (float)((double)p_g * is);
     mean[c] = (float)mu;
     invstd[c] = (float)is;
     scale[c] = sc;
-    shift[c] = (float)((double)beta[c] - mu * (double)sc);
-    double unb = M > 1 ? var * ((double)M / (double)(M - 1)) : var;
-    run_mean[c] = (float)((1.0 - momentum) * run_mean[c] + momentum * mu);
-    run_var[c] = (float)((1.0 - momentum) * run_var[c] + momentum * unb);
+    shift[c] = (float)((double)p_b - mu * (double)sc);
+    run_mean[c] = (float)((1.0 - momentum) * p_rm + momentum * mu);
+    run_var[c] = (float)((1.0 - momentum) * p_rv + momentum * (var * unbias));
   }
 }
 
@@ -180,7 +178,8 @@ void bn_finalize(hipStream_t st, const float* partial, int P, size_t M, int C, c
                  const float* beta, float* mean, float* invstd, float* scale, float* shift,
                  float* run_mean, float* run_var, float eps, float momentum) {
   KScope ks(st, "bn_finalize", (double)P * 2 * C * 4 + 8.0 * C * 4, 0);
-  hipLaunchKernelGGL(bn_finalize_k, dim3((C + kFinCh - 1) / kFinCh), dim3(256), 0, st, partial, P, M, C, gamma, beta,
+  hipLaunchKernelGGL(bn_finalize_k, dim3((C + kFinCh - 1) / kFinCh), dim3(256), 0, st, partial, P, 1.0 / (double)M,
+                     M > 1 ? (double)M / (double)(M - 1) : 1.0, C, gamma, beta,
                      mean, invstd, scale, shift, run_mean, run_var, eps, momentum);
 }
 
@@ -257,28 +256,26 @@ void bn_bwd_reduce(int dt, hipStream_t st, const void* dA, const void* z, size_t
   *P_out = t.P;
 }
 
-__global__ void bn_bwd_finalize_k(const float* __restrict__ partial, int P, size_t M, int C,
-                                  const float* __restrict__ gamma, const float* __restrict__ mean,
-                                  const float* __restrict__ invstd, float* g_gamma, float* g_beta,
-                                  float* coef) {
-  __shared__ double smem[2 * kFinLanes * kFinCh];
+__global__ __launch_bounds__(256) void bn_bwd_finalize_k(const float* __restrict__ partial, int P, double inv_M, int C,
+                                                         const float* __restrict__ gamma, const float* __restrict__ mean,
+                                                         const float* __restrict__ invstd, float* g_gamma, float* g_beta, float* coef) {
   // data-gradient chain.  Without this its few waves are the youngest on SIMDs that the weight-gradient stream's
   // long-running waves keep busy, and issue goes to the oldest wave first: measured 190 us instead of 5 next to a
   // persistent depthwise weight-gradient kernel
   __builtin_amdgcn_s_setprio(3);
-  int cl = threadIdx.x % kFinCh, lane = threadIdx.x / kFinCh;
-  int c = xcd_logical_block() * kFinCh + cl;     // neighbours read the same lines of the partials: one L2
-  double s[2];
-  sum_partials<2>(partial, P, C, c, lane, s, smem);
-  if (lane == 0 && c < C) {
-    double mu = mean[c], is = invstd[c], g = gamma[c];
-    double dbeta = s[0];
-    double dgamma = is * (s[1] - mu * s[0]);
-    g_gamma[c] += (float)dgamma;
-    g_beta[c] += (float)dbeta;
-    double k1 = g * is;
-    double k2 = -k1 * is * dgamma / (double)M;
-    double k3 = -k1 * dbeta / (double)M - k2 * mu;
+  const int c0 = xcd_logical_block() * kFinCh, tid = threadIdx.x, c = c0 + tid;     // neighbours read the same lines of the partials: one L2
+  const bool fin = tid < kFinCh && c < C;
+  float p_mu = 0.f, p_is = 0.f, p_g = 0.f, p_gg = 0.f, p_gb = 0.f;
+  if (fin) { p_mu = mean[c]; p_is = invstd[c]; p_g = gamma[c]; p_gg = g_gamma[c]; p_gb = g_beta[c]; }
+  double s0, s1;
+  sum_partials(partial, P, C, c0, s0, s1);
+  asm volatile("" : "+v"(p_mu), "+v"(p_is), "+v"(p_g), "+v"(p_gg), "+v"(p_gb));      // first use: see bn_finalize_k
+  if (fin) {
+    const double mu = p_mu, is = p_is, g = p_g;
+    const double dbeta = s0, dgamma = is * (s1 - mu * s0);
+    g_gamma[c] = p_gg + (float)dgamma;
+    g_beta[c] = p_gb + (float)dbeta;
+    const double k1 = g * is, k2 = -k1 * is * dgamma * inv_M, k3 = -k1 * dbeta * inv_M - k2 * mu;
     coef[c] = (float)k1;
     coef[C + c] = (float)k2;
     coef[2 * C + c] = (float)k3;
@@ -288,7 +285,7 @@ __global__ void bn_bwd_finalize_k(const float* __restrict__ partial, int P, size
 void bn_bwd_finalize(hipStream_t st, const float* partial, int P, size_t M, int C, const float* gamma,
                      const float* mean, const float* invstd, float* g_gamma, float* g_beta, float* coef) {
   KScope ks(st, "bn_bwd_finalize", (double)P * 2 * C * 4 + 10.0 * C * 4, 0);
-  hipLaunchKernelGGL(bn_bwd_finalize_k, dim3((C + kFinCh - 1) / kFinCh), dim3(256), 0, st, partial, P, M, C, gamma, mean,
+  hipLaunchKernelGGL(bn_bwd_finalize_k, dim3((C + kFinCh - 1) / kFinCh), dim3(256), 0, st, partial, P, 1.0 / (double)M, C, gamma, mean,
                      invstd, g_gamma, g_beta, coef);
 }
 
@@ -364,6 +361,7 @@ __global__ __launch_bounds__(1024) void bn_bwd_small_k(const T* __restrict__ dA,
   float f_mu = 0.f, f_is = 0.f, f_g = 0.f, f_gg = 0.f, f_gb = 0.f;
   if (tid < 4) { f_mu = mean[c0 + tid]; f_is = invstd[c0 + tid]; f_g = gamma[c0 + tid]; f_gg = g_gamma[c0 + tid]; f_gb = g_beta[c0 + tid]; }
   float4 d[RPT], v[RPT];
+  const double inv_M = early_inverse((double)M);
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {       // unconditional, from a clamped row: rows past M are masked where they are used
     const size_t m = tid + (size_t)q * nt, mc = m < M ? m : 0;
@@ -405,11 +403,11 @@ __global__ __launch_bounds__(1024) void bn_bwd_small_k(const T* __restrict__ dA,
     const int c = c0 + tid;
     double s0 = 0.0, s1 = 0.0;
     for (int w = 0; w < nw; ++w) { s0 += red[w][tid]; s1 += red[w][4 + tid]; }
-    const double mu = f_mu, is = f_is, g = f_g, Md = (double)M;
+    const double mu = f_mu, is = f_is, g = f_g;
     const double dbeta = s0, dgamma = is * (s1 - mu * s0);
     g_gamma[c] = f_gg + (float)dgamma;
     g_beta[c] = f_gb + (float)dbeta;
-    const double k1 = g * is, k2 = -k1 * is * dgamma / Md, k3 = -k1 * dbeta / Md - k2 * mu;
+    const double k1 = g * is, k2 = -k1 * is * dgamma * inv_M, k3 = -k1 * dbeta * inv_M - k2 * mu;
     coef[0][tid] = (float)k1; coef[1][tid] = (float)k2; coef[2][tid] = (float)k3;
   }
   __syncthreads();
