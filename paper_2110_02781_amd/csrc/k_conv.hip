@@ -257,45 +257,85 @@ void conv_direct_dgrad(int dt, hipStream_t st, const void* dz, const void* w, co
 // Weight gradient of a small dense convolution: the input patches are written out once as a
 // matrix A[pixel][Kpad] (k = (tap, ci), zero padded to a multiple of 8, producer BatchNorm +
 // activation applied), then dW = dZ^T * A runs on the MFMA weight-gradient kernel.
+// A thread keeps one group of 8 columns and walks pixels: what a column is (tap, channel, offset) is decoded once per thread, the
+// pixel once per block in full and per thread relative to that, all eight loads are requested before the first is used.
+// Bound by vector instructions and 2-byte gathers (it was a table read and two 64-bit products per value and four 64-bit divisions
+// per pixel).  224 x 224 x 3, batch 128, bfloat16: 59.9 -> 50.5 us; 32 x 32 x 3, batch 32, fp32: 5.4 -> 5.5 us, latency.
+struct Im2colArgs {
+  ConvGeom g;
+  size_t M;            // pixels
+  int KG, K, PPT, PB;  // column groups, columns in use, pixels the block writes at once / in all
+  FastDiv dKG, dC, dKw, dW, dH;
+  int fast;            // Hout and Wout small enough for dW, dH over the pixels of a block
+};
+
 template <typename T>
-__global__ void im2col_k(View in, ConvGeom g, int Kpad, T* __restrict__ out) {
-  // which tap and input channel column k of the matrix is: worked out once per block (two divisions per column)
-  // instead of once per element, packed as (row offset + 1) << 24 | column offset << 16 | channel; 0 = padding column
-  extern __shared__ uint32_t taps[];
-  const int KG = Kpad / 8, K = g.kh * g.kw * g.Cin;
-  for (int k = threadIdx.x; k < Kpad; k += blockDim.x) {
-    uint32_t t = 0;
-    if (k < K) {
-      const int tap = k / g.Cin, ci = k - tap * g.Cin, i = tap / g.kw, j = tap - i * g.kw;
-      t = ((uint32_t)(i + 1) << 24) | ((uint32_t)j << 16) | (uint32_t)ci;
-    }
-    taps[k] = t;
-  }
-  __syncthreads();
-  const size_t total = (size_t)g.N * g.Hout * g.Wout * KG;
-  for (size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (size_t)gridDim.x * blockDim.x) {
-    const int kg = (int)(idx % KG);
-    const size_t pix = idx / KG;
-    const int wo = (int)(pix % g.Wout);
-    const size_t r = pix / g.Wout;
-    const int ho = (int)(r % g.Hout), n = (int)(r / g.Hout);
-    const int h0 = ho * g.stride - g.ph, w0 = wo * g.stride - g.pw;
-    const size_t img = (size_t)n * g.Hin;
-    float v[8];
+__global__ __launch_bounds__(256) void im2col_k(View in, Im2colArgs a, T* __restrict__ out) {
+  const ConvGeom& g = a.g;
+  const size_t p0 = (size_t)blockIdx.x * a.PB;
+  const int pl0 = a.KG <= 256 ? (int)a.dKG.div(threadIdx.x) : 0;
+  if (pl0 >= a.PPT) return;
+  const int np = a.M - p0 < (size_t)a.PB ? (int)(a.M - p0) : a.PB;
+  const size_t hw = (size_t)g.Hout * g.Wout;
+  const int n0 = (int)(a.M >> 32 ? p0 / hw : (uint32_t)p0 / (uint32_t)hw);      // a 64-bit division ahead of the first load is a tenth of a short launch
+  const int r0 = (int)(p0 - n0 * hw);
+  const int ho0 = r0 / g.Wout, wo0 = r0 - ho0 * g.Wout;
+  const T* z = reinterpret_cast<const T*>(in.z);
+  for (int kg = (int)threadIdx.x - pl0 * a.KG; kg < a.KG; kg += 256) {       // one turn unless there are more than 256 groups
+    int di[8], dj[8], ch[8];
+    ptrdiff_t off[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const uint32_t t = taps[kg * 8 + e];
-      const int hi = h0 + (int)(t >> 24) - 1, wi = w0 + (int)((t >> 16) & 0xffu), ci = (int)(t & 0xffffu);
-      float x = 0.f;
-      if (t != 0 && hi >= 0 && hi < g.Hin && wi >= 0 && wi < g.Win)
-        x = view_at<T>(in, ((img + hi) * g.Win + wi) * g.Cin + ci, ci);
-      v[e] = x;
+      const int k = kg * 8 + e, tap = (int)a.dC.div(k), ci = k - tap * g.Cin, i = (int)a.dKw.div(tap), j = tap - i * g.kw;
+      di[e] = k < a.K ? i : 1 << 30;                                          // a padding column lies outside every image
+      dj[e] = j;
+      ch[e] = k < a.K ? ci : 0;
+      off[e] = ((ptrdiff_t)i * g.Win + j) * g.Cin + ci;
     }
-    store8(out + idx * 8, v);
+    for (int pl = pl0; pl < np; pl += a.PPT) {
+      const uint32_t t = (uint32_t)(wo0 + pl);
+      const int dr = (int)(a.fast ? a.dW.div(t) : t / (uint32_t)g.Wout), wo = (int)t - dr * g.Wout;
+      const uint32_t hh = (uint32_t)(ho0 + dr);
+      const int dn = (int)(a.fast ? a.dH.div(hh) : hh / (uint32_t)g.Hout), ho = (int)hh - dn * g.Hout;
+      const int h0 = ho * g.stride - g.ph, w0 = wo * g.stride - g.pw;
+      const ptrdiff_t base = (((ptrdiff_t)(n0 + dn) * g.Hin + h0) * g.Win + w0) * g.Cin;
+      T raw[8];
+      bool ok[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        ok[e] = (uint32_t)(h0 + di[e]) < (uint32_t)g.Hin && (uint32_t)(w0 + dj[e]) < (uint32_t)g.Win;
+        raw[e] = z[ok[e] ? base + off[e] : 0];
+      }
+      float v[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        float x = to_f32(raw[e]);
+        if (in.scale) x = round_to<T>(act_apply(fmaf(x, in.scale[ch[e]], in.shift[ch[e]]), in.act));
+        v[e] = ok[e] ? x : 0.f;
+      }
+      store8(out + ((p0 + pl) * a.KG + kg) * 8, v);
+    }
   }
 }
 
 static int direct_kpad(const ConvGeom& g) { return (g.kh * g.kw * g.Cin + 7) / 8 * 8; }
+
+static void write_patches(int dt, hipStream_t st, HView in, const ConvGeom& g, void* out) {
+  Im2colArgs a{};
+  a.g = g;
+  a.M = (size_t)g.N * g.Hout * g.Wout;
+  a.K = g.kh * g.kw * g.Cin;
+  a.KG = direct_kpad(g) / 8;
+  a.PPT = a.KG <= 256 ? 256 / a.KG : 1;
+  // up to 8 pixels a thread, fewer where that would leave less than 2048 blocks (8 per CU)
+  const size_t per = a.M / ((size_t)a.PPT * 2048);
+  a.PB = a.PPT * (per < 1 ? 1 : per > 8 ? 8 : (int)per);
+  a.dKG = FastDiv::of(a.KG); a.dC = FastDiv::of(g.Cin); a.dKw = FastDiv::of(g.kw); a.dW = FastDiv::of(g.Wout); a.dH = FastDiv::of(g.Hout);
+  // the reciprocal is exact while dividend x divisor stays under 2^32; a block has at most 2048 pixels
+  a.fast = g.Wout <= 60000 && g.Hout <= 60000;
+  const View v{in.z, in.scale, in.shift, in.act};
+  FTP_DISPATCH(dt, hipLaunchKernelGGL(im2col_k<T>, dim3((unsigned)((a.M + a.PB - 1) / a.PB)), dim3(256), 0, st, v, a, (T*)out));
+}
 
 size_t conv_direct_im2col_elems(const ConvGeom& g) { return (size_t)g.N * g.Hout * g.Wout * direct_kpad(g); }
 
@@ -307,13 +347,10 @@ void conv_direct_wgrad(int dt, hipStream_t st, const void* dz, HView in, const C
                        float* g_w, bool patches_ready) {
   const int Kpad = direct_kpad(g), K = g.kh * g.kw * g.Cin;
   const size_t M = (size_t)g.N * g.Hout * g.Wout;
-  View v{in.z, in.scale, in.shift, in.act};
   if (!patches_ready) {
     const double es = dt == 0 ? 4.0 : 2.0;
     KScope ks(st, "im2col", ((double)g.N * g.Hin * g.Win * g.Cin + (double)M * Kpad) * es, 0, (long)M, Kpad, g.Cout);
-    size_t nvec = M * (Kpad / 8);
-    unsigned grid = (unsigned)((nvec + 255) / 256 > 65536 ? 65536 : (nvec + 255) / 256);
-    FTP_DISPATCH(dt, hipLaunchKernelGGL(im2col_k<T>, dim3(grid), dim3(256), (size_t)Kpad * sizeof(uint32_t), st, v, g, Kpad, (T*)im2col));
+    write_patches(dt, st, in, g, im2col);
   }
   pw_wgrad(dt, st, dz, HView{im2col, nullptr, nullptr, 0}, M, Kpad, g.Cout, ws, g_w, K);
 }
@@ -340,13 +377,10 @@ void conv_direct_fwd_gemm(int dt, hipStream_t st, HView in, const void* w, const
                           float* stats, int* P_out) {
   const int Kpad = direct_kpad(g), K = g.kh * g.kw * g.Cin;
   const size_t M = (size_t)g.N * g.Hout * g.Wout;
-  View v{in.z, in.scale, in.shift, in.act};
   {
     const double es = dt == 0 ? 4.0 : 2.0;
     KScope ks(st, "im2col", ((double)g.N * g.Hin * g.Win * g.Cin + (double)M * Kpad) * es, 0, (long)M, Kpad, g.Cout);
-    size_t nvec = M * (Kpad / 8);
-    unsigned grid = (unsigned)((nvec + 255) / 256 > 65536 ? 65536 : (nvec + 255) / 256);
-    FTP_DISPATCH(dt, hipLaunchKernelGGL(im2col_k<T>, dim3(grid), dim3(256), (size_t)Kpad * sizeof(uint32_t), st, v, g, Kpad, (T*)im2col));
+    write_patches(dt, st, in, g, im2col);
     FTP_DISPATCH(dt, hipLaunchKernelGGL(pad_rows_k<T>, dim3((g.Cout * Kpad + 255) / 256), dim3(256), 0, st, (const T*)w, g.Cout, K,
                                         Kpad, (T*)wpad));
   }
@@ -392,13 +426,10 @@ void conv_direct_dgrad_gemm(int dt, hipStream_t st, const void* dz, const void* 
   const ConvGeom d = dgrad_as_forward(g);
   const int Kpad = direct_kpad(d);
   const size_t M = (size_t)g.N * g.Hin * g.Win;
-  View v{dz, nullptr, nullptr, 0};
   {
     const double es = dt == 0 ? 4.0 : 2.0;
     KScope ks(st, "im2col", ((double)g.N * g.Hout * g.Wout * g.Cout + (double)M * Kpad) * es, 0, (long)M, Kpad, g.Cin);
-    size_t nvec = M * (Kpad / 8);
-    unsigned grid = (unsigned)((nvec + 255) / 256 > 65536 ? 65536 : (nvec + 255) / 256);
-    FTP_DISPATCH(dt, hipLaunchKernelGGL(im2col_k<T>, dim3(grid), dim3(256), (size_t)Kpad * sizeof(uint32_t), st, v, d, Kpad, (T*)im2col));
+    write_patches(dt, st, HView{dz, nullptr, nullptr, 0}, d, im2col);
     FTP_DISPATCH(dt, hipLaunchKernelGGL(dgrad_weights_k<T>, dim3((g.Cin * Kpad + 255) / 256), dim3(256), 0, st, (const T*)w, g.Cout,
                                         g.kh, g.kw, g.Cin, Kpad, (T*)wscratch));
   }
