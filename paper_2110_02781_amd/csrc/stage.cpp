@@ -475,7 +475,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   }
   for (int i = 0; i < 5; ++i)
     if (!(s->defers && (i == 2 || i == 4)) && (rc = dev_alloc(&s->gbuf[i], max_act))) { stage_free(s); return rc; }
-  if (!s->defers) {
+  {
     hipError_t e = hipStreamCreateWithFlags(&s->side, hipStreamNonBlocking);     // default priority
     for (int i = 0; i < 3 && e == hipSuccess; ++i) {
       e = hipEventCreateWithFlags(&s->ev_fork[i], hipEventDisableTiming);
