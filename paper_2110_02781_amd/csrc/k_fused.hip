@@ -335,7 +335,10 @@ struct WgTrArgs {
   int K, N, itiles, jtiles;
 };
 
-template <bool VIEW>
+// SUM64: the sums of every 64 rows meet in float64.  With many layers in a launch a block takes many more rows than it would alone
+// (wg_tr_plan), and one fp32 chain over all of them was up to 2.5 times further from the exact product (2-norm, bfloat16; 25088 rows,
+// 96 -> 96 in twelve layers: 6.3e-8 layer by layer, 1.3e-7 together in one chain, 5.4e-8 like this).
+template <bool VIEW, bool SUM64>
 __device__ __forceinline__ void pw_wgrad_tr_body(const WgTrArgs& p, const int lb) {
   constexpr int LDN = kWgN + 8, LDK = kWgK + 8;
   __shared__ __attribute__((aligned(16))) bf16_t sZ[2][kWgRows * LDN];
@@ -400,6 +403,14 @@ __device__ __forceinline__ void pw_wgrad_tr_body(const WgTrArgs& p, const int lb
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f4v_t{0.f, 0.f, 0.f, 0.f};
 
+  double tot[2][4][4];
+  if constexpr (SUM64)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tot[i][j][r] = 0.0;
   const int nchunks = (int)((me - mb + kWgRows - 1) / kWgRows);
   if (nchunks > 0) fetch(mb);
   for (int ch = 0; ch < nchunks; ++ch) {
@@ -419,7 +430,21 @@ __device__ __forceinline__ void pw_wgrad_tr_body(const WgTrArgs& p, const int lb
         for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(an, bk[j], acc[i][j], 0, 0, 0);
       }
     }
+    if constexpr (SUM64)
+#pragma unroll
+      for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) { tot[i][j][r] += (double)acc[i][j][r]; acc[i][j][r] = 0.f; }
   }
+  if constexpr (SUM64)
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[i][j][r] = (float)tot[i][j][r];
   // register r of lane l: D[n = tile*16 + 4*G + r][k = j*16 + l16]
   float* out = p.ws + (size_t)split * N * K;
 #pragma unroll
@@ -436,20 +461,21 @@ __device__ __forceinline__ void pw_wgrad_tr_body(const WgTrArgs& p, const int lb
 }
 
 template <bool VIEW>
-__global__ __launch_bounds__(256) void pw_wgrad_tr_k(WgTrArgs p) { pw_wgrad_tr_body<VIEW>(p, xcd_logical_block()); }
+__global__ __launch_bounds__(256) void pw_wgrad_tr_k(WgTrArgs p) { pw_wgrad_tr_body<VIEW, false>(p, xcd_logical_block()); }
 
 // several layers in one launch, the layers' blocks one behind the other
 enum { kWgTrJobs = 24 };
 struct WgTrGroup { WgTrArgs job[kWgTrJobs]; int blk0[kWgTrJobs + 1]; int n; };
 template <bool VIEW>
-__global__ __launch_bounds__(256) void pw_wgrad_tr_group_k(WgTrGroup a) {
+__global__ __launch_bounds__(256, VIEW ? 2 : 3) void pw_wgrad_tr_group_k(WgTrGroup a) {
   int lb;
   const int ji = group_job(a.blk0, a.n, lb);
   const WgTrArgs& p = a.job[ji];
-  if ((size_t)(lb / (p.itiles * p.jtiles)) * p.mchunk < p.M) pw_wgrad_tr_body<VIEW>(p, lb);
+  if ((size_t)(lb / (p.itiles * p.jtiles)) * p.mchunk < p.M) pw_wgrad_tr_body<VIEW, true>(p, lb);
 }
 
-// share: how many layers share the launch (pw_wgrad_tr_group): together they need no more blocks than one alone
+// share: how many layers share the launch (pw_wgrad_tr_group).  The split, and with it the last bit of a gradient (the rounding of
+// the partials), depends on it, as it does on the storage type and the rows.
 static bool wg_tr_plan(size_t M, int K, int N, WgTrArgs* a, int* S, int share = 1) {
   if (K % 8 || N % 8 || M <= 2048 || N < 48) return false;     // a 128-column strip of a narrower dZ is mostly padding: measured slower
   a->itiles = (N + kWgN - 1) / kWgN;

@@ -93,3 +93,64 @@ def test_grouped_weight_gradients_add_in_short_chains(h, w, batch, K, N, layers,
     err, off = last_layers_gradient_error(h, w, batch, K, N, layers, dtype)
     print(f"  error {err:.3e} (bar {BAR[dtype]:.3e}), scale within {off:.1e}", flush=True)
     assert off <= 4e-7 and err <= BAR[dtype]
+
+
+# bfloat16 layers of 48 columns and more above 2048 rows: alone, two and seven in a launch, twelve, and thirty (two launches); one
+# column tile and several; with so many tiles that every block takes all rows; odd rows
+TRANSPOSED = [(14, 14, 32, 64, 384, 1), (14, 14, 32, 96, 576, 7), (14, 14, 32, 96, 96, 12), (14, 14, 128, 96, 96, 12), (7, 7, 128, 320, 1280, 12),
+              (28, 28, 16, 48, 48, 30), (13, 11, 37, 72, 136, 2), (47, 3, 15, 1280, 1536, 1)]
+
+
+@pytest.mark.parametrize("h,w,batch,K,N,layers", TRANSPOSED, ids=["-".join(map(str, c)) for c in TRANSPOSED])
+def test_transposing_weight_gradients_add_in_short_chains(h, w, batch, K, N, layers):
+    print(f"transposing weight gradient sums {h}x{w} batch {batch} {K}->{N} x{layers}", flush=True)
+    err, off = last_layers_gradient_error(h, w, batch, K, N, layers, "bf16")
+    print(f"  error {err:.3e} (bar {BAR['bf16']:.3e}), scale within {off:.1e}", flush=True)
+    assert off <= 4e-7 and err <= BAR["bf16"]
+
+
+@pytest.mark.parametrize("channels,h,w,batch", [([96] * 13, 14, 14, 16), ([56, 48] * 15 + [56], 13, 17, 11), ([24, 64] * 6 + [24], 15, 15, 12)],
+                         ids=["twelve", "thirty", "both_kernels"])
+def test_many_layers_together_give_the_gradients_of_each_alone(channels, h, w, batch):
+    """Every layer of a bfloat16 chain in one stage (weight gradients together at the end of the call) against a stage of its own on
+    the same tensors: the same products, so the gradients differ by the order of additions only.  Both are within the bar above
+    of the exact product, two independent errors of it apart at most."""
+    import torch
+    import paper_2110_02781_amd as P
+    B = P.binding
+    print(f"chain of {len(channels) - 1} layers {channels[:3]} {h}x{w} batch {batch}", flush=True)
+    units = [dict(kind=B.UNIT_CONV, cin=a, cout=b, kh=1, kw=1, stride=1, act=B.ACT_RELU6) for a, b in zip(channels, channels[1:])]
+    L = len(units)
+    model = P.model_create(units, h, w, channels[0], P.BF16)
+    params = P.models.init_unit_params(units, 72)
+    stages = [P.stage_create(model, 0, L, batch, 1)] + [P.stage_create(model, l, l + 1, batch, 1) for l in range(L)]
+    try:
+        for l in range(L):
+            P.stage_import_weights(stages[0], l, params[l])
+            P.stage_import_weights(stages[1 + l], l, params[l])
+        sp = torch.cuda.current_stream().cuda_stream
+        t = [torch.from_numpy(synth.normal(72, "x", (batch, h, w, channels[0])).astype(np.float32)).cuda().to(torch.bfloat16)]
+        for c in channels[1:]:
+            t.append(torch.empty(batch, h, w, c, dtype=torch.bfloat16, device="cuda"))
+        dy = torch.from_numpy(synth.normal(72, "dy", tuple(t[-1].shape)).astype(np.float32)).cuda().to(torch.bfloat16)
+        y, dx = torch.empty_like(t[-1]), torch.empty_like(t[0])
+        P.stage_forward(stages[0], 0, t[0], y, sp)
+        P.stage_backward(stages[0], 0, dy, dx, sp)
+        for l in range(L):
+            P.stage_forward(stages[1 + l], 0, t[l], t[l + 1], sp)
+        assert torch.equal(y, t[-1])
+        d = dy
+        for l in reversed(range(L)):
+            dl = torch.empty_like(t[l])
+            P.stage_backward(stages[1 + l], 0, d, dl, sp)
+            d = dl
+        assert torch.equal(dx, d)
+        for l in range(L):
+            n = P.model_unit_param_count(model, l)
+            a, b = (P.stage_export_grads(s, l, n).astype(np.float64) for s in (stages[0], stages[1 + l]))
+            err = np.linalg.norm(a - b) / np.linalg.norm(b)
+            assert err <= 2 ** 0.5 * BAR["bf16"], f"layer {l}: {err:.3e}"
+    finally:
+        for s in stages:
+            P.stage_destroy(s)
+        P.model_destroy(model)
