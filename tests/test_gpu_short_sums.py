@@ -62,3 +62,14 @@ def test_short_pointwise_products_add_in_short_chains(ci, co, hw, batch):
     # with few rows dz itself is far off: dy - mean(dy) - xhat mean(dy xhat) cancels, by about 1 / rows of its square
     if co <= 64 and batch * hw * hw >= 200:
         assert dx <= bar(16, 4) + 0.4 * 2.0 ** -24
+
+
+# convolutions along one axis above 2048 rows: chains of 64 terms, up to nine of them (64 -> 64 channels, 9 taps); two halves of the
+# reduction for 32 columns and fewer; channels off 8
+@pytest.mark.parametrize("ci,co,taps,w,batch", [(64, 64, 9, 256, 64), (64, 64, 5, 128, 17), (64, 32, 9, 100, 30), (24, 64, 9, 97, 40), (13, 40, 9, 64, 50)])
+def test_products_along_one_axis_add_in_short_chains(ci, co, taps, w, batch):
+    print(f"1-D products {ci}->{co} taps {taps} window {w} batch {batch}", flush=True)
+    z, dx = errors(unit(ci, co, taps), 1, w, batch)
+    chains = [(taps * ((c + 7) // 8 * 8) + 63) // 64 for c in (ci, co)]
+    print(f"  output {z:.3e} (bar {bar(64, chains[0]):.3e}), input gradient {dx:.3e} (bar {bar(64, chains[1]) + 0.4 * 2.0 ** -24:.3e})", flush=True)
+    assert z <= bar(64, chains[0]) and dx <= bar(64, chains[1]) + 0.4 * 2.0 ** -24
