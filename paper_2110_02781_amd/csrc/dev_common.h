@@ -83,7 +83,6 @@ __device__ __forceinline__ float act_lo(int act) { return act == ACT_NONE ? -INF
 __device__ __forceinline__ float act_hi(int act) { return act == ACT_RELU6 ? 6.f : INFINITY; }
 __device__ __forceinline__ float clamp_act(float y, float lo, float hi) { return __builtin_amdgcn_fmed3f(y, lo, hi); }
 __device__ __forceinline__ float act_apply(float y, int act) { return clamp_act(y, act_lo(act), act_hi(act)); }
-__device__ __forceinline__ float act_mask(float y, int act) { return (y > act_lo(act) && y < act_hi(act)) ? 1.f : 0.f; }
 
 // A tensor as its consumer sees it: value(m, c) = act(scale[c] * z[m][c] + shift[c]),
 // rounded to the storage type (what a materialised BatchNorm+activation output

@@ -134,6 +134,7 @@ __global__ __launch_bounds__(256) void conv1d_rows_k(Conv1dArgs p) {
   float psc = 0.f, psh = 0.f;
   const bool sums = DGRAD && p.stats != nullptr;
   if (sums && col_ok) { psc = p.prev.scale[col]; psh = p.prev.shift[col]; }
+  const float plo = act_lo(p.prev.act), phi = act_hi(p.prev.act);
   for (int it = it_beg; it < it_end; ++it) {
     const int m0 = it * TI;
     fetch_w(0);
@@ -250,7 +251,9 @@ __global__ __launch_bounds__(256) void conv1d_rows_k(Conv1dArgs p) {
       if (ok) out[(size_t)m * p.NC + col] = from_f32<T>(tot[r]);
       const float v = round_to<T>(tot[r]);              // sums are those of the values as stored
       if (sums) {
-        const float dy = ok ? v * act_mask(fmaf(zp[r], psc, psh), p.prev.act) : 0.f;
+        // chosen, not multiplied: a gradient that is not finite stays out of the sums of a channel that is off
+        const float yp = fmaf(zp[r], psc, psh);
+        const float dy = ok && (p.prev.act == ACT_NONE || (yp > plo && yp < phi)) ? v : 0.f;
         s1 += dy;
         s2 += ok ? dy * zp[r] : 0.f;
       } else {

@@ -45,3 +45,36 @@ def test_conv1d_edges(cins, cout, k, w, batch, dtype):
         pair.compare_unit_vectors("bn", tol)
     finally:
         pair.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_a_gradient_that_is_not_finite_stays_out_of_channels_that_are_off(dtype):
+    """Two convolutions above 2048 rows: the second's data gradient leaves the first's BatchNorm-backward sums.  An infinite output gradient
+    makes all of them NaN, but a channel whose ReLU is off everywhere passes none of it: its gradients are exactly zero."""
+    import numpy as np
+    import torch
+    import paper_2110_02781_amd as P
+    print(f"channel off, infinite gradient {dtype}", flush=True)
+    _, h = units([16, 24], 32, 5, L.ACT_RELU)
+    batch, w, off = 20, 128, 7
+    tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+    model = P.model_create(h, 1, w, 16, P.F32 if dtype == "f32" else P.BF16)
+    stage = P.stage_create(model, 0, 2, batch, 1)
+    try:
+        vecs = P.models.init_unit_params(h, 3)
+        vecs[0][24 * 5 * 16 + 24 + off] = -100.0                    # that channel's BatchNorm shift
+        for i, v in enumerate(vecs):
+            P.stage_import_weights(stage, i, v)
+        x = torch.from_numpy(synth.normal(22, "x", (batch, 1, w, 16)).astype(np.float32)).cuda().to(tdt)
+        dy = torch.from_numpy(synth.normal(22, "dy", (batch, 1, w, 32)).astype(np.float32)).cuda().to(tdt)
+        dy[3, 0, 40] = float("inf")
+        sp = torch.cuda.current_stream().cuda_stream
+        P.stage_forward(stage, 0, x, None, sp)
+        P.stage_backward(stage, 0, dy, None, sp)
+        g = P.stage_export_grads(stage, 0, vecs[0].size)
+        gw, gamma, beta = g[:24 * 80].reshape(24, 80), g[24 * 80:24 * 80 + 24], g[24 * 80 + 24:]
+        assert np.all(gw[off] == 0) and gamma[off] == 0 and beta[off] == 0, (gamma[off], beta[off])
+        assert not np.isfinite(gw[off - 1]).any()
+    finally:
+        P.stage_destroy(stage)
+        P.model_destroy(model)
