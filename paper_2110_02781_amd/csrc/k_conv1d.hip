@@ -660,6 +660,7 @@ static Conv1dWgArgs conv1d_wgrad_plan(const ConvGeom& g, int* P) {
 }
 
 size_t conv1d_wgrad_ws(const ConvGeom& g) {
+  if (conv1d_small(g)) return 0;
   int P;
   conv1d_wgrad_plan(g, &P);
   return (size_t)P * g.Cout * g.kw * g.Cin;

@@ -45,6 +45,10 @@ extern "C" const char* ftp_last_error(void) { return g_err; }
   } while (0)
 
 static const float kBnEps = 1e-5f, kBnMomentum = 0.1f;
+// What the stores of a stage that defers its weight gradients may take whatever its layers' sizes: bytes, floats.  (Emptying them
+// earlier costs launches that no longer fill the GPU: with 64 MB of partials and no more than two activations of dz a step at 224x224
+// was 1.5 - 2.5 % longer, fp32 batch 32 and 64, bfloat16 batch 32 and 128.)
+static const size_t kDzStore = (size_t)128 << 20, kPartStore = (size_t)32 << 20, kDzRing = (size_t)64 << 20;
 
 static inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 static inline int conv_out(int n, int k, int s, int p) { return (n + 2 * p - k) / s + 1; }
@@ -208,8 +212,7 @@ struct UnitPlan {
   size_t bn_off;                   // channel offset in the running-stat arrays
   std::vector<size_t> z_off;       // per sub: byte offset of z in the slot stash
   std::vector<size_t> st_off;      // per sub: float offset of mean|invstd|scale|shift in the slot stats
-  std::vector<size_t> dz_off;      // per sub: byte offset of its dz in the stage's dz store (stages that defer weight gradients)
-  std::vector<size_t> part_off;    // per sub: float offset of its partial weight gradients (likewise)
+  std::vector<size_t> part;        // per sub: floats of its partial weight gradients (stages that defer them)
   size_t out_off;                  // byte offset of the materialised unit output (if any)
   bool out_virtual;                // CONV unit whose output stays a view
   size_t in_mat_off;               // residual block fed by a view: materialised copy of its input
@@ -272,12 +275,13 @@ struct ftp_stage {
   bool bjoin_pending[2] = {false, false};
   int bset = 0;
   bool bset_open = false;      // a layer of the current unit has written into the set
-  // A stage that does not run weight gradients on a second stream (ftp_stage_create_ex says when) notes them instead: every
-  // layer's dz and partial sums have a place of their own, and the weight gradients of all layers run together at the end
-  // of the backward call, a few launches for all of them.
+  // A stage that does not run weight gradients on a second stream (ftp_stage_create_ex says when) notes them instead: the
+  // layers' dz and partial sums lie one behind the other in two stores, and the weight gradients of all layers run together at the
+  // end of the backward call, a few launches for all of them, or earlier where the next layer does not fit a store any more.
   bool defers = false;
   char* dz_store = nullptr;
   float* parts = nullptr;
+  size_t dz_cap = 0, dz_used = 0, part_cap = 0, part_used = 0;      // bytes, floats
   int n_tr = 0;                // layers that share the launch of the transposing weight gradient (pw_wgrad_group's share)
   std::vector<PwWgradJob> q_pw;
   std::vector<DwWgradJob> q_dw;
@@ -376,7 +380,8 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   s->es = m->dtype == FTP_F32 ? 4 : 2;
   if (hipGetDevice(&s->device) != hipSuccess) { ftp_set_error("stage_create: no HIP device"); delete s; return FTP_ERR_HIP; }
 
-  size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, dz_bytes = 0, part_floats = 0, n_convs = 0, z_values = 0;
+  size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, layer_ws = 0, n_convs = 0, z_values = 0;
+  size_t dz_bytes = 0, dz_max = 0, part_floats = 0, part_max = 0;
   int max_c = 8;
   auto act_bytes = [&](int H, int W, int C) { return align_up((size_t)batch * H * W * C * s->es, 256); };
   const UnitInfo& first = m->units[a];
@@ -406,16 +411,27 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       size_t M = (size_t)batch * g.Hout * g.Wout;
       const bool c1 = sb.type == SUB_DIRECT && conv1d_ok(g), patches = sb.type == SUB_DIRECT && !c1;
       size_t need = c1 ? conv1d_wgrad_ws(g) : patches ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_wgrad_ws(g) : pw_wgrad_ws(M, g.Cin, g.Cout);
-      if (need > ws_floats) ws_floats = need;
+      if (patches && need > ws_floats) ws_floats = need;
+      if (need > layer_ws) layer_ws = need;
       if (i == a && &sb == &u.subs[0]) s->ws_tail_floats = need;
-      size_t part = need;
+      size_t part = patches ? 0 : need;
+      bool dz_stored = true;             // a layer whose dz is not always stored still counts in dz_max
       if (sb.type == SUB_PW) {
         part = pw_wgrad_group_ws(m->dtype, M, g.Cin, g.Cout, s->n_tr);
-        if (m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > part) part = pw_bwd_fused_ws(M, g.Cin, g.Cout);
+        const size_t fused = m->dtype == FTP_BF16 ? pw_bwd_fused_ws(M, g.Cin, g.Cout) : 0;
+        if (fused > 0 && &sb == &u.subs[0]) dz_stored = false;
+        if (fused > part) part = fused;
+      } else if (sb.type == SUB_DW && u.subs.size() == 3 && dw_bwd_small_ok(g)) {
+        dz_stored = false;
+        part = 0;
       }
-      p.dz_off.push_back(dz_bytes); dz_bytes += zb;
+      if (zb > dz_max) dz_max = zb;
+      dz_bytes += dz_stored ? zb : 0;
       z_values += M * g.Cout;
-      p.part_off.push_back(part_floats); part_floats += patches ? 0 : align_up(part, 64);
+      part = align_up(part, 64);
+      p.part.push_back(part);
+      if (part > part_max) part_max = part;
+      part_floats += part;
       if (sb.type == SUB_PW && m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > s->ws_fused_floats)
         s->ws_fused_floats = pw_bwd_fused_ws(M, g.Cin, g.Cout);
       if (patches) ++s->n_direct;
@@ -452,6 +468,15 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   // 128 bfloat16 5.8 / 5.6 (16.5 M values); block 2 alone bfloat16 batch 16 0.25 / 0.20, 32 (16.8 M) 0.295 / 0.289, 64 (34 M)
   // 0.490 / 0.509; units 1-4 bfloat16 batch 32 1.03 / 0.88, 64 (22 M) 1.42 / 1.45; width 1.4 batch 128 bfloat16 (26 M) 7.4 / 7.5.
   s->defers = n_convs == 0 || z_values / n_convs < ((size_t)20 << 20);
+  if (s->defers) {
+    // The stores take every layer of the stage where that is little, and otherwise no more dz than a stage on two streams has
+    // buffers for.  MobileNetV2 at 224x224, bfloat16 batch 128: 4.16 GB (two streams 4.05, with places for all layers 4.97); fp32
+    // batch 32: 2.37 GB (2.25, 2.56); units 15 - 18, bfloat16 batch 64: 197 MB (147, 215).
+    const size_t two = 2 * max_act + 6 * (max_act < kDzRing ? max_act : kDzRing);
+    const size_t dz_lim = two > kDzStore ? two : kDzStore, part_lim = part_max > kPartStore ? part_max : kPartStore;
+    s->dz_cap = dz_bytes < dz_max ? dz_max : dz_bytes < dz_lim ? dz_bytes : dz_lim;
+    s->part_cap = part_floats < part_lim ? part_floats : part_lim;
+  } else if (layer_ws > ws_floats) ws_floats = layer_ws;
   s->stash_bytes = stash; s->stats_floats = stats; s->max_act_bytes = max_act; s->ws_floats = ws_floats; s->max_c = max_c;
 
   s->q_pw.reserve(n_convs); s->q_dw.reserve(n_convs); s->q_red.reserve(n_convs);      // a layer leaves at most one of each
@@ -488,14 +513,14 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     if (e != hipSuccess) { ftp_set_error("stage_create: stream/event creation failed: %s", hipGetErrorString(e)); stage_free(s); return FTP_ERR_HIP; }
   }
   if (!s->defers) {
-    s->dzring_bytes = max_act < ((size_t)64 << 20) ? max_act : ((size_t)64 << 20);
+    s->dzring_bytes = max_act < kDzRing ? max_act : kDzRing;
     for (int i = 0; i < 6; ++i)
       if ((rc = dev_alloc(&s->dzring[i], s->dzring_bytes))) { stage_free(s); return rc; }
   }
   if ((rc = dev_alloc(&s->bn_part, (size_t)kBnPartials * 2 * max_c * 4)) || (rc = dev_alloc(&s->coef, (size_t)3 * max_c * 4)) ||
       (rc = dev_alloc(&s->ws, ws_floats * 4)) || (rc = dev_alloc(&s->row_loss, (size_t)batch * 4))) { stage_free(s); return rc; }
   if (s->im2col_elems && (rc = dev_alloc(&s->im2col, s->im2col_elems * s->es))) { stage_free(s); return rc; }
-  if (s->defers && ((rc = dev_alloc(&s->dz_store, dz_bytes)) || (rc = dev_alloc(&s->parts, part_floats * 4)))) { stage_free(s); return rc; }
+  if (s->defers && ((rc = dev_alloc(&s->dz_store, s->dz_cap)) || (rc = dev_alloc(&s->parts, s->part_cap * 4)))) { stage_free(s); return rc; }
   if (!s->defers && s->ws_fused_floats && (rc = dev_alloc(&s->ws_fused, s->ws_fused_floats * 4))) { stage_free(s); return rc; }
   if (!s->defers && s->ws_tail_floats && s->n_direct <= 1 &&
       (rc = dev_alloc(&s->ws_tail, s->ws_tail_floats * 4))) { stage_free(s); return rc; }
@@ -940,10 +965,26 @@ static bool stage_overlaps(const ftp_stage* s) { return s->prof == nullptr && st
 
 static int join_side(ftp_stage* s, hipStream_t st);
 static int flush_unit_fork(ftp_stage* s, hipStream_t st);
+static void run_noted(ftp_stage* s, hipStream_t st);
 
+// Places for one layer's dz (bytes; 0: none) and partial weight gradients in the stores of a stage that defers.  Both at once: where
+// one does not fit, what is noted so far runs and the stores start again, and nothing not yet noted may lie in them then.
+struct Places { void* dz; float* part; };
+static Places take_places(ftp_stage* s, size_t dz_bytes, size_t part_floats, hipStream_t st) {
+  if (s->dz_used + dz_bytes > s->dz_cap || s->part_used + part_floats > s->part_cap) run_noted(s, st);
+  const Places at{s->dz_store + s->dz_used, s->parts + s->part_used};
+  s->dz_used += dz_bytes;
+  s->part_used += part_floats;
+  return at;
+}
+static size_t dz_size(const ftp_stage* s, const Sub& sb) {
+  return align_up((size_t)s->batch * sb.g.Hout * sb.g.Wout * sb.g.Cout * s->es, 256);
+}
+
+// part: BWD_FROM_DZ in a stage that defers, where the caller has taken the layer's places
 static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, const void* dA, HView in, HView out,
                         void* dIn, const void* res, const WeightSet& W, hipStream_t st, int mode = BWD_FULL,
-                        bool unit_fork = false) {
+                        bool unit_fork = false, float* part = nullptr) {
   const Sub& sb = p.info->subs[k];
   ConvGeom g = sb.g; g.N = s->batch;
   int C = g.Cout;
@@ -974,7 +1015,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       s->join_pending[2] = false;
     }
     pw_bwd_fused(st, dA, out, s->coef, conv_w(s, W, p.p_off + sb.w_off), in.z, res, M, g.Cin, g.Cout,
-                 s->defers ? s->parts + p.part_off[k] : s->ws_fused, s->grads + p.p_off + sb.w_off, dIn, aside ? s->side : st,
+                 s->defers ? take_places(s, 0, p.part[k], st).part : s->ws_fused, s->grads + p.p_off + sb.w_off, dIn, aside ? s->side : st,
                  aside ? s->ev_fork[2] : nullptr, s->defers ? &s->q_red : nullptr);
     if (aside) {
       HIP_TRY(hipEventRecord(s->ev_join[2], s->side));
@@ -986,8 +1027,11 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   const bool noted = s->defers && (sb.type != SUB_DIRECT || conv1d_ok(g));
   if (mode != BWD_FROM_DZ) {
     if (batched) dz = s->dzring[s->bset * 3 + (int)k];
-    else if (s->defers) dz = s->dz_store + p.dz_off[k];
-    else {
+    else if (s->defers) {
+      const Places at = take_places(s, dz_size(s, sb), p.part[k], st);
+      dz = at.dz;
+      part = at.part;
+    } else {
       b = (int)(s->n_sub_bwd++ & 1u);
       dz = s->gbuf[b ? 4 : 2];
     }
@@ -1052,7 +1096,6 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   }
   if (noted) {
     float* gw = s->grads + p.p_off + sb.w_off;
-    float* part = s->parts + p.part_off[k];
     const void* w = conv_w(s, W, p.p_off + sb.w_off);
     if (sb.type == SUB_PW) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
@@ -1125,6 +1168,7 @@ static void run_noted(ftp_stage* s, hipStream_t st) {
   dw_wgrad_group(s->dt, st, s->q_dw.data(), (int)s->q_dw.size(), &s->q_red);
   reduce_group(st, s->q_red.data(), (int)s->q_red.size());
   s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
+  s->dz_used = s->part_used = 0;         // what reads the stores is ahead of what this stream writes there next
 }
 
 // the weight gradients a unit has noted: one fork behind everything the unit has enqueued, all of them on the side
@@ -1188,6 +1232,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
     s->stash_owner = slot;
   }
   s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
+  s->dz_used = s->part_used = 0;
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
   const void* d = dy_dev ? dy_dev : sl.dlogits;     // gradient of the current unit's output (read only)
   int flip = 0;
@@ -1244,7 +1289,8 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
           const Sub& s0 = u.subs[0];
           const Sub& s1 = u.subs[1];
           // the depthwise layer's own BatchNorm backward happens inside too: its dz never reaches memory
-          void* dz1 = s->dz_store + p.dz_off[0];
+          const Places at = take_places(s, dz_size(s, s0), p.part[0], st);
+          void* dz1 = at.dz;
           float* st0 = sl.stats + p.st_off[0];
           float* st1 = sl.stats + p.st_off[1];
           BnBwdIn bo{tmp, v.sub_out[i][1], W.w32 + p.p_off + s1.gamma_off, st1, st1 + s1.g.Cout,
@@ -1252,7 +1298,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
           dw_bwd_small(s->dt, st, nullptr, bo, conv_w(s, W, p.p_off + s1.w_off), v.sub_out[i][0], gd, W.w32 + p.p_off + s0.gamma_off, st0,
                        st0 + s0.g.Cout, s->grads + p.p_off + s1.w_off, s->grads + p.p_off + s0.gamma_off,
                        s->grads + p.p_off + s0.beta_off, dz1);
-          if ((rc = sub_backward(s, sl, p, 0, dz1, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FROM_DZ))) return rc;
+          if ((rc = sub_backward(s, sl, p, 0, dz1, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FROM_DZ, false, at.part))) return rc;
         } else if (ns == 3) {
           if ((rc = sub_backward(s, sl, p, 1, tmp, v.sub_out[i][0], v.sub_out[i][1], tmp, nullptr, W, st, BWD_FULL, uf))) return rc;
           if ((rc = sub_backward(s, sl, p, 0, tmp, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FULL, uf))) return rc;

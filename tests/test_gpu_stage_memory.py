@@ -1,0 +1,88 @@
+"""Device memory of stages that run their weight gradients together at the end of the backward call: their stores of dz and partial sums
+are bounded, and a backward that does not fit them runs what it has noted and starts them again."""
+import numpy as np
+import pytest
+
+import synth
+from harness import TOL
+
+pytestmark = pytest.mark.gpu
+
+
+def stage_bytes(units, h, w, cin, batch, dtype, a=0, b=None):
+    import paper_2110_02781_amd as P
+    model = P.model_create(units, h, w, cin, P.F32 if dtype == "f32" else P.BF16)
+    stage = P.stage_create(model, a, b or len(units), batch, 1)
+    try:
+        return P.stage_device_bytes(stage)
+    finally:
+        P.stage_destroy(stage)
+        P.model_destroy(model)
+
+
+# MB of a stage that runs every weight gradient on a second stream as soon as its dz is there, with two dz buffers for all layers (and
+# six of up to 64 MB more for the large ones), and what running them together may cost on top: a large stage has its dz within as much,
+# a small one keeps all layers' (each is less than the 128 MB that the store may take in any case).
+TWO_STREAMS = [(1.0, 1000, 2, 224, 224, 128, "bf16", 0, None, 4045, 1.06), (1.0, 1000, 2, 224, 224, 32, "f32", 0, None, 2252, 1.06),
+               (1.4, 1000, 2, 224, 224, 32, "bf16", 0, None, 1862, 1.06), (1.0, 1000, 2, 224, 224, 64, "bf16", 15, 19, 147, 1.4),
+               (1.0, 10, 1, 32, 32, 32, "f32", 0, None, 222, 1.25), (1.0, 10, 1, 32, 32, 128, "f32", 0, None, 1067, 1.06)]
+
+
+@pytest.mark.parametrize("width,classes,stem,h,w,batch,dtype,a,b,mb,most", TWO_STREAMS, ids=["-".join(map(str, c[:9])) for c in TWO_STREAMS])
+def test_weight_gradients_together_cost_little_memory(width, classes, stem, h, w, batch, dtype, a, b, mb, most):
+    import paper_2110_02781_amd as P
+    n = stage_bytes(P.models.mobilenet_v2_units(width, classes, stem), h, w, 3, batch, dtype, a, b) / 1e6
+    print(f"{n:.0f} MB, on two streams {mb} MB", flush=True)
+    assert n <= most * mb
+
+
+@pytest.mark.parametrize("kind", ["pointwise", "along_one_axis", "blocks"])
+def test_stores_that_fill_up_change_no_gradient(kind):
+    """fp32 layers of 33 MB and more each: the stores are emptied several times in a backward.  Every layer's gradients against a stage of
+    that layer alone on the same tensors: bit for bit, or, along one axis, where the chain takes its BatchNorm sums from the data gradient
+    and a single layer from a pass of its own (another order of the same sums), within the fp32 tolerance."""
+    import torch
+    import paper_2110_02781_amd as P
+    B = P.binding
+    if kind == "pointwise":
+        h, w, batch, cs = 64, 64, 32, [64] * 16
+        units = [dict(kind=B.UNIT_CONV, cin=a, cout=b, kh=1, kw=1, stride=1, act=B.ACT_RELU6) for a, b in zip(cs, cs[1:])]
+    elif kind == "along_one_axis":
+        h, w, batch, cs = 1, 128, 1024, [16] + [64] * 14
+        units = [dict(kind=B.UNIT_CONV, cin=a, cout=b, kh=1, kw=5, stride=1, pad_h=0, pad_w=2, act=B.ACT_RELU) for a, b in zip(cs, cs[1:])]
+    else:
+        h, w, batch, cs = 28, 28, 64, [24] * 12
+        units = [dict(kind=B.UNIT_INVRES, cin=24, cout=24, stride=1, expand=6) for _ in range(11)]
+    print(f"stores that fill up: {kind}", flush=True)
+    L = len(units)
+    model = P.model_create(units, h, w, cs[0], P.F32)
+    params = P.models.init_unit_params(units, 74)
+    stages = [P.stage_create(model, 0, L, batch, 1)] + [P.stage_create(model, l, l + 1, batch, 1) for l in range(L)]
+    try:
+        for l in range(L):
+            P.stage_import_weights(stages[0], l, params[l])
+            P.stage_import_weights(stages[1 + l], l, params[l])
+        sp = torch.cuda.current_stream().cuda_stream
+        t = [torch.from_numpy(synth.normal(74, "x", (batch, h, w, cs[0])).astype(np.float32)).cuda()]
+        t += [torch.empty(batch, h, w, c, device="cuda") for c in cs[1:]]
+        dy = torch.from_numpy(synth.normal(74, "dy", tuple(t[-1].shape)).astype(np.float32)).cuda()
+        for rep in range(2):                                    # the second backward adds to what the first has left
+            P.stage_forward(stages[0], 0, t[0], None, sp)
+            P.stage_backward(stages[0], 0, dy, None, sp)
+            for l in range(L):
+                P.stage_forward(stages[1 + l], 0, t[l], t[l + 1], sp)
+            d = dy
+            for l in reversed(range(L)):
+                dl = torch.empty_like(t[l]) if l else None
+                P.stage_backward(stages[1 + l], 0, d, dl, sp)
+                d = dl
+            for l in range(L):
+                n = P.model_unit_param_count(model, l)
+                a, b = (P.stage_export_grads(s, l, n) for s in (stages[0], stages[1 + l]))
+                assert np.isfinite(b).all() and np.abs(b).max() > 0
+                err = np.linalg.norm(a.astype(np.float64) - b) / np.linalg.norm(b)
+                assert np.array_equal(a, b) if kind != "along_one_axis" else err <= TOL["f32"], f"layer {l}: {err:.3e}"
+    finally:
+        for s in stages:
+            P.stage_destroy(s)
+        P.model_destroy(model)
