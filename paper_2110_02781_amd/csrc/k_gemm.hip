@@ -1571,7 +1571,7 @@ void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int s
 }
 
 // ---- backward of a fully connected layer ------------------------------------------------------------------------
-// Latency only (a few tiles, every operand a few KB), so everything is one launch: blocks [0, nd) take 16 x 16 tiles of the
+// Latency only (a few tiles over operands that the caches hold), so everything is one launch: blocks [0, nd) take 16 x 16 tiles of the
 // data gradient, the others 16 x 16 tiles of g_w (and, in the first column of tiles, the bias gradient, whose terms pass through their
 // registers anyway); four wavefronts split the reduction.  The class count is arbitrary, so elements are loaded one by one.
 // Weight gradient, bias gradient, data gradient and the average's backward were four launches: 2.5 + 1.4 + 4.9 + 2.7 us for 8 x 64 -> 6
@@ -1659,8 +1659,12 @@ __global__ __launch_bounds__(256) void fc_bwd_k(const T* __restrict__ d, View in
   if (bias) g_b[i0 + threadIdx.x] = b_old + (bred[0][threadIdx.x] + bred[1][threadIdx.x] + bred[2][threadIdx.x] + bred[3][threadIdx.x]);
 }
 
-// a wavefront walks a quarter of the rows (weight gradient) and of the classes (data gradient), 32 and 64 to a trip
-int fc_bwd_ok(int B, int N, int K) { return B <= 512 && N <= 1024 && (size_t)N * K <= ((size_t)1 << 24); }
+// A wavefront walks a quarter of the rows (weight gradient) and of the classes (data gradient), 32 and 64 to a trip, and every tile fetches
+// its operands itself: from about 200 M products on the tiled kernels' launches are faster.  Forward and backward, us, separate launches / one,
+// fp32 (bfloat16 likewise): 512 x 64 -> 12 20 / 12, 32 x 1792 -> 1000 42 / 34, 128 x 1280 -> 1000 (164 M) 64 / 55, 512 x 384 -> 1000 (197 M)
+// 53 / 47, 128 x 1792 -> 1000 (229 M) 75 / 72 and 53 / 54, 512 x 4096 -> 100 (210 M) 120 / 129, 256 x 1280 -> 1000 (328 M) 73 / 80,
+// 512 x 1792 -> 1000 129 / 178.
+int fc_bwd_ok(int B, int N, int K) { return B <= 512 && N <= 1024 && (size_t)N * K <= ((size_t)1 << 24) && (size_t)B * N * K <= 200000000; }
 // the tiles write their 64-byte pieces position by position: for a few MB that is cheaper than a launch
 int fc_bwd_gap_ok(int B, int HW, int K) { return (size_t)B * HW * K <= ((size_t)1 << 20); }
 

@@ -26,10 +26,10 @@ def tail(k, classes, conv, gap):
 
 # (features, classes, batch, H, W, a convolution in front, an average): classes of one, off 4 and off 16, more than a round of 64 per
 # wavefront; batches of one, off 16, more than a round; average as the first unit (its own launch), behind a convolution (part of the
-# data gradient), too large for that; features that are still a view (1 x 1 images); a layer too large for the one launch
+# data gradient), too large for that; features that are still a view (1 x 1 images); layers too large for the one launch
 CASES = [(8, 1, 1, 2, 3, True, True), (24, 6, 5, 7, 1, True, True), (64, 17, 16, 4, 4, True, True), (40, 100, 33, 3, 5, True, True),
          (1280, 1000, 130, 1, 2, True, True), (72, 259, 512, 1, 1, True, False), (48, 10, 9, 5, 5, False, True), (56, 12, 20, 31, 32, True, True),
-         (128, 7, 70, 11, 13, True, True), (16, 1030, 12, 2, 2, True, True), (32, 9, 600, 1, 1, False, False)]
+         (128, 7, 70, 11, 13, True, True), (16, 1030, 12, 2, 2, True, True), (32, 9, 600, 1, 1, False, False), (400, 1000, 512, 1, 1, False, False)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -50,3 +50,25 @@ def test_fully_connected_backward_edges(k, classes, batch, h, w, conv, gap, dtyp
             pair.compare_unit_vectors("grads", tol, floor=1e-6)
     finally:
         pair.close()
+
+
+# fewer than 200 M products: one launch; more: a launch for each gradient, which were faster there (512 x 1792 -> 1000: 129 against 178 us)
+@pytest.mark.parametrize("batch,k,classes,one", [(128, 1280, 1000, True), (512, 384, 1000, True), (512, 400, 1000, False), (256, 1280, 1000, False)])
+def test_fully_connected_backward_takes_one_launch_where_it_is_faster(batch, k, classes, one):
+    import torch
+    import paper_2110_02781_amd as P
+    print(f"fc route {batch} x {k} -> {classes}", flush=True)
+    model = P.model_create(tail(k, classes, False, False)[1], 1, 1, k, P.F32)
+    stage = P.stage_create(model, 0, 1, batch, 1)
+    try:
+        x, dy = torch.zeros(batch, k, device="cuda"), torch.zeros(batch, classes, device="cuda")
+        sp = torch.cuda.current_stream().cuda_stream
+        P.stage_forward(stage, 0, x, None, sp)
+        torch.cuda.synchronize()
+        P.ktrace_begin()
+        P.stage_backward(stage, 0, dy, torch.empty_like(x), sp)
+        torch.cuda.synchronize()
+        assert any(r["name"] == "fc_bwd" for r in P.ktrace_end()) == one
+    finally:
+        P.stage_destroy(stage)
+        P.model_destroy(model)
