@@ -64,6 +64,24 @@ def assert_chained(report, workload):
             assert got <= 1.5 * yard + 1e-2, f"{workload}: {cls} is {got:.3e} from the rounding oracle, the oracles are {yard:.3e} apart"
 
 
+def launches(run):
+    """{kernel family: launches} of run()."""
+    import torch
+    import paper_2110_02781_amd as P
+    torch.cuda.synchronize()
+    P.ktrace_begin()
+    run()
+    torch.cuda.synchronize()
+    return {r["name"]: r["launches"] for r in P.ktrace_end()}
+
+
+def assert_two_streams(layers, backward):
+    """backward() is that of a stage that runs weight gradients on its second stream: it sums the partial weight gradients of each of at
+    least `layers` layers by themselves, where a stage that runs all weight gradients at the end of the call has a launch or two for all."""
+    n = launches(backward).get("reduce_partials", 0)
+    assert n >= layers > 2, f"{n} sums of partial weight gradients, {layers} layers: not on two streams"
+
+
 def unit_shapes(o_units, in_shape):
     """Input shape (H, W, C) of every unit, and the output shape of the last, from the oracle's model description."""
     shapes = [tuple(in_shape)]

@@ -10,7 +10,7 @@ from oracle import layers as L
 from oracle import models as OM
 from oracle.partition import solve_partition as oracle_solve
 from oracle.stage import one_f_one_b_order
-from harness import Pair, TOL, CHAINED_BAR, unit_shapes, assert_close, rel_err, unitwise_check, unit_compare, chained_report, assert_chained
+from harness import Pair, TOL, CHAINED_BAR, unit_shapes, assert_close, rel_err, unitwise_check, unit_compare, chained_report, assert_chained, assert_two_streams
 
 pytestmark = pytest.mark.gpu
 
@@ -450,24 +450,25 @@ def test_recomputation_along_the_one_f_one_b_schedule(dtype):
 
 
 def test_recomputation_on_a_two_stream_stage_is_bit_identical():
-    """A stage large enough to run its weight gradients on the second stream (largest activation 58 MB), two
+    """A stage large enough to run its weight gradients on the second stream (22 M values per convolution output), two
     micro-batches in flight: the recomputing stage's second forward runs in front of each backward while nothing
     of the previous backward is pending, so it must leave exactly the weights of the stage that keeps everything."""
     import torch
     import paper_2110_02781_amd as P
-    print("recomputation, 224x224 w1.4 batch 16 bf16, two slots", flush=True)
+    batch = 128
+    print(f"recomputation, 224x224 w1.4 batch {batch} bf16, two slots", flush=True)
     units = P.models.mobilenet_v2_units(1.4, 1000, 2)
     model = P.model_create(units, 224, 224, 3, P.BF16)
     L = P.model_num_units(model)
     params = P.models.init_unit_params(units, 71)
-    stages = [P.stage_create(model, 0, L, 16, 2, f) for f in (0, P.STAGE_RECOMPUTE)]
+    stages = [P.stage_create(model, 0, L, batch, 2, f) for f in (0, P.STAGE_RECOMPUTE)]
     try:
         dev = torch.device("cuda:0")
         for st in stages:
             for i in range(L):
                 P.stage_import_weights(st, i, params[i])
-        xs = [torch.from_numpy(synth.normal(71, f"x{k}", (16, 224, 224, 3)).astype(np.float32)).to(dev).to(torch.bfloat16) for k in range(2)]
-        ls = [torch.from_numpy(synth.labels(71, f"l{k}", 16, 1000).astype(np.int32)).to(dev) for k in range(2)]
+        xs = [torch.from_numpy(synth.normal(71, f"x{k}", (batch, 224, 224, 3)).astype(np.float32)).to(dev).to(torch.bfloat16) for k in range(2)]
+        ls = [torch.from_numpy(synth.labels(71, f"l{k}", batch, 1000).astype(np.int32)).to(dev) for k in range(2)]
         loss = torch.zeros(1, dtype=torch.float32, device=dev)
         sp = torch.cuda.current_stream().cuda_stream
         assert P.stage_device_bytes(stages[1]) < P.stage_device_bytes(stages[0])
@@ -477,7 +478,10 @@ def test_recomputation_on_a_two_stream_stage_is_bit_identical():
                     P.stage_forward(st, k, xs[k], None, sp)
                     P.stage_loss(st, k, ls[k], loss, sp)
                 for k in range(2):
-                    P.stage_backward(st, k, None, None, sp)
+                    if rep == 0 and k == 0:
+                        assert_two_streams(30, lambda: P.stage_backward(st, 0, None, None, sp))
+                    else:
+                        P.stage_backward(st, k, None, None, sp)
                 P.stage_update(st, 0.005, 0.9, 4e-5, sp)
             torch.cuda.synchronize()
             for i in range(L):
@@ -533,8 +537,8 @@ def test_training_step_replays_from_a_hip_graph(case):
         _, units = small_net()
         shape, batch, dt, tdt, classes = (9, 11, 3), 4, P.F32, torch.float32, 10
     else:
-        units = P.models.mobilenet_v2_units(1.4, 1000, 2)          # largest activation 58 MB: the side stream is on
-        shape, batch, dt, tdt, classes = (224, 224, 3), 16, P.BF16, torch.bfloat16, 1000
+        units = P.models.mobilenet_v2_units(1.4, 1000, 2)          # 22 M values per convolution output: the side stream is on
+        shape, batch, dt, tdt, classes = (224, 224, 3), 128, P.BF16, torch.bfloat16, 1000
     dev = torch.device("cuda:0")
     model = P.model_create(units, *shape, dt)
     L = P.model_num_units(model)
@@ -561,7 +565,11 @@ def test_training_step_replays_from_a_hip_graph(case):
             return [np.array(P.stage_export_weights(stages[k], i, P.model_unit_param_count(model, i)), copy=True)
                     for i in range(L) if P.model_unit_param_count(model, i)]
 
-        step(0); step(1)                                  # first launches (code objects load) stay outside the capture
+        step(0)
+        if case == "two_streams_bf16":
+            assert_two_streams(30, lambda: step(1))
+        else:
+            step(1)                                       # first launches (code objects load) stay outside the capture
         stream.synchronize()
         graph = torch.cuda.CUDAGraph()
         with torch.cuda.graph(graph, stream=stream):
@@ -637,7 +645,7 @@ def test_profiled_unit_costs_add_up_to_the_batch_time(case):
     if case == "one_stream_f32":
         units, shape, batch, dt, tdt, classes = P.models.mobilenet_v2_units(1.0, 10, 1), (32, 32, 3), 32, P.F32, torch.float32, 10
     else:
-        units, shape, batch, dt, tdt, classes = P.models.mobilenet_v2_units(1.0, 1000, 2), (224, 224, 3), 32, P.BF16, torch.bfloat16, 1000
+        units, shape, batch, dt, tdt, classes = P.models.mobilenet_v2_units(1.4, 1000, 2), (224, 224, 3), 128, P.BF16, torch.bfloat16, 1000
     print(f"profile_layers vs stage_timing: {case}", flush=True)
     dev = torch.device("cuda:0")
     model = P.model_create(units, *shape, dt)
@@ -657,6 +665,8 @@ def test_profiled_unit_costs_add_up_to_the_batch_time(case):
             P.stage_loss(stage, 0, labels, loss, sp)
             P.stage_backward(stage, 0, None, None, sp)
             P.stage_update(stage, 0.001, 0.9, 0.0, sp)
+        if case == "two_streams_bf16":
+            assert_two_streams(30, step)
         for _ in range(5):
             step()
         torch.cuda.synchronize()
@@ -795,9 +805,9 @@ def test_config4_middle_stage_of_4way_split_bf16(costs_from):
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 def test_config5_shapes_at_reduced_batch(dtype):
     """MobileNetV2 w1.4, 224x224, 1000 classes, whole model as one stage; batch 4 (float: 6) instead of
-    128 so that the float64 oracle finishes in seconds (same spatial and channel shapes).  At batch 6 in float the
-    largest activation is 43 MB: the stage runs its weight gradients on the second stream, as at full size, and the
-    whole step (a mix of forked layers and layers too short to fork) is compared with the oracle.  bfloat16: the
+    128 so that the float64 oracle finishes in seconds (same spatial and channel shapes; at these batches the
+    weight gradients run at the end of the backward call, at full size on a second stream).  float: the whole step is
+    compared with the oracle.  bfloat16: the
     whole step on its own activations is measured against both oracles, then every unit teacher-forced at 2e-2."""
     batch = 6 if dtype == "f32" else 4
     print(f"config 5 shapes, batch {batch}, {dtype}", flush=True)
