@@ -581,6 +581,41 @@ int conv1d_ok(const ConvGeom& g) {
 
 static bool conv1d_small(const ConvGeom& g) { return (size_t)g.N * g.Win <= kC1Small; }
 
+// Which of these layers run here, and which through patch matrices and the pointwise kernels.  Those multiply bfloat16 on its own matrix
+// instructions, sixteen times the rate of the fp32 ones here, and walk narrow tensors with fewer instructions a row; what they pay is the
+// matrices: one in forward, which the weight gradient reads again if no layer behind has taken the buffer, one of dz, and launches that
+// layers here share with others.  A first layer (no data gradient) needs a single matrix.  A stage that forks has no buffer for
+// that of dz, and its direct data gradient is slower than all else.
+// Steps, us, patch matrices / here.  fp32: 64 -> 64, 5 taps, alone, 32768 rows 100 / 65; first layers alone 9 -> 32, 5 taps, 32768 50 / 55,
+// 131072 77 / 84, 8 -> 32 131072 77 / 73, 3 -> 64, 3 taps, 131072 85 / 80, 262144 107 / 114; chain 8 -> 8, 3 taps, 131072 138 / 137, 262144
+// 200 / 215.  bfloat16: chain 64 -> 64, 9 taps, 2304 rows 104 / 132, 8192 122 / 116, 32768 229 / 206, 7 taps, 131072 600 / 640; 48 -> 48,
+// 7 taps, 2304 91 / 105, 6144 98 / 106, 131072 485 / 549; 32 -> 64, 9 taps, 4096 99 / 102, 6144 107 / 103; chain 8 -> 8, 3 taps, 65536
+// 101 / 98, 131072 112 / 129, 1048576 350 / 670; 32 -> 32, 3 taps, 131072 190 / 174, 524288 522 / 580; first layers 9 -> 32, 5 taps, alone 2304
+// 36 / 38, 65536 48 / 67, in front of two more 16384 180 / 179, 65536 325 / 336; 3 -> 8, 3 taps, alone 8192 41 / 38, 16384 42 / 40,
+// 32768 42 / 46, 524288 76 / 162; 16 -> 16, 5 taps, in front of another 32768 99 / 93, 131072 157 / 157, 524288 390 / 437.
+int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks) {
+  const size_t M = (size_t)g.N * g.Win;
+  const int lo = g.Cin < g.Cout ? g.Cin : g.Cout, hi = g.Cin < g.Cout ? g.Cout : g.Cin;
+  const int K = g.kw * g.Cin, both = g.kw * (g.Cin + g.Cout), weights = K * g.Cout;
+  const bool odd = g.Cin % 8 != 0;                    // read value by value here
+  if (conv1d_small(g)) return 1;
+  if (first && dt == 0) {                             // the patch matrix of a narrow input is little to write
+    if (g.Cout > 32 ? odd && K <= 54 && M >= 200000 : (odd || alone) && K <= 45 && M >= 32768) return 0;
+    if (odd && g.Cin < 12 && K <= 81 && (g.Cout <= 32 || K >= 45) && M >= 131072) return 0;
+  }
+  if (first && dt == 1) {
+    if (K >= 280 && g.Cout <= 32 && M >= 8192) return 1;
+    if (alone && M < 8192) return odd ? K <= 40 : K <= 240 && weights <= 5000;
+    if (alone) return K <= 30 && M < 24576;
+    if (M >= (weights >= 10000 ? 8192u : odd ? 32768u : 98304u)) return 0;
+  }
+  if (forks) return 1;
+  if (dt == 0) return !(hi <= 8 && g.kw == 3 && M >= 200000);
+  if (M < 8192) return M > (size_t)128 * lo || weights < 10000;      // few tiles, each a long chain of fp32 products
+  if (lo >= 40) return M < (g.kw >= 7 ? 49152u : 98304u);           // bound by the fp32 products
+  return !(hi <= 2 * lo && both <= 192 && M >= (size_t)1700 * both);   // narrow: columns filled up to 32
+}
+
 static Conv1dArgs conv1d_args(const ConvGeom& g, bool dgrad) {
   Conv1dArgs a{};
   a.M = g.N * g.Win; a.W = g.Win; a.Cin = g.Cin; a.Cout = g.Cout; a.kw = g.kw;

@@ -165,6 +165,9 @@ void reduce_group(hipStream_t st, const ReduceJob* jobs, int n);
 // ---- 1 x kw convolutions, stride 1, same length, at most 64 channels (conv1d_ok): implicit GEMMs, no scratch but ws ----
 int conv1d_ok(const ConvGeom& g);
 int conv1d_small_ok(const ConvGeom& g);     // few rows
+// of the layers that are conv1d_ok: whether they run here or through patch matrices.  first: no data gradient is wanted, alone: the
+// stage's only convolution, forks: the stage runs weight gradients on a second stream
+int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks);
 // pend.partial != nullptr (few rows only): the BatchNorm of the input is still partial sums, not those in `stats`; finished here
 void conv1d_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, const void* w, const ConvGeom& g, void* z,
                 float* stats, int* P_out);

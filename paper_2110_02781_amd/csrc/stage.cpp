@@ -213,6 +213,7 @@ struct UnitPlan {
   std::vector<size_t> z_off;       // per sub: byte offset of z in the slot stash
   std::vector<size_t> st_off;      // per sub: float offset of mean|invstd|scale|shift in the slot stats
   std::vector<size_t> part;        // per sub: floats of its partial weight gradients (stages that defer them)
+  std::vector<char> axis;          // per sub: a convolution along one axis that the kernels for those run
   size_t out_off;                  // byte offset of the materialised unit output (if any)
   bool out_virtual;                // CONV unit whose output stays a view
   size_t in_mat_off;               // residual block fed by a view: materialised copy of its input
@@ -391,8 +392,17 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   for (int i = a; i < b; ++i)
     for (const Sub& sb : m->units[i].subs) {
       const size_t M = (size_t)batch * sb.g.Hout * sb.g.Wout;
+      z_values += M * sb.g.Cout;
+      ++n_convs;
       if (sb.type == SUB_PW && pw_wgrad_tr_ok(m->dtype, M, sb.g.Cin, sb.g.Cout) && pw_bwd_fused_ws(M, sb.g.Cin, sb.g.Cout) == 0) ++s->n_tr;
     }
+  // Two ways to keep weight gradients off the data-gradient chain: all of them at the end of the call, or each on a second
+  // stream as soon as its dz is there.  The second costs event calls and a division of the memory bandwidth, and pays only where
+  // single layers fill the GPU for long: from about 20 M values per convolution output on average.  A step at 224x224, ms,
+  // second stream / end of the call: whole network batch 32 fp32 4.9 / 4.0, 128 fp32 11.6 / 11.3, 32 bfloat16 (width 1.4) 4.0 / 3.2,
+  // 128 bfloat16 5.8 / 5.6 (16.5 M values); block 2 alone bfloat16 batch 16 0.25 / 0.20, 32 (16.8 M) 0.295 / 0.289, 64 (34 M)
+  // 0.490 / 0.509; units 1-4 bfloat16 batch 32 1.03 / 0.88, 64 (22 M) 1.42 / 1.45; width 1.4 batch 128 bfloat16 (26 M) 7.4 / 7.5.
+  s->defers = n_convs == 0 || z_values / n_convs < ((size_t)20 << 20);
   for (int i = a; i < b; ++i) {
     const UnitInfo& u = m->units[i];
     UnitPlan p;
@@ -409,7 +419,9 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       if (sb.g.Cout > max_c) max_c = sb.g.Cout;
       ConvGeom g = sb.g; g.N = batch;
       size_t M = (size_t)batch * g.Hout * g.Wout;
-      const bool c1 = sb.type == SUB_DIRECT && conv1d_ok(g), patches = sb.type == SUB_DIRECT && !c1;
+      const bool c1 = sb.type == SUB_DIRECT && conv1d_ok(g) && conv1d_pays(m->dtype, g, i == 0, n_convs == 1, !s->defers);
+      const bool patches = sb.type == SUB_DIRECT && !c1;
+      p.axis.push_back(c1);
       size_t need = c1 ? conv1d_wgrad_ws(g) : patches ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_wgrad_ws(g) : pw_wgrad_ws(M, g.Cin, g.Cout);
       if (patches && need > ws_floats) ws_floats = need;
       if (need > layer_ws) layer_ws = need;
@@ -427,7 +439,6 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       }
       if (zb > dz_max) dz_max = zb;
       dz_bytes += dz_stored ? zb : 0;
-      z_values += M * g.Cout;
       part = align_up(part, 64);
       p.part.push_back(part);
       if (part > part_max) part_max = part;
@@ -443,7 +454,6 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
         if (conv_direct_dgrad_gemm_w_elems(g) > ws_floats) ws_floats = conv_direct_dgrad_gemm_w_elems(g);
       }
     }
-    n_convs += u.subs.size();
     p.out_virtual = (u.d.kind == FTP_UNIT_CONV);
     p.out_off = 0;
     if (!p.out_virtual && u.d.kind != FTP_UNIT_LOSS) {
@@ -461,13 +471,6 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     if (u.d.kind == FTP_UNIT_LOSS) { s->has_loss = true; s->classes = u.inC; }
     s->plan.push_back(p);
   }
-  // Two ways to keep weight gradients off the data-gradient chain: all of them at the end of the call, or each on a second
-  // stream as soon as its dz is there.  The second costs event calls and a division of the memory bandwidth, and pays only where
-  // single layers fill the GPU for long: from about 20 M values per convolution output on average.  A step at 224x224, ms,
-  // second stream / end of the call: whole network batch 32 fp32 4.9 / 4.0, 128 fp32 11.6 / 11.3, 32 bfloat16 (width 1.4) 4.0 / 3.2,
-  // 128 bfloat16 5.8 / 5.6 (16.5 M values); block 2 alone bfloat16 batch 16 0.25 / 0.20, 32 (16.8 M) 0.295 / 0.289, 64 (34 M)
-  // 0.490 / 0.509; units 1-4 bfloat16 batch 32 1.03 / 0.88, 64 (22 M) 1.42 / 1.45; width 1.4 batch 128 bfloat16 (26 M) 7.4 / 7.5.
-  s->defers = n_convs == 0 || z_values / n_convs < ((size_t)20 << 20);
   if (s->defers) {
     // The stores take every layer of the stage where that is little, and otherwise no more dz than a stage on two streams has
     // buffers for.  MobileNetV2 at 224x224, bfloat16 batch 128: 4.16 GB (two streams 4.05, with places for all layers 4.97); fp32
@@ -719,7 +722,7 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
       *pend = BnPending{s->bn_part, P, M, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv};
       return;
     }
-  } else if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
+  } else if (p.axis[k]) {
     // the partials of the input's BatchNorm, if it is pending, are read by every block: this layer's go to the other half
     float* part = s->bn_part;
     if (pend && pend->partial == part) part += (size_t)kBnPartials / 2 * 2 * s->max_c;
@@ -1024,7 +1027,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     return FTP_OK;
   }
   // noted for the end of the backward call: dz stays where it is written until then
-  const bool noted = s->defers && (sb.type != SUB_DIRECT || conv1d_ok(g));
+  const bool noted = s->defers && (sb.type != SUB_DIRECT || p.axis[k]);
   if (mode != BWD_FROM_DZ) {
     if (batched) dz = s->dzring[s->bset * 3 + (int)k];
     else if (s->defers) {
@@ -1129,7 +1132,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     pw_bwd(s->dt, st, dz, w, res, in, M, g.Cin, g.Cout, s->ws, gw, dIn);
     return FTP_OK;
   }
-  if (sb.type == SUB_DIRECT && conv1d_ok(g)) {
+  if (p.axis[k]) {
     if (!overlap && dIn && conv1d_small_ok(g)) { conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn); return FTP_OK; }
     conv1d_wgrad(s->dt, ws, dz, in, g, wsp, gw, &s->q_red);
     reduce_group(ws, s->q_red.data(), (int)s->q_red.size());
@@ -1146,7 +1149,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     s->join_pending[b] = true;
   }
   if (dIn) {
-    if (sb.type == SUB_DIRECT && conv1d_ok(g)) run_conv1d_dgrad();
+    if (p.axis[k]) run_conv1d_dgrad();
     else if (sb.type == SUB_DIRECT) {
       // the scratch buffers are shared with the weight gradients: fine on one stream, but a stage that runs them on
       // the side stream keeps the direct kernel

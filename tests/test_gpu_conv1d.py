@@ -2,7 +2,7 @@
 import pytest
 
 import synth
-from harness import Pair, TOL, assert_close
+from harness import Pair, TOL, assert_close, launches
 from oracle import layers as L
 from oracle import models as OM
 
@@ -19,8 +19,9 @@ def units(cins, cout, k, act):
 
 
 # (channels of the chain's inputs, last cout, taps, window, batch).  Up to 2048 rows the 16 x 16 kernels, above them the row
-# tiles (128 x 32 or 64 x 64, weight gradient in pieces of 32 x 80): windows shorter than a tile, longer, odd and the shortest;
+# tiles (64 x 32 or 64 x 64, weight gradient in pieces of 32 x 80): windows shorter than a tile, longer, odd and the shortest;
 # channels off 8 and off 4; columns off 16 and 32; a last tile of one row; more row tiles than partials; each tap count.
+# In bfloat16 the wider of the first layers go through patch matrices: ROUTES has row tiles of that type.
 # A chain of two has the data gradient leave the backward sums of the BatchNorm in front (above 2048 rows).
 CASES = [([16], 8, 5, 16, 1), ([3], 24, 3, 17, 7), ([9], 40, 9, 50, 40), ([16], 32, 5, 128, 16), ([64], 64, 5, 131, 15),
          ([16], 32, 5, 683, 3), ([9], 32, 5, 37, 56), ([13], 24, 3, 16, 200), ([64], 40, 9, 97, 27), ([12, 40], 64, 5, 47, 61),
@@ -43,6 +44,61 @@ def test_conv1d_edges(cins, cout, k, w, batch, dtype):
         assert_close(dx, dxo, tol, "dx")
         pair.compare_unit_vectors("grads", tol, floor=1e-6)
         pair.compare_unit_vectors("bn", tol)
+    finally:
+        pair.close()
+
+
+# (cin, cout, taps, window, batch, copies in the batch, first unit of the model, type, by the kernels for these layers): both sides of the lines
+# of conv1d_pays, single layers and (two couts) chains; 64-row tiles with a last one of one row, of 63, two column halves
+ROUTES = [(32, 64, 9, 64, 64, 8, False, "bf16", False), (32, 64, 9, 65, 64, 1, False, "bf16", True), (24, 32, 9, 49, 47, 1, False, "bf16", True),
+          (64, 64, 3, 127, 64, 8, False, "bf16", False), (64, 64, 9, 83, 99, 1, False, "bf16", True), (48, 40, 7, 65, 127, 1, False, "bf16", True),
+          (64, 48, 7, 128, 400, 40, False, "bf16", False), (64, 64, 3, 128, 400, 40, False, "bf16", True), (40, 64, 3, 128, 800, 80, False, "bf16", False),
+          (8, 8, 3, 128, 560, 56, False, "bf16", True), (8, 8, 3, 128, 768, 64, False, "bf16", False), (16, 48, 3, 128, 2400, 240, False, "bf16", True),
+          (8, 8, 3, 128, 1600, 80, False, "f32", False), (8, 16, 3, 128, 1600, 80, False, "f32", True),
+          (9, 32, 5, 127, 32, 1, True, "bf16", False), (9, 32, 3, 63, 65, 1, True, "bf16", True), (16, 64, 5, 63, 65, 1, True, "bf16", False),
+          (3, 16, 3, 128, 191, 1, True, "bf16", True), (3, 16, 3, 128, 192, 24, True, "bf16", False), (64, 24, 5, 91, 99, 1, True, "bf16", True),
+          (9, 32, 5, 128, 255, 15, True, "f32", True), (9, 32, 5, 128, 256, 32, True, "f32", False), (9, 64, 5, 128, 256, 32, True, "f32", True)]
+
+
+@pytest.mark.parametrize("cin,cout,k,w,batch,tile,first,dtype,here", ROUTES, ids=["-".join(map(str, c)) for c in ROUTES])
+def test_conv1d_routes(cin, cout, k, w, batch, tile, first, dtype, here):
+    print(f"conv1d route {cin}->{cout} taps {k} window {w} batch {batch} first {first} {dtype}", flush=True)
+    o, h = units([cin] if first else [cin, cin], cout, k, L.ACT_NONE)
+    tol = TOL[dtype]
+    pair = Pair(o, h, (1, w, cin), batch, len(o) - 1, len(o), dtype, seed=6, tile=tile)
+    try:
+        got = []
+        n = launches(lambda: got.append(pair.forward(0, synth.normal(23, "x", (batch // tile, 1, w, cin)))))
+        assert ("conv1d_fwd" in n) == here and ("im2col" in n or "conv_direct_fwd" in n) != here, n
+        assert_close(*got[0], tol, "y")
+        dy = synth.normal(23, "dy", (batch // tile,) + tuple(pair.out_shape))
+        n = launches(lambda: got.append(pair.backward(0, dy, want_dx=not first)))
+        assert ("conv1d_wgrad" in n) == here, n
+        if not first:
+            assert_close(*got[1], tol, "dx")
+        pair.compare_unit_vectors("grads", tol, floor=1e-6)
+        pair.compare_unit_vectors("bn", tol)
+    finally:
+        pair.close()
+
+
+@pytest.mark.parametrize("cins,cout,k,w,batch,tile,dtype,n_here", [([9, 32, 64], 64, 5, 128, 240, 24, "bf16", 3), ([9, 32, 64], 64, 5, 128, 280, 28, "bf16", 2),
+                                                                  ([16, 16, 16], 16, 3, 128, 800, 80, "bf16", 2), ([8, 8, 8], 8, 3, 128, 1600, 100, "bf16", 0),
+                                                                  ([8, 8, 16], 64, 3, 128, 1600, 100, "f32", 2)])
+def test_conv1d_chains_of_both_routes(cins, cout, k, w, batch, tile, dtype, n_here):
+    """The first layer's patches wait for its weight gradient while layers of either kind run behind it; the BatchNorm-backward sums of a
+    layer come from the data gradient behind it or from a pass of their own."""
+    print(f"conv1d chain {cins} -> {cout} taps {k} window {w} batch {batch} {dtype}", flush=True)
+    o, h = units(cins, cout, k, L.ACT_NONE if dtype == "bf16" else L.ACT_RELU)
+    pair = Pair(o, h, (1, w, cins[0]), batch, 0, len(o), dtype, seed=7, tile=tile, ties="off" if dtype == "bf16" else "bounded")
+    try:
+        got = []
+        for step in range(2):
+            n = launches(lambda: got.append(pair.forward(0, synth.normal(24, f"x{step}", (batch // tile, 1, w, cins[0])))))
+            assert n.get("conv1d_fwd", 0) == n_here, n
+            assert_close(*got[-1], TOL[dtype], "y")
+            pair.backward(0, synth.normal(24, f"dy{step}", (batch // tile,) + tuple(pair.out_shape)), want_dx=False)
+            pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
     finally:
         pair.close()
 
