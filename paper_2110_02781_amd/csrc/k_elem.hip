@@ -147,8 +147,9 @@ __device__ __forceinline__ void sum_partials(const float* __restrict__ partial, 
   }
 }
 
-// What the last threads need besides the sums is requested before them.  3.1 - 4.2 us a launch (4.4 - 4.7 when all 256 threads added all
-// lanes' sums, the parameters were fetched behind them and M was divided by in float64).
+// What the last threads need besides the sums is requested before them.  Means over a step, us a launch (in brackets: all 256 threads added
+// all lanes' sums, the parameters were fetched behind them and M was divided by in float64): MobileNetV2 at 32x32, batch 32, fp32 3.1
+// (4.0), at 224x224, width 1.4, batch 128, bfloat16 4.7 (4.9); bn_bwd_finalize_k 3.1 (3.7) and 4.9 (5.7).
 __global__ __launch_bounds__(256) void bn_finalize_k(const float* __restrict__ partial, int P, double inv_M, double unbias, int C,
                                                      const float* __restrict__ gamma, const float* __restrict__ beta, float* mean, float* invstd,
                                                      float* scale, float* shift, float* run_mean, float* run_var, float eps, float momentum) {
@@ -767,7 +768,8 @@ __global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ ro
 // One block for everything where its lane groups need at most two rounds of short rows (or one of longer ones), two
 // launches otherwise.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean
 // kernel): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4,
-// 4096 x 10 11.4 / 24 / 6.4, 4096 x 1000 bfloat16 16.8 / - / 7.8, 16384 x 1000 bfloat16 62 / - / 19.
+// 4096 x 10 11.4 / 24 / 6.4, 4096 x 1000 bfloat16 16.8 / - / 7.8 (on logits that no cache holds 21.8 / - / 9.1), 16384 x 1000 bfloat16
+// 62 / - / 19.  Between the one-block form and about 2 M values two launches are all that is timed, as with a block per row.
 template <typename T>
 static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* labels, int B, int classes, float* row_loss, T* dlogits,
                               float* loss) {

@@ -475,7 +475,12 @@ __global__ __launch_bounds__(256, VIEW ? 2 : 3) void pw_wgrad_tr_group_k(WgTrGro
 }
 
 // share: how many layers share the launch (pw_wgrad_tr_group).  The split, and with it the last bit of a gradient (the rounding of
-// the partials), depends on it, as it does on the storage type and the rows.
+// the partials), depends on it, as it does on the storage type and the rows.  One layer or two are cut into 512 blocks each, three to
+// nine into about 1000 together, ten and more into 96 each: the launch is full with fewer blocks per layer, and every split less is
+// a partial gradient less to write and add.  Steps of chains, us, 512 / 256 / 128 / 96 / 64 blocks per layer (runs differ by up to 6 %): two layers
+// 6272 rows, 192 -> 192 76 / 76 / 76 / 81 / 82, 12544 rows, 96 <-> 384 92 / 92 / 96 / 103 / 110; six 3136 rows, 320 <-> 640 306 / 251 / 248 / 258 / 255;
+// fourteen 6272 rows 422 / 415 / 414 / 397 / 393, 12544 rows 587 / 555 / 542 / 526 / 529, 3136 rows 706 / 563 / 554 / 557 / 563.  Units 15 - 18 of MobileNetV2 at
+// 224x224, batch 64 (seven layers), twelve steps: 6.55 / 6.06 / 6.05 / 6.01 / 6.13 ms, with 146 blocks 5.95.
 static bool wg_tr_plan(size_t M, int K, int N, WgTrArgs* a, int* S, int share = 1) {
   if (K % 8 || N % 8 || M <= 2048 || N < 48) return false;     // a 128-column strip of a narrower dZ is mostly padding: measured slower
   a->itiles = (N + kWgN - 1) / kWgN;

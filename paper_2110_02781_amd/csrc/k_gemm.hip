@@ -1529,10 +1529,11 @@ __global__ __launch_bounds__(256, 3) void pw_wgrad_group_k(PwWgGroup a) {
     }
 }
 
-// bfloat16 layers the transposing kernel takes (long ones) run there; both leave partials
-// more rows per block where they are many: at most 512 partials per layer
+// rows per block: more where they are many, so that a layer leaves at most 512 partials
 static int grp_rows(size_t M) { return kGrpRows * (int)((M + 512 * kGrpRows - 1) / (512 * kGrpRows)); }
 
+// Long bfloat16 layers run in the transposing kernel, which leaves partials; of the others those of more than grp_rows rows do, and
+// shorter ones are added to g_w at once.
 size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, int share) {
   if (pw_wgrad_tr_ok(dt, M, K, N)) return pw_wgrad_tr_ws(M, K, N, share);
   const int R = grp_rows(M);
