@@ -769,7 +769,7 @@ __global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ ro
 // launches otherwise.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean
 // kernel): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4,
 // 4096 x 10 11.4 / 24 / 6.4, 4096 x 1000 bfloat16 16.8 / - / 7.8 (on logits that no cache holds 21.8 / - / 9.1), 16384 x 1000 bfloat16
-// 62 / - / 19.  Between the one-block form and about 2 M values two launches are all that is timed, as with a block per row.
+// 62 / - / 19.  With a few hundred rows up to some thousand short ones two launches are all that is timed, as with a block per row.
 template <typename T>
 static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* labels, int B, int classes, float* row_loss, T* dlogits,
                               float* loss) {

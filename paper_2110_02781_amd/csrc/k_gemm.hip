@@ -1155,8 +1155,10 @@ __device__ __forceinline__ void pw_wgrad_tiny_body(const GemmArgs& p, const int 
   float g_old = writer ? *dst : 0.f;
   const size_t per = ((M + 4 * NW - 1) / (4 * NW)) * 4;    // pixels per wavefront, a multiple of 4
   const size_t mb = (size_t)wave * per, me = mb + per < M ? mb + per : M;
-  f4v acc = {0.f, 0.f, 0.f, 0.f};
+  // a chain of fp32 additions per round of 32 rows; the rounds and the wavefronts meet in float64, as in pw_wgrad_group_k
+  double tot[4] = {0.0, 0.0, 0.0, 0.0};
   for (size_t m0 = mb; m0 < me; m0 += 4 * U) {
+    f4v acc = {0.f, 0.f, 0.f, 0.f};
     float x[U], y[U];
     T xr[U], yr[U];                            // converted after all loads of the round are out (see FragRaw)
 #pragma unroll
@@ -1166,6 +1168,7 @@ __device__ __forceinline__ void pw_wgrad_tiny_body(const GemmArgs& p, const int 
       xr[u] = X[mc * p.N];
       yr[u] = Y[mc * p.K];
     }
+    __builtin_amdgcn_sched_barrier(0);         // without it every bfloat16 load is followed by its conversion, and a wait: 512 rows, 64 -> 384 27 us a step instead of 20
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const bool ok = m0 + 4 * u + mg < me;
@@ -1181,17 +1184,19 @@ __device__ __forceinline__ void pw_wgrad_tiny_body(const GemmArgs& p, const int 
       }
       acc = __builtin_amdgcn_mfma_f32_16x16x4f32(x[u], a, acc, 0, 0, 0);
     }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) tot[r] += (double)acc[r];
   }
   // register r of lane l is tile element (row 4*(l/16) + r = n, column l%16 = k)
 #pragma unroll
-  for (int r = 0; r < 4; ++r) red[wave][4 * mg + r][l16] = acc[r];
+  for (int r = 0; r < 4; ++r) red[wave][4 * mg + r][l16] = (float)tot[r];
   __syncthreads();
   asm volatile("" : "+v"(g_old));
   if (writer) {
-    float v = 0.f;
+    double v = 0.0;
 #pragma unroll
-    for (int q = 0; q < NW; ++q) v += red[q][orow][ocol];
-    *dst = g_old + v;
+    for (int q = 0; q < NW; ++q) v += (double)red[q][orow][ocol];
+    *dst = g_old + (float)v;
   }
 }
 
@@ -1381,10 +1386,10 @@ void pw_wgrad(int dt, hipStream_t st, const void* dz, HView av, size_t M, int K,
 // ---- weight gradients of several layers in one launch -----------------------------------------------------------
 // A backward pass over small tensors is a chain of short launches; the weight gradients are not part of the chain, so they
 // are noted and all done here at its end, where their tiles together fill the chip (one layer has 10-60 of them).  A block
-// takes a 128 x 64 tile of one layer's g_w over at most 256 rows: the wider of N and K in slices of 32 per wavefront, the
+// takes a 128 x 64 tile of one layer's g_w over 32 to 256 rows: the wider of N and K in slices of 32 per wavefront, the
 // narrower as up to four tiles of 16 (the ones past its end are not computed, so 24 channels cost 32 and not 64).  Operands lie
 // in LDS as they lie in memory, widened to fp32 (products of bfloat16 values are exact in the fp32 MFMA); six LDS words
-// feed eight MFMAs.  Layers of up to 256 rows are added to g_w here, the others leave one partial per 256 rows.
+// feed eight MFMAs.  Layers of up to 256 rows are added to g_w here, the others leave a partial per block of rows (grp_rows).
 // MobileNetV2, 32x32 input, batch 32, fp32: 33 us for 35 layers, where each layer's own weight gradient (next to its data gradient
 // in one launch, or two launches of its own) put about 200 us on the chain; width 0.5, 161x193, batch 13, bfloat16: 38 us against 250.
 // Bound by the latency of eight chunks (MFMA time about 10 us).  Blocks in the order of the jobs over the XCDs took 45 us:
@@ -1529,19 +1534,31 @@ __global__ __launch_bounds__(256, 3) void pw_wgrad_group_k(PwWgGroup a) {
     }
 }
 
-// rows per block: more where they are many, so that a layer leaves at most 512 partials
-static int grp_rows(size_t M) { return kGrpRows * (int)((M + 512 * kGrpRows - 1) / (512 * kGrpRows)); }
+// Rows per block: as many blocks as fill the chip together with those of the other layers (about 512), 32 to 256 rows each, and more
+// where a layer would leave more than 512 partials.  A step, us, always 256 rows / this: 96 -> 24 channels, 8192 rows, alone fp32 47.9 / 40.8,
+// bfloat16 42.2 / 35.0; 64 <-> 384, 6272 rows, fp32 alone 66.9 / 58.8, two layers 103 / 98; 24 <-> 144, 512 rows, 24 layers 391 / 327;
+// with 32 rows throughout twelve layers of 6272 rows took 562 instead of 516.
+static int grp_rows(size_t M, int K, int N, int share) {
+  if (M <= kGrpRows) return kGrpRows;
+  const int wide = N >= K ? N : K, narrow = N >= K ? K : N;
+  const size_t tiles = (size_t)((wide + kGrpWide - 1) / kGrpWide) * ((narrow + kGrpNarrow - 1) / kGrpNarrow), want = share < 2 ? 512 : share < 512 ? 512 / share : 1;
+  const auto chunks = [](size_t rows) { return (rows + kGrpChunk - 1) / kGrpChunk * kGrpChunk; };
+  size_t rows = chunks((M * tiles + want - 1) / want);
+  if (rows > kGrpRows) rows = kGrpRows;
+  const size_t least = chunks((M + 511) / 512);
+  return (int)(rows > least ? rows : least);
+}
 
 // Long bfloat16 layers run in the transposing kernel, which leaves partials; of the others those of more than grp_rows rows do, and
 // shorter ones are added to g_w at once.
-size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, int share) {
-  if (pw_wgrad_tr_ok(dt, M, K, N)) return pw_wgrad_tr_ws(M, K, N, share);
-  const int R = grp_rows(M);
+size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, PwShare share) {
+  if (pw_wgrad_tr_ok(dt, M, K, N)) return pw_wgrad_tr_ws(M, K, N, share.tr);
+  const int R = grp_rows(M, K, N, share.other);
   return M > (size_t)R ? (M + R - 1) / R * (size_t)N * K : 0;
 }
 
-void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int share, std::vector<ReduceJob>* left) {
-  if (dt == 1) pw_wgrad_tr_group(st, jobs, n, share, left);
+void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, PwShare share, std::vector<ReduceJob>* left) {
+  if (dt == 1) pw_wgrad_tr_group(st, jobs, n, share.tr, left);
   PwWgGroup a{};
   int blocks = 0;
   double bytes = 0, flops = 0;
@@ -1556,7 +1573,7 @@ void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int s
   for (int i = 0; i < n; ++i) {
     const PwWgradJob& w = jobs[i];
     if (pw_wgrad_tr_ok(dt, w.M, w.K, w.N)) continue;
-    const int R = grp_rows(w.M), S = (int)((w.M + R - 1) / R), wide = w.N >= w.K ? w.N : w.K, narrow = w.N >= w.K ? w.K : w.N;
+    const int R = grp_rows(w.M, w.K, w.N, share.other), S = (int)((w.M + R - 1) / R), wide = w.N >= w.K ? w.N : w.K, narrow = w.N >= w.K ? w.K : w.N;
     PwWgGroupJob j{w.dz, w.a.z, w.a.scale, w.a.shift, S == 1 ? w.g_w : w.ws, (int)w.M, w.K, w.N, w.a.act, R,
                    (wide + kGrpWide - 1) / kGrpWide, (narrow + kGrpNarrow - 1) / kGrpNarrow, 0, S == 1};
     j.nblk = j.wtiles * j.ntiles * S;

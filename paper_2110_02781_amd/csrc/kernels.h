@@ -229,9 +229,11 @@ void pw_wgrad(int dt, hipStream_t st, const void* dz, HView a, size_t M, int K, 
 // Weight gradients of several pointwise layers together (K and N multiples of 8); short ones are added to g_w at once, the
 // others leave partial sums in their ws (pw_wgrad_group_ws floats of its own) and append what is left to sum
 struct PwWgradJob { const void* dz; HView a; size_t M; int K, N; float* ws; float* g_w; };
-// share: how many layers such a group holds when it is complete (the same number in both calls)
-size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, int share);
-void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, int share, std::vector<ReduceJob>* left);
+// share: how many layers such a group holds when it is complete, those the transposing kernel takes and the others (the same numbers
+// in both calls)
+struct PwShare { int tr, other; };
+size_t pw_wgrad_group_ws(int dt, size_t M, int K, int N, PwShare share);
+void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, PwShare share, std::vector<ReduceJob>* left);
 
 // Narrow-to-wide pointwise layer (K inputs, N >= 2K outputs, bfloat16, input stored activated), whole backward behind
 // the BatchNorm reductions in one pass: dz = k1*dA*act'(out) + k2*z + k3 formed per row tile on chip,

@@ -213,6 +213,7 @@ struct UnitPlan {
   std::vector<size_t> z_off;       // per sub: byte offset of z in the slot stash
   std::vector<size_t> st_off;      // per sub: float offset of mean|invstd|scale|shift in the slot stats
   std::vector<size_t> part;        // per sub: floats of its partial weight gradients (stages that defer them)
+  std::vector<char> at_once;       // per sub: a pointwise layer of such a stage whose weight gradient runs next to its data gradient all the same
   std::vector<char> axis;          // per sub: a convolution along one axis that the kernels for those run
   size_t out_off;                  // byte offset of the materialised unit output (if any)
   bool out_virtual;                // CONV unit whose output stays a view
@@ -283,7 +284,7 @@ struct ftp_stage {
   char* dz_store = nullptr;
   float* parts = nullptr;
   size_t dz_cap = 0, dz_used = 0, part_cap = 0, part_used = 0;      // bytes, floats
-  int n_tr = 0;                // layers that share the launch of the transposing weight gradient (pw_wgrad_group's share)
+  PwShare share{0, 0};         // pointwise layers that share the launches of weight gradients
   std::vector<PwWgradJob> q_pw;
   std::vector<DwWgradJob> q_dw;
   std::vector<ReduceJob> q_red;
@@ -383,6 +384,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
 
   size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, layer_ws = 0, n_convs = 0, z_values = 0;
   size_t dz_bytes = 0, dz_max = 0, part_floats = 0, part_max = 0;
+  size_t n_long = 0, short_rows = 0, short_products = 0;      // pointwise layers outside the transposing kernel
   int max_c = 8;
   auto act_bytes = [&](int H, int W, int C) { return align_up((size_t)batch * H * W * C * s->es, 256); };
   const UnitInfo& first = m->units[a];
@@ -394,7 +396,12 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       const size_t M = (size_t)batch * sb.g.Hout * sb.g.Wout;
       z_values += M * sb.g.Cout;
       ++n_convs;
-      if (sb.type == SUB_PW && pw_wgrad_tr_ok(m->dtype, M, sb.g.Cin, sb.g.Cout) && pw_bwd_fused_ws(M, sb.g.Cin, sb.g.Cout) == 0) ++s->n_tr;
+      if (sb.type != SUB_PW || (m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, sb.g.Cin, sb.g.Cout) > 0)) continue;
+      if (pw_wgrad_tr_ok(m->dtype, M, sb.g.Cin, sb.g.Cout)) { ++s->share.tr; continue; }
+      ++s->share.other;
+      if (M > 2048) { ++n_long; continue; }
+      short_rows += M;
+      short_products += M * sb.g.Cin * sb.g.Cout;
     }
   // Two ways to keep weight gradients off the data-gradient chain: all of them at the end of the call, or each on a second
   // stream as soon as its dz is there.  The second costs event calls and a division of the memory bandwidth, and pays only where
@@ -403,6 +410,14 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   // 128 bfloat16 5.8 / 5.6 (16.5 M values); block 2 alone bfloat16 batch 16 0.25 / 0.20, 32 (16.8 M) 0.295 / 0.289, 64 (34 M)
   // 0.490 / 0.509; units 1-4 bfloat16 batch 32 1.03 / 0.88, 64 (22 M) 1.42 / 1.45; width 1.4 batch 128 bfloat16 (26 M) 7.4 / 7.5.
   s->defers = n_convs == 0 || z_values / n_convs < ((size_t)20 << 20);
+  // A launch for the weight gradients of a few short layers, and one for their partial sums, cost more than it costs to run each next to
+  // its data gradient, in that one's launch.  A step (forward and backward), us, at once / together: 64 <-> 384 channels, fp32, 512 rows one layer 21 / 31,
+  // two 40 / 46, three 58 / 63, four (2048 rows in all) 82 / 82, six 120 / 116; 2048 rows one 33 / 41, two 68 / 69, three 97 / 96; 128 rows twelve
+  // 187 / 189; bfloat16 512 rows one 20 / 29, three 56 / 60, four 81 / 76; 2048 rows one 31 / 37, two 71 / 61; one block of 64 channels, 512 rows
+  // fp32 44 / 50, bfloat16 46 / 52.  From about 200 M products on the together form is no slower (512 rows, 320 <-> 1280: one 67 / 67,
+  // two 125 / 120).  With a longer layer in the stage the launch is there anyway.
+  const size_t n_short = s->share.other - n_long;
+  const bool short_at_once = n_long == 0 && (n_short == 1 || short_rows <= 1600) && short_products <= 200000000;
   for (int i = a; i < b; ++i) {
     const UnitInfo& u = m->units[i];
     UnitPlan p;
@@ -427,9 +442,11 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       if (need > layer_ws) layer_ws = need;
       if (i == a && &sb == &u.subs[0]) s->ws_tail_floats = need;
       size_t part = patches ? 0 : need;
+      bool at_once = false;
       bool dz_stored = true;             // a layer whose dz is not always stored still counts in dz_max
       if (sb.type == SUB_PW) {
-        part = pw_wgrad_group_ws(m->dtype, M, g.Cin, g.Cout, s->n_tr);
+        at_once = s->defers && M <= 2048 && short_at_once;
+        part = at_once ? 0 : pw_wgrad_group_ws(m->dtype, M, g.Cin, g.Cout, s->share);
         const size_t fused = m->dtype == FTP_BF16 ? pw_bwd_fused_ws(M, g.Cin, g.Cout) : 0;
         if (fused > 0 && &sb == &u.subs[0]) dz_stored = false;
         if (fused > part) part = fused;
@@ -441,6 +458,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       dz_bytes += dz_stored ? zb : 0;
       part = align_up(part, 64);
       p.part.push_back(part);
+      p.at_once.push_back(at_once);
       if (part > part_max) part_max = part;
       part_floats += part;
       if (sb.type == SUB_PW && m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, g.Cin, g.Cout) > s->ws_fused_floats)
@@ -1100,7 +1118,10 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   if (noted) {
     float* gw = s->grads + p.p_off + sb.w_off;
     const void* w = conv_w(s, W, p.p_off + sb.w_off);
-    if (sb.type == SUB_PW) {
+    if (p.at_once[k]) {
+      if (dIn) pw_bwd(s->dt, st, dz, w, res, in, M, g.Cin, g.Cout, nullptr, gw, dIn);      // up to 2048 rows: no partial sums
+      else pw_wgrad(s->dt, st, dz, in, M, g.Cin, g.Cout, nullptr, gw);
+    } else if (sb.type == SUB_PW) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
       if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);
     } else if (sb.type == SUB_DW) {
@@ -1167,7 +1188,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
 
 // every weight gradient noted so far, and the sums of what the kernels left
 static void run_noted(ftp_stage* s, hipStream_t st) {
-  pw_wgrad_group(s->dt, st, s->q_pw.data(), (int)s->q_pw.size(), s->n_tr, &s->q_red);
+  pw_wgrad_group(s->dt, st, s->q_pw.data(), (int)s->q_pw.size(), s->share, &s->q_red);
   dw_wgrad_group(s->dt, st, s->q_dw.data(), (int)s->q_dw.size(), &s->q_red);
   reduce_group(st, s->q_red.data(), (int)s->q_red.size());
   s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();

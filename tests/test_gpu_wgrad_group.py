@@ -3,7 +3,7 @@ the tiles (128 along the wider of the channel counts, 16 to 64 along the narrowe
 import pytest
 
 import synth
-from harness import Pair, TOL, assert_close
+from harness import Pair, TOL, assert_close, launches
 from oracle import layers as L
 from oracle import models as OM
 
@@ -21,7 +21,8 @@ def chain(channels):
 # partials (the two forms of their sum), more than 128; wide before narrow and after it, equal, off 16 / 64 / 128; a chain of 40 layers
 # is more than a launch takes; the second backward adds to what the first has left
 CASES = [([8, 8], 3, 5, 1), ([16, 136, 24], 16, 16, 1), ([24, 144, 40], 257, 1, 1), ([64, 72, 264], 31, 33, 4), ([40, 48], 64, 64, 1),
-         ([72, 80], 241, 17, 1), ([136, 128], 9, 113, 4), ([8, 16, 96, 24], 93, 127, 3), ([16] * 41, 5, 6, 11)]
+         ([72, 80], 241, 17, 1), ([136, 128], 9, 113, 4), ([8, 16, 96, 24], 93, 127, 3), ([16] * 41, 5, 6, 11),
+         ([16, 136, 24] * 3, 16, 16, 1), ([24, 144, 40] * 3, 257, 1, 1), ([8, 264] * 4, 13, 31, 1)]
 
 
 # bfloat16 roundings chained over many layers have no bound to hold a run against
@@ -42,5 +43,49 @@ def test_weight_gradients_at_the_end_of_the_call(channels, h, w, batch, dtype):
             dx, dxo = pair.backward(slot, synth.normal(31, f"dy{slot}", yo.shape))
             assert_close(dx, dxo, tol, f"dx {slot}")
             pair.compare_unit_vectors("grads", tol, floor=1e-6)
+    finally:
+        pair.close()
+
+
+# (channels of a chain, rows as H x W, batch, whether each layer's weight gradient runs next to its data gradient: no partial sums are left
+# then): both sides of the lines, one layer of up to 2048 rows, several of up to 1600 together, 200 M products
+AT_ONCE = [([64, 72], 32, 64, 1, True), ([64, 72], 3, 683, 1, False), ([24, 40, 24, 40, 24], 20, 20, 1, True), ([24, 40, 24, 40, 24], 401, 1, 1, False),
+           ([320, 1280], 16, 30, 1, True), ([320, 1280], 16, 31, 1, False), ([16, 48, 8], 17, 1, 3, True)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("channels,h,w,batch,at_once", AT_ONCE, ids=[f"{'-'.join(map(str, c[0]))}_{c[1]}x{c[2]}_b{c[3]}" for c in AT_ONCE])
+def test_a_few_short_layers_run_both_gradients_at_once(channels, h, w, batch, at_once, dtype):
+    print(f"pointwise chain {channels} {h}x{w} batch {batch} {dtype}", flush=True)
+    o, hu = chain(channels)
+    pair = Pair(o, hu, (h, w, channels[0]), batch, 0, len(o), dtype, seed=8)
+    try:
+        y, yo = pair.forward(0, synth.normal(32, "x", (batch, h, w, channels[0])))
+        got = []
+        n = launches(lambda: got.append(pair.backward(0, synth.normal(32, "dy", yo.shape))))
+        assert ("reduce_partials" not in n) == at_once, n
+        if dtype == "f32" or len(o) <= 2:
+            assert_close(y, yo, TOL[dtype], "y")
+            assert_close(*got[0], TOL[dtype], "dx")
+            pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
+    finally:
+        pair.close()
+
+
+def test_a_stage_with_a_longer_layer_runs_its_short_ones_with_it():
+    """A stride-2 block: the expand layer has 2304 rows, the project layer 576."""
+    import paper_2110_02781_amd.binding as B
+    print("stride-2 block, 2304 and 576 rows f32", flush=True)
+    o = [OM.Unit('invres', 16, 24, 3, 3, 2, 1, 1, expand=6, act=L.ACT_RELU6)]
+    h = [dict(kind=B.UNIT_INVRES, cin=16, cout=24, kh=3, kw=3, stride=2, pad_h=1, pad_w=1, expand=6, act=B.ACT_RELU6)]
+    pair = Pair(o, h, (16, 16, 16), 9, 0, 1, "f32", seed=9, ties="bounded")
+    try:
+        y, yo = pair.forward(0, synth.normal(33, "x", (9, 16, 16, 16)))
+        assert_close(y, yo, TOL["f32"], "y")
+        got = []
+        n = launches(lambda: got.append(pair.backward(0, synth.normal(33, "dy", yo.shape))))
+        assert "pw_bwd" not in n, n
+        assert_close(*got[0], TOL["f32"], "dx")
+        pair.compare_unit_vectors("grads", TOL["f32"], floor=1e-6)
     finally:
         pair.close()
