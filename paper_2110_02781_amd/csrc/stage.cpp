@@ -384,7 +384,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
 
   size_t stash = 0, stats = 0, max_act = 0, ws_floats = 1024, layer_ws = 0, n_convs = 0, z_values = 0;
   size_t dz_bytes = 0, dz_max = 0, part_floats = 0, part_max = 0;
-  size_t n_long = 0, short_rows = 0, short_products = 0;      // pointwise layers outside the transposing kernel
+  size_t n_long = 0, n_narrow = 0, short_rows = 0, short_products = 0;      // pointwise layers outside the transposing kernel
   int max_c = 8;
   auto act_bytes = [&](int H, int W, int C) { return align_up((size_t)batch * H * W * C * s->es, 256); };
   const UnitInfo& first = m->units[a];
@@ -399,7 +399,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       if (sb.type != SUB_PW || (m->dtype == FTP_BF16 && pw_bwd_fused_ws(M, sb.g.Cin, sb.g.Cout) > 0)) continue;
       if (pw_wgrad_tr_ok(m->dtype, M, sb.g.Cin, sb.g.Cout)) { ++s->share.tr; continue; }
       ++s->share.other;
-      if (M > 2048) { ++n_long; continue; }
+      if (M > 2048) { ++n_long; n_narrow += sb.g.Cout <= 32 && M >= 16384; continue; }
       short_rows += M;
       short_products += M * sb.g.Cin * sb.g.Cout;
     }
@@ -414,10 +414,15 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   // its data gradient, in that one's launch.  A step (forward and backward), us, at once / together: 64 <-> 384 channels, fp32, 512 rows one layer 21 / 31,
   // two 40 / 46, three 58 / 63, four (2048 rows in all) 82 / 82, six 120 / 116; 2048 rows one 33 / 41, two 68 / 69, three 97 / 96; 128 rows twelve
   // 187 / 189; bfloat16 512 rows one 20 / 29, three 56 / 60, four 81 / 76; 2048 rows one 31 / 37, two 71 / 61; one block of 64 channels, 512 rows
-  // fp32 44 / 50, bfloat16 46 / 52.  From about 200 M products on the together form is no slower (512 rows, 320 <-> 1280: one 67 / 67,
-  // two 125 / 120).  With a longer layer in the stage the launch is there anyway.
+  // fp32 44 / 50, bfloat16 46 / 52.  From about 300 M products on the together form is the faster one (without the data gradient 512 rows,
+  // 320 -> 1280, 210 M, fp32 41 / 46, 1024 rows 62 / 58; 512 -> 512 1024 rows, 268 M, 40 / 43, 2048 rows 65 / 57).  With a longer layer in the
+  // stage the launch is there anyway.
+  // A single bfloat16 layer of 16384 rows and more with at most 32 outputs has a kernel that multiplies in bfloat16 and reads 128 rows at
+  // once: 96 -> 24 channels 32768 rows 36.5 / 44.4; 32 -> 16 131072 rows 44.7 / 55.4; a block of one depthwise and one such layer
+  // 131072 rows 115 / 122.
   const size_t n_short = s->share.other - n_long;
-  const bool short_at_once = n_long == 0 && (n_short == 1 || short_rows <= 1600) && short_products <= 200000000;
+  const bool narrow_at_once = m->dtype == FTP_BF16 && s->share.other == 1 && n_narrow == 1;
+  const bool short_at_once = n_long == 0 && (n_short == 1 || short_rows <= 1600) && short_products <= 300000000;
   for (int i = a; i < b; ++i) {
     const UnitInfo& u = m->units[i];
     UnitPlan p;
@@ -445,8 +450,9 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       bool at_once = false;
       bool dz_stored = true;             // a layer whose dz is not always stored still counts in dz_max
       if (sb.type == SUB_PW) {
-        at_once = s->defers && M <= 2048 && short_at_once;
-        part = at_once ? 0 : pw_wgrad_group_ws(m->dtype, M, g.Cin, g.Cout, s->share);
+        const bool narrow = M >= 16384 && g.Cout <= 32 && narrow_at_once;
+        at_once = s->defers && (narrow || (M <= 2048 && short_at_once));
+        part = narrow ? pw_wgrad_ws(M, g.Cin, g.Cout) : at_once ? 0 : pw_wgrad_group_ws(m->dtype, M, g.Cin, g.Cout, s->share);
         const size_t fused = m->dtype == FTP_BF16 ? pw_bwd_fused_ws(M, g.Cin, g.Cout) : 0;
         if (fused > 0 && &sb == &u.subs[0]) dz_stored = false;
         if (fused > part) part = fused;
@@ -1119,8 +1125,8 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     float* gw = s->grads + p.p_off + sb.w_off;
     const void* w = conv_w(s, W, p.p_off + sb.w_off);
     if (p.at_once[k]) {
-      if (dIn) pw_bwd(s->dt, st, dz, w, res, in, M, g.Cin, g.Cout, nullptr, gw, dIn);      // up to 2048 rows: no partial sums
-      else pw_wgrad(s->dt, st, dz, in, M, g.Cin, g.Cout, nullptr, gw);
+      if (dIn) pw_bwd(s->dt, st, dz, w, res, in, M, g.Cin, g.Cout, part, gw, dIn);
+      else pw_wgrad(s->dt, st, dz, in, M, g.Cin, g.Cout, part, gw);
     } else if (sb.type == SUB_PW) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
       if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);

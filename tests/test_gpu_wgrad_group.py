@@ -48,9 +48,9 @@ def test_weight_gradients_at_the_end_of_the_call(channels, h, w, batch, dtype):
 
 
 # (channels of a chain, rows as H x W, batch, whether each layer's weight gradient runs next to its data gradient: no partial sums are left
-# then): both sides of the lines, one layer of up to 2048 rows, several of up to 1600 together, 200 M products
+# then): both sides of the lines, one layer of up to 2048 rows, several of up to 1600 together, 300 M products
 AT_ONCE = [([64, 72], 32, 64, 1, True), ([64, 72], 3, 683, 1, False), ([24, 40, 24, 40, 24], 20, 20, 1, True), ([24, 40, 24, 40, 24], 401, 1, 1, False),
-           ([320, 1280], 16, 30, 1, True), ([320, 1280], 16, 31, 1, False), ([16, 48, 8], 17, 1, 3, True)]
+           ([320, 1280], 16, 45, 1, True), ([320, 1280], 16, 46, 1, False), ([16, 48, 8], 17, 1, 3, True)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
@@ -87,5 +87,27 @@ def test_a_stage_with_a_longer_layer_runs_its_short_ones_with_it():
         assert "pw_bwd" not in n, n
         assert_close(*got[0], TOL["f32"], "dx")
         pair.compare_unit_vectors("grads", TOL["f32"], floor=1e-6)
+    finally:
+        pair.close()
+
+
+# (channels, H x W, batch): a single bfloat16 layer of 16384 rows and more with up to 32 outputs runs by itself: a last chunk of one row
+# and of a few, outputs off 16, several column tiles; fewer rows, more outputs and two layers do not
+NARROW = [([24, 32], 113, 145, 1), ([96, 24], 128, 64, 2), ([40, 8], 131, 129, 1), ([200, 32], 64, 64, 9), ([24, 32], 127, 129, 1), ([24, 40], 113, 145, 1),
+          ([24, 32, 16], 113, 145, 1)]
+
+
+@pytest.mark.parametrize("want_dx", [True, False])
+@pytest.mark.parametrize("channels,h,w,batch", NARROW, ids=[f"{'-'.join(map(str, c[0]))}_{c[1]}x{c[2]}_b{c[3]}" for c in NARROW])
+def test_a_single_narrow_layer_runs_by_itself(channels, h, w, batch, want_dx):
+    print(f"narrow pointwise {channels} {h}x{w} batch {batch} bf16 dx {want_dx}", flush=True)
+    o, hu = chain(channels)
+    pair = Pair(o, hu, (h, w, channels[0]), batch, 0, len(o), "bf16", seed=8)
+    try:
+        y, yo = pair.forward(0, synth.normal(34, "x", (batch, h, w, channels[0])))
+        dx, dxo = pair.backward(0, synth.normal(34, "dy", yo.shape), want_dx=want_dx)
+        if want_dx:
+            assert_close(dx, dxo, TOL["bf16"], "dx")
+        pair.compare_unit_vectors("grads", TOL["bf16"], floor=1e-6)
     finally:
         pair.close()

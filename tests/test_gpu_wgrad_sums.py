@@ -84,7 +84,7 @@ def last_layers_gradient_error(h, w, batch, K, N, layers, dtype):
 # several layers together, narrow bfloat16 layers (48 columns and more go through another kernel)
 GROUPED = [(16, 16, 1, 40, 64, 1, "f32"), (14, 14, 8, 64, 384, 1, "f32"), (14, 14, 32, 64, 384, 1, "f32"), (28, 28, 16, 48, 48, 30, "f32"),
            (14, 14, 64, 96, 96, 12, "f32"), (28, 28, 64, 192, 32, 1, "f32"), (13, 11, 37, 72, 136, 2, "f32"), (56, 56, 32, 24, 24, 3, "f32"),
-           (28, 28, 64, 192, 32, 1, "bf16"), (56, 56, 32, 24, 24, 3, "bf16"), (14, 14, 8, 64, 384, 1, "bf16")]
+           (28, 28, 64, 192, 32, 1, "bf16"), (32, 32, 16, 96, 24, 1, "bf16"), (64, 64, 32, 32, 16, 1, "bf16"), (56, 56, 32, 24, 24, 3, "bf16"), (14, 14, 8, 64, 384, 1, "bf16")]
 
 
 @pytest.mark.parametrize("h,w,batch,K,N,layers,dtype", GROUPED, ids=["-".join(map(str, c)) for c in GROUPED])
