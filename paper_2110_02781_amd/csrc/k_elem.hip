@@ -511,8 +511,10 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
 }
 
 // ------------------------------------------------------------------ pooling
-// block = (image n, group of 8 channels); 64 lanes walk the positions, fixed-order sum through LDS
-template <typename T>
+// block = (image n, group of 8 channels); 64 lanes walk the positions, U of them on their way together, fixed-order sum through LDS.
+// One trip to memory where the image has at most 64 positions, and then U = 1: four requests a lane, three of them for nothing, and the code
+// that finishes statistics in every block took 264 x 1792 channels of 9 positions, fp32, from 18.9 to 27.8 us, 73 x 1280 of 4 from 5.8 to 8.3.
+template <typename T, bool PEND, int U>
 __global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float eps, float momentum, int N, int HW, int CG, T* __restrict__ out) {
   __shared__ float red[64][8];
   __shared__ double fin[64];
@@ -522,14 +524,13 @@ __global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float e
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   float sc[8], sh[8];
   const bool view = in.scale != nullptr;
-  constexpr int U = 4;                                  // positions of a lane on their way together
   Raw<T> r[U];
   auto request = [&](const int p0) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) raw_load(r[u], src + (size_t)(p0 + 64 * u < HW ? p0 + 64 * u : 0) * CG * 8);
   };
   request(lane);
-  if (pend.partial) {
+  if constexpr (PEND) {
     finish_pending_n(pend, CG * 8, cg * 8, 8, eps, momentum, n == 0, 64, fin, vec[0], vec[1]);
 #pragma unroll
     for (int e = 0; e < 8; ++e) { sc[e] = vec[0][e]; sh[e] = vec[1][e]; }
@@ -564,7 +565,11 @@ void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps,
   View v{in.z, in.scale, in.shift, in.act};
   int n = N * (C / 8);
   KScope ks(st, "gap_fwd", ((double)N * HW * C + (double)N * C) * (dt == 0 ? 4.0 : 2.0), 3.0 * N * HW * C);
-  FTP_DISPATCH(dt, hipLaunchKernelGGL(gap_fwd_k<T>, dim3(n), dim3(64), 0, st, v, pend, eps, momentum, N, HW, C / 8, (T*)out));
+#define FTP_GAP(PEND, U) FTP_DISPATCH(dt, hipLaunchKernelGGL((gap_fwd_k<T, PEND, U>), dim3(n), dim3(64), 0, st, v, pend, eps, momentum, N, HW, C / 8, (T*)out))
+  if (pend.partial) { if (HW <= 64) FTP_GAP(true, 1); else FTP_GAP(true, 4); }
+  else if (HW <= 64) FTP_GAP(false, 1);
+  else FTP_GAP(false, 4);
+#undef FTP_GAP
 }
 
 template <typename T>

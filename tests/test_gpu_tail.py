@@ -52,6 +52,25 @@ def test_fully_connected_backward_edges(k, classes, batch, h, w, conv, gap, dtyp
         pair.close()
 
 
+# the average over a lane's one position, exactly a wavefront's 64, one more, four rounds and one more; behind a convolution (a view, whose
+# statistics it finishes where the rows are few) and as a stage's first unit
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("conv", [True, False])
+@pytest.mark.parametrize("h,w,batch", [(1, 1, 70), (1, 2, 40), (8, 8, 3), (8, 8, 40), (5, 13, 3), (5, 13, 40), (16, 16, 2), (16, 16, 9), (1, 257, 3), (1, 257, 9)])
+def test_average_edges(h, w, batch, conv, dtype):
+    print(f"average {h}x{w} batch {batch} conv {conv} {dtype}", flush=True)
+    o, hu = tail(24, 10, conv, True)
+    cin = 8 if conv else 24
+    pair = Pair(o, hu, (h, w, cin), batch, 0, len(o), dtype, seed=8, ties="bounded" if conv else "off")
+    try:
+        y, yo = pair.forward(0, synth.normal(43, "x", (batch, h, w, cin)))
+        assert_close(y, yo, TOL[dtype], "y")
+        dx, dxo = pair.backward(0, synth.normal(43, "dy", yo.shape))
+        assert_close(dx, dxo, TOL[dtype], "dx")
+    finally:
+        pair.close()
+
+
 # fewer than 200 M products: one launch; more: a launch for each gradient, which were faster there (512 x 1792 -> 1000: 129 against 178 us)
 @pytest.mark.parametrize("batch,k,classes,one", [(128, 1280, 1000, True), (512, 384, 1000, True), (512, 400, 1000, False), (256, 1280, 1000, False)])
 def test_fully_connected_backward_takes_one_launch_where_it_is_faster(batch, k, classes, one):
