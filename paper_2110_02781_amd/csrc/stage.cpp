@@ -414,7 +414,10 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   // its data gradient, in that one's launch.  A step (forward and backward), us, at once / together: 64 <-> 384 channels, fp32, 512 rows one layer 21 / 31,
   // two 40 / 46, three 58 / 63, four (2048 rows in all) 82 / 82, six 120 / 116; 2048 rows one 33 / 41, two 68 / 69, three 97 / 96; 128 rows twelve
   // 187 / 189; bfloat16 512 rows one 20 / 29, three 56 / 60, four 81 / 76; 2048 rows one 31 / 37, two 71 / 61; one block of 64 channels, 512 rows
-  // fp32 44 / 50, bfloat16 46 / 52.  From about 300 M products on the together form is the faster one (without the data gradient 512 rows,
+  // fp32 44 / 50, bfloat16 46 / 52.  Blocks with their depthwise layer: one of 64 -> 384 -> 96, fp32, 900 rows 63 / 72, 1600 rows 83 / 89, of
+  // 88 channels 900 rows 72 / 78, 1600 rows (149 M products) 109 / 108, two of 64 channels 820 rows 112 / 120, 1040 rows 127 / 127;
+  // bfloat16 one of 64 channels 900 rows 60 / 66, 1040 rows 67 / 70, 1600 rows 81 / 80, of 48 channels 1040 rows 65 / 63, two of 64 channels 700
+  // rows 110 / 110, 1040 rows 130 / 123.  From about 300 M products on the together form is the faster one (without the data gradient 512 rows,
   // 320 -> 1280, 210 M, fp32 41 / 46, 1024 rows 62 / 58; 512 -> 512 1024 rows, 268 M, 40 / 43, 2048 rows 65 / 57).  With a longer layer in the
   // stage the launch is there anyway.
   // A single bfloat16 layer of 16384 rows and more with at most 32 outputs has a kernel that multiplies in bfloat16 and reads 128 rows at
@@ -422,7 +425,8 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   // 131072 rows 115 / 122.
   const size_t n_short = s->share.other - n_long;
   const bool narrow_at_once = m->dtype == FTP_BF16 && s->share.other == 1 && n_narrow == 1;
-  const bool short_at_once = n_long == 0 && (n_short == 1 || short_rows <= 1600) && short_products <= 300000000;
+  const size_t rows_at_once = n_short > 4 || short_products > 150000000 ? 1600 : m->dtype == FTP_F32 ? 3200 : n_short == 2 ? 2080 : 1600;
+  const bool short_at_once = n_long == 0 && (n_short == 1 || short_rows <= rows_at_once) && short_products <= 300000000;
   for (int i = a; i < b; ++i) {
     const UnitInfo& u = m->units[i];
     UnitPlan p;
