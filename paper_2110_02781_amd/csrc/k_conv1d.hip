@@ -592,7 +592,8 @@ static bool conv1d_small(const ConvGeom& g) { return (size_t)g.N * g.Win <= kC1S
 // 7 taps, 2304 91 / 105, 6144 98 / 106, 131072 485 / 549; 32 -> 64, 9 taps, 4096 99 / 102, 6144 107 / 103; chain 8 -> 8, 3 taps, 65536
 // 101 / 98, 131072 112 / 129, 1048576 350 / 670; 32 -> 32, 3 taps, 131072 190 / 174, 524288 522 / 580; first layers 9 -> 32, 5 taps, alone 2304
 // 36 / 38, 65536 48 / 67, in front of two more 16384 180 / 179, 65536 325 / 336; 3 -> 8, 3 taps, alone 8192 41 / 38, 16384 42 / 40,
-// 32768 42 / 46, 524288 76 / 162; 16 -> 16, 5 taps, in front of another 32768 99 / 93, 131072 157 / 157, 524288 390 / 437.
+// 32768 42 / 46, 524288 76 / 162; a layer behind others alone in its stage 64 -> 64, 9 taps 4096 70 / 70, 8192 84 / 94, 24576 108 / 129, 5 taps 32768
+// 97 / 98, 65536 131 / 157, 3 taps 32768 87 / 87, 65536 107 / 131; 16 -> 16, 5 taps, in front of another 32768 99 / 93, 131072 157 / 157, 524288 390 / 437.
 int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks) {
   const size_t M = (size_t)g.N * g.Win;
   const int lo = g.Cin < g.Cout ? g.Cin : g.Cout, hi = g.Cin < g.Cout ? g.Cout : g.Cin;
@@ -612,7 +613,7 @@ int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks) {
   if (forks) return 1;
   if (dt == 0) return !(hi <= 8 && g.kw == 3 && M >= 200000);
   if (M < 8192) return M > (size_t)128 * lo || weights < 10000;      // few tiles, each a long chain of fp32 products
-  if (lo >= 40) return M < (g.kw >= 7 ? 49152u : 98304u);           // bound by the fp32 products
+  if (lo >= 40) return M < (g.kw >= 7 ? (alone ? 8192u : 49152u) : alone ? 40000u : 98304u);           // bound by the fp32 products
   return !(hi <= 2 * lo && both <= 192 && M >= (size_t)1700 * both);   // narrow: columns filled up to 32
 }
 

@@ -51,8 +51,9 @@ def test_conv1d_edges(cins, cout, k, w, batch, dtype):
 # (cin, cout, taps, window, batch, copies in the batch, first unit of the model, type, by the kernels for these layers): both sides of the lines
 # of conv1d_pays, single layers and (two couts) chains; 64-row tiles with a last one of one row, of 63, two column halves
 ROUTES = [(32, 64, 9, 64, 64, 8, False, "bf16", False), (32, 64, 9, 65, 64, 1, False, "bf16", True), (24, 32, 9, 49, 47, 1, False, "bf16", True),
-          (64, 64, 3, 127, 64, 8, False, "bf16", False), (64, 64, 9, 83, 99, 1, False, "bf16", True), (48, 40, 7, 65, 127, 1, False, "bf16", True),
-          (64, 48, 7, 128, 400, 40, False, "bf16", False), (64, 64, 3, 128, 400, 40, False, "bf16", True), (40, 64, 3, 128, 800, 80, False, "bf16", False),
+          (64, 64, 3, 127, 64, 8, False, "bf16", False), (64, 64, 9, 83, 99, 1, False, "bf16", False), (48, 40, 7, 64, 127, 1, False, "bf16", True),
+          (48, 40, 7, 65, 127, 1, False, "bf16", False),
+          (64, 48, 7, 128, 400, 40, False, "bf16", False), (64, 64, 3, 128, 312, 24, False, "bf16", True), (64, 64, 3, 128, 320, 32, False, "bf16", False), (40, 64, 3, 128, 800, 80, False, "bf16", False),
           (8, 8, 3, 128, 560, 56, False, "bf16", True), (8, 8, 3, 128, 768, 64, False, "bf16", False), (16, 48, 3, 128, 2400, 240, False, "bf16", True),
           (8, 8, 3, 128, 1600, 80, False, "f32", False), (8, 16, 3, 128, 1600, 80, False, "f32", True),
           (9, 32, 5, 127, 32, 1, True, "bf16", False), (9, 32, 3, 63, 65, 1, True, "bf16", True), (16, 64, 5, 63, 65, 1, True, "bf16", False),
