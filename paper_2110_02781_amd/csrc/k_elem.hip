@@ -148,8 +148,8 @@ __device__ __forceinline__ void sum_partials(const float* __restrict__ partial, 
 }
 
 // What the last threads need besides the sums is requested before them.  Means over a step, us a launch (in brackets: all 256 threads added
-// all lanes' sums, the parameters were fetched behind them and M was divided by in float64): MobileNetV2 at 32x32, batch 32, fp32 3.2
-// (4.0), at 224x224, width 1.4, batch 128, bfloat16 4.6 (4.9); bn_bwd_finalize_k 3.1 (3.7) and 4.7 (5.7).
+// all lanes' sums, the parameters were fetched behind them and M was divided by in float64): MobileNetV2 at 32x32, batch 32, fp32 3.3
+// (4.0), at 224x224, width 1.4, batch 128, bfloat16 4.7 (4.9); bn_bwd_finalize_k 3.1 (3.7) and 5.0 (5.7).
 __global__ __launch_bounds__(256) void bn_finalize_k(const float* __restrict__ partial, int P, double inv_M, double unbias, int C,
                                                      const float* __restrict__ gamma, const float* __restrict__ beta, float* mean, float* invstd,
                                                      float* scale, float* shift, float* run_mean, float* run_var, float eps, float momentum) {
