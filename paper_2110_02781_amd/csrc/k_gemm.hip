@@ -28,6 +28,7 @@
 #include <type_traits>
 #include "dev_common.h"
 #include "kernels.h"
+#include "bn_pending.h"
 
 namespace ftp {
 
@@ -962,141 +963,295 @@ template <typename T> struct TinyStep;
 template <> struct TinyStep<float> { enum { G = 4, KS = 16 }; };
 template <> struct TinyStep<bf16_t> { enum { G = 8, KS = 32 }; };
 
-__device__ __forceinline__ void load_frag(const float* p, float* v) {
-  float4 a = *reinterpret_cast<const float4*>(p);
-  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w;
-}
-__device__ __forceinline__ void load_frag(const bf16_t* p, float* v) { load8(p, v); }
-// A fragment as loaded: converted only after every load of a round has been issued.  A conversion next to its
-// (conditional) load makes the compiler wait for that one load before it issues the next.
-template <typename T> struct FragRaw;
-template <> struct FragRaw<float> { float4 v; };
-template <> struct FragRaw<bf16_t> { uint4 v; };
-__device__ __forceinline__ void frag_load(FragRaw<float>& r, const float* p) { r.v = *reinterpret_cast<const float4*>(p); }
-__device__ __forceinline__ void frag_load(FragRaw<bf16_t>& r, const bf16_t* p) { r.v = *reinterpret_cast<const uint4*>(p); }
-__device__ __forceinline__ void frag_zero(FragRaw<float>& r) { r.v = make_float4(0.f, 0.f, 0.f, 0.f); }
-__device__ __forceinline__ void frag_zero(FragRaw<bf16_t>& r) { r.v = make_uint4(0u, 0u, 0u, 0u); }
-__device__ __forceinline__ void frag_unpack(const FragRaw<float>& r, float* v) { v[0] = r.v.x; v[1] = r.v.y; v[2] = r.v.z; v[3] = r.v.w; }
-__device__ __forceinline__ void frag_unpack(const FragRaw<bf16_t>& r, float* v) {
+// A fragment as loaded, and as the MFMAs take it: four floats, or eight bfloat16
+template <typename T> struct Frag;
+template <> struct Frag<float> { float4 v; };
+template <> struct Frag<bf16_t> { uint4 v; };
+__device__ __forceinline__ void frag_unpack(const Frag<float>& r, float* v) { v[0] = r.v.x; v[1] = r.v.y; v[2] = r.v.z; v[3] = r.v.w; }
+__device__ __forceinline__ void frag_unpack(const Frag<bf16_t>& r, float* v) {
   v[0] = __uint_as_float(r.v.x << 16); v[1] = __uint_as_float(r.v.x & 0xffff0000u);
   v[2] = __uint_as_float(r.v.y << 16); v[3] = __uint_as_float(r.v.y & 0xffff0000u);
   v[4] = __uint_as_float(r.v.z << 16); v[5] = __uint_as_float(r.v.z & 0xffff0000u);
   v[6] = __uint_as_float(r.v.w << 16); v[7] = __uint_as_float(r.v.w & 0xffff0000u);
 }
-
-__device__ __forceinline__ f4v tiny_mma(const float* a, const float* b, f4v acc, float) {
+__device__ __forceinline__ void frag_pack(Frag<float>& r, const float* v) { r.v = make_float4(v[0], v[1], v[2], v[3]); }
+__device__ __forceinline__ void frag_pack(Frag<bf16_t>& r, const float* v) {       // rounds
+  r.v = make_uint4(f32x2_to_bf16x2(v[0], v[1]), f32x2_to_bf16x2(v[2], v[3]), f32x2_to_bf16x2(v[4], v[5]), f32x2_to_bf16x2(v[6], v[7]));
+}
+// from single elements, each in 32 bits as loaded.  The empty asm keeps a pair from becoming one load into the low and one into the high half
+// of a register, where the second waits for the first.
+template <typename T> struct Elem;
+template <> struct Elem<float> { typedef float R; };
+template <> struct Elem<bf16_t> { typedef uint32_t R; };
+__device__ __forceinline__ float elem_f32(float e) { return e; }
+__device__ __forceinline__ float elem_f32(uint32_t e) { return __uint_as_float(e << 16); }
+__device__ __forceinline__ void frag_of(Frag<float>& r, float* e) { r.v = make_float4(e[0], e[1], e[2], e[3]); }
+__device__ __forceinline__ void frag_of(Frag<bf16_t>& r, uint32_t* e) {
 #pragma unroll
-  for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc, 0, 0, 0);
-  return acc;
+  for (int i = 0; i < 8; ++i) asm volatile("" : "+v"(e[i]));
+  r.v = make_uint4(e[0] | e[1] << 16, e[2] | e[3] << 16, e[4] | e[5] << 16, e[6] | e[7] << 16);
 }
-__device__ __forceinline__ f4v tiny_mma(const float* a, const float* b, f4v acc, bf16_t) {
-  uint4 pa, pb;
-  pa.x = f32x2_to_bf16x2(a[0], a[1]); pa.y = f32x2_to_bf16x2(a[2], a[3]);
-  pa.z = f32x2_to_bf16x2(a[4], a[5]); pa.w = f32x2_to_bf16x2(a[6], a[7]);
-  pb.x = f32x2_to_bf16x2(b[0], b[1]); pb.y = f32x2_to_bf16x2(b[2], b[3]);
-  pb.z = f32x2_to_bf16x2(b[4], b[5]); pb.w = f32x2_to_bf16x2(b[6], b[7]);
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pa), __builtin_bit_cast(bf16x8, pb), acc, 0, 0, 0);
+__device__ __forceinline__ void frag_zero(Frag<float>& r) { r.v = make_float4(0.f, 0.f, 0.f, 0.f); }
+__device__ __forceinline__ void frag_zero(Frag<bf16_t>& r) { r.v = make_uint4(0u, 0u, 0u, 0u); }
+__device__ __forceinline__ void frag_store(float* p, const Frag<float>& r) { *reinterpret_cast<float4*>(p) = r.v; }
+__device__ __forceinline__ void frag_store(bf16_t* p, const Frag<bf16_t>& r) { *reinterpret_cast<uint4*>(p) = r.v; }
+
+__device__ __forceinline__ f4v tiny_mma(const Frag<float>& a, const Frag<float>& b, f4v acc) {
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v.x, b.v.x, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v.y, b.v.y, acc, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a.v.z, b.v.z, acc, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a.v.w, b.v.w, acc, 0, 0, 0);
 }
+__device__ __forceinline__ f4v tiny_mma(const Frag<bf16_t>& a, const Frag<bf16_t>& b, f4v acc) {
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a.v), __builtin_bit_cast(bf16x8, b.v), acc, 0, 0, 0);
+}
+
+// A BatchNorm between two short pointwise layers is finished by the second of them.  Forward: x is the raw output of a layer whose statistics
+// are still partial sums; the operand is act(scale * x + shift) (+ x_add), what the block output holds.  Data gradient: x is the
+// gradient of such an output and x_add the output itself; the operand is the gradient of the raw output, k1 * x + k2 * x_add + k3.  Every
+// block sums the partials of all channels, the tiles of the first column write the operand to x_out, the first block the per-channel
+// results.  A launch of its own owned four channels over all rows, so each of its few CUs walked every row (a CU has some three cycles per
+// 128-byte line and row).  Two launches / one, us, fp32: 512 rows, 64 -> 384 forward 8.6 / 5.8, data gradient of 384 -> 64 8.5 / 5.4;
+// 2048 rows, 32 -> 192 12.1 / 7.4 and 13.7 / 6.7; bfloat16 about 480 rows, 64 -> 384 8.3 / 6.7.  What it costs the layer is the sums: 1.4 us
+// for 16 KB of partials, 3 us for 32 KB.
+struct TinyArgs : GemmArgs {
+  FastDiv dj;                // by jtiles
+  BnPending pend;            // partial == nullptr: x is read as it is; data gradient: partial, P, gamma, mean, invstd
+  const void* x_add;
+  void* x_out;
+  float *g_gamma, *g_beta;   // data gradient
+  double inv_M;
+  float eps, momentum;
+  const void* z_sum;         // data gradient with stats: the raw output whose gradient is written, statistics sum(out), sum(out * z_sum)
+};
+enum { kProChan = 96, kProBytes = 1 << 16 };
+
+// Sums of partial[P][2][C] in float64 (C a multiple of 8), then coef[.][c]: scale and shift, or k1, k2, k3.  A wavefront takes 32 neighbouring
+// values (a 128-byte line) of eight rows of partials at a time, S wavefronts share the rows of a line where there are more
+// wavefronts than lines.  fin: 4 * S rows of 2C, at most kProFin.
+enum { kProFin = 4 * 2 * kProChan };
+template <int MODE, int NW>
+__device__ __forceinline__ void tiny_finish(const TinyArgs& p, const int C, const bool write, double* fin, float (*coef)[kProChan]) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, q = lane & 7, pl = lane >> 3;
+  const int ng = (C + 15) / 16, S = ng >= NW ? 1 : NW >= 4 * ng ? 4 : NW >= 2 * ng ? 2 : 1;       // lines of a row, wavefronts to a line
+  // channels to the threads that add up and finish: tc threads each
+  const int tc = C * 8 <= 64 * NW ? 8 : C * 4 <= 64 * NW ? 4 : C * 2 <= 64 * NW ? 2 : 1;
+  const int ch = tid / tc, sub = tid & (tc - 1), c = ch < C ? ch : 0;
+  // what the finishing threads need is requested before the sums
+  float f0 = p.pend.gamma[c], f1, f2, f3, f4 = 0.f;
+  if (MODE == MODE_FWD) { f1 = p.pend.beta[c]; f2 = p.pend.run_mean[c]; f3 = p.pend.run_var[c]; }
+  else { f1 = p.pend.mean[c]; f2 = p.pend.invstd[c]; f3 = p.g_gamma[c]; f4 = p.g_beta[c]; }
+  const int P = p.pend.P;
+  for (int j = wave; j < ng * S; j += NW) {
+    const int g = S == 1 ? j : j % ng, sl = S == 1 ? 0 : j / ng, v0 = g * 32 + q * 4;
+    const bool in = v0 < 2 * C;
+    const float* src = p.pend.partial + (in ? v0 : 0);
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    constexpr int U = 4;
+    for (int r = sl * 8 + pl; r < P; r += U * 8 * S) {
+      float4 v[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) v[u] = ld4(src + (unsigned)(r + u * 8 * S < P ? r + u * 8 * S : r) * 2u * C);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const bool ok = r + u * 8 * S < P;
+        t[0] += ok ? (double)v[u].x : 0.0; t[1] += ok ? (double)v[u].y : 0.0; t[2] += ok ? (double)v[u].z : 0.0; t[3] += ok ? (double)v[u].w : 0.0;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {                          // eight rows -> four
+      const int2 w = __builtin_bit_cast(int2, t[e]);
+      const int2 o = make_int2(__builtin_amdgcn_update_dpp(0, w.x, 0x128, 0xF, 0xF, false), __builtin_amdgcn_update_dpp(0, w.y, 0x128, 0xF, 0xF, false));
+      t[e] += __builtin_bit_cast(double, o);
+    }
+    if (in && !(pl & 1)) {
+      double2* d = reinterpret_cast<double2*>(fin + (size_t)(sl * 4 + (pl >> 1)) * 2 * C + v0);
+      d[0] = make_double2(t[0], t[1]);
+      d[1] = make_double2(t[2], t[3]);
+    }
+  }
+  __syncthreads();
+  double s0 = 0.0, s1 = 0.0;
+  for (int l = sub; l < 4 * S; l += tc) { s0 += fin[l * 2 * C + c]; s1 += fin[l * 2 * C + C + c]; }
+  for (int o = 1; o < tc; o <<= 1) { s0 += __shfl_xor(s0, o, 64); s1 += __shfl_xor(s1, o, 64); }
+  asm volatile("" : "+v"(f0), "+v"(f1), "+v"(f2), "+v"(f3), "+v"(f4));      // first use: conversions must not move up to the loads
+  if (ch < C && sub == 0) {
+    if (MODE == MODE_FWD) {
+      finish_channel(p.pend, p.inv_M, c, s0, s1, f0, f1, f2, f3, p.eps, p.momentum, write, coef[0][c], coef[1][c]);
+    } else {
+      const double mu = f1, is = f2, k1 = (double)f0 * is, dgamma = is * (s1 - mu * s0);
+      const double k2 = -k1 * is * dgamma * p.inv_M, k3 = -k1 * s0 * p.inv_M - k2 * mu;
+      coef[0][c] = (float)k1; coef[1][c] = (float)k2; coef[2][c] = (float)k3;
+      if (write) { p.g_gamma[c] = f3 + (float)dgamma; p.g_beta[c] = f4 + (float)s0; }
+    }
+  }
+  __syncthreads();
+}
+
+// Operands are read through buffer descriptors: an element outside the problem is requested past the end and comes back as zero, so
+// a fragment costs one 32-bit offset and no branch.  (These kernels are as long as their instructions: 200 in front of the first load
+// took 1600 cycles, half of them exec masks, 64-bit addresses and zeroes for fragments that might not be loaded.)
+enum : uint32_t { kTinyPast = 0x80000000u };
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tiny_rsrc(const void* p, size_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00020000);
+}
+__device__ __forceinline__ uint4 buf_load16(__amdgpu_buffer_rsrc_t rs, uint32_t off) {
+  return __builtin_bit_cast(uint4, (u4v)__builtin_amdgcn_raw_buffer_load_b128(rs, (int)off, 0, 0));
+}
+__device__ __forceinline__ float4 buf_load4f(__amdgpu_buffer_rsrc_t rs, uint32_t off) { return __builtin_bit_cast(float4, buf_load16(rs, off)); }
+__device__ __forceinline__ void buf_load1(float& v, __amdgpu_buffer_rsrc_t rs, uint32_t off, int soff) {
+  v = __builtin_bit_cast(float, (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(rs, (int)off, soff, 0));
+}
+__device__ __forceinline__ void buf_load1(uint32_t& v, __amdgpu_buffer_rsrc_t rs, uint32_t off, int soff) {
+  v = (bf16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, (int)off, soff, 0);
+}
+__device__ __forceinline__ void frag_of(Frag<float>& r, uint4 v) { r.v = __builtin_bit_cast(float4, v); }
+__device__ __forceinline__ void frag_of(Frag<bf16_t>& r, uint4 v) { r.v = v; }
 
 // WT wavefronts share a tile's reduction (launch_tiny picks the number), a block of NW wavefronts works on NW / WT tiles
-template <typename T, int MODE, int WT, int NW>
-__device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int bid) {
-  constexpr int G = TinyStep<T>::G, KS = TinyStep<T>::KS, U = 4;
+template <typename T, int MODE, int WT, int NW, bool PRO = false>
+__device__ __forceinline__ void pw_gemm_tiny_body(const TinyArgs& p, const int bid) {
+  constexpr int G = TinyStep<T>::G, KS = TinyStep<T>::KS, U = 4, ES = sizeof(T);
+  static_assert(KS * ES == 64 && G * ES == 16, "a step is 64 bytes of a row, a fragment 16");
   constexpr int GROUPS = NW / WT;
-  __shared__ float red[WT > 1 ? GROUPS : 1][WT][16][17];
+  __shared__ float red_[WT > 1 && !PRO ? GROUPS * WT * 16 * 17 : 1];
+  __shared__ __attribute__((aligned(16))) double fin_[PRO ? kProFin : 1];
+  __shared__ __attribute__((aligned(16))) float coef[PRO ? 3 : 1][PRO ? kProChan : 1];
+  static_assert(!PRO || sizeof(fin_) >= sizeof(float) * GROUPS * WT * 16 * 17, "the tiles' sums take the place of the statistics'");
+  float (*red)[WT][16][17] = reinterpret_cast<float (*)[WT][16][17]>(PRO ? reinterpret_cast<float*>(fin_) : red_);
   __shared__ float sred[WT > 1 ? GROUPS : 1][2][16][17];
   if (MODE == MODE_DGRAD) __builtin_amdgcn_s_setprio(3);   // data-gradient chain: ahead of the weight-gradient stream's waves
   const int grp = (threadIdx.x >> 6) / WT, wave = (threadIdx.x >> 6) % WT, lane = threadIdx.x & 63;
   const int tile = bid * GROUPS + grp;
   const bool tile_ok = tile < p.jtiles * p.itiles;
-  const int jt = tile % p.jtiles, it = tile / p.jtiles;
-  const size_t i0 = (size_t)it * 16;
-  const int j0 = jt * 16;
+  const int it = (int)p.dj.div(tile), jt = tile - it * p.jtiles;
+  const int i0 = it * 16, j0 = jt * 16, M = (int)p.M;
   const int R = MODE == MODE_FWD ? p.K : p.N;       // reduction extent (a multiple of G)
   const int nj = MODE == MODE_FWD ? p.N : p.K;      // output columns
   const int nst = (R + KS - 1) / KS;
   const int sb = wave * nst / WT, se = (wave + 1) * nst / WT;
   const int l16 = lane & 15, kg = (lane >> 4) * G;
-  const size_t row = i0 + l16;
-  const int col = j0 + l16;
-  const bool row_ok = tile_ok && row < p.M, col_ok = tile_ok && col < nj;
-  const T* X = reinterpret_cast<const T*>(p.x) + row * (size_t)R;
-  const T* W = reinterpret_cast<const T*>(p.y);
-  const bool view = MODE == MODE_FWD && p.view.scale != nullptr;
+  const int row = i0 + l16, col = j0 + l16;
+  const bool row_ok = tile_ok && row < M, col_ok = tile_ok && col < nj;
+  const bool view = MODE == MODE_FWD && !PRO && p.view.scale != nullptr;
   const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
+  const __amdgpu_buffer_rsrc_t bx = tiny_rsrc(p.x, (size_t)M * R * ES), bw = tiny_rsrc(p.y, (size_t)R * nj * ES);
+  const __amdgpu_buffer_rsrc_t bx2 = tiny_rsrc(PRO && p.x_add ? p.x_add : p.x, (size_t)M * R * ES);
+  const __amdgpu_buffer_rsrc_t bsc = tiny_rsrc(p.view.scale, (size_t)R * 4), bsh = tiny_rsrc(p.view.shift, (size_t)R * 4);
+  const int kend = se * KS < R ? se * KS : R;
+  // byte offsets at step 0 (PAST stays past the end when a step's offset is added)
+  const uint32_t ox = row_ok ? (uint32_t)(row * R + kg) * ES : kTinyPast;
+  const uint32_t ow = !col_ok ? kTinyPast : MODE == MODE_FWD ? (uint32_t)(col * R + kg) * ES : (uint32_t)(kg * nj + col) * ES;
+
   // the output elements this thread writes after the reduction (WT == 1: its four accumulators, else one); what is added
   // to them there (residual, bias) is requested now: a load at the end of the kernel would be one more round trip on the
   // launch-latency path
   constexpr int NO = WT == 1 ? 4 : 1;
   const int orow = WT == 1 ? 4 * (lane >> 4) : (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
-  const size_t ig = i0 + orow;
-  const int jg = j0 + ocol;
+  const int ig = i0 + orow, jg = j0 + ocol;
+  const uint32_t oo = (uint32_t)(ig * nj + jg) * ES;       // a row further down: nj elements on, past the end in the last tile
   bool in[NO];
-  float addend[NO];
+  typename Elem<T>::R add_r[NO], zs_r[NO];
+  float bias = 0.f;
 #pragma unroll
-  for (int o = 0; o < NO; ++o) {
-    in[o] = tile_ok && ig + o < p.M && jg < nj && (WT <= 4 || wave < 4);
-    addend[o] = 0.f;
-    if (MODE == MODE_FWD) { if (p.bias && in[o]) addend[o] = p.bias[jg]; }
-    else if (p.res && in[o]) addend[o] = to_f32(reinterpret_cast<const T*>(p.res)[(ig + o) * p.K + jg]);
+  for (int o = 0; o < NO; ++o) in[o] = tile_ok && ig + o < M && jg < nj && (WT <= 4 || wave < 4);
+  const bool with_res = MODE == MODE_DGRAD && p.res != nullptr, with_z = MODE == MODE_DGRAD && p.stats != nullptr;
+  if (MODE == MODE_FWD) {
+    if (p.bias && in[0]) bias = p.bias[jg];
+  } else {
+    if (with_res) {
+      const __amdgpu_buffer_rsrc_t br = tiny_rsrc(p.res, (size_t)M * nj * ES);
+#pragma unroll
+      for (int o = 0; o < NO; ++o) buf_load1(add_r[o], br, in[o] ? oo : kTinyPast, o * nj * ES);
+    }
+    if (with_z) {
+      const __amdgpu_buffer_rsrc_t bz = tiny_rsrc(p.z_sum, (size_t)M * nj * ES);
+#pragma unroll
+      for (int o = 0; o < NO; ++o) buf_load1(zs_r[o], bz, in[o] ? oo : kTinyPast, o * nj * ES);
+    }
   }
 
   f4v acc = {0.f, 0.f, 0.f, 0.f}, step[U];      // step: WT == 1 (one round), a chain for each step
+  Frag<T> xr[U], er[PRO ? U : 1], br[U];        // er: the operand's second tensor (PRO)
+  float sc[U][G], sh[U][G];
+  typename Elem<T>::R bs[U][G];                 // data gradient: single elements of W down a column
+  auto request = [&](const int s) __attribute__((always_inline)) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const bool inb = (s + u) * KS + kg < kend;
+      const uint32_t ko = (uint32_t)(s + u) * 64u;
+      frag_of(xr[u], buf_load16(bx, inb ? ox + ko : kTinyPast));
+      if (PRO) frag_of(er[PRO ? u : 0], buf_load16(bx2, inb ? ox + ko : kTinyPast));
+      if (MODE == MODE_FWD) {
+        frag_of(br[u], buf_load16(bw, inb ? ow + ko : kTinyPast));
+        if (view) {
+          const uint32_t o = inb ? (uint32_t)((s + u) * KS + kg) * 4u : kTinyPast;
+#pragma unroll
+          for (int e = 0; e < G; e += 4) {
+            *reinterpret_cast<float4*>(sc[u] + e) = buf_load4f(bsc, o + 4 * e);
+            *reinterpret_cast<float4*>(sh[u] + e) = buf_load4f(bsh, o + 4 * e);
+          }
+        }
+      } else {
+#pragma unroll
+        for (int e = 0; e < G; ++e) buf_load1(bs[u][e], bw, inb ? ow : kTinyPast, ((s + u) * KS + e) * nj * ES);
+      }
+    }
+  };
+  request(sb);
+  if constexpr (PRO) tiny_finish<MODE, NW>(p, R, bid == 0, fin_, reinterpret_cast<float (*)[kProChan]>(coef));      // while the first round travels
   for (int s = sb; s < se; s += U) {
-    float a[U][G], b[U][G], sc[U][G], sh[U][G];
-    FragRaw<T> ar[U], br[U];
-    T bs[U][G];                                // data gradient: single elements of W down a column
+    if (WT > 1 && s != sb) request(s);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int k = (s + u) * KS + kg;
-      const bool ok = s + u < se && k < R;
-      frag_zero(ar[u]); frag_zero(br[u]);
+      Frag<T> a = xr[u], b = br[u];
+      if (MODE == MODE_DGRAD) frag_of(b, bs[u]);
+      if constexpr (PRO) {
+        const bool inb = k < kend;
+        const int c = inb ? k : 0;
+        float x[G], y[G], k1[G], k2[G], k3[G];
+        frag_unpack(xr[u], x);
+        frag_unpack(er[u], y);
 #pragma unroll
-      for (int e = 0; e < G; ++e) { sc[u][e] = 1.f; sh[u][e] = 0.f; }
-      if (ok && row_ok) {
-        frag_load(ar[u], X + k);
-        if (view) {
-          load_frag(p.view.scale + k, sc[u]);
-          load_frag(p.view.shift + k, sh[u]);
-          if (G == 8) { load_frag(p.view.scale + k + 4, sc[u] + 4); load_frag(p.view.shift + k + 4, sh[u] + 4); }
+        for (int e = 0; e < G; e += 4) {
+          *reinterpret_cast<float4*>(k1 + e) = ld4(&coef[0][c + e]);
+          *reinterpret_cast<float4*>(k2 + e) = ld4(&coef[1][c + e]);
+          if (MODE == MODE_DGRAD) *reinterpret_cast<float4*>(k3 + e) = ld4(&coef[2][c + e]);
         }
-      }
-      if (MODE == MODE_FWD) {
-        if (ok && col_ok) frag_load(br[u], W + (size_t)col * p.K + k);
-      } else {
-        // unconditional, from rows / a column that exist (R is a multiple of G): zeroed below when out of range
-        const int kc = ok ? k : 0, cc = col_ok ? col : 0;
-#pragma unroll
-        for (int e = 0; e < G; ++e) bs[u][e] = W[(size_t)(kc + e) * p.K + cc];
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      frag_unpack(ar[u], a[u]);
-      if (MODE == MODE_FWD) {
-        frag_unpack(br[u], b[u]);
-      } else {
-        const bool okb = s + u < se && (s + u) * KS + kg < R && col_ok;
-#pragma unroll
-        for (int e = 0; e < G; ++e) b[u][e] = okb ? to_f32(bs[u][e]) : 0.f;
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      if (view) {
-        const bool live = s + u < se && (s + u) * KS + kg < R && row_ok;   // padding stays exactly zero
 #pragma unroll
         for (int e = 0; e < G; ++e) {
-          float y = round_to<T>(clamp_act(fmaf(a[u][e], sc[u][e], sh[u][e]), lo, hi));
-          a[u][e] = live ? y : 0.f;
+          if (MODE == MODE_FWD) {
+            x[e] = clamp_act(fmaf(x[e], k1[e], k2[e]), lo, hi);
+            if (p.x_add) x[e] = round_to<T>(x[e]) + y[e];
+          } else {
+            x[e] = fmaf(k1[e], x[e], fmaf(k2[e], y[e], k3[e]));
+          }
         }
+        frag_pack(a, x);
+        if (jt == 0 && inb && row_ok) frag_store(reinterpret_cast<T*>(p.x_out) + (size_t)row * R + k, a);
+        if (!inb) frag_zero(a);
+      } else if (view) {
+        // past the end of the reduction scale and shift are zero, and so is the operand; a row past M is not written
+        float x[G];
+        frag_unpack(xr[u], x);
+#pragma unroll
+        for (int e = 0; e < G; ++e) x[e] = clamp_act(fmaf(x[e], sc[u][e], sh[u][e]), lo, hi);
+        frag_pack(a, x);
       }
-      if constexpr (WT == 1) step[u] = tiny_mma(a[u], b[u], f4v{0.f, 0.f, 0.f, 0.f}, T());
-      else acc = tiny_mma(a[u], b[u], acc, T());
+      if constexpr (WT == 1) step[u] = tiny_mma(a, b, f4v{0.f, 0.f, 0.f, 0.f});
+      else acc = tiny_mma(a, b, acc);
     }
     // the steps' sums are added in their order, as those of four wavefronts are: one chain through all of them would be up to 64 fp32
     // additions long instead of 16 (64 -> 384 channels, fp32: 1.4e-7 off in the 2-norm instead of 8.4e-8)
     if constexpr (WT == 1) acc = ((step[0] + step[1]) + step[2]) + step[3];
+  }
+  float addend[NO], zs[NO];
+#pragma unroll
+  for (int o = 0; o < NO; ++o) {
+    addend[o] = MODE == MODE_FWD ? bias : with_res ? elem_f32(add_r[o]) : 0.f;
+    zs[o] = with_z ? elem_f32(zs_r[o]) : 0.f;
   }
 
   // register r of lane l is C[4*(l/16) + r][l%16]
@@ -1105,35 +1260,34 @@ __device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int b
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const float v = acc[r] + addend[r];
-      if (in[r]) reinterpret_cast<T*>(p.out)[(ig + r) * nj + jg] = from_f32<T>(v);
+      if (in[r]) reinterpret_cast<T*>(p.out)[(size_t)(ig + r) * nj + jg] = from_f32<T>(v);
       const float sv = in[r] ? round_to<T>(v) : 0.f;      // statistics of the values as stored
       s1 += sv;
-      s2 += sv * sv;
+      s2 += sv * (MODE == MODE_FWD ? sv : zs[r]);
     }
-    if (MODE == MODE_FWD && p.stats) {
+    if (p.stats) {
       s1 += __shfl_xor(s1, 16, 64); s2 += __shfl_xor(s2, 16, 64);
       s1 += __shfl_xor(s1, 32, 64); s2 += __shfl_xor(s2, 32, 64);
-      if (lane < 32 && tile_ok && jg < nj) p.stats[((size_t)it * 2 + (lane >> 4)) * p.N + jg] = lane < 16 ? s1 : s2;
+      if (lane < 32 && tile_ok && jg < nj) p.stats[((size_t)it * 2 + (lane >> 4)) * nj + jg] = lane < 16 ? s1 : s2;
     }
     return;
   }
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[grp][wave][4 * (lane >> 4) + r][l16] = acc[r];
   __syncthreads();
-  asm volatile("" : "+v"(addend[0]));       // first use: its conversion stays here
   const bool writer = WT <= 4 || wave < 4;  // 256 threads of a tile hold its elements
   float v = 0.f;
   if (writer) {
 #pragma unroll
     for (int q = 0; q < WT; ++q) v += red[grp][q][orow][ocol];
     v += addend[0];
-    if (in[0]) reinterpret_cast<T*>(p.out)[ig * nj + jg] = from_f32<T>(v);
+    if (in[0]) reinterpret_cast<T*>(p.out)[(size_t)ig * nj + jg] = from_f32<T>(v);
   }
-  if (MODE == MODE_FWD && p.stats) {
+  if (p.stats) {
     const float sv = in[0] ? round_to<T>(v) : 0.f;        // statistics of the values as stored
     if (writer) {
       sred[grp][0][orow][ocol] = sv;
-      sred[grp][1][orow][ocol] = sv * sv;
+      sred[grp][1][orow][ocol] = sv * (MODE == MODE_FWD ? sv : zs[0]);
     }
     __syncthreads();
     if (wave == 0 && lane < 32 && tile_ok) {
@@ -1141,7 +1295,7 @@ __device__ __forceinline__ void pw_gemm_tiny_body(const GemmArgs& p, const int b
       float tot = 0.f;
 #pragma unroll
       for (int rr = 0; rr < 16; ++rr) tot += sred[grp][sq][rr][c];
-      if (j0 + c < p.N) p.stats[((size_t)it * 2 + sq) * p.N + j0 + c] = tot;
+      if (j0 + c < nj) p.stats[((size_t)it * 2 + sq) * nj + j0 + c] = tot;
     }
   }
 }
@@ -1219,15 +1373,15 @@ __device__ __forceinline__ void pw_wgrad_tiny_body(const GemmArgs& p, const int 
   }
 }
 
-template <typename T, int MODE, int WT, int NW>
-__global__ __launch_bounds__(64 * NW) void pw_gemm_tiny_k(GemmArgs p) { pw_gemm_tiny_body<T, MODE, WT, NW>(p, xcd_logical_block()); }   // the column tiles of a row panel share an L2
+template <typename T, int MODE, int WT, int NW, bool PRO>
+__global__ __launch_bounds__(64 * NW) void pw_gemm_tiny_k(TinyArgs p) { pw_gemm_tiny_body<T, MODE, WT, NW, PRO>(p, xcd_logical_block()); }   // the column tiles of a row panel share an L2
 template <typename T>
 __global__ __launch_bounds__(256) void pw_wgrad_tiny_k(GemmArgs p, int K_out) { pw_wgrad_tiny_body<T, 4>(p, K_out, blockIdx.x); }
 // data gradient and weight gradient of one short layer in one launch: both read the same dZ, their tiles are
 // independent, and for these sizes a launch costs more than either of them.  NW wavefronts per block: with many
 // pixels the weight-gradient tiles are few and each walks all pixels, so 16 wavefronts share that walk.
 template <typename T, int NW>
-__global__ __launch_bounds__(64 * NW) void pw_bwd_tiny_k(GemmArgs pd, GemmArgs pw, int K_out, int n_dgrad) {
+__global__ __launch_bounds__(64 * NW) void pw_bwd_tiny_k(TinyArgs pd, GemmArgs pw, int K_out, int n_dgrad) {
   if ((int)blockIdx.x < n_dgrad) pw_gemm_tiny_body<T, MODE_DGRAD, 4, NW>(pd, blockIdx.x);
   else pw_wgrad_tiny_body<T, NW>(pw, K_out, blockIdx.x - n_dgrad);
 }
@@ -1243,7 +1397,7 @@ static bool tiny_ok(int dt, size_t M, int R, int ncols, bool stats) {
 }
 
 template <int MODE>
-static void launch_tiny(int dt, hipStream_t st, GemmArgs& a, int ncols) {
+static void launch_tiny(int dt, hipStream_t st, TinyArgs& a, int ncols) {
   a.jtiles = (ncols + 15) / 16;
   a.itiles = (int)((a.M + 15) / 16);
   a.nranges = a.itiles;
@@ -1252,17 +1406,19 @@ static void launch_tiny(int dt, hipStream_t st, GemmArgs& a, int ncols) {
   // or two.  MobileNetV2 at 32x32, batch 32, fp32: 57 launches a step, 303 us with four wavefronts per tile for all.  Up to four
   // steps a tile to itself (no LDS, no barrier, a quarter of the blocks; 14 launches, 59 us); above sixteen steps eight
   // wavefronts (24 launches: 134 us, with four 150, with sixteen 139).
+  a.dj = FastDiv::of(a.jtiles);
   const int R = MODE == MODE_FWD ? a.K : a.N, nst = (R + (dt == 0 ? 15 : 31)) / (dt == 0 ? 16 : 32);
   const unsigned tiles = (unsigned)((size_t)a.jtiles * a.itiles);
-#define FTP_TINY(WT, NW)                                                                                                              \
+#define FTP_TINY(WT, NW, PRO)                                                                                                         \
   do {                                                                                                                                \
     const dim3 grid((tiles + (NW) / (WT) - 1) / ((NW) / (WT)));                                                                       \
-    if (dt == 0) hipLaunchKernelGGL((pw_gemm_tiny_k<float, MODE, WT, NW>), grid, dim3(64 * (NW)), 0, st, a);                          \
-    else hipLaunchKernelGGL((pw_gemm_tiny_k<bf16_t, MODE, WT, NW>), grid, dim3(64 * (NW)), 0, st, a);                                 \
+    if (dt == 0) hipLaunchKernelGGL((pw_gemm_tiny_k<float, MODE, WT, NW, PRO>), grid, dim3(64 * (NW)), 0, st, a);                     \
+    else hipLaunchKernelGGL((pw_gemm_tiny_k<bf16_t, MODE, WT, NW, PRO>), grid, dim3(64 * (NW)), 0, st, a);                            \
   } while (0)
-  if (nst <= 4) FTP_TINY(1, 4);
-  else if (nst <= 16) FTP_TINY(4, 4);
-  else FTP_TINY(8, 8);
+  if (a.pend.partial) FTP_TINY(1, 4, true);           // pw_pro_ok: at most four steps
+  else if (nst <= 4) FTP_TINY(1, 4, false);
+  else if (nst <= 16) FTP_TINY(4, 4, false);
+  else FTP_TINY(8, 8, false);
 #undef FTP_TINY
 }
 
@@ -1312,9 +1468,28 @@ static void plan_rows(size_t M, int ncols, int R, GemmArgs* a, bool* small) {
   a->nranges = (a->itiles + a->tiles_per_range - 1) / a->tiles_per_range;
 }
 
+// Four steps at most, a tile to a wavefront.  Above, tiles of several wavefronts and partials of more channels cost more than the launch:
+// fp32 512 rows, 96 channels (2 launches / 1) 9.5 / 12.0 us forward, 9.3 / 10.2 backward, 128 rows, 160 channels 7.9 / 9.7 and 7.5 / 8.9;
+// bfloat16 96 channels 8.5 / 8.0, 128 the same as two.
+int pw_pro_ok(int dt, size_t M, int R, int ncols) {
+  const size_t P = (M + 15) / 16;
+  return R % 8 == 0 && R <= (dt == 0 ? 64 : 96) && tiny_ok(dt, M, R, ncols, true) && P * 2 * R * sizeof(float) <= kProBytes;
+}
+int pw_dgrad_sums_ok(int dt, size_t M, int K, int N) { return tiny_ok(dt, M, N, K, true); }
+
+void pw_fwd_pro(int dt, hipStream_t st, const BnPending& pend, HView x, const void* x_add, void* x_out, float eps, float momentum, const void* w,
+                size_t M, int K, int N, void* z, float* stats, int* P_out) {
+  TinyArgs a{};
+  a.x = x.z; a.y = w; a.view = View{x.z, x.scale, x.shift, x.act}; a.out = z; a.stats = stats; a.M = M; a.K = K; a.N = N;
+  a.pend = pend; a.x_add = x_add; a.x_out = x_out; a.inv_M = 1.0 / (double)M; a.eps = eps; a.momentum = momentum;
+  KScope ks(st, "pw_fwd", ((double)M * K * (x_add ? 3.0 : 2.0) + (double)M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
+  launch_tiny<MODE_FWD>(dt, st, a, N);
+  *P_out = a.nranges;
+}
+
 void pw_fwd(int dt, hipStream_t st, HView av, const void* w, const float* bias, size_t M, int K, int N,
             void* z, float* stats, int* P_out) {
-  GemmArgs a{};
+  TinyArgs a{};
   a.x = av.z; a.y = w; a.view = View{av.z, av.scale, av.shift, av.act};
   a.bias = bias; a.out = z; a.stats = stats; a.M = M; a.K = K; a.N = N;
   KScope ks(st, "pw_fwd", ((double)M * K + (double)M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
@@ -1330,13 +1505,23 @@ void pw_fwd(int dt, hipStream_t st, HView av, const void* w, const float* bias, 
   launch<MODE_FWD>(dt, st, a, small);
 }
 
+void pw_dgrad_pro(int dt, hipStream_t st, const BnPending& sums, const BnBwdIn& bn, void* dz, const void* w, size_t M, int K, int N, void* dA) {
+  TinyArgs a{};
+  a.x = bn.dA; a.x_add = bn.out.z; a.x_out = dz; a.y = w; a.out = dA; a.M = M; a.K = K; a.N = N;
+  a.pend = sums; a.g_gamma = bn.g_gamma; a.g_beta = bn.g_beta; a.inv_M = 1.0 / (double)M;
+  KScope ks(st, "pw_dgrad", ((double)M * K + 3.0 * M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
+  launch_tiny<MODE_DGRAD>(dt, st, a, K);
+}
+
 void pw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K,
-              int N, void* dA) {
-  GemmArgs a{};
+              int N, void* dA, const void* z_sum, float* sums, int* P_out) {
+  TinyArgs a{};
   a.x = dz; a.y = w; a.res = res; a.out = dA; a.M = M; a.K = K; a.N = N;
   KScope ks(st, "pw_dgrad", ((double)M * K * (res ? 2.0 : 1.0) + (double)M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
   if (tiny_ok(dt, M, N, K, false)) {
+    a.z_sum = z_sum; a.stats = sums;
     launch_tiny<MODE_DGRAD>(dt, st, a, K);
+    if (sums) *P_out = a.nranges;
     return;
   }
   if (pw_deep_ok(dt, M, N, K, true)) { pw_dgrad_deep(st, dz, w, res, M, K, N, dA); return; }
@@ -1718,9 +1903,10 @@ void fc_bwd(int dt, hipStream_t st, const void* d, HView in, const void* w, int 
 void pw_bwd(int dt, hipStream_t st, const void* dz, const void* w, const void* res, HView av, size_t M, int K, int N,
             float* ws, float* g_w, void* dA) {
   if (M <= 2048 && tiny_ok(dt, M, N, K, false)) {
-    GemmArgs d{}, g{};
+    TinyArgs d{};
+    GemmArgs g{};
     d.x = dz; d.y = w; d.res = res; d.out = dA; d.M = M; d.K = K; d.N = N;
-    d.jtiles = (K + 15) / 16; d.itiles = (int)((M + 15) / 16); d.nranges = d.itiles; d.tiles_per_range = 1;
+    d.jtiles = (K + 15) / 16; d.itiles = (int)((M + 15) / 16); d.nranges = d.itiles; d.tiles_per_range = 1; d.dj = FastDiv::of(d.jtiles);
     g.x = dz; g.y = av.z; g.view = View{av.z, av.scale, av.shift, av.act}; g.out = g_w; g.M = M; g.K = K; g.N = N;
     g.jtiles = (K + 15) / 16; g.itiles = (N + 15) / 16;
     const int nd = d.jtiles * d.itiles, nw = g.jtiles * g.itiles;

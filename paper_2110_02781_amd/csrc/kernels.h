@@ -217,9 +217,18 @@ void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& 
 // partial sums stats[P][2][N] of the stored Z and Z*Z (same layout as bn_stats), P into *P_out
 void pw_fwd(int dt, hipStream_t st, HView a, const void* w, const float* bias, size_t M, int K, int N,
             void* z, float* stats, int* P_out);
-// dA[M][K] = dZ[M][N] * W[N][K] (+ res[M][K])
+// Short layers whose operand is formed on the way in (pw_pro_ok: R = reduction extent).  Forward: x is a raw output whose BatchNorm is
+// still partial sums; A = act(scale * x + shift) (+ x_add), also written to x_out.
+int pw_pro_ok(int dt, size_t M, int R, int ncols);
+void pw_fwd_pro(int dt, hipStream_t st, const BnPending& pend, HView x, const void* x_add, void* x_out, float eps, float momentum, const void* w,
+                size_t M, int K, int N, void* z, float* stats, int* P_out);
+// dA[M][K] = dZ[M][N] * W[N][K] (+ res[M][K]).  sums != nullptr (only if pw_dgrad_sums_ok): also the partial sums [*P_out][2][K] that
+// bn_bwd_reduce would compute for a BatchNorm without activation whose raw output is z_sum and whose output's gradient is dA
+int pw_dgrad_sums_ok(int dt, size_t M, int K, int N);
 void pw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K,
-              int N, void* dA);
+              int N, void* dA, const void* z_sum = nullptr, float* sums = nullptr, int* P_out = nullptr);
+// the consumer of such sums (pw_pro_ok): BatchNorm backward of bn (no activation), dz written, then dA = dz * W
+void pw_dgrad_pro(int dt, hipStream_t st, const BnPending& sums, const BnBwdIn& bn, void* dz, const void* w, size_t M, int K, int N, void* dA);
 // g_w[N][K] += dZ[M][N]^T * A'[M][K]
 size_t pw_wgrad_ws(size_t M, int K, int N);
 // K_out >= 0: g_w is [N][K_out] and the last K - K_out columns of A are zero padding

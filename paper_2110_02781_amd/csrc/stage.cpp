@@ -720,10 +720,17 @@ static void build_views(const ftp_stage* s, const Slot& sl, Views* v) {
   }
 }
 
+// A block output that nobody has written yet: the raw output of its project layer, the statistics as partial sums, the residual
+// (nullptr: none) and where it goes.  The pointwise layer behind it forms it on the way in (pw_fwd_pro).
+struct OutPending { BnPending pend{}; HView z{}; const void* res = nullptr; void* out = nullptr; };
+
+// the second half of the partial sums' buffer, for a layer that reads the first half while it leaves its own
+static float* other_partials(const ftp_stage* s) { return s->bn_part + (size_t)kBnPartials / 2 * 2 * s->max_c; }
+
 // pend (in/out): on entry the unfinished BatchNorm of `in` (partial == nullptr: none); on exit, when
 // defer is set and the statistics of this layer were left as partial sums, their description
 static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HView in, const WeightSet& W, hipStream_t st,
-                        BnPending* pend = nullptr, bool defer = false) {
+                        BnPending* pend = nullptr, bool defer = false, OutPending* block = nullptr) {
   const Sub& sb = p.info->subs[k];
   ConvGeom g = sb.g; g.N = s->batch;
   void* z = sl.stash + p.z_off[k];
@@ -745,15 +752,24 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
     return;
   }
   if (sb.type == SUB_PW) {
-    pw_fwd(s->dt, st, in, w, nullptr, M, g.Cin, g.Cout, z, s->bn_part, &P);   // statistics in the epilogue
+    float* part = s->bn_part;
+    if (block && block->pend.partial) {
+      part = other_partials(s);
+      pw_fwd_pro(s->dt, st, block->pend, block->z, block->res, block->out, kBnEps, s->bn_mom, w, M, g.Cin, g.Cout, z, part, &P);
+      block->pend.partial = nullptr;
+    } else {
+      pw_fwd(s->dt, st, in, w, nullptr, M, g.Cin, g.Cout, z, part, &P);       // statistics in the epilogue
+    }
     if (defer && pend) {
-      *pend = BnPending{s->bn_part, P, M, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv};
+      *pend = BnPending{part, P, M, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv};
       return;
     }
+    bn_finalize(st, part, P, M, C, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv, kBnEps, s->bn_mom);
+    return;
   } else if (p.axis[k]) {
     // the partials of the input's BatchNorm, if it is pending, are read by every block: this layer's go to the other half
     float* part = s->bn_part;
-    if (pend && pend->partial == part) part += (size_t)kBnPartials / 2 * 2 * s->max_c;
+    if (pend && pend->partial == part) part = other_partials(s);
     const BnPending none{};
     conv1d_fwd(s->dt, st, in, pend ? *pend : none, kBnEps, s->bn_mom, w, g, z, part, &P);
     if (pend) pend->partial = nullptr;
@@ -780,8 +796,16 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
   bn_finalize(st, s->bn_part, P, M, C, gamma, beta, stt, stt + C, stt + 2 * C, stt + 3 * C, rm, rv, kBnEps, s->bn_mom);
 }
 
+// the unit behind unit i of the stage starts with a pointwise layer that can form unit i's output
+static bool next_forms_block(const ftp_stage* s, size_t i) {
+  if (i + 1 >= s->plan.size() || s->plan[i + 1].info->subs.empty()) return false;
+  const Sub& n = s->plan[i + 1].info->subs[0];
+  return n.type == SUB_PW && pw_pro_ok(s->dt, (size_t)s->batch * n.g.Hout * n.g.Wout, n.g.Cin, n.g.Cout);
+}
+
 // every unit of the stage over the input at offset 0 of the slot's stash, with the weights W
 static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet& W, hipStream_t st) {
+  OutPending block{};      // the output of a short block, left to the pointwise layer behind it
   BnPending carry{};       // a short 1-D convolution leaves its statistics to the short 1-D convolution or the average behind it
   for (size_t i = 0; i < s->plan.size(); ++i) {
     const UnitPlan& p = s->plan[i];
@@ -803,7 +827,7 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
         };
         const bool defer = small1d(u) && i + 1 < s->plan.size() &&
                            (s->plan[i + 1].info->d.kind == FTP_UNIT_GAP || small1d(*s->plan[i + 1].info));
-        sub_forward(s, sl, p, 0, in, W, st, &carry, defer);
+        sub_forward(s, sl, p, 0, in, W, st, &carry, defer, &block);
         break;
       }
       case FTP_UNIT_INVRES: {
@@ -819,10 +843,12 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
           // ... and the project layer leaves them to the kernel that writes the block output
           const size_t Mo = (size_t)s->batch * u.outH * u.outW;
           if (k + 1 == u.subs.size() && u.subs[k].type == SUB_PW) defer = bn_finalize_apply_small_ok(Mo, u.outC) != 0;
-          sub_forward(s, sl, p, k, h, W, st, &pend, defer);
+          sub_forward(s, sl, p, k, h, W, st, &pend, defer, k == 0 ? &block : nullptr);
           h = v.sub_out[i][k];
         }
-        if (pend.partial) {
+        if (pend.partial && next_forms_block(s, i)) {
+          block = OutPending{pend, h, u.residual ? in.z : nullptr, sl.stash + p.out_off};
+        } else if (pend.partial) {
           bn_finalize_apply_small(s->dt, st, pend, h.z, (size_t)s->batch * u.outH * u.outW, u.outC, h.act, kBnEps, s->bn_mom,
                                   u.residual ? in.z : nullptr, sl.stash + p.out_off);
           pend.partial = nullptr;
@@ -1012,10 +1038,31 @@ static size_t dz_size(const ftp_stage* s, const Sub& sb) {
   return align_up((size_t)s->batch * sb.g.Hout * sb.g.Wout * sb.g.Cout * s->es, 256);
 }
 
+// A short project layer (no activation, k the last of its block) whose BatchNorm backward is done on the way into its data gradient,
+// from sums that the layer behind has left: dIn is wanted, the weight gradient waits for the end of the call.
+static bool takes_sums(const ftp_stage* s, const UnitPlan& p, size_t k) {
+  const UnitInfo& u = *p.info;
+  const Sub& sb = u.subs[k];
+  const size_t M = (size_t)s->batch * sb.g.Hout * sb.g.Wout;
+  return s->defers && u.d.kind == FTP_UNIT_INVRES && k + 1 == u.subs.size() && sb.type == SUB_PW && !p.at_once[k] &&
+         bn_bwd_small_ok(M, sb.g.Cout) && pw_pro_ok(s->dt, M, sb.g.Cout, sb.g.Cin);
+}
+// the raw output of the project layer in front of unit i, where unit i's first layer can leave those sums; else nullptr
+static const void* leaves_sums(const ftp_stage* s, const Views& v, size_t i) {
+  if (i == 0) return nullptr;
+  const UnitPlan& p = s->plan[i];
+  const UnitPlan& q = s->plan[i - 1];
+  if (p.info->subs.empty() || p.info->subs[0].type != SUB_PW || p.at_once[0] || q.info->subs.empty()) return nullptr;
+  const ConvGeom& g = p.info->subs[0].g;
+  if (!takes_sums(s, q, q.info->subs.size() - 1) || !pw_dgrad_sums_ok(s->dt, (size_t)s->batch * g.Hout * g.Wout, g.Cin, g.Cout)) return nullptr;
+  return v.sub_out[i - 1].back().z;
+}
+
 // part: BWD_FROM_DZ in a stage that defers, where the caller has taken the layer's places
+// z_sum: dIn is the gradient of a BatchNorm without activation over this tensor, whose backward can use the sums (leaves_sums)
 static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, const void* dA, HView in, HView out,
                         void* dIn, const void* res, const WeightSet& W, hipStream_t st, int mode = BWD_FULL,
-                        bool unit_fork = false, float* part = nullptr) {
+                        bool unit_fork = false, float* part = nullptr, const void* z_sum = nullptr) {
   const Sub& sb = p.info->subs[k];
   ConvGeom g = sb.g; g.N = s->batch;
   int C = g.Cout;
@@ -1067,6 +1114,14 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       dz = s->gbuf[b ? 4 : 2];
     }
     const bool small = bn_bwd_small_ok(M, C) != 0;
+    if (noted && s->bwd_sums_of == dA && takes_sums(s, p, k)) {
+      const BnPending sums{s->bn_part, s->bwd_sums_P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
+      const BnBwdIn bn{dA, out, nullptr, nullptr, nullptr, s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off};
+      s->bwd_sums_of = nullptr;
+      s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, s->grads + p.p_off + sb.w_off});
+      pw_dgrad_pro(s->dt, st, sums, bn, dz, conv_w(s, W, p.p_off + sb.w_off), M, g.Cin, g.Cout, dIn);
+      return FTP_OK;
+    }
     if (!small) {
       int P = 0;
       if (s->bwd_sums_of == dA) P = s->bwd_sums_P;          // the producer of dA has left the sums
@@ -1133,7 +1188,8 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       else pw_wgrad(s->dt, st, dz, in, M, g.Cin, g.Cout, part, gw);
     } else if (sb.type == SUB_PW) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
-      if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);
+      if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn, z_sum, z_sum ? s->bn_part : nullptr, &s->bwd_sums_P);
+      if (z_sum) s->bwd_sums_of = dIn;
     } else if (sb.type == SUB_DW) {
       s->q_dw.push_back(DwWgradJob{dz, in, g, part, gw});
       if (dIn) run_dw_dgrad();
@@ -1267,6 +1323,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
   }
   s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
   s->dz_used = s->part_used = 0;
+  s->bwd_sums_of = nullptr;
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
   const void* d = dy_dev ? dy_dev : sl.dlogits;     // gradient of the current unit's output (read only)
   int flip = 0;
@@ -1305,7 +1362,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
         else if (next) gap_bwd(s->dt, st, d, s->batch, u.inH * u.inW, u.inC, next);
         break;
       case FTP_UNIT_CONV:
-        if ((rc = sub_backward(s, sl, p, 0, d, in, v.sub_out[i][0], next, nullptr, W, st))) return rc;
+        if ((rc = sub_backward(s, sl, p, 0, d, in, v.sub_out[i][0], next, nullptr, W, st, BWD_FULL, false, nullptr, leaves_sums(s, v, i)))) return rc;
         break;
       case FTP_UNIT_INVRES: {
         size_t ns = u.subs.size();
@@ -1332,10 +1389,12 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
           dw_bwd_small(s->dt, st, nullptr, bo, conv_w(s, W, p.p_off + s1.w_off), v.sub_out[i][0], gd, W.w32 + p.p_off + s0.gamma_off, st0,
                        st0 + s0.g.Cout, s->grads + p.p_off + s1.w_off, s->grads + p.p_off + s0.gamma_off,
                        s->grads + p.p_off + s0.beta_off, dz1);
-          if ((rc = sub_backward(s, sl, p, 0, dz1, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FROM_DZ, false, at.part))) return rc;
+          if ((rc = sub_backward(s, sl, p, 0, dz1, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FROM_DZ, false, at.part,
+                                 leaves_sums(s, v, i)))) return rc;
         } else if (ns == 3) {
           if ((rc = sub_backward(s, sl, p, 1, tmp, v.sub_out[i][0], v.sub_out[i][1], tmp, nullptr, W, st, BWD_FULL, uf))) return rc;
-          if ((rc = sub_backward(s, sl, p, 0, tmp, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FULL, uf))) return rc;
+          if ((rc = sub_backward(s, sl, p, 0, tmp, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FULL, uf, nullptr,
+                                 leaves_sums(s, v, i)))) return rc;
           if ((rc = flush_unit_fork(s, st))) return rc;
         } else {
           if (next && u.residual) {
