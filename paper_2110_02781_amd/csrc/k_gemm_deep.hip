@@ -1,8 +1,8 @@
 // Pointwise layers with a LONG reduction and few rows, bfloat16: the project layers (forward) and the expand layers
-// (data gradient) of the low-resolution inverted residual blocks, 6 K - 25 K rows against a reduction of 256 - 1800
+// (data gradient) of the low-resolution inverted residual blocks, 2 K - 25 K rows against a reduction of 64 - 1800
 // channels.  Their tensors are small (they stay in the memory-side cache) and their arithmetic intensity is at the
 // MFMA / HBM balance, so what they need is a GEMM that keeps the matrix cores fed, not a streaming kernel:
-//   * a block owns a (32*S) x (32*T) output tile (S = 2 or 4, T = 2 .. 5) and walks the whole reduction in steps of 64,
+//   * a block owns a (32*S) x (32*T) output tile (S = 1, 2 or 4, T = 1 .. 5, see deep_plan) and walks the whole reduction in steps of 64,
 //     its four wavefronts in a 2 x 2 arrangement of (16*S) x (16*T) sub-tiles of v_mfma_f32_16x16x32_bf16;
 //   * both operands go through double-buffered LDS (one barrier per step); the 16-byte vectors of the next two
 //     steps are on their way from memory into registers while the current step is multiplied (a layer has about one
@@ -270,27 +270,29 @@ struct DeepPlan { int S, T, itiles, jtiles; size_t lds; };
 
 // rows M, reduction extent R, output columns NC
 static bool deep_plan(size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
-  if (M <= 2048 || M > 65536 || R < 192 || R > kDeepMaxR || R % 8 || NC % 8 || NC < 32) return false;
-  // column tile: the width (96, 128 or 160; 64 for narrow outputs) that pads the fewest columns, the wider on ties
-  int T = 2;
-  if (NC > 64) {
-    int best = 1 << 30;
-    for (int t = 5; t >= 3; --t) {
-      const int padded = (NC + 32 * t - 1) / (32 * t) * (32 * t);
-      if (padded < best) { best = padded; T = t; }
-    }
+  // Shorter reductions only where there are few rows: 3136 rows, 160 -> 960 forward 8.7 us on the streaming kernel and 7.2 here, data gradient
+  // of 160 outputs 8.5 / 7.2; but 25088 rows 88 -> 528 14.8 / 16.3 and 16.0 / 15.4, 136 -> 816 26.4 / 36.4 and 27.5 / 24.5.
+  if (M <= 2048 || M > 65536 || R < (M <= 8192 ? 64 : 192) || R > kDeepMaxR || R % 8 || NC % 8 || NC < 32) return false;
+  // The tile: a step of a block costs what it stages, S + T units of 4 KB (a trip through registers and LDS, in order; the products are a
+  // fifth of it), and 1.4 times that if the block has its CU to itself; blocks beyond the 256 CUs take turns.  3136 rows, us, bfloat16:
+  // 960 -> 160 forward 15.7 (2 x 5, 49 blocks), 12.3 (2 x 2, 147), 11.8 (1 x 3, 196), 10.4 (1 x 1, 490); its mirror, with residual, 13.5, 8.7, 8.5, 7.3;
+  // 1280 -> 320 data gradient 16.1 (2 x 5, 98), 13.0 (2 x 3, 196), 11.3 (2 x 2, 245), 13.8 (1 x 1, 980); 320 -> 960 11.6 (2 x 5, 294), 8.9 (4 x 3, 250).
+  static const int kTiles[][2] = {{4, 5}, {4, 4}, {4, 3}, {4, 2}, {2, 3}, {2, 2}, {2, 1}, {1, 1}};
+  int best = 0;
+  for (const auto& st : kTiles) {
+    const int S = st[0], T = st[1];
+    const size_t itiles = (M + 32 * S - 1) / (32 * S), jtiles = (NC + 32 * T - 1) / (32 * T);
+    if (itiles > kMaxPartials) continue;
+    const size_t xs = (size_t)32 * S * kDeepLD, ys = dgrad ? (size_t)kDeepKS * (32 * T + 8) : (size_t)32 * T * kDeepLD;
+    const size_t lds = 2 * (xs + ys) * sizeof(bf16_t) + (dgrad ? 0 : 2 * (size_t)((R + kDeepKS - 1) / kDeepKS * kDeepKS) * sizeof(float));
+    const int turns = (int)((itiles * jtiles + 255) / 256), alone = turns == 1 || 2 * lds > 160 * 1024;
+    const int cost = turns * (S + T) * (alone ? 7 : 5);
+    if (best && cost >= best) continue;
+    best = cost;
+    const size_t red = (size_t)4 * 32 * T * sizeof(float);
+    *d = DeepPlan{S, T, (int)itiles, (int)jtiles, lds > red ? lds : red};
   }
-  d->T = T;
-  d->jtiles = (NC + 32 * T - 1) / (32 * T);
-  // 128-row tiles when they still give every CU two blocks, 64-row tiles otherwise
-  d->S = ((M + 127) / 128) * d->jtiles >= 512 ? 4 : 2;
-  d->itiles = (int)((M + 32 * d->S - 1) / (32 * d->S));
-  if (d->itiles > kMaxPartials) return false;
-  const size_t xs = (size_t)32 * d->S * kDeepLD, ys = dgrad ? (size_t)kDeepKS * (32 * T + 8) : (size_t)32 * T * kDeepLD;
-  d->lds = 2 * (xs + ys) * sizeof(bf16_t) + (dgrad ? 0 : 2 * (size_t)((R + kDeepKS - 1) / kDeepKS * kDeepKS) * sizeof(float));
-  const size_t red = (size_t)4 * 32 * T * sizeof(float);
-  if (d->lds < red) d->lds = red;
-  return true;
+  return best > 0;
 }
 
 int pw_deep_ok(int dt, size_t M, int R, int NC, bool dgrad) {
@@ -310,20 +312,15 @@ static void deep_launch_mode(hipStream_t st, const DeepArgs& a, const DeepPlan& 
 }
 
 static void deep_launch(hipStream_t st, const DeepArgs& a, const DeepPlan& d, int mode) {
-  if (d.S == 2) {
-    switch (d.T) {
-      case 2: deep_launch_mode<2, 2>(st, a, d, mode); break;
-      case 3: deep_launch_mode<2, 3>(st, a, d, mode); break;
-      case 4: deep_launch_mode<2, 4>(st, a, d, mode); break;
-      default: deep_launch_mode<2, 5>(st, a, d, mode); break;
-    }
-  } else {
-    switch (d.T) {
-      case 2: deep_launch_mode<4, 2>(st, a, d, mode); break;
-      case 3: deep_launch_mode<4, 3>(st, a, d, mode); break;
-      case 4: deep_launch_mode<4, 4>(st, a, d, mode); break;
-      default: deep_launch_mode<4, 5>(st, a, d, mode); break;
-    }
+  switch (d.S * 10 + d.T) {
+    case 11: deep_launch_mode<1, 1>(st, a, d, mode); break;
+    case 21: deep_launch_mode<2, 1>(st, a, d, mode); break;
+    case 22: deep_launch_mode<2, 2>(st, a, d, mode); break;
+    case 23: deep_launch_mode<2, 3>(st, a, d, mode); break;
+    case 42: deep_launch_mode<4, 2>(st, a, d, mode); break;
+    case 43: deep_launch_mode<4, 3>(st, a, d, mode); break;
+    case 44: deep_launch_mode<4, 4>(st, a, d, mode); break;
+    default: deep_launch_mode<4, 5>(st, a, d, mode); break;
   }
 }
 

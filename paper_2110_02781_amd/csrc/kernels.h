@@ -256,7 +256,7 @@ void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, 
                   hipEvent_t ev_sum, std::vector<ReduceJob>* left = nullptr);
 
 
-// bfloat16 pointwise layers with a long reduction (>= 192) and 2 K - 64 K rows: forward (A' * W^T, BatchNorm partial sums
+// bfloat16 pointwise layers with a long reduction (>= 192; >= 64 up to 8192 rows) and 2 K - 64 K rows: forward (A' * W^T, BatchNorm partial sums
 // as pw_fwd leaves them) and data gradient (dZ * W (+ res)) on 2 x 2 wavefront tiles of 16x16x32 MFMAs; pw_fwd and
 // pw_dgrad dispatch to them.  R = reduction extent, NC = output columns.
 int pw_deep_ok(int dt, size_t M, int R, int NC, bool dgrad);

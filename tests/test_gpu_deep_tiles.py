@@ -1,0 +1,40 @@
+"""bfloat16 pointwise layers on the long-reduction kernel (csrc/k_gemm_deep.hip): every tile shape, at its edges, against the float64
+oracle with bfloat16 storage."""
+import pytest
+
+import synth
+from harness import Pair, TOL, assert_close
+from oracle import layers as L
+from oracle import models as OM
+
+pytestmark = pytest.mark.gpu
+
+# (rows as h, w, batch; cin, cout): the tiles that forward (cin -> cout) and data gradient (cout -> cin) take, in units of 32 x 32: a last
+# row tile of one row, columns off 32, reductions off 64, of a single step and of many; both sides of 8192 rows and of 2048
+CASES = [(3, 683, 1, 64, 32), (3, 683, 1, 72, 480), (41, 50, 1, 96, 320), (41, 50, 1, 64, 576), (41, 100, 1, 64, 960), (41, 50, 1, 96, 1280),
+         (50, 52, 1, 64, 1280), (37, 100, 1, 64, 1280), (64, 128, 1, 88, 136), (8193, 1, 1, 200, 88), (7, 7, 64, 960, 160), (45, 46, 1, 1280, 72),
+         (2048, 1, 1, 200, 64), (2049, 1, 1, 56, 64)]
+
+
+@pytest.mark.parametrize("h,w,batch,cin,cout", CASES)
+def test_deep_tiles(h, w, batch, cin, cout):
+    import paper_2110_02781_amd.binding as B
+    print(f"deep tiles {h}x{w} batch {batch} {cin}->{cout}", flush=True)
+    o = [OM.Unit('conv', cin, cin, act=L.ACT_RELU6), OM.Unit('conv', cin, cout, act=L.ACT_NONE)]
+    unit = lambda co, act: dict(kind=B.UNIT_CONV, cin=cin, cout=co, kh=1, kw=1, stride=1, pad_h=0, pad_w=0, act=act)
+    hu = [unit(cin, B.ACT_RELU6), unit(cout, B.ACT_NONE)]
+    # the second unit alone (its input as stored), and behind the first (through that one's BatchNorm and activation)
+    for a in (1, 0):
+        pair = Pair(o, hu, (h, w, cin), batch, a, 2, "bf16", seed=8, ties="off" if a else "bounded")
+        try:
+            x = synth.normal(51, "x", (batch, h, w, cin))
+            y, yo = pair.forward(0, x)
+            assert_close(y, yo, TOL["bf16"], "y")
+            if a == 0:
+                continue
+            dx, dxo = pair.backward(0, synth.normal(51, "dy", yo.shape))
+            assert_close(dx, dxo, TOL["bf16"], "dx")
+            pair.compare_unit_vectors("grads", TOL["bf16"], floor=1e-6)
+            pair.compare_unit_vectors("bn", TOL["bf16"])
+        finally:
+            pair.close()
