@@ -173,6 +173,23 @@ __device__ __forceinline__ float wave_sum(float x) {
   return ((r0 + r1) + r2) + r3;
 }
 
+// The same sum in the last lane only, six additions: the row totals travel by row broadcasts (row 0 to row 1 and 2 to 3, then
+// rows 0-1 to the last two).  The depthwise backward of short tensors sums 44 values a wavefront, the other kernels of theirs 8:
+// 128 rows, 960 channels, fp32 7.7 -> 6.8 us, BatchNorm backward of 128 x 160 4.2 -> 3.1, forward 5.5 -> 5.2.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ float dpp_into(float x) {                 // 0 for the lanes that receive nothing
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, ROWS, 0xF, false));
+}
+__device__ __forceinline__ float wave_sum_last(float x) {
+  x += dpp_move<0xB1>(x);
+  x += dpp_move<0x4E>(x);
+  x += dpp_move<0x141>(x);
+  x += dpp_move<0x140>(x);
+  x += dpp_into<0x142, 0xA>(x);    // row_bcast:15 into rows 1 and 3
+  x += dpp_into<0x143, 0xC>(x);    // row_bcast:31 into rows 2 and 3
+  return x;
+}
+
 // 1 / x computed here, not behind the reductions it is used after (a float64 division is some forty instructions, and there
 // a few threads would do it while all others wait)
 __device__ __forceinline__ double early_inverse(double x) {

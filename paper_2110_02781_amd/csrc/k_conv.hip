@@ -839,9 +839,9 @@ __global__ __launch_bounds__(1024) void dw_fwd_bn_small_k(View in, BnPending pen
     acc[6] = fmaf(sv.z, sv.z, acc[6]); acc[7] = fmaf(sv.w, sv.w, acc[7]);
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = wave_sum(acc[e]);
+  for (int e = 0; e < 8; ++e) acc[e] = wave_sum_last(acc[e]);
   const int wave = tid >> 6, nw = nt >> 6;
-  if ((tid & 63) == 0) {
+  if ((tid & 63) == 63) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[wave][e] = acc[e];
   }
@@ -972,8 +972,8 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
     }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      const float r = wave_sum(b2[e]);
-      if ((tid & 63) == 0) red2[tid >> 6][e] = r;
+      const float r = wave_sum_last(b2[e]);
+      if ((tid & 63) == 63) red2[tid >> 6][e] = r;
     }
     __syncthreads();
     // first use of the values requested at the top: their conversions must not move up to the loads
@@ -1050,15 +1050,15 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
   }
   // block-wide sums in a fixed order: inside each wave, then the waves in order
   const int wave = tid >> 6, nw = nt >> 6;
-  const bool lead = (tid & 63) == 0;
+  const bool lead = (tid & 63) == 63;
 #pragma unroll
   for (int t = 0; t < 9; ++t) {
-    const float r0 = wave_sum(accw[t].x), r1 = wave_sum(accw[t].y), r2 = wave_sum(accw[t].z), r3 = wave_sum(accw[t].w);
+    const float r0 = wave_sum_last(accw[t].x), r1 = wave_sum_last(accw[t].y), r2 = wave_sum_last(accw[t].z), r3 = wave_sum_last(accw[t].w);
     if (lead) { red[wave][t * 4 + 0] = r0; red[wave][t * 4 + 1] = r1; red[wave][t * 4 + 2] = r2; red[wave][t * 4 + 3] = r3; }
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const float r = wave_sum(bsum[e]);
+    const float r = wave_sum_last(bsum[e]);
     if (lead) red[wave][36 + e] = r;
   }
   __syncthreads();

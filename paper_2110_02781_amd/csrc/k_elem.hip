@@ -419,9 +419,9 @@ __global__ __launch_bounds__(1024) void bn_bwd_small_k(const T* __restrict__ dA,
   }
   // fixed-shape reduction: inside each wave, then the waves in order
 #pragma unroll
-  for (int e = 0; e < 8; ++e) acc[e] = wave_sum(acc[e]);
+  for (int e = 0; e < 8; ++e) acc[e] = wave_sum_last(acc[e]);
   const int wave = tid >> 6, nw = nt >> 6;
-  if ((tid & 63) == 0) {
+  if ((tid & 63) == 63) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) red[wave][e] = acc[e];
   }
