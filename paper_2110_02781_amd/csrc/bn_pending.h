@@ -57,6 +57,40 @@ __device__ __forceinline__ void finish_pending_n(const BnPending& pend, int C, i
   __syncthreads();
 }
 
+// The backward counterpart, for all C channels (2 * C <= nt): from sums of dY and dY * z, coef[0..2][c] with dz = k1 * dY + k2 * z + k3.
+// sums: partial, P, M, gamma, mean, invstd; one block (write) adds to g_gamma and g_beta.
+__device__ __forceinline__ void finish_backward_n(const BnPending& sums, int C, float* g_gamma, float* g_beta, bool write, int nt, double* red,
+                                                  float (*coef)[64]) {
+  const int tid = threadIdx.x, nv = 2 * C, L = nt / nv, v = tid % nv, lane = tid / nv;
+  const double inv_M = early_inverse((double)sums.M);
+  const int c = tid < C ? tid : 0;
+  float p_g = sums.gamma[c], p_mu = sums.mean[c], p_is = sums.invstd[c], p_gg = g_gamma[c], p_gb = g_beta[c];
+  double t = 0.0;
+  if (lane < L) {
+    const float* src = sums.partial + v;
+    for (int q0 = lane; q0 < sums.P; q0 += 16 * L) {
+      float x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = src[(size_t)(q0 + u * L < sums.P ? q0 + u * L : lane) * 2 * C];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) t += q0 + u * L < sums.P ? (double)x[u] : 0.0;
+    }
+    red[lane * nv + v] = t;
+  }
+  __syncthreads();
+  asm volatile("" : "+v"(p_g), "+v"(p_mu), "+v"(p_is), "+v"(p_gg), "+v"(p_gb));       // see finish_pending4
+  if (tid < C) {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll 4
+    for (int l = 0; l < L; ++l) { s0 += red[l * nv + tid]; s1 += red[l * nv + C + tid]; }
+    const double mu = p_mu, is = p_is, k1 = (double)p_g * is, dgamma = is * (s1 - mu * s0);
+    const double k2 = -k1 * is * dgamma * inv_M, k3 = -k1 * s0 * inv_M - k2 * mu;
+    coef[0][c] = (float)k1; coef[1][c] = (float)k2; coef[2][c] = (float)k3;
+    if (write) { g_gamma[c] = p_gg + (float)dgamma; g_beta[c] = p_gb + (float)s0; }
+  }
+  __syncthreads();
+}
+
 // finish pending BatchNorm statistics for channels c0..c0+3 (first 256 threads), result in insc[2][4]
 __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, int c0, float eps, float momentum, double (*pre)[8],
                                                 float (*insc)[4]) {

@@ -34,6 +34,12 @@ struct Conv1dArgs {
   BnPending pend;     // few rows, forward: the BatchNorm of x is still partial sums
   float eps, momentum;
   FastDiv dC, dW;     // few rows: by C and by W
+  // few rows, backward: pend.partial != nullptr: the BatchNorm + activation backward of this layer's own output is still to be done.  What is
+  // given as dZ is the gradient of the activated output, own the output; dz = k1 * gated gradient + k2 * z + k3 is formed on the way
+  // in, from partial sums that the layer behind has left, and never written.
+  View own;
+  float *g_gamma, *g_beta;
+  int own_writes;
 };
 
 enum { kC1Chan = 64, kC1Taps = 9, kC1Small = 2048 };
@@ -410,7 +416,7 @@ __global__ __launch_bounds__(256) void conv1d_wgrad_k(Conv1dWgArgs a) {
 // 16 x 16 results of forward or data gradient by four wavefronts that split the reduction, fragments straight from global
 // memory (1024 rows, 64 -> 64 channels: 4.9 us; patch matrix, padded weights and GEMM were three launches of 11) with up to five steps in flight (64 channels x 5 taps: one trip), wavefronts meet in LDS.  CV: channels of x are
 // a multiple of 4, so a lane's four reduction elements lie in one tap and in one vector.
-template <typename T, bool DGRAD, bool CV, int NW>
+template <typename T, bool DGRAD, bool CV, int NW, bool PRO = false>
 __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) {
   constexpr int U = 5, GROUPS = NW / 4;
   __shared__ float red[GROUPS][4][16][17];
@@ -427,11 +433,22 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
   const T* X = reinterpret_cast<const T*>(p.x);
   const T* Wt = reinterpret_cast<const T*>(p.w);
   const bool view = !DGRAD && p.view.scale != nullptr, pending = !DGRAD && p.pend.partial != nullptr;
-  __shared__ double fin[DGRAD ? 1 : 256];
-  __shared__ float vec[DGRAD ? 1 : 2][kC1Chan];
-  const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
+  __shared__ double fin[DGRAD ? (PRO ? 64 * NW : 1) : 256];
+  __shared__ __attribute__((aligned(16))) float vec[DGRAD ? (PRO ? 5 : 1) : 2][kC1Chan];
+  const float lo = DGRAD ? act_lo(p.own.act) : act_lo(p.view.act), hi = DGRAD ? act_hi(p.own.act) : act_hi(p.view.act);
+  const T* Z = reinterpret_cast<const T*>(p.own.z);
+  // data gradient with sums: the prev tensor at the element this thread writes, requested now
+  const int orow = (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
+  const bool in_out = tile_ok && m0 + orow < p.M && j0 + ocol < p.NC, sums = DGRAD && p.stats != nullptr;
+  T zp = T();
+  float psc = 0.f, psh = 0.f;
+  if (sums) {
+    const int pc = in_out ? j0 + ocol : 0;
+    zp = reinterpret_cast<const T*>(p.prev.z)[in_out ? (size_t)(m0 + orow) * p.NC + pc : 0];
+    psc = p.prev.scale[pc]; psh = p.prev.shift[pc];
+  }
   f4v acc = {0.f, 0.f, 0.f, 0.f};
-  float a[U][4], b[U][4], sc[U][4], sh[U][4];
+  float a[U][4], b[U][4], sc[U][4], sh[U][4], zz[PRO ? U : 1][4];
   bool ok[U][4], kin[U][4];
   int ch[U][4];
   auto request = [&](const int s0) __attribute__((always_inline)) {
@@ -451,6 +468,7 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
         const int cc = col_ok ? col : 0;
         if constexpr (CV) {
           *reinterpret_cast<float4*>(a[u]) = load4(X + xa);
+          if (PRO) *reinterpret_cast<float4*>(zz[PRO ? u : 0]) = load4(Z + xa);
           if (view && !pending) { *reinterpret_cast<float4*>(sc[u]) = ld4(p.view.scale + c); *reinterpret_cast<float4*>(sh[u]) = ld4(p.view.shift + c); }
           if constexpr (!DGRAD) *reinterpret_cast<float4*>(b[u]) = load4(Wt + (size_t)cc * K + kc);
           else
@@ -466,17 +484,27 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
   };
   // the first round's fragments travel while the statistics are finished
   request(sb);
+  if (PRO && threadIdx.x < p.C) { vec[PRO ? 3 : 0][threadIdx.x] = p.own.scale[threadIdx.x]; vec[PRO ? 4 : 0][threadIdx.x] = p.own.shift[threadIdx.x]; }
+  if (PRO) finish_backward_n(p.pend, p.C, p.g_gamma, p.g_beta, bid == 0, 64 * NW, fin, vec);
   if (pending) finish_pending_n(p.pend, p.C, 0, p.C, p.eps, p.momentum, bid == 0, 256, fin, vec[0], vec[DGRAD ? 0 : 1]);
   for (int s0 = sb; s0 < se; s0 += U) {
     if (s0 != sb) request(s0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (s0 + u >= se) break;
+      float own[PRO ? 5 : 1][4];
+      if (PRO)
+#pragma unroll
+        for (int q = 0; q < 5; ++q) *reinterpret_cast<float4*>(own[PRO ? q : 0]) = ld4(&vec[PRO ? q : 0][ch[u][0]]);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         if (pending) { const int c = CV ? ch[u][0] + e : ch[u][e]; sc[u][e] = vec[0][c]; sh[u][e] = vec[DGRAD ? 0 : 1][c]; }
         const bool in = ok[u][CV ? 0 : e], kn = kin[u][CV ? 0 : e];
         float x = a[u][e];
+        if constexpr (PRO) {
+          const float y = fmaf(zz[u][e], own[3][e], own[4][e]);
+          x = round_to<T>(fmaf(own[0][e], y > lo && y < hi ? x : 0.f, fmaf(own[1][e], zz[u][e], own[2][e])));
+        }
         if (view) x = round_to<T>(clamp_act(fmaf(x, sc[u][e], sh[u][e]), lo, hi));
         acc = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? x : 0.f, kn ? b[u][e] : 0.f, acc, 0, 0, 0);
       }
@@ -486,14 +514,18 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
 #pragma unroll
   for (int r = 0; r < 4; ++r) red[grp][wave][4 * (lane >> 4) + r][l16] = acc[r];
   __syncthreads();
-  const int orow = (threadIdx.x >> 4) & 15, ocol = threadIdx.x & 15;
-  const bool in = tile_ok && m0 + orow < p.M && j0 + ocol < p.NC;
+  const bool in = in_out;
   const float v = red[grp][0][orow][ocol] + red[grp][1][orow][ocol] + red[grp][2][orow][ocol] + red[grp][3][orow][ocol];
   if (in) reinterpret_cast<T*>(p.out)[(size_t)(m0 + orow) * p.NC + j0 + ocol] = from_f32<T>(v);
-  if (!DGRAD && p.stats) {
-    const float sv = in ? round_to<T>(v) : 0.f;
+  if (p.stats) {
+    float sv = in ? round_to<T>(v) : 0.f, other = sv;
+    if (DGRAD) {                            // chosen, not multiplied, as in conv1d_rows_k
+      other = to_f32(zp);
+      const float y = fmaf(other, psc, psh);
+      sv = p.prev.act == ACT_NONE || (y > act_lo(p.prev.act) && y < act_hi(p.prev.act)) ? sv : 0.f;
+    }
     sred[grp][0][orow][ocol] = sv;
-    sred[grp][1][orow][ocol] = sv * sv;
+    sred[grp][1][orow][ocol] = in ? sv * other : 0.f;
     __syncthreads();
     if ((threadIdx.x & 255) < 32 && tile_ok) {
       const int sq = (threadIdx.x >> 4) & 1, c = threadIdx.x & 15;
@@ -509,9 +541,9 @@ template <typename T, bool CV>
 __global__ __launch_bounds__(256) void conv1d_fwd_small_k(Conv1dArgs p) { conv1d_tile<T, false, CV, 4>(p, xcd_logical_block()); }
 
 // 16 x 16 of g_w by 16 wavefronts that split the rows: no partial buffers, one round of sixteen row groups up to 1024 rows, two at 2048
-template <typename T>
+template <typename T, bool PRO, int NW>
 __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __restrict__ g_w, const int bid) {
-  constexpr int U = 16, NW = 16;
+  constexpr int U = 16;
   __shared__ float red[NW][16][17];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, mg = lane >> 4;
   const int K = p.kw * p.Cin, jt_n = (K + 15) / 16;
@@ -521,6 +553,12 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
   const int tap = k_ok ? k / p.Cin : 0, ci = k_ok ? k - tap * p.Cin : 0, dt = tap - p.pad;
   const T* D = reinterpret_cast<const T*>(p.w) + (co_ok ? co : 0);
   const T* X = reinterpret_cast<const T*>(p.x) + ci;
+  const T* Z = reinterpret_cast<const T*>(p.own.z) + (co_ok ? co : 0);
+  __shared__ double fin[PRO ? 64 * NW : 1];
+  __shared__ float vec[3][kC1Chan];
+  float osc = 0.f, osh = 0.f, k1 = 0.f, k2 = 0.f, k3 = 0.f;
+  const float olo = act_lo(p.own.act), ohi = act_hi(p.own.act);
+  if (PRO) { osc = p.own.scale[co_ok ? co : 0]; osh = p.own.shift[co_ok ? co : 0]; }
   const bool view = p.view.scale != nullptr;
   const float sc = view ? p.view.scale[ci] : 1.f, sh = view ? p.view.shift[ci] : 0.f;
   const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
@@ -532,24 +570,40 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
   const int per = (p.M + 4 * NW - 1) / (4 * NW) * 4, mb = wave * per, me = min(mb + per, p.M);
   f4v acc = {0.f, 0.f, 0.f, 0.f};
   int t = mb + mg - (int)p.dW.div(mb + mg) * p.W;
-  for (int m = mb; m < me; m += 4 * U) {
-    T dr[U], xr[U];
-    bool xin[U];
+  T dr[U], xr[U], zr[PRO ? U : 1];
+  bool xin[U];
+  auto request = [&](const int m) __attribute__((always_inline)) {
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int mm = m + 4 * u + mg;
       xin[u] = mm < me && k_ok && (unsigned)(t + dt) < (unsigned)p.W;
-      dr[u] = D[(size_t)(mm < me ? mm : mb) * p.Cout];
+      const size_t at = (size_t)(mm < me ? mm : mb < p.M ? mb : 0) * p.Cout;
+      dr[u] = D[at];
+      if (PRO) zr[PRO ? u : 0] = Z[at];
       xr[u] = X[xin[u] ? (size_t)(mm + dt) * p.Cin : 0];
       t += 4;
       t -= t >= p.W ? p.W : 0;
     }
+  };
+  request(mb);
+  if constexpr (PRO) {
+    finish_backward_n(p.pend, p.Cout, p.g_gamma, p.g_beta, p.own_writes && bid == 0, 64 * NW, fin, vec);
+    const int c = co_ok ? co : 0;
+    k1 = vec[0][c]; k2 = vec[1][c]; k3 = vec[2][c];
+  }
+  for (int m = mb; m < me; m += 4 * U) {
+    if (m != mb) request(m);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float x = to_f32(xr[u]);
       if (view) x = round_to<T>(clamp_act(fmaf(x, sc, sh), lo, hi));
       const bool din = m + 4 * u + mg < me && co_ok;
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(din ? to_f32(dr[u]) : 0.f, xin[u] ? x : 0.f, acc, 0, 0, 0);
+      float d = to_f32(dr[u]);
+      if constexpr (PRO) {
+        const float z = to_f32(zr[u]), y = fmaf(z, osc, osh);
+        d = round_to<T>(fmaf(k1, y > olo && y < ohi ? d : 0.f, fmaf(k2, z, k3)));
+      }
+      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(din ? d : 0.f, xin[u] ? x : 0.f, acc, 0, 0, 0);
     }
   }
 #pragma unroll
@@ -565,10 +619,13 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
 }
 
 // both gradients of a layer in one launch: blocks [0, n_dgrad) hold four data-gradient tiles each
-template <typename T, bool CV>
-__global__ __launch_bounds__(1024) void conv1d_bwd_small_k(Conv1dArgs d, Conv1dArgs g, float* g_w, int n_dgrad) {
-  if ((int)blockIdx.x < n_dgrad) conv1d_tile<T, true, CV, 16>(d, blockIdx.x);
-  else conv1d_wgrad_tile<T>(g, g_w, blockIdx.x - n_dgrad);
+// The BatchNorm backward on the way in (PRO) doubles a wavefront's instructions, and what a block of 16 takes then is four wavefronts'
+// instructions on each SIMD of a CU that has no neighbour busy: 8 wavefronts.  A step of the sensor network at batch 8 (1024 rows, two such
+// layers), us: BatchNorm backward in launches of its own, 16 wavefronts 68.1, 8 71.7, 4 84.1; on the way in 67.2, 64.0, 76.0.
+template <typename T, bool CV, bool PRO, int NW>
+__global__ __launch_bounds__(64 * NW) void conv1d_bwd_small_k(Conv1dArgs d, Conv1dArgs g, float* g_w, int n_dgrad) {
+  if ((int)blockIdx.x < n_dgrad) conv1d_tile<T, true, CV, NW, PRO>(d, blockIdx.x);
+  else conv1d_wgrad_tile<T, PRO, NW>(g, g_w, blockIdx.x - n_dgrad);
 }
 
 // ---- host ---------------------------------------------------------------------------------------------------
@@ -709,9 +766,7 @@ void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGe
   const int K = g.kw * g.Cin;
   a.c.x = in.z; a.c.w = dz; a.c.view = View{in.z, in.scale, in.shift, in.act};
   if (conv1d_small(g)) {
-    KScope ks(st, "conv1d_wgrad", (double)a.c.M * (g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)g.Cout * K * 8, 2.0 * a.c.M * g.Cout * K,
-              a.c.M, K, g.Cout);
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_bwd_small_k<T, true>), dim3((K + 15) / 16 * ((g.Cout + 15) / 16)), dim3(1024), 0, st, a.c, a.c, g_w, 0));
+    conv1d_bwd_small(dt, st, dz, nullptr, in, g, g_w, nullptr);
     return;
   }
   {
@@ -725,15 +780,29 @@ void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGe
   left->push_back(ReduceJob{ws, g_w, P, g.Cout * K, K, K, 1, K});
 }
 
-void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn) {
+void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn,
+                      const BnPending* sums, const BnBwdIn* own, float* left, int* P_out) {
   Conv1dArgs d = conv1d_args(g, true), a = conv1d_args(g, false);
   d.x = dz; d.w = w; d.out = dIn;
   conv1d_plan_tiles(&d);
   a.x = in.z; a.w = dz; a.view = View{in.z, in.scale, in.shift, in.act};
-  const int K = g.kw * g.Cin, nd = (d.itiles * d.jtiles + 3) / 4, nw = (K + 15) / 16 * ((g.Cout + 15) / 16);
-  KScope ks(st, "conv1d_bwd", (double)d.M * (2.0 * g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)g.Cout * K * 8, 4.0 * d.M * g.Cout * K,
+  if (sums) {
+    d.x = a.w = own->dA;
+    d.pend = a.pend = *sums;
+    d.own = a.own = View{own->out.z, own->out.scale, own->out.shift, own->out.act};
+    d.g_gamma = a.g_gamma = own->g_gamma; d.g_beta = a.g_beta = own->g_beta;
+  }
+  if (left) {
+    d.stats = left; d.prev = View{in.z, in.scale, in.shift, in.act};
+    *P_out = d.itiles;
+  }
+  const int groups = sums ? 2 : 4;     // tiles of the data gradient to a block
+  const int K = g.kw * g.Cin, nd = dIn ? (d.itiles * d.jtiles + groups - 1) / groups : 0, nw = (K + 15) / 16 * ((g.Cout + 15) / 16);
+  a.own_writes = nd == 0;              // who adds to the BatchNorm's gradients: the first data-gradient block, where there is one
+  KScope ks(st, dIn ? "conv1d_bwd" : "conv1d_wgrad", (double)d.M * (2.0 * g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)g.Cout * K * 8, 4.0 * d.M * g.Cout * K,
             d.M, K, g.Cout);
-  FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_bwd_small_k<T, true>), dim3(nd + nw), dim3(1024), 0, st, d, a, g_w, nd));
+  if (sums) FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_bwd_small_k<T, true, true, 8>), dim3(nd + nw), dim3(512), 0, st, d, a, g_w, nd));
+  else FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_bwd_small_k<T, true, false, 16>), dim3(nd + nw), dim3(1024), 0, st, d, a, g_w, nd));
 }
 
 }  // namespace ftp

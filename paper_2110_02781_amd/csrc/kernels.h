@@ -176,8 +176,11 @@ void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const C
 size_t conv1d_wgrad_ws(const ConvGeom& g);
 // partial sums, if any, are left in ws and appended to `left`
 void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left);
-// few rows (conv1d_small_ok): weight and data gradient in one launch
-void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn);
+// few rows (conv1d_small_ok): weight and data gradient (dIn != nullptr) in one launch.  sums != nullptr: the BatchNorm backward of the layer's own
+// output `own` is still to be done, from those sums; dz is not looked at.  left != nullptr (`in` is a view): also the partial sums
+// bn_bwd_reduce would compute for the BatchNorm + activation `in`, [*P_out][2][Cin]
+void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn,
+                      const BnPending* sums = nullptr, const BnBwdIn* own = nullptr, float* left = nullptr, int* P_out = nullptr);
 
 // ---- depthwise 3x3 ----------------------------------------------------------------
 // stats != nullptr (only if dw_fwd_stats_ok): the kernel also writes the BatchNorm partial sums [*P_out][2][C] of z

@@ -309,6 +309,7 @@ struct ftp_stage {
   // gradient that produced it), and how many partials; nullptr: none.
   const void* bwd_sums_of = nullptr;
   int bwd_sums_P = 0;
+  bool bwd_sums_other = false;         // they are in the second half of the buffer (a short 1-D convolution reads one half and fills the other)
   size_t im2col_elems = 0;
   size_t ws_floats = 0;
   int max_c = 0;
@@ -1038,6 +1039,15 @@ static size_t dz_size(const ftp_stage* s, const Sub& sb) {
   return align_up((size_t)s->batch * sb.g.Hout * sb.g.Wout * sb.g.Cout * s->es, 256);
 }
 
+// A short 1-D convolution that does its own BatchNorm backward from sums the layer behind has left, and whether unit i's convolution
+// can leave them for the one in front.
+static bool conv1d_takes_sums(const ftp_stage* s, const UnitPlan& p) {
+  if (p.info->d.kind != FTP_UNIT_CONV || !p.axis[0] || !s->defers) return false;
+  ConvGeom g = p.info->subs[0].g; g.N = s->batch;
+  return conv1d_small_ok(g) && bn_bwd_small_ok((size_t)g.N * g.Wout, g.Cout);
+}
+static bool conv1d_leaves_sums(const ftp_stage* s, size_t i) { return i > 0 && conv1d_takes_sums(s, s->plan[i - 1]); }
+
 // A short project layer (no activation, k the last of its block) whose BatchNorm backward is done on the way into its data gradient,
 // from sums that the layer behind has left: dIn is wanted, the weight gradient waits for the end of the call.
 static bool takes_sums(const ftp_stage* s, const UnitPlan& p, size_t k) {
@@ -1122,6 +1132,17 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       pw_dgrad_pro(s->dt, st, sums, bn, dz, conv_w(s, W, p.p_off + sb.w_off), M, g.Cin, g.Cout, dIn);
       return FTP_OK;
     }
+    if (noted && s->bwd_sums_of == dA && conv1d_takes_sums(s, p)) {
+      float* const from = s->bwd_sums_other ? other_partials(s) : s->bn_part;
+      const BnPending sums{from, s->bwd_sums_P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
+      const BnBwdIn own{dA, out, nullptr, nullptr, nullptr, s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off};
+      const bool leave = dIn && conv1d_leaves_sums(s, &p - s->plan.data());
+      float* left = !leave ? nullptr : s->bwd_sums_other ? s->bn_part : other_partials(s);
+      s->bwd_sums_of = nullptr;
+      conv1d_bwd_small(s->dt, st, nullptr, conv_w(s, W, p.p_off + sb.w_off), in, g, s->grads + p.p_off + sb.w_off, dIn, &sums, &own, left, &s->bwd_sums_P);
+      if (leave) { s->bwd_sums_of = dIn; s->bwd_sums_other = !s->bwd_sums_other; }
+      return FTP_OK;
+    }
     if (!small) {
       int P = 0;
       if (s->bwd_sums_of == dA) P = s->bwd_sums_P;          // the producer of dA has left the sums
@@ -1194,7 +1215,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       s->q_dw.push_back(DwWgradJob{dz, in, g, part, gw});
       if (dIn) run_dw_dgrad();
     } else if (dIn && conv1d_small_ok(g)) {
-      conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn);
+      const bool leave = conv1d_leaves_sums(s, &p - s->plan.data());
+      conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn, nullptr, nullptr, leave ? s->bn_part : nullptr, &s->bwd_sums_P);
+      if (leave) { s->bwd_sums_of = dIn; s->bwd_sums_other = false; }
     } else {
       conv1d_wgrad(s->dt, st, dz, in, g, part, gw, &s->q_red);
       if (dIn) run_conv1d_dgrad();

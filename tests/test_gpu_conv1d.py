@@ -135,3 +135,27 @@ def test_a_gradient_that_is_not_finite_stays_out_of_channels_that_are_off(dtype)
     finally:
         P.stage_destroy(stage)
         P.model_destroy(model)
+
+
+# chains of up to 2048 rows: the BatchNorm backward of all but the last layer is done on the way into its gradients, from sums the layer
+# behind has left (in alternating halves of a buffer, so three in a row); 2048 rows and one window more; rows off 16; few channels, which
+# keep launches of their own; the widest
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("cins,cout,k,w,batch,n_bn", [([9, 32, 64, 64], 64, 5, 128, 8, 1), ([16, 16, 24, 40], 16, 3, 16, 1, 1), ([3, 64, 64], 64, 9, 32, 64, 1),
+                                                      ([12, 8, 32], 24, 7, 37, 11, 1), ([32, 48, 16], 32, 5, 128, 17, 0)])
+def test_conv1d_short_chains(cins, cout, k, w, batch, n_bn, dtype):
+    print(f"conv1d short chain {cins} -> {cout} taps {k} window {w} batch {batch} {dtype}", flush=True)
+    o, h = units(cins, cout, k, L.ACT_NONE if dtype == "bf16" else L.ACT_RELU)
+    pair = Pair(o, h, (1, w, cins[0]), batch, 0, len(o), dtype, seed=9, ties="off" if dtype == "bf16" else "bounded")
+    try:
+        got = []
+        for step in range(2):
+            y, yo = pair.forward(0, synth.normal(25, f"x{step}", (batch, 1, w, cins[0])))
+            assert_close(y, yo, TOL[dtype], "y")
+            n = launches(lambda: got.append(pair.backward(0, synth.normal(25, f"dy{step}", yo.shape))))
+            assert n.get("bn_bwd_small", 0) == n_bn, n
+            assert_close(*got[-1], TOL[dtype], "dx")
+            pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
+            pair.compare_unit_vectors("bn", TOL[dtype])
+    finally:
+        pair.close()
