@@ -3,7 +3,9 @@
 // of rows with its halo goes into LDS once (through the producer's BatchNorm + activation) and every tap reads it
 // there at a row offset; rows are the flattened (window, position) index, so a tile may span windows of any length, and a tap
 // that leaves its own window reads zero.  All products run on the fp32 MFMA (products of bfloat16 values are exact in it).
-// What bounds them is that unit, 256 FLOP a cycle and CU (157 TFLOP/s): 64 -> 64 channels, 5 taps, 32768 rows is 8.5 us a pass.
+// What bounds them is that unit, 256 FLOP a cycle and CU (157 TFLOP/s): 64 -> 64 channels, 5 taps, 32768 rows is 8.5 us a pass.  It does not run
+// beside the vector ALU: in a loop of 16x16x4 instructions with 45 vector instructions to ten of them a step took the sum of both, also with a
+// second wavefront on the SIMD.  So nothing is computed in the loops over the reduction that can be computed in front of them.
 #include "dev_common.h"
 #include "kernels.h"
 #include "bn_pending.h"
@@ -31,6 +33,7 @@ struct Conv1dArgs {
   int Cin, Cout, kw, pad;   // pad: rows in front of the output row at tap 0
   int CP;             // C rounded up to 8: reduction index k = tap * CP + channel
   int itiles, jtiles, tiles_per_range;
+  int kphase;         // row tiles: reduction elements whose weights lie in LDS together
   BnPending pend;     // few rows, forward: the BatchNorm of x is still partial sums
   float eps, momentum;
   FastDiv dC, dW;     // few rows: by C and by W
@@ -42,272 +45,368 @@ struct Conv1dArgs {
   int own_writes;
 };
 
-enum { kC1Chan = 64, kC1Taps = 9, kC1Small = 2048 };
+enum { kC1Chan = 64, kC1Taps = 9, kC1Small = 2048, kC1Blocks = 256 };
+
+// four values as they lie in memory: converted only when they go into LDS, so that a tile on its way is not waited for
+template <typename T> struct Raw4;
+template <> struct Raw4<float> {
+  float4 v;
+  __device__ __forceinline__ void load(const float* p) { v = ld4(p); }
+  __device__ __forceinline__ void set(int e, float x) { (&v.x)[e] = x; }
+  __device__ __forceinline__ float4 get() const { return v; }
+};
+template <> struct Raw4<bf16_t> {
+  uint2 v;
+  __device__ __forceinline__ void load(const bf16_t* p) { v = *reinterpret_cast<const uint2*>(p); }
+  __device__ __forceinline__ void set(int e, bf16_t x) {
+    unsigned& w = e < 2 ? v.x : v.y;
+    w = e & 1 ? (w & 0xffffu) | ((unsigned)x << 16) : (w & 0xffff0000u) | x;
+  }
+  __device__ __forceinline__ float4 get() const {
+    return make_float4(__uint_as_float(v.x << 16), __uint_as_float(v.x & 0xffff0000u), __uint_as_float(v.y << 16), __uint_as_float(v.y & 0xffff0000u));
+  }
+};
+
+// NV vectors of four channels per thread of a tile of `rows` rows of a tensor [M][C], padded to CP channels (a multiple of 4): from
+// row m0 on requested by fetch, through the view and zeros outside the tensor into LDS rows of ld floats by commit.
+template <typename T, int NV>
+struct RowVecs {
+  Raw4<T> raw[NV];
+  int row[NV], chan[NV], lds[NV];        // a row far outside the tensor: padding channels
+  __device__ __forceinline__ void init(const int C, const int CP, const int ld, const int rows, const int spare) {   // spare: four floats that nobody reads
+    const int CG = CP / 4, nv = rows * CG;
+    const unsigned magic = 65536u / (unsigned)CG + 1u;       // v / CG: exact, v * CG < 65536
+#pragma unroll
+    for (int s = 0; s < NV; ++s) {
+      const int v = threadIdx.x + 512 * s, r = (int)(((unsigned)v * magic) >> 16), c = (v - r * CG) * 4;
+      row[s] = v < nv && c < C ? r : -(1 << 28);
+      chan[s] = v < nv && c < C ? c : 0;
+      lds[s] = v < nv ? r * ld + c : spare;
+    }
+  }
+  __device__ __forceinline__ void fetch(const T* __restrict__ X, const int C, const int M, const int m0) {
+    if (C % 4 == 0) {
+#pragma unroll
+      for (int s = 0; s < NV; ++s) {
+        const int m = m0 + row[s];
+        raw[s].load(X + ((unsigned)m < (unsigned)M ? m * C + chan[s] : 0));
+      }
+      return;
+    }
+    T x[NV][4];
+#pragma unroll
+    for (int s = 0; s < NV; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int m = m0 + row[s];
+        x[s][e] = X[(unsigned)m < (unsigned)M && chan[s] + e < C ? m * C + chan[s] + e : 0];
+      }
+#pragma unroll
+    for (int s = 0; s < NV; ++s)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) raw[s].set(e, x[s][e]);
+  }
+  __device__ __forceinline__ void commit(float* dst, const int C, const int M, const int m0, const bool view, const float* sc, const float* sh,
+                                         const float lo, const float hi) const {
+    if (view) put<true>(dst, C, M, m0, sc, sh, lo, hi);
+    else put<false>(dst, C, M, m0, sc, sh, lo, hi);
+  }
+  // no branch between the vectors: their LDS reads go out together
+  template <bool VIEW>
+  __device__ __forceinline__ void put(float* dst, const int C, const int M, const int m0, const float* sc, const float* sh, const float lo, const float hi) const {
+    float4 a[VIEW ? NV : 1], b[VIEW ? NV : 1];
+    if (VIEW)
+#pragma unroll
+      for (int s = 0; s < NV; ++s) { a[VIEW ? s : 0] = ld4(sc + chan[s]); b[VIEW ? s : 0] = ld4(sh + chan[s]); }
+#pragma unroll
+    for (int s = 0; s < NV; ++s) {
+      const bool in = (unsigned)(m0 + row[s]) < (unsigned)M;
+      float4 x = raw[s].get();
+      float* f = &x.x;
+      if (VIEW)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) f[e] = round_to<T>(clamp_act(fmaf(f[e], (&a[VIEW ? s : 0].x)[e], (&b[VIEW ? s : 0].x)[e]), lo, hi));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f[e] = in && chan[s] + e < C ? f[e] : 0.f;
+      *reinterpret_cast<float4*>(dst + lds[s]) = x;
+    }
+  }
+};
 
 // ---- row tiles: forward and data gradient ---------------------------------------------------------------------
-// 4 wavefronts of 32 x 32 results: 64 rows x 64 columns (WC 2), or 64 x 32 with two wavefronts on each half of the reduction
-// (WC 1).  Weights pass through LDS 64 reduction elements per wavefront at a time, the next chunk on its way in registers
-// while one is multiplied.  64-row tiles leave two blocks per CU at 32768 rows (two wavefronts per SIMD hide each other's
-// LDS reads and barriers); 64 -> 64 channels, 5 taps there: 20 us forward, 25 us data
-// gradient; patch matrix + GEMM took 63 and 51.
-template <typename T, bool DGRAD, int WC>
-__global__ __launch_bounds__(256) void conv1d_rows_k(Conv1dArgs p) {
-  constexpr int TI = 64, BC = 32 * WC, KS = 64, KC = KS * 2 / WC, WLD = KC + 4;
+// 8 wavefronts of 32 x 32 results: WC groups of 32 columns, 8 / (WC * KSP) of 32 rows, and KSP wavefronts that split the reduction of
+// each and meet in LDS, where each then finishes its share of the rows.  One block per CU: the weights pass into LDS once for all
+// its tiles (in two phases a tile where they do not fit), the next tile's rows are on their way while one is multiplied, and
+// the reduction runs without a barrier, at 97 % of the matrix unit's rate.  Kernel times at 5 taps, 32768 rows, before (weights in
+// double-buffered chunks of 64 with a barrier each, two blocks of 4 wavefronts per CU) and now, us: 64 -> 64 forward 22.1 / 19.0, data
+// gradient 26.2 / 22.0; 32 -> 64 16.7 / 13.5 and 19.2 / 14.7.  What is left over the 8.5 is the launch, the first tile's way into LDS (4) and the
+// results' way out (2).  A step of the sensor network, us: 2400 rows 154 / 114, 8192 164 / 130, 32768 224 / 203, 131072 595 / 503;
+// bfloat16 8192 166 / 127, 131072 562 / 522 (the weight gradient below included).
+enum { kC1Lds = 160 * 1024 - 4096, kC1Chain = 10 };
+template <typename T, bool DGRAD, int WC, int KSP>
+__global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
+  constexpr int RG = 8 / (WC * KSP), TI = 32 * RG, BC = 32 * WC, SHARE = 16 / KSP, NV = ((TI + kC1Taps - 1) * (kC1Chan / 4) + 511) / 512;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   const int LDR = (p.CP / 4) % 2 ? p.CP : p.CP + 4;       // an odd number of 16-byte units: rows fall into different banks
-  const int prow = TI + p.kw - 1;                         // row prow is the zero row
-  float* xs = smem;
-  float* wsm = smem + (prow + 1) * LDR;                   // [2][BC][WLD]
-  __shared__ float red[2][BC][2];
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, h = lane >> 5, l32 = lane & 31;
-  const int wr = wave & 1, wc = WC == 2 ? wave >> 1 : 0, ks = WC == 2 ? 0 : wave >> 1;
-  const int lb = xcd_logical_block();
-  const int jt = lb % p.jtiles, range = lb / p.jtiles;
-  const int j0 = jt * BC;
-  const int KP = p.kw * p.CP, nchunk = (KP + KC - 1) / KC;
+  const int prow = TI + p.kw - 1, xbuf = (prow + 1) * LDR; // row prow is the zero row; four floats behind each buffer that nobody reads
+  const int WLD = p.kphase + 4;                           // an odd number of 16-byte units too
+  float* ex = smem;                                       // [8][16][64] where the reduction is split
+  float* xs = smem + (KSP > 1 ? 8 * 16 * 64 : 0);         // [2][xbuf], one of them where there is a single tile
+  float* wsm = xs + (p.tiles_per_range > 1 ? 2 : 1) * (xbuf + 4);   // [BC][WLD]
+  __shared__ float red[2][BC][RG * KSP];
+  __shared__ __attribute__((aligned(16))) float vsc[2][kC1Chan];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, h = lane >> 5, l32 = lane & 31;
+  const int ks = wave % KSP, wc = wave / KSP % WC, wr = wave / (KSP * WC);
+  const int range = xcd_logical_block();
+  const int KP = p.kw * p.CP;
   const T* X = reinterpret_cast<const T*>(p.x);
   const T* Wt = reinterpret_cast<const T*>(p.w);
-  const bool vec = p.C % 8 == 0;
   const bool view = !DGRAD && p.view.scale != nullptr;
   const float lo = act_lo(p.view.act), hi = act_hi(p.view.act);
   const int it_beg = range * p.tiles_per_range, it_end = min(it_beg + p.tiles_per_range, p.itiles);
-  const unsigned cp_magic = 65536u / (unsigned)p.CP + 1u;     // k / CP, exact for k * CP < 65536: k < 9 * 64 + 128 with the last chunk's end, CP <= 64
+  const unsigned cp_magic = 65536u / (unsigned)p.CP + 1u;     // k / CP, exact for k * CP < 65536: k <= 9 * 64, CP <= 64
 
-  // weight chunk kc into registers / from there into LDS (column-major: a column's chunk is contiguous)
-  constexpr int WE = BC * KC / 256;
-  float wreg[WE];
-  auto fetch_w = [&](int kc) {
-    if (!DGRAD && vec) {
+  // weights of reduction elements [k0, k0 + n) into LDS, a column's elements contiguous
+  auto load_w = [&](const int k0, const int n) {
+    if (!DGRAD && p.C % 8 == 0) {                            // CP == C: k is the offset in a weight row
+      constexpr int TC = 512 / BC, U = 10;                   // threads to a column; 64 columns, 320 elements: one round
+      const int col = tid / TC, at = (tid % TC) * 4;
+      const T* src = Wt + (col < p.NC ? col * KP : 0) + k0;
+      for (int q0 = at; q0 < n; q0 += U * 4 * TC) {
+        Raw4<T> x[U];
 #pragma unroll
-      for (int s = 0; s < WE / 8; ++s) {
-        const int v = tid + 256 * s, col = v / (KC / 8), k = kc * KC + (v % (KC / 8)) * 8;
-        const bool in = j0 + col < p.NC && k < KP;            // CP == C: k is the offset in a weight row
-        load8(Wt + (in ? (size_t)(j0 + col) * KP + k : 0), wreg + 8 * s);
+        for (int s = 0; s < U; ++s) x[s].load(src + (q0 + 4 * TC * s < n ? q0 + 4 * TC * s : at));
 #pragma unroll
-        for (int e = 0; e < 8; ++e) wreg[8 * s + e] = in ? wreg[8 * s + e] : 0.f;
+        for (int s = 0; s < U; ++s) {
+          float4 f = x[s].get();
+          if (col >= p.NC) f = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (q0 + 4 * TC * s < n) *reinterpret_cast<float4*>(wsm + col * WLD + q0 + 4 * TC * s) = f;
+        }
       }
-    } else if (DGRAD && p.NC % 4 == 0) {                      // CP == C here too: k / C is the tap, k % C the channel of dZ
+    } else if (DGRAD && p.NC % 4 == 0) {                     // CP == C here too: k / C is the tap, k % C the channel of dZ
+      // a wavefront takes 16 columns of 16 elements: 64-byte pieces of memory, and all its LDS words in different banks
+      constexpr int CGN = BC / 4, TK = 512 / CGN, U = 5;     // groups of four columns; elements to a round
+      const int col = (tid / 16 % CGN) * 4, at = tid / (16 * CGN) * 16 + tid % 16;
+      const bool col_in = col < p.NC;
+      for (int q0 = at; q0 < n; q0 += U * TK) {
+        Raw4<T> x[U];
 #pragma unroll
-      for (int s = 0; s < WE / 4; ++s) {
-        const int v = tid + 256 * s, col = v % (BC / 4) * 4, k = kc * KC + v / (BC / 4);
-        const int tap = (int)(((unsigned)k * cp_magic) >> 16), c = k - tap * p.CP;
-        const bool in = j0 + col < p.NC && k < KP;
-        const float4 x = load4(Wt + (in ? ((size_t)c * p.kw + (p.kw - 1 - tap)) * p.Cin + j0 + col : 0));
-        wreg[4 * s] = in ? x.x : 0.f; wreg[4 * s + 1] = in ? x.y : 0.f; wreg[4 * s + 2] = in ? x.z : 0.f; wreg[4 * s + 3] = in ? x.w : 0.f;
+        for (int s = 0; s < U; ++s) {
+          const int kl = q0 + TK * s, k = k0 + (kl < n ? kl : at);
+          const int tap = (int)(((unsigned)k * cp_magic) >> 16), c = k - tap * p.CP;
+          x[s].load(Wt + (c * p.kw + (p.kw - 1 - tap)) * p.Cin + (col_in ? col : 0));
+        }
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+          const int kl = q0 + TK * s;
+          const float4 f = x[s].get();
+          if (kl < n)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wsm[(col + e) * WLD + kl] = col_in ? (&f.x)[e] : 0.f;
+        }
       }
     } else {
+      constexpr int U = 5;
+      for (int e0 = tid; e0 < BC * n; e0 += U * 512) {
+        T x[U];
 #pragma unroll
-      for (int s = 0; s < WE; ++s) {
-        const int e = tid + 256 * s;
-        const int col = DGRAD ? e % BC : e / KC, kk = DGRAD ? e / BC : e % KC;
-        const int k = kc * KC + kk, tap = (int)(((unsigned)k * cp_magic) >> 16), c = k - tap * p.CP;
-        const bool in = j0 + col < p.NC && k < KP && c < p.C;
-        const size_t at = DGRAD ? ((size_t)c * p.kw + (p.kw - 1 - tap)) * p.Cin + j0 + col : ((size_t)(j0 + col) * p.kw + tap) * p.Cin + c;
-        const float x = to_f32(Wt[in ? at : 0]);
-        wreg[s] = in ? x : 0.f;
+        for (int s = 0; s < U; ++s) {
+          const int e = e0 + 512 * s, col = DGRAD ? e % BC : e / n, k = k0 + (DGRAD ? e / BC : e - col * n);
+          const int tap = (int)(((unsigned)k * cp_magic) >> 16), c = k - tap * p.CP;
+          const bool in = e < BC * n && col < p.NC && c < p.C;
+          x[s] = Wt[in ? (DGRAD ? (c * p.kw + (p.kw - 1 - tap)) * p.Cin + col : (col * p.kw + tap) * p.Cin + c) : 0];
+        }
+#pragma unroll
+        for (int s = 0; s < U; ++s) {
+          const int e = e0 + 512 * s, col = DGRAD ? e % BC : e / n, kl = DGRAD ? e / BC : e - col * n, k = k0 + kl;
+          if (e >= BC * n) break;
+          const int c = k - (int)(((unsigned)k * cp_magic) >> 16) * p.CP;
+          wsm[col * WLD + kl] = col < p.NC && c < p.C ? to_f32(x[s]) : 0.f;
+        }
       }
     }
   };
-  auto commit_w = [&](int buf) {
-    float* dst = wsm + buf * BC * WLD;
-    if (!DGRAD && vec) {
-#pragma unroll
-      for (int s = 0; s < WE / 8; ++s) {
-        const int v = tid + 256 * s;
-        store8(dst + v / (KC / 8) * WLD + v % (KC / 8) * 8, wreg + 8 * s);
-      }
-    } else if (DGRAD && p.NC % 4 == 0) {
-#pragma unroll
-      for (int s = 0; s < WE / 4; ++s) {
-        const int v = tid + 256 * s;
-#pragma unroll
-        for (int f = 0; f < 4; ++f) dst[(v % (BC / 4) * 4 + f) * WLD + v / (BC / 4)] = wreg[4 * s + f];
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < WE; ++s) {
-        const int e = tid + 256 * s;
-        const int col = DGRAD ? e % BC : e / KC, kk = DGRAD ? e / BC : e % KC;
-        dst[col * WLD + kk] = wreg[s];
-      }
-    }
-  };
 
-  for (int c = tid; c < LDR; c += 256) xs[prow * LDR + c] = 0.f;
+  RowVecs<T, NV> tile;
+  tile.init(p.C, p.CP, LDR, prow, xbuf);
+  tile.fetch(X, p.C, p.M, it_beg * TI - p.pad);
+  if (view && tid < p.C) { vsc[0][tid] = p.view.scale[tid]; vsc[1][tid] = p.view.shift[tid]; }
+  load_w(0, p.kphase);
+  for (int c = tid; c < LDR; c += 512) {
+    xs[prow * LDR + c] = 0.f;
+    if (p.tiles_per_range > 1) xs[xbuf + 4 + prow * LDR + c] = 0.f;
+  }
   float s1 = 0.f, s2 = 0.f;
-  const int col = j0 + wc * 32 + l32;
+  const int col = wc * 32 + l32;
   const bool col_ok = col < p.NC;
   float psc = 0.f, psh = 0.f;
   const bool sums = DGRAD && p.stats != nullptr;
   if (sums && col_ok) { psc = p.prev.scale[col]; psh = p.prev.shift[col]; }
   const float plo = act_lo(p.prev.act), phi = act_hi(p.prev.act);
+  if (view) __syncthreads();
+  tile.commit(xs, p.C, p.M, it_beg * TI - p.pad, view, vsc[0], vsc[1], lo, hi);
+  if (it_beg + 1 < it_end) tile.fetch(X, p.C, p.M, (it_beg + 1) * TI - p.pad);
+  __syncthreads();
   for (int it = it_beg; it < it_end; ++it) {
-    const int m0 = it * TI;
-    fetch_w(0);
-    const int mb = m0 + wr * 32 + 4 * h;                // rows of this lane's results, see below
-    float zp[16];
+    const int m0 = it * TI, buf = (it - it_beg) & 1;
+    const bool more = it + 1 < it_end;
+    // the next tile goes into LDS, and the one behind it is requested; wavefronts 4 - 7 do that before their products, the others, which share
+    // their SIMDs, behind them: the matrix unit is busy meanwhile
+    auto advance = [&]() __attribute__((always_inline)) {
+      if (!more) return;
+      tile.commit(xs + (buf ^ 1) * (xbuf + 4), p.C, p.M, m0 + TI - p.pad, view, vsc[0], vsc[1], lo, hi);
+      if (it + 2 < it_end) tile.fetch(X, p.C, p.M, m0 + 2 * TI - p.pad);
+    };
+    if (wave >= 4) advance();
+    // registers of this wavefront's results that it finishes: ks * SHARE ..; register r is row 8 * (r / 4) + 4 * h + r % 4, column l32
+    T zp[SHARE];
     if (sums) {
       const T* Z = reinterpret_cast<const T*>(p.prev.z);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = mb + 8 * (r >> 2) + (r & 3);
-        zp[r] = to_f32(Z[col_ok && m < p.M ? (size_t)m * p.NC + col : 0]);
+      for (int i = 0; i < SHARE; ++i) {
+        const int r = ks * SHARE + i, m = m0 + wr * 32 + 4 * h + 8 * (r >> 2) + (r & 3);
+        zp[i] = Z[col_ok && m < p.M ? m * p.NC + col : 0];
       }
     }
-    __syncthreads();                                    // the tile before has been read
-    if (vec) {
-      const int CG = p.CP / 8, nv = prow * CG;
-      for (int v0 = tid; v0 < nv; v0 += 4 * 256) {
-        float val[4][8];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int v = v0 + 256 * s, r = v / CG, m = m0 - p.pad + r;
-          load8(X + (v < nv && m >= 0 && m < p.M ? (size_t)m * p.C + (v - r * CG) * 8 : 0), val[s]);
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int v = v0 + 256 * s, r = v / CG, cg = v - r * CG, m = m0 - p.pad + r;
-          if (v >= nv) break;
-          const bool in = m >= 0 && m < p.M;
-          if (view) {
-            float sc[8], sh[8];
-            load8(p.view.scale + cg * 8, sc);
-            load8(p.view.shift + cg * 8, sh);
-#pragma unroll
-            for (int e = 0; e < 8; ++e) val[s][e] = round_to<T>(clamp_act(fmaf(val[s][e], sc[e], sh[e]), lo, hi));
-          }
-#pragma unroll
-          for (int e = 0; e < 8; ++e) val[s][e] = in ? val[s][e] : 0.f;
-          store8(xs + r * LDR + cg * 8, val[s]);
-        }
-      }
-    } else {
-      const int n = prow * p.CP;
-      for (int i0 = tid; i0 < n; i0 += 4 * 256) {
-        float val[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int i = i0 + 256 * s, r = i / p.CP, c = i - r * p.CP, m = m0 - p.pad + r;
-          const bool in = i < n && m >= 0 && m < p.M && c < p.C;
-          val[s] = to_f32(X[in ? (size_t)m * p.C + c : 0]);
-          if (view) val[s] = round_to<T>(clamp_act(fmaf(val[s], p.view.scale[in ? c : 0], p.view.shift[in ? c : 0]), lo, hi));
-          val[s] = in ? val[s] : 0.f;
-        }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const int i = i0 + 256 * s, r = i / p.CP;
-          if (i < n) xs[r * LDR + i - r * p.CP] = val[s];
-        }
-      }
-    }
-    commit_w(0);
-    __syncthreads();
     const int mrow = m0 + wr * 32 + l32;
     const int t = mrow < p.M ? (int)((unsigned)mrow % (unsigned)p.W) : -(1 << 20);   // a row past the end is outside every window
-    // a chain of fp32 additions per weight chunk, not one through the whole reduction: 64 -> 64 channels, 9 taps were 4.3e-7 off the exact
-    // result (2-norm), 1.6e-7 like this; the additions are a thirtieth of the matrix instructions' time
+    const float* xt = xs + buf * (xbuf + 4);
+    auto tap_row = [&](int tp) { return xt + ((unsigned)(t + tp - p.pad) < (unsigned)p.W ? wr * 32 + l32 + tp : prow) * LDR + 4 * h; };
+    // Chains of at most 80 fp32 additions, not one through the whole reduction: 64 -> 64 channels, 9 taps were 4.3e-7 off the exact result
+    // (2-norm) in one chain, 1.6e-7 in chains of 64; the additions are a thirtieth of the matrix instructions' time
     f16v acc, tot;
 #pragma unroll
     for (int e = 0; e < 16; ++e) tot[e] = 0.f;
-    auto tap_row = [&](int tp) { return xs + ((unsigned)(t + tp - p.pad) < (unsigned)p.W ? wr * 32 + l32 + tp : prow) * LDR + 4 * h; };
-    for (int kc = 0; kc < nchunk; ++kc) {
-      if (kc + 1 < nchunk) fetch_w(kc + 1);
-      const float* brow = wsm + (kc & 1) * BC * WLD + (wc * 32 + l32) * WLD + ks * KS + 4 * h;
-      const int k0 = kc * KC + ks * KS, nq = min(KS, KP - k0) / 8;      // KP is a multiple of 8; may be past the end
-      int tap = (int)(((unsigned)k0 * cp_magic) >> 16), c0 = k0 - tap * p.CP;
-      if (tap > p.kw) tap = p.kw;
+    for (int k0 = 0; k0 < KP; k0 += p.kphase) {
+      const int n = min(p.kphase, KP - k0);
+      if (p.kphase < KP && (k0 > 0 || it > it_beg)) {
+        __syncthreads();                                // the phase before has been read
+        load_w(k0, n);
+        __syncthreads();
+      }
+      const int nq = n / 8, qe = (ks + 1) * nq / KSP;   // KP and the phase are multiples of 8
+      int q = ks * nq / KSP;
+      if (q == qe) continue;
+      int tap = (int)(((unsigned)(k0 + 8 * q) * cp_magic) >> 16), c0 = k0 + 8 * q - tap * p.CP;
       const float* arow = tap_row(tap);
-      float4 a = ld4(arow + c0), b = ld4(brow);
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-      for (int q = 0; q < nq; ++q) {                    // the next operands are on their way while four products run
+      const float* brow = wsm + (wc * 32 + l32) * WLD + 4 * h + 8 * q;
+      float4 a0 = ld4(arow + c0), b0 = ld4(brow), a1, b1;
+      auto next = [&](float4& a, float4& b) __attribute__((always_inline)) {
         c0 += 8;
+        brow += 8;
         if (c0 == p.CP) { c0 = 0; ++tap; arow = tap_row(tap); }       // behind the last tap: at most the zero row, not used
-        const float4 an = ld4(arow + c0), bn = ld4(brow + 8 * (q + 1 < nq ? q + 1 : q));
+        a = ld4(arow + c0);
+        b = ld4(brow);                                  // behind the last element: padding or the next column, not used
+        __builtin_amdgcn_sched_barrier(0);              // requested before the products in front of them run, not behind
+      };
+      auto products = [&](const float4& a, const float4& b) __attribute__((always_inline)) {
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
-        a = an; b = bn;
-      }
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      while (q < qe) {
+        const int qc = min(q + kC1Chain, qe);
 #pragma unroll
-      for (int e = 0; e < 16; ++e) tot[e] += acc[e];
-      if (kc + 1 < nchunk) {
-        commit_w((kc + 1) & 1);                         // the buffer read before this chunk: all have passed the barrier behind it
-        __syncthreads();
+        for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+        for (; q + 2 <= qc; q += 2) {
+          next(a1, b1);
+          products(a0, b0);
+          next(a0, b0);
+          products(a1, b1);
+        }
+        if (q < qc) {
+          next(a1, b1);
+          products(a0, b0);
+          a0 = a1; b0 = b1;
+          ++q;
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) tot[e] += acc[e];
       }
     }
-    if constexpr (WC == 1) {                            // the two halves of the reduction meet
-      __syncthreads();
-      float* half = wsm + wr * 16 * 64 + lane;
-      if (ks == 1)
+    if (wave < 4) advance();
+    if constexpr (KSP > 1) {
+      if (it > it_beg) __syncthreads();                 // the shares of the tile before have been read
 #pragma unroll
-        for (int r = 0; r < 16; ++r) half[r * 64] = tot[r];
-      __syncthreads();
-      if (ks == 1) continue;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) tot[r] += half[r * 64];
+      for (int r = 0; r < 16; ++r) ex[(wave * 16 + r) * 64 + lane] = tot[r];
     }
-    // register r: row 8 * (r / 4) + 4 * h + r % 4, column l32
+    if (KSP > 1 || more) __syncthreads();
     T* out = reinterpret_cast<T*>(p.out);
+    auto finish = [&](const bool whole) __attribute__((always_inline)) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int m = mb + 8 * (r >> 2) + (r & 3);
-      const bool ok = col_ok && m < p.M;
-      if (ok) out[(size_t)m * p.NC + col] = from_f32<T>(tot[r]);
-      const float v = round_to<T>(tot[r]);              // sums are those of the values as stored
-      if (sums) {
-        // chosen, not multiplied: a gradient that is not finite stays out of the sums of a channel that is off
-        const float yp = fmaf(zp[r], psc, psh);
-        const float dy = ok && (p.prev.act == ACT_NONE || (yp > plo && yp < phi)) ? v : 0.f;
-        s1 += dy;
-        s2 += ok ? dy * zp[r] : 0.f;
-      } else {
-        s1 += ok ? v : 0.f;
-        s2 += ok ? v * v : 0.f;
+      for (int i = 0; i < SHARE; ++i) {
+        const int r = ks * SHARE + i, m = m0 + wr * 32 + 4 * h + 8 * (r >> 2) + (r & 3);
+        float x = KSP > 1 ? 0.f : tot[r];
+        if constexpr (KSP > 1)
+#pragma unroll
+          for (int k2 = 0; k2 < KSP; ++k2) x += ex[((wave - ks + k2) * 16 + r) * 64 + lane];
+        const bool ok = whole || (col_ok && m < p.M);
+        if (ok) out[m * p.NC + col] = from_f32<T>(x);
+        const float v = round_to<T>(x);                   // sums are those of the values as stored
+        if (sums) {
+          // chosen, not multiplied: a gradient that is not finite stays out of the sums of a channel that is off
+          const float z = to_f32(zp[i]), yp = fmaf(z, psc, psh);
+          const float dy = ok && (p.prev.act == ACT_NONE || (yp > plo && yp < phi)) ? v : 0.f;
+          s1 += dy;
+          s2 += ok ? dy * z : 0.f;
+        } else {
+          s1 += ok ? v : 0.f;
+          s2 += ok ? v * v : 0.f;
+        }
       }
-    }
+    };
+    if (m0 + TI <= p.M && p.NC == BC) finish(true);     // nothing to ask for each value
+    else finish(false);
   }
   if (p.stats) {
     s1 += __shfl_xor(s1, 32, 64);
     s2 += __shfl_xor(s2, 32, 64);
-    if (h == 0 && ks == 0) { red[0][wc * 32 + l32][wr] = s1; red[1][wc * 32 + l32][wr] = s2; }
+    if (h == 0) { red[0][col][wr * KSP + ks] = s1; red[1][col][wr * KSP + ks] = s2; }
     __syncthreads();
     if (tid < 2 * BC) {
       const int sq = tid / BC, c = tid % BC;
-      if (j0 + c < p.NC) p.stats[((size_t)range * 2 + sq) * p.NC + j0 + c] = red[sq][c][0] + red[sq][c][1];
+      float v = 0.f;
+#pragma unroll
+      for (int q = 0; q < RG * KSP; ++q) v += red[sq][c][q];
+      if (c < p.NC) p.stats[((size_t)range * 2 + sq) * p.NC + c] = v;
     }
   }
 }
 
 // ---- weight gradient over row tiles ---------------------------------------------------------------------------
-// A block takes a range of 64-row tiles (dZ and the input with its halo in LDS) and a set of 32 x 80 pieces of
-// g_w [Cout][kw * Cin]: a wavefront keeps 2 x 5 tiles of 16 x 16 in accumulators over all its rows and reads seven LDS words for
-// ten MFMAs.  Pieces that leave wavefronts over share their rows among them.  One partial per block and row share.  64 -> 64
-// channels, 32768 rows: 28 us (patch matrix + GEMM 73); the next tile in registers while one is multiplied, or four row groups'
-// LDS reads together, measured no faster.
+// A block takes a range of row tiles (dZ and the input with its halo in LDS, the next tile on its way in registers) and a set of 32 x
+// 80 pieces of g_w [Cout][kw * Cin]: a wavefront keeps 2 x 5 tiles of 16 x 16 in accumulators over all its rows and reads seven LDS
+// words for ten MFMAs.  Wavefronts that share a piece's rows meet in LDS: one partial per block.  Half the pieces to a block
+// where there are several: what it then loads twice is less than the partials of twice as many row ranges.  64 -> 64 channels, 32768
+// rows: 24.3 us and 128 partials, added up with those of 32 -> 64 in 5.9; four wavefronts, nothing on its way, two blocks per CU and 256
+// partials 29 and 11.6.
 struct Conv1dWgArgs {
   Conv1dArgs c;
   int nco, nkg;            // pieces along Cout (32 each) and along kw * Cin (80 each)
-  int gpb, rs;             // pieces per block, wavefronts that share a piece's rows: gpb * rs <= 4
+  int rs;                  // wavefronts that share a piece's rows: 8 / rs pieces per block
   int ngrp;                // blocks per row range
+  int rows;                // rows of a tile: 64 or 32
 };
-enum { kC1WgRows = 64, kC1RT = 2, kC1CT = 5 };
+// kC1WgLd: 16 banks between rows, so that the four rows of an MFMA operand fall into different banks; the same for every channel count, so that
+// a step's rows are at an offset known to the compiler
+enum { kC1RT = 2, kC1CT = 5, kC1Acc = kC1RT * kC1CT * 4, kC1WgLd = kC1Chan + 16 };
 
-template <typename T>
-__global__ __launch_bounds__(256) void conv1d_wgrad_k(Conv1dWgArgs a) {
+template <typename T, int RS, int ROWS>
+__global__ __launch_bounds__(512) void conv1d_wgrad_k(Conv1dWgArgs a) {
   const Conv1dArgs& p = a.c;
+  constexpr int NX = ((64 + kC1Taps - 1) * (kC1Chan / 4) + 511) / 512, ND = 64 * (kC1Chan / 4) / 512;
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  // 16 or 48 banks between rows: the four rows of an MFMA operand fall into different banks
-  const int LDR = (p.Cin + 31) / 32 * 32 + 16, LDZ = (p.Cout + 31) / 32 * 32 + 16;
-  const int prow = kC1WgRows + p.kw - 1;
-  float* xs = smem;
-  float* ds = smem + prow * LDR;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, rg = lane >> 4;
-  const int grp = blockIdx.x % a.ngrp, range = blockIdx.x / a.ngrp;
-  const int piece = grp * a.gpb + wave % a.gpb, rsub = wave / a.gpb;
-  const bool live = piece < a.nco * a.nkg && rsub < a.rs;
-  const int pco = piece % a.nco, pkg = piece / a.nco;
+  __shared__ __attribute__((aligned(16))) float vsc[2][kC1Chan];
+  constexpr int LD = kC1WgLd, STEPS = ROWS / (4 * RS);
+  const int prow = ROWS + p.kw - 1, xbuf = prow * LD, buf_n = xbuf + ROWS * LD + 4, CX = (p.Cin + 3) / 4 * 4;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, l16 = lane & 15, rg = lane >> 4;
+  const int lb = xcd_logical_block(), grp = lb % a.ngrp, range = lb / a.ngrp;      // the blocks of a range read the same rows
+  constexpr int GPB = 8 / RS;            // pieces per block
+  const int slot = wave % GPB, piece = grp * GPB + slot, rsub = wave / GPB;
+  const bool live = piece < a.nco * a.nkg;
+  const int pco = piece / a.nkg, pkg = piece % a.nkg;
   const int K = p.kw * p.Cin;
   const T* X = reinterpret_cast<const T*>(p.x);
   const T* D = reinterpret_cast<const T*>(p.w);
@@ -318,13 +417,13 @@ __global__ __launch_bounds__(256) void conv1d_wgrad_k(Conv1dWgArgs a) {
   for (int q = 0; q < kC1CT; ++q) {
     const int k = (pkg * kC1CT + q) * 16 + l16;
     const int tap = k / p.Cin;
-    off[q] = k < K ? tap * LDR + (k - tap * p.Cin) : 0;
-    tj[q] = k < K ? tap - p.pad : -(1 << 20);           // a column past the end is outside every window
+    off[q] = k < K ? (4 * rsub + rg + tap) * LD + (k - tap * p.Cin) : 0;
+    tj[q] = k < K ? tap - p.pad : 0;                    // a column past the end is not written
   }
 #pragma unroll
   for (int q = 0; q < kC1RT; ++q) {
     const int co = (pco * kC1RT + q) * 16 + l16;
-    doff[q] = co < p.Cout ? co : 0;                     // its results are not written
+    doff[q] = xbuf + (4 * rsub + rg) * LD + (live && co < p.Cout ? co : 0);    // a row past the end is not written either
   }
   f4v acc[kC1RT][kC1CT];
 #pragma unroll
@@ -332,84 +431,112 @@ __global__ __launch_bounds__(256) void conv1d_wgrad_k(Conv1dWgArgs a) {
 #pragma unroll
     for (int q = 0; q < kC1CT; ++q) acc[i][q] = f4v{0.f, 0.f, 0.f, 0.f};
 
-  const int it_end = min((range + 1) * p.tiles_per_range, p.itiles);
-  for (int it = range * p.tiles_per_range; it < it_end; ++it) {
-    const int m0 = it * kC1WgRows;
+  const int it_beg = range * p.tiles_per_range, it_end = min(it_beg + p.tiles_per_range, p.itiles);
+  RowVecs<T, NX> xt;
+  RowVecs<T, ND> dt;
+  xt.init(p.Cin, CX, LD, prow, buf_n - 4);
+  dt.init(p.Cout, p.Cout, LD, ROWS, ROWS * LD);         // the same four floats, at the end of a buffer
+  auto fetch = [&](const int it) {
+    xt.fetch(X, p.Cin, p.M, it * ROWS - p.pad);
+    dt.fetch(D, p.Cout, p.M, it * ROWS);
+  };
+  auto commit = [&](const int it, float* dst) {
+    xt.commit(dst, p.Cin, p.M, it * ROWS - p.pad, view, vsc[0], vsc[1], lo, hi);
+    dt.commit(dst + xbuf, p.Cout, p.M, it * ROWS, false, nullptr, nullptr, 0.f, 0.f);
+  };
+  fetch(it_beg);
+  if (view) {
+    if (tid < p.Cin) { vsc[0][tid] = p.view.scale[tid]; vsc[1][tid] = p.view.shift[tid]; }
     __syncthreads();
-    {
-      const int CG = p.Cout / 8, nv = kC1WgRows * CG;
-      for (int v = tid; v < nv; v += 256) {
-        const int r = v / CG, cg = v - r * CG, m = m0 + r;
-        const bool in = m < p.M;
-        float val[8];
-        load8(D + (in ? (size_t)m * p.Cout + cg * 8 : 0), val);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) val[e] = in ? val[e] : 0.f;
-        store8(ds + r * LDZ + cg * 8, val);
-      }
-    }
-    if (p.Cin % 8 == 0) {
-      const int CG = p.Cin / 8, nv = prow * CG;
-      for (int v = tid; v < nv; v += 256) {
-        const int r = v / CG, cg = v - r * CG, m = m0 - p.pad + r;
-        const bool in = m >= 0 && m < p.M;
-        float val[8];
-        load8(X + (in ? (size_t)m * p.Cin + cg * 8 : 0), val);
-        if (view) {
-          float sc[8], sh[8];
-          load8(p.view.scale + cg * 8, sc);
-          load8(p.view.shift + cg * 8, sh);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) val[e] = round_to<T>(clamp_act(fmaf(val[e], sc[e], sh[e]), lo, hi));
-        }
-#pragma unroll
-        for (int e = 0; e < 8; ++e) val[e] = in ? val[e] : 0.f;
-        store8(xs + r * LDR + cg * 8, val);
-      }
-    } else {
-      for (int i = tid; i < prow * p.Cin; i += 256) {
-        const int r = i / p.Cin, c = i - r * p.Cin, m = m0 - p.pad + r;
-        const bool in = m >= 0 && m < p.M;
-        float x = to_f32(X[in ? (size_t)m * p.Cin + c : 0]);
-        if (view) x = round_to<T>(clamp_act(fmaf(x, p.view.scale[c], p.view.shift[c]), lo, hi));
-        xs[r * LDR + c] = in ? x : 0.f;
-      }
-    }
-    __syncthreads();
+  }
+  commit(it_beg, smem);
+  if (it_beg + 1 < it_end) fetch(it_beg + 1);
+  __syncthreads();
+  for (int it = it_beg; it < it_end; ++it) {
+    const int m0 = it * ROWS, buf = (it - it_beg) & 1;
+    const bool more = it + 1 < it_end;
+    // as in conv1d_rows_k: half of the wavefronts bring in the next tile before their products, half behind them
+    auto advance = [&]() __attribute__((always_inline)) {
+      if (!more) return;
+      commit(it + 1, smem + (buf ^ 1) * buf_n);         // read last in the tile before, a barrier ago
+      if (it + 2 < it_end) fetch(it + 2);
+    };
+    if (wave >= 4) advance();
+    const float* xs = smem + buf * buf_n;
     if (live) {
-      const int r_step = 4 * a.rs;
-      int t = (int)((unsigned)(m0 + 4 * rsub + rg) % (unsigned)p.W);
-      for (int r = 4 * rsub + rg; r < kC1WgRows; r += r_step) {
-        const bool row_ok = m0 + r < p.M;
-        float d[kC1RT], x[kC1CT];
+      // Row 4 * rsub + rg and every 4 * RS-th behind it; the LDS words of the next four rows are on their way while ten products run.
+      // t: position in its window of the step's first row.  Only where a tap leaves a window, or the rows end, is anything masked.
+      int t = (int)((unsigned)(m0 + 4 * rsub) % (unsigned)p.W), m = m0 + 4 * rsub;
+      const float *px[kC1CT], *pd[kC1RT];
 #pragma unroll
-        for (int q = 0; q < kC1RT; ++q) d[q] = ds[r * LDZ + doff[q]];
+      for (int q = 0; q < kC1CT; ++q) px[q] = xs + off[q];
 #pragma unroll
-        for (int q = 0; q < kC1CT; ++q) x[q] = xs[r * LDR + off[q]];
+      for (int q = 0; q < kC1RT; ++q) pd[q] = xs + doff[q];
+      float d[2][kC1RT], x[2][kC1CT];
+      auto read = [&](const int s) __attribute__((always_inline)) {
 #pragma unroll
-        for (int q = 0; q < kC1CT; ++q) x[q] = row_ok && (unsigned)(t + tj[q]) < (unsigned)p.W ? x[q] : 0.f;
+        for (int q = 0; q < kC1RT; ++q) d[s & 1][q] = pd[q][s * 4 * RS * LD];
+#pragma unroll
+        for (int q = 0; q < kC1CT; ++q) x[s & 1][q] = px[q][s * 4 * RS * LD];
+        __builtin_amdgcn_sched_barrier(0);
+      };
+      read(0);
+#pragma unroll
+      for (int s = 0; s < STEPS; ++s) {
+        if (s + 1 < STEPS) read(s + 1);
+        if (t < p.pad || t + 3 + p.pad >= p.W || m + 3 >= p.M) {
+          int tl = t + rg;
+          tl = m + rg < p.M ? tl - (tl >= p.W ? p.W : 0) : -(1 << 20);
+#pragma unroll
+          for (int q = 0; q < kC1CT; ++q) x[s & 1][q] = (unsigned)(tl + tj[q]) < (unsigned)p.W ? x[s & 1][q] : 0.f;
+        }
 #pragma unroll
         for (int q = 0; q < kC1CT; ++q)
 #pragma unroll
-          for (int i = 0; i < kC1RT; ++i) acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[i], x[q], acc[i][q], 0, 0, 0);
-        t += r_step;                                    // at most 16, and a window has at least 16 rows
+          for (int i = 0; i < kC1RT; ++i) acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[s & 1][i], x[s & 1][q], acc[i][q], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        m += 4 * RS;
+        t += 4 * RS;                                    // at most 32, and a window has at least 16 rows
         t -= t >= p.W ? p.W : 0;
+        if (RS == 8) t -= t >= p.W ? p.W : 0;
       }
     }
+    if (wave < 4) advance();
+    __syncthreads();
   }
-  if (!live) return;
-  float* out = reinterpret_cast<float*>(p.out) + (size_t)(range * a.rs + rsub) * p.Cout * K;
+  // the wavefronts of a piece meet: each adds and writes its share of the rows of the sixteen-row tiles
+  float* meet = smem;                                   // [8][kC1Acc][64]
 #pragma unroll
   for (int i = 0; i < kC1RT; ++i)
 #pragma unroll
-    for (int q = 0; q < kC1CT; ++q) {
-      const int k = (pkg * kC1CT + q) * 16 + l16;
+    for (int q = 0; q < kC1CT; ++q)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int co = (pco * kC1RT + i) * 16 + 4 * rg + r;
-        if (co < p.Cout && k < K) out[(size_t)co * K + k] = acc[i][q][r];
-      }
+      for (int r = 0; r < 4; ++r) meet[(wave * kC1Acc + (i * kC1CT + q) * 4 + r) * 64 + lane] = acc[i][q][r];
+  __syncthreads();
+  if (!live) return;
+  float* out = reinterpret_cast<float*>(p.out) + (size_t)range * p.Cout * K;
+  constexpr int EACH = kC1Acc / RS;                     // accumulators that a wavefront finishes
+  float v[EACH];
+#pragma unroll
+  for (int j = 0; j < EACH; ++j) {
+    v[j] = 0.f;
+#pragma unroll
+    for (int w = 0; w < RS; ++w) v[j] += meet[((slot + w * GPB) * kC1Acc + rsub * EACH + j) * 64 + lane];
+  }
+  if (pco * 16 * kC1RT + 16 * kC1RT <= p.Cout && pkg * 16 * kC1CT + 16 * kC1CT <= K) {       // a whole piece: nothing to ask for each value
+#pragma unroll
+    for (int j = 0; j < EACH; ++j) {
+      const int e = rsub * EACH + j, i = e / (4 * kC1CT), q = e / 4 % kC1CT, r = e % 4;
+      out[((pco * kC1RT + i) * 16 + 4 * rg + r) * K + (pkg * kC1CT + q) * 16 + l16] = v[j];
     }
+    return;
+  }
+#pragma unroll
+  for (int j = 0; j < EACH; ++j) {
+    const int e = rsub * EACH + j, i = e / (4 * kC1CT), q = e / 4 % kC1CT, r = e % 4;
+    const int k = (pkg * kC1CT + q) * 16 + l16, co = (pco * kC1RT + i) * 16 + 4 * rg + r;
+    if (co < p.Cout && k < K) out[co * K + k] = v[j];
+  }
 }
 
 // ---- few rows: latency only ----------------------------------------------------------------------------------
@@ -689,21 +816,31 @@ static void conv1d_plan_tiles(Conv1dArgs* a) {
   a->itiles = (a->M + 15) / 16; a->jtiles = (a->NC + 15) / 16; a->tiles_per_range = 1;
 }
 
-// tile shape by the columns (a 64-wide tile over 32 columns or fewer would be half padding); at most kBnPartials row
-// ranges, since each leaves one partial
+// One block per CU over a range of tiles, each leaving one partial.  Tiles of 128 rows, 64 or 32, by the longest range (a tile costs as much
+// as some 24 rows on top of its own): 32768 rows are one of 128 to a block, 8192 one of 32.  64 columns or 32: a 64-wide tile over 32
+// columns or fewer would be half padding.
 template <typename T, bool DGRAD>
 static void conv1d_rows(hipStream_t st, Conv1dArgs& a, int* P_out) {
-  const int WC = a.NC <= 32 ? 1 : 2, TI = 64;
+  const int WC = a.NC <= 32 ? 1 : 2;
+  auto ranges = [&](int ti) { const int n = (a.M + ti - 1) / ti; return (n + kC1Blocks - 1) / kC1Blocks; };
+  int TI = 128;
+  for (int ti : {64, 32})
+    if (ranges(ti) * (ti + 24) < ranges(TI) * (TI + 24)) TI = ti;
   a.itiles = (a.M + TI - 1) / TI;
-  a.jtiles = (a.NC + 32 * WC - 1) / (32 * WC);
-  a.tiles_per_range = (a.itiles + kBnPartials - 1) / kBnPartials;
+  a.tiles_per_range = ranges(TI);
   const int nr = (a.itiles + a.tiles_per_range - 1) / a.tiles_per_range;
-  const int LDR = (a.CP / 4) % 2 ? a.CP : a.CP + 4;
-  const size_t lds = ((size_t)(TI + a.kw) * LDR + (size_t)2 * 32 * WC * (128 / WC + 4)) * sizeof(float);
-  if (lds > 65536 - 1024) { launch_plan_failed("conv1d: tile does not fit LDS"); return; }
+  const int LDR = (a.CP / 4) % 2 ? a.CP : a.CP + 4, KP = a.kw * a.CP;
+  const bool split = !(WC == 2 && TI == 128);
+  const size_t fixed = (split ? 8 * 16 * 64 : 0) + (size_t)(a.tiles_per_range > 1 ? 2 : 1) * ((TI + a.kw) * LDR + 4) + 8;       // floats
+  const int fit = (int)((kC1Lds / sizeof(float) - fixed) / (32 * WC)) - 4, phases = (KP + fit - 1) / fit;
+  a.kphase = ((KP / 8 + phases - 1) / phases) * 8;
+  if (a.kphase > fit) a.kphase = fit / 8 * 8;
+  const size_t lds = (fixed + (size_t)32 * WC * (a.kphase + 4)) * sizeof(float);
   if (P_out) *P_out = nr;
-  if (WC == 1) hipLaunchKernelGGL((conv1d_rows_k<T, DGRAD, 1>), dim3(nr * a.jtiles), dim3(256), lds, st, a);
-  else hipLaunchKernelGGL((conv1d_rows_k<T, DGRAD, 2>), dim3(nr * a.jtiles), dim3(256), lds, st, a);
+#define FTP_ROWS(wc, ksp) hipLaunchKernelGGL((conv1d_rows_k<T, DGRAD, wc, ksp>), dim3(nr), dim3(512), lds, st, a)
+  if (WC == 1) { if (TI == 128) FTP_ROWS(1, 2); else if (TI == 64) FTP_ROWS(1, 4); else FTP_ROWS(1, 8); }
+  else { if (TI == 128) FTP_ROWS(2, 1); else if (TI == 64) FTP_ROWS(2, 2); else FTP_ROWS(2, 4); }
+#undef FTP_ROWS
 }
 
 int conv1d_small_ok(const ConvGeom& g) { return conv1d_ok(g) && conv1d_small(g); }
@@ -740,15 +877,14 @@ static Conv1dWgArgs conv1d_wgrad_plan(const ConvGeom& g, int* P) {
   a.nco = (g.Cout + 16 * kC1RT - 1) / (16 * kC1RT);
   a.nkg = (g.kw * g.Cin + 16 * kC1CT - 1) / (16 * kC1CT);
   const int pieces = a.nco * a.nkg;
-  a.gpb = pieces >= 4 ? 4 : pieces >= 2 ? 2 : 1;
-  a.rs = 4 / a.gpb;
-  a.ngrp = (pieces + a.gpb - 1) / a.gpb;
-  a.c.itiles = (a.c.M + kC1WgRows - 1) / kC1WgRows;
-  // two blocks per CU; every row share leaves a partial of the whole gradient.  One block per CU halves the partials, but
-  // its single wavefront per SIMD waits for every LDS read (64 -> 64 channels, 32768 rows: 37 us against 28)
-  const int want = 512 / a.ngrp > 0 ? 512 / a.ngrp : 1;
+  const int gpb = pieces >= 8 ? 4 : pieces >= 4 ? 2 : 1;
+  a.rs = 8 / gpb;
+  a.ngrp = (pieces + gpb - 1) / gpb;
+  const int want = kC1Blocks / a.ngrp > 0 ? kC1Blocks / a.ngrp : 1;
+  a.rows = (a.c.M + 63) / 64 * 2 <= want ? 32 : 64;      // tiles of 64 would leave half of the CUs idle
+  a.c.itiles = (a.c.M + a.rows - 1) / a.rows;
   a.c.tiles_per_range = (a.c.itiles + want - 1) / want;
-  *P = (a.c.itiles + a.c.tiles_per_range - 1) / a.c.tiles_per_range * a.rs;
+  *P = (a.c.itiles + a.c.tiles_per_range - 1) / a.c.tiles_per_range;
   return a;
 }
 
@@ -773,9 +909,13 @@ void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGe
     KScope ks(st, "conv1d_wgrad", (double)a.c.M * (g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)P * g.Cout * K * 4, 2.0 * a.c.M * g.Cout * K,
               a.c.M, K, g.Cout);
     a.c.out = ws;
-    const int LDR = (g.Cin + 31) / 32 * 32 + 16, LDZ = (g.Cout + 31) / 32 * 32 + 16;
-    const size_t lds = ((size_t)(kC1WgRows + g.kw - 1) * LDR + (size_t)kC1WgRows * LDZ) * sizeof(float);
-    FTP_DISPATCH(dt, hipLaunchKernelGGL(conv1d_wgrad_k<T>, dim3(P / a.rs * a.ngrp), dim3(256), lds, st, a));
+    const size_t tiles = (size_t)2 * ((2 * a.rows + g.kw - 1) * kC1WgLd + 4), meet = (size_t)8 * kC1Acc * 64;
+    const size_t lds = (tiles > meet ? tiles : meet) * sizeof(float);
+    const dim3 grid(P * a.ngrp);
+#define FTP_WGRAD(rs, rows) FTP_DISPATCH(dt, hipLaunchKernelGGL((conv1d_wgrad_k<T, rs, rows>), grid, dim3(512), lds, st, a))
+    if (a.rows == 64) { if (a.rs == 2) FTP_WGRAD(2, 64); else if (a.rs == 4) FTP_WGRAD(4, 64); else FTP_WGRAD(8, 64); }
+    else { if (a.rs == 2) FTP_WGRAD(2, 32); else if (a.rs == 4) FTP_WGRAD(4, 32); else FTP_WGRAD(8, 32); }
+#undef FTP_WGRAD
   }
   left->push_back(ReduceJob{ws, g_w, P, g.Cout * K, K, K, 1, K});
 }

@@ -48,6 +48,18 @@ def test_conv1d_edges(cins, cout, k, w, batch, dtype):
         pair.close()
 
 
+# Row tiles: 32, 64 and 128 rows with a last one of 31, 1 and 63 rows; two and three tiles to a block; weights in two phases, with one tile
+# and with two; windows of 16 (the weight gradient's counter wraps twice a step); whole tiles only; 4, 2 and 1 pieces to a wavefront group.
+TILES = [([64], 64, 5, 8191, 1, "f32"), ([64], 64, 5, 2731, 3, "f32"), ([9], 32, 5, 2340, 7, "f32"), ([64], 64, 9, 21, 1563, "f32"), ([8], 8, 3, 16, 2050, "f32"),
+         ([32], 32, 5, 128, 256, "f32"), ([40], 24, 7, 5471, 3, "f32"), ([64], 64, 9, 16, 3073, "f32"), ([12, 24], 32, 5, 16, 3073, "f32"),
+         ([16], 32, 5, 16, 1040, "bf16"), ([24, 24], 32, 9, 49, 47, "bf16")]
+
+
+@pytest.mark.parametrize("cins,cout,k,w,batch,dtype", TILES, ids=["-".join(map(str, c)).replace(" ", "") for c in TILES])
+def test_conv1d_row_tiles(cins, cout, k, w, batch, dtype):
+    test_conv1d_edges(cins, cout, k, w, batch, dtype)
+
+
 # (cin, cout, taps, window, batch, copies in the batch, first unit of the model, type, by the kernels for these layers): both sides of the lines
 # of conv1d_pays, single layers and (two couts) chains; 64-row tiles with a last one of one row, of 63, two column halves
 ROUTES = [(32, 64, 9, 64, 64, 8, False, "bf16", False), (32, 64, 9, 65, 64, 1, False, "bf16", True), (24, 32, 9, 49, 47, 1, False, "bf16", True),
