@@ -1,50 +1,58 @@
-// Pointwise layers with a LONG reduction and few rows, bfloat16: the project layers (forward) and the expand layers
+// Pointwise layers with a LONG reduction and few rows: in bfloat16 the project layers (forward) and the expand layers
 // (data gradient) of the low-resolution inverted residual blocks, 2 K - 25 K rows against a reduction of 64 - 1800
-// channels.  Their tensors are small (they stay in the memory-side cache) and their arithmetic intensity is at the
-// MFMA / HBM balance, so what they need is a GEMM that keeps the matrix cores fed, not a streaming kernel:
-//   * a block owns a (32*S) x (32*T) output tile (S = 1, 2 or 4, T = 1 .. 5, see deep_plan) and walks the whole reduction in steps of 64,
-//     its four wavefronts in a 2 x 2 arrangement of (16*S) x (16*T) sub-tiles of v_mfma_f32_16x16x32_bf16;
+// channels; in fp32 nearly all layers up to 65536 rows (deep_plan).  Their tensors are small (they stay in the memory-side cache) and
+// their arithmetic intensity is at the MFMA / HBM balance, so what they need is a GEMM that keeps the matrix cores fed, not a streaming kernel.
+// In fp32 the matrix instructions are what bounds it (they run at a sixteenth of the rate and not beside vector instructions): there a grid that
+// fills the 256 CUs with small tiles, and few instructions a step, are what counts.
+//   * a block owns a (32*S) x (32*T) output tile (S = 1, 2 or 4, T = 1 .. 5, see deep_plan) and walks the whole reduction in steps of 64 (fp32: 32),
+//     its four wavefronts in a 2 x 2 arrangement of (16*S) x (16*T) sub-tiles of v_mfma_f32_16x16x32_bf16 or 16x16x4_f32;
 //   * both operands go through double-buffered LDS (one barrier per step); the 16-byte vectors of the next two
 //     steps are on their way from memory into registers while the current step is multiplied (a layer has about one
 //     block per CU and a round trip to memory takes several steps: what hides it is bytes in flight per block);
 //   * the weights of the data gradient are stored [reduction][column]: they are staged as they lie in memory and
-//     read back through the LDS transpose read, so neither mode repacks anything;
+//     read back through the LDS transpose read (fp32: word by word), so neither mode repacks anything;
 //   * the weight operand is the MFMA's first operand: a lane then holds four CONSECUTIVE output columns of one row
-//     and stores (and adds the residual, and sums the BatchNorm statistics of) 8-byte groups.
+//     and stores (and adds the residual, and sums the BatchNorm statistics of) them together.
 // Forward applies the producer's BatchNorm + activation to the rows on their way into LDS and leaves the column sums of
 // the stored output (one partial per row tile, summed in a fixed order) for the BatchNorm that follows.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "kernels.h"
 #include "mfma_frag.h"
 
 namespace ftp {
 
-enum { kDeepKS = 64, kDeepLD = kDeepKS + 8, kDeepMaxR = 2048 };
+enum { kDeepMaxR = 2048 };
+// a reduction step is 128 bytes of a row, moved in vectors of 16; an odd number of those between LDS rows
+template <typename E> struct Deep { enum { V = 16 / sizeof(E), KS = 8 * V, LD = KS + V, F32 = sizeof(E) == 4 }; };
 enum { DEEP_FWD = 0, DEEP_FWD_VIEW = 1, DEEP_DGRAD = 2, DEEP_DGRAD_RES = 3 };
 
 struct DeepArgs {
-  const bf16_t* x;      // [M][R]: A as stored (forward) or dZ (data gradient)
-  const bf16_t* y;      // W[N][K]: forward [column][reduction], data gradient [reduction][column]
+  const void* x;      // [M][R]: A as stored (forward) or dZ (data gradient)
+  const void* y;      // W[N][K]: forward [column][reduction], data gradient [reduction][column]
   const float* scale;   // forward: view of x, indexed by the reduction channel (DEEP_FWD_VIEW)
   const float* shift;
-  const bf16_t* res;    // [M][NC] added to the result (DEEP_DGRAD_RES)
-  bf16_t* out;          // [M][NC]
+  const void* res;    // [M][NC] added to the result (DEEP_DGRAD_RES)
+  void* out;          // [M][NC]
   float* stats;         // forward: [row tiles][2][NC] column sums of the stored output and of its squares, or nullptr
   int act;
   int M, R, NC;         // rows, reduction extent, output columns
   int jtiles;           // column tiles; the grid is jtiles * row tiles
 };
 
-template <int S, int T, int MODE>
+template <typename E, int S, int T, int MODE>
 __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
+  constexpr int V = Deep<E>::V, KS = Deep<E>::KS;
+  constexpr bool F32 = Deep<E>::F32;
   constexpr bool DG = MODE >= DEEP_DGRAD;
-  constexpr int BM = 32 * S, BN = 32 * T, LD = kDeepLD, LDY = BN + 8;
+  constexpr int BM = 32 * S, BN = 32 * T, LD = Deep<E>::LD, LDY = BN + V;
   constexpr int XS = BM * LD;                               // elements of one x buffer
-  constexpr int YS = DG ? kDeepKS * LDY : BN * LD;          // elements of one y buffer
+  constexpr int YS = DG ? KS * LDY : BN * LD;          // elements of one y buffer
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  bf16_t* xs = reinterpret_cast<bf16_t*>(smem_raw);         // [2][BM][LD]
-  bf16_t* ys = xs + 2 * XS;                                 // [2][BN][LD] or [2][64][LDY]
-  float* vw = reinterpret_cast<float*>(ys + 2 * YS);        // forward with a view: scale[RP], shift[RP], RP = R rounded up to 64
+  E* xs = reinterpret_cast<E*>(smem_raw);                   // [2][BM][LD]
+  E* ys = xs + 2 * XS;                                      // [2][BN][LD] or [2][KS][LDY]
+  float* vw = reinterpret_cast<float*>(ys + 2 * YS);        // forward with a view: scale[RP], shift[RP], RP = R rounded up to KS
   if (DG) __builtin_amdgcn_s_setprio(3);                    // data-gradient chain
 
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, l16 = lane & 15, G = lane >> 4;
@@ -61,31 +69,33 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   // load and its use, one 32-bit offset register per vector, and the only waits in the loop are the counted ones in
   // front of each step.  Through the view a zero row becomes act(shift): such rows (past M) are never stored and are
   // masked out of the statistics; past R the weights are zero, so the products vanish.
-  const int xkv = (tid & 7) * 8, xrow = tid >> 3;           // x: 8 threads cover the 64 reduction elements of a row
+  const int xkv = (tid & 7) * V, xrow = tid >> 3;           // x: 8 threads cover the reduction elements of a row
   // steps in flight: two.  A third costs about a hundred registers here, and two resident blocks per CU, which hide each
   // other's barrier and LDS phases, measured worth more than the third step.
   constexpr int D = 2;
   constexpr uint32_t kPast = 0x80000000u;                   // beyond any operand here (they are smaller than 2 GiB), also after adding a step
+  constexpr uint32_t ES = sizeof(E);
+  constexpr int VR = BN / V;                                // data gradient: vectors to a staged row of weights
   struct Set { uint4 x[S]; uint4 y[T]; };
   Set set[D];
-  const int RP = (R + kDeepKS - 1) / kDeepKS * kDeepKS;
-  const __amdgpu_buffer_rsrc_t bx = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.x), 0, (int)((size_t)M * R * 2), 0x00020000);
-  const __amdgpu_buffer_rsrc_t by = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(p.y), 0, (int)((size_t)R * NC * 2), 0x00020000);
+  const int RP = (R + KS - 1) / KS * KS;
+  const __amdgpu_buffer_rsrc_t bx = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.x), 0, (int)((size_t)M * R * sizeof(E)), 0x00020000);
+  const __amdgpu_buffer_rsrc_t by = __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p.y), 0, (int)((size_t)R * NC * sizeof(E)), 0x00020000);
   uint32_t ox[S], oy[T];                                    // byte offsets of this thread's vectors at step 0
 #pragma unroll
   for (int q = 0; q < S; ++q) {
     const int m = m0 + xrow + q * 32;
-    ox[q] = m < M ? (uint32_t)(m * R + xkv) * 2u : kPast;
+    ox[q] = m < M ? (uint32_t)(m * R + xkv) * ES : kPast;
   }
 #pragma unroll
   for (int q = 0; q < T; ++q) {
     if (!DG) {
       const int j = j0 + xrow + q * 32;
-      oy[q] = j < NC ? (uint32_t)(j * R + xkv) * 2u : kPast;
+      oy[q] = j < NC ? (uint32_t)(j * R + xkv) * ES : kPast;
     } else {
       const int v = tid + q * 256;
-      const int j = j0 + (v % (4 * T)) * 8;
-      oy[q] = j < NC ? (uint32_t)((v / (4 * T)) * NC + j) * 2u : kPast;
+      const int j = j0 + (v % VR) * V;
+      oy[q] = j < NC ? (uint32_t)((v / VR) * NC + j) * ES : kPast;
     }
   }
   if (MODE == DEEP_FWD_VIEW) {
@@ -102,28 +112,35 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   auto fetch = [&](Set& f, const int r0) __attribute__((always_inline)) {
     const bool kin = r0 + xkv < R;
 #pragma unroll
-    for (int q = 0; q < S; ++q) f.x[q] = ld(bx, kin ? ox[q] + (uint32_t)r0 * 2u : kPast);
+    for (int q = 0; q < S; ++q) f.x[q] = ld(bx, kin ? ox[q] + (uint32_t)r0 * ES : kPast);
 #pragma unroll
     for (int q = 0; q < T; ++q) {
       if (!DG) {
-        f.y[q] = ld(by, kin ? oy[q] + (uint32_t)r0 * 2u : kPast);
+        f.y[q] = ld(by, kin ? oy[q] + (uint32_t)r0 * ES : kPast);
       } else {
         const int v = tid + q * 256;
-        f.y[q] = ld(by, r0 + v / (4 * T) < R ? oy[q] + (uint32_t)(r0 * NC) * 2u : kPast);
+        f.y[q] = ld(by, r0 + v / VR < R ? oy[q] + (uint32_t)(r0 * NC) * ES : kPast);
       }
     }
   };
-  auto commit = [&](const Set& f, const int r0, bf16_t* xb, bf16_t* yb) __attribute__((always_inline)) {
+  auto commit = [&](const Set& f, const int r0, E* xb, E* yb) __attribute__((always_inline)) {
     const float lo = act_lo(p.act), hi = act_hi(p.act);
-    float vsc[8], vsh[8];
-    if (MODE == DEEP_FWD_VIEW) {           // r0 + xkv < RP: the steps stop at RP
-      load8(vw + r0 + xkv, vsc);
-      load8(vw + RP + r0 + xkv, vsh);
-    }
+    float vsc[V], vsh[V];
+    if (MODE == DEEP_FWD_VIEW)             // r0 + xkv < RP: the steps stop at RP
+#pragma unroll
+      for (int e = 0; e < V; e += 4) {
+        *reinterpret_cast<float4*>(vsc + e) = ld4(vw + r0 + xkv + e);
+        *reinterpret_cast<float4*>(vsh + e) = ld4(vw + RP + r0 + xkv + e);
+      }
 #pragma unroll
     for (int q = 0; q < S; ++q) {
       uint4 v = f.x[q];
-      if (MODE == DEEP_FWD_VIEW) {
+      if (MODE == DEEP_FWD_VIEW && F32) {
+        float* t = reinterpret_cast<float*>(&v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = clamp_act(fmaf(t[e], vsc[e], vsh[e]), lo, hi);
+      }
+      if constexpr (MODE == DEEP_FWD_VIEW && !F32) {
         Raw<bf16_t> raw;
         raw.a = v;
         float t[8];
@@ -141,7 +158,7 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
         *reinterpret_cast<uint4*>(yb + (xrow + q * 32) * LD + xkv) = f.y[q];
       } else {
         const int i = tid + q * 256;
-        *reinterpret_cast<uint4*>(yb + (i / (4 * T)) * LDY + (i % (4 * T)) * 8) = f.y[q];
+        *reinterpret_cast<uint4*>(yb + (i / VR) * LDY + (i % VR) * V) = f.y[q];
       }
     }
   };
@@ -155,34 +172,77 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   // one step: set -> LDS buffer s % 2, barrier (which also says that everyone has finished multiplying the step before
   // last, this buffer's previous contents), the set's next request (D steps ahead; past the end: zeros), multiply
   auto step = [&](Set& f, const int s) __attribute__((always_inline)) {
-    bf16_t* xb = xs + (s & 1) * XS;
-    bf16_t* yb = ys + (s & 1) * YS;
-    commit(f, s * kDeepKS, xb, yb);
+    E* xb = xs + (s & 1) * XS;
+    E* yb = ys + (s & 1) * YS;
+    commit(f, s * KS, xb, yb);
     __syncthreads();
     __builtin_amdgcn_sched_barrier(0);   // the requests stay here, D steps ahead of their use (the scheduler would move them down to it)
-    fetch(f, (s + D) * kDeepKS);
+    fetch(f, (s + D) * KS);
     __builtin_amdgcn_sched_barrier(0);
+    if constexpr (F32) {
+      // a lane holds four consecutive reduction elements of both operands, one for each of four instructions
 #pragma unroll
-    for (int ks = 0; ks < kDeepKS / 32; ++ks) {
-      bf16x8_t xf[S], yf[T];
+      for (int ks = 0; ks < KS / 16; ++ks) {
+        float4 xf[S], yf[T];
 #pragma unroll
-      for (int a = 0; a < S; ++a) xf[a] = lds_frag(xb + (wm * 16 * S + a * 16 + l16) * LD + ks * 32 + G * 8);
+        for (int a = 0; a < S; ++a) xf[a] = ld4(xb + (wm * 16 * S + a * 16 + l16) * LD + ks * 16 + G * 4);
 #pragma unroll
-      for (int b = 0; b < T; ++b) {
-        if (DG) yf[b] = lds_frag_tr(yb, LDY, ks * 32 + G * 8, wn * 16 * T + b * 16, l16);
-        else yf[b] = lds_frag(yb + (wn * 16 * T + b * 16 + l16) * LD + ks * 32 + G * 8);
+        for (int b = 0; b < T; ++b) {
+          if (DG) {
+            const float* yr = yb + (ks * 16 + G * 4) * LDY + wn * 16 * T + b * 16 + l16;
+            yf[b] = make_float4(yr[0], yr[LDY], yr[2 * LDY], yr[3 * LDY]);
+          } else {
+            yf[b] = ld4(yb + (wn * 16 * T + b * 16 + l16) * LD + ks * 16 + G * 4);
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int a = 0; a < S; ++a)
+#pragma unroll
+            for (int b = 0; b < T; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32((&yf[b].x)[e], (&xf[a].x)[e], acc[a][b], 0, 0, 0);
       }
+    } else {
+#pragma unroll
+      for (int ks = 0; ks < KS / 32; ++ks) {
+        bf16x8_t xf[S], yf[T];
+#pragma unroll
+        for (int a = 0; a < S; ++a) xf[a] = lds_frag(xb + (wm * 16 * S + a * 16 + l16) * LD + ks * 32 + G * 8);
+#pragma unroll
+        for (int b = 0; b < T; ++b) {
+          if (DG) yf[b] = lds_frag_tr(yb, LDY, ks * 32 + G * 8, wn * 16 * T + b * 16, l16);
+          else yf[b] = lds_frag(yb + (wn * 16 * T + b * 16 + l16) * LD + ks * 32 + G * 8);
+        }
+#pragma unroll
+        for (int a = 0; a < S; ++a)
+#pragma unroll
+          for (int b = 0; b < T; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yf[b], xf[a], acc[a][b], 0, 0, 0);
+      }
+    }
+  };
+  // fp32: a chain of additions per 64 reduction elements, not one through the whole reduction (1568 rows, 960 -> 160: 1.4e-7 off the exact product
+  // (2-norm), the streaming kernel 2.0e-7)
+  f4v_t tot[F32 ? S : 1][F32 ? T : 1];
+  auto clear_tot = [&]() __attribute__((always_inline)) {
+    if constexpr (F32)
 #pragma unroll
       for (int a = 0; a < S; ++a)
 #pragma unroll
-        for (int b = 0; b < T; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(yf[b], xf[a], acc[a][b], 0, 0, 0);
-    }
+        for (int b = 0; b < T; ++b) tot[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f};
+  };
+  auto meet = [&]() __attribute__((always_inline)) {
+    if constexpr (F32)
+#pragma unroll
+      for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) { tot[a][b] += acc[a][b]; acc[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f}; }
   };
 
-  const int nsteps = RP / kDeepKS;
+  const int nsteps = RP / KS;
+  clear_tot();
 #pragma unroll
   for (int d = 0; d < D; ++d) {
-    fetch(set[d], d * kDeepKS);
+    fetch(set[d], d * KS);
     // the sets are requested in order: a wait for set d is then a wait for "all but the youngest loads" on every path
     __builtin_amdgcn_sched_barrier(0);
   }
@@ -193,10 +253,18 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   for (; s0 + D <= nsteps; s0 += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) step(set[d], s0 + d);
+    meet();
   }
 #pragma unroll
   for (int d = 0; d + 1 < D; ++d)
     if (s0 + d < nsteps) step(set[d], s0 + d);
+  if constexpr (F32) {
+    meet();
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+      for (int b = 0; b < T; ++b) acc[a][b] = tot[a][b];
+  }
 
   // ---- results: acc[a][b][e] is out[m0 + wm*16S + 16a + l16][j0 + wn*16T + 16b + 4G + e] ----
   float s1[T][4], s2[T][4];
@@ -204,7 +272,8 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   for (int b = 0; b < T; ++b)
 #pragma unroll
     for (int e = 0; e < 4; ++e) { s1[b][e] = 0.f; s2[b][e] = 0.f; }
-  uint2 rs[S][T];
+  typedef typename std::conditional<F32, float4, uint2>::type Out4;      // four consecutive columns as stored
+  Out4 rs[S][T];
   if (MODE == DEEP_DGRAD_RES) {          // all residual groups are requested before the first store
 #pragma unroll
     for (int a = 0; a < S; ++a)
@@ -212,7 +281,7 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
       for (int b = 0; b < T; ++b) {
         const int m = m0 + wm * 16 * S + a * 16 + l16, j = j0 + wn * 16 * T + b * 16 + 4 * G;
         const bool in = m < M && j < NC;
-        rs[a][b] = *reinterpret_cast<const uint2*>(p.res + (in ? (size_t)m * NC + j : 0));
+        rs[a][b] = *reinterpret_cast<const Out4*>((const E*)p.res + (in ? (size_t)m * NC + j : 0));
       }
   }
 #pragma unroll
@@ -221,21 +290,27 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
     for (int b = 0; b < T; ++b) {
       const int m = m0 + wm * 16 * S + a * 16 + l16, j = j0 + wn * 16 * T + b * 16 + 4 * G;
       float v0 = acc[a][b][0], v1 = acc[a][b][1], v2 = acc[a][b][2], v3 = acc[a][b][3];
-      if (MODE == DEEP_DGRAD_RES) {
-        v0 += __uint_as_float(rs[a][b].x << 16); v1 += __uint_as_float(rs[a][b].x & 0xffff0000u);
-        v2 += __uint_as_float(rs[a][b].y << 16); v3 += __uint_as_float(rs[a][b].y & 0xffff0000u);
+      if constexpr (MODE == DEEP_DGRAD_RES) {
+        const float4 r = load4(reinterpret_cast<const E*>(&rs[a][b]));
+        v0 += r.x; v1 += r.y; v2 += r.z; v3 += r.w;
       }
-      uint2 u;
-      u.x = f32x2_to_bf16x2(v0, v1);
-      u.y = f32x2_to_bf16x2(v2, v3);
-      if (m < M && j < NC) *reinterpret_cast<uint2*>(p.out + (size_t)m * NC + j) = u;
+      Out4 u;
+      if constexpr (F32) {
+        u = make_float4(v0, v1, v2, v3);
+      } else {
+        u.x = f32x2_to_bf16x2(v0, v1);
+        u.y = f32x2_to_bf16x2(v2, v3);
+      }
+      if (m < M && j < NC) *reinterpret_cast<Out4*>((E*)p.out + (size_t)m * NC + j) = u;
       if (!DG) {                         // statistics of the values as stored; columns past NC are exact zeros, rows past M are masked
-        if (m >= M) u = make_uint2(0u, 0u);
-        const float r0v = __uint_as_float(u.x << 16), r1v = __uint_as_float(u.x & 0xffff0000u);
-        const float r2v = __uint_as_float(u.y << 16), r3v = __uint_as_float(u.y & 0xffff0000u);
-        s1[b][0] += r0v; s1[b][1] += r1v; s1[b][2] += r2v; s1[b][3] += r3v;
-        s2[b][0] = fmaf(r0v, r0v, s2[b][0]); s2[b][1] = fmaf(r1v, r1v, s2[b][1]);
-        s2[b][2] = fmaf(r2v, r2v, s2[b][2]); s2[b][3] = fmaf(r3v, r3v, s2[b][3]);
+        const float4 t = load4(reinterpret_cast<const E*>(&u));
+        const float v[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float r = m < M ? v[e] : 0.f;
+          s1[b][e] += r;
+          s2[b][e] = fmaf(r, r, s2[b][e]);
+        }
       }
     }
   if (!DG && p.stats) {
@@ -269,12 +344,26 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
 struct DeepPlan { int S, T, itiles, jtiles; size_t lds; };
 
 // rows M, reduction extent R, output columns NC
-static bool deep_plan(size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
-  // Shorter reductions only where there are few rows: 3136 rows, 160 -> 960 forward 8.7 us on the streaming kernel and 7.2 here, data gradient
-  // of 160 outputs 8.5 / 7.2; but 25088 rows 88 -> 528 14.8 / 16.3 and 16.0 / 15.4, 136 -> 816 26.4 / 36.4 and 27.5 / 24.5.
-  if (M <= 2048 || M > 65536 || R < (M <= 8192 ? 64 : 192) || R > kDeepMaxR || R % 8 || NC % 8 || NC < 32) return false;
+static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
+  // bfloat16: shorter reductions only where there are few rows: 3136 rows, 160 -> 960 forward 8.7 us on the streaming kernel and 7.2 here, data
+  // gradient of 160 outputs 8.5 / 7.2; but 25088 rows 88 -> 528 14.8 / 16.3 and 16.0 / 15.4, 136 -> 816 26.4 / 36.4 and 27.5 / 24.5.
+  // fp32: everything that is not for the short kernel in front, up to 65536 rows, but forward layers that widen a short reduction, whose time is
+  // the output's: us on the streaming kernels and here, forward 1568 rows 960 -> 160 18.9 / 12.9, 3136 960 -> 160 30.1 / 17.1, 6272 384 -> 96
+  // 20.8 / 10.3, 12544 64 -> 384 13.8 / 13.6, 16384 192 -> 32 11.5 / 5.5, 50176 144 -> 32 17.9 / 16.3; but 8192 32 -> 192 4.8 / 5.1, 25088 64 -> 384 20.9 / 22.8,
+  // 96 -> 576 37.3 / 37.9, 50176 32 -> 192 14.6 / 17.0, 100352 144 -> 32 33.8 / 34.3.  Data gradient 800 rows of 960 -> 320 17.8 / 8.6, 6272 96 -> 576 20.8 / 12.3, 25088 69.0 / 34.3,
+  // 8192 48 -> 96 7.1 / 3.4, 50176 192 -> 64 21.3 / 20.5, 144 -> 32 13.0 / 13.1.
+  if (M > 65536 || R > kDeepMaxR || R % 8 || NC % 8 || NC < 32) return false;
+  if (dt == 0) {
+    if (M <= 512 || R < 16) return false;
+    if (!dgrad && ((M > 4096 && R < 64 && NC > 2 * R) || (M > 16384 && NC > R))) return false;
+  } else if (M <= 2048 || R < (M <= 8192 ? 64 : 192)) {
+    return false;
+  }
+  const int KS = dt == 0 ? 32 : 64, LD = dt == 0 ? 36 : 72, V = dt == 0 ? 4 : 8, es = dt == 0 ? 4 : 2;
   // The tile: a step of a block costs what it stages, S + T units of 4 KB (a trip through registers and LDS, in order; the products are a
-  // fifth of it), and 1.4 times that if the block has its CU to itself; blocks beyond the 256 CUs take turns.  3136 rows, us, bfloat16:
+  // fifth of it), and 1.4 times that if the block has its CU to itself; blocks beyond the 256 CUs take turns.  fp32: 256
+  // cycles of products for each 32 x 32 results, which nothing else runs beside, some 60 for each unit staged, and 400 for the trip of a block that has its
+  // CU to itself.  3136 rows, us, bfloat16:
   // 960 -> 160 forward 15.7 (2 x 5, 49 blocks), 12.3 (2 x 2, 147), 11.8 (1 x 3, 196), 10.4 (1 x 1, 490); its mirror, with residual, 13.5, 8.7, 8.5, 7.3;
   // 1280 -> 320 data gradient 16.1 (2 x 5, 98), 13.0 (2 x 3, 196), 11.3 (2 x 2, 245), 13.8 (1 x 1, 980); 320 -> 960 11.6 (2 x 5, 294), 8.9 (4 x 3, 250).
   static const int kTiles[][2] = {{4, 5}, {4, 4}, {4, 3}, {4, 2}, {2, 3}, {2, 2}, {2, 1}, {1, 1}};
@@ -282,11 +371,11 @@ static bool deep_plan(size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
   for (const auto& st : kTiles) {
     const int S = st[0], T = st[1];
     const size_t itiles = (M + 32 * S - 1) / (32 * S), jtiles = (NC + 32 * T - 1) / (32 * T);
-    if (itiles > kMaxPartials) continue;
-    const size_t xs = (size_t)32 * S * kDeepLD, ys = dgrad ? (size_t)kDeepKS * (32 * T + 8) : (size_t)32 * T * kDeepLD;
-    const size_t lds = 2 * (xs + ys) * sizeof(bf16_t) + (dgrad ? 0 : 2 * (size_t)((R + kDeepKS - 1) / kDeepKS * kDeepKS) * sizeof(float));
+    if (itiles > kMaxPartials || (dt == 0 && S * T > 8)) continue;      // (fp32: an accumulator more for every one)
+    const size_t xs = (size_t)32 * S * LD, ys = dgrad ? (size_t)KS * (32 * T + V) : (size_t)32 * T * LD;
+    const size_t lds = 2 * (xs + ys) * es + (dgrad ? 0 : 2 * (size_t)((R + KS - 1) / KS * KS) * sizeof(float));
     const int turns = (int)((itiles * jtiles + 255) / 256), alone = turns == 1 || 2 * lds > 160 * 1024;
-    const int cost = turns * (S + T) * (alone ? 7 : 5);
+    const int cost = dt == 0 ? turns * (256 * S * T + 60 * (S + T) + (alone ? 400 : 100)) : turns * (S + T) * (alone ? 7 : 5);
     if (best && cost >= best) continue;
     best = cost;
     const size_t red = (size_t)4 * 32 * T * sizeof(float);
@@ -297,52 +386,61 @@ static bool deep_plan(size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
 
 int pw_deep_ok(int dt, size_t M, int R, int NC, bool dgrad) {
   DeepPlan d;
-  return dt == 1 && deep_plan(M, R, NC, dgrad, &d);
+  return deep_plan(dt, M, R, NC, dgrad, &d);
 }
 
-template <int S, int T>
+template <typename E, int S, int T>
 static void deep_launch_mode(hipStream_t st, const DeepArgs& a, const DeepPlan& d, int mode) {
   const dim3 grid((unsigned)d.itiles * d.jtiles), block(256);
   switch (mode) {
-    case DEEP_FWD: hipLaunchKernelGGL((pw_gemm_deep_k<S, T, DEEP_FWD>), grid, block, d.lds, st, a); break;
-    case DEEP_FWD_VIEW: hipLaunchKernelGGL((pw_gemm_deep_k<S, T, DEEP_FWD_VIEW>), grid, block, d.lds, st, a); break;
-    case DEEP_DGRAD: hipLaunchKernelGGL((pw_gemm_deep_k<S, T, DEEP_DGRAD>), grid, block, d.lds, st, a); break;
-    default: hipLaunchKernelGGL((pw_gemm_deep_k<S, T, DEEP_DGRAD_RES>), grid, block, d.lds, st, a); break;
+    case DEEP_FWD: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_FWD>), grid, block, d.lds, st, a); break;
+    case DEEP_FWD_VIEW: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_FWD_VIEW>), grid, block, d.lds, st, a); break;
+    case DEEP_DGRAD: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_DGRAD>), grid, block, d.lds, st, a); break;
+    default: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_DGRAD_RES>), grid, block, d.lds, st, a); break;
   }
 }
 
-static void deep_launch(hipStream_t st, const DeepArgs& a, const DeepPlan& d, int mode) {
+template <typename E>
+static void deep_launch_tile(hipStream_t st, const DeepArgs& a, const DeepPlan& d, int mode) {
   switch (d.S * 10 + d.T) {
-    case 11: deep_launch_mode<1, 1>(st, a, d, mode); break;
-    case 21: deep_launch_mode<2, 1>(st, a, d, mode); break;
-    case 22: deep_launch_mode<2, 2>(st, a, d, mode); break;
-    case 23: deep_launch_mode<2, 3>(st, a, d, mode); break;
-    case 42: deep_launch_mode<4, 2>(st, a, d, mode); break;
-    case 43: deep_launch_mode<4, 3>(st, a, d, mode); break;
-    case 44: deep_launch_mode<4, 4>(st, a, d, mode); break;
-    default: deep_launch_mode<4, 5>(st, a, d, mode); break;
+    case 11: deep_launch_mode<E, 1, 1>(st, a, d, mode); break;
+    case 21: deep_launch_mode<E, 2, 1>(st, a, d, mode); break;
+    case 22: deep_launch_mode<E, 2, 2>(st, a, d, mode); break;
+    case 23: deep_launch_mode<E, 2, 3>(st, a, d, mode); break;
+    case 42: deep_launch_mode<E, 4, 2>(st, a, d, mode); break;
+    default:
+      if constexpr (!Deep<E>::F32) {
+        if (d.T == 3) deep_launch_mode<E, 4, 3>(st, a, d, mode);
+        else if (d.T == 4) deep_launch_mode<E, 4, 4>(st, a, d, mode);
+        else deep_launch_mode<E, 4, 5>(st, a, d, mode);
+      }
   }
+}
+
+static void deep_launch(int dt, hipStream_t st, const DeepArgs& a, const DeepPlan& d, int mode) {
+  if (dt == 0) deep_launch_tile<float>(st, a, d, mode);
+  else deep_launch_tile<bf16_t>(st, a, d, mode);
 }
 
 // z[M][N] = A'[M][K] * W[N][K]^T; stats as in pw_fwd (P_out = partials written)
-void pw_fwd_deep(hipStream_t st, HView av, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out) {
+void pw_fwd_deep(int dt, hipStream_t st, HView av, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out) {
   DeepPlan d;
-  if (!deep_plan(M, K, N, false, &d)) { launch_plan_failed("long-reduction pointwise forward called for a shape it does not take"); return; }
+  if (!deep_plan(dt, M, K, N, false, &d)) { launch_plan_failed("long-reduction pointwise forward called for a shape it does not take"); return; }
   DeepArgs a{};
-  a.x = (const bf16_t*)av.z; a.y = (const bf16_t*)w; a.scale = av.scale; a.shift = av.shift; a.act = av.act;
-  a.out = (bf16_t*)z; a.stats = stats; a.M = (int)M; a.R = K; a.NC = N; a.jtiles = d.jtiles;
+  a.x = av.z; a.y = w; a.scale = av.scale; a.shift = av.shift; a.act = av.act;
+  a.out = z; a.stats = stats; a.M = (int)M; a.R = K; a.NC = N; a.jtiles = d.jtiles;
   if (P_out) *P_out = d.itiles;
-  deep_launch(st, a, d, av.scale ? DEEP_FWD_VIEW : DEEP_FWD);
+  deep_launch(dt, st, a, d, av.scale ? DEEP_FWD_VIEW : DEEP_FWD);
 }
 
 // dA[M][K] = dZ[M][N] * W[N][K] (+ res)
-void pw_dgrad_deep(hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA) {
+void pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA) {
   DeepPlan d;
-  if (!deep_plan(M, N, K, true, &d)) { launch_plan_failed("long-reduction pointwise data gradient called for a shape it does not take"); return; }
+  if (!deep_plan(dt, M, N, K, true, &d)) { launch_plan_failed("long-reduction pointwise data gradient called for a shape it does not take"); return; }
   DeepArgs a{};
-  a.x = (const bf16_t*)dz; a.y = (const bf16_t*)w; a.res = (const bf16_t*)res; a.out = (bf16_t*)dA;
+  a.x = dz; a.y = w; a.res = res; a.out = dA;
   a.M = (int)M; a.R = N; a.NC = K; a.jtiles = d.jtiles;
-  deep_launch(st, a, d, res ? DEEP_DGRAD_RES : DEEP_DGRAD);
+  deep_launch(dt, st, a, d, res ? DEEP_DGRAD_RES : DEEP_DGRAD);
 }
 
 }  // namespace ftp

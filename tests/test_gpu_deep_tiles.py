@@ -1,5 +1,5 @@
-"""bfloat16 pointwise layers on the long-reduction kernel (csrc/k_gemm_deep.hip): every tile shape, at its edges, against the float64
-oracle with bfloat16 storage."""
+"""Pointwise layers on the long-reduction kernel (csrc/k_gemm_deep.hip): every tile shape, at its edges, against the float64
+oracle, in bfloat16 with bfloat16 storage."""
 import pytest
 
 import synth
@@ -36,5 +36,33 @@ def test_deep_tiles(h, w, batch, cin, cout):
             assert_close(dx, dxo, TOL["bf16"], "dx")
             pair.compare_unit_vectors("grads", TOL["bf16"], floor=1e-6)
             pair.compare_unit_vectors("bn", TOL["bf16"])
+        finally:
+            pair.close()
+
+
+# fp32: every tile in either direction, rows off 32, 64 and 128, reductions off 32 and of a single step, columns off 32, more and fewer than 256 blocks;
+# both sides of the short kernel's limit of products (700 rows), of 4096 and 16384 rows for forward layers that widen, of 65536 rows
+CASES_F32 = [(3, 683, 1, 64, 32), (3, 683, 1, 72, 480), (41, 100, 1, 64, 960), (41, 50, 1, 96, 1280), (37, 100, 1, 64, 1280), (64, 128, 1, 88, 136),
+             (8193, 1, 1, 200, 88), (7, 10, 10, 960, 320), (7, 7, 64, 960, 160), (45, 46, 1, 1280, 72), (2049, 1, 1, 24, 40), (4097, 1, 1, 24, 56),
+             (16385, 1, 1, 200, 96), (16384, 1, 1, 64, 72), (16385, 1, 1, 64, 72), (33001, 1, 1, 72, 40), (256, 257, 1, 32, 40)]
+
+
+@pytest.mark.parametrize("h,w,batch,cin,cout", CASES_F32)
+def test_deep_tiles_f32(h, w, batch, cin, cout):
+    import paper_2110_02781_amd.binding as B
+    print(f"deep tiles f32 {h}x{w} batch {batch} {cin}->{cout}", flush=True)
+    o = [OM.Unit('conv', cin, cin, act=L.ACT_RELU6), OM.Unit('conv', cin, cout, act=L.ACT_NONE)]
+    unit = lambda co, act: dict(kind=B.UNIT_CONV, cin=cin, cout=co, kh=1, kw=1, stride=1, pad_h=0, pad_w=0, act=act)
+    hu = [unit(cin, B.ACT_RELU6), unit(cout, B.ACT_NONE)]
+    for a in (1, 0):
+        pair = Pair(o, hu, (h, w, cin), batch, a, 2, "f32", seed=8, ties="off" if a else "bounded")
+        try:
+            x = synth.normal(51, "x", (batch, h, w, cin))
+            y, yo = pair.forward(0, x)
+            assert_close(y, yo, TOL["f32"], "y")
+            dx, dxo = pair.backward(0, synth.normal(51, "dy", yo.shape))
+            assert_close(dx, dxo, TOL["f32"], "dx")
+            pair.compare_unit_vectors("grads", TOL["f32"], floor=1e-6)
+            pair.compare_unit_vectors("bn", TOL["f32"])
         finally:
             pair.close()
