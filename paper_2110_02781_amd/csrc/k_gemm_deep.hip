@@ -1,6 +1,6 @@
 // Pointwise layers with a LONG reduction and few rows: in bfloat16 the project layers (forward) and the expand layers
-// (data gradient) of the low-resolution inverted residual blocks, 2 K - 25 K rows against a reduction of 64 - 1800
-// channels; in fp32 nearly all layers up to 65536 rows (deep_plan).  Their tensors are small (they stay in the memory-side cache) and
+// (data gradient) of the low-resolution inverted residual blocks, up to 25 K rows against a reduction of up to 1800
+// channels, and most shorter ones there; in fp32 nearly all layers up to 65536 rows (deep_plan).  Their tensors are small (they stay in the memory-side cache) and
 // their arithmetic intensity is at the MFMA / HBM balance, so what they need is a GEMM that keeps the matrix cores fed, not a streaming kernel.
 // In fp32 the matrix instructions are what bounds it (they run at a sixteenth of the rate and not beside vector instructions): there a grid that
 // fills the 256 CUs with small tiles, and few instructions a step, are what counts.
@@ -345,18 +345,24 @@ struct DeepPlan { int S, T, itiles, jtiles; size_t lds; };
 
 // rows M, reduction extent R, output columns NC
 static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
-  // bfloat16: shorter reductions only where there are few rows: 3136 rows, 160 -> 960 forward 8.7 us on the streaming kernel and 7.2 here, data
-  // gradient of 160 outputs 8.5 / 7.2; but 25088 rows 88 -> 528 14.8 / 16.3 and 16.0 / 15.4, 136 -> 816 26.4 / 36.4 and 27.5 / 24.5.
+  // bfloat16: reductions of 192 and more as they come; shorter ones up to 32768 rows, but layers that widen them there, whose time is the
+  // output's.  us on the streaming kernels and here, forward 700 rows 960 -> 320 10.5 / 7.0, 2100 24 -> 144 6.3 / 2.9, 3136 160 -> 960 8.7 / 7.2, 6825 48 -> 288
+  // 5.7 / 5.0, 12544 40 -> 96 4.3 / 3.8, 144 -> 64 6.2 / 4.2, 25088 96 -> 64 5.0 / 4.8; but 12544 64 -> 384 6.7 / 7.6, 25088 32 -> 192 5.4 / 7.5, 88 -> 528 14.8 / 16.3, 136 -> 816
+  // 26.4 / 36.4.  Data gradient 1568 rows of 960 -> 320 8.7 / 5.2, 2048 160 -> 960 9.9 / 6.2, 8192 96 -> 48 3.5 / 2.9, 25088 96 -> 64 4.7 / 4.1, 136 -> 816
+  // 27.5 / 24.5; but 20800 96 -> 32 3.6 / 3.9, 25088 144 -> 32 4.4 / 4.8.
   // fp32: everything that is not for the short kernel in front, up to 65536 rows, but forward layers that widen a short reduction, whose time is
   // the output's: us on the streaming kernels and here, forward 1568 rows 960 -> 160 18.9 / 12.9, 3136 960 -> 160 30.1 / 17.1, 6272 384 -> 96
   // 20.8 / 10.3, 12544 64 -> 384 13.8 / 13.6, 16384 192 -> 32 11.5 / 5.5, 50176 144 -> 32 17.9 / 16.3; but 8192 32 -> 192 4.8 / 5.1, 25088 64 -> 384 20.9 / 22.8,
-  // 96 -> 576 37.3 / 37.9, 50176 32 -> 192 14.6 / 17.0, 100352 144 -> 32 33.8 / 34.3.  Data gradient 800 rows of 960 -> 320 17.8 / 8.6, 6272 96 -> 576 20.8 / 12.3, 25088 69.0 / 34.3,
+  // 96 -> 576 37.3 / 37.9, 50176 32 -> 192 14.6 / 17.0, 100352 144 -> 32 33.8 / 34.3.  Data gradient 800 rows of 960 -> 320 17.8 / 8.6, 6272 96 -> 576 20.8 / 12.3, 25088 69.0 / 35.2,
   // 8192 48 -> 96 7.1 / 3.4, 50176 192 -> 64 21.3 / 20.5, 144 -> 32 13.0 / 13.1.
   if (M > 65536 || R > kDeepMaxR || R % 8 || NC % 8 || NC < 32) return false;
   if (dt == 0) {
     if (M <= 512 || R < 16) return false;
     if (!dgrad && ((M > 4096 && R < 64 && NC > 2 * R) || (M > 16384 && NC > R))) return false;
-  } else if (M <= 2048 || R < (M <= 8192 ? 64 : 192)) {
+  } else if (R < 192) {
+    if (M <= 512 || M > 32768 || R < 16) return false;
+    if (dgrad ? M > 16384 && R < 64 && NC > 2 * R : M > 8192 && NC > 3 * R) return false;
+  } else if (M <= 512) {
     return false;
   }
   const int KS = dt == 0 ? 32 : 64, LD = dt == 0 ? 36 : 72, V = dt == 0 ? 4 : 8, es = dt == 0 ? 4 : 2;

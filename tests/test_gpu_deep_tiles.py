@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 CASES = [(3, 683, 1, 64, 32), (3, 683, 1, 72, 480), (41, 50, 1, 96, 320), (41, 50, 1, 64, 576), (41, 100, 1, 64, 960), (41, 50, 1, 96, 1280),
          (50, 52, 1, 64, 1280), (37, 100, 1, 64, 1280), (64, 128, 1, 88, 136), (8193, 1, 1, 200, 88), (7, 7, 64, 960, 160), (45, 46, 1, 1280, 72),
          (2048, 1, 1, 200, 64), (2049, 1, 1, 56, 64)]
+# short reductions, fewer rows than 2048, both sides of what widens them at 8192 and 16384 rows, and of 32768 rows
+CASES += [(7, 10, 10, 960, 320), (2051, 1, 1, 24, 144), (8193, 1, 1, 32, 96), (8193, 1, 1, 32, 104), (16385, 1, 1, 40, 96), (32769, 1, 1, 64, 32)]
 
 
 @pytest.mark.parametrize("h,w,batch,cin,cout", CASES)
