@@ -10,6 +10,8 @@
 // reduction for d(gamma), d(beta), one elementwise pass that forms dz, then
 // weight- and data-gradient kernels.
 #include <hip/hip_runtime.h>
+#include <sys/mman.h>
+#include <unistd.h>
 
 #include <cmath>
 #include <cstdarg>
@@ -605,10 +607,26 @@ extern "C" int ftp_stage_import_weights(ftp_stage* s, int unit, const float* hos
   return FTP_OK;
 }
 
+// A caller's new array has no pages yet, and the copy would take a fault for each.  They are asked for together instead, while the GPU may still
+// be busy; contents stay as they are, and where the kernel does not know the request the copy takes its faults as before.  Only where the last
+// page is missing: going through pages that are there costs 0.25 ms for 14 MB.  The weights of MobileNetV2 (20 units, 14 MB) into new arrays
+// 2.65 -> 1.88 ms, into ones used before 1.05.
+static void populate(void* p, size_t bytes) {
+#ifndef MADV_POPULATE_WRITE
+#define MADV_POPULATE_WRITE 23
+#endif
+  if (bytes < ((size_t)256 << 10)) return;
+  const uintptr_t page = (uintptr_t)sysconf(_SC_PAGESIZE), lo = ((uintptr_t)p + page - 1) / page * page, hi = ((uintptr_t)p + bytes) / page * page;
+  unsigned char here = 1;
+  if (mincore((void*)(hi - page), page, &here) == 0 && (here & 1)) return;      // written before: nothing to ask for
+  (void)madvise((void*)lo, hi - lo, MADV_POPULATE_WRITE);
+}
+
 static int export_from(const ftp_stage* s, const float* base, int unit, float* host, size_t n, const char* who) {
   int rc = unit_check(s, unit, n, s ? (unit >= s->a && unit < s->b ? s->plan[unit - s->a].info->n_param : 0) : 0, host, who);
   if (rc) return rc;
   if (n == 0) return FTP_OK;
+  populate(host, n * 4);
   HIP_TRY(hipDeviceSynchronize());
   HIP_TRY(hipMemcpy(host, base + s->plan[unit - s->a].p_off, n * 4, hipMemcpyDeviceToHost));
   return FTP_OK;
