@@ -667,10 +667,13 @@ __device__ __forceinline__ void conv1d_tile(const Conv1dArgs& p, const int bid) 
 template <typename T, bool CV>
 __global__ __launch_bounds__(256) void conv1d_fwd_small_k(Conv1dArgs p) { conv1d_tile<T, false, CV, 4>(p, xcd_logical_block()); }
 
-// 16 x 16 of g_w by 16 wavefronts that split the rows: no partial buffers, one round of sixteen row groups up to 1024 rows, two at 2048
+// 16 x 16 of g_w by NW wavefronts that split the rows: no partial buffers, rounds of sixteen row groups (16 wavefronts: one up to 1024 rows, two
+// at 2048; the 8 with PRO twice as many).  Every wavefront adds in 16 / NW chains, so that none is longer than 16 wavefronts would have (a
+// step of four rows is one addition): with one chain each the gradients of three layers in one stage were 3.2e-7 and 3.8e-7 off 64 bits at 1024 and 2048
+// rows, 2.97e-7 and 3.25e-7 in launches of their own with 16 wavefronts.
 template <typename T, bool PRO, int NW>
 __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __restrict__ g_w, const int bid) {
-  constexpr int U = 16;
+  constexpr int U = 16, CH = 16 / NW;
   __shared__ float red[NW][16][17];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l16 = lane & 15, mg = lane >> 4;
   const int K = p.kw * p.Cin, jt_n = (K + 15) / 16;
@@ -695,7 +698,9 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
   float* dst = g_w + (writer ? (size_t)(it * 16 + orow) * K + jt * 16 + ocol : 0);
   float g_old = writer ? *dst : 0.f;
   const int per = (p.M + 4 * NW - 1) / (4 * NW) * 4, mb = wave * per, me = min(mb + per, p.M);
-  f4v acc = {0.f, 0.f, 0.f, 0.f};
+  f4v acc[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) acc[c] = f4v{0.f, 0.f, 0.f, 0.f};
   int t = mb + mg - (int)p.dW.div(mb + mg) * p.W;
   T dr[U], xr[U], zr[PRO ? U : 1];
   bool xin[U];
@@ -730,11 +735,13 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
         const float z = to_f32(zr[u]), y = fmaf(z, osc, osh);
         d = round_to<T>(fmaf(k1, y > olo && y < ohi ? d : 0.f, fmaf(k2, z, k3)));
       }
-      acc = __builtin_amdgcn_mfma_f32_16x16x4f32(din ? d : 0.f, xin[u] ? x : 0.f, acc, 0, 0, 0);
+      acc[u % CH] = __builtin_amdgcn_mfma_f32_16x16x4f32(din ? d : 0.f, xin[u] ? x : 0.f, acc[u % CH], 0, 0, 0);
     }
   }
 #pragma unroll
-  for (int r = 0; r < 4; ++r) red[wave][4 * mg + r][l16] = acc[r];
+  for (int c = 1; c < CH; ++c) acc[0] += acc[c];
+#pragma unroll
+  for (int r = 0; r < 4; ++r) red[wave][4 * mg + r][l16] = acc[0][r];
   __syncthreads();
   asm volatile("" : "+v"(g_old));
   if (writer) {

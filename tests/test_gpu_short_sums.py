@@ -73,3 +73,53 @@ def test_products_along_one_axis_add_in_short_chains(ci, co, taps, w, batch):
     chains = [(taps * ((c + 7) // 8 * 8) + 63) // 64 for c in (ci, co)]
     print(f"  output {z:.3e} (bar {bar(64, chains[0]):.3e}), input gradient {dx:.3e} (bar {bar(64, chains[1]) + 0.4 * 2.0 ** -24:.3e})", flush=True)
     assert z <= bar(64, chains[0]) and dx <= bar(64, chains[1]) + 0.4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("w,batch", [(128, 8), (128, 16), (100, 20)])
+def test_short_layers_along_one_axis_that_take_sums_lose_nothing_in_their_weight_gradients(w, batch):
+    """Layers of one stage do their BatchNorm backward on the way into both gradients, layers of a stage each have a launch for it and more
+    wavefronts to the weight gradient's rows: the first may be no further from 64 bits than the second, but for what a sample of
+    this size scatters (5 %; a chain of twice the length: 8 - 20 %)."""
+    import torch
+    import paper_2110_02781_amd as P
+    print(f"short 1-D weight gradients window {w} batch {batch}", flush=True)
+    units = [unit(16, 32, 5), unit(32, 64, 5), unit(64, 64, 5)]
+    vecs = P.models.init_unit_params(units, 74)
+    x = torch.from_numpy(synth.normal(74, "x", (batch, 1, w, 16)).astype(np.float32)).cuda()
+    dy = torch.from_numpy(synth.normal(74, "dy", (batch, 1, w, 64)).astype(np.float32)).cuda()
+
+    def gradients(cuts):
+        model = P.model_create(units, 1, w, 16, P.F32)
+        stages = [(a, b, P.stage_create(model, a, b, batch, 1)) for a, b in zip(cuts, cuts[1:])]
+        sp = torch.cuda.current_stream().cuda_stream
+        try:
+            t, d = x, dy
+            for a, b, s in stages:
+                for u in range(a, b):
+                    P.stage_import_weights(s, u, vecs[u])
+                y = torch.empty((batch,) + P.model_unit_in_shape(model, b), device="cuda")
+                P.stage_forward(s, 0, t, y, sp)
+                t = y
+            for a, b, s in stages[::-1]:
+                dx = torch.empty((batch,) + P.model_unit_in_shape(model, a), device="cuda")
+                P.stage_backward(s, 0, d, dx, sp)
+                d = dx
+            return [P.stage_export_grads(s, u, vecs[u].size)[:-2 * units[u]["cout"]].astype(np.float64) for a, b, s in stages for u in range(a, b)]
+        finally:
+            for _, _, s in stages:
+                P.stage_destroy(s)
+            P.model_destroy(model)
+
+    wt = [torch.from_numpy(v[:-2 * u["cout"]].astype(np.float64)).cuda().requires_grad_() for v, u in zip(vecs, units)]
+    h = x.double()
+    for u, p in zip(units, wt):
+        padded = torch.nn.functional.pad(h, (0, 0, 2, 2))
+        z = torch.cat([padded[:, :, i:i + w] for i in range(5)], dim=3) @ p.reshape(u["cout"], -1).t()
+        var, mean = torch.var_mean(z, (0, 1, 2), correction=0)
+        h = (z - mean) * torch.rsqrt(var + 1e-5)
+    want = [g.cpu().numpy() for g in torch.autograd.grad(h, wt, dy.double())]
+    one, each = gradients([0, 3]), gradients([0, 1, 2, 3])
+    for u, (a, b, g) in enumerate(zip(one, each, want)):
+        ea, eb = (np.linalg.norm(t - g) / np.linalg.norm(g) for t in (a, b))
+        print(f"  layer {u}: {ea:.3e} in one stage, {eb:.3e} alone", flush=True)
+        assert ea <= 1.05 * eb
