@@ -142,7 +142,7 @@ struct RowVecs {
 // gradient 26.2 / 22.0; 32 -> 64 16.7 / 13.5 and 19.2 / 14.7.  What is left over the 8.5 is the launch, the first tile's way into LDS (4) and the
 // results' way out (2).  A step of the sensor network, us: 2400 rows 154 / 114, 8192 164 / 130, 32768 224 / 203, 131072 595 / 503;
 // bfloat16 8192 166 / 127, 131072 562 / 522 (the weight gradient below included).
-enum { kC1Lds = 160 * 1024 - 4096, kC1Chain = 10 };
+enum { kC1Lds = 160 * 1024 - 4096 };
 template <typename T, bool DGRAD, int WC, int KSP>
 __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
   constexpr int RG = 8 / (WC * KSP), TI = 32 * RG, BC = 32 * WC, SHARE = 16 / KSP, NV = ((TI + kC1Taps - 1) * (kC1Chan / 4) + 511) / 512;
@@ -272,8 +272,10 @@ __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
     const int t = mrow < p.M ? (int)((unsigned)mrow % (unsigned)p.W) : -(1 << 20);   // a row past the end is outside every window
     const float* xt = xs + buf * (xbuf + 4);
     auto tap_row = [&](int tp) { return xt + ((unsigned)(t + tp - p.pad) < (unsigned)p.W ? wr * 32 + l32 + tp : prow) * LDR + 4 * h; };
-    // Chains of at most 80 fp32 additions, not one through the whole reduction: 64 -> 64 channels, 9 taps were 4.3e-7 off the exact result
-    // (2-norm) in one chain, 1.6e-7 in chains of 64; the additions are a thirtieth of the matrix instructions' time
+    // Chains of at most 64 fp32 additions, not one through the whole reduction: 64 -> 64 channels, 9 taps were 4.3e-7 off the exact result
+    // (2-norm) in one chain, 1.6e-7 in chains of 64.  32 columns and fewer: of 32, 32 -> 32 channels, 5 taps, 1.45e-7 (in chains of 80 1.67e-7).
+    // The additions are a sixteenth and an eighth of the matrix instructions' time, which start a chain from a constant zero.
+    constexpr int CHAIN = WC == 1 ? 4 : 8;              // steps of eight elements
     f16v acc, tot;
 #pragma unroll
     for (int e = 0; e < 16; ++e) tot[e] = 0.f;
@@ -299,28 +301,37 @@ __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
         b = ld4(brow);                                  // behind the last element: padding or the next column, not used
         __builtin_amdgcn_sched_barrier(0);              // requested before the products in front of them run, not behind
       };
-      auto products = [&](const float4& a, const float4& b) __attribute__((always_inline)) {
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, acc, 0, 0, 0);
+      auto products = [&](const float4& a, const float4& b, const bool first) __attribute__((always_inline)) {
+        const f16v none = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.x, b.x, first ? none : acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.y, b.y, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.z, b.z, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(a.w, b.w, acc, 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
       };
-      while (q < qe) {
-        const int qc = min(q + kC1Chain, qe);
+      for (; q + CHAIN <= qe; q += CHAIN) {
+#pragma unroll
+        for (int i = 0; i < CHAIN; i += 2) {
+          next(a1, b1);
+          products(a0, b0, i == 0);
+          next(a0, b0);
+          products(a1, b1, false);
+        }
+#pragma unroll
+        for (int e = 0; e < 16; ++e) tot[e] += acc[e];
+      }
+      if (q < qe) {                                     // a shorter one
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-        for (; q + 2 <= qc; q += 2) {
+        for (; q + 2 <= qe; q += 2) {
           next(a1, b1);
-          products(a0, b0);
+          products(a0, b0, false);
           next(a0, b0);
-          products(a1, b1);
+          products(a1, b1, false);
         }
-        if (q < qc) {
+        if (q < qe) {
           next(a1, b1);
-          products(a0, b0);
-          a0 = a1; b0 = b1;
-          ++q;
+          products(a0, b0, false);
         }
 #pragma unroll
         for (int e = 0; e < 16; ++e) tot[e] += acc[e];

@@ -75,6 +75,39 @@ def test_products_along_one_axis_add_in_short_chains(ci, co, taps, w, batch):
     assert z <= bar(64, chains[0]) and dx <= bar(64, chains[1]) + 0.4 * 2.0 ** -24
 
 
+def lost_in_the_longest_chain(unit, h, w, batch):
+    """How many terms of a product vanish next to a large one: all inputs are 1, the first weight of every channel is 2^24 and the others
+    are 1/4, so what is added to the large term one by one rounds away, and what is added up elsewhere first does not (chains of a multiple
+    of 8 terms: their sums are even).  The largest number over all rows that see every tap."""
+    import torch
+    import paper_2110_02781_amd as P
+    model = P.model_create([unit], h, w, unit["cin"], P.F32)
+    stage = P.stage_create(model, 0, 1, batch, 1)
+    try:
+        kw, co, ci = unit["kw"], unit["cout"], unit["cin"]
+        wt = np.full((co, kw * ci), 0.25, np.float32)
+        wt[:, 0] = 2.0 ** 24
+        P.stage_import_weights(stage, 0, np.concatenate([wt.ravel(), np.ones(co), np.zeros(co)]).astype(np.float32))
+        x = torch.ones(batch, h, w, ci, device="cuda")
+        P.stage_forward(stage, 0, x, None, torch.cuda.current_stream().cuda_stream)
+        z = P.stage_export_conv_output(stage, 0, 0, 0, batch * h * w * co).reshape(batch * h, w, co).astype(np.float64)
+        z = z[:, kw // 2:w - kw // 2]
+        return float(((kw * ci - 1) * 0.25 - (z - 2.0 ** 24)).max() * 4)
+    finally:
+        P.stage_destroy(stage)
+        P.model_destroy(model)
+
+
+# 64 columns: chains of 64 terms; 32 columns and fewer, where wavefronts share a tile's reduction: of 32.  Tiles of 32, 64 and 128 rows
+@pytest.mark.parametrize("ci,co,taps,w,batch,chain", [(64, 64, 5, 128, 17, 64), (64, 64, 5, 128, 80, 64), (64, 64, 5, 128, 256, 64), (64, 64, 9, 128, 256, 64),
+                                                      (32, 32, 5, 128, 256, 32), (64, 32, 9, 128, 256, 32), (64, 32, 9, 128, 80, 32), (32, 24, 9, 128, 600, 32)])
+def test_no_longer_chains_along_one_axis(ci, co, taps, w, batch, chain):
+    print(f"1-D chain {ci}->{co} taps {taps} window {w} batch {batch}", flush=True)
+    lost = lost_in_the_longest_chain(unit(ci, co, taps), 1, w, batch)
+    print(f"  {lost:.0f} terms lost", flush=True)
+    assert 0 <= lost < chain
+
+
 @pytest.mark.parametrize("w,batch", [(128, 8), (128, 16), (100, 20)])
 def test_short_layers_along_one_axis_that_take_sums_lose_nothing_in_their_weight_gradients(w, batch):
     """Layers of one stage do their BatchNorm backward on the way into both gradients, layers of a stage each have a launch for it and more
