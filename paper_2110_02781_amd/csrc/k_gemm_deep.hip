@@ -168,6 +168,23 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   for (int a = 0; a < S; ++a)
 #pragma unroll
     for (int b = 0; b < T; ++b) acc[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f};
+  // fp32: a chain of additions per step, 32 reduction elements, not one through the whole reduction: the streaming kernel's wavefronts share a
+  // reduction of 128 and more where rows are few, and this may not be further off.  8192 rows, 192 -> 32: 1.38e-7 off the exact product
+  // (2-norm) there, 1.48e-7 in chains of 64, 1.14e-7 in these; 1568 rows, 960 -> 160: 2.8e-7, 1.63e-7, 1.46e-7.  Against chains of 64 a launch is 0 - 3 %
+  // longer (3136 rows 160 -> 960 data gradient 18.4 / 19.0 us, 25088 rows 576 -> 96 forward 41.6 / 41.7).
+  f4v_t tot[F32 ? S : 1][F32 ? T : 1];
+  if constexpr (F32)
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+      for (int b = 0; b < T; ++b) tot[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f};
+  auto meet = [&]() __attribute__((always_inline)) {
+    if constexpr (F32)
+#pragma unroll
+      for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) tot[a][b] += acc[a][b];
+  };
 
   // one step: set -> LDS buffer s % 2, barrier (which also says that everyone has finished multiplying the step before
   // last, this buffer's previous contents), the set's next request (D steps ahead; past the end: zeros), multiply
@@ -200,8 +217,10 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
 #pragma unroll
           for (int a = 0; a < S; ++a)
 #pragma unroll
-            for (int b = 0; b < T; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32((&yf[b].x)[e], (&xf[a].x)[e], acc[a][b], 0, 0, 0);
+            for (int b = 0; b < T; ++b)
+              acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32((&yf[b].x)[e], (&xf[a].x)[e], ks + e == 0 ? f4v_t{0.f, 0.f, 0.f, 0.f} : acc[a][b], 0, 0, 0);
       }
+      meet();
     } else {
 #pragma unroll
       for (int ks = 0; ks < KS / 32; ++ks) {
@@ -220,26 +239,7 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
       }
     }
   };
-  // fp32: a chain of additions per 64 reduction elements, not one through the whole reduction (1568 rows, 960 -> 160: 1.4e-7 off the exact product
-  // (2-norm), the streaming kernel 2.0e-7)
-  f4v_t tot[F32 ? S : 1][F32 ? T : 1];
-  auto clear_tot = [&]() __attribute__((always_inline)) {
-    if constexpr (F32)
-#pragma unroll
-      for (int a = 0; a < S; ++a)
-#pragma unroll
-        for (int b = 0; b < T; ++b) tot[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f};
-  };
-  auto meet = [&]() __attribute__((always_inline)) {
-    if constexpr (F32)
-#pragma unroll
-      for (int a = 0; a < S; ++a)
-#pragma unroll
-        for (int b = 0; b < T; ++b) { tot[a][b] += acc[a][b]; acc[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f}; }
-  };
-
   const int nsteps = RP / KS;
-  clear_tot();
 #pragma unroll
   for (int d = 0; d < D; ++d) {
     fetch(set[d], d * KS);
@@ -253,18 +253,15 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
   for (; s0 + D <= nsteps; s0 += D) {
 #pragma unroll
     for (int d = 0; d < D; ++d) step(set[d], s0 + d);
-    meet();
   }
 #pragma unroll
   for (int d = 0; d + 1 < D; ++d)
     if (s0 + d < nsteps) step(set[d], s0 + d);
-  if constexpr (F32) {
-    meet();
+  if constexpr (F32)
 #pragma unroll
     for (int a = 0; a < S; ++a)
 #pragma unroll
       for (int b = 0; b < T; ++b) acc[a][b] = tot[a][b];
-  }
 
   // ---- results: acc[a][b][e] is out[m0 + wm*16S + 16a + l16][j0 + wn*16T + 16b + 4G + e] ----
   float s1[T][4], s2[T][4];

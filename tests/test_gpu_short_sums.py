@@ -156,3 +156,13 @@ def test_short_layers_along_one_axis_that_take_sums_lose_nothing_in_their_weight
         ea, eb = (np.linalg.norm(t - g) / np.linalg.norm(g) for t in (a, b))
         print(f"  layer {u}: {ea:.3e} in one stage, {eb:.3e} alone", flush=True)
         assert ea <= 1.05 * eb
+
+
+# fp32 pointwise layers above 512 rows on the long-reduction kernel: chains of 32 terms in short and long reductions, as short as where four
+# wavefronts share a reduction of 128 (192 -> 32, 8192 rows: 1.38e-7 off in that way, 1.48e-7 in chains of 64)
+@pytest.mark.parametrize("ci,co,hw,batch", [(192, 32, 64, 2), (128, 64, 32, 3), (960, 160, 14, 16), (64, 64, 64, 4), (136, 88, 33, 5)])
+def test_long_pointwise_products_add_in_short_chains(ci, co, hw, batch):
+    print(f"long product {ci}->{co} {hw}x{hw} batch {batch}", flush=True)
+    lost = lost_in_the_longest_chain(unit(ci, co), hw, hw, batch)
+    print(f"  {lost:.0f} terms lost", flush=True)
+    assert 0 <= lost < 32
