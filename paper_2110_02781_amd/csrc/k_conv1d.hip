@@ -393,6 +393,9 @@ __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
 // where there are several: what it then loads twice is less than the partials of twice as many row ranges.  64 -> 64 channels, 32768
 // rows: 24.3 us and 128 partials, added up with those of 32 -> 64 in 5.9; four wavefronts, nothing on its way, two blocks per CU and 256
 // partials 29 and 11.6.
+// Partials meet in float64, and so do the wavefronts of a piece; a wavefront adds every other step of its rows to a second set of accumulators.
+// Where it was one chain and the wavefronts met in fp32, 32768 rows of 16 -> 16, 3 taps, were 1.13e-7 off 64 bits (2-norm), of 64 -> 64, 5 taps, 2.10e-7;
+// with each wavefront's chain a partial 0.95e-7 and 2.08e-7; so 0.89e-7 and 1.55e-7, at the same time.
 struct Conv1dWgArgs {
   Conv1dArgs c;
   int nco, nkg;            // pieces along Cout (32 each) and along kw * Cin (80 each)
@@ -436,11 +439,14 @@ __global__ __launch_bounds__(512) void conv1d_wgrad_k(Conv1dWgArgs a) {
     const int co = (pco * kC1RT + q) * 16 + l16;
     doff[q] = xbuf + (4 * rsub + rg) * LD + (live && co < p.Cout ? co : 0);    // a row past the end is not written either
   }
-  f4v acc[kC1RT][kC1CT];
+  constexpr int SETS = STEPS > 1 ? 2 : 1;
+  f4v acc[SETS][kC1RT][kC1CT];
 #pragma unroll
-  for (int i = 0; i < kC1RT; ++i)
+  for (int h = 0; h < SETS; ++h)
 #pragma unroll
-    for (int q = 0; q < kC1CT; ++q) acc[i][q] = f4v{0.f, 0.f, 0.f, 0.f};
+    for (int i = 0; i < kC1RT; ++i)
+#pragma unroll
+      for (int q = 0; q < kC1CT; ++q) acc[h][i][q] = f4v{0.f, 0.f, 0.f, 0.f};
 
   const int it_beg = range * p.tiles_per_range, it_end = min(it_beg + p.tiles_per_range, p.itiles);
   RowVecs<T, NX> xt;
@@ -504,7 +510,8 @@ __global__ __launch_bounds__(512) void conv1d_wgrad_k(Conv1dWgArgs a) {
 #pragma unroll
         for (int q = 0; q < kC1CT; ++q)
 #pragma unroll
-          for (int i = 0; i < kC1RT; ++i) acc[i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[s & 1][i], x[s & 1][q], acc[i][q], 0, 0, 0);
+          for (int i = 0; i < kC1RT; ++i)
+            acc[s % SETS][i][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(d[s & 1][i], x[s & 1][q], acc[s % SETS][i][q], 0, 0, 0);
         __builtin_amdgcn_sched_barrier(0);
         m += 4 * RS;
         t += 4 * RS;                                    // at most 32, and a window has at least 16 rows
@@ -515,14 +522,16 @@ __global__ __launch_bounds__(512) void conv1d_wgrad_k(Conv1dWgArgs a) {
     if (wave < 4) advance();
     __syncthreads();
   }
-  // the wavefronts of a piece meet: each adds and writes its share of the rows of the sixteen-row tiles
+  // The wavefronts of a piece meet in float64: each adds and writes its share of the rows of the sixteen-row tiles
   float* meet = smem;                                   // [8][kC1Acc][64]
 #pragma unroll
   for (int i = 0; i < kC1RT; ++i)
 #pragma unroll
-    for (int q = 0; q < kC1CT; ++q)
+    for (int q = 0; q < kC1CT; ++q) {
+      if (SETS > 1) acc[0][i][q] += acc[SETS - 1][i][q];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) meet[(wave * kC1Acc + (i * kC1CT + q) * 4 + r) * 64 + lane] = acc[i][q][r];
+      for (int r = 0; r < 4; ++r) meet[(wave * kC1Acc + (i * kC1CT + q) * 4 + r) * 64 + lane] = acc[0][i][q][r];
+    }
   __syncthreads();
   if (!live) return;
   float* out = reinterpret_cast<float*>(p.out) + (size_t)range * p.Cout * K;
@@ -530,9 +539,10 @@ __global__ __launch_bounds__(512) void conv1d_wgrad_k(Conv1dWgArgs a) {
   float v[EACH];
 #pragma unroll
   for (int j = 0; j < EACH; ++j) {
-    v[j] = 0.f;
+    double t = 0.0;
 #pragma unroll
-    for (int w = 0; w < RS; ++w) v[j] += meet[((slot + w * GPB) * kC1Acc + rsub * EACH + j) * 64 + lane];
+    for (int w = 0; w < RS; ++w) t += (double)meet[((slot + w * GPB) * kC1Acc + rsub * EACH + j) * 64 + lane];
+    v[j] = (float)t;
   }
   if (pco * 16 * kC1RT + 16 * kC1RT <= p.Cout && pkg * 16 * kC1CT + 16 * kC1CT <= K) {       // a whole piece: nothing to ask for each value
 #pragma unroll

@@ -166,3 +166,39 @@ def test_long_pointwise_products_add_in_short_chains(ci, co, hw, batch):
     lost = lost_in_the_longest_chain(unit(ci, co), hw, hw, batch)
     print(f"  {lost:.0f} terms lost", flush=True)
     assert 0 <= lost < 32
+
+
+# 1-D weight gradients above 2048 rows: a wavefront adds its share of a block's rows (half of them, a quarter or an eighth) in two chains, what meets
+# behind them is four more roundings at most, and dz carries its own three
+@pytest.mark.parametrize("ci,co,taps,w,batch,chain", [(16, 16, 3, 128, 256, 16), (12, 32, 5, 128, 256, 16), (32, 32, 5, 128, 256, 16), (64, 64, 9, 128, 40, 32),
+                                                      (64, 64, 5, 128, 256, 64), (64, 64, 5, 256, 512, 256)])
+def test_weight_gradients_along_one_axis_add_in_short_chains(ci, co, taps, w, batch, chain):
+    import torch
+    import paper_2110_02781_amd as P
+    print(f"1-D weight gradient {ci}->{co} taps {taps} window {w} batch {batch}", flush=True)
+    u = unit(ci, co, taps)
+    model = P.model_create([u], 1, w, ci, P.F32)
+    stage = P.stage_create(model, 0, 1, batch, 1)
+    try:
+        vec = P.models.init_unit_params([u], 75)[0]
+        P.stage_import_weights(stage, 0, vec)
+        x = torch.from_numpy(synth.normal(75, "x", (batch, 1, w, ci)).astype(np.float32)).cuda()
+        dy = torch.from_numpy(synth.normal(75, "dy", (batch, 1, w, co)).astype(np.float32)).cuda()
+        sp = torch.cuda.current_stream().cuda_stream
+        P.stage_forward(stage, 0, x, None, sp)
+        P.stage_backward(stage, 0, dy, torch.empty_like(x), sp)
+        n = co * taps * ci
+        g = P.stage_export_grads(stage, 0, vec.size)[:n].astype(np.float64)
+    finally:
+        P.stage_destroy(stage)
+        P.model_destroy(model)
+    wt = torch.from_numpy(vec[:n].astype(np.float64)).cuda().requires_grad_()
+    padded = torch.nn.functional.pad(x.double(), (0, 0, taps // 2, taps // 2))
+    z = torch.cat([padded[:, :, i:i + w] for i in range(taps)], dim=3).reshape(-1, taps * ci) @ wt.reshape(co, -1).t()
+    var, mean = torch.var_mean(z, 0, correction=0)
+    want, = torch.autograd.grad((z - mean) * torch.rsqrt(var + 1e-5), wt, dy.double().reshape(-1, co))
+    want = want.cpu().numpy()
+    err = np.linalg.norm(g - want) / np.linalg.norm(want)
+    limit = 1.1 * 0.4 * 2.0 ** -24 * np.sqrt((chain + 1) / 2 + 6)
+    print(f"  error {err:.3e} (bar {limit:.3e})", flush=True)
+    assert err <= limit
