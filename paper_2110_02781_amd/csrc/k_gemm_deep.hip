@@ -342,23 +342,32 @@ struct DeepPlan { int S, T, itiles, jtiles; size_t lds; };
 
 // rows M, reduction extent R, output columns NC
 static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
-  // bfloat16: reductions of 192 and more as they come; shorter ones up to 32768 rows, but layers that widen them there, whose time is the
-  // output's.  us on the streaming kernels and here, forward 700 rows 960 -> 320 10.5 / 7.0, 2100 24 -> 144 6.3 / 2.9, 3136 160 -> 960 8.7 / 7.2, 6825 48 -> 288
-  // 5.7 / 5.0, 12544 40 -> 96 4.3 / 3.8, 144 -> 64 6.2 / 4.2, 25088 96 -> 64 5.0 / 4.8; but 12544 64 -> 384 6.7 / 7.6, 25088 32 -> 192 5.4 / 7.5, 88 -> 528 14.8 / 16.3, 136 -> 816
-  // 26.4 / 36.4.  Data gradient 1568 rows of 960 -> 320 8.7 / 5.2, 2048 160 -> 960 9.9 / 6.2, 8192 96 -> 48 3.5 / 2.9, 25088 96 -> 64 4.7 / 4.1, 136 -> 816
-  // 27.5 / 24.5; but 20800 96 -> 32 3.6 / 3.9, 25088 144 -> 32 4.4 / 4.8.
+  // bfloat16: reductions of 192 and more as they come; shorter ones up to 32768 rows, but layers that widen them much there, whose time is the
+  // output's.  us on the streaming kernels and here, forward 700 rows 960 -> 320 10.5 / 7.0, 2100 24 -> 144 6.3 / 2.9, 3136 160 -> 960 8.7 / 7.2, 6825 48 -> 288 5.7 / 5.0, 12544 40 -> 96 4.3 /
+  // 3.8, 144 -> 64 6.2 / 4.2, 25088 96 -> 64 5.0 / 4.8; but 12544 64 -> 384 6.7 / 7.6, 25088 32 -> 192 5.4 / 7.5, 88 -> 528 14.8 / 16.3, 136 -> 816 26.4 / 36.4.
+  // Data gradient 1568 rows of 960 -> 320 8.7 / 5.2, 2048 160 -> 960 9.9 / 6.2, 8192 96 -> 48 3.5 / 2.9, 25088 96 -> 64 4.7 / 4.1, 136 -> 816 27.5 / 24.5; but 20800
+  // 96 -> 32 3.6 / 3.9, 25088 144 -> 32 4.4 / 4.8.
+  // The streaming kernels take 32 reduction elements and 64 columns a step, a step here is 64 and a tile up to 160: where the layer is whole in the first
+  // and has more than 4 M results, they are the faster ones from twice the width on.  These with some 3 us of the events around the launch: forward 8192 rows 96 -> 576 10.5 / 11.6, 160 -> 960 14.4 / 15.7, 16385
+  // 160 -> 320 12.4 / 14.8, 25088 96 -> 288 11.9 / 14.3, 64 -> 192 9.3 / 10.0 (20480 9.2 / 8.3), 128 -> 256 12.6 / 13.5.  Data gradient (columns of 64, and a reduction of
+  // one step or with half a step left over) 25088 rows 576 -> 96 16.6 / 19.7, 384 -> 96 13.5 / 16.5, 384 -> 64 12.1 / 13.4, 320 -> 160 14.2 / 16.1, 16385 576 -> 160 16.7 / 17.6; but
+  // 768 -> 128 18.0 / 18.8 and 23.1 / 23.0, 528 -> 88 17.0 / 16.1, 720 -> 120 24.4 / 19.9, 480 -> 160 20.2 / 18.9.
   // fp32: everything that is not for the short kernel in front, up to 65536 rows, but forward layers that widen a short reduction, whose time is
-  // the output's: us on the streaming kernels and here, forward 1568 rows 960 -> 160 18.9 / 12.9, 3136 960 -> 160 30.1 / 17.1, 6272 384 -> 96
+  // the output's, and beyond 32768 rows reductions of few steps: forward 1568 rows 960 -> 160 18.9 / 12.9, 3136 960 -> 160 30.1 / 17.1, 6272 384 -> 96
   // 20.8 / 10.3, 12544 64 -> 384 13.8 / 13.6, 16384 192 -> 32 11.5 / 5.5, 50176 144 -> 32 17.9 / 16.3; but 8192 32 -> 192 4.8 / 5.1, 25088 64 -> 384 20.9 / 22.8,
-  // 96 -> 576 37.3 / 37.9, 50176 32 -> 192 14.6 / 17.0, 100352 144 -> 32 33.8 / 34.3.  Data gradient 800 rows of 960 -> 320 17.8 / 8.6, 6272 96 -> 576 20.8 / 12.3, 25088 69.0 / 35.2,
-  // 8192 48 -> 96 7.1 / 3.4, 50176 192 -> 64 21.3 / 20.5, 144 -> 32 13.0 / 13.1.
+  // 96 -> 576 37.3 / 37.9, 50176 32 -> 192 14.6 / 17.0, 100352 144 -> 32 33.8 / 34.3.  Data gradient 800 rows of 960 -> 320
+  // 17.8 / 8.6, 6272 96 -> 576 20.8 / 12.3, 25088 69.0 / 35.2, 8192 48 -> 96 7.1 / 3.4, 50176 192 -> 64 21.3 / 20.5, 144 -> 32 13.0 / 13.1.  With the events' 3 us:
+  // forward 50176 64 -> 64 12.8 / 13.9 (25088 9.5 / 9.3), 96 -> 96 24.1 / 25.3, data gradient 50176 192 -> 32 16.5 / 17.9, 65536 18.7 / 20.7, 96 -> 24 13.7 / 14.8.
+  const bool many = M * (size_t)NC > ((size_t)4 << 20);
   if (M > 65536 || R > kDeepMaxR || R % 8 || NC % 8 || NC < 32) return false;
   if (dt == 0) {
     if (M <= 512 || R < 16) return false;
-    if (!dgrad && ((M > 4096 && R < 64 && NC > 2 * R) || (M > 16384 && NC > R))) return false;
+    if (!dgrad && ((M > 4096 && R < 64 && NC > 2 * R) || (M > 16384 && NC > R) || (M > 32768 && R <= 128 && NC > 32))) return false;
+    if (dgrad && M > 32768 && R <= 32 && NC > R) return false;
   } else if (R < 192) {
     if (M <= 512 || M > 32768 || R < 16) return false;
     if (dgrad ? M > 16384 && R < 64 && NC > 2 * R : M > 8192 && NC > 3 * R) return false;
+    if (many && NC >= 2 * R && (dgrad ? NC % 64 == 0 && (R == 64 || R % 64 == 32) : R % 32 == 0)) return false;
   } else if (M <= 512) {
     return false;
   }
