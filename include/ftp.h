@@ -320,7 +320,8 @@ int ftp_stage_copy_units(ftp_stage* dst, const ftp_stage* src, int unit_lo, int 
  * a launch counted once) and floating-point operations.  max_launches bounds the
  * event pool; exceeding it makes end return FTP_ERR_ARG with partial rows.  A
  * negative max_launches (pool size = its magnitude) splits the rows further by
- * problem shape: the name then reads "family d0 d1 d2" (GEMMs: M K N).
+ * problem shape: the name then reads "family d0 d1 d2" (GEMMs: M K N).  Where a family has a kernel on several tiles, rows
+ * "__route <kernel> <tile> family d0 d1 d2" count its launches (no time of their own).
  * One more row, named "__event_pair_overhead" (launches = 1), gives in total_ms what a pair of events adds
  * to the launch it brackets, measured at begin on empty kernels: take it off every launch's time to get kernel
  * durations comparable with a profiler's.

@@ -1,6 +1,6 @@
-// Pointwise layers with a LONG reduction and few rows: in bfloat16 the project layers (forward) and the expand layers
-// (data gradient) of the low-resolution inverted residual blocks, up to 25 K rows against a reduction of up to 1800
-// channels, and most shorter ones there; in fp32 nearly all layers up to 65536 rows (deep_plan).  Their tensors are small (they stay in the memory-side cache) and
+// Pointwise layers with a LONG reduction and few rows: the project layers (forward) and the expand layers (data gradient) of the
+// low-resolution inverted residual blocks, against a reduction of up to 2048 channels, and most shorter ones there; in fp32
+// nearly all layers (deep_plan says which, in either type).  Their tensors are small (they stay in the memory-side cache) and
 // their arithmetic intensity is at the MFMA / HBM balance, so what they need is a GEMM that keeps the matrix cores fed, not a streaming kernel.
 // In fp32 the matrix instructions are what bounds it (they run at a sixteenth of the rate and not beside vector instructions): there a grid that
 // fills the 256 CUs with small tiles, and few instructions a step, are what counts.
@@ -434,25 +434,40 @@ static void deep_launch(int dt, hipStream_t st, const DeepArgs& a, const DeepPla
   else deep_launch_tile<bf16_t>(st, a, d, mode);
 }
 
+static const char* deep_name(const DeepPlan& d) {
+  switch (d.S * 10 + d.T) {
+    case 11: return "deep 1x1";
+    case 21: return "deep 2x1";
+    case 22: return "deep 2x2";
+    case 23: return "deep 2x3";
+    case 42: return "deep 4x2";
+    case 43: return "deep 4x3";
+    case 44: return "deep 4x4";
+    default: return "deep 4x5";
+  }
+}
+
 // z[M][N] = A'[M][K] * W[N][K]^T; stats as in pw_fwd (P_out = partials written)
-void pw_fwd_deep(int dt, hipStream_t st, HView av, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out) {
+const char* pw_fwd_deep(int dt, hipStream_t st, HView av, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out) {
   DeepPlan d;
-  if (!deep_plan(dt, M, K, N, false, &d)) { launch_plan_failed("long-reduction pointwise forward called for a shape it does not take"); return; }
+  if (!deep_plan(dt, M, K, N, false, &d)) { launch_plan_failed("long-reduction pointwise forward called for a shape it does not take"); return nullptr; }
   DeepArgs a{};
   a.x = av.z; a.y = w; a.scale = av.scale; a.shift = av.shift; a.act = av.act;
   a.out = z; a.stats = stats; a.M = (int)M; a.R = K; a.NC = N; a.jtiles = d.jtiles;
   if (P_out) *P_out = d.itiles;
   deep_launch(dt, st, a, d, av.scale ? DEEP_FWD_VIEW : DEEP_FWD);
+  return deep_name(d);
 }
 
 // dA[M][K] = dZ[M][N] * W[N][K] (+ res)
-void pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA) {
+const char* pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA) {
   DeepPlan d;
-  if (!deep_plan(dt, M, N, K, true, &d)) { launch_plan_failed("long-reduction pointwise data gradient called for a shape it does not take"); return; }
+  if (!deep_plan(dt, M, N, K, true, &d)) { launch_plan_failed("long-reduction pointwise data gradient called for a shape it does not take"); return nullptr; }
   DeepArgs a{};
   a.x = dz; a.y = w; a.res = res; a.out = dA;
   a.M = (int)M; a.R = N; a.NC = K; a.jtiles = d.jtiles;
   deep_launch(dt, st, a, d, res ? DEEP_DGRAD_RES : DEEP_DGRAD);
+  return deep_name(d);
 }
 
 }  // namespace ftp

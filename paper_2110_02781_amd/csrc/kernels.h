@@ -18,6 +18,7 @@ namespace ftp {
 struct KScope {
   KScope(hipStream_t st, const char* name, double alg_bytes, double flops, long d0 = -1, long d1 = -1, long d2 = -1);
   ~KScope();
+  void route(const char* name);      // which kernel of the family took it (a literal)
   int slot;
   hipStream_t st;
 };
@@ -259,12 +260,12 @@ void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, 
                   hipEvent_t ev_sum, std::vector<ReduceJob>* left = nullptr);
 
 
-// bfloat16 pointwise layers with a long reduction (>= 192; >= 64 up to 8192 rows) and 2 K - 64 K rows: forward (A' * W^T, BatchNorm partial sums
-// as pw_fwd leaves them) and data gradient (dZ * W (+ res)) on 2 x 2 wavefront tiles of 16x16x32 MFMAs; pw_fwd and
-// pw_dgrad dispatch to them.  R = reduction extent, NC = output columns.
+// Pointwise layers on double-buffered LDS tiles: forward (A' * W^T, BatchNorm partial sums as pw_fwd leaves them) and data gradient (dZ * W (+ res)).
+// Which layers, in either type: deep_plan in k_gemm_deep.hip.  pw_fwd and pw_dgrad dispatch to them.  R = reduction extent, NC = output columns.
+// They return the tile for the trace.
 int pw_deep_ok(int dt, size_t M, int R, int NC, bool dgrad);
-void pw_fwd_deep(int dt, hipStream_t st, HView a, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out);
-void pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA);
+const char* pw_fwd_deep(int dt, hipStream_t st, HView a, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out);
+const char* pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA);
 // the weight gradient for bfloat16 layers with more than 2048 rows: operands staged untransposed, transposed on the
 // way out of LDS (pw_wgrad dispatches to it; ws: pw_wgrad_tr_ws floats)
 int pw_wgrad_tr_ok(int dt, size_t M, int K, int N);

@@ -14,7 +14,7 @@
 void ftp_set_error(const char* fmt, ...);
 
 namespace {
-struct Rec { const char* name; double bytes, flops; long d[3]; hipEvent_t e0, e1; };
+struct Rec { const char *name, *route; double bytes, flops; long d[3]; hipEvent_t e0, e1; };
 struct Trace {
   bool on = false;
   std::vector<Rec> recs;
@@ -69,8 +69,11 @@ KScope::KScope(hipStream_t s, const char* name, double alg_bytes, double flops, 
   if (g_trace.used >= g_trace.recs.size()) { g_trace.overflow = true; return; }
   slot = (int)g_trace.used++;
   Rec& r = g_trace.recs[slot];
-  r.name = name; r.bytes = alg_bytes; r.flops = flops; r.d[0] = d0; r.d[1] = d1; r.d[2] = d2;
+  r.name = name; r.route = nullptr; r.bytes = alg_bytes; r.flops = flops; r.d[0] = d0; r.d[1] = d1; r.d[2] = d2;
   (void)hipEventRecord(r.e0, st);
+}
+void KScope::route(const char* name) {
+  if (slot >= 0) g_trace.recs[slot].route = name;
 }
 KScope::~KScope() {
   if (slot >= 0) (void)hipEventRecord(g_trace.recs[slot].e1, st);
@@ -123,6 +126,12 @@ extern "C" int ftp_ktrace_end(ftp_ktrace_row* rows, int max_rows, int* n_rows) {
     ftp_ktrace_row& row = agg[key];
     if (row.launches == 0) { memset(&row, 0, sizeof(row)); strncpy(row.name, key, sizeof(row.name) - 1); }
     row.launches += 1; row.total_ms += ms; row.alg_bytes += r.bytes; row.flops += r.flops;
+    if (g_trace.detail && r.route) {
+      snprintf(key, sizeof(key), "__route %s %s %ld %ld %ld", r.route, r.name, r.d[0], r.d[1], r.d[2]);
+      ftp_ktrace_row& at = agg[key];
+      if (at.launches == 0) { memset(&at, 0, sizeof(at)); strncpy(at.name, key, sizeof(at.name) - 1); }
+      at.launches += 1;                    // no time of its own: the sum over the rows stays what it is
+    }
   }
   int n = 0;
   for (auto& kv : agg) { if (n < max_rows) rows[n++] = kv.second; }

@@ -75,6 +75,17 @@ def launches(run):
     return {r["name"]: r["launches"] for r in P.ktrace_end()}
 
 
+def routes(run):
+    """{"<kernel> <tile> family d0 d1 d2": launches} of run(), of the kernels that say which tile they run."""
+    import torch
+    import paper_2110_02781_amd as P
+    torch.cuda.synchronize()
+    P.ktrace_begin(-4096)
+    run()
+    torch.cuda.synchronize()
+    return {r["name"][8:]: r["launches"] for r in P.ktrace_end() if r["name"].startswith("__route ")}
+
+
 def assert_two_streams(layers, backward):
     """backward() is that of a stage that runs weight gradients on its second stream: it sums the partial weight gradients of each of at
     least `layers` layers by themselves, where a stage that runs all weight gradients at the end of the call has a launch or two for all."""
