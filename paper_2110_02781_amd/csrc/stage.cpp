@@ -307,11 +307,10 @@ struct ftp_stage {
   // patch matrix leaves it behind; if nothing has used the buffer since, the weight gradient of the same layer and
   // slot takes it as it is instead of writing the same matrix again.
   const void* im2col_of = nullptr;
-  // The gradient tensor whose BatchNorm-backward partial sums bn_part holds already (left there by the depthwise data
-  // gradient that produced it), and how many partials; nullptr: none.
-  const void* bwd_sums_of = nullptr;
-  int bwd_sums_P = 0;
-  bool bwd_sums_other = false;         // they are in the second half of the buffer (a short 1-D convolution reads one half and fills the other)
+  // BatchNorm-backward partial sums that the data gradient of a layer has left while it wrote the gradient tensor `of` (nullptr: none), for the
+  // layer that reads that tensor next: where in bn_part they are, and how many.  Whoever leaves them sets all three (leave_sums), whoever needs
+  // sums asks for them by its gradient tensor (take_sums).
+  struct LeftSums { const void* of = nullptr; float* partial = nullptr; int P = 0; } left;
   size_t im2col_elems = 0;
   size_t ws_floats = 0;
   int max_c = 0;
@@ -1057,6 +1056,14 @@ static size_t dz_size(const ftp_stage* s, const Sub& sb) {
   return align_up((size_t)s->batch * sb.g.Hout * sb.g.Wout * sb.g.Cout * s->es, 256);
 }
 
+static void leave_sums(ftp_stage* s, const void* of, float* partial, int P) { s->left = ftp_stage::LeftSums{of, partial, P}; }
+// the sums left for the gradient dA, if there are any (P > 0): they can be taken once
+static ftp_stage::LeftSums take_sums(ftp_stage* s, const void* dA) {
+  const ftp_stage::LeftSums l = s->left.of == dA ? s->left : ftp_stage::LeftSums{};
+  s->left.of = nullptr;
+  return l;
+}
+
 // A short 1-D convolution that does its own BatchNorm backward from sums the layer behind has left, and whether unit i's convolution
 // can leave them for the one in front.
 static bool conv1d_takes_sums(const ftp_stage* s, const UnitPlan& p) {
@@ -1107,11 +1114,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   // weight gradient) is one pass on this stream; dz never reaches memory.
   if (mode == BWD_FULL && sb.type == SUB_PW && dIn && !bn_bwd_small_ok(M, C) && pw_bwd_fused_ok(s->dt, M, g.Cin, g.Cout, in) &&
       (s->defers || (s->ws_fused && pw_bwd_fused_ws(M, g.Cin, g.Cout) <= s->ws_fused_floats))) {
-    int P = 0;
-    if (s->bwd_sums_of == dA) P = s->bwd_sums_P;
-    else bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, s->bn_part, &P);
-    s->bwd_sums_of = nullptr;
-    bn_bwd_finalize(st, s->bn_part, P, M, C, W.w32 + p.p_off + sb.gamma_off, stt, stt + C, s->grads + p.p_off + sb.gamma_off,
+    ftp_stage::LeftSums sums = take_sums(s, dA);
+    if (!sums.of) bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, sums.partial = s->bn_part, &sums.P);
+    bn_bwd_finalize(st, sums.partial, sums.P, M, C, W.w32 + p.p_off + sb.gamma_off, stt, stt + C, s->grads + p.p_off + sb.gamma_off,
                     s->grads + p.p_off + sb.beta_off, s->coef);
     // the sum of the kernel's partial weight gradients is off the data-gradient chain: it goes to the side stream,
     // and the next user of the partial buffer waits for it
@@ -1132,6 +1137,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   // noted for the end of the backward call: dz stays where it is written until then
   const bool noted = s->defers && (sb.type != SUB_DIRECT || p.axis[k]);
   if (mode != BWD_FROM_DZ) {
+    ftp_stage::LeftSums sums = take_sums(s, dA);
+    const BnPending left{sums.partial, sums.P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
+    const BnBwdIn own{dA, out, nullptr, nullptr, nullptr, s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off};
     if (batched) dz = s->dzring[s->bset * 3 + (int)k];
     else if (s->defers) {
       const Places at = take_places(s, dz_size(s, sb), p.part[k], st);
@@ -1142,30 +1150,21 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       dz = s->gbuf[b ? 4 : 2];
     }
     const bool small = bn_bwd_small_ok(M, C) != 0;
-    if (noted && s->bwd_sums_of == dA && takes_sums(s, p, k)) {
-      const BnPending sums{s->bn_part, s->bwd_sums_P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
-      const BnBwdIn bn{dA, out, nullptr, nullptr, nullptr, s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off};
-      s->bwd_sums_of = nullptr;
+    if (noted && sums.of && takes_sums(s, p, k)) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, s->grads + p.p_off + sb.w_off});
-      pw_dgrad_pro(s->dt, st, sums, bn, dz, conv_w(s, W, p.p_off + sb.w_off), M, g.Cin, g.Cout, dIn);
+      pw_dgrad_pro(s->dt, st, left, own, dz, conv_w(s, W, p.p_off + sb.w_off), M, g.Cin, g.Cout, dIn);
       return FTP_OK;
     }
-    if (noted && s->bwd_sums_of == dA && conv1d_takes_sums(s, p)) {
-      float* const from = s->bwd_sums_other ? other_partials(s) : s->bn_part;
-      const BnPending sums{from, s->bwd_sums_P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
-      const BnBwdIn own{dA, out, nullptr, nullptr, nullptr, s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off};
-      const bool leave = dIn && conv1d_leaves_sums(s, &p - s->plan.data());
-      float* left = !leave ? nullptr : s->bwd_sums_other ? s->bn_part : other_partials(s);
-      s->bwd_sums_of = nullptr;
-      conv1d_bwd_small(s->dt, st, nullptr, conv_w(s, W, p.p_off + sb.w_off), in, g, s->grads + p.p_off + sb.w_off, dIn, &sums, &own, left, &s->bwd_sums_P);
-      if (leave) { s->bwd_sums_of = dIn; s->bwd_sums_other = !s->bwd_sums_other; }
+    if (noted && sums.of && conv1d_takes_sums(s, p)) {
+      float* const fill = !dIn || !conv1d_leaves_sums(s, &p - s->plan.data()) ? nullptr : sums.partial == s->bn_part ? other_partials(s) : s->bn_part;
+      int P = 0;
+      conv1d_bwd_small(s->dt, st, nullptr, conv_w(s, W, p.p_off + sb.w_off), in, g, s->grads + p.p_off + sb.w_off, dIn, &left, &own, fill, &P);
+      if (fill) leave_sums(s, dIn, fill, P);
       return FTP_OK;
     }
     if (!small) {
-      int P = 0;
-      if (s->bwd_sums_of == dA) P = s->bwd_sums_P;          // the producer of dA has left the sums
-      else bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, s->bn_part, &P);
-      bn_bwd_finalize(st, s->bn_part, P, M, C, W.w32 + p.p_off + sb.gamma_off, stt, stt + C, s->grads + p.p_off + sb.gamma_off,
+      if (!sums.of) bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, sums.partial = s->bn_part, &sums.P);
+      bn_bwd_finalize(st, sums.partial, sums.P, M, C, W.w32 + p.p_off + sb.gamma_off, stt, stt + C, s->grads + p.p_off + sb.gamma_off,
                       s->grads + p.p_off + sb.beta_off, s->coef);
     }
     if (batched) {
@@ -1191,15 +1190,16 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   // takes nearly twice as long.  The data gradient goes first, alone; the weight gradient then shares the GPU with
   // the memory-bound BatchNorm backward of the layer in front.
   const bool dgrad_first = overlap && sb.type == SUB_DW && dIn != nullptr;
-  s->bwd_sums_of = nullptr;
+  s->left.of = nullptr;                // where the caller formed dz
   // a depthwise layer behind a BatchNorm + activation of the same unit (the expand layer's): its data gradient is that
   // BatchNorm's dA and can leave the backward sums on the way
   const bool with_sums = sb.type == SUB_DW && dIn != nullptr && mode == BWD_FULL && k > 0 && in.scale != nullptr &&
                          !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cout) && dw_dgrad_sums_ok(s->dt, g);
   auto run_dw_dgrad = [&]() {
     if (with_sums) {
-      dw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, s->bn_part, &s->bwd_sums_P);
-      s->bwd_sums_of = dIn;
+      int P = 0;
+      dw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, s->bn_part, &P);
+      leave_sums(s, dIn, s->bn_part, P);
     } else {
       dw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn);
     }
@@ -1207,8 +1207,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   auto run_conv1d_dgrad = [&]() {
     // behind another convolution of the stage: this is the dA of that one's BatchNorm + activation
     const bool sums = in.scale != nullptr && !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cin);
-    conv1d_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, sums ? s->bn_part : nullptr, &s->bwd_sums_P);
-    if (sums) s->bwd_sums_of = dIn;
+    int P = 0;
+    conv1d_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, sums ? s->bn_part : nullptr, &P);
+    if (sums) leave_sums(s, dIn, s->bn_part, P);
   };
   if (dgrad_first) run_dw_dgrad();
   if (batched && mode == BWD_FULL) {
@@ -1227,15 +1228,17 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       else pw_wgrad(s->dt, st, dz, in, M, g.Cin, g.Cout, part, gw);
     } else if (sb.type == SUB_PW) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
-      if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn, z_sum, z_sum ? s->bn_part : nullptr, &s->bwd_sums_P);
-      if (z_sum) s->bwd_sums_of = dIn;
+      int P = 0;
+      if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn, z_sum, z_sum ? s->bn_part : nullptr, &P);
+      if (z_sum && dIn) leave_sums(s, dIn, s->bn_part, P);
     } else if (sb.type == SUB_DW) {
       s->q_dw.push_back(DwWgradJob{dz, in, g, part, gw});
       if (dIn) run_dw_dgrad();
     } else if (dIn && conv1d_small_ok(g)) {
-      const bool leave = conv1d_leaves_sums(s, &p - s->plan.data());
-      conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn, nullptr, nullptr, leave ? s->bn_part : nullptr, &s->bwd_sums_P);
-      if (leave) { s->bwd_sums_of = dIn; s->bwd_sums_other = false; }
+      float* const fill = conv1d_leaves_sums(s, &p - s->plan.data()) ? s->bn_part : nullptr;
+      int P = 0;
+      conv1d_bwd_small(s->dt, st, dz, w, in, g, gw, dIn, nullptr, nullptr, fill, &P);
+      if (fill) leave_sums(s, dIn, fill, P);
     } else {
       conv1d_wgrad(s->dt, st, dz, in, g, part, gw, &s->q_red);
       if (dIn) run_conv1d_dgrad();
@@ -1364,7 +1367,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
   }
   s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
   s->dz_used = s->part_used = 0;
-  s->bwd_sums_of = nullptr;
+  s->left.of = nullptr;
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
   const void* d = dy_dev ? dy_dev : sl.dlogits;     // gradient of the current unit's output (read only)
   int flip = 0;
