@@ -1140,6 +1140,13 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     ftp_stage::LeftSums sums = take_sums(s, dA);
     const BnPending left{sums.partial, sums.P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
     const BnBwdIn own{dA, out, nullptr, nullptr, nullptr, s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off};
+    if (noted && sums.of && conv1d_takes_sums(s, p)) {         // no dz, and no partial weight gradients: it needs no places
+      float* const fill = !dIn || !conv1d_leaves_sums(s, &p - s->plan.data()) ? nullptr : sums.partial == s->bn_part ? other_partials(s) : s->bn_part;
+      int P = 0;
+      conv1d_bwd_small(s->dt, st, nullptr, conv_w(s, W, p.p_off + sb.w_off), in, g, s->grads + p.p_off + sb.w_off, dIn, &left, &own, fill, &P);
+      if (fill) leave_sums(s, dIn, fill, P);
+      return FTP_OK;
+    }
     if (batched) dz = s->dzring[s->bset * 3 + (int)k];
     else if (s->defers) {
       const Places at = take_places(s, dz_size(s, sb), p.part[k], st);
@@ -1153,13 +1160,6 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     if (noted && sums.of && takes_sums(s, p, k)) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, s->grads + p.p_off + sb.w_off});
       pw_dgrad_pro(s->dt, st, left, own, dz, conv_w(s, W, p.p_off + sb.w_off), M, g.Cin, g.Cout, dIn);
-      return FTP_OK;
-    }
-    if (noted && sums.of && conv1d_takes_sums(s, p)) {
-      float* const fill = !dIn || !conv1d_leaves_sums(s, &p - s->plan.data()) ? nullptr : sums.partial == s->bn_part ? other_partials(s) : s->bn_part;
-      int P = 0;
-      conv1d_bwd_small(s->dt, st, nullptr, conv_w(s, W, p.p_off + sb.w_off), in, g, s->grads + p.p_off + sb.w_off, dIn, &left, &own, fill, &P);
-      if (fill) leave_sums(s, dIn, fill, P);
       return FTP_OK;
     }
     if (!small) {
