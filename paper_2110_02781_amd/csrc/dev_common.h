@@ -102,20 +102,6 @@ __device__ __forceinline__ float view_at(const View& v, size_t idx, int c) {
   return x;
 }
 
-// 8 consecutive channels starting at channel c (c % 8 == 0)
-template <typename T>
-__device__ __forceinline__ void view_load8(const View& v, size_t idx, int c, float out[8]) {
-  load8(reinterpret_cast<const T*>(v.z) + idx, out);
-  if (v.scale) {
-    float s[8], b[8];
-    load8(v.scale + c, s);
-    load8(v.shift + c, b);
-    const float lo = act_lo(v.act), hi = act_hi(v.act);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) out[e] = round_to<T>(clamp_act(fmaf(out[e], s[e], b[e]), lo, hi));
-  }
-}
-
 // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  Renumbering them so that
 // consecutive logical ids share an XCD keeps blocks that touch the same cache lines (column tiles of one row range,
 // neighbouring spatial tiles, adjacent channel groups of one pixel row) behind one L2.

@@ -147,7 +147,7 @@ template <typename T, bool DGRAD, int WC, int KSP>
 __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
   constexpr int RG = 8 / (WC * KSP), TI = 32 * RG, BC = 32 * WC, SHARE = 16 / KSP, NV = ((TI + kC1Taps - 1) * (kC1Chan / 4) + 511) / 512;
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  const int LDR = (p.CP / 4) % 2 ? p.CP : p.CP + 4;       // an odd number of 16-byte units: rows fall into different banks
+  const int LDR = p.CP + 4;                               // CP is a multiple of 8: an odd number of 16-byte units, rows fall into different banks
   const int prow = TI + p.kw - 1, xbuf = (prow + 1) * LDR; // row prow is the zero row; four floats behind each buffer that nobody reads
   const int WLD = p.kphase + 4;                           // an odd number of 16-byte units too
   float* ex = smem;                                       // [8][16][64] where the reduction is split
@@ -857,7 +857,7 @@ static void conv1d_rows(hipStream_t st, Conv1dArgs& a, int* P_out) {
   a.itiles = (a.M + TI - 1) / TI;
   a.tiles_per_range = ranges(TI);
   const int nr = (a.itiles + a.tiles_per_range - 1) / a.tiles_per_range;
-  const int LDR = (a.CP / 4) % 2 ? a.CP : a.CP + 4, KP = a.kw * a.CP;
+  const int LDR = a.CP + 4, KP = a.kw * a.CP;
   const bool split = !(WC == 2 && TI == 128);
   const size_t fixed = (split ? 8 * 16 * 64 : 0) + (size_t)(a.tiles_per_range > 1 ? 2 : 1) * ((TI + a.kw) * LDR + 4) + 8;       // floats
   const int fit = (int)((kC1Lds / sizeof(float) - fixed) / (32 * WC)) - 4, phases = (KP + fit - 1) / fit;
