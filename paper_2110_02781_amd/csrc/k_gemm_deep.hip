@@ -170,8 +170,9 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
     for (int b = 0; b < T; ++b) acc[a][b] = f4v_t{0.f, 0.f, 0.f, 0.f};
   // fp32: a chain of additions per step, 32 reduction elements, not one through the whole reduction: the streaming kernel's wavefronts share a
   // reduction of 128 and more where rows are few, and this may not be further off.  8192 rows, 192 -> 32: 1.38e-7 off the exact product
-  // (2-norm) there, 1.48e-7 in chains of 64, 1.14e-7 in these; 1568 rows, 960 -> 160: 2.8e-7, 1.63e-7, 1.46e-7.  Against chains of 64 a launch is 0 - 3 %
-  // longer (3136 rows 160 -> 960 data gradient 18.4 / 19.0 us, 25088 rows 576 -> 96 forward 41.6 / 41.7).
+  // (2-norm) there, 1.48e-7 in chains of 64, 1.14e-7 in these; 1568 rows, 960 -> 160: 2.8e-7, 1.63e-7, 1.46e-7.  The sums of a step are added in front of
+  // the next one's products: behind its own they were waited for (6272 rows 576 -> 96 data gradient 15.5 / 14.8 us, 25088 rows forward 41.9 / 40.1).  Against chains of 64
+  // within 4 % either way (those 14.7 and 41.9, 3136 rows 1280 -> 320 forward 35.6 / 36.9, 160 -> 960 data gradient 18.6 / 18.8).
   f4v_t tot[F32 ? S : 1][F32 ? T : 1];
   if constexpr (F32)
 #pragma unroll
@@ -197,6 +198,7 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
     fetch(f, (s + D) * KS);
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (F32) {
+      meet();                              // the step before: its products are long done here, behind them each addition would wait
       // a lane holds four consecutive reduction elements of both operands, one for each of four instructions
 #pragma unroll
       for (int ks = 0; ks < KS / 16; ++ks) {
@@ -220,7 +222,6 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
             for (int b = 0; b < T; ++b)
               acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32((&yf[b].x)[e], (&xf[a].x)[e], ks + e == 0 ? f4v_t{0.f, 0.f, 0.f, 0.f} : acc[a][b], 0, 0, 0);
       }
-      meet();
     } else {
 #pragma unroll
       for (int ks = 0; ks < KS / 32; ++ks) {
@@ -257,11 +258,13 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
 #pragma unroll
   for (int d = 0; d + 1 < D; ++d)
     if (s0 + d < nsteps) step(set[d], s0 + d);
-  if constexpr (F32)
+  if constexpr (F32) {
+    meet();
 #pragma unroll
     for (int a = 0; a < S; ++a)
 #pragma unroll
       for (int b = 0; b < T; ++b) acc[a][b] = tot[a][b];
+  }
 
   // ---- results: acc[a][b][e] is out[m0 + wm*16S + 16a + l16][j0 + wn*16T + 16b + 4G + e] ----
   float s1[T][4], s2[T][4];
