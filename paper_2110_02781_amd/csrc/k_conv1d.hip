@@ -730,22 +730,24 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
     for (int u = 0; u < U; ++u) {
       const int mm = m + 4 * u + mg;
       xin[u] = mm < me && k_ok && (unsigned)(t + dt) < (unsigned)p.W;
-      const size_t at = (size_t)(mm < me ? mm : mb < p.M ? mb : 0) * p.Cout;
+      // rows outside are read at the nearest one inside and not used: of a select between two rows the compiler makes two loads, each behind a
+      // branch, and waits for most of them on its own (two layers of 8 -> 8 channels, 2048 rows, no sums taken 25.6 / 24.3 us)
+      const int at = min(mm, me - 1) * p.Cout, xat = min(max(mm + dt, 0), p.M - 1) * p.Cin;
       dr[u] = D[at];
       if (PRO) zr[PRO ? u : 0] = Z[at];
-      xr[u] = X[xin[u] ? (size_t)(mm + dt) * p.Cin : 0];
+      xr[u] = X[xat];
       t += 4;
       t -= t >= p.W ? p.W : 0;
     }
   };
-  request(mb);
   if constexpr (PRO) {
+    request(mb);                         // in front of the loop only where something else happens meanwhile
     finish_backward_n(p.pend, p.Cout, p.g_gamma, p.g_beta, p.own_writes && bid == 0, 64 * NW, fin, vec);
     const int c = co_ok ? co : 0;
     k1 = vec[0][c]; k2 = vec[1][c]; k3 = vec[2][c];
   }
   for (int m = mb; m < me; m += 4 * U) {
-    if (m != mb) request(m);
+    if (!PRO || m != mb) request(m);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       float x = to_f32(xr[u]);
