@@ -875,6 +875,23 @@ static void conv1d_rows(hipStream_t st, Conv1dArgs& a, int* P_out) {
 
 int conv1d_small_ok(const ConvGeom& g) { return conv1d_ok(g) && conv1d_small(g); }
 
+// tiles of the data gradient and of the weight gradient of a short layer
+static int conv1d_bwd_tiles(const ConvGeom& g, int* weights) {
+  *weights = (g.kw * g.Cin + 15) / 16 * ((g.Cout + 15) / 16);
+  return (g.N * g.Win + 15) / 16 * ((g.Cin + 15) / 16);
+}
+
+// The BatchNorm backward on the way into both gradients saves a launch and costs instructions in every block: as long as each block has a CU to
+// itself, and in bfloat16, whose gradient elements are read one by one, up to 1536 rows (three rounds of a weight tile's rows).  A step of a chain of
+// two such layers, us, launches of their own / on the way in: fp32 64 channels, 5 taps, 1152 rows (224 blocks) 53.6 / 50.1, 1536 (272) 56.2 / 56.9, 2048 (336)
+// 60.0 / 63.3, 9 taps, 512 rows (208) 45.9 / 42.6, 1024 (272) 49.8 / 52.0, 1600 (344) 61.5 / 67.8; 32 channels, 5 taps, 2048 rows (148) 51.9 / 48.9; bfloat16 1536 rows
+// 46.8 / 44.3, 2048 48.4 / 48.2, 16 channels, 3 taps, 1536 rows 41.4 / 40.2, 2048 41.9 / 43.6.
+int conv1d_bwd_sums_ok(int dt, const ConvGeom& g) {
+  int weights;
+  const int data = conv1d_bwd_tiles(g, &weights);
+  return conv1d_small_ok(g) && (data + 1) / 2 + weights <= kC1Blocks && (dt == 0 || g.N * g.Win <= 1536);
+}
+
 void conv1d_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, const void* w, const ConvGeom& g, void* z,
                 float* stats, int* P_out) {
   Conv1dArgs a = conv1d_args(g, false);
@@ -967,7 +984,9 @@ void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HVi
     *P_out = d.itiles;
   }
   const int groups = sums ? 2 : 4;     // tiles of the data gradient to a block
-  const int K = g.kw * g.Cin, nd = dIn ? (d.itiles * d.jtiles + groups - 1) / groups : 0, nw = (K + 15) / 16 * ((g.Cout + 15) / 16);
+  const int K = g.kw * g.Cin;
+  int nw;
+  const int tiles = conv1d_bwd_tiles(g, &nw), nd = dIn ? (tiles + groups - 1) / groups : 0;
   a.own_writes = nd == 0;              // who adds to the BatchNorm's gradients: the first data-gradient block, where there is one
   KScope ks(st, dIn ? "conv1d_bwd" : "conv1d_wgrad", (double)d.M * (2.0 * g.Cin + g.Cout) * (dt == 0 ? 4.0 : 2.0) + (double)g.Cout * K * 8, 4.0 * d.M * g.Cout * K,
             d.M, K, g.Cout);

@@ -166,6 +166,7 @@ void reduce_group(hipStream_t st, const ReduceJob* jobs, int n);
 // ---- 1 x kw convolutions, stride 1, same length, at most 64 channels (conv1d_ok): implicit GEMMs, no scratch but ws ----
 int conv1d_ok(const ConvGeom& g);
 int conv1d_small_ok(const ConvGeom& g);     // few rows
+int conv1d_bwd_sums_ok(int dt, const ConvGeom& g);      // conv1d_bwd_small with sums pays
 // of the layers that are conv1d_ok: whether they run here or through patch matrices.  first: no data gradient is wanted, alone: the
 // stage's only convolution, forks: the stage runs weight gradients on a second stream
 int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks);
@@ -177,7 +178,7 @@ void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const C
 size_t conv1d_wgrad_ws(const ConvGeom& g);
 // partial sums, if any, are left in ws and appended to `left`
 void conv1d_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left);
-// few rows (conv1d_small_ok): weight and data gradient (dIn != nullptr) in one launch.  sums != nullptr: the BatchNorm backward of the layer's own
+// few rows (conv1d_small_ok): weight and data gradient (dIn != nullptr) in one launch.  sums != nullptr (conv1d_bwd_sums_ok): the BatchNorm backward of the layer's own
 // output `own` is still to be done, from those sums; dz is not looked at.  left != nullptr (`in` is a view): also the partial sums
 // bn_bwd_reduce would compute for the BatchNorm + activation `in`, [*P_out][2][Cin]
 void conv1d_bwd_small(int dt, hipStream_t st, const void* dz, const void* w, HView in, const ConvGeom& g, float* g_w, void* dIn,

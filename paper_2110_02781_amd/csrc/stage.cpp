@@ -1069,7 +1069,7 @@ static ftp_stage::LeftSums take_sums(ftp_stage* s, const void* dA) {
 static bool conv1d_takes_sums(const ftp_stage* s, const UnitPlan& p) {
   if (p.info->d.kind != FTP_UNIT_CONV || !p.axis[0] || !s->defers) return false;
   ConvGeom g = p.info->subs[0].g; g.N = s->batch;
-  return conv1d_small_ok(g) && bn_bwd_small_ok((size_t)g.N * g.Wout, g.Cout);
+  return conv1d_bwd_sums_ok(s->dt, g) && bn_bwd_small_ok((size_t)g.N * g.Wout, g.Cout);
 }
 static bool conv1d_leaves_sums(const ftp_stage* s, size_t i) { return i > 0 && conv1d_takes_sums(s, s->plan[i - 1]); }
 
