@@ -918,16 +918,25 @@ void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const C
   FTP_DISPATCH(dt, (conv1d_rows<T, true>(st, a, P_out)));
 }
 
+// Pieces to a block: one, two from four pieces on, four from eight; the blocks of a range each bring in all its rows.  From four tiles to a range
+// on that costs more than the partials of twice as many ranges, and a block takes twice the pieces, as long as at most one wavefront group in
+// a range is left without one.  Launch and the sum of its partials, us (6 of the events), before / now: fp32 131072 rows 3 -> 64, 3 taps, 45 / 35, 32 -> 32,
+// 3 taps, 44 / 35 (two pieces), 64 -> 8, 3 taps, 73 / 46 (three), 64 -> 64, 3 taps, 84 / 84 (six: 83 - 89 with four to a block), 32 -> 64, 5 taps,
+// 56 / 51 (four); 32768 rows 3 -> 64, 3 taps, 21 / 19, 64 -> 8 30 / 23, 32 -> 64, 5 taps, 25 / 25; 8192 rows (one or two tiles to a range) 8 -> 64, 5 taps, 16, 17 with
+// two.  bfloat16 131072 rows 3 -> 64, 3 taps, 45 / 34, 64 -> 8, 3 taps, 51 / 43, 32 -> 64, 5 taps, 50 / 46.
 static Conv1dWgArgs conv1d_wgrad_plan(const ConvGeom& g, int* P) {
   Conv1dWgArgs a{};
   a.c = conv1d_args(g, false);
   a.nco = (g.Cout + 16 * kC1RT - 1) / (16 * kC1RT);
   a.nkg = (g.kw * g.Cin + 16 * kC1CT - 1) / (16 * kC1CT);
   const int pieces = a.nco * a.nkg;
-  const int gpb = pieces >= 8 ? 4 : pieces >= 4 ? 2 : 1;
+  int gpb = pieces >= 8 ? 4 : pieces >= 4 ? 2 : 1;
+  auto groups = [&](int n) { return (pieces + n - 1) / n; };
+  auto ranges = [&](int n) { const int r = kC1Blocks / groups(n); return r > 0 ? r : 1; };
+  while (gpb < 4 && gpb < pieces && groups(2 * gpb) * 2 * gpb <= pieces + 1 && ((a.c.M + 63) / 64 + ranges(gpb) - 1) / ranges(gpb) >= 4) gpb *= 2;
   a.rs = 8 / gpb;
-  a.ngrp = (pieces + gpb - 1) / gpb;
-  const int want = kC1Blocks / a.ngrp > 0 ? kC1Blocks / a.ngrp : 1;
+  a.ngrp = groups(gpb);
+  const int want = ranges(gpb);
   a.rows = (a.c.M + 63) / 64 * 2 <= want ? 32 : 64;      // tiles of 64 would leave half of the CUs idle
   a.c.itiles = (a.c.M + a.rows - 1) / a.rows;
   a.c.tiles_per_range = (a.c.itiles + want - 1) / want;

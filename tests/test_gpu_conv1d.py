@@ -95,6 +95,34 @@ def test_conv1d_routes(cin, cout, k, w, batch, tile, first, dtype, here):
         pair.close()
 
 
+# Two, three and four pieces of the weight gradient on both sides of the lines at which a block takes more of them (so that fewer blocks read the
+# same rows), a last tile of 62 rows and less; partials: what the launch leaves, one for every range of rows
+PIECES = [(8, 64, 3, 252, "f32", 128), (8, 64, 3, 256, "f32", 194), (32, 32, 3, 256, "bf16", 194), (64, 8, 3, 168, "f32", 85), (64, 8, 3, 252, "f32", 128),
+          (64, 8, 3, 256, "f32", 194), (64, 8, 3, 256, "bf16", 194), (32, 64, 3, 252, "f32", 128), (32, 64, 3, 256, "f32", 194), (64, 64, 3, 256, "f32", 78)]
+
+
+@pytest.mark.parametrize("cin,cout,k,batch,dtype,partials", PIECES, ids=["-".join(map(str, c)) for c in PIECES])
+def test_conv1d_weight_gradient_pieces(cin, cout, k, batch, dtype, partials):
+    import torch
+    import paper_2110_02781_amd as P
+    print(f"conv1d weight gradient {cin}->{cout} taps {k} batch {batch} {dtype}", flush=True)
+    o, h = units([cin, cin], cout, k, L.ACT_NONE)
+    pair = Pair(o, h, (1, 97, cin), batch, 1, 2, dtype, seed=7, tile=4)
+    try:
+        pair.forward(0, synth.normal(24, "x", (batch // 4, 1, 97, cin)))
+        torch.cuda.synchronize()
+        P.ktrace_begin()
+        dx, dxo = pair.backward(0, synth.normal(24, "dy", (batch // 4,) + tuple(pair.out_shape)))
+        torch.cuda.synchronize()
+        row = {r["name"]: r for r in P.ktrace_end()}["conv1d_wgrad"]
+        moved = row["alg_bytes"] / row["launches"] - batch * 97 * (cin + cout) * (4 if dtype == "f32" else 2)
+        assert moved == partials * cout * k * cin * 4
+        assert_close(dx, dxo, TOL[dtype], "dx")
+        pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
+    finally:
+        pair.close()
+
+
 @pytest.mark.parametrize("cins,cout,k,w,batch,tile,dtype,n_here", [([9, 32, 64], 64, 5, 128, 240, 24, "bf16", 3), ([9, 32, 64], 64, 5, 128, 280, 28, "bf16", 2),
                                                                   ([16, 16, 16], 16, 3, 128, 800, 80, "bf16", 2), ([8, 8, 8], 8, 3, 128, 1600, 100, "bf16", 0),
                                                                   ([8, 8, 16], 64, 3, 128, 1600, 100, "f32", 2)])
