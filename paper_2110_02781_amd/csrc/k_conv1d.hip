@@ -139,9 +139,9 @@ struct RowVecs {
 // its tiles (in two phases a tile where they do not fit), the next tile's rows are on their way while one is multiplied, and
 // the reduction runs without a barrier, at 97 % of the matrix unit's rate.  Kernel times at 5 taps, 32768 rows, before (weights in
 // double-buffered chunks of 64 with a barrier each, two blocks of 4 wavefronts per CU) and now, us: 64 -> 64 forward 22.1 / 19.0, data
-// gradient 26.2 / 22.0; 32 -> 64 16.7 / 13.5 and 19.2 / 14.7.  What is left over the 8.5 is the launch, the first tile's way into LDS (4) and the
-// results' way out (2).  A step of the sensor network, us: 2400 rows 154 / 114, 8192 164 / 130, 32768 224 / 203, 131072 595 / 503;
-// bfloat16 8192 166 / 127, 131072 562 / 522 (the weight gradient below included).
+// gradient 26.2 / 21.5; 32 -> 64 16.7 / 13.5 and 19.2 / 14.2.  What is left over the 8.5 is the launch, the first tile's way into LDS (4) and the
+// results' way out (2).  A step of the sensor network, us: 2400 rows 146 / 104, 8192 158 / 120, 32768 238 / 218, 131072 638 / 544;
+// bfloat16 8192 158 / 114, 131072 566 / 527 (the weight gradient below and the sums the layers leave each other included).
 enum { kC1Lds = 160 * 1024 - 4096 };
 template <typename T, bool DGRAD, int WC, int KSP>
 __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
@@ -391,7 +391,7 @@ __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
 // 80 pieces of g_w [Cout][kw * Cin]: a wavefront keeps 2 x 5 tiles of 16 x 16 in accumulators over all its rows and reads seven LDS
 // words for ten MFMAs.  Wavefronts that share a piece's rows meet in LDS: one partial per block.  Half the pieces to a block
 // where there are several: what it then loads twice is less than the partials of twice as many row ranges.  64 -> 64 channels, 32768
-// rows: 24.3 us and 128 partials, added up with those of 32 -> 64 in 5.9; four wavefronts, nothing on its way, two blocks per CU and 256
+// rows: 25.9 us and 128 partials, added up in 5.0; four wavefronts, nothing on its way, two blocks per CU and 256
 // partials 29 and 11.6.
 // Partials meet in float64, and so do the wavefronts of a piece; a wavefront adds every other step of its rows to a second set of accumulators.
 // Where it was one chain and the wavefronts met in fp32, 32768 rows of 16 -> 16, 3 taps, were 1.13e-7 off 64 bits (2-norm), of 64 -> 64, 5 taps, 2.10e-7;
@@ -800,14 +800,17 @@ static bool conv1d_small(const ConvGeom& g) { return (size_t)g.N * g.Win <= kC1S
 // matrices: one in forward, which the weight gradient reads again if no layer behind has taken the buffer, one of dz, and launches that
 // layers here share with others.  A first layer (no data gradient) needs a single matrix.  A stage that forks has no buffer for
 // that of dz, and its direct data gradient is slower than all else.
-// Steps, us, patch matrices / here.  fp32: 64 -> 64, 5 taps, alone, 32768 rows 100 / 65; first layers alone 9 -> 32, 5 taps, 32768 50 / 55,
-// 131072 77 / 84, 8 -> 32 131072 77 / 73, 3 -> 64, 3 taps, 131072 85 / 80, 262144 107 / 114; chain 8 -> 8, 3 taps, 131072 138 / 137, 262144
-// 200 / 215.  bfloat16: chain 64 -> 64, 9 taps, 2304 rows 104 / 132, 8192 122 / 116, 32768 229 / 206, 7 taps, 131072 600 / 640; 48 -> 48,
-// 7 taps, 2304 91 / 105, 6144 98 / 106, 131072 485 / 549; 32 -> 64, 9 taps, 4096 99 / 102, 6144 107 / 103; chain 8 -> 8, 3 taps, 65536
-// 101 / 98, 131072 112 / 129, 1048576 350 / 670; 32 -> 32, 3 taps, 131072 190 / 174, 524288 522 / 580; first layers 9 -> 32, 5 taps, alone 2304
-// 36 / 38, 65536 48 / 67, in front of two more 16384 180 / 179, 65536 325 / 336; 3 -> 8, 3 taps, alone 8192 41 / 38, 16384 42 / 40,
-// 32768 42 / 46, 524288 76 / 162; a layer behind others alone in its stage 64 -> 64, 9 taps 4096 70 / 70, 8192 84 / 94, 24576 108 / 129, 5 taps 32768
-// 97 / 98, 65536 131 / 157, 3 taps 32768 87 / 87, 65536 107 / 131; 16 -> 16, 5 taps, in front of another 32768 99 / 93, 131072 157 / 157, 524288 390 / 437.
+// The lines lie where both sides were even when the row tiles took their weights through LDS in chunks; the kernels here have since gained 7 - 45 %
+// and the other side nothing, so layers just beyond a line are now often faster here too (marked +: sent to the patch matrices all the same), and none is
+// slower than it was.  Steps, us, patch matrices / here.  fp32: 64 -> 64, 5 taps, alone, 32768 rows 164 / 88; first layers alone 9 -> 32, 5 taps, 32768
+// 41.7 / 36.0 +, 131072 79.9 / 70.3 +, 8 -> 32 131072 78.0 / 63.4 +, 3 -> 64, 3 taps, 131072 97.6 / 84.3, 262144 142 / 139 +; chain 8 -> 8, 3 taps, 131072 207 / 177,
+// 262144 327 / 287 +.  bfloat16: chain 64 -> 64, 9 taps, 2304 rows 143 / 136 +, 8192 237 / 151, 32768 487 / 288, 7 taps, 131072 1121 / 772 +;
+// 48 -> 48, 7 taps, 2304 127 / 109 +, 6144 157 / 123 +, 32768 352 / 228, 131072 893 / 637 +; 32 -> 64, 9 taps, 4096 153 / 115 +, 6144 176 / 117; chain
+// 8 -> 8, 3 taps, 65536 148 / 118, 131072 181 / 169 +, 1048576 614 / 912; 32 -> 32, 3 taps, 131072 341 / 222, 524288 929 / 668 +; first layers 9 -> 32, 5
+// taps, alone 2304 29.5 / 29.4, 65536 42.4 / 45.0, in front of two more 16384 196 / 129, 65536 354 / 233 (there by patch matrices itself, 235); 3 -> 8, 3 taps,
+// alone 8192 37.3 / 30.7, 16384 37.6 / 32.4, 32768 38.6 / 35.5 +, 524288 76 / 144; a layer behind others alone in its stage 64 -> 64, 9 taps 4096
+// 55.3 / 56.7, 8192 72.0 / 61.6 +, 24576 106 / 104, 5 taps 32768 93.8 / 78.9, 65536 128 / 120 +, 3 taps 32768 80.0 / 66.9, 65536 104 / 103; 16 -> 16, 5
+// taps, in front of another 32768 120 / 74, 131072 219 / 144, 524288 480 / 423 +.
 int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks) {
   const size_t M = (size_t)g.N * g.Win;
   const int lo = g.Cin < g.Cout ? g.Cin : g.Cout, hi = g.Cin < g.Cout ? g.Cout : g.Cin;

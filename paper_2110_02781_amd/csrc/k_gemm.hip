@@ -1390,10 +1390,14 @@ __global__ __launch_bounds__(64 * NW) void pw_bwd_tiny_k(TinyArgs pd, GemmArgs p
 }
 
 // the 16 x 16 kernel serves problems whose output is short (few rows) and whose reduction extent
-// allows aligned vector fragments
+// allows aligned vector fragments.  Beyond 2048 rows the kernels behind it are the faster ones throughout; below, against the
+// long-reduction kernel, the layer's time (us, with some 3 of the events around the launch) here / there: fp32 forward 384 -> 64 513 rows 6.9 / 9.6, 2048
+// 8.8 / 9.8, 576 -> 96 513 8.0 / 11.9, 144 -> 24 6.5 / 9.2, data gradient 64 -> 384 513 6.3 / 8.2, 2048 6.9 / 8.5; but layers that widen lose here from some
+// 700 rows on: forward 96 -> 576 700 9.9 / 6.8, 1040 12.1 / 7.5, 64 -> 384 1600 8.6 / 6.8, data gradient 576 -> 96 1040 10.3 / 6.9.  bfloat16 is
+// mostly even: forward 576 -> 96 513 6.9 / 8.0, 1040 9.2 / 8.0, 64 -> 384 2048 8.2 / 6.7.
 static bool tiny_ok(int dt, size_t M, int R, int ncols, bool stats) {
   const int G = dt == 0 ? 4 : 8;
-  if (M > 2048 || R % G != 0) return false;      // measured: taller problems run faster on the staged kernels
+  if (M > 2048 || R % G != 0) return false;
   if ((double)M * R * ncols > 64.0 * 1024 * 1024) return false;   // every block re-reads its operand rows
   if (stats && (M + 15) / 16 > (size_t)kMaxPartials) return false;
   return true;

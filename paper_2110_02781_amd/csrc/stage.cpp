@@ -413,18 +413,19 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   // 0.490 / 0.509; units 1-4 bfloat16 batch 32 1.03 / 0.88, 64 (22 M) 1.42 / 1.45; width 1.4 batch 128 bfloat16 (26 M) 7.4 / 7.5.
   s->defers = n_convs == 0 || z_values / n_convs < ((size_t)20 << 20);
   // A launch for the weight gradients of a few short layers, and one for their partial sums, cost more than it costs to run each next to
-  // its data gradient, in that one's launch.  A step (forward and backward), us, at once / together: 64 <-> 384 channels, fp32, 512 rows one layer 21 / 31,
-  // two 40 / 46, three 58 / 63, four (2048 rows in all) 82 / 82, six 120 / 116; 2048 rows one 33 / 41, two 68 / 69, three 97 / 96; 128 rows twelve
-  // 187 / 189; bfloat16 512 rows one 20 / 29, three 56 / 60, four 81 / 76; 2048 rows one 31 / 37, two 71 / 61; one block of 64 channels, 512 rows
-  // fp32 44 / 50, bfloat16 46 / 52.  Blocks with their depthwise layer: one of 64 -> 384 -> 96, fp32, 900 rows 63 / 72, 1600 rows 83 / 89, of
-  // 88 channels 900 rows 72 / 78, 1600 rows (149 M products) 109 / 108, two of 64 channels 820 rows 112 / 120, 1040 rows 127 / 127;
-  // bfloat16 one of 64 channels 900 rows 60 / 66, 1040 rows 67 / 70, 1600 rows 81 / 80, of 48 channels 1040 rows 65 / 63, two of 64 channels 700
-  // rows 110 / 110, 1040 rows 130 / 123.  From about 300 M products on the together form is the faster one (without the data gradient 512 rows,
-  // 320 -> 1280, 210 M, fp32 41 / 46, 1024 rows 62 / 58; 512 -> 512 1024 rows, 268 M, 40 / 43, 2048 rows 65 / 57).  With a longer layer in the
-  // stage the launch is there anyway.
+  // its data gradient, in that one's launch.  A step (forward and backward), us, at once / together: 64 <-> 384 channels, fp32, 512 rows one layer
+  // 18.2 / 26.1, two 35.8 / 41.2, three 52.2 / 56.6, four (2048 rows in all) 70.1 / 72.0, six 104 / 106; 2048 rows one 33.1 / 37.8, two 65.0 / 66.7, three
+  // 94 / 92; 128 rows twelve 190 / 184; bfloat16 512 rows one 18.0 / 24.3, three 52.1 / 52.4, four 69.1 / 67.5; 2048 rows one 30.8 / 33.8, two 64.3 / 60.5; one
+  // block of 64 channels, 512 rows fp32 42.7 / 48.0, bfloat16 42.3 / 45.1.  Blocks with their depthwise layer: one of 64 -> 384 -> 96, fp32, 900 rows
+  // 55.7 / 62.2, 1600 rows 76.6 / 82.3, of 88 channels 900 rows 65.8 / 67.9, 1600 rows (149 M products) 88.0 / 86.7, two of 64 channels 820 rows 101 / 102,
+  // 1040 rows 118 / 114; bfloat16 one of 64 channels 900 rows 51.2 / 54.3, 1040 rows 59.3 / 58.7, 1600 rows 72.7 / 69.1, of 48 channels 1040 rows
+  // 55.8 / 51.8, two of 64 channels 700 rows 96.4 / 93.4, 1040 rows 118 / 107: in bfloat16 the two are even near 1000 rows of one block, and the line
+  // below lies some hundred rows beyond that.  From about 300 M products on the together form is the faster one; without a data gradient from somewhat less
+  // (512 rows, 320 -> 1280, 210 M, fp32 41.0 / 44.4, 1024 rows 56.5 / 52.1; 512 -> 512 1024 rows, 268 M, 39.0 / 40.6, 2048 rows 61.8 / 53.7).  With a longer layer
+  // in the stage the launch is there anyway.
   // A single bfloat16 layer of 16384 rows and more with at most 32 outputs has a kernel that multiplies in bfloat16 and reads 128 rows at
-  // once: 96 -> 24 channels 32768 rows 36.5 / 44.4; 32 -> 16 131072 rows 44.7 / 55.4; a block of one depthwise and one such layer
-  // 131072 rows 115 / 122.
+  // once: 96 -> 24 channels 32768 rows 34.8 / 40.0; 32 -> 16 131072 rows 43.5 / 51.4; a block of one depthwise and one such layer
+  // 131072 rows 98.3 / 103.4.
   const size_t n_short = s->share.other - n_long;
   const bool narrow_at_once = m->dtype == FTP_BF16 && s->share.other == 1 && n_narrow == 1;
   const size_t rows_at_once = n_short > 4 || short_products > 150000000 ? 1600 : m->dtype == FTP_F32 ? 3200 : n_short == 2 ? 2080 : 1600;
