@@ -730,9 +730,11 @@ __device__ __forceinline__ void conv1d_wgrad_tile(const Conv1dArgs& p, float* __
     for (int u = 0; u < U; ++u) {
       const int mm = m + 4 * u + mg;
       xin[u] = mm < me && k_ok && (unsigned)(t + dt) < (unsigned)p.W;
-      // rows outside are read at the nearest one inside and not used: of a select between two rows the compiler makes two loads, each behind a
-      // branch, and waits for most of them on its own (two layers of 8 -> 8 channels, 2048 rows, no sums taken 25.6 / 24.3 us)
-      const int at = min(mm, me - 1) * p.Cout, xat = min(max(mm + dt, 0), p.M - 1) * p.Cin;
+      // Rows outside are read at the nearest one inside and not used: of a select between two rows the compiler makes two loads, each behind a
+      // branch, and waits for most of them on its own (two layers of 8 -> 8 channels, 2048 rows, no sums taken 25.6 / 24.3 us).  Where the sums are
+      // finished behind the requests nothing waits for these, and a load that is not made is the cheaper one (sensor network, batch 8, 52.6 / 52.2).
+      const int at = (PRO ? mm < me ? mm : mb < p.M ? mb : 0 : min(mm, me - 1)) * p.Cout;
+      const int xat = (PRO ? xin[u] ? mm + dt : 0 : min(max(mm + dt, 0), p.M - 1)) * p.Cin;
       dr[u] = D[at];
       if (PRO) zr[PRO ? u : 0] = Z[at];
       xr[u] = X[xat];
