@@ -91,6 +91,56 @@ __device__ __forceinline__ void finish_backward_n(const BnPending& sums, int C, 
   __syncthreads();
 }
 
+enum { kSlabSumsBytes = 1024 * 8 };      // slab_sums' red
+// Column sums of partial[P][2][C] for the nc channels from c0 (multiples of 4), by every block of a kernel that is cut into slabs of
+// up to 64 channels: 16-byte loads, all of a thread's (up to 16) on their way together, float64 sums in a fixed order.  red: 1024
+// doubles; on return thread t < nc has its channel's two sums (behind a barrier; red may be used again after another).
+__device__ __forceinline__ void slab_sums(const float* __restrict__ partial, int P, int C, int c0, int nc, double* red, double& s0, double& s1) {
+  const int tid = threadIdx.x, n4 = nc >> 2, nv = 2 * n4, L = (int)blockDim.x / nv, lane = tid / nv, v = tid - lane * nv;
+  if (lane < L) {
+    const float* src = partial + (v < n4 ? c0 + 4 * v : C + c0 + 4 * (v - n4));
+    double t[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int q0 = lane; q0 < P; q0 += 16 * L) {
+      float4 x[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) x[u] = ld4(src + (size_t)(q0 + u * L < P ? q0 + u * L : q0) * 2 * C);
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+        if (q0 + u * L < P) { t[0] += (double)x[u].x; t[1] += (double)x[u].y; t[2] += (double)x[u].z; t[3] += (double)x[u].w; }
+    }
+    double* r = red + (size_t)lane * 2 * nc + 4 * v;
+    r[0] = t[0]; r[1] = t[1]; r[2] = t[2]; r[3] = t[3];
+  }
+  __syncthreads();
+  s0 = s1 = 0.0;
+  if (tid < nc) {
+#pragma unroll 4
+    for (int l = 0; l < L; ++l) { s0 += red[(size_t)l * 2 * nc + tid]; s1 += red[(size_t)l * 2 * nc + nc + tid]; }
+  }
+}
+
+// finish pending BatchNorm statistics for nc channels from c0 by every block that reads them (see slab_sums); write: one block per channel also
+// leaves the vectors and running statistics in memory.  sc / sh: [nc], behind a barrier.
+__device__ __forceinline__ void finish_slab(const BnPending& pend, int C, int c0, int nc, float eps, float momentum, bool write, double* red,
+                                            float* sc, float* sh) {
+  const int tid = threadIdx.x, f = c0 + (tid < nc ? tid : 0);
+  const double inv_M = early_inverse((double)pend.M);
+  float p_g = pend.gamma[f], p_b = pend.beta[f], p_rm = 0.f, p_rv = 0.f;
+  if (write && tid < nc) { p_rm = pend.run_mean[f]; p_rv = pend.run_var[f]; }
+  double s0, s1;
+  slab_sums(pend.partial, pend.P, C, c0, nc, red, s0, s1);
+  asm volatile("" : "+v"(p_g), "+v"(p_b), "+v"(p_rm), "+v"(p_rv));       // see finish_pending4
+  if (tid < nc) finish_channel(pend, inv_M, f, s0, s1, p_g, p_b, p_rm, p_rv, eps, momentum, write, sc[tid], sh[tid]);
+  __syncthreads();
+}
+
+// one channel's backward from its sums of dY and dY * z: dz = k1 * dY + k2 * z + k3
+struct BwdChannel { float k1, k2, k3, dgamma, dbeta; };
+__device__ __forceinline__ BwdChannel backward_channel(double s0, double s1, double gamma, double mu, double is, double inv_M) {
+  const double k1 = gamma * is, dgamma = is * (s1 - mu * s0), k2 = -k1 * is * dgamma * inv_M, k3 = -k1 * s0 * inv_M - k2 * mu;
+  return BwdChannel{(float)k1, (float)k2, (float)k3, (float)dgamma, (float)s0};
+}
+
 // finish pending BatchNorm statistics for channels c0..c0+3 (first 256 threads), result in insc[2][4]
 __device__ __forceinline__ void finish_pending4(const BnPending& pend, int C, int c0, float eps, float momentum, double (*pre)[8],
                                                 float (*insc)[4]) {

@@ -49,7 +49,7 @@ RowTile make_rowtile(size_t M, int C, int max_partials) {
 // fetch their coefficients once for more rows.  A whole training interval, blocks 512 / 2048 / 8192 against four rounds a block at least,
 // and the rows dealt round-robin: MobileNetV2 at 32x32 fp32 1.011 / 1.006 / 1.004, 224x224 bfloat16 batch 32 recomputing 1.003 / 1.006 /
 // 1.007, width 1.4 batch 128 0.997 / 1.002 / 1.005.
-enum { kApplyBlocks = 2048 };
+enum { kApplyBlocks = 2048, kFinishBlocks = 1024 };
 static RowTile apply_rowtile(size_t M, int C) {
   RowTile t;
   const int CG = C / 8;
@@ -515,6 +515,155 @@ void bn_apply(int dt, hipStream_t st, HView in, size_t M, int C, const void* res
   if (in.scale) { if (res) FTP_APPLY(true, true); else FTP_APPLY(true, false); }
   else { if (res) FTP_APPLY(false, true); else FTP_APPLY(false, false); }
 #undef FTP_APPLY
+}
+
+// ---- finish and apply in one launch ------------------------------------------------------------------------------
+// (rows, slabs) blocks of up to 64 channels: each adds the partial sums of its own channels before it works off its rows, which were
+// requested first.  Bound by trips to memory: a finalize launch is some 3.3 us of a chain, the sums here 1.5.
+static RowTile finish_rowtile(size_t M, int C) {
+  RowTile t;
+  const int CG = C / 8;
+  t.nslab = (CG + 7) / 8;
+  t.W = (CG + t.nslab - 1) / t.nslab;
+  t.nslab = (CG + t.W - 1) / t.W;
+  t.R = 256 / t.W;
+  const size_t round = 2 * (size_t)t.R, rounds = (M + round - 1) / round, per = (rounds * t.nslab + kFinishBlocks - 1) / kFinishBlocks;
+  t.rows_per_block = per * round;
+  t.P = (int)((M + t.rows_per_block - 1) / t.rows_per_block);
+  return t;
+}
+
+template <typename T, int ACT>
+__global__ __launch_bounds__(256) void bn_bwd_finish_apply_k(const T* __restrict__ dA, const T* __restrict__ z, size_t M, int C,
+                                                             const float* __restrict__ scale, const float* __restrict__ shift, BnPending sums,
+                                                             float* g_gamma, float* g_beta, int W, int R, size_t rpb, T* __restrict__ dz) {
+  __shared__ double red[kSlabSumsBytes / 8];
+  __shared__ __attribute__((aligned(16))) float coef[3][64];
+  __builtin_amdgcn_s_setprio(3);     // data-gradient chain
+  const ChunkSlab at = chunk_slab();
+  const int tid = threadIdx.x, tx = tid % W, ty = tid / W, c0 = at.slab * W * 8, nc = C - c0 < W * 8 ? C - c0 : W * 8;
+  const bool in = tx * 8 < nc;
+  const int c = in ? c0 + tx * 8 : c0;
+  const size_t m0 = (size_t)at.chunk * rpb, m1 = m0 + rpb < M ? m0 + rpb : M;
+  Raw<T> rd[2], rv[2];
+  auto request = [&](const size_t m) __attribute__((always_inline)) {      // past the end: the block's first row, not used
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const size_t mu = m + (size_t)u * R < m1 ? m + (size_t)u * R : m0;
+      raw_load(rd[u], dA + mu * C + c);
+      raw_load(rv[u], z + mu * C + c);
+    }
+  };
+  request(m0 + ty);
+  float sc[8], sh[8], k1[8], k2[8], k3[8];
+  if (ACT != ACT_NONE) { load8(scale + c, sc); load8(shift + c, sh); }
+  const double inv_M = early_inverse((double)M);
+  const int f = c0 + (tid < nc ? tid : 0);
+  const bool write = at.chunk == 0 && tid < nc;
+  float p_g = sums.gamma[f], p_mu = sums.mean[f], p_is = sums.invstd[f], p_gg = 0.f, p_gb = 0.f;
+  if (write) { p_gg = g_gamma[f]; p_gb = g_beta[f]; }
+  double s0, s1;
+  slab_sums(sums.partial, sums.P, C, c0, nc, red, s0, s1);
+  asm volatile("" : "+v"(p_g), "+v"(p_mu), "+v"(p_is), "+v"(p_gg), "+v"(p_gb));      // first use: see bn_finalize_k
+  if (tid < nc) {
+    const BwdChannel b = backward_channel(s0, s1, p_g, p_mu, p_is, inv_M);
+    coef[0][tid] = b.k1; coef[1][tid] = b.k2; coef[2][tid] = b.k3;
+    if (write) { g_gamma[f] = p_gg + b.dgamma; g_beta[f] = p_gb + b.dbeta; }
+  }
+  __syncthreads();
+  if (!in) return;
+  load8(coef[0] + tx * 8, k1); load8(coef[1] + tx * 8, k2); load8(coef[2] + tx * 8, k3);
+  for (size_t m = m0 + ty; m < m1; m += 2 * (size_t)R) {
+    if (m != m0 + ty) request(m);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (m + (size_t)u * R >= m1) break;
+      float d[8], v[8], o[8];
+      raw_unpack(rd[u], d);
+      raw_unpack(rv[u], v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float dy = act_gate<ACT>(d[e], v[e], sc[e], sh[e]);
+        o[e] = fmaf(k1[e], dy, fmaf(k2[e], v[e], k3[e]));
+      }
+      store8(dz + (m + (size_t)u * R) * C + c, o);
+    }
+  }
+}
+
+// Every block reads 512 bytes for each partial: up to 200 of them, and tensors whose blocks run in one turn.  Steps, ms, finalize launches / this rule:
+// units 15-18 at 224x224 bfloat16 batch 64 (12 steps) 4.81 / 4.60, 32x32 fp32 (10) 9.58 / 9.47, 161x193 width 0.5 bfloat16 (8) 8.91 / 8.79, 224x224
+// bfloat16 recomputing (4) 12.46 / 12.26, 224x224 fp32 (3) 10.61 / 10.54.  With up to 512 partials 10.72 there and 12.41 recomputing, width 1.4
+// batch 128 (4) 29.14 / 29.17 / 29.55; with tensors of up to 64 M values too 30.0.  (The depthwise forward doing the same for its input's
+// BatchNorm took as long as the launch it saved.)
+int bn_finish_ok(size_t M, int C, int P) {
+  return P <= 200 && M * (size_t)C <= ((size_t)16 << 20);
+}
+
+void bn_bwd_finish_apply(int dt, hipStream_t st, const void* dA, const void* z, size_t M, int C, const float* scale, const float* shift, int act,
+                         const BnPending& sums, float* g_gamma, float* g_beta, void* dz) {
+  KScope ks(st, "bn_bwd_apply", 3.0 * M * C * (dt == 0 ? 4.0 : 2.0) + (double)sums.P * 2 * C * 4, 6.0 * M * C, (long)M, C, act);
+  ks.route("finish");
+  const RowTile t = finish_rowtile(M, C);
+  const dim3 grid(t.P, t.nslab), block(t.W * t.R);
+  FTP_DISPATCH_ACT(dt, act, hipLaunchKernelGGL((bn_bwd_finish_apply_k<T, ACT>), grid, block, 0, st, (const T*)dA, (const T*)z, M, C, scale, shift,
+                                               sums, g_gamma, g_beta, t.W, t.R, t.rows_per_block, (T*)dz));
+}
+
+// forward: out = act(scale * z + shift) (+ res) from the partial sums of z
+template <typename T, bool RES>
+__global__ __launch_bounds__(256) void bn_finish_apply_k(BnPending pend, const T* __restrict__ z, size_t M, int C, int act, float eps, float momentum,
+                                                         const T* __restrict__ res, int W, int R, size_t rpb, T* __restrict__ out) {
+  __shared__ double red[kSlabSumsBytes / 8];
+  __shared__ __attribute__((aligned(16))) float vec[2][64];
+  const ChunkSlab at = chunk_slab();
+  const int tid = threadIdx.x, tx = tid % W, ty = tid / W, c0 = at.slab * W * 8, nc = C - c0 < W * 8 ? C - c0 : W * 8;
+  const bool in = tx * 8 < nc;
+  const int c = in ? c0 + tx * 8 : c0;
+  const size_t m0 = (size_t)at.chunk * rpb, m1 = m0 + rpb < M ? m0 + rpb : M;
+  Raw<T> rv[2], rr[2];
+  auto request = [&](const size_t m) __attribute__((always_inline)) {      // past the end: the block's first row, not used
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const size_t mu = m + (size_t)u * R < m1 ? m + (size_t)u * R : m0;
+      raw_load(rv[u], z + mu * C + c);
+      if (RES) raw_load(rr[u], res + mu * C + c);
+    }
+  };
+  request(m0 + ty);
+  finish_slab(pend, C, c0, nc, eps, momentum, at.chunk == 0, red, vec[0], vec[1]);
+  if (!in) return;
+  float sc[8], sh[8];
+  load8(vec[0] + tx * 8, sc); load8(vec[1] + tx * 8, sh);
+  const float lo = act_lo(act), hi = act_hi(act);
+  for (size_t m = m0 + ty; m < m1; m += 2 * (size_t)R) {
+    if (m != m0 + ty) request(m);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (m + (size_t)u * R >= m1) break;
+      float v[8], r[8];
+      raw_unpack(rv[u], v);
+      if (RES) raw_unpack(rr[u], r);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        v[e] = round_to<T>(clamp_act(fmaf(v[e], sc[e], sh[e]), lo, hi));
+        if (RES) v[e] += r[e];
+      }
+      store8(out + (m + (size_t)u * R) * C + c, v);
+    }
+  }
+}
+
+void bn_finish_apply(int dt, hipStream_t st, const BnPending& pend, const void* z, size_t M, int C, int act, float eps, float momentum,
+                     const void* res, void* out) {
+  KScope ks(st, "bn_apply", (res ? 3.0 : 2.0) * M * C * (dt == 0 ? 4.0 : 2.0) + (double)pend.P * 2 * C * 4, 3.0 * M * C);
+  ks.route("finish");
+  const RowTile t = finish_rowtile(M, C);
+  const dim3 grid(t.P, t.nslab), block(t.W * t.R);
+  if (res) FTP_DISPATCH(dt, hipLaunchKernelGGL((bn_finish_apply_k<T, true>), grid, block, 0, st, pend, (const T*)z, M, C, act, eps, momentum,
+                                               (const T*)res, t.W, t.R, t.rows_per_block, (T*)out));
+  else FTP_DISPATCH(dt, hipLaunchKernelGGL((bn_finish_apply_k<T, false>), grid, block, 0, st, pend, (const T*)z, M, C, act, eps, momentum,
+                                           (const T*)nullptr, t.W, t.R, t.rows_per_block, (T*)out));
 }
 
 // Finish a BatchNorm whose statistics are still partial sums and materialise its output (+ residual) in ONE

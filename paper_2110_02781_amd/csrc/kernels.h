@@ -101,6 +101,13 @@ int bn_bwd_small_ok(size_t M, int C);
 void bn_bwd_small(int dt, hipStream_t st, const void* dA, const void* z, size_t M, int C, const float* scale,
                   const float* shift, int act, const float* gamma, const float* mean, const float* invstd,
                   float* g_gamma, float* g_beta, void* dz);
+// the last two steps in one launch (bn_finish_ok): from P partial sums, no coef; sums: partial, P, M, gamma, mean, invstd
+int bn_finish_ok(size_t M, int C, int P);
+void bn_bwd_finish_apply(int dt, hipStream_t st, const void* dA, const void* z, size_t M, int C, const float* scale, const float* shift, int act,
+                         const BnPending& sums, float* g_gamma, float* g_beta, void* dz);
+// the same for forward (bn_finish_ok): finishes the pending statistics of z and writes act(scale*z+shift) (+ res)
+void bn_finish_apply(int dt, hipStream_t st, const BnPending& pend, const void* z, size_t M, int C, int act, float eps, float momentum,
+                     const void* res, void* out);
 // out = act(scale*z+shift) (+ res)
 void bn_apply(int dt, hipStream_t st, HView in, size_t M, int C, const void* res, void* out);
 

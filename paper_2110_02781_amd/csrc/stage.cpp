@@ -746,6 +746,10 @@ struct OutPending { BnPending pend{}; HView z{}; const void* res = nullptr; void
 // the second half of the partial sums' buffer, for a layer that reads the first half while it leaves its own
 static float* other_partials(const ftp_stage* s) { return s->bn_part + (size_t)kBnPartials / 2 * 2 * s->max_c; }
 
+static void finish_now(const ftp_stage* s, hipStream_t st, const BnPending& b, int C) {
+  bn_finalize(st, b.partial, b.P, b.M, C, b.gamma, b.beta, b.mean, b.invstd, b.scale, b.shift, b.run_mean, b.run_var, kBnEps, s->bn_mom);
+}
+
 // pend (in/out): on entry the unfinished BatchNorm of `in` (partial == nullptr: none); on exit, when
 // defer is set and the statistics of this layer were left as partial sums, their description
 static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HView in, const WeightSet& W, hipStream_t st,
@@ -859,20 +863,22 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
             ConvGeom gn = u.subs[k + 1].g; gn.N = s->batch;
             defer = dw_fwd_bn_small_ok(gn) && (size_t)s->batch * u.subs[k].g.Hout * u.subs[k].g.Wout <= 16 * 128;
           }
-          // ... and the project layer leaves them to the kernel that writes the block output
-          const size_t Mo = (size_t)s->batch * u.outH * u.outW;
-          if (k + 1 == u.subs.size() && u.subs[k].type == SUB_PW) defer = bn_finalize_apply_small_ok(Mo, u.outC) != 0;
+          // ... and the project layer leaves them to whatever writes the block output
+          if (k + 1 == u.subs.size() && u.subs[k].type == SUB_PW) defer = true;
           sub_forward(s, sl, p, k, h, W, st, &pend, defer, k == 0 ? &block : nullptr);
           h = v.sub_out[i][k];
         }
-        if (pend.partial && next_forms_block(s, i)) {
-          block = OutPending{pend, h, u.residual ? in.z : nullptr, sl.stash + p.out_off};
-        } else if (pend.partial) {
-          bn_finalize_apply_small(s->dt, st, pend, h.z, (size_t)s->batch * u.outH * u.outW, u.outC, h.act, kBnEps, s->bn_mom,
-                                  u.residual ? in.z : nullptr, sl.stash + p.out_off);
-          pend.partial = nullptr;
+        const size_t Mo = (size_t)s->batch * u.outH * u.outW;
+        const void* res = u.residual ? in.z : nullptr;
+        char* out = sl.stash + p.out_off;
+        if (bn_finalize_apply_small_ok(Mo, u.outC)) {
+          if (next_forms_block(s, i)) block = OutPending{pend, h, res, out};
+          else bn_finalize_apply_small(s->dt, st, pend, h.z, Mo, u.outC, h.act, kBnEps, s->bn_mom, res, out);
+        } else if (bn_finish_ok(Mo, u.outC, pend.P)) {
+          bn_finish_apply(s->dt, st, pend, h.z, Mo, u.outC, h.act, kBnEps, s->bn_mom, res, out);
         } else {
-          bn_apply(s->dt, st, h, (size_t)s->batch * u.outH * u.outW, u.outC, u.residual ? in.z : nullptr, sl.stash + p.out_off);
+          finish_now(s, st, pend, u.outC);
+          bn_apply(s->dt, st, h, Mo, u.outC, res, out);
         }
         break;
       }
@@ -1158,6 +1164,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       dz = s->gbuf[b ? 4 : 2];
     }
     const bool small = bn_bwd_small_ok(M, C) != 0;
+    bool finishes = false;
     if (noted && sums.of && takes_sums(s, p, k)) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, s->grads + p.p_off + sb.w_off});
       pw_dgrad_pro(s->dt, st, left, own, dz, conv_w(s, W, p.p_off + sb.w_off), M, g.Cin, g.Cout, dIn);
@@ -1165,8 +1172,10 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     }
     if (!small) {
       if (!sums.of) bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, sums.partial = s->bn_part, &sums.P);
-      bn_bwd_finalize(st, sums.partial, sums.P, M, C, W.w32 + p.p_off + sb.gamma_off, stt, stt + C, s->grads + p.p_off + sb.gamma_off,
-                      s->grads + p.p_off + sb.beta_off, s->coef);
+      finishes = bn_finish_ok(M, C, sums.P) != 0;
+      if (!finishes)
+        bn_bwd_finalize(st, sums.partial, sums.P, M, C, W.w32 + p.p_off + sb.gamma_off, stt, stt + C, s->grads + p.p_off + sb.gamma_off,
+                        s->grads + p.p_off + sb.beta_off, s->coef);
     }
     if (batched) {
       if (!s->bset_open) {                // the unit's first write into this set: the weight gradients that last read it must be done
@@ -1183,6 +1192,10 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     if (small)
       bn_bwd_small(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, W.w32 + p.p_off + sb.gamma_off, stt, stt + C,
                    s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off, dz);
+    else if (finishes)
+      bn_bwd_finish_apply(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act,
+                          BnPending{sums.partial, sums.P, M, W.w32 + p.p_off + sb.gamma_off, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr},
+                          s->grads + p.p_off + sb.gamma_off, s->grads + p.p_off + sb.beta_off, dz);
     else
       bn_bwd_apply(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, s->coef, dz);
   }
