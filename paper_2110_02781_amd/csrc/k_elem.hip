@@ -857,6 +857,15 @@ __device__ __forceinline__ float group_all(float x, F op) {
 template <int G> __device__ __forceinline__ float group_max(float x) { return group_all<G>(x, [](float a, float b) { return fmaxf(a, b); }); }
 template <int G> __device__ __forceinline__ float group_sum(float x) { return group_all<G>(x, [](float a, float b) { return a + b; }); }
 
+// exp(t) for t <= 0 (NaN stays NaN): 2^h times 2^l with h = t * log2(e) rounded and l what that leaves out, 2^l = 1 + l * ln(2) to 2^-40.
+__device__ __forceinline__ float exp_below(float t) {
+  t = t < -150.f ? -150.f : t;                             // 2^h is zero there; -inf has no rest
+  const float h = t * 1.44269502f;
+  const float l = fmaf(t, 1.92596303e-8f, fmaf(t, 1.44269502f, -h));
+  const float e = __builtin_amdgcn_exp2f(h);
+  return fmaf(e, l * 0.693147181f, e);
+}
+
 template <typename T, int G, int E, int VEC, bool AL>
 struct CeRow {
   float v[E];
@@ -873,53 +882,120 @@ struct CeRow {
         for (int e = 0; e < VEC; ++e) v[q * VEC + e] = to_f32(src[e]);
     }
   }
-  // the row's loss, the same in all its lanes
-  __device__ __forceinline__ float finish(T* __restrict__ drow, int classes, int l, float invB) {
+  float invs;
+  // the row's loss, the same in all its lanes; what is left in v is for store().  WHOLE: the group is a wavefront, so the row, its label and what the
+  // columns allow are scalar
+  template <bool WHOLE>
+  __device__ __forceinline__ float sums(int classes, int l) {
     float mx = -INFINITY, z = 0.f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int c = (l + G * (e / VEC)) * VEC + e % VEC;
-      mx = fmaxf(mx, c < classes ? v[e] : -INFINITY);
+    for (int q = 0; q < E / VEC; ++q) {
+      const int c0 = (l + G * q) * VEC;
+      if (!WHOLE || G * VEC * (q + 1) > classes)            // else every lane's vector is in the row
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) v[q * VEC + e] = c0 < classes ? v[q * VEC + e] : -INFINITY;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) mx = fmaxf(mx, v[q * VEC + e]);
     }
     mx = group_max<G>(mx);
+    if (WHOLE) lab = __builtin_amdgcn_readfirstlane(lab);
+    const int lb = lab;
     float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < E; ++e) {
-      const int c = (l + G * (e / VEC)) * VEC + e % VEC;
-      z += c == lab ? v[e] - mx : 0.f;
-      v[e] = c < classes ? expf(v[e] - mx) : 0.f;
-      s += v[e];
+    for (int q = 0; q < E / VEC; ++q) {
+      const int c0 = (l + G * q) * VEC;
+      const bool in = WHOLE ? lb >= G * VEC * q && lb < G * VEC * (q + 1) : true;      // the label may lie in one of these vectors
+      if (in)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) z += c0 + e == lb ? v[q * VEC + e] - mx : 0.f;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) {
+        // past the row: exp(-inf) = 0; a row of nothing but -inf is NaN as it was
+        v[q * VEC + e] = exp_below(v[q * VEC + e] - mx);
+        s += v[q * VEC + e];
+      }
     }
     s = group_sum<G>(s);
     z = group_sum<G>(z);
-    const float invs = 1.f / s;
+    invs = 1.f / s;
+    return lb >= 0 && lb < classes ? -(z - logf(s)) : NAN;    // an invalid label yields a NaN loss, never a stray read
+  }
+  template <bool WHOLE>
+  __device__ __forceinline__ void store(T* __restrict__ drow, int classes, int l, float invB) {
+    const int lb = WHOLE ? __builtin_amdgcn_readfirstlane(lab) : lab;
 #pragma unroll
     for (int q = 0; q < E / VEC; ++q) {
       const int c = (l + G * q) * VEC;
-      if (c >= classes) continue;
+      const bool in = WHOLE ? lb >= G * VEC * q && lb < G * VEC * (q + 1) : true;
       float d[VEC];
 #pragma unroll
-      for (int e = 0; e < VEC; ++e) d[e] = (v[q * VEC + e] * invs - (c + e == lab ? 1.f : 0.f)) * invB;
+      for (int e = 0; e < VEC; ++e) d[e] = v[q * VEC + e] * invs;
+      if (in)
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) d[e] -= c + e == lb ? 1.f : 0.f;
+#pragma unroll
+      for (int e = 0; e < VEC; ++e) d[e] *= invB;
+      if (c >= classes) continue;
       if constexpr (VEC == 8 && AL) store8(drow + c, d);
       else
 #pragma unroll
         for (int e = 0; e < VEC; ++e) drow[c + e] = from_f32<T>(d[e]);
     }
-    return lab >= 0 && lab < classes ? -(z - logf(s)) : NAN;    // an invalid label yields a NaN loss, never a stray read
   }
 };
 
 // Wavefront = row.  Bound by memory: 4096 x 1000 bfloat16 moves 16 MB; a block per row, which goes over its row three
 // times with six block-wide reductions between, took 14 us.
+// The mean: a block's rows are one partial, and the last block to arrive adds all of them, in order; a launch for it cost as much as the rows where
+// they are few (64 x 1000 bfloat16 7.5 us a call, 5.0 so; 4096 x 1000 8.4 / 7.6, 16384 x 1000 18.5 / 16.6, 9000 x 100 fp32 7.2 / 7.25).  partial and arrived go past the L2s (each
+// XCD has its own) one by one: a fence would write a whole L2 back.  Additions to one counter take some 12 ns each, so the blocks arrive in
+// kCeGroups groups and the groups at the first counter (563 blocks at one: 3.5 us more).  Whoever arrives last leaves zeros.
+// 8 rows a block: with 16 the few rows take 0.6 us more, with 4 the 4096 x 1000 0.5.  arrived == nullptr: the partials only.
 template <typename T, int E, int VEC, bool AL>
-__global__ __launch_bounds__(256) void softmax_ce_wave_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B,
-                                                         int classes, float* __restrict__ row_loss, T* __restrict__ dlogits) {
-  const int l = threadIdx.x & 63, b = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (b >= B) return;
+__global__ __launch_bounds__(kCeRows * 64) void softmax_ce_wave_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B, int classes,
+                                                                  float* partial, unsigned* arrived, T* __restrict__ dlogits, float* __restrict__ loss) {
+  __shared__ float rows[kCeRows];
+  constexpr bool WHOLE = VEC > 1;
+  const int l = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), b = blockIdx.x * kCeRows + wave;
   CeRow<T, 64, E, VEC, AL> r;
-  r.fetch(logits + (size_t)b * classes, labels + b, classes, l);
-  const float loss = r.finish(dlogits + (size_t)b * classes, classes, l, 1.f / (float)B);
-  if (l == 0) row_loss[b] = loss;
+  if (b < B) {
+    r.fetch(logits + (size_t)b * classes, labels + b, classes, l);
+    const float t = r.template sums<WHOLE>(classes, l);
+    if (l == 0) rows[wave] = t;
+  } else if (l == 0) {
+    rows[wave] = 0.f;
+  }
+  __syncthreads();
+  unsigned before = 0, *const mine = arrived + kCeLine * (1 + blockIdx.x % kCeGroups);
+  const unsigned groups = gridDim.x < kCeGroups ? gridDim.x : kCeGroups, members = (gridDim.x - blockIdx.x % kCeGroups + kCeGroups - 1) / kCeGroups;
+  if (wave == 0) {
+    const float t = wave_sum(l < kCeRows ? rows[l] : 0.f);
+    if (l == 0) {
+      __hip_atomic_store(partial + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // it is there before this block counts as arrived
+      if (arrived) before = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+  if (b < B) r.template store<WHOLE>(dlogits + (size_t)b * classes, classes, l, 1.f / (float)B);
+  if (wave != 0 || !arrived || __builtin_amdgcn_readfirstlane(before) + 1 != members) return;
+  if (l == 0) {
+    __hip_atomic_store(mine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (__builtin_amdgcn_readfirstlane(before) + 1 != groups) return;
+  float s = 0.f;
+  for (int i0 = l; i0 < (int)gridDim.x; i0 += 8 * 64) {        // eight loads per trip to memory
+    float x[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) x[u] = __hip_atomic_load(partial + (i0 + 64 * u < (int)gridDim.x ? i0 + 64 * u : i0), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += i0 + 64 * u < (int)gridDim.x ? x[u] : 0.f;
+  }
+  s = wave_sum(s);
+  if (l == 0) {
+    *loss = s / (float)B;
+    __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
 // Few elements: one block does all rows and their mean.  Latency only, and a second dependent launch is half of it.
@@ -938,7 +1014,8 @@ __global__ __launch_bounds__(1024) void softmax_ce_one_k(const T* __restrict__ l
   for (; b < B; b += ROWS) {
     const int bn = b + ROWS < B ? b + ROWS : b;
     next.fetch(logits + (size_t)bn * classes, labels + bn, classes, l);     // in flight while this row is worked on
-    sum += r.finish(dlogits + (size_t)b * classes, classes, l, invB);
+    sum += r.template sums<false>(classes, l);
+    r.template store<false>(dlogits + (size_t)b * classes, classes, l, invB);
     r = next;
   }
   sum = wave_sum(l == 0 ? sum : 0.f);
@@ -952,16 +1029,17 @@ __global__ __launch_bounds__(1024) void softmax_ce_one_k(const T* __restrict__ l
   }
 }
 
-__global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ row_loss, int B, float* __restrict__ loss) {
+// the sum of n partial sums over B rows
+__global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ row_loss, int n, int B, float* __restrict__ loss) {
   __shared__ float part[16];
   const int nt = blockDim.x;
   float s = 0.f;
-  for (int i0 = threadIdx.x; i0 < B; i0 += 8 * nt) {        // eight loads per trip to memory
+  for (int i0 = threadIdx.x; i0 < n; i0 += 8 * nt) {        // eight loads per trip to memory
     float x[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = row_loss[i0 + nt * u < B ? i0 + nt * u : 0];
+    for (int u = 0; u < 8; ++u) x[u] = row_loss[i0 + nt * u < n ? i0 + nt * u : 0];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += i0 + nt * u < B ? x[u] : 0.f;
+    for (int u = 0; u < 8; ++u) s += i0 + nt * u < n ? x[u] : 0.f;
   }
   s = wave_sum(s);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
@@ -973,16 +1051,18 @@ __global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ ro
   }
 }
 
-// One block for everything where its lane groups need at most two rounds of short rows (or one of longer ones), two
-// launches otherwise.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean
-// kernel): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4,
-// 4096 x 10 11.4 / 24 / 6.4, 4096 x 1000 bfloat16 16.8 / - / 7.8 (on logits that no cache holds 21.8 / - / 9.1), 16384 x 1000 bfloat16
-// 62 / - / 19.  With a few hundred rows up to some thousand short ones two launches are all that is timed, as with a block per row.
+// One block for everything where its lane groups need at most two rounds of short rows (or one of longer ones), else a wavefront per row and the
+// mean by the last block.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean kernel; the last without that
+// launch, above): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4, 4096 x 10 11.4 / 24 / 6.4, 4096 x
+// 1000 bfloat16 16.8 / - / 7.8 (on logits that no cache holds 21.8 / - / 9.1), 16384 x 1000 bfloat16 62 / - / 19.
+static int ce_lanes(int classes) { return classes <= 16 ? 8 : classes <= 64 ? 16 : classes <= 128 ? 32 : 64; }       // of a row in the one-block kernel
+static bool ce_one_block(int B, int classes) { return classes <= 1024 && B <= (classes <= 256 ? 2 : 1) * (1024 / ce_lanes(classes)); }
+int softmax_ce_arrives(int B, int classes) { return !ce_one_block(B, classes) && classes <= 1024; }
+
 template <typename T>
 static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* labels, int B, int classes, float* row_loss, T* dlogits,
-                              float* loss) {
-  const int G = classes <= 16 ? 8 : classes <= 64 ? 16 : classes <= 128 ? 32 : 64;      // lanes of a row in the one-block kernel
-  if (classes <= 1024 && B <= (classes <= 256 ? 2 : 1) * (1024 / G)) {
+                              float* loss, unsigned* arrived) {
+  if (ce_one_block(B, classes)) {
 #define FTP_CE_ONE(G, E) hipLaunchKernelGGL((softmax_ce_one_k<T, G, E>), dim3(1), dim3(1024), 0, st, logits, labels, B, classes, dlogits, loss)
     if (classes <= 16) FTP_CE_ONE(8, 2);
     else if (classes <= 32) FTP_CE_ONE(16, 2);
@@ -994,13 +1074,16 @@ static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* la
 #undef FTP_CE_ONE
     return;
   }
-  const dim3 rows((unsigned)((B + 3) / 4));
+  const dim3 rows((unsigned)((B + kCeRows - 1) / kCeRows));
   const bool al = ((uintptr_t)logits | (uintptr_t)dlogits) % 16 == 0;      // the buffers are the caller's
-#define FTP_CE_WAVE(E, VEC, AL)   hipLaunchKernelGGL((softmax_ce_wave_k<T, E, VEC, AL>), rows, dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits)
+#define FTP_CE_WAVE(E, VEC, AL)   hipLaunchKernelGGL((softmax_ce_wave_k<T, E, VEC, AL>), rows, dim3(kCeRows * 64), 0, st, logits, labels, B, classes, row_loss, arrived, dlogits, loss)
 #define FTP_CE_WAVE8(E) do { if (al) FTP_CE_WAVE(E, 8, true); else FTP_CE_WAVE(E, 8, false); } while (0)
-  if (classes > 1024)
+  if (classes > 1024) {
     hipLaunchKernelGGL(softmax_ce_k<T>, dim3(B), dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits);
-  else if (classes % 8 == 0 && classes > 256) { if (classes <= 512) FTP_CE_WAVE8(8); else FTP_CE_WAVE8(16); }
+    hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(B <= 2048 ? 256 : 1024), 0, st, row_loss, B, B, loss);
+    return;
+  }
+  if (classes % 8 == 0 && classes > 256) { if (classes <= 512) FTP_CE_WAVE8(8); else FTP_CE_WAVE8(16); }
   else if (classes <= 64) FTP_CE_WAVE(1, 1, false);
   else if (classes <= 128) FTP_CE_WAVE(2, 1, false);
   else if (classes <= 256) FTP_CE_WAVE(4, 1, false);
@@ -1008,13 +1091,13 @@ static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* la
   else FTP_CE_WAVE(16, 1, false);
 #undef FTP_CE_WAVE8
 #undef FTP_CE_WAVE
-  hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(B <= 2048 ? 256 : 1024), 0, st, row_loss, B, loss);
+  if (!arrived) hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(64), 0, st, row_loss, (int)rows.x, B, loss);      // in the same order
 }
 
 void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* labels, int B, int classes,
-                float* row_loss, void* dlogits, float* loss) {
+                float* row_loss, void* dlogits, float* loss, unsigned* arrived) {
   KScope ks(st, "softmax_ce", 2.0 * B * classes * (dt == 0 ? 4.0 : 2.0), 8.0 * B * classes);
-  FTP_DISPATCH(dt, softmax_ce_launch<T>(st, (const T*)logits, labels, B, classes, row_loss, (T*)dlogits, loss));
+  FTP_DISPATCH(dt, softmax_ce_launch<T>(st, (const T*)logits, labels, B, classes, row_loss, (T*)dlogits, loss, arrived));
 }
 
 // block = 16 output columns x 16 row lanes; the row lanes' sums meet in LDS in a fixed order

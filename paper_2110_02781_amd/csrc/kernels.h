@@ -120,9 +120,12 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
 // pend.partial != nullptr: the BatchNorm of the input is still partial sums; finished here
 void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out);
 void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn);
-// per-row loss into row_loss[B], dlogits[B][classes] = (softmax - onehot)/B, then mean into *loss
+// dlogits[B][classes] = (softmax - onehot)/B, mean loss into *loss; row_loss: B floats of scratch.  arrived: kCeCounters zeros, zeros again afterwards,
+// for one call at a time; without them what softmax_ce_arrives takes a launch more
+int softmax_ce_arrives(int B, int classes);
+enum { kCeRows = 8, kCeGroups = 32, kCeLine = 16, kCeCounters = (kCeGroups + 1) * kCeLine };     // rows of a block, groups of blocks
 void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* labels, int B, int classes,
-                float* row_loss, void* dlogits, float* loss);
+                float* row_loss, void* dlogits, float* loss, unsigned* arrived);
 // g_bias[j] += sum_b d[b][j]
 void bias_grad(int dt, hipStream_t st, const void* d, int B, int Nout, float* g_bias);
 // the whole backward of a fully connected layer d[B][N] -> in[B][K] in one launch: g_w += d^T in, g_b += column sums of d,

@@ -292,6 +292,7 @@ struct ftp_stage {
   std::vector<ReduceJob> q_red;
   unsigned n_sub_bwd = 0;
   float *bn_part = nullptr, *coef = nullptr, *ws = nullptr, *row_loss = nullptr;
+  unsigned* arrived = nullptr;
   // A second partial-sum workspace for the weight gradient of the stage's very first layer when the stage forks
   // its weight gradients: that layer has no data gradient, so nothing follows it on the caller's stream and it
   // runs there, next to whatever the side stream still has queued, instead of behind it.
@@ -345,7 +346,7 @@ static void stage_free(ftp_stage* s) {
     if (s->ev_bjoin[i]) (void)hipEventDestroy(s->ev_bjoin[i]);
   }
   for (int i = 0; i < 6; ++i) dfree(s->dzring[i]);
-  dfree(s->bn_part); dfree(s->coef); dfree(s->ws); dfree(s->ws_tail); dfree(s->ws_fused); dfree(s->row_loss); dfree(s->im2col);
+  dfree(s->bn_part); dfree(s->coef); dfree(s->ws); dfree(s->ws_tail); dfree(s->ws_fused); dfree(s->row_loss); dfree(s->arrived); dfree(s->im2col);
   dfree(s->dz_store); dfree(s->parts);
   if (s->timer) {
     if (s->timer->created)
@@ -552,7 +553,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       if ((rc = dev_alloc(&s->dzring[i], s->dzring_bytes))) { stage_free(s); return rc; }
   }
   if ((rc = dev_alloc(&s->bn_part, (size_t)kBnPartials * 2 * max_c * 4)) || (rc = dev_alloc(&s->coef, (size_t)3 * max_c * 4)) ||
-      (rc = dev_alloc(&s->ws, ws_floats * 4)) || (rc = dev_alloc(&s->row_loss, (size_t)batch * 4))) { stage_free(s); return rc; }
+      (rc = dev_alloc(&s->ws, ws_floats * 4)) || (rc = dev_alloc(&s->row_loss, (size_t)batch * 4)) || (s->has_loss && (rc = dev_alloc(&s->arrived, kCeCounters * 4)))) { stage_free(s); return rc; }
   if (s->im2col_elems && (rc = dev_alloc(&s->im2col, s->im2col_elems * s->es))) { stage_free(s); return rc; }
   if (s->defers && ((rc = dev_alloc(&s->dz_store, s->dz_cap)) || (rc = dev_alloc(&s->parts, s->part_cap * 4)))) { stage_free(s); return rc; }
   if (!s->defers && s->ws_fused_floats && (rc = dev_alloc(&s->ws_fused, s->ws_fused_floats * 4))) { stage_free(s); return rc; }
@@ -566,6 +567,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   if (e == hipSuccess) e = hipMemset(s->mom, 0, np * 4);
   if (e == hipSuccess) e = hipMemset(s->run_mean, 0, nb * 4);
   if (e == hipSuccess) e = hipMemcpy(s->run_var, ones.data(), nb * 4, hipMemcpyHostToDevice);
+  if (e == hipSuccess && s->arrived) e = hipMemset(s->arrived, 0, kCeCounters * 4);
   if (e == hipSuccess && s->w_lp) e = hipMemset(s->w_lp, 0, np * 2);
   if (e == hipSuccess) e = hipDeviceSynchronize();
   if (e != hipSuccess) { ftp_set_error("stage_create: initialisation failed: %s", hipGetErrorString(e)); stage_free(s); return FTP_ERR_HIP; }
@@ -957,7 +959,7 @@ extern "C" int ftp_stage_loss(ftp_stage* s, int slot, const int32_t* labels_dev,
   build_views(s, sl, &v);
   size_t li = s->plan.size() - 1;
   if (s->prof) HIP_TRY(hipEventRecord(s->prof->f0[li], st));
-  softmax_ce(s->dt, st, v.unit_in[li].z, labels_dev, s->batch, s->classes, s->row_loss, sl.dlogits, loss_dev);
+  softmax_ce(s->dt, st, v.unit_in[li].z, labels_dev, s->batch, s->classes, s->row_loss, sl.dlogits, loss_dev, s->arrived);
   if (s->prof) HIP_TRY(hipEventRecord(s->prof->f1[li], st));
   HIP_TRY(hipGetLastError());
   if (const char* why = launch_plan_failure_take()) { ftp_set_error("%s", why); return FTP_ERR_UNSUPPORTED; }
@@ -1544,14 +1546,19 @@ extern "C" int ftp_stage_update(ftp_stage* s, const ftp_sgd* opt, void* stream) 
 }
 
 // ------------------------------------------------------------ loss without a stage, without allocation
-// Per-row losses of ftp_softmax_ce_static: partial results between its two kernels.  One copy per GPU, held until the
+// Sums of row losses of ftp_softmax_ce_static: partial results inside the call.  One copy per GPU, held until the
 // process ends; in host code the name is only a handle for hipGetSymbolAddress, the kernels get the address.
-enum { kStaticLossMaxBatch = FTP_STATIC_LOSS_MAX_BATCH, kStaticMaxDevices = 64 };
-static __device__ __align__(256) float scratch[kStaticLossMaxBatch];
+enum { kStaticLossMaxBatch = FTP_STATIC_LOSS_MAX_BATCH, kStaticMaxDevices = 64, kStaticStreams = 64 };
+static __device__ __align__(256) float scratch[kStaticLossMaxBatch + kStaticStreams * kCeCounters];
 static float* g_scratch_ptr[kStaticMaxDevices];     // per device: the address of that GPU's copy
 static std::mutex g_scratch_mu;
+// Behind the losses: counters for the one-launch form, those of each stream its own (calls of one stream follow one another).  The first
+// kStaticStreams streams of a GPU have some; a stream that comes later, the handle that stands for a stream of each thread, and a call that is being
+// captured (its graph may run on any stream) take two launches.
+static hipStream_t g_scratch_stream[kStaticMaxDevices][kStaticStreams];
+static int g_scratch_streams[kStaticMaxDevices];
 
-static int static_scratch(float** out) {
+static int static_scratch(hipStream_t st, bool counters, float** out, unsigned** arrived) {
   int dev = -1;
   HIP_TRY(hipGetDevice(&dev));
   if (dev < 0 || dev >= kStaticMaxDevices) { ftp_set_error("softmax_ce_static: device ordinal %d not supported", dev); return FTP_ERR_UNSUPPORTED; }
@@ -1563,6 +1570,16 @@ static int static_scratch(float** out) {
     g_scratch_ptr[dev] = p;
   }
   *out = g_scratch_ptr[dev];
+  *arrived = nullptr;
+  if (!counters) return FTP_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return FTP_OK; }
+  if (st == hipStreamPerThread || cap != hipStreamCaptureStatusNone) return FTP_OK;
+  int i = 0;
+  for (; i < g_scratch_streams[dev] && g_scratch_stream[dev][i] != st; ++i) {}
+  if (i == kStaticStreams) return FTP_OK;
+  if (i == g_scratch_streams[dev]) g_scratch_stream[dev][g_scratch_streams[dev]++] = st;
+  *arrived = (unsigned*)*out + kStaticLossMaxBatch + i * kCeCounters;
   return FTP_OK;
 }
 
@@ -1576,10 +1593,11 @@ extern "C" int ftp_softmax_ce_static(const void* logits_dev, const int32_t* labe
     return FTP_ERR_ARG;
   }
   float* rows = nullptr;
-  int rc = static_scratch(&rows);
+  unsigned* arrived = nullptr;
+  int rc = static_scratch((hipStream_t)stream, softmax_ce_arrives(batch, classes) != 0, &rows, &arrived);
   if (rc) return rc;
   // every row < batch is written before it is read and nothing beyond is read: nothing has to start at zero
-  softmax_ce((int)dtype, (hipStream_t)stream, logits_dev, labels_dev, batch, classes, rows, dlogits_dev, loss_dev);
+  softmax_ce((int)dtype, (hipStream_t)stream, logits_dev, labels_dev, batch, classes, rows, dlogits_dev, loss_dev, arrived);
   HIP_TRY(hipGetLastError());
   if (const char* why = launch_plan_failure_take()) { ftp_set_error("%s", why); return FTP_ERR_UNSUPPORTED; }
   return FTP_OK;

@@ -1,0 +1,52 @@
+"""The mean loss added by the last block to arrive (csrc/k_elem.hip, softmax_ce_wave_k): calls behind one another on the same counters, the forms
+without them (a captured call, more streams than there are counters for), all bit for bit the same, against the oracle."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+# one block and a few rows, 31, 32 and 33 blocks (the groups), a last block of one row, 513 and more blocks
+SIZES = [(17, 1000), (248, 300), (256, 1000), (257, 300), (600, 33), (1025, 65), (4097, 264), (4096, 9), (16390, 9)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_last_block_adds_the_mean(dtype):
+    import torch
+    import paper_2110_02781_amd as P
+    from oracle import layers as L
+    tdt, code = (torch.float32, P.F32) if dtype == "f32" else (torch.bfloat16, P.BF16)
+    first = {}
+    streams = [torch.cuda.Stream() for _ in range(70)]                # torch deals handles out of a pool of its own: some repeat
+
+    def call(i, b, n, sp, logits, labels, d, loss):
+        P.softmax_ce_static(logits, labels, b, n, code, d, loss, sp)
+
+    for i, (b, n) in enumerate(SIZES):
+        print(f"loss arrival {dtype} {b} x {n}", flush=True)
+        logits = torch.from_numpy(synth.normal(95 + i, "logits", (b, n), std=3.0).astype(np.float32)).cuda().to(tdt)
+        lab = synth.labels(95 + i, "labels", b, n).astype(np.int32)
+        labels, d, loss = torch.from_numpy(lab).cuda(), torch.empty_like(logits), torch.zeros(1, device="cuda")
+        torch.cuda.synchronize()
+        for sp in [streams[0], streams[0], streams[1]] + (streams[2:] if i == 0 else []):
+            loss.fill_(-1.0)
+            torch.cuda.synchronize()
+            call(i, b, n, sp.cuda_stream, logits, labels, d, loss)
+            torch.cuda.synchronize()
+            first.setdefault(i, (loss.clone(), d.clone()))
+            assert torch.equal(loss, first[i][0]) and torch.equal(d, first[i][1])
+        lo, do = L.softmax_ce(logits.float().cpu().numpy().astype(np.float64), lab)
+        # sums of 8 rows, then of partials in chains of up to 33, then a tree over 64 lanes: some 45 additions in 32 bits at most
+        assert abs(float(loss) - lo) <= 45 * 2.0 ** -24 * max(1.0, abs(lo))
+        assert np.abs(d.float().cpu().numpy() - do).max() <= (2e-6 if dtype == "f32" else 2.0 ** -8) * np.abs(do).max() + 2e-7 / b
+        g = torch.cuda.CUDAGraph()
+        side = torch.cuda.Stream()
+        with torch.cuda.graph(g, stream=side):
+            call(i, b, n, side.cuda_stream, logits, labels, d, loss)
+        for _ in range(3):
+            loss.fill_(-1.0)
+            d.fill_(0.0)
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(loss, first[i][0]) and torch.equal(d, first[i][1])
