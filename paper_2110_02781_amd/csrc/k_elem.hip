@@ -717,14 +717,20 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
 // block = (image n, group of 8 channels); 64 lanes walk the positions, U of them on their way together, fixed-order sum through LDS.
 // One trip to memory where the image has at most 64 positions, and then U = 1: four requests a lane, three of them for nothing, and the code
 // that finishes statistics in every block took 264 x 1792 channels of 9 positions, fp32, from 18.9 to 27.8 us, 73 x 1280 of 4 from 5.8 to 8.3.
-template <typename T, bool PEND, int U>
-__global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float eps, float momentum, int N, int HW, int CG, T* __restrict__ out) {
-  __shared__ float red[64][8];
+// OPEN: also, per image and channel, the number of positions that the activation passes and the sum of the raw values there, open[N][2][C].  Behind an
+// average the gradient is the same at all positions, so times these it is that BatchNorm's backward sums, and nobody has to read the tensor for them.
+template <typename T, bool PEND, int U, bool OPEN>
+__global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float eps, float momentum, int N, int HW, int CG, T* __restrict__ out,
+                                                float* __restrict__ open) {
+  constexpr int V = OPEN ? 24 : 8;
+  __shared__ float red[64][V];
   __shared__ double fin[64];
   __shared__ float vec[2][8];
   const int i = blockIdx.x, n = i / CG, cg = i % CG, lane = threadIdx.x;
   const T* src = reinterpret_cast<const T*>(in.z) + (size_t)n * HW * CG * 8 + cg * 8;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  float acc[V];
+#pragma unroll
+  for (int e = 0; e < V; ++e) acc[e] = 0.f;
   float sc[8], sh[8];
   const bool view = in.scale != nullptr;
   Raw<T> r[U];
@@ -750,35 +756,77 @@ __global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float e
       float v[8];
       raw_unpack(r[u], v);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += view ? round_to<T>(clamp_act(fmaf(v[e], sc[e], sh[e]), lo, hi)) : v[e];
+      for (int e = 0; e < 8; ++e) {
+        const float y = fmaf(v[e], sc[e], sh[e]);
+        acc[e] += view ? round_to<T>(clamp_act(y, lo, hi)) : v[e];
+        if constexpr (OPEN) {
+          const bool on = y > lo && y < hi;
+          acc[8 + e] += on ? 1.f : 0.f;
+          acc[16 + e] += on ? v[e] : 0.f;
+        }
+      }
     }
   }
 #pragma unroll
-  for (int e = 0; e < 8; ++e) red[lane][e] = acc[e];
+  for (int e = 0; e < V; ++e) red[lane][e] = acc[e];
   __syncthreads();
-  if (lane < 8) {
+  if (lane < V) {
     float s = 0.f;
     for (int l = 0; l < 64; ++l) s += red[l][lane];
     float o = s * (1.f / (float)HW);
-    out[(size_t)i * 8 + lane] = from_f32<T>(o);
+    if (lane < 8) out[(size_t)i * 8 + lane] = from_f32<T>(o);
+    else open[((size_t)n * 2 + (lane >> 4)) * CG * 8 + cg * 8 + (lane & 7)] = s;
   }
 }
 
-void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out) {
+void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out, float* open) {
   View v{in.z, in.scale, in.shift, in.act};
   int n = N * (C / 8);
   KScope ks(st, "gap_fwd", ((double)N * HW * C + (double)N * C) * (dt == 0 ? 4.0 : 2.0), 3.0 * N * HW * C);
-#define FTP_GAP(PEND, U) FTP_DISPATCH(dt, hipLaunchKernelGGL((gap_fwd_k<T, PEND, U>), dim3(n), dim3(64), 0, st, v, pend, eps, momentum, N, HW, C / 8, (T*)out))
+#define FTP_GAP(PEND, U)                                                                                                                          \
+  do {                                                                                                                                            \
+    if (open) FTP_DISPATCH(dt, hipLaunchKernelGGL((gap_fwd_k<T, PEND, U, true>), dim3(n), dim3(64), 0, st, v, pend, eps, momentum, N, HW, C / 8, (T*)out, open)); \
+    else FTP_DISPATCH(dt, hipLaunchKernelGGL((gap_fwd_k<T, PEND, U, false>), dim3(n), dim3(64), 0, st, v, pend, eps, momentum, N, HW, C / 8, (T*)out, open)); \
+  } while (0)
   if (pend.partial) { if (HW <= 64) FTP_GAP(true, 1); else FTP_GAP(true, 4); }
   else if (HW <= 64) FTP_GAP(false, 1);
   else FTP_GAP(false, 4);
 #undef FTP_GAP
 }
 
+// Blocks from nmain on (sums != nullptr): the backward sums of the BatchNorm in front from what gap_fwd_k has left in open, sums[chunk][2][C] for
+// chunks of per images
 template <typename T>
-__global__ void gap_bwd_k(const T* __restrict__ dOut, size_t nvec, int HW, int CG, T* __restrict__ dIn) {
+__global__ void gap_bwd_k(const T* __restrict__ dOut, size_t nvec, int HW, int CG, T* __restrict__ dIn, int nmain, const float* __restrict__ open,
+                          float* __restrict__ sums, int N, int per) {
   float inv = 1.f / (float)HW;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += (size_t)gridDim.x * blockDim.x) {
+  if ((int)blockIdx.x >= nmain) {
+    const int C = CG * 8, nc = (C + 255) / 256, j = blockIdx.x - nmain, c = j % nc * 256 + threadIdx.x, chunk = j / nc;
+    const int n0 = chunk * per, n1 = min(n0 + per, N);
+    if (c >= C) return;
+    float s1 = 0.f, s2 = 0.f;
+    for (int n = n0; n < n1; n += 8) {
+      float o[8], cnt[8], z[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const size_t nu = n + u < n1 ? n + u : n0;
+        o[u] = to_f32(dOut[nu * C + c]);
+        cnt[u] = open[nu * 2 * C + c];
+        z[u] = open[(nu * 2 + 1) * C + c];
+      }
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float d = round_to<T>(o[u] * inv);          // as stored below
+        const bool on = n + u < n1 && cnt[u] > 0.f;       // chosen, not multiplied: an infinite gradient of what is off stays out
+        s1 += on ? d * cnt[u] : 0.f;
+        s2 += on ? d * z[u] : 0.f;
+      }
+    }
+    sums[((size_t)chunk * 2) * C + c] = s1;
+    sums[((size_t)chunk * 2 + 1) * C + c] = s2;
+    return;
+  }
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += (size_t)nmain * blockDim.x) {
     size_t n = i / ((size_t)HW * CG);
     int cg = (int)(i % CG);
     float v[8];
@@ -789,11 +837,13 @@ __global__ void gap_bwd_k(const T* __restrict__ dOut, size_t nvec, int HW, int C
   }
 }
 
-void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn) {
+void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn, const float* open, float* sums, int* P_out) {
   size_t nvec = (size_t)N * HW * (C / 8);
+  const int nmain = flat_grid(nvec, 256), per = N <= 512 ? 8 : (N + 63) / 64, P = (N + per - 1) / per;
+  if (sums) *P_out = P;
   KScope ks(st, "gap_bwd", ((double)N * HW * C + (double)N * C) * (dt == 0 ? 4.0 : 2.0), 1.0 * N * HW * C);
-  FTP_DISPATCH(dt, hipLaunchKernelGGL(gap_bwd_k<T>, dim3(flat_grid(nvec, 256)), dim3(256), 0, st,
-                                      (const T*)dOut, nvec, HW, C / 8, (T*)dIn));
+  FTP_DISPATCH(dt, hipLaunchKernelGGL(gap_bwd_k<T>, dim3(nmain + (sums ? P * ((C + 255) / 256) : 0)), dim3(256), 0, st,
+                                      (const T*)dOut, nvec, HW, C / 8, (T*)dIn, nmain, open, sums, N, per));
 }
 
 // ----------------------------------------------------- softmax cross-entropy

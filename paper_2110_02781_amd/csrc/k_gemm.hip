@@ -1807,7 +1807,8 @@ void pw_wgrad_group(int dt, hipStream_t st, const PwWgradJob* jobs, int n, PwSha
 // fp32, 4.7 + 2.2 + 12.0 + 3.8 for 13 x 1280 -> 100 bfloat16; one: 5.3 and 5.9.
 template <typename T>
 __global__ __launch_bounds__(256) void fc_bwd_k(const T* __restrict__ d, View in, const T* __restrict__ w, int B, int N, int K, float* __restrict__ g_w,
-                                                float* __restrict__ g_b, T* __restrict__ dIn, int HW, int nd) {
+                                                float* __restrict__ g_b, T* __restrict__ dIn, int HW, int nd, const float* __restrict__ open,
+                                                float* __restrict__ sums) {
   constexpr int U = 4;
   __shared__ float red[4][16][17];
   __shared__ float bred[4][16];
@@ -1820,6 +1821,14 @@ __global__ __launch_bounds__(256) void fc_bwd_k(const T* __restrict__ d, View in
   if (dgrad) {                                          // rows b, reduction over n
     const int b = i0 + l16, bc = b < B ? b : 0;
     const int nst = (N + 15) / 16, sb = wave * nst / 4, se = (wave + 1) * nst / 4;
+    const int ob = i0 + orow, ok = k0 + ocol;
+    const bool written = ob < B && ok < K;
+    float cnt = 0.f, z = 0.f;
+    if (sums) {                                         // requested now, used behind the products
+      const size_t at = written ? (size_t)ob * 2 * K + ok : 0;
+      cnt = open[at];
+      z = open[at + (written ? K : 0)];
+    }
     for (int s0 = sb; s0 < se; s0 += U) {
       T x[U][4], y[U][4];
 #pragma unroll
@@ -1841,12 +1850,25 @@ __global__ __launch_bounds__(256) void fc_bwd_k(const T* __restrict__ d, View in
 #pragma unroll
     for (int r = 0; r < 4; ++r) red[wave][4 * rg + r][l16] = acc[r];
     __syncthreads();
-    const int ob = i0 + orow, ok = k0 + ocol;
-    if (ob >= B || ok >= K) return;
     const float v = red[0][orow][ocol] + red[1][orow][ocol] + red[2][orow][ocol] + red[3][orow][ocol];
-    if (HW == 0) { dIn[(size_t)ob * K + ok] = from_f32<T>(v); return; }
+    if (HW == 0) { if (written) dIn[(size_t)ob * K + ok] = from_f32<T>(v); return; }
     // the mean's gradient: the pooled feature's, as stored, times 1 / HW at every position
     const T o = from_f32<T>(round_to<T>(v) * (1.f / (float)HW));
+    if (sums) {
+      const bool on = written && cnt > 0.f;             // chosen, not multiplied: an infinite gradient of what is off stays out
+      __syncthreads();
+      red[0][orow][ocol] = on ? to_f32(o) * cnt : 0.f;
+      red[1][orow][ocol] = on ? to_f32(o) * z : 0.f;
+      __syncthreads();
+      if (threadIdx.x < 32 && k0 + (int)(threadIdx.x & 15) < K) {
+        const int q = threadIdx.x >> 4, c = threadIdx.x & 15;
+        float t = 0.f;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) t += red[q][r][c];
+        sums[((size_t)(tile / kt) * 2 + q) * K + k0 + c] = t;
+      }
+    }
+    if (!written) return;
     T* dst = dIn + (size_t)ob * HW * K + ok;
     for (int p = 0; p < HW; ++p) dst[(size_t)p * K] = o;
     return;
@@ -1897,13 +1919,15 @@ int fc_bwd_ok(int B, int N, int K) { return B <= 512 && N <= 1024 && (size_t)N *
 // the tiles write their 64-byte pieces position by position: for a few MB that is cheaper than a launch
 int fc_bwd_gap_ok(int B, int HW, int K) { return (size_t)B * HW * K <= ((size_t)1 << 20); }
 
-void fc_bwd(int dt, hipStream_t st, const void* d, HView in, const void* w, int B, int N, int K, float* g_w, float* g_b, void* dIn, int HW) {
+void fc_bwd(int dt, hipStream_t st, const void* d, HView in, const void* w, int B, int N, int K, float* g_w, float* g_b, void* dIn, int HW,
+            const float* open, float* sums, int* P_out) {
   const int kt = (K + 15) / 16, nd = dIn ? (B + 15) / 16 * kt : 0, nw = (N + 15) / 16 * kt;
   const double es = dt == 0 ? 4.0 : 2.0;
   KScope ks(st, "fc_bwd", ((double)B * K * (1.0 + (HW > 0 ? HW : 1)) + (double)B * N + (double)N * K) * es + (double)N * K * 8, 4.0 * B * N * K, B, K, N);
   const View v{in.z, in.scale, in.shift, in.act};
-  if (dt == 0) hipLaunchKernelGGL(fc_bwd_k<float>, dim3(nd + nw), dim3(256), 0, st, (const float*)d, v, (const float*)w, B, N, K, g_w, g_b, (float*)dIn, HW, nd);
-  else hipLaunchKernelGGL(fc_bwd_k<bf16_t>, dim3(nd + nw), dim3(256), 0, st, (const bf16_t*)d, v, (const bf16_t*)w, B, N, K, g_w, g_b, (bf16_t*)dIn, HW, nd);
+  if (sums) *P_out = (B + 15) / 16;
+  if (dt == 0) hipLaunchKernelGGL(fc_bwd_k<float>, dim3(nd + nw), dim3(256), 0, st, (const float*)d, v, (const float*)w, B, N, K, g_w, g_b, (float*)dIn, HW, nd, open, sums);
+  else hipLaunchKernelGGL(fc_bwd_k<bf16_t>, dim3(nd + nw), dim3(256), 0, st, (const bf16_t*)d, v, (const bf16_t*)w, B, N, K, g_w, g_b, (bf16_t*)dIn, HW, nd, open, sums);
 }
 
 // wgrad then dgrad of one pointwise layer; short problems take one launch for both

@@ -118,8 +118,13 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
 
 // ---- pooling, loss, optimiser ---------------------------------------------------
 // pend.partial != nullptr: the BatchNorm of the input is still partial sums; finished here
-void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out);
-void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn);
+// open != nullptr (in is a view): also, for each image, how many positions of a channel the activation passes and the sum of the raw values there,
+// open[N][2][C]: all that the backward sums of that BatchNorm need of the tensor
+void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, int N, int HW, int C, void* out,
+             float* open = nullptr);
+// sums != nullptr: also the partial sums [*P_out][2][C] that bn_bwd_reduce would compute for that BatchNorm + activation
+void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn, const float* open = nullptr, float* sums = nullptr,
+             int* P_out = nullptr);
 // dlogits[B][classes] = (softmax - onehot)/B, mean loss into *loss; row_loss: B floats of scratch.  arrived: kCeCounters zeros, zeros again afterwards,
 // for one call at a time; without them what softmax_ce_arrives takes a launch more
 int softmax_ce_arrives(int B, int classes);
@@ -130,10 +135,11 @@ void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* label
 void bias_grad(int dt, hipStream_t st, const void* d, int B, int Nout, float* g_bias);
 // the whole backward of a fully connected layer d[B][N] -> in[B][K] in one launch: g_w += d^T in, g_b += column sums of d,
 // and unless dIn is nullptr dIn = d W.  HW >= 1: the layer stands behind an average over HW positions and dIn [B][HW][K] is
-// that one's input gradient.  fc_bwd_ok: few enough rows that the tiles' walks over them stay short.
+// that one's input gradient, and with sums != nullptr the layer also leaves them as gap_bwd does.  fc_bwd_ok: few enough rows that the tiles' walks over them stay short.
 int fc_bwd_ok(int B, int N, int K);
 int fc_bwd_gap_ok(int B, int HW, int K);
-void fc_bwd(int dt, hipStream_t st, const void* d, HView in, const void* w, int B, int N, int K, float* g_w, float* g_b, void* dIn, int HW);
+void fc_bwd(int dt, hipStream_t st, const void* d, HView in, const void* w, int B, int N, int K, float* g_w, float* g_b, void* dIn, int HW,
+            const float* open = nullptr, float* sums = nullptr, int* P_out = nullptr);
 // g += wd*w; v = mu*v+g; w -= lr*v; g = 0; optional working copy w_lp (bfloat16)
 void sgd_update(hipStream_t st, float* w, float* g, float* v, void* w_lp, size_t n, float lr, float mu,
                 float wd);

@@ -221,6 +221,7 @@ struct UnitPlan {
   bool out_virtual;                // CONV unit whose output stays a view
   size_t in_mat_off;               // residual block fed by a view: materialised copy of its input
   bool need_in_mat;
+  size_t open_off;                 // an average behind a convolution: byte offset of what its forward leaves of the activation (gap_fwd's open)
 };
 
 struct Slot {
@@ -496,6 +497,8 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     p.need_in_mat = u.residual && i > a && m->units[i - 1].d.kind == FTP_UNIT_CONV;
     p.in_mat_off = 0;
     if (p.need_in_mat) { p.in_mat_off = stash; stash += act_bytes(u.inH, u.inW, u.inC); }
+    p.open_off = stash;
+    if (u.d.kind == FTP_UNIT_GAP && i > a && m->units[i - 1].d.kind == FTP_UNIT_CONV) stash += align_up((size_t)batch * 2 * u.inC * 4, 256);
     if (u.d.kind == FTP_UNIT_FC) {
       size_t need = pw_wgrad_ws((size_t)batch, u.inC, u.outC);
       if (need > ws_floats) ws_floats = need;
@@ -828,6 +831,25 @@ static bool next_forms_block(const ftp_stage* s, size_t i) {
   return n.type == SUB_PW && pw_pro_ok(s->dt, (size_t)s->batch * n.g.Hout * n.g.Wout, n.g.Cin, n.g.Cout);
 }
 
+// A short 1-D convolution that does its own BatchNorm backward from sums the layer behind has left, and whether unit i's convolution
+// can leave them for the one in front.
+static bool conv1d_takes_sums(const ftp_stage* s, const UnitPlan& p) {
+  if (p.info->d.kind != FTP_UNIT_CONV || !p.axis[0] || !s->defers) return false;
+  ConvGeom g = p.info->subs[0].g; g.N = s->batch;
+  return conv1d_bwd_sums_ok(s->dt, g) && bn_bwd_small_ok((size_t)g.N * g.Wout, g.Cout);
+}
+static bool conv1d_leaves_sums(const ftp_stage* s, size_t i) { return i > 0 && conv1d_takes_sums(s, s->plan[i - 1]); }
+
+// what the forward of unit i, an average, leaves of the activation in front for that BatchNorm's backward sums (nullptr: nothing, its backward
+// does not take sums)
+static float* open_sums(const ftp_stage* s, const Slot& sl, size_t i) {
+  if (i == 0 || s->plan[i - 1].info->d.kind != FTP_UNIT_CONV) return nullptr;
+  const UnitPlan& q = s->plan[i - 1];
+  const ConvGeom& g = q.info->subs[0].g;
+  if (!conv1d_takes_sums(s, q) && bn_bwd_small_ok((size_t)s->batch * g.Hout * g.Wout, g.Cout)) return nullptr;
+  return (float*)(sl.stash + s->plan[i].open_off);
+}
+
 // every unit of the stage over the input at offset 0 of the slot's stash, with the weights W
 static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet& W, hipStream_t st) {
   OutPending block{};      // the output of a short block, left to the pointwise layer behind it
@@ -885,7 +907,7 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
         break;
       }
       case FTP_UNIT_GAP:
-        gap_fwd(s->dt, st, in, carry, kBnEps, s->bn_mom, s->batch, u.inH * u.inW, u.inC, sl.stash + p.out_off);
+        gap_fwd(s->dt, st, in, carry, kBnEps, s->bn_mom, s->batch, u.inH * u.inW, u.inC, sl.stash + p.out_off, open_sums(s, sl, i));
         carry.partial = nullptr;
         break;
       case FTP_UNIT_FC:
@@ -1072,15 +1094,6 @@ static ftp_stage::LeftSums take_sums(ftp_stage* s, const void* dA) {
   s->left.of = nullptr;
   return l;
 }
-
-// A short 1-D convolution that does its own BatchNorm backward from sums the layer behind has left, and whether unit i's convolution
-// can leave them for the one in front.
-static bool conv1d_takes_sums(const ftp_stage* s, const UnitPlan& p) {
-  if (p.info->d.kind != FTP_UNIT_CONV || !p.axis[0] || !s->defers) return false;
-  ConvGeom g = p.info->subs[0].g; g.N = s->batch;
-  return conv1d_bwd_sums_ok(s->dt, g) && bn_bwd_small_ok((size_t)g.N * g.Wout, g.Cout);
-}
-static bool conv1d_leaves_sums(const ftp_stage* s, size_t i) { return i > 0 && conv1d_takes_sums(s, s->plan[i - 1]); }
 
 // A short project layer (no activation, k the last of its block) whose BatchNorm backward is done on the way into its data gradient,
 // from sums that the layer behind has left: dIn is wanted, the weight gradient waits for the end of the call.
@@ -1408,7 +1421,11 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
           const UnitInfo* pu = i > 1 ? s->plan[i - 1].info : nullptr;
           const int HW = pu && pu->d.kind == FTP_UNIT_GAP && s->prof == nullptr && fc_bwd_gap_ok(s->batch, pu->inH * pu->inW, u.inC)
                              ? pu->inH * pu->inW : 0;
-          fc_bwd(s->dt, st, d, in, conv_w(s, W, woff), s->batch, u.outC, u.inC, s->grads + woff, s->grads + woff + (size_t)u.outC * u.inC, next, HW);
+          const float* open = HW > 0 ? open_sums(s, sl, i - 1) : nullptr;
+          int P = 0;
+          fc_bwd(s->dt, st, d, in, conv_w(s, W, woff), s->batch, u.outC, u.inC, s->grads + woff, s->grads + woff + (size_t)u.outC * u.inC, next, HW,
+                 open, open ? s->bn_part : nullptr, &P);
+          if (open) leave_sums(s, next, s->bn_part, P);
           gap_done = HW > 0;
           break;
         }
@@ -1419,7 +1436,12 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
       }
       case FTP_UNIT_GAP:
         if (gap_done) { produced = false; gap_done = false; }         // d is its input's gradient already
-        else if (next) gap_bwd(s->dt, st, d, s->batch, u.inH * u.inW, u.inC, next);
+        else if (next) {
+          const float* open = open_sums(s, sl, i);
+          int P = 0;
+          gap_bwd(s->dt, st, d, s->batch, u.inH * u.inW, u.inC, next, open, open ? s->bn_part : nullptr, &P);
+          if (open) leave_sums(s, next, s->bn_part, P);
+        }
         break;
       case FTP_UNIT_CONV:
         if ((rc = sub_backward(s, sl, p, 0, d, in, v.sub_out[i][0], next, nullptr, W, st, BWD_FULL, false, nullptr, leaves_sums(s, v, i)))) return rc;
