@@ -91,12 +91,12 @@ __device__ __forceinline__ void finish_backward_n(const BnPending& sums, int C, 
   __syncthreads();
 }
 
-enum { kSlabSumsBytes = 1024 * 8 };      // slab_sums' red
+enum { kSlabSumsBytes = 1024 * 8 };      // slab_sums' red, blocks of 256 threads
 // Column sums of partial[P][2][C] for the nc channels from c0 (multiples of 4), by every block of a kernel that is cut into slabs of
-// up to 64 channels: 16-byte loads, all of a thread's (up to 16) on their way together, float64 sums in a fixed order.  red: 1024
-// doubles; on return thread t < nc has its channel's two sums (behind a barrier; red may be used again after another).
+// up to 64 channels: 16-byte loads, all of a thread's (up to 16) on their way together, float64 sums in a fixed order.  red: four doubles a
+// thread, at most 32 a channel; on return thread t < nc has its channel's two sums (behind a barrier; red may be used again after another).
 __device__ __forceinline__ void slab_sums(const float* __restrict__ partial, int P, int C, int c0, int nc, double* red, double& s0, double& s1) {
-  const int tid = threadIdx.x, n4 = nc >> 2, nv = 2 * n4, L = (int)blockDim.x / nv, lane = tid / nv, v = tid - lane * nv;
+  const int tid = threadIdx.x, n4 = nc >> 2, nv = 2 * n4, most = (int)blockDim.x / nv, L = most < 16 ? most : 16, lane = tid / nv, v = tid - lane * nv;
   if (lane < L) {
     const float* src = partial + (v < n4 ? c0 + 4 * v : C + c0 + 4 * (v - n4));
     double t[4] = {0.0, 0.0, 0.0, 0.0};

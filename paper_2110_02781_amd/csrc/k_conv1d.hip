@@ -230,7 +230,11 @@ __global__ __launch_bounds__(512) void conv1d_rows_k(Conv1dArgs p) {
   RowVecs<T, NV> tile;
   tile.init(p.C, p.CP, LDR, prow, xbuf);
   tile.fetch(X, p.C, p.M, it_beg * TI - p.pad);
-  if (view && tid < p.C) { vsc[0][tid] = p.view.scale[tid]; vsc[1][tid] = p.view.shift[tid]; }
+  // The BatchNorm of x still partial sums: every block adds them, on their way with its first rows, where a tile or the meeting of the wavefronts
+  // will lie (256 bytes a channel; a tile is more).  A finalize launch took 4.1 us of the chain.
+  const bool pending = !DGRAD && p.pend.partial != nullptr;
+  if (pending) finish_slab(p.pend, p.C, 0, p.C, p.eps, p.momentum, range == 0, reinterpret_cast<double*>(smem), vsc[0], vsc[1]);
+  if (view && !pending && tid < p.C) { vsc[0][tid] = p.view.scale[tid]; vsc[1][tid] = p.view.shift[tid]; }
   load_w(0, p.kphase);
   for (int c = tid; c < LDR; c += 512) {
     xs[prow * LDR + c] = 0.f;
@@ -802,27 +806,32 @@ static bool conv1d_small(const ConvGeom& g) { return (size_t)g.N * g.Win <= kC1S
 // matrices: one in forward, which the weight gradient reads again if no layer behind has taken the buffer, one of dz, and launches that
 // layers here share with others.  A first layer (no data gradient) needs a single matrix.  A stage that forks has no buffer for
 // that of dz, and its direct data gradient is slower than all else.
-// The lines lie where both sides were even when the row tiles took their weights through LDS in chunks; the kernels here have since gained 7 - 45 %
+// First layers in front of others, a step of the stage (forward, backward, update) with an average, a fully connected layer and the loss behind, us, patch matrices /
+// here, 32768, 65536, 131072 and 262144 rows.  fp32: in front of a layer of 3 taps 3 -> 16, 3 taps, 103 / 90, 122 / 114, 178 / 178, 282 / 288; 1 -> 32, 5 taps 102 / 93,
+// 130 / 124, 192 / 195, 297 / 311; 5 -> 32, 9 taps 105 / 96, 139 / 127, 213 / 199, 330 / 319; 12 -> 24, 3 taps 101 / 90, 131 / 119, 203 / 186, 313 / 296; 9 -> 64, 5 taps 122 /
+// 113, 168 / 157, 262 / 249, 442 / 423; the sensor network's 9 -> 32, 5 taps 199 / 192, 297 / 288, 485 / 474.  bfloat16 (odd channels +): 3 -> 16 90 / 86, 113 / 108, 159 /
+// 164; 12 -> 24 96 / 86, 115 / 107, 172 / 167, 254 / 263; 9 -> 64, 5 taps 106 / 106, 139 / 144; 10 -> 64, 9 taps 112 / 111, 149 / 152; the sensor network 177 / 173, 261 / 260.
+// The other lines lie where both sides were even when the row tiles took their weights through LDS in chunks; the kernels here have since gained 7 - 45 %
 // and the other side nothing, so layers just beyond a line are now often faster here too (marked +: sent to the patch matrices all the same), and none is
-// slower than it was.  Steps, us, patch matrices / here.  fp32: 64 -> 64, 5 taps, alone, 32768 rows 164 / 88; first layers alone 9 -> 32, 5 taps, 32768
-// 41.7 / 36.0 +, 131072 79.9 / 70.3 +, 8 -> 32 131072 78.0 / 63.4 +, 3 -> 64, 3 taps, 131072 97.6 / 84.3, 262144 142 / 139 +; chain 8 -> 8, 3 taps, 131072 207 / 177,
-// 262144 327 / 287 +.  bfloat16: chain 64 -> 64, 9 taps, 2304 rows 143 / 136 +, 8192 237 / 151, 32768 487 / 288, 7 taps, 131072 1121 / 772 +;
+// slower than it was.  Steps, us: fp32 64 -> 64, 5 taps, alone, 32768 rows 164 / 88; first layers alone 9 -> 32, 5 taps, 32768 41.7 / 36.0 +, 131072 79.9 / 70.3 +, 3 ->
+// 64, 3 taps, 131072 97.6 / 84.3, 262144 142 / 139 +, bfloat16 3 -> 8, 3 taps, 16384 37.6 / 32.4, 32768 38.6 / 35.5 +, 524288 76 / 144, 9 -> 32, 5 taps, 2304 29.5 / 29.4,
+// 65536 42.4 / 45.0; chain 8 -> 8, 3 taps, 131072 207 / 177, 262144 327 / 287 +.  bfloat16: chain
+// 64 -> 64, 9 taps, 2304 rows 143 / 136 +, 8192 237 / 151, 32768 487 / 288, 7 taps, 131072 1121 / 772 +;
 // 48 -> 48, 7 taps, 2304 127 / 109 +, 6144 157 / 123 +, 32768 352 / 228, 131072 893 / 637 +; 32 -> 64, 9 taps, 4096 153 / 115 +, 6144 176 / 117; chain
-// 8 -> 8, 3 taps, 65536 148 / 118, 131072 181 / 169 +, 1048576 614 / 912; 32 -> 32, 3 taps, 131072 341 / 222, 524288 929 / 668 +; first layers 9 -> 32, 5
-// taps, alone 2304 29.5 / 29.4, 65536 42.4 / 45.0, in front of two more 16384 196 / 129, 65536 354 / 233 (there by patch matrices itself, 235); 3 -> 8, 3 taps,
-// alone 8192 37.3 / 30.7, 16384 37.6 / 32.4, 32768 38.6 / 35.5 +, 524288 76 / 144; a layer behind others alone in its stage 64 -> 64, 9 taps 4096
-// 55.3 / 56.7, 8192 72.0 / 61.6 +, 24576 106 / 104, 5 taps 32768 93.8 / 78.9, 65536 128 / 120 +, 3 taps 32768 80.0 / 66.9, 65536 104 / 103; 16 -> 16, 5
-// taps, in front of another 32768 120 / 74, 131072 219 / 144, 524288 480 / 423 +.
+// 8 -> 8, 3 taps, 65536 148 / 118, 131072 181 / 169 +, 1048576 614 / 912; 32 -> 32, 3 taps, 131072 341 / 222, 524288 929 / 668 +; a layer behind others alone in
+// its stage 64 -> 64, 9 taps 4096 55.3 / 56.7, 8192 72.0 / 61.6 +, 24576 106 / 104, 5 taps 32768 93.8 / 78.9, 65536 128 / 120 +, 3 taps 32768 80.0 / 66.9, 65536
+// 104 / 103; 16 -> 16, 5 taps, in front of another 32768 120 / 74, 131072 219 / 144, 524288 480 / 423 +.
 int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks) {
   const size_t M = (size_t)g.N * g.Win;
   const int lo = g.Cin < g.Cout ? g.Cin : g.Cout, hi = g.Cin < g.Cout ? g.Cout : g.Cin;
   const int K = g.kw * g.Cin, both = g.kw * (g.Cin + g.Cout), weights = K * g.Cout;
   const bool odd = g.Cin % 8 != 0;                    // read value by value here
   if (conv1d_small(g)) return 1;
-  if (first && dt == 0) {                             // the patch matrix of a narrow input is little to write
-    if (g.Cout > 32 ? odd && K <= 54 && M >= 200000 : (odd || alone) && K <= 45 && M >= 32768) return 0;
+  if (first && dt == 0 && alone) {
+    if (g.Cout > 32 ? odd && K <= 54 && M >= 200000 : K <= 45 && M >= 32768) return 0;
     if (odd && g.Cin < 12 && K <= 81 && (g.Cout <= 32 || K >= 45) && M >= 131072) return 0;
   }
+  if (first && dt == 0 && !alone && odd && K < 24 && g.Cout <= 32 && M >= 98304) return 0;      // little to multiply for each row read value by value
   if (first && dt == 1) {
     if (K >= 280 && g.Cout <= 32 && M >= 8192) return 1;
     if (alone && M < 8192) return odd ? K <= 40 : K <= 240 && weights <= 5000;
@@ -914,6 +923,7 @@ void conv1d_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float e
   }
   FTP_DISPATCH(dt, (conv1d_rows<T, false>(st, a, P_out)));
 }
+int conv1d_finish_ok(const ConvGeom& g, int P) { return P <= kC1Blocks && g.Cin % 8 == 0; }
 
 void conv1d_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out) {
   Conv1dArgs a = conv1d_args(g, true);

@@ -597,7 +597,7 @@ __global__ __launch_bounds__(256) void bn_bwd_finish_apply_k(const T* __restrict
 // batch 128 (4) 29.14 / 29.17 / 29.55; with tensors of up to 64 M values too 30.0.  (The depthwise forward doing the same for its input's
 // BatchNorm took as long as the launch it saved.)
 int bn_finish_ok(size_t M, int C, int P) {
-  return P <= 200 && M * (size_t)C <= ((size_t)16 << 20);
+  return P <= 256 && M * (size_t)C <= ((size_t)16 << 20);
 }
 
 void bn_bwd_finish_apply(int dt, hipStream_t st, const void* dA, const void* z, size_t M, int C, const float* scale, const float* shift, int act,

@@ -186,7 +186,8 @@ int conv1d_bwd_sums_ok(int dt, const ConvGeom& g);      // conv1d_bwd_small with
 // of the layers that are conv1d_ok: whether they run here or through patch matrices.  first: no data gradient is wanted, alone: the
 // stage's only convolution, forks: the stage runs weight gradients on a second stream
 int conv1d_pays(int dt, const ConvGeom& g, bool first, bool alone, bool forks);
-// pend.partial != nullptr (few rows only): the BatchNorm of the input is still partial sums, not those in `stats`; finished here
+// pend.partial != nullptr (few rows, or conv1d_finish_ok for its P): the BatchNorm of the input is still partial sums, not those in `stats`; finished here
+int conv1d_finish_ok(const ConvGeom& g, int P);
 void conv1d_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps, float momentum, const void* w, const ConvGeom& g, void* z,
                 float* stats, int* P_out);
 // sums != nullptr (prev is a view): also the partial sums bn_bwd_reduce would compute for the BatchNorm + activation `prev`

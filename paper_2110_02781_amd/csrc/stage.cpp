@@ -797,6 +797,10 @@ static void sub_forward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, HVi
   } else if (p.axis[k]) {
     // the partials of the input's BatchNorm, if it is pending, are read by every block: this layer's go to the other half
     float* part = s->bn_part;
+    if (pend && pend->partial && !conv1d_small_ok(g) && !conv1d_finish_ok(g, pend->P)) {
+      finish_now(s, st, *pend, g.Cin);
+      pend->partial = nullptr;
+    }
     if (pend && pend->partial == part) part = other_partials(s);
     const BnPending none{};
     conv1d_fwd(s->dt, st, in, pend ? *pend : none, kBnEps, s->bn_mom, w, g, z, part, &P);
@@ -867,13 +871,11 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
     switch (u.d.kind) {
       case FTP_UNIT_CONV:
       {
-        auto small1d = [&](const UnitInfo& x) {
-          if (x.d.kind != FTP_UNIT_CONV || x.subs[0].type != SUB_DIRECT) return false;
-          ConvGeom g = x.subs[0].g; g.N = s->batch;
-          return conv1d_small_ok(g) != 0;
-        };
-        const bool defer = small1d(u) && i + 1 < s->plan.size() &&
-                           (s->plan[i + 1].info->d.kind == FTP_UNIT_GAP || small1d(*s->plan[i + 1].info));
+        // the statistics of a convolution on the 1-D kernels are left to the one behind, and those of a short one to an average too
+        auto on_axis = [&](size_t j) { return s->plan[j].info->d.kind == FTP_UNIT_CONV && s->plan[j].axis[0]; };
+        ConvGeom g = u.subs[0].g; g.N = s->batch;
+        const bool defer = on_axis(i) && i + 1 < s->plan.size() &&
+                           (on_axis(i + 1) || (s->plan[i + 1].info->d.kind == FTP_UNIT_GAP && conv1d_small_ok(g)));
         sub_forward(s, sl, p, 0, in, W, st, &carry, defer, &block);
         break;
       }
