@@ -452,7 +452,9 @@ struct DwPlan {
   int tiles_h, tiles_w, ntiles, nblocks;
   unsigned m_cgb, m_qb, m_pw, m_segw;   // reciprocals for dw_div (divisors < 64, dividends < 1024)
 };
-enum { kDwFillNV = 6 };     // passes the patch staging is unrolled for
+enum { kDwFillNV = 6 };     // passes the patch staging is unrolled for: 128 bytes of bfloat16 channels, a patch of 10 x 18 pixels
+// passes of a kernel's patch staging at most: a load past the patch is made all the same, and fp32 slabs are half as many column groups
+template <typename T> struct DwFill { enum { CONV = sizeof(T) == 4 ? 3 : 6, DGRAD_S2 = sizeof(T) == 4 ? 1 : 2 }; };
 enum { kDwSegs = 2 };       // 4-pixel runs of a tile a weight-gradient thread keeps the dz of
 
 // x / d for x < 1024, d < 64 with m = 65536 / d + 1: two full-rate instructions instead of the
@@ -484,9 +486,9 @@ static DwPlan dw_plan(int C, int es, bool half_rows, int out_h, int out_w) {
 // into LDS as float [PH][PW][CGB][8].  Thread = (pixel lane, column group); fetch() issues all global
 // loads, commit() applies the view and writes LDS, so a caller can keep the loads of the next tile
 // in flight while it works on the current one.
-template <typename T>
+template <typename T, int NV = kDwFillNV>
 struct DwPatch {
-  Raw<T> raw[kDwFillNV];
+  Raw<T> raw[NV];
   unsigned ok;
   // image n is at most 2^31 elements: offsets inside it are 32-bit, products of 24-bit factors
   __device__ __forceinline__ void fetch(const T* __restrict__ src, int n, int h0, int w0, const DwPlan& d, int H, int W,
@@ -500,9 +502,9 @@ struct DwPatch {
     // Offsets first, then the loads back to back and unconditional (a pixel outside the image or the patch reads the
     // image's first pixel and is zeroed in commit): with a branch around each load, and its address computed next to
     // it, every load waited for the one before.
-    unsigned off[kDwFillNV];
+    unsigned off[NV];
 #pragma unroll
-    for (int q = 0; q < kDwFillNV; ++q) {
+    for (int q = 0; q < NV; ++q) {
       const int h = h0 + ph, w = w0 + pw;
       const bool in = pl + q * d.PPB < npix && h >= 0 && h < H && w >= 0 && w < W;
       off[q] = in ? __umul24(__umul24(h, W) + w, C) : 0u;
@@ -511,7 +513,7 @@ struct DwPatch {
       if (pw >= d.PW) { pw -= d.PW; ++ph; }
     }
 #pragma unroll
-    for (int q = 0; q < kDwFillNV; ++q) raw_load(raw[q], img + off[q]);
+    for (int q = 0; q < NV; ++q) raw_load(raw[q], img + off[q]);
   }
   __device__ __forceinline__ void commit(T* patch, const View& vw, const DwPlan& d, int cg0) const {
     const int pl = dw_div(threadIdx.x, d.m_cgb), cg = threadIdx.x - pl * d.CGB;
@@ -527,7 +529,7 @@ struct DwPatch {
     T* dst = patch + (pl * d.CGB + cg) * 8;            // stored in the tensor's own type: the values are already rounded to it
     const int step = d.PPB * d.CGB * 8;
 #pragma unroll
-    for (int q = 0; q < kDwFillNV; ++q) {
+    for (int q = 0; q < NV; ++q) {
       if (pl + q * d.PPB >= npix) break;
       float val[8] = {0, 0, 0, 0, 0, 0, 0, 0};
       if (ok & (1u << q)) {
@@ -575,7 +577,28 @@ __device__ __forceinline__ void dw_stage_weights(float* wl, const T* __restrict_
 // own).  2, for the data gradient: the output is the gradient dA of the BatchNorm + activation in front of this layer,
 // whose conv output zp sits at the same positions; the sums are those of bn_bwd_reduce (dY = dA where the activation
 // passes, sum of dY and of dY * zp), so that BatchNorm's backward starts at its finalize.
+template <typename T> __device__ __forceinline__ float4 round4(float4 v) {
+  return make_float4(round_to<T>(v.x), round_to<T>(v.y), round_to<T>(v.z), round_to<T>(v.w));
+}
 struct DwPrev { const void* z; const float* scale; const float* shift; int act; };
+
+// The runs of a channel quad are spread over spp threads: through LDS (red: [spp][QB][8]), summed in
+// a fixed order by one thread per channel and value into partial[2][C]
+__device__ __forceinline__ void dw_leave_sums(float4 s1, float4 s2, bool worker, int seg0, int cq, int QB, int cg0, int C, int spp, float* red,
+                                              float* __restrict__ partial) {
+  if (worker) {
+    float* r = red + ((size_t)seg0 * QB + cq) * 8;
+    r[0] = s1.x; r[1] = s1.y; r[2] = s1.z; r[3] = s1.w; r[4] = s2.x; r[5] = s2.y; r[6] = s2.z; r[7] = s2.w;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < QB * 8; i += 256) {
+    const int q = i >> 3, e = i & 7, c = cg0 * 8 + q * 4 + (e & 3);
+    if (c >= C) continue;
+    float t = 0.f;
+    for (int sgi = 0; sgi < spp; ++sgi) t += red[((size_t)sgi * QB + q) * 8 + e];
+    partial[(size_t)(e >> 2) * C + c] = t;
+  }
+}
 template <typename T, int S, bool FLIP, int STATS = 0, int RL = (S == 2 ? 2 : 4)>
 __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ w, DwPlan d, int Hin, int Win, int Hout,
                                                  int Wout, int C, T* __restrict__ out, float* __restrict__ stats = nullptr,
@@ -588,7 +611,7 @@ __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ 
   const int slab = lb % d.nslab, tile = lb / d.nslab;     // the slabs of a tile run together: they share cache lines when a slab is not 128 bytes
   const int tw = tile % d.tiles_w, th = (tile / d.tiles_w) % d.tiles_h, n = tile / (d.tiles_w * d.tiles_h);
   const int ho0 = th * d.TH, wo0 = tw * d.TW, cg0 = slab * d.CGB;
-  DwPatch<T> lp;
+  DwPatch<T, DwFill<T>::CONV> lp;
   lp.fetch(reinterpret_cast<const T*>(in.z), n, ho0 * S - 1, wo0 * S - 1, d, Hin, Win, C, cg0);
   dw_stage_weights(wl, w, C, cg0, d.CGB, d.m_cgb);
   lp.commit(patch, in, d, cg0);
@@ -652,22 +675,8 @@ __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ 
       }
   }
   if (STATS) {
-    // the runs of a channel quad are spread over spp threads: through LDS (the patch is no longer needed), summed in
-    // a fixed order by one thread per channel and value
-    __syncthreads();
-    float* red = reinterpret_cast<float*>(smem_raw);            // [spp][QB][8]
-    if (worker) {
-      float* r = red + ((size_t)seg0 * QB + cq) * 8;
-      r[0] = s1.x; r[1] = s1.y; r[2] = s1.z; r[3] = s1.w; r[4] = s2.x; r[5] = s2.y; r[6] = s2.z; r[7] = s2.w;
-    }
-    __syncthreads();
-    for (int i = threadIdx.x; i < QB * 8; i += 256) {
-      const int q = i >> 3, e = i & 7, c = cg0 * 8 + q * 4 + (e & 3);
-      if (c >= C) continue;
-      float t = 0.f;
-      for (int sgi = 0; sgi < d.spp; ++sgi) t += red[((size_t)sgi * QB + q) * 8 + e];
-      stats[((size_t)tile * 2 + (e >> 2)) * C + c] = t;
-    }
+    __syncthreads();                    // the patch is no longer needed
+    dw_leave_sums(s1, s2, worker, seg0, cq, QB, cg0, C, d.spp, reinterpret_cast<float*>(smem_raw), stats + (size_t)tile * 2 * C);
   }
 }
 
@@ -677,8 +686,8 @@ static size_t dw_lds_bytes(const DwPlan& d, int es) { return dw_patch_bytes(d, e
 
 // staging is unrolled for kDwFillNV passes; dw_div needs small divisors.  The plans of every shape a model can
 // describe satisfy this; if one ever does not, the launch is skipped and the stage call reports it.
-static bool dw_check_plan(DwPlan& d, int segs = kDwSegs) {
-  if (d.PH * d.PW > kDwFillNV * d.PPB || d.PW > 63 || d.CGB > 16 || d.segw > 32 || d.nseg > segs * d.spp) {
+static bool dw_check_plan(DwPlan& d, int fill = kDwFillNV, int segs = kDwSegs) {
+  if (d.PH * d.PW > fill * d.PPB || d.PW > 63 || d.CGB > 16 || d.segw > 32 || d.nseg > segs * d.spp) {
     launch_plan_failed("depthwise tile plan outside the kernels' limits");
     return false;
   }
@@ -703,7 +712,7 @@ void dw_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, 
   d.PH = (d.TH - 1) * s + 3;
   d.PW = (d.segw * run - 1) * s + 3;             // runs are whole: the patch covers the rounded-up tile width
   d.ntiles = g.N * d.tiles_h * d.tiles_w;
-  if (!dw_check_plan(d)) return;
+  if (!dw_check_plan(d, dt == 0 ? DwFill<float>::CONV : DwFill<bf16_t>::CONV)) return;
   View v{in.z, in.scale, in.shift, in.act};
   size_t total = (size_t)g.N * g.Hout * g.Wout;
   KScope ks(st, "dw_fwd", ((double)g.N * g.Hin * g.Win * g.Cout + (double)total * g.Cout) * es, 18.0 * total * g.Cout,
@@ -744,9 +753,6 @@ void dw_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, 
 __device__ __forceinline__ float4 view4(float4 v, const float* sc, const float* sh, float lo, float hi) {
   return make_float4(clamp_act(fmaf(v.x, sc[0], sh[0]), lo, hi), clamp_act(fmaf(v.y, sc[1], sh[1]), lo, hi),
                      clamp_act(fmaf(v.z, sc[2], sh[2]), lo, hi), clamp_act(fmaf(v.w, sc[3], sh[3]), lo, hi));
-}
-template <typename T> __device__ __forceinline__ float4 round4(float4 v) {
-  return make_float4(round_to<T>(v.x), round_to<T>(v.y), round_to<T>(v.z), round_to<T>(v.w));
 }
 
 // four channels of one pixel as loaded, converted at the point of use (so the load can stay in flight)
@@ -1116,7 +1122,7 @@ void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, con
   }
 }
 
-// Stride-2 data gradient over 8 x 8 input tiles: dIn[h][w] = sum over taps (i, j) with h+1-i and w+1-j
+// Stride-2 data gradient over 8 x 16 input tiles: dIn[h][w] = sum over taps (i, j) with h+1-i and w+1-j
 // even of dz[(h+1-i)/2][(w+1-j)/2] * w[i][j].  A run of 4 input pixels starting at an even column
 // touches three dz columns per dz row.
 template <typename T>
@@ -1131,7 +1137,7 @@ __global__ __launch_bounds__(256) void dw_dgrad_s2_k(const T* __restrict__ dz, c
   const int h0 = th * d.TH, w0 = tw * d.TW, cg0 = slab * d.CGB;       // tile origin, even
   __builtin_amdgcn_s_setprio(3);             // data-gradient chain: ahead of the weight-gradient stream's waves
   const int ho_lo = h0 / 2, wo_lo = w0 / 2;
-  DwPatch<T> lp;
+  DwPatch<T, DwFill<T>::DGRAD_S2> lp;
   View none{nullptr, nullptr, nullptr, 0};
   lp.fetch(dz, n, ho_lo, wo_lo, d, Hout, Wout, C, cg0);
   dw_stage_weights(wl, w, C, cg0, d.CGB, d.m_cgb);
@@ -1172,6 +1178,153 @@ __global__ __launch_bounds__(256) void dw_dgrad_s2_k(const T* __restrict__ dz, c
   }
 }
 
+// The whole backward of a stride-2 depthwise layer behind a BatchNorm + activation (prev, raw output zp at the data gradient's positions) in one pass: data
+// gradient, that BatchNorm's backward sums (as dw_conv_k leaves them with STATS = 2, sums[block][2][C]) and the weight gradient's partial sums
+// (gw[block][9][C]: dW[tap] = sum over pixels p of dz[the output that sees p at that tap] * activation[p]).  All three want the same dz, the last two the
+// same zp, which as passes of their own read it twice more.  A thread takes 2 x 2 pixels, which four dz values reach (nine products, no
+// parity to branch on); a block takes `per` tiles of 8 x 16 in a row, the next tile's dz on its way meanwhile, so that there are no more partials than
+// kMaxPartials.  Bound by memory.
+template <typename T>
+__global__ __launch_bounds__(256) void dw_bwd_s2_k(const T* __restrict__ dz, const T* __restrict__ w, DwPlan d, int Hin, int Win, int Hout, int Wout, int C,
+                                                   T* __restrict__ dIn, int per, float* __restrict__ sums, DwPrev prev, float* __restrict__ gw) {
+  constexpr int NR = sizeof(T) == 4 ? 1 : 2;          // rounds of a tile's at most 32 pixel quads: at least 16 lanes to a channel quad, fp32 32
+  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+  const int patch_bytes = (d.PH * d.PW * d.CGB * 8 * (int)sizeof(T) + 15) / 16 * 16;
+  float* wl = reinterpret_cast<float*>(smem_raw + 2 * patch_bytes);
+  const int lb = xcd_logical_block();
+  const int slab = lb % d.nslab, part = lb / d.nslab, cg0 = slab * d.CGB, t0 = part * per, t1 = min(t0 + per, d.ntiles);
+  __builtin_amdgcn_s_setprio(3);                      // data-gradient chain: ahead of the weight-gradient stream's waves
+  const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB, c4 = cq * 4, gc = cg0 * 8 + c4;
+  const bool worker = seg0 < d.spp && gc < C;
+  const int vs = d.CGB * 8;
+  int tw = t0 % d.tiles_w, th = t0 / d.tiles_w % d.tiles_h, n = t0 / (d.tiles_w * d.tiles_h);
+  DwPatch<T, DwFill<T>::DGRAD_S2> lp;
+  const View none{nullptr, nullptr, nullptr, 0};
+  lp.fetch(dz, n, th * d.TH / 2, tw * d.TW / 2, d, Hout, Wout, C, cg0);
+  dw_stage_weights(wl, w, C, cg0, d.CGB, d.m_cgb);
+  lp.commit(reinterpret_cast<T*>(smem_raw), none, d, cg0);
+  float4 aw[9], s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1, psc = s1, psh = s1;
+#pragma unroll
+  for (int t = 0; t < 9; ++t) aw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (worker) { psc = ld4(prev.scale + gc); psh = ld4(prev.shift + gc); }
+  const float plo = act_lo(prev.act), phi = act_hi(prev.act);
+  const T* Z = reinterpret_cast<const T*>(prev.z);
+  int hq[NR], wq[NR];                                 // this thread's quads in a tile
+  bool has[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int sg = seg0 + r * d.spp;
+    has[r] = worker && sg < d.nseg;
+    hq[r] = dw_div(has[r] ? sg : 0, d.m_segw);
+    wq[r] = (has[r] ? sg : 0) - hq[r] * d.segw;
+  }
+  __syncthreads();
+  for (int tile = t0; tile < t1; ++tile) {
+    const int h0 = th * d.TH, w0 = tw * d.TW;
+    const size_t img = (size_t)n * Hin * Win * C + gc;
+    Raw4<T> zp[NR][4];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {                   // a pixel outside the image reads its first and is not used
+        const int h = h0 + 2 * hq[r] + (o >> 1), x = w0 + 2 * wq[r] + (o & 1);
+        raw4_load(zp[r][o], Z + (worker ? img : 0) + (has[r] && h < Hin && x < Win ? __umul24(__umul24(h, Win) + x, C) : 0u));
+      }
+    if (++tw == d.tiles_w) { tw = 0; if (++th == d.tiles_h) { th = 0; ++n; } }
+    if (tile + 1 < t1) lp.fetch(dz, n, th * d.TH / 2, tw * d.TW / 2, d, Hout, Wout, C, cg0);
+    const T* patch = reinterpret_cast<const T*>(smem_raw + ((tile - t0) & 1) * patch_bytes);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if (!has[r]) continue;
+      const T* q = patch + (hq[r] * d.PW + wq[r]) * vs + c4;
+      const float4 d00 = load4(q), d01 = load4(q + vs), d10 = load4(q + d.PW * vs), d11 = load4(q + d.PW * vs + vs);
+      T* const out = dIn + img;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        const int h = h0 + 2 * hq[r] + (o >> 1), x = w0 + 2 * wq[r] + (o & 1);
+        const bool in = h < Hin && x < Win;
+        const float4 z = raw4_unpack(zp[r][o]), y = fma4(z, psc, psh);
+        float4 a = round4<T>(make_float4(clamp_act(y.x, plo, phi), clamp_act(y.y, plo, phi), clamp_act(y.z, plo, phi), clamp_act(y.w, plo, phi)));
+        if (!in) a = make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+        auto tap = [&](const int t, const float4 g) __attribute__((always_inline)) {
+          v = fma4(g, ld4(wl + t * vs + c4), v);
+          aw[t] = fma4(g, a, aw[t]);
+        };
+        if (o == 0) { tap(4, d00); }
+        else if (o == 1) { tap(3, d01); tap(5, d00); }
+        else if (o == 2) { tap(1, d10); tap(7, d00); }
+        else { tap(0, d11); tap(2, d10); tap(6, d01); tap(8, d00); }
+        if (!in) continue;
+        store4(out + __umul24(__umul24(h, Win) + x, C), v);
+        const float4 g = round4<T>(v);                // sums over the values as stored
+        const float4 p = make_float4(y.x > plo && y.x < phi ? g.x : 0.f, y.y > plo && y.y < phi ? g.y : 0.f, y.z > plo && y.z < phi ? g.z : 0.f,
+                                     y.w > plo && y.w < phi ? g.w : 0.f);
+        s1.x += p.x; s1.y += p.y; s1.z += p.z; s1.w += p.w;
+        s2 = fma4(p, z, s2);
+      }
+    }
+    if (tile + 1 < t1) lp.commit(reinterpret_cast<T*>(smem_raw + ((tile - t0 + 1) & 1) * patch_bytes), none, d, cg0);
+    __syncthreads();
+  }
+  float* red = reinterpret_cast<float*>(smem_raw);
+  dw_leave_sums(s1, s2, worker, seg0, cq, QB, cg0, C, d.spp, red, sums + (size_t)part * 2 * C);
+  // three taps at a time: [spp][QB][12]
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    __syncthreads();
+    if (worker)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) *reinterpret_cast<float4*>(red + ((size_t)seg0 * QB + cq) * 12 + j * 4) = aw[i * 3 + j];
+    __syncthreads();
+    for (int v = threadIdx.x; v < QB * 12; v += 256) {
+      const int q = v / 12, e = v - q * 12, c = cg0 * 8 + q * 4 + (e & 3);
+      if (c >= C) continue;
+      float t = 0.f;
+      for (int sgi = 0; sgi < d.spp; ++sgi) t += red[((size_t)sgi * QB + q) * 12 + e];
+      gw[((size_t)part * 9 + i * 3 + (e >> 2)) * C + c] = t;
+    }
+  }
+}
+
+static DwPlan dw_bwd_s2_plan(int dt, const ConvGeom& g, int* per, int* P) {
+  DwPlan d = dw_plan(g.Cout, dt == 0 ? 4 : 2, false, g.Hin, g.Win);       // tiles in input resolution
+  d.ntiles = g.N * d.tiles_h * d.tiles_w;
+  d.segw = (d.TW + 1) / 2;
+  d.nseg = (d.TH + 1) / 2 * d.segw;
+  d.m_segw = dw_magic(d.segw);
+  d.PH = (d.TH + 1) / 2 + 1;
+  d.PW = d.segw + 1;
+  *per = (d.ntiles + kMaxPartials - 1) / kMaxPartials;
+  *P = (d.ntiles + *per - 1) / *per;
+  return d;
+}
+size_t dw_bwd_s2_ws(int dt, const ConvGeom& g) {
+  if (g.stride != 2) return 0;
+  int per, P;
+  dw_bwd_s2_plan(dt, g, &per, &P);
+  return (size_t)P * 9 * g.Cout;
+}
+
+void dw_bwd_s2(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out, float* gw_part) {
+  const int es = dt == 0 ? 4 : 2;
+  int per;
+  DwPlan d = dw_bwd_s2_plan(dt, g, &per, P_out);
+  const size_t total = (size_t)g.N * g.Hin * g.Win, outs = (size_t)g.N * g.Hout * g.Wout;
+  KScope ks(st, "dw_dgrad", (2.0 * total + (double)outs) * g.Cout * es + (double)*P_out * 11 * g.Cout * 4, 36.0 * outs * g.Cout, (long)total, g.Cout, 2);
+  ks.route("one pass");
+  if (!dw_check_plan(d, dt == 0 ? DwFill<float>::DGRAD_S2 : DwFill<bf16_t>::DGRAD_S2) || d.nseg > (dt == 0 ? 1 : 2) * d.spp || !prev.scale) {
+    launch_plan_failed("stride-2 depthwise backward called for a layer it does not take");
+    return;
+  }
+  size_t lds = dw_lds_bytes(d, es) + dw_patch_bytes(d, es);
+  const size_t red = (size_t)d.spp * 2 * d.CGB * 12 * sizeof(float);
+  if (lds < red) lds = red;
+  const DwPrev pv{prev.z, prev.scale, prev.shift, prev.act};
+  FTP_DISPATCH(dt, hipLaunchKernelGGL(dw_bwd_s2_k<T>, dim3((unsigned)*P_out * d.nslab), dim3(256), lds, st, (const T*)dz, (const T*)w, d, g.Hin, g.Win, g.Hout,
+                                      g.Wout, g.Cout, (T*)dIn, per, sums, pv, gw_part));
+}
+
 // the stride-1 data gradient can leave the backward sums of the BatchNorm in front (dw_conv_k, STATS = 2) when its
 // tiles are few enough to be the partials
 int dw_dgrad_sums_ok(int dt, const ConvGeom& g) {
@@ -1194,7 +1347,7 @@ void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvG
     // the forward kernel on dz with the weights flipped
     d.PH = d.TH + 2;
     d.PW = d.segw * 4 + 2;
-    if (!dw_check_plan(d)) return;
+    if (!dw_check_plan(d, dt == 0 ? DwFill<float>::CONV : DwFill<bf16_t>::CONV)) return;
     View v{dz, nullptr, nullptr, 0};
     if (sums) {
       if (d.ntiles > kMaxPartials || !prev.scale) { launch_plan_failed("depthwise data gradient with BatchNorm sums: not for this layer"); return; }
@@ -1212,7 +1365,7 @@ void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvG
   } else {
     d.PH = d.TH / 2 + 2;
     d.PW = d.segw * 2 + 2;
-    if (!dw_check_plan(d)) return;
+    if (!dw_check_plan(d, dt == 0 ? DwFill<float>::DGRAD_S2 : DwFill<bf16_t>::DGRAD_S2)) return;
     FTP_DISPATCH(dt, hipLaunchKernelGGL(dw_dgrad_s2_k<T>, dim3(grid), dim3(256), dw_lds_bytes(d, es), st, (const T*)dz, (const T*)w,
                                         d, g.Hin, g.Win, g.Hout, g.Wout, g.Cout, (T*)dIn));
   }
@@ -1944,7 +2097,7 @@ void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& 
   }
   size_t lds;
   DwPlan d = dw_wgrad_plan(g, es, &lds);
-  if (!dw_check_plan(d, g.stride == 2 ? 1 : kDwSegs)) return;     // also: the runs of a tile whose dz a thread holds
+  if (!dw_check_plan(d, kDwFillNV, g.stride == 2 ? 1 : kDwSegs)) return;     // also: the runs of a tile whose dz a thread holds
   View v{in.z, in.scale, in.shift, in.act};
   {
     KScope ks(st, "dw_wgrad", ((double)g.N * g.Hin * g.Win * g.Cout + (double)g.N * g.Hout * g.Wout * g.Cout) * es + (double)d.nblocks * 9 * g.Cout * 4,

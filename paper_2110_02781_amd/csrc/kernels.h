@@ -226,6 +226,10 @@ void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, con
 int dw_dgrad_sums_ok(int dt, const ConvGeom& g);
 void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev = HView{},
               float* sums = nullptr, int* P_out = nullptr);
+// Stride-2 layers (dw_bwd_s2_ws > 0 floats of gw_part) whose input is the view prev: data gradient, those sums, and the weight gradient's partial sums
+// [*P_out][9][C] in one pass
+size_t dw_bwd_s2_ws(int dt, const ConvGeom& g);
+void dw_bwd_s2(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out, float* gw_part);
 // Weight gradients of several depthwise layers together: the kernels leave partial sums in each job's ws (dw_wgrad_ws
 // floats of its own) and append what is left to sum
 struct DwWgradJob { const void* dz; HView in; ConvGeom g; float* ws; float* g_w; };

@@ -215,6 +215,7 @@ struct UnitPlan {
   std::vector<size_t> z_off;       // per sub: byte offset of z in the slot stash
   std::vector<size_t> st_off;      // per sub: float offset of mean|invstd|scale|shift in the slot stats
   std::vector<size_t> part;        // per sub: floats of its partial weight gradients (stages that defer them)
+  size_t late_part;                // floats in front of its depthwise layer's place in ws_late
   std::vector<char> at_once;       // per sub: a pointwise layer of such a stage whose weight gradient runs next to its data gradient all the same
   std::vector<char> axis;          // per sub: a convolution along one axis that the kernels for those run
   size_t out_off;                  // byte offset of the materialised unit output (if any)
@@ -291,6 +292,11 @@ struct ftp_stage {
   std::vector<PwWgradJob> q_pw;
   std::vector<DwWgradJob> q_dw;
   std::vector<ReduceJob> q_red;
+  // Partial weight gradients that a stage on two streams leaves on the caller's until the end of the call: those of stride-2 depthwise layers
+  // (a place for each in ws_late) and of its first unit's expand layer, behind which nothing is left to run beside.
+  std::vector<ReduceJob> q_late;
+  float* ws_late = nullptr;
+  size_t ws_late_floats = 0;
   unsigned n_sub_bwd = 0;
   float *bn_part = nullptr, *coef = nullptr, *ws = nullptr, *row_loss = nullptr;
   unsigned* arrived = nullptr;
@@ -347,7 +353,7 @@ static void stage_free(ftp_stage* s) {
     if (s->ev_bjoin[i]) (void)hipEventDestroy(s->ev_bjoin[i]);
   }
   for (int i = 0; i < 6; ++i) dfree(s->dzring[i]);
-  dfree(s->bn_part); dfree(s->coef); dfree(s->ws); dfree(s->ws_tail); dfree(s->ws_fused); dfree(s->row_loss); dfree(s->arrived); dfree(s->im2col);
+  dfree(s->bn_part); dfree(s->coef); dfree(s->ws); dfree(s->ws_tail); dfree(s->ws_fused); dfree(s->ws_late); dfree(s->row_loss); dfree(s->arrived); dfree(s->im2col);
   dfree(s->dz_store); dfree(s->parts);
   if (s->timer) {
     if (s->timer->created)
@@ -436,6 +442,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     const UnitInfo& u = m->units[i];
     UnitPlan p;
     p.info = &u;
+    p.late_part = 0;
     p.p_off = s->n_param; s->n_param += align_up(u.n_param, 8);
     p.bn_off = s->n_bn; s->n_bn += u.n_bn;
     for (const Sub& sb : u.subs) {
@@ -468,6 +475,9 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       } else if (sb.type == SUB_DW && u.subs.size() == 3 && dw_bwd_small_ok(g)) {
         dz_stored = false;
         part = 0;
+      } else if (sb.type == SUB_DW && u.subs.size() == 3 && dw_bwd_s2_ws(m->dtype, g) > 0) {     // with the data gradient (sub_backward)
+        part = dw_bwd_s2_ws(m->dtype, g);
+        p.late_part = s->ws_late_floats; s->ws_late_floats += align_up(part, 64);
       }
       if (zb > dz_max) dz_max = zb;
       dz_bytes += dz_stored ? zb : 0;
@@ -517,7 +527,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   } else if (layer_ws > ws_floats) ws_floats = layer_ws;
   s->stash_bytes = stash; s->stats_floats = stats; s->max_act_bytes = max_act; s->ws_floats = ws_floats; s->max_c = max_c;
 
-  s->q_pw.reserve(n_convs); s->q_dw.reserve(n_convs); s->q_red.reserve(n_convs);      // a layer leaves at most one of each
+  s->q_pw.reserve(n_convs); s->q_dw.reserve(n_convs); s->q_red.reserve(n_convs); s->q_late.reserve(n_convs);      // a layer leaves at most one of each
   int rc = FTP_OK;
   size_t np = s->n_param ? s->n_param : 8;
   size_t nb = s->n_bn ? s->n_bn : 8;
@@ -560,6 +570,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   if (s->im2col_elems && (rc = dev_alloc(&s->im2col, s->im2col_elems * s->es))) { stage_free(s); return rc; }
   if (s->defers && ((rc = dev_alloc(&s->dz_store, s->dz_cap)) || (rc = dev_alloc(&s->parts, s->part_cap * 4)))) { stage_free(s); return rc; }
   if (!s->defers && s->ws_fused_floats && (rc = dev_alloc(&s->ws_fused, s->ws_fused_floats * 4))) { stage_free(s); return rc; }
+  if (!s->defers && s->ws_late_floats && (rc = dev_alloc(&s->ws_late, s->ws_late_floats * 4))) { stage_free(s); return rc; }
   if (!s->defers && s->ws_tail_floats && s->n_direct <= 1 &&
       (rc = dev_alloc(&s->ws_tail, s->ws_tail_floats * 4))) { stage_free(s); return rc; }
 
@@ -1144,14 +1155,14 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
                     s->grads + p.p_off + sb.beta_off, s->coef);
     // the sum of the kernel's partial weight gradients is off the data-gradient chain: it goes to the side stream,
     // and the next user of the partial buffer waits for it
-    const bool aside = stage_overlaps(s);
+    const bool last = !s->defers && &p == &s->plan[0], aside = stage_overlaps(s) && !last;
     if (s->join_pending[2]) {
       HIP_TRY(hipStreamWaitEvent(st, s->ev_join[2], 0));
       s->join_pending[2] = false;
     }
     pw_bwd_fused(st, dA, out, s->coef, conv_w(s, W, p.p_off + sb.w_off), in.z, res, M, g.Cin, g.Cout,
                  s->defers ? take_places(s, 0, p.part[k], st).part : s->ws_fused, s->grads + p.p_off + sb.w_off, dIn, aside ? s->side : st,
-                 aside ? s->ev_fork[2] : nullptr, s->defers ? &s->q_red : nullptr);
+                 aside ? s->ev_fork[2] : nullptr, s->defers ? &s->q_red : last ? &s->q_late : nullptr);
     if (aside) {
       HIP_TRY(hipEventRecord(s->ev_join[2], s->side));
       s->join_pending[2] = true;
@@ -1224,8 +1235,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   s->left.of = nullptr;                // where the caller formed dz
   // a depthwise layer behind a BatchNorm + activation of the same unit (the expand layer's): its data gradient is that
   // BatchNorm's dA and can leave the backward sums on the way
-  const bool with_sums = sb.type == SUB_DW && dIn != nullptr && mode == BWD_FULL && k > 0 && in.scale != nullptr &&
-                         !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cout) && dw_dgrad_sums_ok(s->dt, g);
+  const bool prev_sums = sb.type == SUB_DW && dIn != nullptr && mode == BWD_FULL && k > 0 && in.scale != nullptr &&
+                         !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cout);
+  const bool with_sums = prev_sums && dw_dgrad_sums_ok(s->dt, g);
   auto run_dw_dgrad = [&]() {
     if (with_sums) {
       int P = 0;
@@ -1242,6 +1254,14 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     conv1d_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, sums ? s->bn_part : nullptr, &P);
     if (sums) leave_sums(s, dIn, s->bn_part, P);
   };
+  if (prev_sums && dw_bwd_s2_ws(s->dt, g) > 0) {        // at stride 2 the weight gradient comes with it
+    int P = 0;
+    float* const gp = s->defers ? part : s->ws_late + p.late_part;
+    dw_bwd_s2(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, s->bn_part, &P, gp);
+    leave_sums(s, dIn, s->bn_part, P);
+    (s->defers ? s->q_red : s->q_late).push_back(ReduceJob{gp, s->grads + p.p_off + sb.w_off, P, 9 * C, C, 1, 9, C});
+    return FTP_OK;
+  }
   if (dgrad_first) run_dw_dgrad();
   if (batched && mode == BWD_FULL) {
     // noted for the unit's fork; the data gradient goes on as it would behind a forked weight gradient
@@ -1332,7 +1352,8 @@ static void run_noted(ftp_stage* s, hipStream_t st) {
   pw_wgrad_group(s->dt, st, s->q_pw.data(), (int)s->q_pw.size(), s->share, &s->q_red);
   dw_wgrad_group(s->dt, st, s->q_dw.data(), (int)s->q_dw.size(), &s->q_red);
   reduce_group(st, s->q_red.data(), (int)s->q_red.size());
-  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
+  reduce_group(st, s->q_late.data(), (int)s->q_late.size());
+  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear(); s->q_late.clear();
   s->dz_used = s->part_used = 0;         // what reads the stores is ahead of what this stream writes there next
 }
 
@@ -1396,7 +1417,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
     if (rc) return rc;
     s->stash_owner = slot;
   }
-  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear();
+  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear(); s->q_late.clear();
   s->dz_used = s->part_used = 0;
   s->left.of = nullptr;
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
