@@ -3,6 +3,8 @@
 // applied on load and zero padding is inserted after it (a halo cell is 0, not
 // act(bn(0))).  Depthwise layers over short tensors (at most 2048 pixels) run whole
 // forward / backward sub-chains in one launch (dw_fwd_bn_small_k, dw_bwd_small_k).
+#include <type_traits>
+
 #include "dev_common.h"
 #include "kernels.h"
 #include "bn_pending.h"
@@ -452,17 +454,16 @@ struct DwPlan {
   int tiles_h, tiles_w, ntiles, nblocks;
   unsigned m_cgb, m_qb, m_pw, m_segw;   // reciprocals for dw_div (divisors < 64, dividends < 1024)
 };
-enum { kDwFillNV = 6 };     // passes the patch staging is unrolled for: 128 bytes of bfloat16 channels, a patch of 10 x 18 pixels
-// passes of a kernel's patch staging at most: a load past the patch is made all the same, and fp32 slabs are half as many column groups
-template <typename T> struct DwFill { enum { CONV = sizeof(T) == 4 ? 3 : 6, DGRAD_S2 = sizeof(T) == 4 ? 1 : 2 }; };
-enum { kDwSegs = 2 };       // 4-pixel runs of a tile a weight-gradient thread keeps the dz of
+// passes of the forward kernel's patch staging at most (128 bytes of channels, a patch of 10 x 18 pixels): a load past the patch is made all the same, and
+// fp32 slabs are half as many column groups
+template <typename T> struct DwFill { enum { NV = sizeof(T) == 4 ? 3 : 6 }; };
 
 // x / d for x < 1024, d < 64 with m = 65536 / d + 1: two full-rate instructions instead of the
 // ~25-instruction integer division sequence (thread-index decoding was a third of the kernel's VALU work)
 static unsigned dw_magic(int d) { return 65536u / (unsigned)d + 1u; }
 __device__ __forceinline__ int dw_div(int x, unsigned m) { return (int)(__umul24((unsigned)x, m) >> 16); }
 
-static DwPlan dw_plan(int C, int es, bool half_rows, int out_h, int out_w) {
+static DwPlan dw_plan(int C, int es, bool half_rows, int out_h, int out_w, int wide = 16) {
   DwPlan d;
   const int cgs = C / 8, cap = es == 2 ? 8 : 4;            // 128 bytes of channels per pixel
   d.nslab = (cgs + cap - 1) / cap;
@@ -470,7 +471,7 @@ static DwPlan dw_plan(int C, int es, bool half_rows, int out_h, int out_w) {
   d.PPB = 256 / d.CGB;
   d.spp = 256 / (2 * d.CGB);
   d.TH = half_rows ? 4 : 8;
-  d.TW = half_rows ? 8 : 16;     // measured: 8x16 tiles beat 8x8 by 10-25 % (less halo, fewer blocks), 4x8 is best for stride 2
+  d.TW = half_rows ? 8 : wide;   // measured: 8x16 tiles beat 8x8 by 10-25 % (less halo, fewer blocks), 4x8 is best for stride 2
   if (d.TH > out_h) d.TH = out_h;
   if (d.TW > out_w) d.TW = out_w;
   d.segw = (d.TW + 3) / 4;
@@ -486,8 +487,9 @@ static DwPlan dw_plan(int C, int es, bool half_rows, int out_h, int out_w) {
 // into LDS as float [PH][PW][CGB][8].  Thread = (pixel lane, column group); fetch() issues all global
 // loads, commit() applies the view and writes LDS, so a caller can keep the loads of the next tile
 // in flight while it works on the current one.
-template <typename T, int NV = kDwFillNV>
+template <typename T>
 struct DwPatch {
+  enum { NV = DwFill<T>::NV };
   Raw<T> raw[NV];
   unsigned ok;
   // image n is at most 2^31 elements: offsets inside it are 32-bit, products of 24-bit factors
@@ -568,17 +570,19 @@ __device__ __forceinline__ void dw_stage_weights(float* wl, const T* __restrict_
   }
 }
 
-// out[ho][wo] = sum_{ky,kx} src[ho*S-1+ky][wo*S-1+kx] * w[ky][kx]   (FLIP: w[2-ky][2-kx], which for
-// S = 1 is the data gradient with src = dz)
+// out[ho][wo] = sum_{ky,kx} src[ho*S-1+ky][wo*S-1+kx] * w[ky][kx]
 // RL = pixels per run: four at stride 1; two at stride 2, where a run of four keeps 9 patch vectors and 4 sums live
 // (111 registers, four resident blocks per CU) and a 4 x 8 tile has work for only 96 of the 256 threads
 // STATS (layers with at most kMaxPartials tiles): the block also leaves per-channel sums over its stored outputs, one
-// partial per tile ([tile][2][C]).  1: the sum and the sum of squares (what bn_stats would compute in a pass of its
-// own).  2, for the data gradient: the output is the gradient dA of the BatchNorm + activation in front of this layer,
-// whose conv output zp sits at the same positions; the sums are those of bn_bwd_reduce (dY = dA where the activation
-// passes, sum of dY and of dY * zp), so that BatchNorm's backward starts at its finalize.
+// partial per tile ([tile][2][C]): the sum and the sum of squares (what bn_stats would compute in a pass of its own).
 template <typename T> __device__ __forceinline__ float4 round4(float4 v) {
   return make_float4(round_to<T>(v.x), round_to<T>(v.y), round_to<T>(v.z), round_to<T>(v.w));
+}
+// four of the eight channels of a raw vector
+__device__ __forceinline__ float4 raw_half(const Raw<float>& r, int half) { return half ? r.b : r.a; }
+__device__ __forceinline__ float4 raw_half(const Raw<bf16_t>& r, int half) {
+  const uint32_t lo = half ? r.a.z : r.a.x, hi = half ? r.a.w : r.a.y;
+  return make_float4(__uint_as_float(lo << 16), __uint_as_float(lo & 0xffff0000u), __uint_as_float(hi << 16), __uint_as_float(hi & 0xffff0000u));
 }
 struct DwPrev { const void* z; const float* scale; const float* shift; int act; };
 
@@ -599,19 +603,17 @@ __device__ __forceinline__ void dw_leave_sums(float4 s1, float4 s2, bool worker,
     partial[(size_t)(e >> 2) * C + c] = t;
   }
 }
-template <typename T, int S, bool FLIP, int STATS = 0, int RL = (S == 2 ? 2 : 4)>
+template <typename T, int S, bool STATS = false, int RL = (S == 2 ? 2 : 4)>
 __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ w, DwPlan d, int Hin, int Win, int Hout,
-                                                 int Wout, int C, T* __restrict__ out, float* __restrict__ stats = nullptr,
-                                                 DwPrev prev = DwPrev{nullptr, nullptr, nullptr, 0}) {
+                                                 int Wout, int C, T* __restrict__ out, float* __restrict__ stats = nullptr) {
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  if (FLIP) __builtin_amdgcn_s_setprio(3);   // data-gradient chain: ahead of the weight-gradient stream's waves
   T* patch = reinterpret_cast<T*>(smem_raw);
   float* wl = reinterpret_cast<float*>(smem_raw + (((size_t)d.PH * d.PW * d.CGB * 8 * sizeof(T) + 15) / 16 * 16));
   const int lb = xcd_logical_block();
   const int slab = lb % d.nslab, tile = lb / d.nslab;     // the slabs of a tile run together: they share cache lines when a slab is not 128 bytes
   const int tw = tile % d.tiles_w, th = (tile / d.tiles_w) % d.tiles_h, n = tile / (d.tiles_w * d.tiles_h);
   const int ho0 = th * d.TH, wo0 = tw * d.TW, cg0 = slab * d.CGB;
-  DwPatch<T, DwFill<T>::CONV> lp;
+  DwPatch<T> lp;
   lp.fetch(reinterpret_cast<const T*>(in.z), n, ho0 * S - 1, wo0 * S - 1, d, Hin, Win, C, cg0);
   dw_stage_weights(wl, w, C, cg0, d.CGB, d.m_cgb);
   lp.commit(patch, in, d, cg0);
@@ -622,25 +624,13 @@ __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ 
   if (!STATS && !worker) return;
   float4 wr[9];
 #pragma unroll
-  for (int t = 0; t < 9; ++t) wr[t] = worker ? ld4(wl + (size_t)(FLIP ? 8 - t : t) * d.CGB * 8 + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int t = 0; t < 9; ++t) wr[t] = worker ? ld4(wl + (size_t)t * d.CGB * 8 + c4) : make_float4(0.f, 0.f, 0.f, 0.f);
   const int vs = d.CGB * 8;                       // floats per patch pixel
   float4 s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = make_float4(0.f, 0.f, 0.f, 0.f);
-  float4 psc = make_float4(0.f, 0.f, 0.f, 0.f), psh = psc;
-  if (STATS == 2 && worker) { psc = ld4(prev.scale + gc); psh = ld4(prev.shift + gc); }
-  const float plo = act_lo(prev.act), phi = act_hi(prev.act);
   for (int sg = worker ? seg0 : d.nseg; sg < d.nseg; sg += d.spp) {
     const int hl = dw_div(sg, d.m_segw), wl0 = (sg - hl * d.segw) * RL;
     const int ho = ho0 + hl;
     if (ho >= Hout) continue;
-    float4 zp[RL];
-    if (STATS == 2) {                             // requested before the taps are worked off, used after the stores
-      const T* zrow = reinterpret_cast<const T*>(prev.z) + ((size_t)n * Hout + ho) * Wout * C + gc;
-#pragma unroll
-      for (int o = 0; o < RL; ++o) {              // a pixel past the row's end reads the row's first pixel and is not used
-        const int wq = wo0 + wl0 + o;
-        zp[o] = load4(zrow + (size_t)(wq < Wout ? wq : 0) * C);
-      }
-    }
     float4 acc[RL];
 #pragma unroll
     for (int o = 0; o < RL; ++o) acc[o] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -661,16 +651,9 @@ __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ 
       if (wo0 + wl0 + o < Wout) {
         store4(dst + (size_t)o * C, acc[o]);
         if (STATS) {                              // sums over the values as stored
-          float4 r = make_float4(round_to<T>(acc[o].x), round_to<T>(acc[o].y), round_to<T>(acc[o].z), round_to<T>(acc[o].w));
-          float4 f = r;
-          if (STATS == 2) {
-            const float4 y = fma4(zp[o], psc, psh);
-            r.x = (y.x > plo && y.x < phi) ? r.x : 0.f; r.y = (y.y > plo && y.y < phi) ? r.y : 0.f;
-            r.z = (y.z > plo && y.z < phi) ? r.z : 0.f; r.w = (y.w > plo && y.w < phi) ? r.w : 0.f;
-            f = zp[o];
-          }
+          const float4 r = round4<T>(acc[o]);
           s1.x += r.x; s1.y += r.y; s1.z += r.z; s1.w += r.w;
-          s2 = fma4(r, f, s2);
+          s2 = fma4(r, r, s2);
         }
       }
   }
@@ -684,10 +667,10 @@ __global__ __launch_bounds__(256) void dw_conv_k(View in, const T* __restrict__ 
 static size_t dw_patch_bytes(const DwPlan& d, int es) { return (((size_t)d.PH * d.PW * d.CGB * 8 * es) + 15) / 16 * 16; }
 static size_t dw_lds_bytes(const DwPlan& d, int es) { return dw_patch_bytes(d, es) + (size_t)9 * d.CGB * 8 * 4; }
 
-// staging is unrolled for kDwFillNV passes; dw_div needs small divisors.  The plans of every shape a model can
+// staging is unrolled for `fill` passes; dw_div needs small divisors.  The plans of every shape a model can
 // describe satisfy this; if one ever does not, the launch is skipped and the stage call reports it.
-static bool dw_check_plan(DwPlan& d, int fill = kDwFillNV, int segs = kDwSegs) {
-  if (d.PH * d.PW > fill * d.PPB || d.PW > 63 || d.CGB > 16 || d.segw > 32 || d.nseg > segs * d.spp) {
+static bool dw_check_plan(DwPlan& d, int fill, int rounds) {
+  if (d.PH * d.PW > fill * d.PPB || d.PW > 63 || d.CGB > 16 || d.segw > 32 || d.nseg > rounds * d.spp) {
     launch_plan_failed("depthwise tile plan outside the kernels' limits");
     return false;
   }
@@ -712,7 +695,7 @@ void dw_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, 
   d.PH = (d.TH - 1) * s + 3;
   d.PW = (d.segw * run - 1) * s + 3;             // runs are whole: the patch covers the rounded-up tile width
   d.ntiles = g.N * d.tiles_h * d.tiles_w;
-  if (!dw_check_plan(d, dt == 0 ? DwFill<float>::CONV : DwFill<bf16_t>::CONV)) return;
+  if (!dw_check_plan(d, dt == 0 ? DwFill<float>::NV : DwFill<bf16_t>::NV, 2)) return;
   View v{in.z, in.scale, in.shift, in.act};
   size_t total = (size_t)g.N * g.Hout * g.Wout;
   KScope ks(st, "dw_fwd", ((double)g.N * g.Hin * g.Win * g.Cout + (double)total * g.Cout) * es, 18.0 * total * g.Cout,
@@ -725,20 +708,20 @@ void dw_fwd(int dt, hipStream_t st, HView in, const void* w, const ConvGeom& g, 
     const size_t red = (size_t)d.spp * 2 * d.CGB * 8 * sizeof(float);
     if (lds < red) lds = red;
     if (s == 1) {
-      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 1, false, 1>), dim3(grid), dim3(256), lds, st, v, (const T*)w, d,
+      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 1, true>), dim3(grid), dim3(256), lds, st, v, (const T*)w, d,
                                           g.Hin, g.Win, g.Hout, g.Wout, g.Cout, (T*)z, stats));
     } else {
-      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 2, false, 1>), dim3(grid), dim3(256), lds, st, v, (const T*)w, d,
+      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 2, true>), dim3(grid), dim3(256), lds, st, v, (const T*)w, d,
                                           g.Hin, g.Win, g.Hout, g.Wout, g.Cout, (T*)z, stats));
     }
     *P_out = d.ntiles;
     return;
   }
   if (s == 1) {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 1, false>), dim3(grid), dim3(256), dw_lds_bytes(d, es), st, v, (const T*)w, d,
+    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 1>), dim3(grid), dim3(256), dw_lds_bytes(d, es), st, v, (const T*)w, d,
                                         g.Hin, g.Win, g.Hout, g.Wout, g.Cout, (T*)z));
   } else {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 2, false>), dim3(grid), dim3(256), dw_lds_bytes(d, es), st, v, (const T*)w, d,
+    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 2>), dim3(grid), dim3(256), dw_lds_bytes(d, es), st, v, (const T*)w, d,
                                         g.Hin, g.Win, g.Hout, g.Wout, g.Cout, (T*)z));
   }
 }
@@ -1122,153 +1105,249 @@ void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, con
   }
 }
 
-// Stride-2 data gradient over 8 x 16 input tiles: dIn[h][w] = sum over taps (i, j) with h+1-i and w+1-j
-// even of dz[(h+1-i)/2][(w+1-j)/2] * w[i][j].  A run of 4 input pixels starting at an even column
-// touches three dz columns per dz row.
-template <typename T>
-__global__ __launch_bounds__(256) void dw_dgrad_s2_k(const T* __restrict__ dz, const T* __restrict__ w, DwPlan d, int Hin,
-                                                     int Win, int Hout, int Wout, int C, T* __restrict__ dIn) {
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  T* patch = reinterpret_cast<T*>(smem_raw);
-  float* wl = reinterpret_cast<float*>(smem_raw + (((size_t)d.PH * d.PW * d.CGB * 8 * sizeof(T) + 15) / 16 * 16));
-  const int lb = xcd_logical_block();
-  const int slab = lb % d.nslab, tile = lb / d.nslab;     // the slabs of a tile run together: they share cache lines when a slab is not 128 bytes
-  const int tw = tile % d.tiles_w, th = (tile / d.tiles_w) % d.tiles_h, n = tile / (d.tiles_w * d.tiles_h);
-  const int h0 = th * d.TH, w0 = tw * d.TW, cg0 = slab * d.CGB;       // tile origin, even
-  __builtin_amdgcn_s_setprio(3);             // data-gradient chain: ahead of the weight-gradient stream's waves
-  const int ho_lo = h0 / 2, wo_lo = w0 / 2;
-  DwPatch<T, DwFill<T>::DGRAD_S2> lp;
-  View none{nullptr, nullptr, nullptr, 0};
-  lp.fetch(dz, n, ho_lo, wo_lo, d, Hout, Wout, C, cg0);
-  dw_stage_weights(wl, w, C, cg0, d.CGB, d.m_cgb);
-  lp.commit(patch, none, d, cg0);
-  __syncthreads();
-  const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB;
-  const int c4 = cq * 4, gc = cg0 * 8 + c4;
-  if (seg0 >= d.spp || gc >= C) return;
-  float4 wr[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) wr[t] = ld4(wl + (size_t)t * d.CGB * 8 + c4);
-  const int vs = d.CGB * 8;
-  for (int sg = seg0; sg < d.nseg; sg += d.spp) {
-    const int hl = dw_div(sg, d.m_segw), wl0 = (sg - hl * d.segw) * 4;
-    const int h = h0 + hl;
-    if (h >= Hin) continue;
-    float4 acc[4];
-#pragma unroll
-    for (int o = 0; o < 4; ++o) acc[o] = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const int hn = h + 1 - i;
-      if (hn & 1) continue;                        // also skips hn = -1
-      const T* row = patch + (size_t)((hn / 2 - ho_lo) * d.PW + wl0 / 2) * vs + c4;
-      const float4 d0 = load4(row), d1 = load4(row + vs), d2 = load4(row + 2 * (size_t)vs);
-      // pixel 0, 2 (even columns): tap j = 1; pixel 1, 3 (odd): taps j = 0 (next dz column) and j = 2
-      acc[0] = fma4(d0, wr[i * 3 + 1], acc[0]);
-      acc[1] = fma4(d1, wr[i * 3 + 0], acc[1]);
-      acc[1] = fma4(d0, wr[i * 3 + 2], acc[1]);
-      acc[2] = fma4(d1, wr[i * 3 + 1], acc[2]);
-      acc[3] = fma4(d2, wr[i * 3 + 0], acc[3]);
-      acc[3] = fma4(d1, wr[i * 3 + 2], acc[3]);
-    }
-    T* dst = dIn + (((size_t)n * Hin + h) * Win + w0 + wl0) * C + gc;
-#pragma unroll
-    for (int o = 0; o < 4; ++o)
-      if (w0 + wl0 + o < Win) store4(dst + (size_t)o * C, acc[o]);
-  }
-}
+// ---- the whole backward of a depthwise layer in one pass ---------------------------------------------------------
+// From the gradient dA of the layer's activated output (FORM: dz = k1 * gated dA + k2 * z + k3 is formed on the way into LDS and never written; else dz
+// itself): data gradient, weight gradient (gw[block][9][C]: dW[tap] = sum over input pixels p of dz[the output that sees p at that tap] *
+// activation[p]) and, where the input is the view prev of a raw output, the backward sums of that BatchNorm (as bn_bwd_reduce leaves them,
+// sums[block][2][C]).  As passes of their own these move the expanded tensors nine times, here it is four and the halo.  A block takes `per` tiles of
+// 8 x 16 pixels (bfloat16 at stride 1: 8 x 8) of 128 bytes of channels in a row, so that there are no more partials than kMaxPartials.  A thread owns four channels; stride 1: runs of four pixels
+// with the six dz under each row of taps, in LDS in fp32 (converted once instead of for up to nine taps); stride 2: quads of 2 x 2 pixels, which
+// four dz values reach (nine products, no parity to branch on).  The weights stay in LDS: in registers, one block less would fit a CU.
+// Bound by memory at stride 2 (112x112x144, batch 64, bfloat16: 126 us, 4.7 TB/s; its passes were 18 + 48 + 106 + 70) and by vector instructions at stride 1,
+// some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.57 ms a step; their data
+// and weight gradients were 1.80 and the passes for dz and the sums another 0.9, on two streams (a step 7.27 -> 6.79 ms; 224x224 fp32 3.51 -> 3.21).
+// bfloat16 tiles of 8 x 16 at stride 1: 207 registers, two blocks to a CU, or scratch with three: 1.12 and 1.24 ms for the stride-1 layers, 1.03 so.
+struct DwBwdArgs {
+  const void *dA, *w;       // dA: dz if nothing is to be formed
+  View own;                 // the layer's own output (FORM)
+  BnPending pend;           // its backward sums, if the blocks finish them (partial != nullptr), else coef[3][C]
+  const float* coef;
+  float *g_gamma, *g_beta;
+  DwPlan d;
+  int Hin, Win, Hout, Wout, C, per;
+  void* dIn;                // may be nullptr, as sums
+  float *sums, *gw;
+  DwPrev prev;              // scale == nullptr: the input is stored as it is
+};
+__device__ __forceinline__ void keep_here(float4& v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); }
+template <typename T, int S> struct DwBwd {
+  enum { F32 = sizeof(T) == 4, TW = S == 1 && !F32 ? 8 : 16,              // tiles of 8 x TW
+         NR = S == 1 || F32 ? 1 : 2,                                             // rounds of a tile's runs or quads
+         VS = F32 ? 32 : 64, PH = S == 1 ? 10 : 5, PW = S == 1 ? TW + 2 : 9 };          // the patch has its largest size whatever the tile: offsets are constants
+  typedef typename std::conditional<S == 1, float, T>::type P;                                  // patch elements
+  enum { PATCH = PH * PW * VS * sizeof(P) > kSlabSumsBytes ? PH * PW * VS * sizeof(P) : kSlabSumsBytes, LDS = PATCH + 9 * VS * 4 };
+};
+template <typename T, int S, bool FORM, int NV>
+__global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // three blocks to a CU: 168 registers
 
-// The whole backward of a stride-2 depthwise layer behind a BatchNorm + activation (prev, raw output zp at the data gradient's positions) in one pass: data
-// gradient, that BatchNorm's backward sums (as dw_conv_k leaves them with STATS = 2, sums[block][2][C]) and the weight gradient's partial sums
-// (gw[block][9][C]: dW[tap] = sum over pixels p of dz[the output that sees p at that tap] * activation[p]).  All three want the same dz, the last two the
-// same zp, which as passes of their own read it twice more.  A thread takes 2 x 2 pixels, which four dz values reach (nine products, no
-// parity to branch on); a block takes `per` tiles of 8 x 16 in a row, the next tile's dz on its way meanwhile, so that there are no more partials than
-// kMaxPartials.  Bound by memory.
-template <typename T>
-__global__ __launch_bounds__(256) void dw_bwd_s2_k(const T* __restrict__ dz, const T* __restrict__ w, DwPlan d, int Hin, int Win, int Hout, int Wout, int C,
-                                                   T* __restrict__ dIn, int per, float* __restrict__ sums, DwPrev prev, float* __restrict__ gw) {
-  constexpr int NR = sizeof(T) == 4 ? 1 : 2;          // rounds of a tile's at most 32 pixel quads: at least 16 lanes to a channel quad, fp32 32
+  typedef DwBwd<T, S> X;
+  typedef typename X::P PT;
+  constexpr int NR = X::NR, VS = X::VS, PW = X::PW;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  const int patch_bytes = (d.PH * d.PW * d.CGB * 8 * (int)sizeof(T) + 15) / 16 * 16;
-  float* wl = reinterpret_cast<float*>(smem_raw + 2 * patch_bytes);
-  const int lb = xcd_logical_block();
-  const int slab = lb % d.nslab, part = lb / d.nslab, cg0 = slab * d.CGB, t0 = part * per, t1 = min(t0 + per, d.ntiles);
+  __shared__ __attribute__((aligned(16))) float vec[FORM ? 5 : 1][64], prv[2][64];
   __builtin_amdgcn_s_setprio(3);                      // data-gradient chain: ahead of the weight-gradient stream's waves
+  const DwPlan& d = p.d;
+  const int C = p.C, Hin = p.Hin, Win = p.Win;
+  PT* const patch = reinterpret_cast<PT*>(smem_raw);
+  float* const wl = reinterpret_cast<float*>(smem_raw + X::PATCH);         // [9][VS]
+  const int lb = xcd_logical_block();
+  const int slab = lb % d.nslab, part = lb / d.nslab, cg0 = slab * d.CGB, t0 = part * p.per, t1 = min(t0 + p.per, d.ntiles);
   const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB, c4 = cq * 4, gc = cg0 * 8 + c4;
-  const bool worker = seg0 < d.spp && gc < C;
-  const int vs = d.CGB * 8;
-  int tw = t0 % d.tiles_w, th = t0 / d.tiles_w % d.tiles_h, n = t0 / (d.tiles_w * d.tiles_h);
-  DwPatch<T, DwFill<T>::DGRAD_S2> lp;
-  const View none{nullptr, nullptr, nullptr, 0};
-  lp.fetch(dz, n, th * d.TH / 2, tw * d.TW / 2, d, Hout, Wout, C, cg0);
-  dw_stage_weights(wl, w, C, cg0, d.CGB, d.m_cgb);
-  lp.commit(reinterpret_cast<T*>(smem_raw), none, d, cg0);
-  float4 aw[9], s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1, psc = s1, psh = s1;
+  const int nc = min(C - cg0 * 8, d.CGB * 8);
+  const bool worker = seg0 < d.spp && gc < C, viewed = p.prev.scale != nullptr;
+  T w0[(9 * VS + 255) / 256];
+#pragma unroll
+  for (int q = 0; q < (9 * VS + 255) / 256; ++q) {
+    const int i = threadIdx.x + q * 256, t = i / VS, c = i - t * VS;
+    w0[q] = reinterpret_cast<const T*>(p.w)[c < nc && t < 9 ? (size_t)(cg0 * 8 + c) * 9 + t : 0];
+  }
+  if (viewed && (int)threadIdx.x < nc) { prv[0][threadIdx.x] = p.prev.scale[cg0 * 8 + threadIdx.x]; prv[1][threadIdx.x] = p.prev.shift[cg0 * 8 + threadIdx.x]; }
+  if (FORM) {
+    const int t = threadIdx.x, f = cg0 * 8 + (t < nc ? t : 0);
+    const float osc = p.own.scale[f], osh = p.own.shift[f];
+    if (p.pend.partial) {
+      const bool write = part == 0 && t < nc;
+      float g = p.pend.gamma[f], mu = p.pend.mean[f], is = p.pend.invstd[f], gg = 0.f, gb = 0.f;
+      if (write) { gg = p.g_gamma[f]; gb = p.g_beta[f]; }
+      const double inv_M = early_inverse((double)p.pend.M);
+      double s0, s1;
+      slab_sums(p.pend.partial, p.pend.P, C, cg0 * 8, nc, reinterpret_cast<double*>(smem_raw), s0, s1);
+      asm volatile("" : "+v"(g), "+v"(mu), "+v"(is), "+v"(gg), "+v"(gb));
+      if (t < nc) {
+        const BwdChannel b = backward_channel(s0, s1, g, mu, is, inv_M);
+        vec[FORM ? 2 : 0][t] = b.k1; vec[FORM ? 3 : 0][t] = b.k2; vec[FORM ? 4 : 0][t] = b.k3;
+        if (write) { p.g_gamma[f] = gg + b.dgamma; p.g_beta[f] = gb + b.dbeta; }
+      }
+    } else if (t < nc) {
+#pragma unroll
+      for (int q = 0; q < 3; ++q) vec[FORM ? 2 + q : 0][t] = p.coef[q * C + f];
+    }
+    if (t < nc) { vec[0][t] = osc; vec[FORM ? 1 : 0][t] = osh; }
+  }
+#pragma unroll
+  for (int q = 0; q < (9 * VS + 255) / 256; ++q) {
+    const int i = threadIdx.x + q * 256, t = i / VS, c = i - t * VS;
+    if (t < 9) wl[i] = c < nc ? to_f32(w0[q]) : 0.f;
+  }
+  __syncthreads();
+  float4 aw[9], s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1;
 #pragma unroll
   for (int t = 0; t < 9; ++t) aw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (worker) { psc = ld4(prev.scale + gc); psh = ld4(prev.shift + gc); }
-  const float plo = act_lo(prev.act), phi = act_hi(prev.act);
-  const T* Z = reinterpret_cast<const T*>(prev.z);
-  int hq[NR], wq[NR];                                 // this thread's quads in a tile
-  bool has[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const int sg = seg0 + r * d.spp;
-    has[r] = worker && sg < d.nseg;
-    hq[r] = dw_div(has[r] ? sg : 0, d.m_segw);
-    wq[r] = (has[r] ? sg : 0) - hq[r] * d.segw;
-  }
-  __syncthreads();
+  const float plo = act_lo(p.prev.act), phi = act_hi(p.prev.act), olo = act_lo(p.own.act), ohi = act_hi(p.own.act);
+  // staging: thread = (pixel lane, column group)
+  const int pl = dw_div(threadIdx.x, d.m_cgb), cg = threadIdx.x - pl * d.CGB;
+  const bool stager = pl < d.PPB && cg0 + cg < C / 8;
+  const int dph = dw_div(d.PPB, d.m_pw), dpw = d.PPB - dph * d.PW;
+  const int ph_first = dw_div(pl, d.m_pw), pw_first = pl - ph_first * d.PW;
+  int tw = t0 % d.tiles_w, th = t0 / d.tiles_w % d.tiles_h, n = t0 / (d.tiles_w * d.tiles_h);
   for (int tile = t0; tile < t1; ++tile) {
-    const int h0 = th * d.TH, w0 = tw * d.TW;
-    const size_t img = (size_t)n * Hin * Win * C + gc;
-    Raw4<T> zp[NR][4];
+    const int h0 = th * d.TH, w0 = tw * d.TW, ph_lo = S == 1 ? h0 - 1 : h0 / 2, pw_lo = S == 1 ? w0 - 1 : w0 / 2;
+    // Where a thread works is decoded again for every tile: kept over the loop, the compiler holds some eighty registers of addresses
+    int ph0 = ph_first, pw0 = pw_first, sg0 = seg0;
+    asm volatile("" : "+v"(ph0), "+v"(pw0), "+v"(sg0));
+    // the patch and the input under it, all requested together and unconditionally (outside: the image's first pixel, not used)
+    Raw<T> ra[NV], rz[FORM ? NV : 1];
+    unsigned ok = 0;
+    {
+      const size_t img = (size_t)n * p.Hout * p.Wout * C + (stager ? (cg0 + cg) * 8 : 0);
+      const T* A = reinterpret_cast<const T*>(p.dA) + img;
+      const T* O = reinterpret_cast<const T*>(p.own.z) + img;
+      unsigned off[NV];
+      int ph = ph0, pw = pw0;
 #pragma unroll
-    for (int r = 0; r < NR; ++r)
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {                   // a pixel outside the image reads its first and is not used
-        const int h = h0 + 2 * hq[r] + (o >> 1), x = w0 + 2 * wq[r] + (o & 1);
-        raw4_load(zp[r][o], Z + (worker ? img : 0) + (has[r] && h < Hin && x < Win ? __umul24(__umul24(h, Win) + x, C) : 0u));
+      for (int q = 0; q < NV; ++q) {
+        const int h = ph_lo + ph, x = pw_lo + pw;
+        const bool in = stager && ph < d.PH && (unsigned)h < (unsigned)p.Hout && (unsigned)x < (unsigned)p.Wout;
+        off[q] = in ? __umul24(__umul24(h, p.Wout) + x, C) : 0u;
+        ok |= (in ? 1u : 0u) << q;
+        ph += dph; pw += dpw;
+        if (pw >= d.PW) { pw -= d.PW; ++ph; }
       }
-    if (++tw == d.tiles_w) { tw = 0; if (++th == d.tiles_h) { th = 0; ++n; } }
-    if (tile + 1 < t1) lp.fetch(dz, n, th * d.TH / 2, tw * d.TW / 2, d, Hout, Wout, C, cg0);
-    const T* patch = reinterpret_cast<const T*>(smem_raw + ((tile - t0) & 1) * patch_bytes);
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      if (!has[r]) continue;
-      const T* q = patch + (hq[r] * d.PW + wq[r]) * vs + c4;
-      const float4 d00 = load4(q), d01 = load4(q + vs), d10 = load4(q + d.PW * vs), d11 = load4(q + d.PW * vs + vs);
-      T* const out = dIn + img;
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        const int h = h0 + 2 * hq[r] + (o >> 1), x = w0 + 2 * wq[r] + (o & 1);
-        const bool in = h < Hin && x < Win;
-        const float4 z = raw4_unpack(zp[r][o]), y = fma4(z, psc, psh);
-        float4 a = round4<T>(make_float4(clamp_act(y.x, plo, phi), clamp_act(y.y, plo, phi), clamp_act(y.z, plo, phi), clamp_act(y.w, plo, phi)));
-        if (!in) a = make_float4(0.f, 0.f, 0.f, 0.f);
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        auto tap = [&](const int t, const float4 g) __attribute__((always_inline)) {
-          v = fma4(g, ld4(wl + t * vs + c4), v);
-          aw[t] = fma4(g, a, aw[t]);
-        };
-        if (o == 0) { tap(4, d00); }
-        else if (o == 1) { tap(3, d01); tap(5, d00); }
-        else if (o == 2) { tap(1, d10); tap(7, d00); }
-        else { tap(0, d11); tap(2, d10); tap(6, d01); tap(8, d00); }
-        if (!in) continue;
-        store4(out + __umul24(__umul24(h, Win) + x, C), v);
-        const float4 g = round4<T>(v);                // sums over the values as stored
-        const float4 p = make_float4(y.x > plo && y.x < phi ? g.x : 0.f, y.y > plo && y.y < phi ? g.y : 0.f, y.z > plo && y.z < phi ? g.z : 0.f,
-                                     y.w > plo && y.w < phi ? g.w : 0.f);
-        s1.x += p.x; s1.y += p.y; s1.z += p.z; s1.w += p.w;
-        s2 = fma4(p, z, s2);
+      for (int q = 0; q < NV; ++q) {
+        raw_load(ra[q], A + off[q]);
+        if (FORM) raw_load(rz[FORM ? q : 0], O + off[q]);
       }
     }
-    if (tile + 1 < t1) lp.commit(reinterpret_cast<T*>(smem_raw + ((tile - t0 + 1) & 1) * patch_bytes), none, d, cg0);
+    // nothing of the tile or its patch lies outside the image: a branch for the wavefront instead of a mask for every value
+    const bool all_in = h0 + d.TH <= Hin && w0 + d.TW <= Win && d.TW % 4 == 0 && d.TH % 2 == 0 && ph_lo >= 0 && pw_lo >= 0 && ph_lo + d.PH <= p.Hout && pw_lo + d.PW <= p.Wout;
+    const size_t img = (size_t)n * Hin * Win * C + (worker ? gc : 0);
+    const T* const Z = reinterpret_cast<const T*>(p.prev.z) + img;
+    T* const out = reinterpret_cast<T*>(p.dIn) + img;
+    Raw4<T> zp[NR][4];
+    int lds[NR];                                      // this thread's runs or quads in the tile: where their dz lies, negative: none
+    unsigned at[NR];                                  // pixel of the first
+    unsigned inside = 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int sg = sg0 + r * d.spp;
+      const bool has = worker && sg < d.nseg;
+      const int hl = dw_div(has ? sg : 0, d.m_segw), wl0 = (has ? sg : 0) - hl * d.segw, h = h0 + hl * S, x = w0 + wl0 * (S == 1 ? 4 : 2);
+      lds[r] = has ? (hl * PW + wl0 * (S == 1 ? 4 : 1)) * VS + c4 : -1;
+      at[r] = __umul24(h, Win) + x;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        const bool in = has && h + (S == 1 ? 0 : o >> 1) < Hin && x + (S == 1 ? o : o & 1) < Win;
+        inside |= (in ? 1u : 0u) << (4 * r + o);
+        raw4_load(zp[r][o], Z + (in ? __umul24(at[r] + (S == 1 ? o : (o >> 1) * Win + (o & 1)), C) : 0u));
+      }
+    }
+    if (tile > t0) __syncthreads();                   // the tile before has been read
+    asm volatile("" ::: "memory");                    // the coefficients come from LDS again, not out of forty registers
+    if (pl < d.PPB) {
+#pragma unroll
+      for (int half = 0; half < 2; ++half) {          // four channels at a time: their five coefficients are twenty registers
+        const int c = cg * 8 + half * 4;
+        float4 k1, k2, k3, sc, sh;
+        if (FORM) { sc = ld4(vec[0] + c); sh = ld4(vec[FORM ? 1 : 0] + c); k1 = ld4(vec[FORM ? 2 : 0] + c); k2 = ld4(vec[FORM ? 3 : 0] + c); k3 = ld4(vec[FORM ? 4 : 0] + c); }
+        int ph = ph0, pw = pw0;
+#pragma unroll
+        for (int q = 0; q < NV; ++q) {
+          float4 v = raw_half(ra[q], half);
+          if (FORM) {
+            const float4 z = raw_half(rz[FORM ? q : 0], half), y = fma4(z, sc, sh);
+            v = make_float4(y.x > olo && y.x < ohi ? v.x : 0.f, y.y > olo && y.y < ohi ? v.y : 0.f, y.z > olo && y.z < ohi ? v.z : 0.f, y.w > olo && y.w < ohi ? v.w : 0.f);
+            v = round4<T>(fma4(k1, v, fma4(k2, z, k3)));  // as a stored dz would read back
+          }
+          if (!all_in && !(ok & (1u << q))) v = make_float4(0.f, 0.f, 0.f, 0.f);
+          if (ph < d.PH) store4(patch + (ph * PW + pw) * VS + c, v);
+          ph += dph; pw += dpw;
+          if (pw >= d.PW) { pw -= d.PW; ++ph; }
+        }
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
     __syncthreads();
+    if (++tw == d.tiles_w) { tw = 0; if (++th == d.tiles_h) { th = 0; ++n; } }
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      // the rounds one behind the other, each with its own reads
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+      if (lds[r] < 0) continue;
+      const PT* const q = patch + lds[r];
+      const float* const wt = wl + c4;
+      const float4 psc = ld4(prv[0] + c4), psh = ld4(prv[1] + c4);       // not used where the input is no view
+      auto input = [&](const int o) __attribute__((always_inline)) {
+        const float4 z = raw4_unpack(zp[r][o]), y = fma4(z, psc, psh);
+        float4 a = !viewed ? z : round4<T>(make_float4(clamp_act(y.x, plo, phi), clamp_act(y.y, plo, phi), clamp_act(y.z, plo, phi), clamp_act(y.w, plo, phi)));
+        if (!all_in && !(inside >> (4 * r + o) & 1u)) a = make_float4(0.f, 0.f, 0.f, 0.f);
+        return a;
+      };
+      auto leave = [&](const int o, const float4 v) __attribute__((always_inline)) {
+        if (!(inside >> (4 * r + o) & 1u)) return;
+        if (p.dIn) store4(out + __umul24(at[r] + (S == 1 ? o : (o >> 1) * Win + (o & 1)), C), v);
+        const float4 g = round4<T>(v), z = raw4_unpack(zp[r][o]), y = fma4(z, psc, psh);             // sums over the values as stored
+        const float4 t = make_float4(y.x > plo && y.x < phi ? g.x : 0.f, y.y > plo && y.y < phi ? g.y : 0.f, y.z > plo && y.z < phi ? g.z : 0.f,
+                                     y.w > plo && y.w < phi ? g.w : 0.f);
+        s1.x += t.x; s1.y += t.y; s1.z += t.z; s1.w += t.w;
+        s2 = fma4(t, z, s2);
+      };
+      if constexpr (S == 1) {
+        float4 v[4], a[4];
+#pragma unroll
+        for (int o = 0; o < 4; ++o) { a[o] = input(o); v[o] = make_float4(0.f, 0.f, 0.f, 0.f); }
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {                 // row k of the patch under the run: taps 2 - k
+          __builtin_amdgcn_sched_barrier(0);
+          float4 g[6];
+#pragma unroll
+          for (int x = 0; x < 6; ++x) g[x] = load4(q + (k * PW + x) * VS);
+#pragma unroll
+          for (int j = 0; j < 3; ++j) {
+            const int t = (2 - k) * 3 + j;
+            const float4 w4 = ld4(wt + t * VS);
+#pragma unroll
+            for (int o = 0; o < 4; ++o) { v[o] = fma4(g[o + 2 - j], w4, v[o]); aw[t] = fma4(g[o + 2 - j], a[o], aw[t]); }
+            keep_here(aw[t]);
+          }
+          // the products of a row of taps stay here: moved behind the branches of the results, all 27 vectors of LDS would be held until there
+#pragma unroll
+          for (int o = 0; o < 4; ++o) keep_here(v[o]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) leave(o, v[o]);
+      } else {
+        const float4 d00 = load4(q), d01 = load4(q + VS), d10 = load4(q + PW * VS), d11 = load4(q + (PW + 1) * VS);
+#pragma unroll
+        for (int o = 0; o < 4; ++o) {
+          const float4 a = input(o);
+          float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+          auto tap = [&](const int t, const float4 g) __attribute__((always_inline)) { v = fma4(g, ld4(wt + t * VS), v); aw[t] = fma4(g, a, aw[t]); };
+          if (o == 0) { tap(4, d00); }
+          else if (o == 1) { tap(3, d01); tap(5, d00); }
+          else if (o == 2) { tap(1, d10); tap(7, d00); }
+          else { tap(0, d11); tap(2, d10); tap(6, d01); tap(8, d00); }
+          leave(o, v);
+        }
+      }
+    }
   }
   float* red = reinterpret_cast<float*>(smem_raw);
-  dw_leave_sums(s1, s2, worker, seg0, cq, QB, cg0, C, d.spp, red, sums + (size_t)part * 2 * C);
+  __syncthreads();
+  if (p.sums) dw_leave_sums(s1, s2, worker, seg0, cq, QB, cg0, C, d.spp, red, p.sums + (size_t)part * 2 * C);
   // three taps at a time: [spp][QB][12]
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -1282,873 +1361,72 @@ __global__ __launch_bounds__(256) void dw_bwd_s2_k(const T* __restrict__ dz, con
       if (c >= C) continue;
       float t = 0.f;
       for (int sgi = 0; sgi < d.spp; ++sgi) t += red[((size_t)sgi * QB + q) * 12 + e];
-      gw[((size_t)part * 9 + i * 3 + (e >> 2)) * C + c] = t;
+      p.gw[((size_t)part * 9 + i * 3 + (e >> 2)) * C + c] = t;
     }
   }
 }
 
-static DwPlan dw_bwd_s2_plan(int dt, const ConvGeom& g, int* per, int* P) {
-  DwPlan d = dw_plan(g.Cout, dt == 0 ? 4 : 2, false, g.Hin, g.Win);       // tiles in input resolution
+static DwPlan dw_bwd_plan(int dt, const ConvGeom& g, int* per, int* P) {
+  DwPlan d = dw_plan(g.Cout, dt == 0 ? 4 : 2, false, g.Hin, g.Win, g.stride == 1 && dt != 0 ? DwBwd<bf16_t, 1>::TW : 16);       // tiles in input resolution
+  // bfloat16 at stride 1: tiles of 7 rows take three passes to stage instead of four and nine tenths of the time; images of 7, 14 and 28 rows divide by them
+  const int rows7 = (g.Hin + 6) / 7;
+  if (g.stride == 1 && dt != 0 && d.TH == 8 && rows7 * 9 < d.tiles_h * 10) {
+    d.TH = 7; d.tiles_h = rows7; d.nseg = d.TH * d.segw;
+  }
   d.ntiles = g.N * d.tiles_h * d.tiles_w;
-  d.segw = (d.TW + 1) / 2;
-  d.nseg = (d.TH + 1) / 2 * d.segw;
-  d.m_segw = dw_magic(d.segw);
-  d.PH = (d.TH + 1) / 2 + 1;
-  d.PW = d.segw + 1;
+  if (g.stride == 1) {
+    d.PH = d.TH + 2;
+    d.PW = d.segw * 4 + 2;
+  } else {
+    d.segw = (d.TW + 1) / 2;
+    d.nseg = (d.TH + 1) / 2 * d.segw;
+    d.m_segw = dw_magic(d.segw);
+    d.PH = (d.TH + 1) / 2 + 1;
+    d.PW = d.segw + 1;
+  }
   *per = (d.ntiles + kMaxPartials - 1) / kMaxPartials;
   *P = (d.ntiles + *per - 1) / *per;
   return d;
 }
-size_t dw_bwd_s2_ws(int dt, const ConvGeom& g) {
-  if (g.stride != 2) return 0;
+int dw_bwd_partials(int dt, const ConvGeom& g) {
   int per, P;
-  dw_bwd_s2_plan(dt, g, &per, &P);
-  return (size_t)P * 9 * g.Cout;
+  dw_bwd_plan(dt, g, &per, &P);
+  return P;
 }
+size_t dw_bwd_ws(int dt, const ConvGeom& g) { return (size_t)dw_bwd_partials(dt, g) * 9 * g.Cout; }
 
-void dw_bwd_s2(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out, float* gw_part) {
+void dw_bwd(int dt, hipStream_t st, const void* dA, const HView* own, const BnPending* sums_in, const float* coef, float* g_gamma, float* g_beta, const void* w,
+            const ConvGeom& g, void* dIn, HView in, float* sums, float* gw_part) {
   const int es = dt == 0 ? 4 : 2;
-  int per;
-  DwPlan d = dw_bwd_s2_plan(dt, g, &per, P_out);
+  int P;
+  DwBwdArgs a{};
+  a.d = dw_bwd_plan(dt, g, &a.per, &P);
   const size_t total = (size_t)g.N * g.Hin * g.Win, outs = (size_t)g.N * g.Hout * g.Wout;
-  KScope ks(st, "dw_dgrad", (2.0 * total + (double)outs) * g.Cout * es + (double)*P_out * 11 * g.Cout * 4, 36.0 * outs * g.Cout, (long)total, g.Cout, 2);
-  ks.route("one pass");
-  if (!dw_check_plan(d, dt == 0 ? DwFill<float>::DGRAD_S2 : DwFill<bf16_t>::DGRAD_S2) || d.nseg > (dt == 0 ? 1 : 2) * d.spp || !prev.scale) {
-    launch_plan_failed("stride-2 depthwise backward called for a layer it does not take");
-    return;
-  }
-  size_t lds = dw_lds_bytes(d, es) + dw_patch_bytes(d, es);
-  const size_t red = (size_t)d.spp * 2 * d.CGB * 12 * sizeof(float);
+  KScope ks(st, "dw_bwd", (2.0 * total + (own ? 2.0 : 1.0) * outs) * g.Cout * es + (double)P * 11 * g.Cout * 4, 36.0 * outs * g.Cout, (long)total, g.Cout, g.stride);
+  // passes of the staging: a kernel for each number, so that registers are held and loads made for no more
+  const int passes = (a.d.PH * a.d.PW + a.d.PPB - 1) / a.d.PPB, fill = g.stride == 2 ? (dt == 0 ? 1 : 2) : dt == 0 || passes <= 3 ? 3 : 4;
+  if (!dw_check_plan(a.d, fill, dt == 0 || g.stride == 1 ? 1 : 2)) return;
+  a.dA = dA; a.w = w; a.coef = coef; a.g_gamma = g_gamma; a.g_beta = g_beta;
+  if (own) a.own = View{own->z, own->scale, own->shift, own->act};
+  if (sums_in) a.pend = *sums_in;
+  a.Hin = g.Hin; a.Win = g.Win; a.Hout = g.Hout; a.Wout = g.Wout; a.C = g.Cout;
+  a.dIn = dIn; a.sums = sums; a.gw = gw_part;
+  a.prev = DwPrev{in.z, in.scale, in.shift, in.act};
+  if (a.d.PH > (g.stride == 1 ? 10 : 5) || a.d.PW > (g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::PW : DwBwd<bf16_t, 1>::PW) : 9)) { launch_plan_failed("depthwise backward patch beyond the kernel's"); return; }
+  size_t lds = g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::LDS : DwBwd<bf16_t, 1>::LDS) : (dt == 0 ? DwBwd<float, 2>::LDS : DwBwd<bf16_t, 2>::LDS);
+  const size_t red = (size_t)a.d.spp * 2 * a.d.CGB * 12 * sizeof(float);
   if (lds < red) lds = red;
-  const DwPrev pv{prev.z, prev.scale, prev.shift, prev.act};
-  FTP_DISPATCH(dt, hipLaunchKernelGGL(dw_bwd_s2_k<T>, dim3((unsigned)*P_out * d.nslab), dim3(256), lds, st, (const T*)dz, (const T*)w, d, g.Hin, g.Win, g.Hout,
-                                      g.Wout, g.Cout, (T*)dIn, per, sums, pv, gw_part));
-}
-
-// the stride-1 data gradient can leave the backward sums of the BatchNorm in front (dw_conv_k, STATS = 2) when its
-// tiles are few enough to be the partials
-int dw_dgrad_sums_ok(int dt, const ConvGeom& g) {
-  if (g.stride != 1) return 0;
-  const DwPlan d = dw_plan(g.Cout, dt == 0 ? 4 : 2, false, g.Hin, g.Win);
-  return (size_t)g.N * d.tiles_h * d.tiles_w <= (size_t)kMaxPartials;
-}
-
-void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums,
-              int* P_out) {
-  const int es = dt == 0 ? 4 : 2;
-  size_t total = (size_t)g.N * g.Hin * g.Win;
-  KScope ks(st, "dw_dgrad", ((double)total * g.Cout + (double)g.N * g.Hout * g.Wout * g.Cout) * es, 18.0 * g.N * g.Hout * g.Wout * g.Cout,
-            (long)total, g.Cout, g.stride);
-  // tiles are in input resolution
-  DwPlan d = dw_plan(g.Cout, es, false, g.Hin, g.Win);
-  d.ntiles = g.N * d.tiles_h * d.tiles_w;
-  const unsigned grid = (unsigned)d.ntiles * d.nslab;
-  if (g.stride == 1) {
-    // the forward kernel on dz with the weights flipped
-    d.PH = d.TH + 2;
-    d.PW = d.segw * 4 + 2;
-    if (!dw_check_plan(d, dt == 0 ? DwFill<float>::CONV : DwFill<bf16_t>::CONV)) return;
-    View v{dz, nullptr, nullptr, 0};
-    if (sums) {
-      if (d.ntiles > kMaxPartials || !prev.scale) { launch_plan_failed("depthwise data gradient with BatchNorm sums: not for this layer"); return; }
-      size_t lds = dw_lds_bytes(d, es);
-      const size_t red = (size_t)d.spp * 2 * d.CGB * 8 * sizeof(float);
-      if (lds < red) lds = red;
-      const DwPrev pv{prev.z, prev.scale, prev.shift, prev.act};
-      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 1, true, 2>), dim3(grid), dim3(256), lds, st, v, (const T*)w, d,
-                                          g.Hout, g.Wout, g.Hin, g.Win, g.Cout, (T*)dIn, sums, pv));
-      *P_out = d.ntiles;
-      return;
-    }
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_conv_k<T, 1, true>), dim3(grid), dim3(256), dw_lds_bytes(d, es), st, v, (const T*)w, d,
-                                        g.Hout, g.Wout, g.Hin, g.Win, g.Cout, (T*)dIn));
-  } else {
-    d.PH = d.TH / 2 + 2;
-    d.PW = d.segw * 2 + 2;
-    if (!dw_check_plan(d, dt == 0 ? DwFill<float>::DGRAD_S2 : DwFill<bf16_t>::DGRAD_S2)) return;
-    FTP_DISPATCH(dt, hipLaunchKernelGGL(dw_dgrad_s2_k<T>, dim3(grid), dim3(256), dw_lds_bytes(d, es), st, (const T*)dz, (const T*)w,
-                                        d, g.Hin, g.Win, g.Hout, g.Wout, g.Cout, (T*)dIn));
-  }
-}
-
-// dW[c][ky][kx] += sum over output pixels dz[p][c] * in[p*S-1+(ky,kx)][c].  Blocks are persistent over
-// tiles; a thread reads the dz of its run straight from global memory (nobody else needs it), keeps
-// 9 x 4 sums over all its runs, and the block leaves one partial ws[block][9][C].
-// The dz values of a thread's (at most kDwSegs) 4-pixel runs of one tile, requested a whole tile ahead like the
-// input patch: a persistent block has few neighbours on its CU to hide a load behind.
-template <typename T, int RL = 4, int SEGS = kDwSegs>
-struct DwDzRuns {
-  Raw4<T> r[SEGS][RL];
-  unsigned ok;
-  __device__ __forceinline__ void fetch(const T* __restrict__ dz, int tile, const DwPlan& d, int Hout, int Wout, int C,
-                                        int seg0, int gc, bool worker) {
-    ok = 0;
-    if (!worker) return;
-    const int tw = tile % d.tiles_w, th = (tile / d.tiles_w) % d.tiles_h, n = tile / (d.tiles_w * d.tiles_h);
-    const int ho0 = th * d.TH, wo0 = tw * d.TW;
-    // offsets first, then unconditional loads back to back (a pixel outside reads the image's first pixel and is
-    // not used): see DwPatch::fetch
-    const T* img = dz + (size_t)n * Hout * Wout * C + gc;
-    unsigned off[SEGS][RL];
-#pragma unroll
-    for (int k = 0; k < SEGS; ++k) {
-      const int sg = seg0 + k * d.spp;
-      const int hl = dw_div(sg < d.nseg ? sg : 0, d.m_segw), wl0 = ((sg < d.nseg ? sg : 0) - hl * d.segw) * RL;
-      const int ho = ho0 + hl;
-#pragma unroll
-      for (int o = 0; o < RL; ++o) {
-        const bool in = sg < d.nseg && ho < Hout && wo0 + wl0 + o < Wout;
-        off[k][o] = in ? __umul24(__umul24(ho, Wout) + wo0 + wl0 + o, C) : 0u;
-        ok |= (in ? 1u : 0u) << (RL * k + o);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < SEGS; ++k)
-#pragma unroll
-      for (int o = 0; o < RL; ++o) raw4_load(r[k][o], img + off[k][o]);
-  }
-};
-
-// RL = pixels per run: four at stride 1, two at stride 2 (see dw_conv_k); SEGS = runs of a tile per thread: the 4 x 8
-// stride-2 tile has 16 runs, one per thread
-template <typename T, int S, int RL = (S == 2 ? 2 : 4), int SEGS = (S == 2 ? 1 : kDwSegs)>
-__global__ __launch_bounds__(256) void dw_wgrad_k(const T* __restrict__ dz, View in, DwPlan d, int Hin, int Win, int Hout,
-                                                  int Wout, int C, float* __restrict__ ws) {
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  T* patch = reinterpret_cast<T*>(smem_raw);
-  const int lb = xcd_logical_block();
-  const int slab = lb % d.nslab, b = lb / d.nslab, cg0 = slab * d.CGB;     // the slabs of a tile run together
-  const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB;
-  const int c4 = cq * 4, gc = cg0 * 8 + c4;
-  const bool worker = seg0 < d.spp && gc < C;
-  const int vs = d.CGB * 8;
-  const T* src = reinterpret_cast<const T*>(in.z);
-  float4 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-  DwPatch<T> lp;
-  DwDzRuns<T, RL, SEGS> dq[2];
-  if (b < d.ntiles) {
-    const int tw = b % d.tiles_w, th = (b / d.tiles_w) % d.tiles_h, n = b / (d.tiles_w * d.tiles_h);
-    lp.fetch(src, n, th * d.TH * S - 1, tw * d.TW * S - 1, d, Hin, Win, C, cg0);
-    dq[0].fetch(dz, b, d, Hout, Wout, C, seg0, gc, worker);
-  }
-  // two tiles per round so that the two sets of dz registers are addressed statically
-  for (int tile0 = b; tile0 < d.ntiles; tile0 += 2 * d.nblocks) {
-#pragma unroll
-    for (int par = 0; par < 2; ++par) {
-      const int tile = tile0 + par * d.nblocks;
-      if (tile >= d.ntiles) break;
-      __syncthreads();                                       // the previous tile has been consumed
-      lp.commit(patch, in, d, cg0);
-      __syncthreads();
-      const int nt = tile + d.nblocks;
-      if (nt < d.ntiles) {
-        const int tw2 = nt % d.tiles_w, th2 = (nt / d.tiles_w) % d.tiles_h, n2 = nt / (d.tiles_w * d.tiles_h);
-        // the dz runs first: a wait the compiler puts in front of them (their registers were read in the last
-        // round's taps) then finds nothing outstanding, instead of the six patch loads
-        dq[par ^ 1].fetch(dz, nt, d, Hout, Wout, C, seg0, gc, worker);
-        lp.fetch(src, n2, th2 * d.TH * S - 1, tw2 * d.TW * S - 1, d, Hin, Win, C, cg0);
-      }
-      if (!worker) continue;
-      const DwDzRuns<T, RL, SEGS>& cur = dq[par];
-#pragma unroll
-      for (int k = 0; k < SEGS; ++k) {
-        const int sg = seg0 + k * d.spp;
-        if (sg >= d.nseg) break;
-        if (((cur.ok >> (RL * k)) & ((1u << RL) - 1u)) == 0u) continue;     // the run lies outside the image
-        const int hl = dw_div(sg, d.m_segw), wl0 = (sg - hl * d.segw) * RL;
-        float4 dv[RL];
-#pragma unroll
-        for (int o = 0; o < RL; ++o)
-          dv[o] = (cur.ok >> (RL * k + o)) & 1u ? raw4_unpack(cur.r[k][o]) : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-          const T* row = patch + (size_t)((hl * S + ky) * d.PW + wl0 * S) * vs + c4;
-          float4 iv[(RL - 1) * S + 3];
-#pragma unroll
-          for (int x = 0; x < (RL - 1) * S + 3; ++x) iv[x] = load4(row + (size_t)x * vs);
-#pragma unroll
-          for (int kx = 0; kx < 3; ++kx)
-#pragma unroll
-            for (int o = 0; o < RL; ++o) acc[ky * 3 + kx] = fma4(dv[o], iv[o * S + kx], acc[ky * 3 + kx]);
-        }
-      }
-    }
-  }
-  // sum the runs of every channel quad in a fixed order: red[spp][9][QB] float4
-  __syncthreads();
-  float4* red = reinterpret_cast<float4*>(smem_raw);
-  if (seg0 < d.spp) {
-#pragma unroll
-    for (int t = 0; t < 9; ++t) red[(seg0 * 9 + t) * QB + cq] = worker ? acc[t] : make_float4(0.f, 0.f, 0.f, 0.f);
-  }
-  __syncthreads();
-  for (int i = threadIdx.x; i < 9 * QB; i += blockDim.x) {
-    const int q = i % QB, t = i / QB;
-    if (cg0 * 8 + q * 4 >= C) continue;
-    float4 tot = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int r = 0; r < d.spp; ++r) {
-      const float4 v = red[(r * 9 + t) * QB + q];
-      tot.x += v.x; tot.y += v.y; tot.z += v.z; tot.w += v.w;
-    }
-    store4(ws + ((size_t)b * 9 + t) * C + cg0 * 8 + q * 4, tot);
-  }
-}
-
-// ---- depthwise weight gradient without LDS staging: a lane walks down the image ------------------------
-// g_w[c][ky][kx] = sum over output pixels of dz[ho][wo][c] * in[ho*S+ky-1][wo*S+kx-1][c].  A lane owns 4 channels and a
-// strip of R output columns of one image (R = 2 at stride 1, 1 at stride 2) and walks it from the top row down with
-// the input window under the current output pixels in registers ((R-1)*S+3 columns x 3 rows, already through the view,
-// as float): per step it brings in S new input rows and R new dz vectors from global memory (requested three steps
-// ahead) and does 9 * R four-wide FMAs.  Every input element is converted once per strip it lies under, there is no
-// barrier and no LDS traffic inside the walk, and the 36 sums stay in registers over all strips of the lane.
-// The lanes of a wavefront (and the wavefronts of a block) take neighbouring strips, so what they request in one
-// step is one contiguous stretch of an image row (walking ALONG the rows instead put every lane on a row of its own:
-// thousands of 256-byte streams, which the memory served at 2 TB/s).
-// The 4-channel groups of a layer are cut into slabs whose widths are powers of two (144 channels = 36 groups =
-// 32 + 4), so that gw groups x sw strips fill the 64 lanes of a wavefront exactly; a block's four wavefronts
-// take 4 * sw strips of one slab per pass, and the block leaves one partial ws[p][9][C] (its slab's channels).
-struct DwMarchSlab { int ch0, gw, sw; int blk0, nblk; };   // first channel, lanes per strip, strips per wavefront; first block, blocks
-enum { kDwMarchSlabs = 16, kDwMarchBlocks = 2048, kDwMarchCpl = 2 };   // slabs a layer may need, blocks in all, channels per lane
-struct DwMarchArgs {
-  const void* dz;
-  View in;
-  float* ws;
-  int Hin, Win, Hout, Wout, C;
-  int ncb, nseg, seglen;    // strips side by side, row segments per image (a strip is one segment high), rows per segment
-  int nstrips;              // N * nseg * ncb
-  int P, nslab;             // partial rows (the most blocks any slab has), slabs
-  int nblocks;              // all blocks: the slabs' block ranges one after the other
-  DwMarchSlab slab[kDwMarchSlabs];
-};
-
-template <int V> struct IntC { static constexpr int value = V; };
-
-// two channels of one pixel as loaded
-template <typename T> struct Raw2;
-template <> struct Raw2<float> { float2 v; };
-template <> struct Raw2<bf16_t> { uint32_t v; };
-__device__ __forceinline__ void raw2_load(Raw2<float>& r, const float* p) { r.v = *reinterpret_cast<const float2*>(p); }
-__device__ __forceinline__ void raw2_load(Raw2<bf16_t>& r, const bf16_t* p) { r.v = *reinterpret_cast<const uint32_t*>(p); }
-__device__ __forceinline__ float2 raw2_unpack(const Raw2<float>& r) { return r.v; }
-__device__ __forceinline__ float2 raw2_unpack(const Raw2<bf16_t>& r) {
-  return make_float2(__uint_as_float(r.v << 16), __uint_as_float(r.v & 0xffff0000u));
-}
-// the pair as it reads back after being stored in T (one conversion instruction for both halves)
-__device__ __forceinline__ float2 round2(float2 v, float) { return v; }
-__device__ __forceinline__ float2 round2(float2 v, bf16_t) {
-  const uint32_t u = f32x2_to_bf16x2(v.x, v.y);
-  return make_float2(__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u));
-}
-
-template <typename T, int S, bool VIEW>
-__device__ __forceinline__ void dw_wgrad_march_body(const DwMarchArgs& a, const int lb) {
-  constexpr int R = S == 1 ? 2 : 1;
-  constexpr int NCOL = (R - 1) * S + 3;
-  __shared__ float2 red[4][9][64];
-  // Every slab has blocks in proportion to its work (a narrow tail slab takes many strips per wavefront and needs
-  // few): with the same number for all, half the resident blocks of a layer with a tail slab had nothing to do and the
-  // wide slabs' blocks took a second round.
-  int si = 0;
-  while (si + 1 < a.nslab && lb >= a.slab[si + 1].blk0) ++si;
-  const DwMarchSlab sl = a.slab[si];
-  const int p = lb - sl.blk0;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int g = lane & (sl.gw - 1), s_l = lane / sl.gw;
-  const int c = sl.ch0 + kDwMarchCpl * g;
-  const T* src = reinterpret_cast<const T*>(a.in.z);
-  const T* dzp = reinterpret_cast<const T*>(a.dz);
-  constexpr bool view = VIEW;
-  // The walk must be free of branches: only then does the compiler count the loads in flight and wait for the oldest
-  // register set alone (with a branch in the loop it waits for all of them).  The heights therefore live in vector
-  // registers (a comparison with them is a lane mask, never a jump), and every walk takes a multiple of three steps;
-  // the steps behind the last row see dz = 0.
-  int hinL = a.Hin, houtL = a.Hout;
-  asm volatile("" : "+v"(hinL), "+v"(houtL));
-  float2 sc = make_float2(1.f, 1.f), sh = make_float2(0.f, 0.f);
-  if (view) {
-    sc = *reinterpret_cast<const float2*>(a.in.scale + c);
-    sh = *reinterpret_cast<const float2*>(a.in.shift + c);
-  }
-  const float lo = act_lo(a.in.act), hi = act_hi(a.in.act);
-  const float2 zero2 = make_float2(0.f, 0.f);
-  float2 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = zero2;
-  const unsigned in_row = __umul24(a.Win, a.C), dz_row = __umul24(a.Wout, a.C);
-
-  const int spb = 4 * sl.sw;
-  for (int sidx = p * spb + wave * sl.sw + s_l; sidx < a.nstrips; sidx += sl.nblk * spb) {
-    const int ns = sidx / a.ncb, cb = sidx - ns * a.ncb;
-    const int n = ns / a.nseg, h_beg = (ns - n * a.nseg) * a.seglen;       // a multiple of three: the phases line up
-    const int wo0 = cb * R, wi0 = wo0 * S - 1;
-    int hendL = h_beg + a.seglen < a.Hout ? h_beg + a.seglen : a.Hout;
-    asm volatile("" : "+v"(hendL));
-    const T* img = src + (size_t)n * a.Hin * a.Win * a.C + c;
-    const T* dimg = dzp + (size_t)n * a.Hout * a.Wout * a.C + c;
-    unsigned coff[NCOL], doff[R];
-    bool cok[NCOL], dok[R];
-#pragma unroll
-    for (int r = 0; r < NCOL; ++r) {
-      cok[r] = wi0 + r >= 0 && wi0 + r < a.Win;
-      coff[r] = cok[r] ? __umul24(wi0 + r, a.C) : 0u;
-    }
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      dok[r] = wo0 + r < a.Wout;
-      doff[r] = dok[r] ? __umul24(wo0 + r, a.C) : 0u;
-    }
-    float2 win[NCOL][3];
-#pragma unroll
-    for (int r = 0; r < NCOL; ++r)
-#pragma unroll
-      for (int y = 0; y < 3; ++y) win[r][y] = zero2;
-    // Three steps' loads are in flight (one register set per phase): a lane has nothing else to hide a memory round
-    // trip behind, and one step's arithmetic is a fraction of it.
-    Raw2<T> rin[3][NCOL][S], rdz[3][R];
-    // what output row ho brings in: its S new input rows (y < Hin, else nothing is there) under every column of the
-    // strip, and its dz
-    auto request_row = [&](auto BUF, const int q, const int y) __attribute__((always_inline)) {
-      constexpr int buf = decltype(BUF)::value;
-      const unsigned ro = (unsigned)y < (unsigned)hinL ? (unsigned)y * in_row : 0u;
-#pragma unroll
-      for (int r = 0; r < NCOL; ++r) raw2_load(rin[buf][r][q], img + ro + coff[r]);
-    };
-    auto request = [&](auto BUF, const int ho) __attribute__((always_inline)) {
-      constexpr int buf = decltype(BUF)::value;
-      const int y0 = S == 1 ? ho + 1 : 2 * ho;
-#pragma unroll
-      for (int q = 0; q < S; ++q) request_row(BUF, q, y0 + q);
-      const unsigned hr = ho < houtL ? (unsigned)ho * dz_row : 0u;
-#pragma unroll
-      for (int r = 0; r < R; ++r) raw2_load(rdz[buf][r], dimg + hr + doff[r]);
-    };
-    auto bring = [&](auto BUF, auto SLOT, const int q, const int y) __attribute__((always_inline)) {
-      constexpr int buf = decltype(BUF)::value;
-      constexpr int slot = decltype(SLOT)::value;
-      const bool yok = (unsigned)y < (unsigned)hinL;
-#pragma unroll
-      for (int r = 0; r < NCOL; ++r) {
-        float2 v = raw2_unpack(rin[buf][r][q]);
-        if (view) v = round2(make_float2(clamp_act(fmaf(v.x, sc.x, sh.x), lo, hi), clamp_act(fmaf(v.y, sc.y, sh.y), lo, hi)), T());
-        win[r][slot] = (yok && cok[r]) ? v : zero2;       // padding is zero AFTER the view
-      }
-    };
-    // one output row: phase = ho % 3 fixes which window slot holds which input row (row y sits in slot y % 3)
-    auto step = [&](auto PH, const int ho) __attribute__((always_inline)) {
-      constexpr int ph = decltype(PH)::value;
-      constexpr int base = (S * ph + 2) % 3;              // slot of input row ho*S - 1
-      if (S == 1) {
-        bring(PH, IntC<(ph + 1) % 3>(), 0, ho + 1);
-      } else {
-        bring(PH, IntC<(2 * ph) % 3>(), 0, 2 * ho);
-        bring(PH, IntC<(2 * ph + 1) % 3>(), 1, 2 * ho + 1);
-      }
-      float2 dv[R];
-#pragma unroll
-      for (int r = 0; r < R; ++r) dv[r] = (dok[r] && ho < hendL) ? raw2_unpack(rdz[ph][r]) : zero2;
-      request(PH, ho + 3);                                 // this register set is free again: the step three ahead
-#pragma unroll
-      for (int r = 0; r < R; ++r)
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-          for (int kx = 0; kx < 3; ++kx) {
-            const float2 w2 = win[r * S + kx][(base + ky) % 3];
-            acc[ky * 3 + kx].x = fmaf(dv[r].x, w2.x, acc[ky * 3 + kx].x);
-            acc[ky * 3 + kx].y = fmaf(dv[r].y, w2.y, acc[ky * 3 + kx].y);
-          }
-    };
-    // the input rows above the segment's first output row that are under it already: row h_beg*S - 1 (slot 2), and
-    // at stride 1 row h_beg as well (slot 0)
-    request_row(IntC<0>(), 0, h_beg * S - 1);
-    if (S == 1) request_row(IntC<1>(), 0, h_beg);
-    bring(IntC<0>(), IntC<2>(), 0, h_beg * S - 1);
-    if (S == 1) bring(IntC<1>(), IntC<0>(), 0, h_beg);
-    request(IntC<0>(), h_beg);
-    request(IntC<1>(), h_beg + 1);
-    request(IntC<2>(), h_beg + 2);
-    for (int i = 0; i < a.seglen; i += 3) {
-      step(IntC<0>(), h_beg + i);
-      step(IntC<1>(), h_beg + i + 1);
-      step(IntC<2>(), h_beg + i + 2);
-    }
-  }
-
-  // the block's partial: lanes of one channel group over strips and wavefronts, in a fixed order
-#pragma unroll
-  for (int t = 0; t < 9; ++t) red[wave][t][lane] = acc[t];
-  __syncthreads();
-  for (int i = threadIdx.x; i < 9 * sl.gw; i += 256) {
-    const int t = i / sl.gw, gg = i - t * sl.gw;
-    float2 tot = zero2;
-    for (int w = 0; w < 4; ++w)
-      for (int q = 0; q < sl.sw; ++q) {
-        const float2 v = red[w][t][q * sl.gw + gg];
-        tot.x += v.x; tot.y += v.y;
-      }
-    *reinterpret_cast<float2*>(a.ws + ((size_t)p * 9 + t) * a.C + sl.ch0 + kDwMarchCpl * gg) = tot;
-    // the partial rows this slab has no block for (the sum runs over a.P rows for every channel)
-    for (int pz = sl.nblk + p; pz < a.P; pz += sl.nblk)
-      *reinterpret_cast<float2*>(a.ws + ((size_t)pz * 9 + t) * a.C + sl.ch0 + kDwMarchCpl * gg) = zero2;
-  }
-}
-
-template <typename T, int S, bool VIEW>
-__global__ __launch_bounds__(256) void dw_wgrad_march_k(DwMarchArgs a) { dw_wgrad_march_body<T, S, VIEW>(a, xcd_logical_block()); }
-
-// several layers in one launch, the layers' blocks one behind the other
-enum { kDwMarchJobs = 8 };
-struct DwMarchGroup { DwMarchArgs job[kDwMarchJobs]; int blk0[kDwMarchJobs + 1]; int n; };
-template <typename T, int S, bool VIEW>
-__global__ __launch_bounds__(256) void dw_wgrad_march_group_k(DwMarchGroup a) {
-  int lb;
-  const int ji = group_job(a.blk0, a.n, lb);
-  if (lb < a.job[ji].nblocks) dw_wgrad_march_body<T, S, VIEW>(a.job[ji], lb);
-}
-
-// slabs (powers of two, widest first) and the number of blocks; false if the layer needs more slabs than the kernel takes
-static bool dw_march_plan(const ConvGeom& g, DwMarchArgs* a) {
-  int G = g.Cout / kDwMarchCpl, ch = 0, n = 0;
-  while (G > 0) {
-    int gw = 64;
-    while (gw > G) gw >>= 1;
-    if (n == kDwMarchSlabs) return false;
-    a->slab[n++] = DwMarchSlab{ch, gw, 64 / gw};
-    ch += kDwMarchCpl * gw; G -= gw;
-  }
-  a->nslab = n;
-  const int R = g.stride == 1 ? 2 : 1;
-  a->ncb = (g.Wout + R - 1) / R;
-  // Row segments: a lane's walk is one long chain of dependent steps, so a layer with few strips is cut across its
-  // rows until about 2048 wavefronts' worth of lanes exist (cutting further only added partial sums: measured); a segment is a
-  // multiple of three rows (the window's phases) and at least 12 rows (its first rows are read twice).
-  {
-    const double waves = (double)g.N * a->ncb * (g.Cout / kDwMarchCpl) / 64.0;
-    int want = (int)(2048.0 / (waves > 1.0 ? waves : 1.0) + 0.999);
-    if (want < 1) want = 1;
-    int len = (g.Hout + want - 1) / want;
-    if (len < 12) len = 12;
-    len = (len + 2) / 3 * 3;
-    a->seglen = len;
-    a->nseg = (g.Hout + len - 1) / len;
-  }
-  a->nstrips = g.N * a->nseg * a->ncb;
-  // blocks per slab: one per pass while all of them fit kDwMarchBlocks, else in proportion to the passes
-  long passes[kDwMarchSlabs], total = 0;
-  for (int i = 0; i < n; ++i) {
-    const int per_pass = 4 * a->slab[i].sw;
-    passes[i] = (a->nstrips + per_pass - 1) / per_pass;
-    total += passes[i];
-  }
-  int blk = 0, pmax = 1;
-  for (int i = 0; i < n; ++i) {
-    long b = total <= kDwMarchBlocks ? passes[i] : (passes[i] * kDwMarchBlocks + total - 1) / total;
-    if (b < 1) b = 1;
-    if (b > passes[i]) b = passes[i];
-    a->slab[i].blk0 = blk;
-    a->slab[i].nblk = (int)b;
-    blk += (int)b;
-    if ((int)b > pmax) pmax = (int)b;
-  }
-  a->nblocks = blk;
-  a->P = pmax;
-  a->Hin = g.Hin; a->Win = g.Win; a->Hout = g.Hout; a->Wout = g.Wout; a->C = g.Cout;
-  return g.Cout % 8 == 0 && (g.stride == 1 || g.stride == 2);
-}
-
-static DwPlan dw_wgrad_plan(const ConvGeom& g, int es, size_t* lds) {
-  const int s = g.stride;
-  DwPlan d = dw_plan(g.Cout, es, s == 2, g.Hout, g.Wout);
-  const int run = s == 2 ? 2 : 4;                // pixels per run, as the kernel's RL
-  d.segw = (d.TW + run - 1) / run;
-  d.nseg = d.TH * d.segw;
-  d.m_segw = dw_magic(d.segw);
-  d.PH = (d.TH - 1) * s + 3;
-  d.PW = (d.segw * run - 1) * s + 3;
-  d.ntiles = g.N * d.tiles_h * d.tiles_w;
-  // Persistent blocks over all slabs: fewer than fit the GPU at once next to the other stream's kernels.  The stride-1
-  // kernel holds 207 registers (two blocks per CU): with 512 blocks some waited for a place, and a 5 us finalize kernel
-  // of the data-gradient chain was measured waiting up to 200 us with them (a trace shows it ending when the first
-  // blocks end); 256 leave the weight gradient itself too slow.  The stride-2 kernel holds 149 registers (three blocks
-  // per CU): 480 measured best of 384-768.
-  const int capn = s == 2 ? 480 : 384;
-  const int cap = capn / d.nslab > 1 ? capn / d.nslab : 1;
-  d.nblocks = d.ntiles < cap ? d.ntiles : cap;
-  size_t a = (size_t)d.PH * d.PW * d.CGB * 8 * es;          // the patch in the tensor's type
-  size_t b = (size_t)d.spp * 9 * 2 * d.CGB * 16;
-  *lds = a > b ? a : b;
-  return d;
-}
-
-// ---- depthwise weight gradient, bfloat16: rows staged through LDS ---------------------------------------------
-// The marching kernel above reads memory with one 4-byte access per lane.  With a power-of-two channel count a
-// wavefront's access is exactly one aligned pixel and it streams at 4.4 - 4.7 TB/s; with 48, 144, 192 ... channels
-// (every layer of a width-1.4 MobileNetV2) pixels straddle cache lines and a narrow tail slab needs accesses of its
-// own: 2.1 - 3.4 TB/s, although the arithmetic alone would take a quarter of the time (measured with all rows
-// redirected to one cached row).  Here the memory side is decoupled from the channel count: a block owns a band of
-// WB output columns of one image (all channels of a slab of at most 256) and walks down a segment of its rows; the
-// S new input rows of a step and the dz row are contiguous runs of several KB in memory, fetched with 16-byte
-// vectors a step ahead, put through the view once, and kept in an LDS ring of rows; a thread owns one channel QUAD
-// and every NCG-th column of the band and reads its nine taps from the ring (8-byte LDS reads, no bounds logic: the
-// ring holds zeros where the image ends).  One barrier per step; one fp32 partial [9][C] per block at the end.
-enum { kDwRowsNV = 4, kDwRowsDzNV = 2, kDwRowsMaxCpt = 4 };
-struct DwRowsArgs {
-  const bf16_t* dz;
-  const bf16_t* in;
-  const float* scale;
-  const float* shift;
-  int act;
-  float* ws;
-  int Hin, Win, Hout, Wout, C;
-  int CS, nslab;            // channels per slab (a multiple of 8), slabs
-  int Q, NCG, CPT, WB;      // channel quads of a slab, column groups, columns per thread and step, columns per band
-  int WIN;                  // input columns under a band
-  int bands, nseg, seglen;  // bands across, row segments per image, output rows per segment
-  int P;                    // blocks (= partials) per slab: N * bands * nseg
-};
-
-template <int S, bool VIEW>
-__global__ __launch_bounds__(256) void dw_wgrad_rows_k(DwRowsArgs a) {
-  constexpr int RING = S == 1 ? 4 : 5;
-  extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  const int tid = threadIdx.x;
-  const int lb = xcd_logical_block();
-  const int si = lb % a.nslab, pb = lb / a.nslab;             // the slabs of a band run side by side
-  const int band = pb % a.bands, rest = pb / a.bands, seg = rest % a.nseg, n = rest / a.nseg;
-  const int c0 = si * a.CS, cs = a.C - c0 < a.CS ? a.C - c0 : a.CS;      // this slab's channels
-  const int CS = a.CS, WIN = a.WIN, WB = a.WB;
-  const int wb0 = band * WB, wi0 = wb0 * S - 1;
-  const int h0 = seg * a.seglen, h1 = h0 + a.seglen < a.Hout ? h0 + a.seglen : a.Hout;
-  const int rowElems = WIN * CS;                               // one ring slot
-  bf16_t* ring = reinterpret_cast<bf16_t*>(smem_raw);          // [RING][WIN][CS]
-  bf16_t* dzs = ring + RING * rowElems;                        // [2][WB][CS]
-  const bf16_t* img = a.in + (size_t)n * a.Hin * a.Win * a.C + c0;
-  const bf16_t* dimg = a.dz + (size_t)n * a.Hout * a.Wout * a.C + c0;
-  const int VR = CS / 8;                                       // vectors per pixel of the slab
-  const int nin = WIN * VR, ndz = WB * VR;                     // vectors per input row, per dz row
-
-  // ---- staging: vector v of a row is (column v / VR, channels 8 * (v % VR) ..); a thread's vectors are the same
-  // in every row, so their offsets are worked out once ----
-  float* vsc = reinterpret_cast<float*>(dzs + 2 * WB * CS);    // [CS] scale, [CS] shift of the view
-  if (VIEW) {
-    for (int i = tid; i < CS; i += 256) {
-      vsc[i] = i < cs ? a.scale[c0 + i] : 0.f;
-      vsc[CS + i] = i < cs ? a.shift[c0 + i] : 0.f;
-    }
-  }
-  int goff[kDwRowsNV], loff[kDwRowsNV];                        // offset inside an image row (-1: nothing there), inside a ring slot
-#pragma unroll
-  for (int q = 0; q < kDwRowsNV; ++q) {
-    const int v = tid + q * 256;
-    const int col = v / VR, ch = (v - col * VR) * 8, wi = wi0 + col;
-    loff[q] = col * CS + ch;
-    goff[q] = (v < nin && wi >= 0 && wi < a.Win && ch < cs) ? wi * a.C + ch : -1;
-  }
-  int dgoff[kDwRowsDzNV], dloff[kDwRowsDzNV];
-#pragma unroll
-  for (int q = 0; q < kDwRowsDzNV; ++q) {
-    const int v = tid + q * 256;
-    const int col = v / VR, ch = (v - col * VR) * 8;
-    dloff[q] = col * CS + ch;
-    dgoff[q] = (v < ndz && wb0 + col < a.Wout && ch < cs) ? (wb0 + col) * a.C + ch : -1;
-  }
-  const int nq = (nin + 255) / 256;                            // passes a row takes (uniform)
-  uint4 rin[S][kDwRowsNV], rdz[kDwRowsDzNV];
-  unsigned okin[S], okdz;
-  // an input row y of the image; the ring holds zeros outside the image and past the slab's channels
-  auto fetch_row = [&](uint4* r, unsigned& ok, const int y) __attribute__((always_inline)) {
-    ok = 0;
-    const bool yin = y >= 0 && y < a.Hin;
-    const bf16_t* rowp = img + (size_t)(yin ? y : 0) * a.Win * a.C;
-#pragma unroll
-    for (int q = 0; q < kDwRowsNV; ++q) {
-      if (q >= nq) break;
-      const bool in = yin && goff[q] >= 0;
-      r[q] = *reinterpret_cast<const uint4*>(rowp + (in ? goff[q] : 0));
-      ok |= (in ? 1u : 0u) << q;
-    }
-  };
-  auto commit_row = [&](const uint4* r, const unsigned ok, const int y) __attribute__((always_inline)) {
-    bf16_t* dst = ring + ((y + RING) % RING) * rowElems;
-    const float lo = act_lo(a.act), hi = act_hi(a.act);
-#pragma unroll
-    for (int q = 0; q < kDwRowsNV; ++q) {
-      if (q >= nq) break;
-      if (tid + q * 256 >= nin) break;
-      uint4 o = make_uint4(0u, 0u, 0u, 0u);
-      if (ok & (1u << q)) {
-        o = r[q];
-        if (VIEW) {
-          Raw<bf16_t> raw; raw.a = o;
-          float f[8], sc[8], sh[8];
-          raw_unpack(raw, f);
-          const int ch = loff[q] % CS;
-          load8(vsc + ch, sc);
-          load8(vsc + CS + ch, sh);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) f[e] = clamp_act(fmaf(f[e], sc[e], sh[e]), lo, hi);
-          o.x = f32x2_to_bf16x2(f[0], f[1]); o.y = f32x2_to_bf16x2(f[2], f[3]);
-          o.z = f32x2_to_bf16x2(f[4], f[5]); o.w = f32x2_to_bf16x2(f[6], f[7]);
-        }
-      }
-      *reinterpret_cast<uint4*>(dst + loff[q]) = o;
-    }
-  };
-  auto fetch_dz = [&](const int ho) __attribute__((always_inline)) {
-    okdz = 0;
-    const bf16_t* rowp = dimg + (size_t)(ho < h1 ? ho : h0) * a.Wout * a.C;
-#pragma unroll
-    for (int q = 0; q < kDwRowsDzNV; ++q) {
-      if (q * 256 >= ndz) break;
-      const bool in = dgoff[q] >= 0 && ho < h1;
-      rdz[q] = *reinterpret_cast<const uint4*>(rowp + (in ? dgoff[q] : 0));
-      okdz |= (in ? 1u : 0u) << q;
-    }
-  };
-  auto commit_dz = [&](const int ho) __attribute__((always_inline)) {
-#pragma unroll
-    for (int q = 0; q < kDwRowsDzNV; ++q) {
-      if (tid + q * 256 >= ndz) break;
-      *reinterpret_cast<uint4*>(dzs + (ho & 1) * WB * CS + dloff[q]) = (okdz & (1u << q)) ? rdz[q] : make_uint4(0u, 0u, 0u, 0u);
-    }
-  };
-
-  // ---- this thread's work: channel quad q4 of the slab, columns cgi + j * NCG of the band ----
-  const int q4 = tid % a.Q, cgi = tid / a.Q;
-  const bool worker = cgi < a.NCG && q4 * 4 < cs;
-  float4 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-
-  if (VIEW) __syncthreads();                                   // the view vectors are in LDS
-  // rows above the first step's new ones
-  if (S == 1) {
-    fetch_row(rin[0], okin[0], h0 - 1);
-    commit_row(rin[0], okin[0], h0 - 1);
-    fetch_row(rin[0], okin[0], h0);
-    commit_row(rin[0], okin[0], h0);
-  } else {
-    fetch_row(rin[0], okin[0], 2 * h0 - 1);
-    commit_row(rin[0], okin[0], 2 * h0 - 1);
-  }
-  // the new rows of step ho: S == 1: row ho + 1; S == 2: rows 2 ho and 2 ho + 1
-  auto fetch_step = [&](const int ho) __attribute__((always_inline)) {
-#pragma unroll
-    for (int r = 0; r < S; ++r) fetch_row(rin[r], okin[r], S == 1 ? ho + 1 : 2 * ho + r);
-    fetch_dz(ho);
-  };
-  fetch_step(h0);
-  for (int ho = h0; ho < h1; ++ho) {
-#pragma unroll
-    for (int r = 0; r < S; ++r) commit_row(rin[r], okin[r], S == 1 ? ho + 1 : 2 * ho + r);
-    commit_dz(ho);
-    __syncthreads();          // also: every thread is done with the step before last, whose ring slots are written next
-    fetch_step(ho + 1);       // past the segment: rows of the image that are simply not used (dz past h1 is zero)
-    if (worker) {
-      const bf16_t* dzr = dzs + (ho & 1) * WB * CS + q4 * 4;
-      const bf16_t* rows[3];
-#pragma unroll
-      for (int ky = 0; ky < 3; ++ky) rows[ky] = ring + ((ho * S - 1 + ky + RING) % RING) * rowElems + q4 * 4;
-#pragma unroll
-      for (int j = 0; j < kDwRowsMaxCpt; ++j) {
-        if (j >= a.CPT) break;
-        const int lc = cgi + j * a.NCG;                        // column of the band
-        const float4 d = load4(dzr + lc * CS);
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) {
-          const bf16_t* row = rows[ky] + (lc * S) * CS;
-#pragma unroll
-          for (int kx = 0; kx < 3; ++kx) acc[ky * 3 + kx] = fma4(d, load4(row + kx * CS), acc[ky * 3 + kx]);
-        }
-      }
-    }
-  }
-  // ---- the block's partial: the column groups of a channel quad in a fixed order ----
-  __syncthreads();
-  float* red = reinterpret_cast<float*>(smem_raw);             // [NCG][9][CS]
-  if (worker) {
-#pragma unroll
-    for (int t = 0; t < 9; ++t) *reinterpret_cast<float4*>(red + ((size_t)cgi * 9 + t) * CS + q4 * 4) = acc[t];
-  }
-  __syncthreads();
-  for (int i = tid; i < 9 * cs; i += 256) {
-    const int t = i / cs, c = i - t * cs;
-    float tot = 0.f;
-    for (int g = 0; g < a.NCG; ++g) tot += red[((size_t)g * 9 + t) * CS + c];
-    a.ws[((size_t)pb * 9 + t) * a.C + c0 + c] = tot;
-  }
-}
-
-static bool dw_rows_plan(const ConvGeom& g, DwRowsArgs* a, size_t* lds) {
-  const int S = g.stride, C = g.Cout;
-  if (C % 8 || (S != 1 && S != 2) || g.kh != 3 || g.kw != 3) return false;
-  a->nslab = (C + 255) / 256;
-  a->CS = ((C + a->nslab - 1) / a->nslab + 7) / 8 * 8;
-  a->Q = a->CS / 4;
-  a->NCG = 256 / a->Q;
-  if (a->NCG < 1) return false;
-  if (a->NCG > g.Wout) a->NCG = g.Wout;
-  // columns per thread and step
-  // ring rows of about 8 KB at stride 2, 4 KB at stride 1, and about 1024 / 2048 blocks: measured on the 112 x 112 layers
-  const double row_bytes = S == 2 ? 8192.0 : 4096.0, want_blocks = S == 2 ? 1024.0 : 2048.0;
-  int cpt = (int)(row_bytes / ((double)a->NCG * S * a->CS * 2) + 0.5);
-  if (cpt < 1) cpt = 1;
-  if (cpt > kDwRowsMaxCpt) cpt = kDwRowsMaxCpt;
-  while (cpt > 1 && a->NCG * (cpt - 1) >= g.Wout) --cpt;
-  a->CPT = cpt;
-  a->WB = a->NCG * cpt;
-  a->WIN = (a->WB - 1) * S + 3;
-  a->bands = (g.Wout + a->WB - 1) / a->WB;
-  while (a->CPT > 1 && ((size_t)a->WIN * (a->CS / 8) > (size_t)kDwRowsNV * 256 || (size_t)a->WB * (a->CS / 8) > (size_t)kDwRowsDzNV * 256)) {
-    --a->CPT;
-    a->WB = a->NCG * a->CPT;
-    a->WIN = (a->WB - 1) * S + 3;
-    a->bands = (g.Wout + a->WB - 1) / a->WB;
-  }
-  if ((size_t)a->WIN * (a->CS / 8) > (size_t)kDwRowsNV * 256 || (size_t)a->WB * (a->CS / 8) > (size_t)kDwRowsDzNV * 256) return false;
-  // row segments, at least 8 rows each
-  const double blocks = (double)g.N * a->bands * a->nslab;
-  int want = (int)(want_blocks / (blocks > 1.0 ? blocks : 1.0) + 0.999);
-  if (want < 1) want = 1;
-  int len = (g.Hout + want - 1) / want;
-  if (len < 8) len = 8;
-  if (len > g.Hout) len = g.Hout;
-  a->seglen = len;
-  a->nseg = (g.Hout + len - 1) / len;
-  a->P = g.N * a->bands * a->nseg;
-  a->Hin = g.Hin; a->Win = g.Win; a->Hout = g.Hout; a->Wout = g.Wout; a->C = C;
-  const int RING = S == 1 ? 4 : 5;
-  const size_t stage = ((size_t)RING * a->WIN + 2 * (size_t)a->WB) * a->CS * sizeof(bf16_t) + 2 * (size_t)a->CS * sizeof(float);
-  const size_t red = (size_t)a->NCG * 9 * a->CS * sizeof(float);
-  *lds = stage > red ? stage : red;
-  return *lds <= 64 * 1024 && a->P <= 65535;
-}
-
-size_t dw_wgrad_ws(const ConvGeom& g) {
-  size_t lds;
-  DwPlan d = dw_wgrad_plan(g, 4, &lds);          // the float plan has at least as many slabs, the bound holds for both
-  DwPlan e = dw_wgrad_plan(g, 2, &lds);
-  size_t n = (size_t)(d.nblocks > e.nblocks ? d.nblocks : e.nblocks);
-  DwMarchArgs m{};
-  if (dw_march_plan(g, &m) && (size_t)m.P > n) n = m.P;
-  DwRowsArgs r{};
-  size_t rl;
-  if (dw_rows_plan(g, &r, &rl) && (size_t)r.P > n) n = r.P;
-  return n * 9 * g.Cout;
-}
-
-// Where the row kernel pays (measured, all layer shapes of the two MobileNetV2 widths): images of 112 x 112 and more whose
-// channel count the marching kernel has to cut into a wide slab and a narrow tail.  Power-of-two channel counts, and the
-// smaller images (too few rows per block to hide the step's barrier behind), stay with the marching kernel.
-static bool dw_rows_pays(int dt, const ConvGeom& g) {
-  DwMarchArgs m{};
-  DwRowsArgs r{};
-  size_t lds;
-  return dt == 1 && (size_t)g.Hin * g.Win >= (size_t)112 * 112 && dw_march_plan(g, &m) && m.nslab > 1 && dw_rows_plan(g, &r, &lds);
-}
-
-void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left) {
-  auto sum = [&](int P) {
-    if (left) left->push_back(ReduceJob{ws, g_w, P, 9 * g.Cout, g.Cout, 1, 9, g.Cout});
-    else reduce_partials(st, ws, P, (size_t)9 * g.Cout, g.Cout, 1, 9, g_w);
-  };
-  const int es = dt == 0 ? 4 : 2;
-  {
-    DwRowsArgs r{};
-    size_t lds;
-    if (dw_rows_pays(dt, g) && dw_rows_plan(g, &r, &lds)) {
-      r.dz = (const bf16_t*)dz; r.in = (const bf16_t*)in.z; r.scale = in.scale; r.shift = in.shift; r.act = in.act; r.ws = ws;
-      {
-        KScope ks(st, "dw_wgrad", ((double)g.N * g.Hin * g.Win * g.Cout + (double)g.N * g.Hout * g.Wout * g.Cout) * es + (double)r.P * 9 * g.Cout * 4,
-                  18.0 * g.N * g.Hout * g.Wout * g.Cout, (long)g.N * g.Hout * g.Wout, g.Cout, g.stride);
-        const dim3 grid((unsigned)r.P * r.nslab), block(256);
-        if (g.stride == 1) {
-          if (in.scale) hipLaunchKernelGGL((dw_wgrad_rows_k<1, true>), grid, block, lds, st, r);
-          else hipLaunchKernelGGL((dw_wgrad_rows_k<1, false>), grid, block, lds, st, r);
-        } else {
-          if (in.scale) hipLaunchKernelGGL((dw_wgrad_rows_k<2, true>), grid, block, lds, st, r);
-          else hipLaunchKernelGGL((dw_wgrad_rows_k<2, false>), grid, block, lds, st, r);
-        }
-      }
-      sum(r.P);
-      return;
-    }
-  }
-  DwMarchArgs m{};
-  if (dw_march_plan(g, &m)) {
-    m.dz = dz; m.in = View{in.z, in.scale, in.shift, in.act}; m.ws = ws;
-    {
-      KScope ks(st, "dw_wgrad", ((double)g.N * g.Hin * g.Win * g.Cout + (double)g.N * g.Hout * g.Wout * g.Cout) * es + (double)m.P * 9 * g.Cout * 4,
-                18.0 * g.N * g.Hout * g.Wout * g.Cout, (long)g.N * g.Hout * g.Wout, g.Cout, g.stride);
-      const unsigned grid = (unsigned)m.nblocks;
-      const bool vw = in.scale != nullptr;
-      if (g.stride == 1) {
-        if (vw) { FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_k<T, 1, true>), dim3(grid), dim3(256), 0, st, m)); }
-        else { FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_k<T, 1, false>), dim3(grid), dim3(256), 0, st, m)); }
-      } else {
-        if (vw) { FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_k<T, 2, true>), dim3(grid), dim3(256), 0, st, m)); }
-        else { FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_k<T, 2, false>), dim3(grid), dim3(256), 0, st, m)); }
-      }
-    }
-    sum(m.P);
-    return;
-  }
-  size_t lds;
-  DwPlan d = dw_wgrad_plan(g, es, &lds);
-  if (!dw_check_plan(d, kDwFillNV, g.stride == 2 ? 1 : kDwSegs)) return;     // also: the runs of a tile whose dz a thread holds
-  View v{in.z, in.scale, in.shift, in.act};
-  {
-    KScope ks(st, "dw_wgrad", ((double)g.N * g.Hin * g.Win * g.Cout + (double)g.N * g.Hout * g.Wout * g.Cout) * es + (double)d.nblocks * 9 * g.Cout * 4,
-              18.0 * g.N * g.Hout * g.Wout * g.Cout, (long)g.N * g.Hout * g.Wout, g.Cout, g.stride);
-    const unsigned grid = (unsigned)d.nblocks * d.nslab;
-    if (g.stride == 1) {
-      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_k<T, 1>), dim3(grid), dim3(256), lds, st, (const T*)dz, v, d, g.Hin, g.Win,
-                                          g.Hout, g.Wout, g.Cout, ws));
-    } else {
-      FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_k<T, 2>), dim3(grid), dim3(256), lds, st, (const T*)dz, v, d, g.Hin, g.Win,
-                                          g.Hout, g.Wout, g.Cout, ws));
-    }
-  }
-  sum(d.nblocks);
-}
-
-void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::vector<ReduceJob>* left) {
-  const int es = dt == 0 ? 4 : 2;
-  for (int kind = 0; kind < 4; ++kind) {
-    const int stride = 1 + (kind & 1);
-    const bool vw = (kind & 2) != 0;
-    DwMarchGroup a{};
-    int blocks = 0;
-    double bytes = 0, flops = 0;
-    auto launch = [&]() {
-      if (a.n == 0) return;
-      a.blk0[a.n] = blocks;
-      KScope ks(st, "dw_wgrad", bytes, flops);
-#define FTP_MARCH(S, V) FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_wgrad_march_group_k<T, S, V>), dim3(blocks), dim3(256), 0, st, a))
-      if (stride == 1) { if (vw) FTP_MARCH(1, true); else FTP_MARCH(1, false); }
-      else { if (vw) FTP_MARCH(2, true); else FTP_MARCH(2, false); }
-#undef FTP_MARCH
-      a.n = 0; blocks = 0; bytes = flops = 0;
-    };
-    for (int i = 0; i < n; ++i) {
-      const DwWgradJob& w = jobs[i];
-      if (w.g.stride != stride || (w.in.scale != nullptr) != vw) continue;
-      DwMarchArgs m{};
-      // what another kernel serves (a layer the marching kernel cannot cut into its slabs, the large images) goes by itself
-      if (dw_rows_pays(dt, w.g) || !dw_march_plan(w.g, &m)) { dw_wgrad(dt, st, w.dz, w.in, w.g, w.ws, w.g_w, left); continue; }
-      m.dz = w.dz; m.in = View{w.in.z, w.in.scale, w.in.shift, w.in.act}; m.ws = w.ws;
-      a.blk0[a.n] = blocks;
-      a.job[a.n++] = m;
-      blocks += (m.nblocks + 7) / 8 * 8;
-      bytes += ((double)w.g.N * w.g.Hin * w.g.Win * w.g.Cout + (double)w.g.N * w.g.Hout * w.g.Wout * w.g.Cout) * es + (double)m.P * 9 * w.g.Cout * 4;
-      flops += 18.0 * w.g.N * w.g.Hout * w.g.Wout * w.g.Cout;
-      left->push_back(ReduceJob{w.ws, w.g_w, m.P, 9 * w.g.Cout, w.g.Cout, 1, 9, w.g.Cout});
-      if (a.n == kDwMarchJobs) launch();
-    }
-    launch();
-  }
+  const dim3 grid((unsigned)P * a.d.nslab);
+#define FTP_DW_BWD(T, S, NV)                                                                                  \
+  do {                                                                                                        \
+    if (own) hipLaunchKernelGGL((dw_bwd_k<T, S, true, NV>), grid, dim3(256), lds, st, a);                     \
+    else hipLaunchKernelGGL((dw_bwd_k<T, S, false, NV>), grid, dim3(256), lds, st, a);                        \
+  } while (0)
+  if (g.stride == 2) { if (dt == 0) FTP_DW_BWD(float, 2, 1); else FTP_DW_BWD(bf16_t, 2, 2); }
+  else if (dt == 0) FTP_DW_BWD(float, 1, 3);
+  else if (fill == 3) FTP_DW_BWD(bf16_t, 1, 3);
+  else FTP_DW_BWD(bf16_t, 1, 4);
+#undef FTP_DW_BWD
 }
 
 }  // namespace ftp

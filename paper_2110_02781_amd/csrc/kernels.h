@@ -221,22 +221,13 @@ int dw_bwd_small_ok(const ConvGeom& g);
 void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, const void* w, HView in, const ConvGeom& g,
                   const float* gamma, const float* mean, const float* invstd, float* g_w, float* g_gamma, float* g_beta,
                   void* dz_prev);
-// sums != nullptr (only if dw_dgrad_sums_ok and prev is a view): the kernel also leaves the partial sums
-// [*P_out][2][C] that bn_bwd_reduce would compute for the BatchNorm + activation `prev` in front of this layer
-int dw_dgrad_sums_ok(int dt, const ConvGeom& g);
-void dw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev = HView{},
-              float* sums = nullptr, int* P_out = nullptr);
-// Stride-2 layers (dw_bwd_s2_ws > 0 floats of gw_part) whose input is the view prev: data gradient, those sums, and the weight gradient's partial sums
-// [*P_out][9][C] in one pass
-size_t dw_bwd_s2_ws(int dt, const ConvGeom& g);
-void dw_bwd_s2(int dt, hipStream_t st, const void* dz, const void* w, const ConvGeom& g, void* dIn, HView prev, float* sums, int* P_out, float* gw_part);
-// Weight gradients of several depthwise layers together: the kernels leave partial sums in each job's ws (dw_wgrad_ws
-// floats of its own) and append what is left to sum
-struct DwWgradJob { const void* dz; HView in; ConvGeom g; float* ws; float* g_w; };
-void dw_wgrad_group(int dt, hipStream_t st, const DwWgradJob* jobs, int n, std::vector<ReduceJob>* left);
-size_t dw_wgrad_ws(const ConvGeom& g);
-// left != nullptr: the sum over the partials is appended there instead of done
-void dw_wgrad(int dt, hipStream_t st, const void* dz, HView in, const ConvGeom& g, float* ws, float* g_w, std::vector<ReduceJob>* left = nullptr);
+// The whole backward of a layer in one pass (dIn == nullptr: without the data gradient): from the gradient dA of its activated output own (whose BatchNorm backward it does on the way, from
+// coef or, sums_in != nullptr, from up to 256 partial sums; dIn must not be dA) or, own == nullptr, from dz = dA.  Leaves the weight gradient's
+// partial sums gw_part[P][9][C] (dw_bwd_ws floats) and, sums != nullptr (in is a view), those of the BatchNorm + activation in front [P][2][C]
+int dw_bwd_partials(int dt, const ConvGeom& g);      // P
+size_t dw_bwd_ws(int dt, const ConvGeom& g);
+void dw_bwd(int dt, hipStream_t st, const void* dA, const HView* own, const BnPending* sums_in, const float* coef, float* g_gamma, float* g_beta, const void* w,
+            const ConvGeom& g, void* dIn, HView in, float* sums, float* gw_part);
 
 // ---- pointwise / fully connected GEMMs (MFMA) ---------------------------------------
 // Z[M][N] = A'[M][K] * W[N][K]^T (+ bias[N]); when stats != nullptr also writes the per-column

@@ -272,7 +272,7 @@ struct ftp_stage {
   // measured), per layer as much as a finalize kernel.  Such a unit forks ONCE, behind its last layer: its layers write
   // their dz into a set of three buffers of their own (two sets, alternating from unit to unit), the weight gradients
   // are noted and all enqueued on the side stream at the end of the unit.
-  struct PendingWgrad { int type; const void* dz; HView in; ConvGeom g; size_t M; float* gw; };
+  struct PendingWgrad { const void* dz; HView in; ConvGeom g; size_t M; float* gw; };
   PendingWgrad pend[3];
   int n_pend = 0;
   char* dzring[6] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
@@ -282,7 +282,7 @@ struct ftp_stage {
   int bset = 0;
   bool bset_open = false;      // a layer of the current unit has written into the set
   // A stage that does not run weight gradients on a second stream (ftp_stage_create_ex says when) notes them instead: the
-  // layers' dz and partial sums lie one behind the other in two stores, and the weight gradients of all layers run together at the
+  // layers' dz and partial sums lie one behind the other in two stores, and the pointwise weight gradients of all layers run together at the
   // end of the backward call, a few launches for all of them, or earlier where the next layer does not fit a store any more.
   bool defers = false;
   char* dz_store = nullptr;
@@ -290,7 +290,6 @@ struct ftp_stage {
   size_t dz_cap = 0, dz_used = 0, part_cap = 0, part_used = 0;      // bytes, floats
   PwShare share{0, 0};         // pointwise layers that share the launches of weight gradients
   std::vector<PwWgradJob> q_pw;
-  std::vector<DwWgradJob> q_dw;
   std::vector<ReduceJob> q_red;
   // Partial weight gradients that a stage on two streams leaves on the caller's until the end of the call: those of stride-2 depthwise layers
   // (a place for each in ws_late) and of its first unit's expand layer, behind which nothing is left to run beside.
@@ -458,10 +457,10 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       const bool c1 = sb.type == SUB_DIRECT && conv1d_ok(g) && conv1d_pays(m->dtype, g, i == 0, n_convs == 1, !s->defers);
       const bool patches = sb.type == SUB_DIRECT && !c1;
       p.axis.push_back(c1);
-      size_t need = c1 ? conv1d_wgrad_ws(g) : patches ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_wgrad_ws(g) : pw_wgrad_ws(M, g.Cin, g.Cout);
+      size_t need = c1 ? conv1d_wgrad_ws(g) : patches ? conv_direct_wgrad_ws(g) : sb.type == SUB_DW ? dw_bwd_ws(m->dtype, g) : pw_wgrad_ws(M, g.Cin, g.Cout);
       if (patches && need > ws_floats) ws_floats = need;
-      if (need > layer_ws) layer_ws = need;
-      if (i == a && &sb == &u.subs[0]) s->ws_tail_floats = need;
+      if (sb.type != SUB_DW && need > layer_ws) layer_ws = need;
+      if (i == a && &sb == &u.subs[0] && sb.type != SUB_DW) s->ws_tail_floats = need;
       size_t part = patches ? 0 : need;
       bool at_once = false;
       bool dz_stored = true;             // a layer whose dz is not always stored still counts in dz_max
@@ -475,9 +474,9 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       } else if (sb.type == SUB_DW && u.subs.size() == 3 && dw_bwd_small_ok(g)) {
         dz_stored = false;
         part = 0;
-      } else if (sb.type == SUB_DW && u.subs.size() == 3 && dw_bwd_s2_ws(m->dtype, g) > 0) {     // with the data gradient (sub_backward)
-        part = dw_bwd_s2_ws(m->dtype, g);
-        p.late_part = s->ws_late_floats; s->ws_late_floats += align_up(part, 64);
+      } else if (sb.type == SUB_DW) {
+        p.late_part = s->ws_late_floats; s->ws_late_floats += align_up(need, 64);
+        dz_stored = bn_bwd_small_ok(M, g.Cout) != 0;
       }
       if (zb > dz_max) dz_max = zb;
       dz_bytes += dz_stored ? zb : 0;
@@ -527,7 +526,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
   } else if (layer_ws > ws_floats) ws_floats = layer_ws;
   s->stash_bytes = stash; s->stats_floats = stats; s->max_act_bytes = max_act; s->ws_floats = ws_floats; s->max_c = max_c;
 
-  s->q_pw.reserve(n_convs); s->q_dw.reserve(n_convs); s->q_red.reserve(n_convs); s->q_late.reserve(n_convs);      // a layer leaves at most one of each
+  s->q_pw.reserve(n_convs); s->q_red.reserve(n_convs); s->q_late.reserve(n_convs);      // a layer leaves at most one of each
   int rc = FTP_OK;
   size_t np = s->n_param ? s->n_param : 8;
   size_t nb = s->n_bn ? s->n_bn : 8;
@@ -1143,7 +1142,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   int b = 0, rc_join = 0;
   void* dz = const_cast<void*>(dA);
   // one fork for the whole unit (see PendingWgrad): this layer's dz goes into the unit's buffer set
-  const bool batched = unit_fork && overlap && k < 3 && sb.type != SUB_DIRECT && dIn != nullptr && s->dzring[0] != nullptr &&
+  const bool batched = unit_fork && overlap && k < 3 && sb.type == SUB_PW && dIn != nullptr && s->dzring[0] != nullptr &&
                        M * (size_t)C * s->es <= s->dzring_bytes;
   // An expand layer in bfloat16: behind the BatchNorm reductions the rest of its backward (dz, data gradient,
   // weight gradient) is one pass on this stream; dz never reaches memory.
@@ -1167,6 +1166,46 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       HIP_TRY(hipEventRecord(s->ev_join[2], s->side));
       s->join_pending[2] = true;
     }
+    return FTP_OK;
+  }
+  // A depthwise layer: behind the sums of its BatchNorm one pass does the rest, and leaves the sums of the BatchNorm in front
+  // and the weight gradient's partials.  dIn is not dA.
+  if (sb.type == SUB_DW) {
+    const bool small = bn_bwd_small_ok(M, C) != 0;
+    Places at{nullptr, s->ws_late + p.late_part};
+    if (s->defers) {
+      at = take_places(s, small ? dz_size(s, sb) : 0, p.part[k], st);
+    } else if (small) {
+      b = (int)(s->n_sub_bwd++ & 1u);
+      at.dz = s->gbuf[b ? 4 : 2];
+      if (s->join_pending[b]) {            // the weight gradient that last read this dz buffer must be done
+        HIP_TRY(hipStreamWaitEvent(st, s->ev_join[b], 0));
+        s->join_pending[b] = false;
+      }
+    }
+    const float* gamma = W.w32 + p.p_off + sb.gamma_off;
+    float *gg = s->grads + p.p_off + sb.gamma_off, *gb = s->grads + p.p_off + sb.beta_off;
+    const int P = dw_bwd_partials(s->dt, g);
+    ftp_stage::LeftSums sums = take_sums(s, dA);
+    BnPending left{};
+    float* fill = s->bn_part;
+    if (small) {
+      bn_bwd_small(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, gamma, stt, stt + C, gg, gb, at.dz);
+    } else {
+      if (!sums.of) bn_bwd_reduce(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, sums.partial = s->bn_part, &sums.P);
+      if (bn_finish_ok(M, C, sums.P) && P <= kBnPartials / 2) {
+        left = BnPending{sums.partial, sums.P, M, gamma, nullptr, stt, stt + C, nullptr, nullptr, nullptr, nullptr};
+        if (sums.partial == fill) fill = other_partials(s);
+      } else {
+        bn_bwd_finalize(st, sums.partial, sums.P, M, C, gamma, stt, stt + C, gg, gb, s->coef);
+      }
+    }
+    // behind another layer's BatchNorm: dIn is the gradient of its activated output
+    if (!dIn || in.scale == nullptr || bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cin)) fill = nullptr;
+    dw_bwd(s->dt, st, small ? at.dz : dA, small ? nullptr : &out, left.partial ? &left : nullptr, s->coef, gg, gb, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in,
+           fill, at.part);
+    if (fill) leave_sums(s, dIn, fill, P);
+    (s->defers ? s->q_red : s->q_late).push_back(ReduceJob{at.part, s->grads + p.p_off + sb.w_off, P, 9 * C, C, 1, 9, C});
     return FTP_OK;
   }
   // noted for the end of the backward call: dz stays where it is written until then
@@ -1228,25 +1267,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       bn_bwd_apply(s->dt, st, dA, out.z, M, C, out.scale, out.shift, sb.act, s->coef, dz);
   }
   hipStream_t ws = st;
-  // The depthwise data gradient and weight gradient want the same units (LDS tiles, vector ALU): side by side each
-  // takes nearly twice as long.  The data gradient goes first, alone; the weight gradient then shares the GPU with
-  // the memory-bound BatchNorm backward of the layer in front.
-  const bool dgrad_first = overlap && sb.type == SUB_DW && dIn != nullptr;
   s->left.of = nullptr;                // where the caller formed dz
-  // a depthwise layer behind a BatchNorm + activation of the same unit (the expand layer's): its data gradient is that
-  // BatchNorm's dA and can leave the backward sums on the way
-  const bool prev_sums = sb.type == SUB_DW && dIn != nullptr && mode == BWD_FULL && k > 0 && in.scale != nullptr &&
-                         !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cout);
-  const bool with_sums = prev_sums && dw_dgrad_sums_ok(s->dt, g);
-  auto run_dw_dgrad = [&]() {
-    if (with_sums) {
-      int P = 0;
-      dw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, s->bn_part, &P);
-      leave_sums(s, dIn, s->bn_part, P);
-    } else {
-      dw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn);
-    }
-  };
   auto run_conv1d_dgrad = [&]() {
     // behind another convolution of the stage: this is the dA of that one's BatchNorm + activation
     const bool sums = in.scale != nullptr && !bn_bwd_small_ok((size_t)s->batch * g.Hin * g.Win, g.Cin);
@@ -1254,21 +1275,11 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     conv1d_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, sums ? s->bn_part : nullptr, &P);
     if (sums) leave_sums(s, dIn, s->bn_part, P);
   };
-  if (prev_sums && dw_bwd_s2_ws(s->dt, g) > 0) {        // at stride 2 the weight gradient comes with it
-    int P = 0;
-    float* const gp = s->defers ? part : s->ws_late + p.late_part;
-    dw_bwd_s2(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), g, dIn, in, s->bn_part, &P, gp);
-    leave_sums(s, dIn, s->bn_part, P);
-    (s->defers ? s->q_red : s->q_late).push_back(ReduceJob{gp, s->grads + p.p_off + sb.w_off, P, 9 * C, C, 1, 9, C});
-    return FTP_OK;
-  }
-  if (dgrad_first) run_dw_dgrad();
   if (batched && mode == BWD_FULL) {
     // noted for the unit's fork; the data gradient goes on as it would behind a forked weight gradient
     if (s->n_pend >= 3) { ftp_set_error("stage_backward: more weight gradients noted for a unit than it has layers"); return FTP_ERR_UNSUPPORTED; }
-    s->pend[s->n_pend++] = ftp_stage::PendingWgrad{sb.type, dz, in, g, M, s->grads + p.p_off + sb.w_off};
-    if (sb.type == SUB_PW) pw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), res, M, g.Cin, g.Cout, dIn);
-    else if (!dgrad_first) run_dw_dgrad();
+    s->pend[s->n_pend++] = ftp_stage::PendingWgrad{dz, in, g, M, s->grads + p.p_off + sb.w_off};
+    pw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), res, M, g.Cin, g.Cout, dIn);
     return FTP_OK;
   }
   if (noted) {
@@ -1282,9 +1293,6 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       int P = 0;
       if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn, z_sum, z_sum ? s->bn_part : nullptr, &P);
       if (z_sum && dIn) leave_sums(s, dIn, s->bn_part, P);
-    } else if (sb.type == SUB_DW) {
-      s->q_dw.push_back(DwWgradJob{dz, in, g, part, gw});
-      if (dIn) run_dw_dgrad();
     } else if (dIn && conv1d_small_ok(g)) {
       float* const fill = conv1d_leaves_sums(s, &p - s->plan.data()) ? s->bn_part : nullptr;
       int P = 0;
@@ -1324,8 +1332,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     conv_direct_wgrad(s->dt, ws, dz, in, g, s->im2col, wsp, gw, s->im2col_of == out.z);
     s->im2col_of = nullptr;      // one weight gradient per forward: nobody else can want these patches
   }
-  else if (sb.type == SUB_PW) pw_wgrad(s->dt, ws, dz, in, M, g.Cin, g.Cout, wsp, gw);
-  else dw_wgrad(s->dt, ws, dz, in, g, wsp, gw);
+  else pw_wgrad(s->dt, ws, dz, in, M, g.Cin, g.Cout, wsp, gw);
   if (overlap && !tail_here) {
     HIP_TRY(hipEventRecord(s->ev_join[b], s->side));
     s->join_pending[b] = true;
@@ -1341,8 +1348,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       }
       else conv_direct_dgrad(s->dt, st, dz, w, g, dIn);
     }
-    else if (sb.type == SUB_PW) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);
-    else if (!dgrad_first) run_dw_dgrad();
+    else pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);
   }
   return FTP_OK;
 }
@@ -1350,10 +1356,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
 // every weight gradient noted so far, and the sums of what the kernels left
 static void run_noted(ftp_stage* s, hipStream_t st) {
   pw_wgrad_group(s->dt, st, s->q_pw.data(), (int)s->q_pw.size(), s->share, &s->q_red);
-  dw_wgrad_group(s->dt, st, s->q_dw.data(), (int)s->q_dw.size(), &s->q_red);
   reduce_group(st, s->q_red.data(), (int)s->q_red.size());
   reduce_group(st, s->q_late.data(), (int)s->q_late.size());
-  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear(); s->q_late.clear();
+  s->q_pw.clear(); s->q_red.clear(); s->q_late.clear();
   s->dz_used = s->part_used = 0;         // what reads the stores is ahead of what this stream writes there next
 }
 
@@ -1365,8 +1370,7 @@ static int flush_unit_fork(ftp_stage* s, hipStream_t st) {
   HIP_TRY(hipStreamWaitEvent(s->side, s->ev_bfork[s->bset], 0));
   for (int i = 0; i < s->n_pend; ++i) {
     const ftp_stage::PendingWgrad& w = s->pend[i];
-    if (w.type == SUB_PW) pw_wgrad(s->dt, s->side, w.dz, w.in, w.M, w.g.Cin, w.g.Cout, s->ws, w.gw);
-    else dw_wgrad(s->dt, s->side, w.dz, w.in, w.g, s->ws, w.gw);
+    pw_wgrad(s->dt, s->side, w.dz, w.in, w.M, w.g.Cin, w.g.Cout, s->ws, w.gw);
   }
   HIP_TRY(hipEventRecord(s->ev_bjoin[s->bset], s->side));
   s->bjoin_pending[s->bset] = true;
@@ -1417,7 +1421,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
     if (rc) return rc;
     s->stash_owner = slot;
   }
-  s->q_pw.clear(); s->q_dw.clear(); s->q_red.clear(); s->q_late.clear();
+  s->q_pw.clear(); s->q_red.clear(); s->q_late.clear();
   s->dz_used = s->part_used = 0;
   s->left.of = nullptr;
   s->n_pend = 0; s->bset_open = false;              // nothing is left noted by a call that ended in an error
@@ -1471,13 +1475,15 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
         break;
       case FTP_UNIT_INVRES: {
         size_t ns = u.subs.size();
-        void* tmp = s->gbuf[3];
+        // the gradients of the depthwise layer's output and input lie in different buffers; the boundary buffer that the unit's input gradient will take is
+        // free until then
+        void *tmp = s->gbuf[3], *mid = ns == 3 || u.residual ? (void*)s->gbuf[flip] : tmp;
         // project: gradient of the activated depthwise output
         // one fork for the unit when every layer's dz fits the small buffer sets
         bool uf = ns == 3 && s->dzring[0] != nullptr;
         for (const Sub& sb : u.subs)
           if ((size_t)s->batch * sb.g.Hout * sb.g.Wout * sb.g.Cout * s->es > s->dzring_bytes) uf = false;
-        if ((rc = sub_backward(s, sl, p, ns - 1, d, v.sub_out[i][ns - 2], v.sub_out[i][ns - 1], tmp, nullptr, W, st, BWD_FULL, uf))) return rc;
+        if ((rc = sub_backward(s, sl, p, ns - 1, d, v.sub_out[i][ns - 2], v.sub_out[i][ns - 1], mid, nullptr, W, st, BWD_FULL, uf))) return rc;
         ConvGeom gd = ns == 3 ? u.subs[1].g : ConvGeom{};
         gd.N = s->batch;
         if (ns == 3 && s->defers && dw_bwd_small_ok(gd)) {
@@ -1489,7 +1495,7 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
           void* dz1 = at.dz;
           float* st0 = sl.stats + p.st_off[0];
           float* st1 = sl.stats + p.st_off[1];
-          BnBwdIn bo{tmp, v.sub_out[i][1], W.w32 + p.p_off + s1.gamma_off, st1, st1 + s1.g.Cout,
+          BnBwdIn bo{mid, v.sub_out[i][1], W.w32 + p.p_off + s1.gamma_off, st1, st1 + s1.g.Cout,
                      s->grads + p.p_off + s1.gamma_off, s->grads + p.p_off + s1.beta_off};
           dw_bwd_small(s->dt, st, nullptr, bo, conv_w(s, W, p.p_off + s1.w_off), v.sub_out[i][0], gd, W.w32 + p.p_off + s0.gamma_off, st0,
                        st0 + s0.g.Cout, s->grads + p.p_off + s1.w_off, s->grads + p.p_off + s0.gamma_off,
@@ -1497,16 +1503,16 @@ extern "C" int ftp_stage_backward(ftp_stage* s, int slot, const void* dy_dev, vo
           if ((rc = sub_backward(s, sl, p, 0, dz1, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FROM_DZ, false, at.part,
                                  leaves_sums(s, v, i)))) return rc;
         } else if (ns == 3) {
-          if ((rc = sub_backward(s, sl, p, 1, tmp, v.sub_out[i][0], v.sub_out[i][1], tmp, nullptr, W, st, BWD_FULL, uf))) return rc;
+          if ((rc = sub_backward(s, sl, p, 1, mid, v.sub_out[i][0], v.sub_out[i][1], tmp, nullptr, W, st, BWD_FULL, uf))) return rc;
           if ((rc = sub_backward(s, sl, p, 0, tmp, in, v.sub_out[i][0], next, u.residual ? d : nullptr, W, st, BWD_FULL, uf, nullptr,
                                  leaves_sums(s, v, i)))) return rc;
           if ((rc = flush_unit_fork(s, st))) return rc;
         } else {
           if (next && u.residual) {
-            if ((rc = sub_backward(s, sl, p, 0, tmp, in, v.sub_out[i][0], tmp, nullptr, W, st))) return rc;
+            if ((rc = sub_backward(s, sl, p, 0, mid, in, v.sub_out[i][0], tmp, nullptr, W, st))) return rc;
             bn_apply(s->dt, st, plain(tmp), (size_t)s->batch * u.inH * u.inW, u.inC, d, next);
           } else {
-            if ((rc = sub_backward(s, sl, p, 0, tmp, in, v.sub_out[i][0], next, nullptr, W, st))) return rc;
+            if ((rc = sub_backward(s, sl, p, 0, mid, in, v.sub_out[i][0], next, nullptr, W, st))) return rc;
           }
         }
         break;

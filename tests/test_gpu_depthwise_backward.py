@@ -1,0 +1,70 @@
+"""Depthwise layers backward in one pass (csrc/k_conv.hip, dw_bwd_k): data gradient, weight gradient and the BatchNorm sums of the layer in front, which has no
+pass of its own for them, against the float64 oracle."""
+import pytest
+
+import synth
+from harness import Pair, TOL, assert_close, launches
+from oracle import layers as L
+from oracle import models as OM
+
+pytestmark = pytest.mark.gpu
+
+# (stride, cin, cout, expand, h, w, batch, copies in the batch).  Fewer tiles than partials, one more than as many, two and three to a block with a
+# last block of fewer; odd sizes, a tile of one row and of one column; slabs of 1, 3, 6 and 8 column groups, a last slab of fewer; images of 7, 14 and 28
+# rows (tiles of 7 in bfloat16) and one row more; an output of up to 2048 rows (its BatchNorm backward is a launch of its own)
+CASES = [(2, 8, 16, 3, 41, 51, 1, 1), (2, 16, 24, 6, 9, 17, 19, 1), (2, 8, 8, 3, 8, 16, 513, 27), (2, 24, 16, 6, 33, 35, 60, 6), (2, 16, 32, 4, 45, 50, 48, 4),
+         (2, 8, 16, 6, 2, 1030, 8, 1), (2, 16, 16, 6, 7, 1, 700, 35),
+         (1, 8, 16, 3, 41, 51, 1, 1), (1, 16, 24, 6, 14, 14, 32, 4), (1, 16, 16, 5, 15, 14, 33, 3), (1, 24, 24, 6, 28, 30, 4, 1), (1, 8, 8, 3, 8, 16, 513, 27),
+         (1, 24, 16, 6, 33, 35, 60, 6), (1, 88, 40, 6, 7, 7, 64, 8), (1, 8, 16, 6, 2, 1030, 3, 1), (1, 16, 8, 6, 2051, 1, 1, 1)]
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stride,cin,cout,expand,h,w,batch,tile", CASES)
+def test_depthwise_backward_in_one_pass(dtype, stride, cin, cout, expand, h, w, batch, tile):
+    import paper_2110_02781_amd.binding as B
+    print(f"depthwise backward {dtype} stride {stride} {cin}->{cout} x{expand} {h}x{w} batch {batch}", flush=True)
+    o = [OM.Unit('invres', cin, cout, stride=stride, expand=expand)]
+    hu = [dict(kind=B.UNIT_INVRES, cin=cin, cout=cout, stride=stride, expand=expand)]
+    pair = Pair(o, hu, (h, w, cin), batch, 0, 1, dtype, seed=8, ties="bounded", tile=tile)
+    try:
+        y, yo = pair.forward(0, synth.normal(51, "x", (batch // tile, h, w, cin)))
+        assert_close(y, yo, TOL[dtype], "y")
+        got = []
+        n = launches(lambda: got.append(pair.backward(0, synth.normal(51, "dy", (batch // tile,) + tuple(pair.out_shape)))))
+        rows = batch * -(-h // stride) * -(-w // stride)
+        assert n.get("bn_bwd_reduce", 0) == (2 if rows > 2048 else 0) and n.get("dw_bwd", 0) == 1, n
+        assert_close(*got[0], TOL[dtype], "dx")
+        pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
+        pair.compare_unit_vectors("bn", TOL[dtype])
+    finally:
+        pair.close()
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stem,stride,cin,cout,h,w,batch", [(True, 1, 16, 24, 41, 51, 2), (True, 2, 24, 16, 30, 45, 4), (True, 1, 16, 16, 41, 51, 2), (False, 1, 24, 24, 37, 60, 3),
+                                                            (False, 2, 16, 24, 61, 55, 3), (False, 1, 16, 8, 9, 9, 3)])
+def test_depthwise_layer_without_expansion(dtype, stem, stride, cin, cout, h, w, batch):
+    """Its input is the view of a convolution in front (whose BatchNorm gets its sums, unless a residual is added on the way) or as it is stored; a
+    second backward without an input gradient adds to the first one's gradients."""
+    import paper_2110_02781_amd.binding as B
+    print(f"depthwise backward, no expansion {dtype} stem {stem} stride {stride} {cin}->{cout} {h}x{w} batch {batch}", flush=True)
+    o = [OM.Unit('invres', cin, cout, stride=stride, expand=1)]
+    hu = [dict(kind=B.UNIT_INVRES, cin=cin, cout=cout, stride=stride, expand=1)]
+    if stem:
+        o.insert(0, OM.Unit('conv', 8, cin, act=L.ACT_RELU6))
+        hu.insert(0, dict(kind=B.UNIT_CONV, cin=8, cout=cin, kh=1, kw=1, stride=1, pad_h=0, pad_w=0, act=B.ACT_RELU6))
+    c = 8 if stem else cin
+    pair = Pair(o, hu, (h, w, c), batch, 0, len(o), dtype, n_slots=2, seed=8, ties="bounded")
+    try:
+        for slot in range(2):
+            y, yo = pair.forward(slot, synth.normal(51, f"x{slot}", (batch, h, w, c)))
+            assert_close(y, yo, TOL[dtype], "y")
+        for slot in range(2):
+            got = []
+            n = launches(lambda: got.append(pair.backward(slot, synth.normal(51, f"dy{slot}", yo.shape), want_dx=slot == 0)))
+            assert n.get("dw_bwd", 0) == 1, n
+            if slot == 0:
+                assert_close(*got[0], TOL[dtype], "dx")
+            pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
+    finally:
+        pair.close()
