@@ -1117,6 +1117,9 @@ void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, con
 // some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.57 ms a step; their data
 // and weight gradients were 1.80 and the passes for dz and the sums another 0.9, on two streams (a step 7.27 -> 6.79 ms; 224x224 fp32 3.51 -> 3.21).
 // bfloat16 tiles of 8 x 16 at stride 1: 207 registers, two blocks to a CU, or scratch with three: 1.12 and 1.24 ms for the stride-1 layers, 1.03 so.
+// ONE: a block of a single tile requests the tile together with the weights and the partial sums.  The eleven sums of a block leave in one round
+// through LDS, a wavefront to each in turn.  Both against a request after the prologue and four rounds of twelve numbers: the width-1.4 step
+// 6.82 -> 6.77 ms, a 13-image step of width 0.5 at 161x193 1.070 -> 1.061.
 struct DwBwdArgs {
   const void *dA, *w;       // dA: dz if nothing is to be formed
   View own;                 // the layer's own output (FORM)
@@ -1135,11 +1138,11 @@ template <typename T, int S> struct DwBwd {
          NR = S == 1 || F32 ? 1 : 2,                                             // rounds of a tile's runs or quads
          VS = F32 ? 32 : 64, PH = S == 1 ? 10 : 5, PW = S == 1 ? TW + 2 : 9 };          // the patch has its largest size whatever the tile: offsets are constants
   typedef typename std::conditional<S == 1, float, T>::type P;                                  // patch elements
-  enum { PATCH = PH * PW * VS * sizeof(P) > kSlabSumsBytes ? PH * PW * VS * sizeof(P) : kSlabSumsBytes, LDS = PATCH + 9 * VS * 4 };
+  enum { PATCH = PH * PW * VS * sizeof(P) > kSlabSumsBytes ? PH * PW * VS * sizeof(P) : kSlabSumsBytes, STAGED = PATCH + 9 * VS * 4,
+         RED = 11 * 256 * 16, LDS = STAGED > RED ? STAGED : RED };
 };
-template <typename T, int S, bool FORM, int NV>
+template <typename T, int S, bool FORM, int NV, bool ONE>
 __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // three blocks to a CU: 168 registers
-
   typedef DwBwd<T, S> X;
   typedef typename X::P PT;
   constexpr int NR = X::NR, VS = X::VS, PW = X::PW;
@@ -1155,6 +1158,72 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
   const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB, c4 = cq * 4, gc = cg0 * 8 + c4;
   const int nc = min(C - cg0 * 8, d.CGB * 8);
   const bool worker = seg0 < d.spp && gc < C, viewed = p.prev.scale != nullptr;
+  const float plo = act_lo(p.prev.act), phi = act_hi(p.prev.act), olo = act_lo(p.own.act), ohi = act_hi(p.own.act);
+  // staging: thread = (pixel lane, column group)
+  const int pl = dw_div(threadIdx.x, d.m_cgb), cg = threadIdx.x - pl * d.CGB;
+  const bool stager = pl < d.PPB && cg0 + cg < C / 8;
+  const int dph = dw_div(d.PPB, d.m_pw), dpw = d.PPB - dph * d.PW;
+  const int ph_first = dw_div(pl, d.m_pw), pw_first = pl - ph_first * d.PW;
+  int tw = t0 % d.tiles_w, th = t0 / d.tiles_w % d.tiles_h, n = t0 / (d.tiles_w * d.tiles_h);
+  // a tile on its way: its patch, the input under it, and where they lie
+  Raw<T> ra[NV], rz[FORM ? NV : 1];
+  Raw4<T> zp[NR][4];
+  unsigned ok = 0, inside = 0, at[NR];                // vectors and pixels inside the image; pixel of this thread's first run or quad
+  int lds[NR], ph0 = 0, pw0 = 0;                      // where its dz lies in the patch, negative: none
+  bool all_in = false;
+  T* out = nullptr;
+  auto request = [&]() __attribute__((always_inline)) {
+    const int h0 = th * d.TH, w0 = tw * d.TW, ph_lo = S == 1 ? h0 - 1 : h0 / 2, pw_lo = S == 1 ? w0 - 1 : w0 / 2;
+    // Where a thread works is decoded again for every tile: kept over the loop, the compiler holds some eighty registers of addresses
+    ph0 = ph_first; pw0 = pw_first;
+    int sg0 = seg0;
+    asm volatile("" : "+v"(ph0), "+v"(pw0), "+v"(sg0));
+    // the patch and the input under it, all requested together and unconditionally (outside: the image's first pixel, not used)
+    ok = inside = 0;
+    {
+      const size_t img = (size_t)n * p.Hout * p.Wout * C + (stager ? (cg0 + cg) * 8 : 0);
+      const T* A = reinterpret_cast<const T*>(p.dA) + img;
+      const T* O = reinterpret_cast<const T*>(p.own.z) + img;
+      unsigned off[NV];
+      int ph = ph0, pw = pw0;
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        const int h = ph_lo + ph, x = pw_lo + pw;
+        const bool in = stager && ph < d.PH && (unsigned)h < (unsigned)p.Hout && (unsigned)x < (unsigned)p.Wout;
+        off[q] = in ? __umul24(__umul24(h, p.Wout) + x, C) : 0u;
+        ok |= (in ? 1u : 0u) << q;
+        ph += dph; pw += dpw;
+        if (pw >= d.PW) { pw -= d.PW; ++ph; }
+      }
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        raw_load(ra[q], A + off[q]);
+        if (FORM) raw_load(rz[FORM ? q : 0], O + off[q]);
+      }
+    }
+    // nothing of the tile or its patch lies outside the image: a branch for the wavefront instead of a mask for every value
+    all_in = h0 + d.TH <= Hin && w0 + d.TW <= Win && d.TW % 4 == 0 && d.TH % 2 == 0 && ph_lo >= 0 && pw_lo >= 0 && ph_lo + d.PH <= p.Hout && pw_lo + d.PW <= p.Wout;
+    const size_t img = (size_t)n * Hin * Win * C + (worker ? gc : 0);
+    const T* const Z = reinterpret_cast<const T*>(p.prev.z) + img;
+    out = reinterpret_cast<T*>(p.dIn) + img;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int sg = sg0 + r * d.spp;
+      const bool has = worker && sg < d.nseg;
+      const int hl = dw_div(has ? sg : 0, d.m_segw), wl0 = (has ? sg : 0) - hl * d.segw, h = h0 + hl * S, x = w0 + wl0 * (S == 1 ? 4 : 2);
+      lds[r] = has ? (hl * PW + wl0 * (S == 1 ? 4 : 1)) * VS + c4 : -1;
+      at[r] = __umul24(h, Win) + x;
+#pragma unroll
+      for (int o = 0; o < 4; ++o) {
+        const bool in = has && h + (S == 1 ? 0 : o >> 1) < Hin && x + (S == 1 ? o : o & 1) < Win;
+        inside |= (in ? 1u : 0u) << (4 * r + o);
+        raw4_load(zp[r][o], Z + (in ? __umul24(at[r] + (S == 1 ? o : (o >> 1) * Win + (o & 1)), C) : 0u));
+      }
+    }
+  };
+  // a block of a single tile: what depends on nothing is requested together, the tile, the weights and the sums (in front of a loop the compiler has no
+  // registers for that)
+  if (ONE) request();
   T w0[(9 * VS + 255) / 256];
 #pragma unroll
   for (int q = 0; q < (9 * VS + 255) / 256; ++q) {
@@ -1193,66 +1262,9 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
   float4 aw[9], s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1;
 #pragma unroll
   for (int t = 0; t < 9; ++t) aw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
-  const float plo = act_lo(p.prev.act), phi = act_hi(p.prev.act), olo = act_lo(p.own.act), ohi = act_hi(p.own.act);
-  // staging: thread = (pixel lane, column group)
-  const int pl = dw_div(threadIdx.x, d.m_cgb), cg = threadIdx.x - pl * d.CGB;
-  const bool stager = pl < d.PPB && cg0 + cg < C / 8;
-  const int dph = dw_div(d.PPB, d.m_pw), dpw = d.PPB - dph * d.PW;
-  const int ph_first = dw_div(pl, d.m_pw), pw_first = pl - ph_first * d.PW;
-  int tw = t0 % d.tiles_w, th = t0 / d.tiles_w % d.tiles_h, n = t0 / (d.tiles_w * d.tiles_h);
-  for (int tile = t0; tile < t1; ++tile) {
-    const int h0 = th * d.TH, w0 = tw * d.TW, ph_lo = S == 1 ? h0 - 1 : h0 / 2, pw_lo = S == 1 ? w0 - 1 : w0 / 2;
-    // Where a thread works is decoded again for every tile: kept over the loop, the compiler holds some eighty registers of addresses
-    int ph0 = ph_first, pw0 = pw_first, sg0 = seg0;
-    asm volatile("" : "+v"(ph0), "+v"(pw0), "+v"(sg0));
-    // the patch and the input under it, all requested together and unconditionally (outside: the image's first pixel, not used)
-    Raw<T> ra[NV], rz[FORM ? NV : 1];
-    unsigned ok = 0;
-    {
-      const size_t img = (size_t)n * p.Hout * p.Wout * C + (stager ? (cg0 + cg) * 8 : 0);
-      const T* A = reinterpret_cast<const T*>(p.dA) + img;
-      const T* O = reinterpret_cast<const T*>(p.own.z) + img;
-      unsigned off[NV];
-      int ph = ph0, pw = pw0;
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        const int h = ph_lo + ph, x = pw_lo + pw;
-        const bool in = stager && ph < d.PH && (unsigned)h < (unsigned)p.Hout && (unsigned)x < (unsigned)p.Wout;
-        off[q] = in ? __umul24(__umul24(h, p.Wout) + x, C) : 0u;
-        ok |= (in ? 1u : 0u) << q;
-        ph += dph; pw += dpw;
-        if (pw >= d.PW) { pw -= d.PW; ++ph; }
-      }
-#pragma unroll
-      for (int q = 0; q < NV; ++q) {
-        raw_load(ra[q], A + off[q]);
-        if (FORM) raw_load(rz[FORM ? q : 0], O + off[q]);
-      }
-    }
-    // nothing of the tile or its patch lies outside the image: a branch for the wavefront instead of a mask for every value
-    const bool all_in = h0 + d.TH <= Hin && w0 + d.TW <= Win && d.TW % 4 == 0 && d.TH % 2 == 0 && ph_lo >= 0 && pw_lo >= 0 && ph_lo + d.PH <= p.Hout && pw_lo + d.PW <= p.Wout;
-    const size_t img = (size_t)n * Hin * Win * C + (worker ? gc : 0);
-    const T* const Z = reinterpret_cast<const T*>(p.prev.z) + img;
-    T* const out = reinterpret_cast<T*>(p.dIn) + img;
-    Raw4<T> zp[NR][4];
-    int lds[NR];                                      // this thread's runs or quads in the tile: where their dz lies, negative: none
-    unsigned at[NR];                                  // pixel of the first
-    unsigned inside = 0;
-#pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const int sg = sg0 + r * d.spp;
-      const bool has = worker && sg < d.nseg;
-      const int hl = dw_div(has ? sg : 0, d.m_segw), wl0 = (has ? sg : 0) - hl * d.segw, h = h0 + hl * S, x = w0 + wl0 * (S == 1 ? 4 : 2);
-      lds[r] = has ? (hl * PW + wl0 * (S == 1 ? 4 : 1)) * VS + c4 : -1;
-      at[r] = __umul24(h, Win) + x;
-#pragma unroll
-      for (int o = 0; o < 4; ++o) {
-        const bool in = has && h + (S == 1 ? 0 : o >> 1) < Hin && x + (S == 1 ? o : o & 1) < Win;
-        inside |= (in ? 1u : 0u) << (4 * r + o);
-        raw4_load(zp[r][o], Z + (in ? __umul24(at[r] + (S == 1 ? o : (o >> 1) * Win + (o & 1)), C) : 0u));
-      }
-    }
-    if (tile > t0) __syncthreads();                   // the tile before has been read
+  for (int tile = t0; tile < (ONE ? t0 + 1 : t1); ++tile) {
+    if (!ONE) request();
+    if (!ONE && tile > t0) __syncthreads();           // the tile before has been read
     asm volatile("" ::: "memory");                    // the coefficients come from LDS again, not out of forty registers
     if (pl < d.PPB) {
 #pragma unroll
@@ -1345,24 +1357,23 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
       }
     }
   }
-  float* red = reinterpret_cast<float*>(smem_raw);
+  // The runs of a channel quad are spread over spp threads: eleven vectors of each through LDS, summed in a fixed order, a wavefront to each vector in turn
+  float4* const red = reinterpret_cast<float4*>(smem_raw);         // [11][256]
   __syncthreads();
-  if (p.sums) dw_leave_sums(s1, s2, worker, seg0, cq, QB, cg0, C, d.spp, red, p.sums + (size_t)part * 2 * C);
-  // three taps at a time: [spp][QB][12]
+  const int tid = threadIdx.x, wave = tid >> 6, ch = tid & 63;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    __syncthreads();
-    if (worker)
-#pragma unroll
-      for (int j = 0; j < 3; ++j) *reinterpret_cast<float4*>(red + ((size_t)seg0 * QB + cq) * 12 + j * 4) = aw[i * 3 + j];
-    __syncthreads();
-    for (int v = threadIdx.x; v < QB * 12; v += 256) {
-      const int q = v / 12, e = v - q * 12, c = cg0 * 8 + q * 4 + (e & 3);
-      if (c >= C) continue;
-      float t = 0.f;
-      for (int sgi = 0; sgi < d.spp; ++sgi) t += red[((size_t)sgi * QB + q) * 12 + e];
-      p.gw[((size_t)part * 9 + i * 3 + (e >> 2)) * C + c] = t;
-    }
+  for (int t = 0; t < 9; ++t) red[t * 256 + tid] = aw[t];
+  red[9 * 256 + tid] = s1;
+  red[10 * 256 + tid] = s2;
+  __syncthreads();
+  if (ch >= nc) return;
+  for (int v = wave; v < (p.sums ? 11 : 9); v += 4) {
+    const float* src = reinterpret_cast<const float*>(red + v * 256) + ch;
+    float t = 0.f;
+#pragma unroll 8
+    for (int sgi = 0; sgi < d.spp; ++sgi) t += src[sgi * QB * 4];
+    float* dst = v < 9 ? p.gw + ((size_t)part * 9 + v) * C : p.sums + ((size_t)part * 2 + v - 9) * C;
+    dst[cg0 * 8 + ch] = t;
   }
 }
 
@@ -1414,19 +1425,19 @@ void dw_bwd(int dt, hipStream_t st, const void* dA, const HView* own, const BnPe
   a.prev = DwPrev{in.z, in.scale, in.shift, in.act};
   if (a.d.PH > (g.stride == 1 ? 10 : 5) || a.d.PW > (g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::PW : DwBwd<bf16_t, 1>::PW) : 9)) { launch_plan_failed("depthwise backward patch beyond the kernel's"); return; }
   size_t lds = g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::LDS : DwBwd<bf16_t, 1>::LDS) : (dt == 0 ? DwBwd<float, 2>::LDS : DwBwd<bf16_t, 2>::LDS);
-  const size_t red = (size_t)a.d.spp * 2 * a.d.CGB * 12 * sizeof(float);
-  if (lds < red) lds = red;
   const dim3 grid((unsigned)P * a.d.nslab);
-#define FTP_DW_BWD(T, S, NV)                                                                                  \
+#define FTP_DW_BWD1(T, S, NV, ONE)                                                                            \
   do {                                                                                                        \
-    if (own) hipLaunchKernelGGL((dw_bwd_k<T, S, true, NV>), grid, dim3(256), lds, st, a);                     \
-    else hipLaunchKernelGGL((dw_bwd_k<T, S, false, NV>), grid, dim3(256), lds, st, a);                        \
+    if (own) hipLaunchKernelGGL((dw_bwd_k<T, S, true, NV, ONE>), grid, dim3(256), lds, st, a);                \
+    else hipLaunchKernelGGL((dw_bwd_k<T, S, false, NV, ONE>), grid, dim3(256), lds, st, a);                   \
   } while (0)
+#define FTP_DW_BWD(T, S, NV) do { if (a.per == 1) FTP_DW_BWD1(T, S, NV, true); else FTP_DW_BWD1(T, S, NV, false); } while (0)
   if (g.stride == 2) { if (dt == 0) FTP_DW_BWD(float, 2, 1); else FTP_DW_BWD(bf16_t, 2, 2); }
   else if (dt == 0) FTP_DW_BWD(float, 1, 3);
   else if (fill == 3) FTP_DW_BWD(bf16_t, 1, 3);
   else FTP_DW_BWD(bf16_t, 1, 4);
 #undef FTP_DW_BWD
+#undef FTP_DW_BWD1
 }
 
 }  // namespace ftp
