@@ -873,143 +873,139 @@ void dw_fwd_bn_small(int dt, hipStream_t st, HView in, const BnPending& pend, co
                                       gamma, beta, mean, invstd, scale, shift, run_mean, run_var, eps, momentum, (T*)z));
 }
 
-// Backward of a depthwise layer and of the BatchNorm in front of it.  A thread owns input pixels; it gathers the
-// dz values that reach a pixel once (from the LDS copy) and uses each twice: times the tap weight for the data
-// gradient, times the pixel's own activation for the weight gradient (dW[tap] = sum_p dz[p] * a[p*s-1+tap] is
-// the same sum walked from the input side).  The data gradient never leaves the registers: it is gated by the
-// activation, reduced into the BatchNorm sums, and after the block-wide reduction turned into the gradient of
-// the raw convolution output in front (dz_prev).  Replaces depthwise dgrad + wgrad + partial reduction +
-// BatchNorm backward.
-template <typename T, int RPT>
-__global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, BnBwdIn bo, const T* __restrict__ w, View in,
-                                                      ConvGeom g, FastDiv dW, FastDiv dH, int M, int Mout, const float* __restrict__ gamma,
-                                                      const float* __restrict__ mean, const float* __restrict__ invstd, float* g_w,
-                                                      float* g_gamma, float* g_beta, T* __restrict__ dz_prev) {
+// V channels of one pixel, as floats
+template <int V> struct alignas(4 * V) Chans { float v[V]; };
+__device__ __forceinline__ Chans<4> load_chans(const float* p, Chans<4>*) { const float4 f = *reinterpret_cast<const float4*>(p); return {{f.x, f.y, f.z, f.w}}; }
+__device__ __forceinline__ Chans<4> load_chans(const bf16_t* p, Chans<4>*) { const float4 f = load4(p); return {{f.x, f.y, f.z, f.w}}; }
+__device__ __forceinline__ Chans<2> load_chans(const float* p, Chans<2>*) { const float2 f = *reinterpret_cast<const float2*>(p); return {{f.x, f.y}}; }
+__device__ __forceinline__ Chans<2> load_chans(const bf16_t* p, Chans<2>*) {
+  const uint32_t u = *reinterpret_cast<const uint32_t*>(p);
+  return {{__uint_as_float(u << 16), __uint_as_float(u & 0xffff0000u)}};
+}
+template <typename T> __device__ __forceinline__ void store_chans(T* p, Chans<4> c) { store4(p, make_float4(c.v[0], c.v[1], c.v[2], c.v[3])); }
+__device__ __forceinline__ void store_chans(float* p, Chans<2> c) { *reinterpret_cast<float2*>(p) = make_float2(c.v[0], c.v[1]); }
+__device__ __forceinline__ void store_chans(bf16_t* p, Chans<2> c) { *reinterpret_cast<uint32_t*>(p) = f32x2_to_bf16x2(c.v[0], c.v[1]); }
+
+// Backward of a depthwise layer, of its own BatchNorm and of the BatchNorm in front of it.  A block owns V channels of all pixels, a thread RPT
+// pixels.  The layer's own BatchNorm backward comes first (block-local: same channels), its dz goes into LDS and never to memory.  A thread
+// gathers the dz values that reach an input pixel once and uses each twice: times the tap weight for the data gradient, times the pixel's own
+// activation for the weight gradient (dW[tap] = sum_p dz[p] * a[p*s-1+tap] is the same sum walked from the input side).  The data gradient never
+// leaves the registers: it is gated by the activation, reduced into the BatchNorm sums, and after the block-wide reduction turned into the
+// gradient of the raw convolution output in front (dz_prev).
+// Bound by the lines that a CU fetches and the instructions it issues: a block reads 16 or 8 bytes of every line of three tensors and sums 11 values a channel
+// over its wavefronts.  Two channels a block (C <= 512: no more blocks than CUs) halve the instructions and leave room for twice the wavefronts: 1859 rows,
+// 192 channels, bfloat16 15.6 -> 13.5 us; 512 x 384, fp32 8.5 -> 7.1; 2048 x 192 16.8 -> 14.5.  With more blocks than CUs it loses (512 x 576:
+// 9.4, four channels 8.4).  All sums of a thread are formed before the last lane stores them (a branch for each sum: 256 x 960 7.0 us, now 6.1).
+template <typename T, int V, int RPT, int NT>
+__global__ __launch_bounds__(NT) void dw_bwd_small_k(BnBwdIn bo, const T* __restrict__ w, View in,
+                                                     ConvGeom g, FastDiv dW, FastDiv dH, int M, int Mout, const float* __restrict__ gamma,
+                                                     const float* __restrict__ mean, const float* __restrict__ invstd, float* g_w,
+                                                     float* g_gamma, float* g_beta, T* __restrict__ dz_prev) {
+  typedef Chans<V> F;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-  float4* tile = reinterpret_cast<float4*>(smem_raw);           // dz, [Mout + 1], the last one zero
-  __shared__ float wl[9][4];
-  __shared__ float red[8][44];    // [wave][value]
+  F* tile = reinterpret_cast<F*>(smem_raw);           // dz, [Mout + 1], the last one zero
+  __shared__ F wl[9];
+  __shared__ __attribute__((aligned(16))) float red[NT / 64][11 * V], red2[NT / 64][2 * V];    // [wave][value]
+  __shared__ F coef[3], coef2[3];
   __builtin_amdgcn_s_setprio(3);             // data-gradient chain: ahead of the weight-gradient stream's waves
-  __shared__ float coef[3][4];
   // adjacent channel groups share cache lines: keep them on one XCD
-  const int C = g.Cout, c0 = xcd_logical_block() * 4, tid = threadIdx.x, nt = blockDim.x, s = g.stride;
-  const T* zin = reinterpret_cast<const T*>(in.z);
+  const int C = g.Cout, c0 = xcd_logical_block() * V, tid = threadIdx.x, nt = blockDim.x, s = g.stride;
+  const T* zin = reinterpret_cast<const T*>(in.z) + c0;
+  const T* dA2 = reinterpret_cast<const T*>(bo.dA) + c0;
+  const T* z2 = reinterpret_cast<const T*>(bo.out.z) + c0;
+  F* const none = nullptr;
   // Everything that depends on nothing is requested first, unconditionally and from clamped addresses: this thread's
   // rows of the layer input, the old weight gradient, and what the finishing threads need after each reduction.
   // The kernel is a chain of memory round trips; these then overlap with the first of them.
-  float4 zv[RPT];
+  F zv[RPT], dy2[RPT], z2v[RPT];
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
     const int m = tid + q * nt;
-    zv[q] = load4(zin + (size_t)(m < M ? m : 0) * C + c0);
+    const size_t mc = m < Mout ? m : 0;
+    dy2[q] = load_chans(dA2 + mc * C, none);
+    z2v[q] = load_chans(z2 + mc * C, none);
+  }
+#pragma unroll
+  for (int q = 0; q < RPT; ++q) {
+    const int m = tid + q * nt;
+    zv[q] = load_chans(zin + (size_t)(m < M ? m : 0) * C, none);
   }
   const double inv_M = early_inverse((double)M), inv_Mo = early_inverse((double)Mout);
   float gw_old = 0.f, f_mu = 0.f, f_is = 0.f, f_g = 0.f, f_gg = 0.f, f_gb = 0.f;
   float f2_mu = 0.f, f2_is = 0.f, f2_g = 0.f, f2_gg = 0.f, f2_gb = 0.f;
-  if (tid < 36) gw_old = g_w[(size_t)(c0 + tid % 4) * 9 + tid / 4];
-  if (tid >= 64 && tid < 68) {
+  if (tid < 9 * V) gw_old = g_w[(size_t)(c0 + tid % V) * 9 + tid / V];
+  if (tid >= 64 && tid < 64 + V) {
     const int c = c0 + tid - 64;
     f_mu = mean[c]; f_is = invstd[c]; f_g = gamma[c]; f_gg = g_gamma[c]; f_gb = g_beta[c];
   }
-  if (bo.dA && tid < 4) {
+  if (tid < V) {
     const int c = c0 + tid;
     f2_mu = bo.mean[c]; f2_is = bo.invstd[c]; f2_g = bo.gamma[c]; f2_gg = bo.g_gamma[c]; f2_gb = bo.g_beta[c];
   }
-  if (tid < 36) wl[tid / 4][tid % 4] = to_f32(w[(size_t)(c0 + tid % 4) * 9 + tid / 4]);
-  float sc[4], sh[4];
+  const T w_raw = w[tid < 9 * V ? (size_t)(c0 + tid % V) * 9 + tid / V : 0];
+  float sc[V], sh[V], sc2[V], sh2[V];
 #pragma unroll
-  for (int e = 0; e < 4; ++e) { sc[e] = in.scale[c0 + e]; sh[e] = in.shift[c0 + e]; }
-  const float lo = act_lo(in.act), hi = act_hi(in.act);
-  if (bo.dA) {
-    // dz is not formed yet: this layer's own BatchNorm backward first (same channels, all pixels: block-local),
-    // its result goes straight into the LDS tile and never to memory
-    __shared__ float red2[8][8];
-    __shared__ float coef2[3][4];
-    const T* dA2 = reinterpret_cast<const T*>(bo.dA);
-    const T* z2 = reinterpret_cast<const T*>(bo.out.z);
-    float sc2[4], sh2[4];
+  for (int e = 0; e < V; ++e) { sc[e] = in.scale[c0 + e]; sh[e] = in.shift[c0 + e]; sc2[e] = bo.out.scale[c0 + e]; sh2[e] = bo.out.shift[c0 + e]; }
+  const float lo = act_lo(in.act), hi = act_hi(in.act), lo2 = act_lo(bo.out.act), hi2 = act_hi(bo.out.act);
+  const bool lead = (tid & 63) == 63;
+  const int wave = tid >> 6, nw = nt >> 6;
+  float b2[2 * V] = {};
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { sc2[e] = bo.out.scale[c0 + e]; sh2[e] = bo.out.shift[c0 + e]; }
-    const float lo2 = act_lo(bo.out.act), hi2 = act_hi(bo.out.act);
-    float4 dy2[RPT], z2v[RPT];
-    float b2[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    float4 d2r[RPT];
+  for (int q = 0; q < RPT; ++q) {
+    const bool row = tid + q * nt < Mout;
 #pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int m = tid + q * nt;
-      const size_t mc = m < Mout ? m : 0;
-      d2r[q] = load4(dA2 + mc * C + c0);
-      z2v[q] = load4(z2 + mc * C + c0);
+    for (int e = 0; e < V; ++e) {
+      const float zz = row ? z2v[q].v[e] : 0.f, y = fmaf(zz, sc2[e], sh2[e]), v = row && y > lo2 && y < hi2 ? dy2[q].v[e] : 0.f;
+      z2v[q].v[e] = zz; dy2[q].v[e] = v;
+      b2[e] += v;
+      b2[V + e] = fmaf(v, zz, b2[V + e]);
     }
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int m = tid + q * nt;
-      dy2[q] = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (m >= Mout) { z2v[q] = dy2[q]; continue; }
-      const float4 d = d2r[q];
-      const float4 zz = z2v[q];
-      const float y0 = fmaf(zz.x, sc2[0], sh2[0]), y1 = fmaf(zz.y, sc2[1], sh2[1]), y2 = fmaf(zz.z, sc2[2], sh2[2]),
-                  y3 = fmaf(zz.w, sc2[3], sh2[3]);
-      float4 v;
-      v.x = (y0 > lo2 && y0 < hi2) ? d.x : 0.f;
-      v.y = (y1 > lo2 && y1 < hi2) ? d.y : 0.f;
-      v.z = (y2 > lo2 && y2 < hi2) ? d.z : 0.f;
-      v.w = (y3 > lo2 && y3 < hi2) ? d.w : 0.f;
-      dy2[q] = v;
-      b2[0] += v.x; b2[1] += v.y; b2[2] += v.z; b2[3] += v.w;
-      b2[4] = fmaf(v.x, zz.x, b2[4]); b2[5] = fmaf(v.y, zz.y, b2[5]); b2[6] = fmaf(v.z, zz.z, b2[6]); b2[7] = fmaf(v.w, zz.w, b2[7]);
-    }
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float r = wave_sum_last(b2[e]);
-      if ((tid & 63) == 63) red2[tid >> 6][e] = r;
-    }
-    __syncthreads();
-    // first use of the values requested at the top: their conversions must not move up to the loads
-    asm volatile("" : "+v"(f2_mu), "+v"(f2_is), "+v"(f2_g), "+v"(f2_gg), "+v"(f2_gb));
-    if (tid < 4) {
-      const int c = c0 + tid;
-      double s0 = 0.0, s1 = 0.0;
-      for (int q = 0; q < (nt >> 6); ++q) { s0 += red2[q][tid]; s1 += red2[q][4 + tid]; }
-      const double mu = f2_mu, is = f2_is, gm = f2_g;
-      const double dbeta = s0, dgamma = is * (s1 - mu * s0);
-      bo.g_gamma[c] = f2_gg + (float)dgamma;
-      bo.g_beta[c] = f2_gb + (float)dbeta;
-      const double k1 = gm * is, k2 = -k1 * is * dgamma * inv_Mo, k3 = -k1 * dbeta * inv_Mo - k2 * mu;
-      coef2[0][tid] = (float)k1; coef2[1][tid] = (float)k2; coef2[2][tid] = (float)k3;
-    }
-    __syncthreads();
-    const float4 k1 = make_float4(coef2[0][0], coef2[0][1], coef2[0][2], coef2[0][3]);
-    const float4 k2 = make_float4(coef2[1][0], coef2[1][1], coef2[1][2], coef2[1][3]);
-    const float4 k3 = make_float4(coef2[2][0], coef2[2][1], coef2[2][2], coef2[2][3]);
-#pragma unroll
-    for (int q = 0; q < RPT; ++q) {
-      const int m = tid + q * nt;
-      if (m < Mout) tile[m] = round4<T>(fma4(k1, dy2[q], fma4(k2, z2v[q], k3)));   // as a stored dz would read back
-    }
-  } else {
-    for (int m = tid; m < Mout; m += nt) tile[m] = load4(dz + (size_t)m * C + c0);
   }
-  if (tid == 0) tile[Mout] = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+  for (int e = 0; e < 2 * V; ++e) b2[e] = wave_sum_last(b2[e]);
+  if (lead)
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) red2[wave][e] = b2[e];
+  if (tid < 9 * V) wl[tid / V].v[tid % V] = to_f32(w_raw);
   __syncthreads();
-  float4 wr[9], accw[9], dy[RPT];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    wr[t] = make_float4(wl[t][0], wl[t][1], wl[t][2], wl[t][3]);
-    accw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // first use of the values requested at the top: their conversions must not move up to the loads
+  asm volatile("" : "+v"(f2_mu), "+v"(f2_is), "+v"(f2_g), "+v"(f2_gg), "+v"(f2_gb));
+  if (tid < V) {
+    const int c = c0 + tid;
+    double s0 = 0.0, s1 = 0.0;
+    for (int q = 0; q < nw; ++q) { s0 += red2[q][tid]; s1 += red2[q][V + tid]; }
+    const double mu = f2_mu, is = f2_is, gm = f2_g;
+    const double dbeta = s0, dgamma = is * (s1 - mu * s0);
+    bo.g_gamma[c] = f2_gg + (float)dgamma;
+    bo.g_beta[c] = f2_gb + (float)dbeta;
+    const double k1 = gm * is, k2 = -k1 * is * dgamma * inv_Mo, k3 = -k1 * dbeta * inv_Mo - k2 * mu;
+    coef2[0].v[tid] = (float)k1; coef2[1].v[tid] = (float)k2; coef2[2].v[tid] = (float)k3;
   }
-  float bsum[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  __syncthreads();
+  {
+    const F k1 = coef2[0], k2 = coef2[1], k3 = coef2[2];
+#pragma unroll
+    for (int q = 0; q < RPT; ++q) {
+      const int m = tid + q * nt;
+      F dz;
+#pragma unroll
+      for (int e = 0; e < V; ++e) dz.v[e] = round_to<T>(fmaf(k1.v[e], dy2[q].v[e], fmaf(k2.v[e], z2v[q].v[e], k3.v[e])));   // as a stored dz would read back
+      if (m < Mout) tile[m] = dz;
+    }
+  }
+  if (tid == 0) tile[Mout] = F{};
+  __syncthreads();
+  F wr[9], accw[9], dy[RPT];
+#pragma unroll
+  for (int t = 0; t < 9; ++t) { wr[t] = wl[t]; accw[t] = F{}; }
+  float bsum[2 * V] = {};
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
     const int m = tid + q * nt;
-    dy[q] = make_float4(0.f, 0.f, 0.f, 0.f);
+    dy[q] = F{};
     if (m >= M) { zv[q] = dy[q]; continue; }
     const int r = (int)dW.div(m), ww = m - r * g.Win, n = (int)dH.div(r), h = r - n * g.Hin;
-    const float4 y = make_float4(fmaf(zv[q].x, sc[0], sh[0]), fmaf(zv[q].y, sc[1], sh[1]), fmaf(zv[q].z, sc[2], sh[2]),
-                                 fmaf(zv[q].w, sc[3], sh[3]));
-    const float4 a = round4<T>(make_float4(clamp_act(y.x, lo, hi), clamp_act(y.y, lo, hi), clamp_act(y.z, lo, hi),
-                                           clamp_act(y.w, lo, hi)));
-    float4 dA = make_float4(0.f, 0.f, 0.f, 0.f), t[9];
+    F t[9];
     // the nine values first, from the zero slot where no output pixel lies: no branches between the reads
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -1022,60 +1018,61 @@ __global__ __launch_bounds__(512) void dw_bwd_small_k(const T* __restrict__ dz, 
       }
     }
 #pragma unroll
-    for (int k = 0; k < 9; ++k) {
-      dA = fma4(t[k], wr[k], dA);
-      accw[k] = fma4(t[k], a, accw[k]);
+    for (int e = 0; e < V; ++e) {
+      const float z = zv[q].v[e], y = fmaf(z, sc[e], sh[e]), a = round_to<T>(clamp_act(y, lo, hi));
+      float dA = 0.f;
+#pragma unroll
+      for (int k = 0; k < 9; ++k) {
+        dA = fmaf(t[k].v[e], wr[k].v[e], dA);
+        accw[k].v[e] = fmaf(t[k].v[e], a, accw[k].v[e]);
+      }
+      dA = round_to<T>(dA);                    // the data gradient as the separate kernels would store it
+      const float v = y > lo && y < hi ? dA : 0.f;
+      dy[q].v[e] = v;
+      bsum[e] += v;
+      bsum[V + e] = fmaf(v, z, bsum[V + e]);
     }
-    dA = round4<T>(dA);                    // the data gradient as the separate kernels would store it
-    float4 v;
-    v.x = (y.x > lo && y.x < hi) ? dA.x : 0.f;
-    v.y = (y.y > lo && y.y < hi) ? dA.y : 0.f;
-    v.z = (y.z > lo && y.z < hi) ? dA.z : 0.f;
-    v.w = (y.w > lo && y.w < hi) ? dA.w : 0.f;
-    dy[q] = v;
-    bsum[0] += v.x; bsum[1] += v.y; bsum[2] += v.z; bsum[3] += v.w;
-    bsum[4] = fmaf(v.x, zv[q].x, bsum[4]); bsum[5] = fmaf(v.y, zv[q].y, bsum[5]);
-    bsum[6] = fmaf(v.z, zv[q].z, bsum[6]); bsum[7] = fmaf(v.w, zv[q].w, bsum[7]);
   }
   // block-wide sums in a fixed order: inside each wave, then the waves in order
-  const int wave = tid >> 6, nw = nt >> 6;
-  const bool lead = (tid & 63) == 63;
 #pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    const float r0 = wave_sum_last(accw[t].x), r1 = wave_sum_last(accw[t].y), r2 = wave_sum_last(accw[t].z), r3 = wave_sum_last(accw[t].w);
-    if (lead) { red[wave][t * 4 + 0] = r0; red[wave][t * 4 + 1] = r1; red[wave][t * 4 + 2] = r2; red[wave][t * 4 + 3] = r3; }
-  }
+  for (int t = 0; t < 9; ++t)
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float r = wave_sum_last(bsum[e]);
-    if (lead) red[wave][36 + e] = r;
+    for (int e = 0; e < V; ++e) accw[t].v[e] = wave_sum_last(accw[t].v[e]);
+#pragma unroll
+  for (int e = 0; e < 2 * V; ++e) bsum[e] = wave_sum_last(bsum[e]);
+  if (lead) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t) *reinterpret_cast<F*>(&red[wave][t * V]) = accw[t];
+#pragma unroll
+    for (int e = 0; e < 2 * V; ++e) red[wave][9 * V + e] = bsum[e];
   }
   __syncthreads();
   asm volatile("" : "+v"(gw_old), "+v"(f_mu), "+v"(f_is), "+v"(f_g), "+v"(f_gg), "+v"(f_gb));
-  if (tid < 36) {
+  if (tid < 9 * V) {
     float tot = 0.f;
     for (int q = 0; q < nw; ++q) tot += red[q][tid];
-    g_w[(size_t)(c0 + tid % 4) * 9 + tid / 4] = gw_old + tot;
-  } else if (tid >= 64 && tid < 68) {
+    g_w[(size_t)(c0 + tid % V) * 9 + tid / V] = gw_old + tot;
+  } else if (tid >= 64 && tid < 64 + V) {
     const int e = tid - 64, c = c0 + e;
     double s0 = 0.0, s1 = 0.0;
-    for (int q = 0; q < nw; ++q) { s0 += red[q][36 + e]; s1 += red[q][40 + e]; }
+    for (int q = 0; q < nw; ++q) { s0 += red[q][9 * V + e]; s1 += red[q][10 * V + e]; }
     const double mu = f_mu, is = f_is, gm = f_g;
     const double dbeta = s0, dgamma = is * (s1 - mu * s0);
     g_gamma[c] = f_gg + (float)dgamma;
     g_beta[c] = f_gb + (float)dbeta;
     const double k1 = gm * is, k2 = -k1 * is * dgamma * inv_M, k3 = -k1 * dbeta * inv_M - k2 * mu;
-    coef[0][e] = (float)k1; coef[1][e] = (float)k2; coef[2][e] = (float)k3;
+    coef[0].v[e] = (float)k1; coef[1].v[e] = (float)k2; coef[2].v[e] = (float)k3;
   }
   __syncthreads();
-  const float4 k1 = make_float4(coef[0][0], coef[0][1], coef[0][2], coef[0][3]);
-  const float4 k2 = make_float4(coef[1][0], coef[1][1], coef[1][2], coef[1][3]);
-  const float4 k3 = make_float4(coef[2][0], coef[2][1], coef[2][2], coef[2][3]);
+  const F k1 = coef[0], k2 = coef[1], k3 = coef[2];
 #pragma unroll
   for (int q = 0; q < RPT; ++q) {
     const int m = tid + q * nt;
     if (m >= M) continue;
-    store4(dz_prev + (size_t)m * C + c0, fma4(k1, dy[q], fma4(k2, zv[q], k3)));
+    F o;
+#pragma unroll
+    for (int e = 0; e < V; ++e) o.v[e] = fmaf(k1.v[e], dy[q].v[e], fmaf(k2.v[e], zv[q].v[e], k3.v[e]));
+    store_chans(dz_prev + (size_t)m * C + c0, o);
   }
 }
 
@@ -1083,26 +1080,24 @@ int dw_bwd_small_ok(const ConvGeom& g) {
   return (size_t)g.N * g.Hin * g.Win <= 2048 && g.Cout >= 32 && g.Cout % 8 == 0 && (g.stride == 1 || g.stride == 2);
 }
 
-void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, const void* w, HView in, const ConvGeom& g,
+void dw_bwd_small(int dt, hipStream_t st, const BnBwdIn& bo, const void* w, HView in, const ConvGeom& g,
                   const float* gamma, const float* mean, const float* invstd, float* g_w, float* g_gamma, float* g_beta,
                   void* dz_prev) {
   const size_t M = (size_t)g.N * g.Hin * g.Win, Mout = (size_t)g.N * g.Hout * g.Wout;
   const int es = dt == 0 ? 4 : 2;
   View v{in.z, in.scale, in.shift, in.act};
-  KScope ks(st, "dw_bwd_small", ((double)M * g.Cout * 2 + (double)Mout * g.Cout) * es, 42.0 * M * g.Cout, (long)M, g.Cout, g.stride);
-  const dim3 grid(g.Cout / 4);
-  const size_t lds = (Mout + 1) * 16;
+  KScope ks(st, "dw_bwd_small", ((double)M * g.Cout * 2 + (double)Mout * g.Cout * 2) * es, 42.0 * M * g.Cout, (long)M, g.Cout, g.stride);
   const FastDiv dW = FastDiv::of(g.Win), dH = FastDiv::of(g.Hin);
-  if (M > 1024) {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 4>), grid, dim3(512), lds, st, (const T*)dz, bo, (const T*)w, v, g, dW, dH, (int)M, (int)Mout,
-                                        gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
-  } else if (M > 256) {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 2>), grid, dim3(M > 512 ? 512 : 256), lds, st, (const T*)dz, bo, (const T*)w,
-                                        v, g, dW, dH, (int)M, (int)Mout, gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
-  } else {
-    FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, 1>), grid, dim3(256), lds, st, (const T*)dz, bo, (const T*)w, v, g, dW, dH, (int)M, (int)Mout,
-                                        gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev));
-  }
+#define FTP_DW_SMALL(V, RPT, NT, THREADS)                                                                                       \
+  FTP_DISPATCH(dt, hipLaunchKernelGGL((dw_bwd_small_k<T, V, RPT, NT>), dim3(g.Cout / V), dim3(THREADS), (Mout + 1) * 4 * V, st, bo, (const T*)w, v, g, \
+                                      dW, dH, (int)M, (int)Mout, gamma, mean, invstd, g_w, g_gamma, g_beta, (T*)dz_prev))
+  if (g.Cout <= 512 && M > 256) {
+    if (M > 1024) FTP_DW_SMALL(2, 2, 1024, 1024);
+    else FTP_DW_SMALL(2, 1, 1024, M > 512 ? 1024 : 512);
+  } else if (M > 1024) FTP_DW_SMALL(4, 4, 512, 512);
+  else if (M > 512) FTP_DW_SMALL(4, 2, 512, 512);
+  else FTP_DW_SMALL(4, 1, 512, M > 256 ? 512 : 256);
+#undef FTP_DW_SMALL
 }
 
 // ---- the whole backward of a depthwise layer in one pass ---------------------------------------------------------

@@ -216,9 +216,9 @@ void dw_fwd_bn_small(int dt, hipStream_t st, HView in, const BnPending& pend, co
 // depthwise dgrad + wgrad + the BatchNorm backward of the layer in front, one launch, short tensors
 // (dw_bwd_small_ok): dz_prev = gradient of the raw output of the convolution that feeds `in`
 int dw_bwd_small_ok(const ConvGeom& g);
-// bo.dA != nullptr: dz is not formed yet; the kernel first runs the BatchNorm backward of the depthwise layer's own
-// output (bo: gradient of the activated output, the output view, its BatchNorm vectors and gradient slots)
-void dw_bwd_small(int dt, hipStream_t st, const void* dz, const BnBwdIn& bo, const void* w, HView in, const ConvGeom& g,
+// after the BatchNorm backward of the depthwise layer's own output
+// (bo: gradient of the activated output, the output view, its BatchNorm vectors and gradient slots)
+void dw_bwd_small(int dt, hipStream_t st, const BnBwdIn& bo, const void* w, HView in, const ConvGeom& g,
                   const float* gamma, const float* mean, const float* invstd, float* g_w, float* g_gamma, float* g_beta,
                   void* dz_prev);
 // The whole backward of a layer in one pass (dIn == nullptr: without the data gradient): from the gradient dA of its activated output own (whose BatchNorm backward it does on the way, from

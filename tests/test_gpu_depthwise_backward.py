@@ -68,3 +68,28 @@ def test_depthwise_layer_without_expansion(dtype, stem, stride, cin, cout, h, w,
             pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
     finally:
         pair.close()
+
+
+# input rows (h * w * batch) at each line of the split: up to 256 | 512 | 1024 | 2048, up to 512 channels and more, and one row or pixel beyond
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("stride,cin,cout,expand,h,w,batch", [(1, 8, 8, 4, 16, 16, 1), (1, 128, 24, 4, 257, 1, 1), (2, 24, 16, 4, 16, 16, 2), (1, 16, 16, 6, 19, 27, 1), (2, 16, 16, 6, 9, 19, 3),
+                                                             (1, 32, 32, 6, 16, 16, 4), (2, 32, 24, 6, 41, 25, 1), (1, 32, 32, 6, 32, 32, 2), (1, 104, 24, 5, 257, 1, 1), (1, 104, 24, 5, 19, 27, 1),
+                                                             (2, 104, 24, 5, 5, 41, 5), (1, 104, 104, 5, 16, 16, 8)])
+def test_short_depthwise_backward(dtype, stride, cin, cout, expand, h, w, batch):
+    """Up to 2048 rows: both BatchNorm backwards in the same launch (dw_bwd_small_k)."""
+    import paper_2110_02781_amd.binding as B
+    print(f"short depthwise backward {dtype} stride {stride} {cin}->{cout} x{expand} {h}x{w} batch {batch}", flush=True)
+    o = [OM.Unit('invres', cin, cout, stride=stride, expand=expand)]
+    hu = [dict(kind=B.UNIT_INVRES, cin=cin, cout=cout, stride=stride, expand=expand)]
+    pair = Pair(o, hu, (h, w, cin), batch, 0, 1, dtype, seed=8, ties="bounded")
+    try:
+        y, yo = pair.forward(0, synth.normal(51, "x", (batch, h, w, cin)))
+        assert_close(y, yo, TOL[dtype], "y")
+        got = []
+        n = launches(lambda: got.append(pair.backward(0, synth.normal(51, "dy", yo.shape))))
+        assert n.get("dw_bwd_small", 0) == 1 and n.get("dw_bwd", 0) == 0, n
+        assert_close(*got[0], TOL[dtype], "dx")
+        pair.compare_unit_vectors("grads", TOL[dtype], floor=1e-6)
+        pair.compare_unit_vectors("bn", TOL[dtype])
+    finally:
+        pair.close()
