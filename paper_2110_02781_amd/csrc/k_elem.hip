@@ -599,6 +599,11 @@ __global__ __launch_bounds__(256) void bn_bwd_finish_apply_k(const T* __restrict
 int bn_finish_ok(size_t M, int C, int P) {
   return P <= 256 && M * (size_t)C <= ((size_t)16 << 20);
 }
+// P partial sums that a data gradient would leave, against those of a reduction pass: not where only the pass's are few enough to be finished in the layer
+// that needs them (width 1.4 at 14x14, batch 128, 88 -> 528: 36 us with sums and the launch to finish them 5, without 21 and the pass 16)
+int bn_left_sums_ok(size_t M, int C, int P) {
+  return P <= kBnPartials && (bn_finish_ok(M, C, P) || !bn_finish_ok(M, C, make_rowtile(M, C, kBnPartials).P));
+}
 
 void bn_bwd_finish_apply(int dt, hipStream_t st, const void* dA, const void* z, size_t M, int C, const float* scale, const float* shift, int act,
                          const BnPending& sums, float* g_gamma, float* g_beta, void* dz) {

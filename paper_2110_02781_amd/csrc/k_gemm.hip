@@ -704,6 +704,8 @@ __device__ __forceinline__ void load_pair(const bf16_t* p, float& a, float& b) {
   a = __uint_as_float(v << 16); b = __uint_as_float(v & 0xffff0000u);
 }
 
+template <typename T> struct alignas(2 * sizeof(T)) Pair2 { T v[2]; };
+
 // CH = reduction elements staged per step (32 everywhere, see launch_t).
 // RES: data gradient with a residual to add (a variant of its own: the sixteen prefetched residual pairs cost
 // registers that the plain data gradient should not pay for)
@@ -714,7 +716,8 @@ __device__ __forceinline__ void load_pair(const bf16_t* p, float& a, float& b) {
 // the youngest n loads" exists only while no store is pending and only if n is the same on every path: the chunk
 // loop of a tile has no stores, it is entered after an explicit wait for everything, every step requests its
 // successor's successor unconditionally (past the end: a valid tile again, never used), and the tile's stores follow.
-template <typename T, int MODE, bool VEC, int CH, bool RES = false, bool DEEP = false>
+// SUMS: data gradient that also leaves the backward sums of the BatchNorm in front (p.view: its view; scale == nullptr: no activation)
+template <typename T, int MODE, bool VEC, int CH, bool RES = false, bool DEEP = false, bool SUMS = false>
 __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
   constexpr int TI = 128;
   constexpr int PD = DEEP ? 2 : 1;
@@ -777,6 +780,16 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
     if (jc < nj) b0 = p.bias[jc];
     if (jc + 1 < nj) b1 = p.bias[jc + 1];
   }
+  const bool gated = SUMS && p.view.scale != nullptr;
+  float gsc0 = 0.f, gsc1 = 0.f, gsh0 = 0.f, gsh1 = 0.f;
+  const float glo = act_lo(p.view.act), ghi = act_hi(p.view.act);
+  if (SUMS && gated && jc < nj) { gsc0 = p.view.scale[jc]; gsc1 = p.view.scale[jc + 1]; gsh0 = p.view.shift[jc]; gsh1 = p.view.shift[jc + 1]; }     // an even width
+  if (SUMS) asm volatile("" ::"v"(gsc0), "v"(gsc1), "v"(gsh0), "v"(gsh1));
+  auto add_sums = [&](const float a, const float b, const float za, const float zb) __attribute__((always_inline)) {
+    const float ya = fmaf(za, gsc0, gsh0), yb = fmaf(zb, gsc1, gsh1);
+    const float ga = !gated || (ya > glo && ya < ghi) ? a : 0.f, gb = !gated || (yb > glo && yb < ghi) ? b : 0.f;
+    s0 += ga; q0 = fmaf(ga, za, q0); s1 += gb; q1 = fmaf(gb, zb, q1);
+  };
   // Have the two values arrive here.  Their first use is in the tile epilogue inside the loop, where the compiler
   // cannot tell how many younger loads are outstanding and waits for all of them: the prefetch of the next tile
   // would be drained before every output pass.
@@ -801,6 +814,24 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
           for (int r = 0; r < 16; ++r)
             load_pair(reinterpret_cast<const T*>(p.res) + obase + (size_t)(8 * (r / 4) + (r % 4)) * ldo, ra[RES ? r : 0], rb[RES ? r : 0]);
         }
+        if constexpr (SUMS) {
+          // a row's address is one for the block and an offset that all rows share
+          const uint32_t voff = (uint32_t)(wave * 32 + 4 * h) * (uint32_t)ldo + (uint32_t)jc;
+          Pair2<T> zr[16];
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            zr[r] = *reinterpret_cast<const Pair2<T>*>(reinterpret_cast<const T*>(p.view.z) + (i0 + 8 * (r / 4) + (r % 4)) * ldo + voff);
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            float v0 = acc[0][r], v1 = acc[1][r], a, b, za, zb;
+            if (RES) { v0 += ra[RES ? r : 0]; v1 += rb[RES ? r : 0]; }
+            store_pair_rounded(reinterpret_cast<T*>(p.out) + (i0 + 8 * (r / 4) + (r % 4)) * ldo + voff, v0, v1, a, b);      // the sums are of the values as stored
+            load_pair(reinterpret_cast<const T*>(&zr[r]), za, zb);
+            add_sums(a, b, za, zb);
+            // two steps' loads are in flight around this: results in order, or the registers of sixteen rows at once cost a block of occupancy (192, so 152)
+            if (DEEP) asm volatile("" : "+v"(s0), "+v"(s1), "+v"(q0), "+v"(q1) :: "memory");
+          }
+        } else
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const size_t o = obase + (size_t)(8 * (r / 4) + (r % 4)) * ldo;
@@ -846,6 +877,11 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
         }
         if (pair_ok) store_pair(dst, v0, v1);
         else { dst[0] = from_f32<T>(v0); if (jc + 1 < nj) dst[1] = from_f32<T>(v1); }
+        if (SUMS) {
+          float za, zb;
+          load_pair(reinterpret_cast<const T*>(p.view.z) + ig * ldo + jc, za, zb);
+          add_sums(round_to<T>(v0), round_to<T>(v1), za, zb);
+        }
       } else {
         float* dst = reinterpret_cast<float*>(p.out) + ((size_t)split * p.N + ig) * ldo + jc;
         if (pair_ok) store_pair(dst, v0, v1);
@@ -937,7 +973,7 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
     }
   }
 
-  if (MODE == MODE_FWD && p.stats) {
+  if (SUMS || (MODE == MODE_FWD && p.stats)) {
     // one partial per block: sum the 8 (wave, half) contributions of every column in a fixed order
     red[wave][lane][0] = s0; red[wave][lane][1] = s1; red[wave][lane][2] = q0; red[wave][lane][3] = q1;
     __syncthreads();
@@ -948,7 +984,7 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
 #pragma unroll
       for (int w = 0; w < 4; ++w) tot += red[w][l][2 * sq + t] + red[w][l + 32][2 * sq + t];
       const size_t j = j0 + col;
-      if (j < (size_t)p.N) p.stats[((size_t)range * 2 + sq) * p.N + j] = tot;
+      if (j < nj) p.stats[((size_t)range * 2 + sq) * nj + j] = tot;
     }
   }
 }
@@ -1440,8 +1476,15 @@ static void launch_t(hipStream_t st, const GemmArgs& a, bool small, unsigned gri
     hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, false, MODE == MODE_WGRAD>), dim3(grid), dim3(256), 0, st, a);
   else if (MODE == MODE_DGRAD && red > 32) {     // at least two steps per tile: two steps' loads in flight
     constexpr bool D = MODE == MODE_DGRAD;
-    if (a.res) hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, D, D>), dim3(grid), dim3(256), 0, st, a);
+    if (VEC && a.stats && a.res) hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, D, D, D && VEC>), dim3(grid), dim3(256), 0, st, a);
+    else if (VEC && a.stats) hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, false, D, D && VEC>), dim3(grid), dim3(256), 0, st, a);
+    else if (a.res) hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, D, D>), dim3(grid), dim3(256), 0, st, a);
     else hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, false, D>), dim3(grid), dim3(256), 0, st, a);
+  }
+  else if (MODE == MODE_DGRAD && VEC && a.stats) {
+    constexpr bool D = MODE == MODE_DGRAD && VEC;
+    if (a.res) hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, D, false, D>), dim3(grid), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, false, false, D>), dim3(grid), dim3(256), 0, st, a);
   }
   else if (MODE == MODE_DGRAD && a.res) hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32, MODE == MODE_DGRAD>), dim3(grid), dim3(256), 0, st, a);
   else hipLaunchKernelGGL((pw_gemm_rows_k<T, MODE, VEC, 32>), dim3(grid), dim3(256), 0, st, a);
@@ -1482,7 +1525,15 @@ int pw_pro_ok(int dt, size_t M, int R, int ncols) {
   const size_t P = (M + 15) / 16;
   return R % 8 == 0 && R <= (dt == 0 ? 64 : 96) && tiny_ok(dt, M, R, ncols, true) && P * 2 * R * sizeof(float) <= kProBytes;
 }
-int pw_dgrad_sums_ok(int dt, size_t M, int K, int N) { return tiny_ok(dt, M, N, K, true); }
+int pw_dgrad_sums_ok(int dt, size_t M, int K, int N, HView of) {
+  if (tiny_ok(dt, M, N, K, false)) return of.scale == nullptr && tiny_ok(dt, M, N, K, true);
+  if (of.scale != nullptr && of.act != ACT_RELU6) return 0;
+  if (pw_deep_ok(dt, M, N, K, true)) return pw_deep_sums_ok(dt, M, N, K);
+  GemmArgs a{};
+  bool small;
+  plan_rows(M, K, N, &a, &small);
+  return !small && K % 8 == 0 && N % 8 == 0 && bn_left_sums_ok(M, K, a.nranges);
+}
 
 void pw_fwd_pro(int dt, hipStream_t st, const BnPending& pend, HView x, const void* x_add, void* x_out, float eps, float momentum, const void* w,
                 size_t M, int K, int N, void* z, float* stats, int* P_out) {
@@ -1521,19 +1572,20 @@ void pw_dgrad_pro(int dt, hipStream_t st, const BnPending& sums, const BnBwdIn& 
 }
 
 void pw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K,
-              int N, void* dA, const void* z_sum, float* sums, int* P_out) {
+              int N, void* dA, HView of, float* sums, int* P_out) {
   TinyArgs a{};
   a.x = dz; a.y = w; a.res = res; a.out = dA; a.M = M; a.K = K; a.N = N;
   KScope ks(st, "pw_dgrad", ((double)M * K * (res ? 2.0 : 1.0) + (double)M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
   if (tiny_ok(dt, M, N, K, false)) {
-    a.z_sum = z_sum; a.stats = sums;
+    a.z_sum = of.z; a.stats = sums;
     launch_tiny<MODE_DGRAD>(dt, st, a, K);
     if (sums) *P_out = a.nranges;
     return;
   }
-  if (pw_deep_ok(dt, M, N, K, true)) { ks.route(pw_dgrad_deep(dt, st, dz, w, res, M, K, N, dA)); return; }
+  if (pw_deep_ok(dt, M, N, K, true)) { ks.route(pw_dgrad_deep(dt, st, dz, w, res, M, K, N, dA, of, sums, P_out)); return; }
   bool small;
   plan_rows(M, K, N, &a, &small);
+  if (sums) { a.view = View{of.z, of.scale, of.shift, of.act}; a.stats = sums; *P_out = a.nranges; }
   launch<MODE_DGRAD>(dt, st, a, small);
 }
 

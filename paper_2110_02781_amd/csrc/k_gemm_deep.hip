@@ -26,16 +26,17 @@ namespace ftp {
 enum { kDeepMaxR = 2048 };
 // a reduction step is 128 bytes of a row, moved in vectors of 16; an odd number of those between LDS rows
 template <typename E> struct Deep { enum { V = 16 / sizeof(E), KS = 8 * V, LD = KS + V, F32 = sizeof(E) == 4 }; };
-enum { DEEP_FWD = 0, DEEP_FWD_VIEW = 1, DEEP_DGRAD = 2, DEEP_DGRAD_RES = 3 };
+enum { DEEP_FWD = 0, DEEP_FWD_VIEW = 1, DEEP_DGRAD = 2, DEEP_DGRAD_RES = 3, DEEP_DGRAD_GATED = 4, DEEP_DGRAD_SUMS = 5 };
 
 struct DeepArgs {
   const void* x;      // [M][R]: A as stored (forward) or dZ (data gradient)
   const void* y;      // W[N][K]: forward [column][reduction], data gradient [reduction][column]
   const float* scale;   // forward: view of x, indexed by the reduction channel (DEEP_FWD_VIEW)
   const float* shift;
-  const void* res;    // [M][NC] added to the result (DEEP_DGRAD_RES)
+  const void* res;    // [M][NC] added to the result (DEEP_DGRAD_RES; GATED, SUMS: may be nullptr)
+  const void* z;      // [M][NC] the raw output that the result is the gradient behind (DEEP_DGRAD_GATED: through scale, shift, act of its columns)
   void* out;          // [M][NC]
-  float* stats;         // forward: [row tiles][2][NC] column sums of the stored output and of its squares, or nullptr
+  float* stats;         // forward: [row tiles][2][NC] column sums of the stored output and of its squares, or nullptr; GATED, SUMS: of the (gated) output and of it times z
   int act;
   int M, R, NC;         // rows, reduction extent, output columns
   int jtiles;           // column tiles; the grid is jtiles * row tiles
@@ -247,6 +248,24 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
     // the sets are requested in order: a wait for set d is then a wait for "all but the youngest loads" on every path
     __builtin_amdgcn_sched_barrier(0);
   }
+  // with sums a thread has V columns and every RL-th row of the tile; its part of z is requested behind the first two steps (short reductions have no others)
+  // where that costs no resident block
+  constexpr bool SUMS = MODE >= DEEP_DGRAD_GATED, EARLY = SUMS && S * T <= 6;
+  constexpr int CG = BN / V, RL = 256 / CG, NP = SUMS ? (BM + RL - 1) / RL : 1;
+  const int cg = tid % CG, rl = tid / CG, jv = j0 + cg * V;
+  const bool cin = rl < RL && jv < NC;
+  uint4 zq[NP];
+  auto request_z = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int row = rl + q * RL, m = m0 + row;
+      zq[q] = *reinterpret_cast<const uint4*>((const E*)p.z + (cin && row < BM && m < M ? (size_t)m * NC + jv : 0));
+    }
+  };
+  if (EARLY) {
+    request_z();
+    __builtin_amdgcn_sched_barrier(0);
+  }
   if (MODE == DEEP_FWD_VIEW) __syncthreads();                        // the view vectors are in LDS
   // whole groups of D steps without a branch inside (a path from the middle of a group back to the loop head would
   // turn every wait at the head into a wait for all loads), then the remaining steps
@@ -266,6 +285,86 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
       for (int b = 0; b < T; ++b) acc[a][b] = tot[a][b];
   }
 
+  // ---- results with sums: the rounded tile goes through LDS, so that its stores, z and the sums go by rows of 16-byte vectors.  As the accumulators lie a
+  // lane has four columns, a wavefront 32 bytes of a row: 12544 rows 56 -> 336 with gate 9.9 us, so 9.0; without sums 6.7, and a pass for them 5.7 ----
+  if constexpr (SUMS) {
+    constexpr int LDO = BN + V;
+    if (!EARLY) request_z();
+    float sc[V], sh[V], s1[V], s2[V];
+#pragma unroll
+    for (int e = 0; e < V; ++e) {
+      s1[e] = s2[e] = 0.f;
+      if (MODE == DEEP_DGRAD_GATED) { sc[e] = p.scale[(cin ? jv : 0) + e]; sh[e] = p.shift[(cin ? jv : 0) + e]; }
+    }
+    typedef typename std::conditional<F32, float4, uint2>::type Out4;
+    if (p.res) {                         // added in front of the rounding; all groups are requested before the first is used
+      Out4 rs[S][T];
+#pragma unroll
+      for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) {
+          const int m = m0 + wm * 16 * S + a * 16 + l16, j = j0 + wn * 16 * T + b * 16 + 4 * G;
+          rs[a][b] = *reinterpret_cast<const Out4*>((const E*)p.res + (m < M && j < NC ? (size_t)m * NC + j : 0));
+        }
+#pragma unroll
+      for (int a = 0; a < S; ++a)
+#pragma unroll
+        for (int b = 0; b < T; ++b) {
+          const float4 r = load4(reinterpret_cast<const E*>(&rs[a][b]));
+          acc[a][b][0] += r.x; acc[a][b][1] += r.y; acc[a][b][2] += r.z; acc[a][b][3] += r.w;
+        }
+    }
+    E* const ot = reinterpret_cast<E*>(smem_raw);
+    __syncthreads();                     // the staging buffers are free
+#pragma unroll
+    for (int a = 0; a < S; ++a)
+#pragma unroll
+      for (int b = 0; b < T; ++b)
+        store4(ot + (wm * 16 * S + a * 16 + l16) * LDO + wn * 16 * T + b * 16 + 4 * G, make_float4(acc[a][b][0], acc[a][b][1], acc[a][b][2], acc[a][b][3]));
+    __syncthreads();
+    const float lo = act_lo(p.act), hi = act_hi(p.act);
+#pragma unroll
+    for (int q = 0; q < NP; ++q) {
+      const int row = rl + q * RL, m = m0 + row;
+      if (cin && row < BM && m < M) {
+        const uint4 u = *reinterpret_cast<const uint4*>(ot + row * LDO + cg * V);
+        *reinterpret_cast<uint4*>((E*)p.out + (size_t)m * NC + jv) = u;
+#pragma unroll
+        for (int h = 0; h < V; h += 4) {
+          const float4 d4 = load4(reinterpret_cast<const E*>(&u) + h), z4 = load4(reinterpret_cast<const E*>(&zq[q]) + h);
+          const float d[4] = {d4.x, d4.y, d4.z, d4.w}, z[4] = {z4.x, z4.y, z4.z, z4.w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            float r = d[e];
+            if (MODE == DEEP_DGRAD_GATED) {
+              const float y = fmaf(z[e], sc[h + e], sh[h + e]);
+              r = y > lo && y < hi ? r : 0.f;
+            }
+            s1[h + e] += r;
+            s2[h + e] = fmaf(r, z[e], s2[h + e]);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    float* const red = reinterpret_cast<float*>(smem_raw);             // [2][RL][BN]
+    if (rl < RL)
+#pragma unroll
+      for (int e = 0; e < V; e += 4) {
+        *reinterpret_cast<float4*>(red + rl * BN + cg * V + e) = make_float4(s1[e], s1[e + 1], s1[e + 2], s1[e + 3]);
+        *reinterpret_cast<float4*>(red + (RL + rl) * BN + cg * V + e) = make_float4(s2[e], s2[e + 1], s2[e + 2], s2[e + 3]);
+      }
+    __syncthreads();
+    for (int i = tid; i < 2 * BN; i += 256) {
+      const int which = i / BN, col = i - which * BN, j = j0 + col;
+      if (j >= NC) continue;
+      float t = 0.f;
+#pragma unroll 4
+      for (int r = 0; r < RL; ++r) t += red[(which * RL + r) * BN + col];
+      p.stats[((size_t)it * 2 + which) * NC + j] = t;
+    }
+    return;
+  }
   // ---- results: acc[a][b][e] is out[m0 + wm*16S + 16a + l16][j0 + wn*16T + 16b + 4G + e] ----
   float s1[T][4], s2[T][4];
 #pragma unroll
@@ -344,7 +443,7 @@ __global__ __launch_bounds__(256) void pw_gemm_deep_k(DeepArgs p) {
 struct DeepPlan { int S, T, itiles, jtiles; size_t lds; };
 
 // rows M, reduction extent R, output columns NC
-static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d) {
+static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d, bool sums = false) {
   // bfloat16: reductions of 192 and more as they come; shorter ones up to 32768 rows, but layers that widen them much there, whose time is the
   // output's.  us on the streaming kernels and here, forward 700 rows 960 -> 320 10.5 / 7.0, 2100 24 -> 144 6.3 / 2.9, 3136 160 -> 960 8.7 / 7.2, 6825 48 -> 288 5.7 / 5.0, 12544 40 -> 96 4.3 /
   // 3.8, 144 -> 64 6.2 / 4.2, 25088 96 -> 64 5.0 / 4.8; but 12544 64 -> 384 6.7 / 7.6, 25088 32 -> 192 5.4 / 7.5, 88 -> 528 14.8 / 16.3, 136 -> 816 26.4 / 36.4.
@@ -381,12 +480,14 @@ static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d) 
   // CU to itself.  3136 rows, us, bfloat16:
   // 960 -> 160 forward 15.7 (2 x 5, 49 blocks), 12.3 (2 x 2, 147), 11.8 (1 x 3, 196), 10.4 (1 x 1, 490); its mirror, with residual, 13.5, 8.7, 8.5, 7.3;
   // 1280 -> 320 data gradient 16.1 (2 x 5, 98), 13.0 (2 x 3, 196), 11.3 (2 x 2, 245), 13.8 (1 x 1, 980); 320 -> 960 11.6 (2 x 5, 294), 8.9 (4 x 3, 250).
+  // With sums, bfloat16: up to two.  What such a layer waits for is z, and of the larger tiles two blocks at most share a CU: width 1.4, batch 128, 4 steps
+  // 26.98 ms with 4 x 3 and 4 x 4, 26.85 without; 4 x 5 (one block) 25088 rows 136 -> 816 67 us, 4 x 4 51, without sums 33.
   static const int kTiles[][2] = {{4, 5}, {4, 4}, {4, 3}, {4, 2}, {2, 3}, {2, 2}, {2, 1}, {1, 1}};
   int best = 0;
   for (const auto& st : kTiles) {
     const int S = st[0], T = st[1];
     const size_t itiles = (M + 32 * S - 1) / (32 * S), jtiles = (NC + 32 * T - 1) / (32 * T);
-    if (itiles > kMaxPartials || (dt == 0 && S * T > 8)) continue;      // (fp32: an accumulator more for every one)
+    if (itiles > kMaxPartials || (dt == 0 && S * T > 8) || (sums && dt && S == 4)) continue;      // (fp32: an accumulator more for every one)
     const size_t xs = (size_t)32 * S * LD, ys = dgrad ? (size_t)KS * (32 * T + V) : (size_t)32 * T * LD;
     const size_t lds = 2 * (xs + ys) * es + (dgrad ? 0 : 2 * (size_t)((R + KS - 1) / KS * KS) * sizeof(float));
     const int turns = (int)((itiles * jtiles + 255) / 256), alone = turns == 1 || 2 * lds > 160 * 1024;
@@ -411,6 +512,15 @@ static void deep_launch_mode(hipStream_t st, const DeepArgs& a, const DeepPlan& 
     case DEEP_FWD: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_FWD>), grid, block, d.lds, st, a); break;
     case DEEP_FWD_VIEW: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_FWD_VIEW>), grid, block, d.lds, st, a); break;
     case DEEP_DGRAD: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_DGRAD>), grid, block, d.lds, st, a); break;
+    case DEEP_DGRAD_GATED:
+    case DEEP_DGRAD_SUMS:
+      if constexpr (Deep<E>::F32 || S < 4) {               // deep_plan
+        if (mode == DEEP_DGRAD_GATED) hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_DGRAD_GATED>), grid, block, d.lds, st, a);
+        else hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_DGRAD_SUMS>), grid, block, d.lds, st, a);
+      } else {
+        launch_plan_failed("data gradient with sums: no such tile");
+      }
+      break;
     default: hipLaunchKernelGGL((pw_gemm_deep_k<E, S, T, DEEP_DGRAD_RES>), grid, block, d.lds, st, a); break;
   }
 }
@@ -462,14 +572,25 @@ const char* pw_fwd_deep(int dt, hipStream_t st, HView av, const void* w, size_t 
   return deep_name(d);
 }
 
-// dA[M][K] = dZ[M][N] * W[N][K] (+ res)
-const char* pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA) {
+int pw_deep_sums_ok(int dt, size_t M, int R, int NC) {
   DeepPlan d;
-  if (!deep_plan(dt, M, N, K, true, &d)) { launch_plan_failed("long-reduction pointwise data gradient called for a shape it does not take"); return nullptr; }
+  return deep_plan(dt, M, R, NC, true, &d, true) && bn_left_sums_ok(M, NC, d.itiles);
+}
+
+// dA[M][K] = dZ[M][N] * W[N][K] (+ res); sums != nullptr: with the sums of dA and dA * of.z, dA gated by the activation that the view `of` has (P_out partials)
+const char* pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA, HView of, float* sums, int* P_out) {
+  DeepPlan d;
+  if (!deep_plan(dt, M, N, K, true, &d, sums != nullptr)) { launch_plan_failed("long-reduction pointwise data gradient called for a shape it does not take"); return nullptr; }
   DeepArgs a{};
   a.x = dz; a.y = w; a.res = res; a.out = dA;
   a.M = (int)M; a.R = N; a.NC = K; a.jtiles = d.jtiles;
-  deep_launch(dt, st, a, d, res ? DEEP_DGRAD_RES : DEEP_DGRAD);
+  if (sums) {
+    a.z = of.z; a.scale = of.scale; a.shift = of.shift; a.act = of.act; a.stats = sums;
+    *P_out = d.itiles;
+    deep_launch(dt, st, a, d, of.scale ? DEEP_DGRAD_GATED : DEEP_DGRAD_SUMS);
+  } else {
+    deep_launch(dt, st, a, d, res ? DEEP_DGRAD_RES : DEEP_DGRAD);
+  }
   return deep_name(d);
 }
 

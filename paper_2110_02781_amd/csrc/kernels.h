@@ -103,6 +103,7 @@ void bn_bwd_small(int dt, hipStream_t st, const void* dA, const void* z, size_t 
                   float* g_gamma, float* g_beta, void* dz);
 // the last two steps in one launch (bn_finish_ok): from P partial sums, no coef; sums: partial, P, M, gamma, mean, invstd
 int bn_finish_ok(size_t M, int C, int P);
+int bn_left_sums_ok(size_t M, int C, int P);
 void bn_bwd_finish_apply(int dt, hipStream_t st, const void* dA, const void* z, size_t M, int C, const float* scale, const float* shift, int act,
                          const BnPending& sums, float* g_gamma, float* g_beta, void* dz);
 // the same for forward (bn_finish_ok): finishes the pending statistics of z and writes act(scale*z+shift) (+ res)
@@ -240,10 +241,10 @@ int pw_pro_ok(int dt, size_t M, int R, int ncols);
 void pw_fwd_pro(int dt, hipStream_t st, const BnPending& pend, HView x, const void* x_add, void* x_out, float eps, float momentum, const void* w,
                 size_t M, int K, int N, void* z, float* stats, int* P_out);
 // dA[M][K] = dZ[M][N] * W[N][K] (+ res[M][K]).  sums != nullptr (only if pw_dgrad_sums_ok): also the partial sums [*P_out][2][K] that
-// bn_bwd_reduce would compute for a BatchNorm without activation whose raw output is z_sum and whose output's gradient is dA
-int pw_dgrad_sums_ok(int dt, size_t M, int K, int N);
+// bn_bwd_reduce would compute for the BatchNorm of the view `of` (of.scale == nullptr: without activation, of.z its raw output), dA being the gradient of its output
+int pw_dgrad_sums_ok(int dt, size_t M, int K, int N, HView of);
 void pw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K,
-              int N, void* dA, const void* z_sum = nullptr, float* sums = nullptr, int* P_out = nullptr);
+              int N, void* dA, HView of = HView{}, float* sums = nullptr, int* P_out = nullptr);
 // the consumer of such sums (pw_pro_ok): BatchNorm backward of bn (no activation), dz written, then dA = dz * W
 void pw_dgrad_pro(int dt, hipStream_t st, const BnPending& sums, const BnBwdIn& bn, void* dz, const void* w, size_t M, int K, int N, void* dA);
 // g_w[N][K] += dZ[M][N]^T * A'[M][K]
@@ -278,7 +279,8 @@ void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, 
 // They return the tile for the trace.
 int pw_deep_ok(int dt, size_t M, int R, int NC, bool dgrad);
 const char* pw_fwd_deep(int dt, hipStream_t st, HView a, const void* w, size_t M, int K, int N, void* z, float* stats, int* P_out);
-const char* pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA);
+const char* pw_dgrad_deep(int dt, hipStream_t st, const void* dz, const void* w, const void* res, size_t M, int K, int N, void* dA, HView of, float* sums, int* P_out);
+int pw_deep_sums_ok(int dt, size_t M, int R, int NC);
 // the weight gradient for bfloat16 layers with more than 2048 rows: operands staged untransposed, transposed on the
 // way out of LDS (pw_wgrad dispatches to it; ws: pw_wgrad_tr_ws floats)
 int pw_wgrad_tr_ok(int dt, size_t M, int K, int N);

@@ -1116,15 +1116,17 @@ static bool takes_sums(const ftp_stage* s, const UnitPlan& p, size_t k) {
   return s->defers && u.d.kind == FTP_UNIT_INVRES && k + 1 == u.subs.size() && sb.type == SUB_PW && !p.at_once[k] &&
          bn_bwd_small_ok(M, sb.g.Cout) && pw_pro_ok(s->dt, M, sb.g.Cout, sb.g.Cin);
 }
-// the raw output of the project layer in front of unit i, where unit i's first layer can leave those sums; else nullptr
+// the raw output of the project layer in front of unit i, where unit i's first layer can leave the backward sums of its BatchNorm; else nullptr
 static const void* leaves_sums(const ftp_stage* s, const Views& v, size_t i) {
   if (i == 0) return nullptr;
   const UnitPlan& p = s->plan[i];
   const UnitPlan& q = s->plan[i - 1];
   if (p.info->subs.empty() || p.info->subs[0].type != SUB_PW || p.at_once[0] || q.info->subs.empty()) return nullptr;
   const ConvGeom& g = p.info->subs[0].g;
-  if (!takes_sums(s, q, q.info->subs.size() - 1) || !pw_dgrad_sums_ok(s->dt, (size_t)s->batch * g.Hout * g.Wout, g.Cin, g.Cout)) return nullptr;
-  return v.sub_out[i - 1].back().z;
+  const size_t M = (size_t)s->batch * g.Hout * g.Wout;
+  const HView of{v.sub_out[i - 1].back().z, nullptr, nullptr, FTP_ACT_NONE};
+  if (q.info->d.kind != FTP_UNIT_INVRES || !pw_dgrad_sums_ok(s->dt, M, g.Cin, g.Cout, of)) return nullptr;
+  return !bn_bwd_small_ok(M, g.Cin) || takes_sums(s, q, q.info->subs.size() - 1) ? of.z : nullptr;
 }
 
 // part: BWD_FROM_DZ in a stage that defers, where the caller has taken the layer's places
@@ -1208,6 +1210,16 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     (s->defers ? s->q_red : s->q_late).push_back(ReduceJob{at.part, s->grads + p.p_off + sb.w_off, P, 9 * C, C, 1, 9, C});
     return FTP_OK;
   }
+  // A pointwise layer's data gradient, with the backward sums of the BatchNorm in front where its kernel can leave them and that layer takes them: the one
+  // in front within the block, or that of the block in front (z_sum).  Convolutions as units of their own keep the pass, and with it the gradients of a stage of
+  // one layer bit for bit.
+  auto run_pw_dgrad = [&]() {
+    const HView of = z_sum ? HView{z_sum, nullptr, nullptr, FTP_ACT_NONE} : k > 0 && in.scale && !bn_bwd_small_ok(M, g.Cin) ? in : HView{};
+    float* const sums = of.z && pw_dgrad_sums_ok(s->dt, M, g.Cin, g.Cout, of) ? s->bn_part : nullptr;
+    int P = 0;
+    pw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), res, M, g.Cin, g.Cout, dIn, of, sums, &P);
+    if (sums) leave_sums(s, dIn, sums, P);
+  };
   // noted for the end of the backward call: dz stays where it is written until then
   const bool noted = s->defers && (sb.type != SUB_DIRECT || p.axis[k]);
   if (mode != BWD_FROM_DZ) {
@@ -1279,7 +1291,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     // noted for the unit's fork; the data gradient goes on as it would behind a forked weight gradient
     if (s->n_pend >= 3) { ftp_set_error("stage_backward: more weight gradients noted for a unit than it has layers"); return FTP_ERR_UNSUPPORTED; }
     s->pend[s->n_pend++] = ftp_stage::PendingWgrad{dz, in, g, M, s->grads + p.p_off + sb.w_off};
-    pw_dgrad(s->dt, st, dz, conv_w(s, W, p.p_off + sb.w_off), res, M, g.Cin, g.Cout, dIn);
+    run_pw_dgrad();
     return FTP_OK;
   }
   if (noted) {
@@ -1290,9 +1302,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       else pw_wgrad(s->dt, st, dz, in, M, g.Cin, g.Cout, part, gw);
     } else if (sb.type == SUB_PW) {
       s->q_pw.push_back(PwWgradJob{dz, in, M, g.Cin, g.Cout, part, gw});
-      int P = 0;
-      if (dIn) pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn, z_sum, z_sum ? s->bn_part : nullptr, &P);
-      if (z_sum && dIn) leave_sums(s, dIn, s->bn_part, P);
+      if (dIn) run_pw_dgrad();
     } else if (dIn && conv1d_small_ok(g)) {
       float* const fill = conv1d_leaves_sums(s, &p - s->plan.data()) ? s->bn_part : nullptr;
       int P = 0;
@@ -1348,7 +1358,7 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
       }
       else conv_direct_dgrad(s->dt, st, dz, w, g, dIn);
     }
-    else pw_dgrad(s->dt, st, dz, w, res, M, g.Cin, g.Cout, dIn);
+    else run_pw_dgrad();
   }
   return FTP_OK;
 }
