@@ -865,7 +865,8 @@ static float* open_sums(const ftp_stage* s, const Slot& sl, size_t i) {
 }
 
 // every unit of the stage over the input at offset 0 of the slot's stash, with the weights W
-static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet& W, hipStream_t st) {
+// y: where the caller wants the stage's output (nullptr: nowhere); *y_written: it is there
+static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet& W, hipStream_t st, void* y = nullptr, bool* y_written = nullptr) {
   OutPending block{};      // the output of a short block, left to the pointwise layer behind it
   BnPending carry{};       // a short 1-D convolution leaves its statistics to the short 1-D convolution or the average behind it
   for (size_t i = 0; i < s->plan.size(); ++i) {
@@ -906,7 +907,11 @@ static int forward_units(ftp_stage* s, Slot& sl, const Views& v, const WeightSet
         }
         const size_t Mo = (size_t)s->batch * u.outH * u.outW;
         const void* res = u.residual ? in.z : nullptr;
-        char* out = sl.stash + p.out_off;
+        // the stage's output goes to the caller at once where its vectors allow it: nothing here reads it again (block 2 at 112x112, batch 64, bfloat16: a step
+        // 0.427 -> 0.423 ms without the copy)
+        const bool direct = y && i + 1 == s->plan.size() && ((uintptr_t)y & 15) == 0;
+        char* out = direct ? (char*)y : sl.stash + p.out_off;
+        if (direct) *y_written = true;
         if (bn_finalize_apply_small_ok(Mo, u.outC)) {
           if (next_forms_block(s, i)) block = OutPending{pend, h, res, out};
           else bn_finalize_apply_small(s->dt, st, pend, h.z, Mo, u.outC, h.act, kBnEps, s->bn_mom, res, out);
@@ -957,8 +962,9 @@ extern "C" int ftp_stage_forward(ftp_stage* s, int slot, const void* x_dev, void
   Views v;
   build_views(s, sl, &v);
   WeightSet W{s->params, (const char*)s->w_lp};
-  if ((rc = forward_units(s, sl, v, W, st))) return rc;
-  if (y_dev) {
+  bool y_written = false;
+  if ((rc = forward_units(s, sl, v, W, st, y_dev, &y_written))) return rc;
+  if (y_dev && !y_written) {
     size_t li = s->plan.size() - 1;
     const UnitPlan& p = s->plan[li];
     const UnitInfo& u = *p.info;
