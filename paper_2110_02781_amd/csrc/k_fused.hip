@@ -14,6 +14,8 @@
 // of a block stay in its MFMA accumulators over all its row tiles; it leaves one fp32 partial [N][K].
 // Only layers whose N x K accumulators fit the registers of a block take this path (N <= 320, K <= 48: the layers
 // with the largest tensors); the rest keep the layer-by-layer kernels.
+// Behind another block it also leaves the backward sums of that one's BatchNorm (z_in), which were a pass over dIn and z: width 0.5 at 161x193, batch 13,
+// 1.035 -> 1.014 ms a step, 224x224 recomputing 2.89 -> 2.86.
 #include "dev_common.h"
 #include "kernels.h"
 #include "mfma_frag.h"
@@ -33,6 +35,8 @@ struct FusedArgs {
   const bf16_t* res;     // [M][K] added to dIn, or nullptr
   bf16_t* dIn;           // [M][K]
   float* ws;             // [P][N][K] partial weight gradients
+  const bf16_t* z_in;    // [M][K] the raw output whose BatchNorm (no activation) is in front, or nullptr
+  float* sums;           // z_in: [P][2][K] its backward sums
   size_t M;
   int K, N, NP, KP;      // NP, KP: N rounded up to 32, K rounded up to 16 (LDS tiles, zero padded)
   int ntiles;
@@ -45,6 +49,7 @@ struct FusedArgs {
 template <int ACT, int NTW, int KT, int IT, bool RES, int ROWS>
 __global__ __launch_bounds__(256) void pw_bwd_fused_k(FusedArgs p) {
   constexpr int kFusedRows = ROWS;
+  constexpr bool SUMS = KT < 3;               // the widest shape has no registers for them: one block to a CU instead of two
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   __builtin_amdgcn_s_setprio(3);              // data-gradient chain
   const int LDN = p.NP + 8, LDK = p.KP + 8;
@@ -108,6 +113,11 @@ __global__ __launch_bounds__(256) void pw_bwd_fused_k(FusedArgs p) {
     for (int kt = 0; kt < KT; ++kt) accw[i][kt] = f4v_t{0.f, 0.f, 0.f, 0.f};
   const int NT = N / 16;
 
+  float s1[KT][4], s2[KT][4];
+#pragma unroll
+  for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s1[kt][e] = s2[kt][e] = 0.f;
   int tile = blockIdx.x;
   if (tile < p.ntiles) fetch(tile);
   for (; tile < p.ntiles; tile += gridDim.x) {
@@ -164,6 +174,14 @@ __global__ __launch_bounds__(256) void pw_bwd_fused_k(FusedArgs p) {
           rs[kt][2] = __uint_as_float(u.y << 16); rs[kt][3] = __uint_as_float(u.y & 0xffff0000u);
         }
       }
+      uint2 zi[KT];
+      if (SUMS && p.z_in) {
+#pragma unroll
+        for (int kt = 0; kt < KT; ++kt) {
+          const int k = kt * 16 + G * 4;
+          zi[kt] = *reinterpret_cast<const uint2*>(p.z_in + (m < p.M && k < K && kt % WPT == kpart ? m * K + k : 0));
+        }
+      }
       f4v_t accd[KT];
 #pragma unroll
       for (int kt = 0; kt < KT; ++kt) accd[kt] = f4v_t{0.f, 0.f, 0.f, 0.f};
@@ -187,6 +205,12 @@ __global__ __launch_bounds__(256) void pw_bwd_fused_k(FusedArgs p) {
           u.x = f32x2_to_bf16x2(v0, v1);
           u.y = f32x2_to_bf16x2(v2, v3);
           *reinterpret_cast<uint2*>(p.dIn + m * K + k) = u;
+          if (SUMS && p.z_in) {                                    // of the values as stored
+            const float4 d4 = load4(reinterpret_cast<const bf16_t*>(&u)), z4 = load4(reinterpret_cast<const bf16_t*>(&zi[kt]));
+            s1[kt][0] += d4.x; s1[kt][1] += d4.y; s1[kt][2] += d4.z; s1[kt][3] += d4.w;
+            s2[kt][0] = fmaf(d4.x, z4.x, s2[kt][0]); s2[kt][1] = fmaf(d4.y, z4.y, s2[kt][1]);
+            s2[kt][2] = fmaf(d4.z, z4.z, s2[kt][2]); s2[kt][3] = fmaf(d4.w, z4.w, s2[kt][3]);
+          }
         }
       }
     }
@@ -206,6 +230,32 @@ __global__ __launch_bounds__(256) void pw_bwd_fused_k(FusedArgs p) {
           for (int kt = 0; kt < KT; ++kt) accw[i][kt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(an, bk[kt], accw[i][kt], 0, 0, 0);
         }
       }
+    }
+  }
+
+  if (SUMS && p.z_in) {
+    // the sixteen rows of a lane group, then the wavefronts in order
+    __syncthreads();
+    float* red = reinterpret_cast<float*>(smem_raw);       // [4][2][KT * 16]
+#pragma unroll
+    for (int kt = 0; kt < KT; ++kt)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float a1 = s1[kt][e], a2 = s2[kt][e];
+        a1 += dpp_move<0xB1>(a1); a1 += dpp_move<0x4E>(a1); a1 += dpp_move<0x141>(a1); a1 += dpp_move<0x140>(a1);
+        a2 += dpp_move<0xB1>(a2); a2 += dpp_move<0x4E>(a2); a2 += dpp_move<0x141>(a2); a2 += dpp_move<0x140>(a2);
+        if (l16 == 0) {
+          red[(wave * 2 + 0) * KT * 16 + kt * 16 + 4 * G + e] = a1;
+          red[(wave * 2 + 1) * KT * 16 + kt * 16 + 4 * G + e] = a2;
+        }
+      }
+    __syncthreads();
+    if (tid < 2 * KT * 16) {
+      const int which = tid / (KT * 16), k = tid - which * KT * 16;
+      float t = 0.f;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) t += red[(w * 2 + which) * KT * 16 + k];
+      if (k < K) p.sums[((size_t)blockIdx.x * 2 + which) * K + k] = t;
     }
   }
 
@@ -263,6 +313,12 @@ size_t pw_bwd_fused_ws(size_t M, int K, int N) {
   return (size_t)f.P * N * K;
 }
 
+// the partial sums it would leave of the BatchNorm in front (0: it leaves none)
+int pw_bwd_fused_sums(size_t M, int K, int N) {
+  FusedPlan f;
+  return fused_plan(M, K, N, &f) && f.NTW <= 3 && f.KT <= 2 && bn_left_sums_ok(M, K, f.P) ? f.P : 0;
+}
+
 template <int ACT, int NTW, int KT, int IT, int ROWS>
 static void fused_launch(hipStream_t st, const FusedArgs& a, const FusedPlan& f) {
   if (a.res) hipLaunchKernelGGL((pw_bwd_fused_k<ACT, NTW, KT, IT, true, ROWS>), dim3(f.P), dim3(256), f.lds, st, a);
@@ -287,12 +343,13 @@ static void fused_launch_shape(hipStream_t st, const FusedArgs& a, const FusedPl
 
 void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, const void* w, const void* a_in,
                   const void* res, size_t M, int K, int N, float* ws, float* g_w, void* dIn, hipStream_t st_sum,
-                  hipEvent_t ev_sum, std::vector<ReduceJob>* left) {
+                  hipEvent_t ev_sum, std::vector<ReduceJob>* left, const void* z_in, float* sums) {
   FusedPlan f;
   if (!fused_plan(M, K, N, &f)) { launch_plan_failed("fused pointwise backward called for a shape it does not take"); return; }
   FusedArgs a{};
   a.dA = (const bf16_t*)dA; a.z = (const bf16_t*)out.z; a.scale = out.scale; a.shift = out.shift; a.coef = coef;
   a.w = (const bf16_t*)w; a.a = (const bf16_t*)a_in; a.res = (const bf16_t*)res; a.dIn = (bf16_t*)dIn; a.ws = ws;
+  a.z_in = (const bf16_t*)z_in; a.sums = sums;
   a.M = M; a.K = K; a.N = N; a.NP = f.NP; a.KP = f.KP; a.ntiles = f.ntiles;
   {
     KScope ks(st, "pw_bwd_fused", ((double)M * N * 2.0 + (double)M * K * (res ? 3.0 : 2.0)) * 2.0 + (double)f.P * N * K * 4.0,

@@ -271,7 +271,9 @@ int pw_bwd_fused_ok(int dt, size_t M, int K, int N, HView a);
 size_t pw_bwd_fused_ws(size_t M, int K, int N);
 void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, const void* w, const void* a_in,
                   const void* res, size_t M, int K, int N, float* ws, float* g_w, void* dIn, hipStream_t st_sum,
-                  hipEvent_t ev_sum, std::vector<ReduceJob>* left = nullptr);
+                  hipEvent_t ev_sum, std::vector<ReduceJob>* left = nullptr, const void* z_in = nullptr, float* sums = nullptr);
+// z_in: also the backward sums of the BatchNorm without activation whose raw output z_in is ([pw_bwd_fused_sums][2][K], which is not 0)
+int pw_bwd_fused_sums(size_t M, int K, int N);
 
 
 // Pointwise layers on double-buffered LDS tiles: forward (A' * W^T, BatchNorm partial sums as pw_fwd leaves them) and data gradient (dZ * W (+ res)).

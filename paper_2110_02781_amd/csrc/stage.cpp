@@ -1122,7 +1122,7 @@ static bool takes_sums(const ftp_stage* s, const UnitPlan& p, size_t k) {
   return s->defers && u.d.kind == FTP_UNIT_INVRES && k + 1 == u.subs.size() && sb.type == SUB_PW && !p.at_once[k] &&
          bn_bwd_small_ok(M, sb.g.Cout) && pw_pro_ok(s->dt, M, sb.g.Cout, sb.g.Cin);
 }
-// the raw output of the project layer in front of unit i, where unit i's first layer can leave the backward sums of its BatchNorm; else nullptr
+// the raw output of the project layer in front of unit i, whose BatchNorm takes backward sums that unit i's first layer may leave; else nullptr
 static const void* leaves_sums(const ftp_stage* s, const Views& v, size_t i) {
   if (i == 0) return nullptr;
   const UnitPlan& p = s->plan[i];
@@ -1131,8 +1131,8 @@ static const void* leaves_sums(const ftp_stage* s, const Views& v, size_t i) {
   const ConvGeom& g = p.info->subs[0].g;
   const size_t M = (size_t)s->batch * g.Hout * g.Wout;
   const HView of{v.sub_out[i - 1].back().z, nullptr, nullptr, FTP_ACT_NONE};
-  if (q.info->d.kind != FTP_UNIT_INVRES || !pw_dgrad_sums_ok(s->dt, M, g.Cin, g.Cout, of)) return nullptr;
-  return !bn_bwd_small_ok(M, g.Cin) || takes_sums(s, q, q.info->subs.size() - 1) ? of.z : nullptr;
+  if (q.info->d.kind != FTP_UNIT_INVRES) return nullptr;
+  return !bn_bwd_small_ok(M, g.Cin) || (takes_sums(s, q, q.info->subs.size() - 1) && pw_dgrad_sums_ok(s->dt, M, g.Cin, g.Cout, of)) ? of.z : nullptr;
 }
 
 // part: BWD_FROM_DZ in a stage that defers, where the caller has taken the layer's places
@@ -1163,13 +1163,15 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
     // the sum of the kernel's partial weight gradients is off the data-gradient chain: it goes to the side stream,
     // and the next user of the partial buffer waits for it
     const bool last = !s->defers && &p == &s->plan[0], aside = stage_overlaps(s) && !last;
+    const int sums_in = z_sum ? pw_bwd_fused_sums(M, g.Cin, g.Cout) : 0;
     if (s->join_pending[2]) {
       HIP_TRY(hipStreamWaitEvent(st, s->ev_join[2], 0));
       s->join_pending[2] = false;
     }
     pw_bwd_fused(st, dA, out, s->coef, conv_w(s, W, p.p_off + sb.w_off), in.z, res, M, g.Cin, g.Cout,
                  s->defers ? take_places(s, 0, p.part[k], st).part : s->ws_fused, s->grads + p.p_off + sb.w_off, dIn, aside ? s->side : st,
-                 aside ? s->ev_fork[2] : nullptr, s->defers ? &s->q_red : last ? &s->q_late : nullptr);
+                 aside ? s->ev_fork[2] : nullptr, s->defers ? &s->q_red : last ? &s->q_late : nullptr, sums_in > 0 ? z_sum : nullptr, s->bn_part);
+    if (sums_in > 0) leave_sums(s, dIn, s->bn_part, sums_in);
     if (aside) {
       HIP_TRY(hipEventRecord(s->ev_join[2], s->side));
       s->join_pending[2] = true;

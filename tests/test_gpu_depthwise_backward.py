@@ -115,7 +115,7 @@ def test_sums_left_by_data_gradients(dtype, c0, c1, c2, expand, h, w, batch):
         assert_close(y, yo, TOL[dtype], "y")
         got = []
         n = launches(lambda: got.append(pair.backward(0, synth.normal(51, "dy", yo.shape))))
-        # nothing is behind the last block; no sums are left for a block in front by the fused backward of an expand layer (bfloat16), nor where a pass
+        # nothing is behind the last block; no sums are left for a block in front by the widest fused backward of an expand layer (bfloat16), nor where a pass
         # leaves few partial sums and the data gradient many (24 channels, and 96 of some 20000 rows)
         assert n.get("bn_bwd_reduce", 0) <= 1 + (0 if c1 >= 32 and dtype == "f32" else 3 if c1 < 32 else n.get("pw_bwd_fused", 0)), n
         assert_close(*got[0], TOL[dtype], "dx")
