@@ -172,7 +172,8 @@ int ftp_stage_loss(ftp_stage*, int slot, const int32_t* labels_dev, float* loss_
 /* The loss of ftp_stage_loss for callers that cannot allocate device memory and have no stage object at hand: code
  * under HIP graph capture, tight serving or evaluation loops, harnesses that forbid hipMalloc.  Same kernels, same
  * results bit for bit; the per-row losses that ftp_stage_loss keeps in memory the stage allocated live in a
- * file-scope device array of FTP_STATIC_LOSS_MAX_BATCH floats (256 KiB per GPU, held until the process ends).
+ * file-scope device array of FTP_STATIC_LOSS_MAX_BATCH floats (256 KiB per GPU, held until the process ends), next to
+ * the counters by which the last block to arrive takes their mean.
  * logits_dev [batch, classes] and dlogits_dev (same shape, receives (softmax - onehot) / batch) are of `dtype`;
  * labels_dev int32 [batch], 0 <= label < classes (a label outside gives a NaN loss); loss_dev one float.  The caller
  * owns all four buffers.  batch > FTP_STATIC_LOSS_MAX_BATCH: FTP_ERR_ARG, nothing is launched.  Calls no hipMalloc,

@@ -289,7 +289,7 @@ __global__ __launch_bounds__(256) void bn_bwd_finalize_k(const float* __restrict
                                                          const float* __restrict__ invstd, float* g_gamma, float* g_beta, float* coef) {
   // data-gradient chain.  Without this its few waves are the youngest on SIMDs that the weight-gradient stream's
   // long-running waves keep busy, and issue goes to the oldest wave first: measured 190 us instead of 5 next to a
-  // persistent depthwise weight-gradient kernel
+  // persistent weight-gradient kernel
   __builtin_amdgcn_s_setprio(3);
   const int c0 = xcd_logical_block() * kFinCh, tid = threadIdx.x, c = c0 + tid;     // neighbours read the same lines of the partials: one L2
   const bool fin = tid < kFinCh && c < C;

@@ -352,7 +352,7 @@ void pw_bwd_fused(hipStream_t st, const void* dA, HView out, const float* coef, 
   a.z_in = (const bf16_t*)z_in; a.sums = sums;
   a.M = M; a.K = K; a.N = N; a.NP = f.NP; a.KP = f.KP; a.ntiles = f.ntiles;
   {
-    KScope ks(st, "pw_bwd_fused", ((double)M * N * 2.0 + (double)M * K * (res ? 3.0 : 2.0)) * 2.0 + (double)f.P * N * K * 4.0,
+    KScope ks(st, "pw_bwd_fused", ((double)M * N * 2.0 + (double)M * K * (2.0 + (res != nullptr) + (z_in != nullptr))) * 2.0 + (double)f.P * N * K * 4.0,
               4.0 * M * K * N, (long)M, K, N);
     if (out.act == ACT_NONE) fused_launch_shape<ACT_NONE>(st, a, f);
     else if (out.act == ACT_RELU) fused_launch_shape<ACT_RELU>(st, a, f);

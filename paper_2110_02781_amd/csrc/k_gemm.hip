@@ -1575,7 +1575,7 @@ void pw_dgrad(int dt, hipStream_t st, const void* dz, const void* w, const void*
               int N, void* dA, HView of, float* sums, int* P_out) {
   TinyArgs a{};
   a.x = dz; a.y = w; a.res = res; a.out = dA; a.M = M; a.K = K; a.N = N;
-  KScope ks(st, "pw_dgrad", ((double)M * K * (res ? 2.0 : 1.0) + (double)M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
+  KScope ks(st, "pw_dgrad", ((double)M * K * (1.0 + (res != nullptr) + (sums != nullptr)) + (double)M * N + (double)N * K) * (dt == 0 ? 4.0 : 2.0), 2.0 * M * K * N, (long)M, K, N);
   if (tiny_ok(dt, M, N, K, false)) {
     a.z_sum = of.z; a.stats = sums;
     launch_tiny<MODE_DGRAD>(dt, st, a, K);

@@ -291,7 +291,7 @@ struct ftp_stage {
   PwShare share{0, 0};         // pointwise layers that share the launches of weight gradients
   std::vector<PwWgradJob> q_pw;
   std::vector<ReduceJob> q_red;
-  // Partial weight gradients that a stage on two streams leaves on the caller's until the end of the call: those of stride-2 depthwise layers
+  // Partial weight gradients that a stage on two streams leaves on the caller's until the end of the call: those of depthwise layers
   // (a place for each in ws_late) and of its first unit's expand layer, behind which nothing is left to run beside.
   std::vector<ReduceJob> q_late;
   float* ws_late = nullptr;
