@@ -215,7 +215,7 @@ struct UnitPlan {
   std::vector<size_t> z_off;       // per sub: byte offset of z in the slot stash
   std::vector<size_t> st_off;      // per sub: float offset of mean|invstd|scale|shift in the slot stats
   std::vector<size_t> part;        // per sub: floats of its partial weight gradients (stages that defer them)
-  size_t late_part;                // floats in front of its depthwise layer's place in ws_late
+  size_t late_part, late_floats;   // floats in front of its depthwise layer's place in ws_late, and those of the place
   std::vector<char> at_once;       // per sub: a pointwise layer of such a stage whose weight gradient runs next to its data gradient all the same
   std::vector<char> axis;          // per sub: a convolution along one axis that the kernels for those run
   size_t out_off;                  // byte offset of the materialised unit output (if any)
@@ -441,7 +441,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
     const UnitInfo& u = m->units[i];
     UnitPlan p;
     p.info = &u;
-    p.late_part = 0;
+    p.late_part = p.late_floats = 0;
     p.p_off = s->n_param; s->n_param += align_up(u.n_param, 8);
     p.bn_off = s->n_bn; s->n_bn += u.n_bn;
     for (const Sub& sb : u.subs) {
@@ -471,12 +471,12 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
         const size_t fused = m->dtype == FTP_BF16 ? pw_bwd_fused_ws(M, g.Cin, g.Cout) : 0;
         if (fused > 0 && &sb == &u.subs[0]) dz_stored = false;
         if (fused > part) part = fused;
-      } else if (sb.type == SUB_DW && u.subs.size() == 3 && dw_bwd_small_ok(g)) {
-        dz_stored = false;
-        part = 0;
       } else if (sb.type == SUB_DW) {
-        p.late_part = s->ws_late_floats; s->ws_late_floats += align_up(need, 64);
-        dz_stored = bn_bwd_small_ok(M, g.Cout) != 0;
+        // the short kernel, which leaves no partials, is for stages that defer: on two streams every layer has a place of its own until the call's end
+        const bool in_one = s->defers && u.subs.size() == 3 && dw_bwd_small_ok(g);
+        if (!s->defers) { p.late_part = s->ws_late_floats; p.late_floats = need; s->ws_late_floats += align_up(need, 64); }
+        if (in_one) part = 0;
+        dz_stored = !in_one && bn_bwd_small_ok(M, g.Cout);
       }
       if (zb > dz_max) dz_max = zb;
       dz_bytes += dz_stored ? zb : 0;
@@ -1182,6 +1182,9 @@ static int sub_backward(ftp_stage* s, Slot& sl, const UnitPlan& p, size_t k, con
   // and the weight gradient's partials.  dIn is not dA.
   if (sb.type == SUB_DW) {
     const bool small = bn_bwd_small_ok(M, C) != 0;
+    if (dw_bwd_ws(s->dt, g) > (s->defers ? p.part[k] : p.late_floats)) {
+      ftp_set_error("stage_backward: no place for a depthwise layer's partial weight gradients"); return FTP_ERR_UNSUPPORTED;
+    }
     Places at{nullptr, s->ws_late + p.late_part};
     if (s->defers) {
       at = take_places(s, small ? dz_size(s, sb) : 0, p.part[k], st);

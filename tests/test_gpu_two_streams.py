@@ -54,6 +54,23 @@ def test_layers_too_short_to_fork_behind_forked_ones():
     two_steps(units, (112, 112, 8), 64, 16, "f32", 6)
 
 
+# behind two long layers and one of 14x14: convolutions (3x3, by stride) and blocks (output channels, stride).  The depthwise layers' input rows: 12544 and
+# 256, 1024 alone, 256 twice; every one's partial weight gradients wait for the end of the call
+SHORT = {"behind a long one": [(32, 2), 4, (32, 1)], "alone": [4, (32, 1)], "two": [8, (24, 1), (32, 1)]}
+
+
+@pytest.mark.parametrize("which", SHORT)
+def test_short_blocks_on_two_streams(which):
+    """Blocks that a stage of short layers would run in the short kernels.  Single precision: the places do not depend on the type, and through BatchNorms over
+    16 different values a bfloat16 chain has no bound (activation decisions off by more than a tie)."""
+    print(f"two streams: short blocks, {which}", flush=True)
+    units, c = [conv(8, 144), conv(144, 144), conv(144, 32, 3, 3, 8)], 32
+    for what in SHORT[which]:
+        units.append(conv(c, c, 3, 3, what) if isinstance(what, int) else block(c, *what))
+        c = c if isinstance(what, int) else what[0]
+    two_steps(units, (112, 112, 8), 64, 16, "f32", 4)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_convolutions_along_one_axis_on_two_streams(dtype):
     """655360 rows of 64 channels: weight gradients on the side stream, that of the first layer on the caller's where there is no input gradient."""
