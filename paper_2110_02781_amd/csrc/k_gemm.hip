@@ -785,10 +785,17 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
   const float glo = act_lo(p.view.act), ghi = act_hi(p.view.act);
   if (SUMS && gated && jc < nj) { gsc0 = p.view.scale[jc]; gsc1 = p.view.scale[jc + 1]; gsh0 = p.view.shift[jc]; gsh1 = p.view.shift[jc + 1]; }     // an even width
   if (SUMS) asm volatile("" ::"v"(gsc0), "v"(gsc1), "v"(gsh0), "v"(gsh1));
+  // Eight rows of a tile are a chain of their own, and the chains of a block's tiles meet in s0 .. q1: with 25 tiles a block (112x112, batch 128) the results of
+  // a lane went through 400 additions one behind the other, where a pass over rows has 75 and 42 where its lanes meet; so it is 8 and 50.
+  float e0 = 0.f, e1 = 0.f, f0 = 0.f, f1 = 0.f;
   auto add_sums = [&](const float a, const float b, const float za, const float zb) __attribute__((always_inline)) {
     const float ya = fmaf(za, gsc0, gsh0), yb = fmaf(zb, gsc1, gsh1);
     const float ga = !gated || (ya > glo && ya < ghi) ? a : 0.f, gb = !gated || (yb > glo && yb < ghi) ? b : 0.f;
-    s0 += ga; q0 = fmaf(ga, za, q0); s1 += gb; q1 = fmaf(gb, zb, q1);
+    e0 += ga; f0 = fmaf(ga, za, f0); e1 += gb; f1 = fmaf(gb, zb, f1);
+  };
+  auto chain_ends = [&]() __attribute__((always_inline)) {
+    s0 += e0; q0 += f0; s1 += e1; q1 += f1;
+    e0 = e1 = f0 = f1 = 0.f;
   };
   // Have the two values arrive here.  Their first use is in the tile epilogue inside the loop, where the compiler
   // cannot tell how many younger loads are outstanding and waits for all of them: the prefetch of the next tile
@@ -829,7 +836,8 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
             load_pair(reinterpret_cast<const T*>(&zr[r]), za, zb);
             add_sums(a, b, za, zb);
             // two steps' loads are in flight around this: results in order, or the registers of sixteen rows at once cost a block of occupancy (192, so 152)
-            if (DEEP) asm volatile("" : "+v"(s0), "+v"(s1), "+v"(q0), "+v"(q1) :: "memory");
+            if (DEEP) asm volatile("" : "+v"(e0), "+v"(e1), "+v"(f0), "+v"(f1) :: "memory");
+            if (r % 8 == 7) chain_ends();
           }
         } else
 #pragma unroll
@@ -858,6 +866,7 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
       const size_t ig = irow + 8 * (r / 4) + (r % 4);
       float v0 = acc[0][r], v1 = acc[1][r];
       acc[0][r] = 0.f; acc[1][r] = 0.f;
+      if (SUMS && r == 8) chain_ends();
       if (ig >= ni || jc >= nj) continue;
       if (MODE == MODE_FWD) {
         v0 += b0; v1 += b1;
@@ -888,6 +897,7 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
         else { dst[0] = v0; if (jc + 1 < nj) dst[1] = v1; }
       }
     }
+    if (SUMS) chain_ends();
   };
 
   if constexpr (!DEEP) {
@@ -980,11 +990,14 @@ __global__ __launch_bounds__(256) void pw_gemm_rows_k(GemmArgs p) {
     if (threadIdx.x < 128) {
       const int col = threadIdx.x & 63, sq = threadIdx.x >> 6;   // column within the tile; 0 = sum, 1 = squares
       const int l = col >> 1, t = col & 1;
-      float tot = 0.f;
+      typename std::conditional<SUMS, double, float>::type tot = 0;      // sums of a data gradient: no chain of eight more
 #pragma unroll
-      for (int w = 0; w < 4; ++w) tot += red[w][l][2 * sq + t] + red[w][l + 32][2 * sq + t];
+      for (int w = 0; w < 4; ++w) {
+        if (SUMS) { tot += red[w][l][2 * sq + t]; tot += red[w][l + 32][2 * sq + t]; }
+        else tot += red[w][l][2 * sq + t] + red[w][l + 32][2 * sq + t];
+      }
       const size_t j = j0 + col;
-      if (j < nj) p.stats[((size_t)range * 2 + sq) * nj + j] = tot;
+      if (j < nj) p.stats[((size_t)range * 2 + sq) * nj + j] = (float)tot;
     }
   }
 }

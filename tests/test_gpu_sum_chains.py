@@ -1,0 +1,145 @@
+"""Sums over rows that kernels leave on the way (BatchNorm backward sums, depthwise weight gradients): their rounding error is no larger than that of a pass of its
+own.  The values that are summed are had bit for bit: the gradient at a unit boundary is the input gradient of a stage that begins there, and behind a depthwise
+layer whose weights are one at the centre it is the gradient of its raw output."""
+import math
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# A pass leaves at most 512 partial sums, of 32 rows at least, which are added in float64; the rows of a partial go through chains in single precision that
+# meet in another one: 2 * sqrt(rows) additions at the least.  For terms of either sign the error of n additions one behind the other is sqrt(n / 2) times the rounding
+# error of one, whose r.m.s. is 0.425 * 2^-24 of the value (uniform within half a last place, values spread over their logarithm), times the
+# r.m.s. of the sum.  SLACK: the r.m.s. error over some 64 sums is itself off by 9 %; and the result is rounded once more.
+SLACK = 1.3
+
+
+def bound(rows):
+    return SLACK * 0.425 * math.sqrt(math.sqrt(max(rows / 512.0, 32.0)) + 1.0)
+
+
+class Stage:
+    """A stage of single units with given parameter vectors, on the GPU."""
+
+    def __init__(self, P, units, params, in_shape, batch, dtype):
+        import torch
+        self.P, self.units = P, units
+        self.tdt = torch.float32 if dtype == "f32" else torch.bfloat16
+        self.m = P.model_create(units, *in_shape, P.F32 if dtype == "f32" else P.BF16)
+        self.s = P.stage_create(self.m, 0, len(units), batch, 1, 0)
+        self.n = [0 if p is None else p.size for p in params]
+        for u, p in enumerate(params):
+            if p is not None:
+                P.stage_import_weights(self.s, u, p)
+        shape = [P.model_unit_in_shape(self.m, u) for u in (0, len(units))]
+        self.x, self.y = (torch.empty((batch,) + tuple(s), dtype=self.tdt, device="cuda") for s in shape)
+        self.dx = torch.empty_like(self.x)
+
+    def forward(self, x):
+        self.P.stage_forward(self.s, 0, x, self.y, 0)
+        return self.y
+
+    def backward(self, dy):
+        self.P.stage_backward(self.s, 0, dy, self.dx, 0)
+        return self.dx
+
+    def grads(self, u):
+        return self.P.stage_export_grads(self.s, u, self.n[u]).astype(np.float64)
+
+    def close(self):
+        import torch
+        torch.cuda.synchronize()
+        self.P.stage_destroy(self.s)
+        self.P.model_destroy(self.m)
+
+
+def params(P, u, seed, centre=False):
+    """Weights; behind each BatchNorm in front of an activation 0.3 * N(0, 1) + 3: no value is near 0 or 6, no decision in question."""
+    import synth
+    import paper_2110_02781_amd.binding as B
+    out, act = [], u["kind"] == B.UNIT_CONV
+    layout = P.models.unit_param_layout(u)
+    if not layout:
+        return None
+    for k, (name, n, fan) in enumerate(layout):
+        on = act or (u["kind"] == B.UNIT_INVRES and k + 3 < len(layout))
+        if name == "wd" and centre:
+            out.append((np.arange(n) % 9 == 4).astype(np.float64))
+        elif fan > 0:
+            out.append(synth.normal(seed, f"{name}", (n,), std=float(np.sqrt(2.0 / fan))))
+        elif fan == 0:
+            out.append(np.full(n, 0.3 if on else 1.0))
+        else:
+            out.append(np.full(n, 3.0 if on and name != "b" else 0.0))
+    return np.concatenate(out).astype(np.float32)
+
+
+def error(got, ref, unit):
+    return float(np.sqrt(np.mean(((got - ref) / (unit * 2.0 ** -24)) ** 2)))
+
+
+def bn_errors(dtype, front, back, in_shape, batch, via, images=False):
+    """(errors of the shift and scale gradients of front's last BatchNorm in units of 2^-24 times the r.m.s. of the sum, rows): `back` leaves the sums.  via: begins the name
+    of a launch that has to be there.  The two stages do the same, bit for bit, as far as neither has a single convolution with few outputs, whose weight
+    gradient runs next to its data gradient.  images: the terms are those of whole images (behind an average the gradient is one for all its positions)."""
+    import torch
+    import paper_2110_02781_amd as P
+    import paper_2110_02781_amd.binding as B
+    pf, pb = [params(P, front, 1)], [params(P, u, 2 + i) for i, u in enumerate(back)]
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(7)
+    a, whole = Stage(P, [front], pf, in_shape, batch, dtype), Stage(P, [front] + back, pf + pb, in_shape, batch, dtype)
+    b = Stage(P, back, pb, tuple(a.y.shape[1:]), batch, dtype)
+    try:
+        x = torch.randn(a.x.shape, generator=gen, device="cuda").to(a.tdt)
+        dy = torch.randn(b.y.shape, generator=gen, device="cuda").to(a.tdt)
+        b.forward(a.forward(x))
+        da = b.backward(dy).double().reshape(-1, a.y.shape[-1])
+        whole.forward(x)
+        rows, c = da.shape
+        conv = 0 if front["kind"] == B.UNIT_CONV else 1
+        z = torch.from_numpy(P.stage_export_conv_output(whole.s, 0, 0, conv, rows * c)).cuda().double().reshape(rows, c)
+        mean, inv = P.stage_export_bn_batch_stats(whole.s, 0, 0, conv, 4 * c).astype(np.float64).reshape(4, c)[:2]
+        torch.cuda.synchronize()
+        P.ktrace_begin(-4096)
+        whole.backward(dy)
+        torch.cuda.synchronize()
+        names = [r["name"] for r in P.ktrace_end()]
+        assert any(n.startswith(via) for n in names) and f"bn_bwd_reduce {rows} {c} {front.get('act', B.ACT_NONE)}" not in names, names
+        s0, s1 = da.sum(0).cpu().numpy(), (da * z).sum(0).cpu().numpy()
+        terms = [v.reshape(batch, -1, c).sum(1) if images else v for v in (da, da * z)]
+        r0, r1 = (v.pow(2).sum(0).sqrt().cpu().numpy() for v in terms)
+        g = whole.grads(0)
+        return (error(g[-c:], s0, r0), error(g[-2 * c:-c], inv * (s1 - mean * s0), inv * (r1 + np.abs(mean) * r0))), rows
+    finally:
+        for s in (a, b, whole):
+            s.close()
+
+
+def invres(B, cin, cout, stride=1, expand=1):
+    return dict(kind=B.UNIT_INVRES, cin=cin, cout=cout, stride=stride, expand=expand)
+
+
+def conv1(B, cin, cout):
+    return dict(kind=B.UNIT_CONV, cin=cin, cout=cout, kh=1, kw=1, stride=1, pad_h=0, pad_w=0, act=B.ACT_RELU6)
+
+
+def check(what, errors, rows):
+    print(f"\n{what}: {rows} rows, errors {['%.2f' % e for e in errors]} of at most {bound(rows):.2f}", flush=True)
+    assert max(errors) <= bound(rows), what
+
+
+# an expand layer behind a block: many rows to a block of the streaming kernel, with a remainder; a tile to a block
+@pytest.mark.parametrize("dtype,c,h,w,batch", [("f32", 64, 112, 112, 256), ("f32", 64, 113, 111, 64), ("f32", 24, 260, 261, 5), ("bf16", 64, 112, 112, 256)])
+def test_streaming_data_gradient(dtype, c, h, w, batch):
+    import paper_2110_02781_amd.binding as B
+    e, rows = bn_errors(dtype, invres(B, 8, c), [invres(B, c, 8, 1, 2), invres(B, 8, 8)], (h, w, 8), batch, "pw_dgrad")
+    check(f"streaming data gradient {dtype}", e, rows)
+
+
+@pytest.mark.parametrize("dtype,c,h,w,batch", [("bf16", 32, 112, 112, 64), ("bf16", 32, 56, 56, 33)])
+def test_fused_backward(dtype, c, h, w, batch):
+    import paper_2110_02781_amd.binding as B
+    e, rows = bn_errors(dtype, invres(B, 8, c), [invres(B, c, 8, 1, 6), invres(B, 8, 8)], (h, w, 8), batch, "pw_bwd_fused")
+    check(f"fused backward {dtype}", e, rows)
