@@ -1133,8 +1133,15 @@ template <typename T, int S> struct DwBwd {
          NR = S == 1 || F32 ? 1 : 2,                                             // rounds of a tile's runs or quads
          VS = F32 ? 32 : 64, PH = S == 1 ? 10 : 5, PW = S == 1 ? TW + 2 : 9 };          // the patch has its largest size whatever the tile: offsets are constants
   typedef typename std::conditional<S == 1, float, T>::type P;                                  // patch elements
-  enum { PATCH = PH * PW * VS * sizeof(P) > kSlabSumsBytes ? PH * PW * VS * sizeof(P) : kSlabSumsBytes, STAGED = PATCH + 9 * VS * 4,
-         RED = 11 * 256 * 16, LDS = STAGED > RED ? STAGED : RED };
+  // the patch, where the eleven sums of all threads meet, or those of the layer's own BatchNorm; behind it the weights
+  enum { PATCH = PH * PW * VS * sizeof(P), RED = 11 * 256 * 16, WEIGHTS = PATCH > RED ? PATCH : RED, LDS = WEIGHTS + 9 * VS * 4 };
+  // Tiles whose values go through one chain of additions: at stride 1 68 for a tap or a sum, no more than in kernels of their own (a walk down strips for the weights: 12 rows
+  // of two columns and more, then up to 64 strips; a pass for the sums: 75 rows, then 42 lanes); at stride 2 half as many and less for a tap, 100 to 200 for a sum.  Errors in
+  // 2^-24 of the sums' r.m.s., 3.2 M rows, kernels of their own / one chain a block / this: fp32 stride 1 sums 3.0 and 4.0 / 5.0 and 4.3 / 3.0 and 2.2, weights 4.4 / 4.5 /
+  // 2.6, bfloat16 weights 2.0 / 2.7 / 1.2; stride 2 sums 3.8 and 4.1 / 4.6 and 4.5 / 2.7 and 3.3, bfloat16 (whose terms have few bits) 1.2 and 3.2 / 1.2 and 2.5 / 0.7 and 1.7.
+  // Chains of 12 and 8 tiles: width 1.4, batch 128, 26.8 -> 27.1 ms for 4 steps, these 26.9.
+  enum { CHAIN = S == 1 ? 17 : 25 };
+  static_assert((int)WEIGHTS >= (int)kSlabSumsBytes, "the partial sums of the layer's own BatchNorm");
 };
 template <typename T, int S, bool FORM, int NV, bool ONE>
 __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // three blocks to a CU: 168 registers
@@ -1143,11 +1150,12 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
   constexpr int NR = X::NR, VS = X::VS, PW = X::PW;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   __shared__ __attribute__((aligned(16))) float vec[FORM ? 5 : 1][64], prv[2][64];
+  __shared__ float met[ONE ? 1 : 11][64];             // sums of the chains that have met
   __builtin_amdgcn_s_setprio(3);                      // data-gradient chain: ahead of the weight-gradient stream's waves
   const DwPlan& d = p.d;
   const int C = p.C, Hin = p.Hin, Win = p.Win;
   PT* const patch = reinterpret_cast<PT*>(smem_raw);
-  float* const wl = reinterpret_cast<float*>(smem_raw + X::PATCH);         // [9][VS]
+  float* const wl = reinterpret_cast<float*>(smem_raw + X::WEIGHTS);       // [9][VS]
   const int lb = xcd_logical_block();
   const int slab = lb % d.nslab, part = lb / d.nslab, cg0 = slab * d.CGB, t0 = part * p.per, t1 = min(t0 + p.per, d.ntiles);
   const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB, c4 = cq * 4, gc = cg0 * 8 + c4;
@@ -1351,24 +1359,33 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
         }
       }
     }
-  }
-  // The runs of a channel quad are spread over spp threads: eleven vectors of each through LDS, summed in a fixed order, a wavefront to each vector in turn
-  float4* const red = reinterpret_cast<float4*>(smem_raw);         // [11][256]
-  __syncthreads();
-  const int tid = threadIdx.x, wave = tid >> 6, ch = tid & 63;
+    // The sums of CHAIN tiles (or of the block's last) meet: the runs of a channel quad are spread over spp threads, eleven vectors of each go through LDS and are
+    // summed in a fixed order, a wavefront to each vector in turn.
+    const bool last = ONE || tile + 1 == t1;
+    if (!last && (tile + 1 - t0) % X::CHAIN != 0) continue;
+    float4* const red = reinterpret_cast<float4*>(smem_raw);         // [11][256]
+    const int tid = threadIdx.x, wave = tid >> 6, ch = tid & 63;
+    __syncthreads();
 #pragma unroll
-  for (int t = 0; t < 9; ++t) red[t * 256 + tid] = aw[t];
-  red[9 * 256 + tid] = s1;
-  red[10 * 256 + tid] = s2;
-  __syncthreads();
-  if (ch >= nc) return;
-  for (int v = wave; v < (p.sums ? 11 : 9); v += 4) {
-    const float* src = reinterpret_cast<const float*>(red + v * 256) + ch;
-    float t = 0.f;
+    for (int t = 0; t < 9; ++t) red[t * 256 + tid] = aw[t];
+    red[9 * 256 + tid] = s1;
+    red[10 * 256 + tid] = s2;
+    __syncthreads();
+    if (ch < nc)
+      for (int v = wave; v < (p.sums ? 11 : 9); v += 4) {
+        const float* src = reinterpret_cast<const float*>(red + v * 256) + ch;
+        double t = ONE || tile - t0 < X::CHAIN ? 0.0 : (double)met[ONE ? 0 : v][ch];
 #pragma unroll 8
-    for (int sgi = 0; sgi < d.spp; ++sgi) t += src[sgi * QB * 4];
-    float* dst = v < 9 ? p.gw + ((size_t)part * 9 + v) * C : p.sums + ((size_t)part * 2 + v - 9) * C;
-    dst[cg0 * 8 + ch] = t;
+        for (int sgi = 0; sgi < d.spp; ++sgi) t += (double)src[sgi * QB * 4];
+        float* dst = v < 9 ? p.gw + ((size_t)part * 9 + v) * C : p.sums + ((size_t)part * 2 + v - 9) * C;
+        if (last) dst[cg0 * 8 + ch] = (float)t;
+        else met[ONE ? 0 : v][ch] = (float)t;
+      }
+    if (!ONE) {
+#pragma unroll
+      for (int t = 0; t < 9; ++t) aw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+      s1 = s2 = aw[0];
+    }
   }
 }
 

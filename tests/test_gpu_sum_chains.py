@@ -143,3 +143,40 @@ def test_fused_backward(dtype, c, h, w, batch):
     import paper_2110_02781_amd.binding as B
     e, rows = bn_errors(dtype, invres(B, 8, c), [invres(B, c, 8, 1, 6), invres(B, 8, 8)], (h, w, 8), batch, "pw_bwd_fused")
     check(f"fused backward {dtype}", e, rows)
+
+
+# many tiles to a block (and a last block of fewer), one tile to a block; either stride
+DW = [("f32", 1, 32, 112, 112, 256), ("bf16", 1, 32, 112, 112, 256), ("f32", 1, 96, 28, 28, 32), ("bf16", 1, 96, 28, 28, 32), ("bf16", 1, 16, 81, 97, 41),
+      ("f32", 2, 32, 112, 112, 256), ("bf16", 2, 32, 113, 111, 256), ("f32", 2, 96, 28, 28, 32), ("bf16", 2, 96, 28, 28, 32)]
+
+
+@pytest.mark.parametrize("dtype,stride,c,h,w,batch", DW)
+def test_depthwise_backward_sums(dtype, stride, c, h, w, batch):
+    import paper_2110_02781_amd.binding as B
+    e, rows = bn_errors(dtype, conv1(B, 8, c), [invres(B, c, 24, stride), invres(B, 24, 8)], (h, w, 8), batch, "dw_bwd")
+    check(f"depthwise backward, sums, stride {stride} {dtype}", e, rows)
+
+
+@pytest.mark.parametrize("dtype,c,h,w,batch", [d[:1] + d[2:] for d in DW if d[1] == 1])
+def test_depthwise_weight_gradient(dtype, c, h, w, batch):
+    """At stride 1 with weights of one at the centre the data gradient is dz."""
+    import torch
+    import paper_2110_02781_amd as P
+    import paper_2110_02781_amd.binding as B
+    u = invres(B, c, 24)
+    s = Stage(P, [u], [params(P, u, 3, centre=True)], (h, w, c), batch, dtype)
+    try:
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(7)
+        x = torch.randn(s.x.shape, generator=gen, device="cuda").to(s.tdt)
+        s.forward(x)
+        dz = s.backward(torch.randn(s.y.shape, generator=gen, device="cuda").to(s.tdt)).double()
+        got, xp, refs, terms = s.grads(0)[:9 * c].reshape(c, 9), torch.nn.functional.pad(x.double(), (0, 0, 1, 1, 1, 1)), [], []
+        for i in range(3):
+            for j in range(3):
+                p = dz * xp[:, i:i + h, j:j + w]
+                refs.append(p.sum((0, 1, 2)).cpu().numpy())
+                terms.append(p.pow(2).sum((0, 1, 2)).sqrt().cpu().numpy())
+        check(f"depthwise weight gradient {dtype}", [error(got, np.stack(refs, 1), np.stack(terms, 1))], batch * h * w)
+    finally:
+        s.close()
