@@ -5,6 +5,8 @@
 // are reduced in a fixed order (per thread -> LDS across the block -> float64
 // across blocks), so results are run-to-run deterministic.  Short tensors (at most
 // 2048 rows) use one-launch variants in which a block owns 4 channels over all rows.
+#include <type_traits>
+
 #include "dev_common.h"
 #include "kernels.h"
 #include "bn_pending.h"
@@ -724,18 +726,19 @@ void bn_finalize_apply_small(int dt, hipStream_t st, const BnPending& pend, cons
 // that finishes statistics in every block took 264 x 1792 channels of 9 positions, fp32, from 18.9 to 27.8 us, 73 x 1280 of 4 from 5.8 to 8.3.
 // OPEN: also, per image and channel, the number of positions that the activation passes and the sum of the raw values there, open[N][2][C].  Behind an
 // average the gradient is the same at all positions, so times these it is that BatchNorm's backward sums, and nobody has to read the tensor for them.
+// A lane's sum over more than 64 positions is kept in float64, lanes meet two by two and images in float64: errors of the scale gradient in 2^-24 of the sum's
+// r.m.s., fp32, 64 channels, 512 images of 7x7, 100 of 14x14, 16 of 40x40: a pass over the tensor 1.9, 2.0 and 1.8, lanes one behind the other and images in fp32
+// 2.5, 2.4 and 3.2, so 1.2, 1.2 and 1.4.
 template <typename T, bool PEND, int U, bool OPEN>
 __global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float eps, float momentum, int N, int HW, int CG, T* __restrict__ out,
                                                 float* __restrict__ open) {
-  constexpr int V = OPEN ? 24 : 8;
-  __shared__ float red[64][V];
+  __shared__ float red[64][8];
   __shared__ double fin[64];
   __shared__ float vec[2][8];
   const int i = blockIdx.x, n = i / CG, cg = i % CG, lane = threadIdx.x;
   const T* src = reinterpret_cast<const T*>(in.z) + (size_t)n * HW * CG * 8 + cg * 8;
-  float acc[V];
-#pragma unroll
-  for (int e = 0; e < V; ++e) acc[e] = 0.f;
+  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, open_n[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+  typename std::conditional<(U > 1), double, float>::type open_z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   float sc[8], sh[8];
   const bool view = in.scale != nullptr;
   Raw<T> r[U];
@@ -766,21 +769,30 @@ __global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float e
         acc[e] += view ? round_to<T>(clamp_act(y, lo, hi)) : v[e];
         if constexpr (OPEN) {
           const bool on = y > lo && y < hi;
-          acc[8 + e] += on ? 1.f : 0.f;
-          acc[16 + e] += on ? v[e] : 0.f;
+          open_n[e] += on ? 1.f : 0.f;
+          open_z[e] += on ? v[e] : 0.f;
         }
       }
     }
   }
 #pragma unroll
-  for (int e = 0; e < V; ++e) red[lane][e] = acc[e];
+  for (int e = 0; e < 8; ++e) red[lane][e] = acc[e];
+  if constexpr (OPEN) {
+    float z[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { open_n[e] = wave_sum_last(open_n[e]); z[e] = wave_sum_last((float)open_z[e]); }
+    if (lane == 63) {
+      float* o = open + (size_t)n * 2 * CG * 8 + cg * 8;
+      store8(o, open_n);
+      store8(o + CG * 8, z);
+    }
+  }
   __syncthreads();
-  if (lane < V) {
+  if (lane < 8) {
     float s = 0.f;
     for (int l = 0; l < 64; ++l) s += red[l][lane];
     float o = s * (1.f / (float)HW);
-    if (lane < 8) out[(size_t)i * 8 + lane] = from_f32<T>(o);
-    else open[((size_t)n * 2 + (lane >> 4)) * CG * 8 + cg * 8 + (lane & 7)] = s;
+    out[(size_t)i * 8 + lane] = from_f32<T>(o);
   }
 }
 
@@ -809,7 +821,7 @@ __global__ void gap_bwd_k(const T* __restrict__ dOut, size_t nvec, int HW, int C
     const int C = CG * 8, nc = (C + 255) / 256, j = blockIdx.x - nmain, c = j % nc * 256 + threadIdx.x, chunk = j / nc;
     const int n0 = chunk * per, n1 = min(n0 + per, N);
     if (c >= C) return;
-    float s1 = 0.f, s2 = 0.f;
+    double s1 = 0.0, s2 = 0.0;
     for (int n = n0; n < n1; n += 8) {
       float o[8], cnt[8], z[8];
 #pragma unroll
@@ -823,12 +835,12 @@ __global__ void gap_bwd_k(const T* __restrict__ dOut, size_t nvec, int HW, int C
       for (int u = 0; u < 8; ++u) {
         const float d = round_to<T>(o[u] * inv);          // as stored below
         const bool on = n + u < n1 && cnt[u] > 0.f;       // chosen, not multiplied: an infinite gradient of what is off stays out
-        s1 += on ? d * cnt[u] : 0.f;
-        s2 += on ? d * z[u] : 0.f;
+        s1 += on ? (double)d * cnt[u] : 0.0;
+        s2 += on ? (double)d * z[u] : 0.0;
       }
     }
-    sums[((size_t)chunk * 2) * C + c] = s1;
-    sums[((size_t)chunk * 2 + 1) * C + c] = s2;
+    sums[((size_t)chunk * 2) * C + c] = (float)s1;
+    sums[((size_t)chunk * 2 + 1) * C + c] = (float)s2;
     return;
   }
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < nvec; i += (size_t)nmain * blockDim.x) {

@@ -1927,10 +1927,10 @@ __global__ __launch_bounds__(256) void fc_bwd_k(const T* __restrict__ d, View in
       __syncthreads();
       if (threadIdx.x < 32 && k0 + (int)(threadIdx.x & 15) < K) {
         const int q = threadIdx.x >> 4, c = threadIdx.x & 15;
-        float t = 0.f;
+        double t = 0.0;                                 // images meet in float64, as in gap_bwd_k
 #pragma unroll
         for (int r = 0; r < 16; ++r) t += red[q][r][c];
-        sums[((size_t)(tile / kt) * 2 + q) * K + k0 + c] = t;
+        sums[((size_t)(tile / kt) * 2 + q) * K + k0 + c] = (float)t;
       }
     }
     if (!written) return;

@@ -180,3 +180,13 @@ def test_depthwise_weight_gradient(dtype, c, h, w, batch):
         check(f"depthwise weight gradient {dtype}", [error(got, np.stack(refs, 1), np.stack(terms, 1))], batch * h * w)
     finally:
         s.close()
+
+
+# up to 64 positions and more; with a fully connected layer behind the average whose backward writes the average's
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("hw,batch,fc", [((7, 7), 512, False), ((14, 14), 100, False), ((1, 256), 128, False), ((40, 40), 16, False), ((1, 128), 64, True)])
+def test_average(dtype, hw, batch, fc):
+    import paper_2110_02781_amd.binding as B
+    back = [dict(kind=B.UNIT_GAP, cin=64, cout=64)] + ([dict(kind=B.UNIT_FC, cin=64, cout=10)] if fc else [])
+    e, rows = bn_errors(dtype, conv1(B, 8, 64), back, hw + (8,), batch, "fc_bwd" if fc else "gap_bwd", images=True)
+    check(f"average {dtype}", e, rows)
