@@ -924,13 +924,14 @@ __device__ __forceinline__ float group_all(float x, F op) {
 template <int G> __device__ __forceinline__ float group_max(float x) { return group_all<G>(x, [](float a, float b) { return fmaxf(a, b); }); }
 template <int G> __device__ __forceinline__ float group_sum(float x) { return group_all<G>(x, [](float a, float b) { return a + b; }); }
 
-// exp(t) for t <= 0 (NaN stays NaN): 2^h times 2^l with h = t * log2(e) rounded and l what that leaves out, 2^l = 1 + l * ln(2) to 2^-40.
+// exp(t) for t <= 0 (NaN stays NaN), down to the smallest numbers: 2^n times 2^f, n the integer next to t * log2(e) and f what that leaves out, log2(e) in two parts.  Nine
+// instructions; probabilities off by 0.615 * 2^-24 of their value, r.m.s., as with expf (0.61, thirteen); 2^(t log2(e)) times one plus a rest was
+// eight and 0.74, and zero below 2^-126: 4096 x 1000 bfloat16 7.55 -> 7.67 us.
 __device__ __forceinline__ float exp_below(float t) {
-  t = t < -150.f ? -150.f : t;                             // 2^h is zero there; -inf has no rest
-  const float h = t * 1.44269502f;
-  const float l = fmaf(t, 1.92596303e-8f, fmaf(t, 1.44269502f, -h));
-  const float e = __builtin_amdgcn_exp2f(h);
-  return fmaf(e, l * 0.693147181f, e);
+  t = t < -150.f ? -150.f : t;                             // zero there; -inf has no rest
+  const float n = rintf(t * 1.44269502f);
+  const float f = fmaf(t, 1.92596303e-8f, fmaf(t, 1.44269502f, -n));
+  return ldexpf(__builtin_amdgcn_exp2f(f), (int)n);
 }
 
 template <typename T, int G, int E, int VEC, bool AL>

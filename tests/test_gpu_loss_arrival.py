@@ -50,3 +50,36 @@ def test_last_block_adds_the_mean(dtype):
             g.replay()
             torch.cuda.synchronize()
             assert torch.equal(loss, first[i][0]) and torch.equal(d, first[i][1])
+
+
+@pytest.mark.parametrize("b,n,std", [(64, 1000, 2.0), (2048, 1000, 3.0), (4096, 10, 3.0), (256, 200, 3.0)])
+def test_exponentials(b, n, std):
+    """Logits on a grid of 2^-10: what is taken from the row's largest is exact.  Divided by a power of two of rows, a probability has the error of its exponential (a power of two that is right to about half
+    a last place, r.m.s. 0.43 * 2^-24 as after a rounding) and of its product with the inverse sum (0.43): 0.60, and a tenth for the sample; the sum's own error, the same for
+    a whole row, is taken out."""
+    import torch
+    import paper_2110_02781_amd as P
+    print(f"loss, exponentials {b} x {n}", flush=True)
+    x = torch.from_numpy((np.round(synth.normal(7, "logits", (b, n), std=std) * 1024) / 1024).astype(np.float32)).cuda()
+    d, loss = torch.empty_like(x), torch.zeros(1, device="cuda")
+    P.softmax_ce_static(x, torch.zeros(b, dtype=torch.int32, device="cuda"), b, n, P.F32, d, loss, 0)
+    torch.cuda.synchronize()
+    p = torch.softmax(x.double(), 1) / b
+    e = ((d.double() - p) / p)[:, 1:]                                   # column 0 is the label's
+    e = (e - e.median(1, keepdim=True).values) * 2.0 ** 24
+    assert float(e.pow(2).mean().sqrt()) <= 0.66
+
+
+def test_smallest_exponentials():
+    """Probabilities below 2^-126 are kept as far as single precision holds them."""
+    import torch
+    import paper_2110_02781_amd as P
+    x = torch.zeros(32, 300, device="cuda")
+    x[:, 1:] = -torch.linspace(80, 104, 299, device="cuda")
+    d, loss = torch.empty_like(x), torch.zeros(1, device="cuda")
+    P.softmax_ce_static(x, torch.zeros(32, dtype=torch.int32, device="cuda"), 32, 300, P.F32, d, loss, 0)
+    torch.cuda.synchronize()
+    p = (torch.softmax(x.double(), 1) / 32)[:, 1:]
+    # half a step of the smallest numbers in front of the division by 32 rows and behind it, and a few roundings
+    assert bool(((d[:, 1:].double() - p).abs() <= 2.0 ** -149 + 4 * 2.0 ** -24 * p).all())
+    assert float(d[0, 200]) > 0.0
