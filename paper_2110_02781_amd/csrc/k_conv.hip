@@ -1049,9 +1049,9 @@ __global__ __launch_bounds__(NT) void dw_bwd_small_k(BnBwdIn bo, const T* __rest
   __syncthreads();
   asm volatile("" : "+v"(gw_old), "+v"(f_mu), "+v"(f_is), "+v"(f_g), "+v"(f_gg), "+v"(f_gb));
   if (tid < 9 * V) {
-    float tot = 0.f;
+    double tot = 0.0;                        // up to sixteen wavefronts: no chain of that length in fp32
     for (int q = 0; q < nw; ++q) tot += red[q][tid];
-    g_w[(size_t)(c0 + tid % V) * 9 + tid / V] = gw_old + tot;
+    g_w[(size_t)(c0 + tid % V) * 9 + tid / V] = gw_old + (float)tot;
   } else if (tid >= 64 && tid < 64 + V) {
     const int e = tid - 64, c = c0 + e;
     double s0 = 0.0, s1 = 0.0;
