@@ -1165,6 +1165,7 @@ static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* la
 void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* labels, int B, int classes,
                 float* row_loss, void* dlogits, float* loss, unsigned* arrived) {
   KScope ks(st, "softmax_ce", 2.0 * B * classes * (dt == 0 ? 4.0 : 2.0), 8.0 * B * classes);
+  if (softmax_ce_arrives(B, classes)) ks.route(arrived ? "arrival" : "two launches");
   FTP_DISPATCH(dt, softmax_ce_launch<T>(st, (const T*)logits, labels, B, classes, row_loss, (T*)dlogits, loss, arrived));
 }
 

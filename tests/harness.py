@@ -75,15 +75,20 @@ def launches(run):
     return {r["name"]: r["launches"] for r in P.ktrace_end()}
 
 
-def routes(run):
-    """{"<kernel> <tile> family d0 d1 d2": launches} of run(), of the kernels that say which tile they run."""
+def launches_by_shape(run):
+    """{"family d0 d1 d2": launches} of run(), and under "__route <kernel> <tile> family d0 d1 d2" those of the kernels that say which tile they run."""
     import torch
     import paper_2110_02781_amd as P
     torch.cuda.synchronize()
     P.ktrace_begin(-4096)
     run()
     torch.cuda.synchronize()
-    return {r["name"][8:]: r["launches"] for r in P.ktrace_end() if r["name"].startswith("__route ")}
+    return {r["name"]: r["launches"] for r in P.ktrace_end()}
+
+
+def routes(run):
+    """{"<kernel> <tile> family d0 d1 d2": launches} of run(), of the kernels that say which tile they run."""
+    return {k[8:]: n for k, n in launches_by_shape(run).items() if k.startswith("__route ")}
 
 
 def assert_two_streams(layers, backward):
