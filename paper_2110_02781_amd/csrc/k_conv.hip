@@ -1109,8 +1109,8 @@ void dw_bwd_small(int dt, hipStream_t st, const BnBwdIn& bo, const void* w, HVie
 // with the six dz under each row of taps, in LDS in fp32 (converted once instead of for up to nine taps); stride 2: quads of 2 x 2 pixels, which
 // four dz values reach (nine products, no parity to branch on).  The weights stay in LDS: in registers, one block less would fit a CU.
 // Bound by memory at stride 2 (112x112x144, batch 64, bfloat16: 126 us, 4.7 TB/s; its passes were 18 + 48 + 106 + 70) and by vector instructions at stride 1,
-// some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.57 ms a step; their data
-// and weight gradients were 1.80 and the passes for dz and the sums another 0.9, on two streams (a step 7.27 -> 6.79 ms; 224x224 fp32 3.51 -> 3.21).
+// some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.79 ms a step (of kernels that run beside weight
+// gradients); their data and weight gradients were 1.80 and the passes for dz and the sums another 0.9, on two streams (a step 7.27 -> 6.79 ms; 224x224 fp32 3.51 -> 3.21).
 // bfloat16 tiles of 8 x 16 at stride 1: 207 registers, two blocks to a CU, or scratch with three: 1.12 and 1.24 ms for the stride-1 layers, 1.03 so.
 // ONE: a block of a single tile requests the tile together with the weights and the partial sums.  The eleven sums of a block leave in one round
 // through LDS, a wavefront to each in turn.  Both against a request after the prologue and four rounds of twelve numbers: the width-1.4 step
@@ -1133,15 +1133,16 @@ template <typename T, int S> struct DwBwd {
          NR = S == 1 || F32 ? 1 : 2,                                             // rounds of a tile's runs or quads
          VS = F32 ? 32 : 64, PH = S == 1 ? 10 : 5, PW = S == 1 ? TW + 2 : 9 };          // the patch has its largest size whatever the tile: offsets are constants
   typedef typename std::conditional<S == 1, float, T>::type P;                                  // patch elements
-  // the patch, where the eleven sums of all threads meet, or those of the layer's own BatchNorm; behind it the weights
-  enum { PATCH = PH * PW * VS * sizeof(P), RED = 11 * 256 * 16, WEIGHTS = PATCH > RED ? PATCH : RED, LDS = WEIGHTS + 9 * VS * 4 };
+  // the patch, or the sums of the layer's own BatchNorm; behind it the weights.  The eleven sums of all threads meet all over that, or, where another tile may follow, in front
+  // of the weights.
+  enum { PATCH = PH * PW * VS * sizeof(P) > kSlabSumsBytes ? PH * PW * VS * sizeof(P) : kSlabSumsBytes, RED = 11 * 256 * 16, STAGED = PATCH + 9 * VS * 4,
+         LDS_ONE = STAGED > RED ? STAGED : RED, WEIGHTS = PATCH > RED ? PATCH : RED, LDS_MORE = WEIGHTS + 9 * VS * 4 };
   // Tiles whose values go through one chain of additions: at stride 1 68 for a tap or a sum, no more than in kernels of their own (a walk down strips for the weights: 12 rows
   // of two columns and more, then up to 64 strips; a pass for the sums: 75 rows, then 42 lanes); at stride 2 half as many and less for a tap, 100 to 200 for a sum.  Errors in
-  // 2^-24 of the sums' r.m.s., 3.2 M rows, kernels of their own / one chain a block / this: fp32 stride 1 sums 3.0 and 4.0 / 5.0 and 4.3 / 3.0 and 2.2, weights 4.4 / 4.5 /
-  // 2.6, bfloat16 weights 2.0 / 2.7 / 1.2; stride 2 sums 3.8 and 4.1 / 4.6 and 4.5 / 2.7 and 3.3, bfloat16 (whose terms have few bits) 1.2 and 3.2 / 1.2 and 2.5 / 0.7 and 1.7.
-  // Chains of 12 and 8 tiles: width 1.4, batch 128, 26.8 -> 27.1 ms for 4 steps, these 26.9.
+  // 2^-24 of the sums' r.m.s., 3.2 M rows, kernels of their own / one chain a block / this: fp32 stride 1 sums 3.0 and 4.0 / 5.0 and 4.3 / 3.0 and 2.7, weights 4.4 / 4.5 /
+  // 2.8, bfloat16 weights 2.0 / 2.7 / 1.6; stride 2 sums 3.8 and 4.1 / 4.6 and 4.5 / 3.1 and 3.8, bfloat16 (whose terms have few bits) 1.2 and 3.2 / 1.2 and 2.5 / 1.0 and 1.6.
+  // Width 1.4, batch 128: 105.2 us a launch, one chain a block 103.9; with chains of 12 and 8 tiles a step takes 1 % longer.
   enum { CHAIN = S == 1 ? 17 : 25 };
-  static_assert((int)WEIGHTS >= (int)kSlabSumsBytes, "the partial sums of the layer's own BatchNorm");
 };
 template <typename T, int S, bool FORM, int NV, bool ONE>
 __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // three blocks to a CU: 168 registers
@@ -1155,7 +1156,7 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
   const DwPlan& d = p.d;
   const int C = p.C, Hin = p.Hin, Win = p.Win;
   PT* const patch = reinterpret_cast<PT*>(smem_raw);
-  float* const wl = reinterpret_cast<float*>(smem_raw + X::WEIGHTS);       // [9][VS]
+  float* const wl = reinterpret_cast<float*>(smem_raw + (ONE ? X::PATCH : X::WEIGHTS));       // [9][VS]
   const int lb = xcd_logical_block();
   const int slab = lb % d.nslab, part = lb / d.nslab, cg0 = slab * d.CGB, t0 = part * p.per, t1 = min(t0 + p.per, d.ntiles);
   const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB, c4 = cq * 4, gc = cg0 * 8 + c4;
@@ -1374,12 +1375,20 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
     if (ch < nc)
       for (int v = wave; v < (p.sums ? 11 : 9); v += 4) {
         const float* src = reinterpret_cast<const float*>(red + v * 256) + ch;
-        double t = ONE || tile - t0 < X::CHAIN ? 0.0 : (double)met[ONE ? 0 : v][ch];
-#pragma unroll 8
-        for (int sgi = 0; sgi < d.spp; ++sgi) t += (double)src[sgi * QB * 4];
+        // four chains, 6 to 10 additions one behind the other in most layers.  In float64 the blocks of one tile took 4 to 10 % longer; as one chain in fp32 of 16 or 32 the error of fp32
+        // layers with few rows was 2.0 where a pass has 1.7 (25088 x 96), so it is 1.4.
+        float q[4] = {0.f, 0.f, 0.f, 0.f};
+        int sgi = 0;
+#pragma unroll 2
+        for (; sgi + 3 < d.spp; sgi += 4)
+#pragma unroll
+          for (int u = 0; u < 4; ++u) q[u] += src[(sgi + u) * QB * 4];
+        for (; sgi < d.spp; ++sgi) q[0] += src[sgi * QB * 4];
+        float t = (q[0] + q[1]) + (q[2] + q[3]);
+        if (!ONE && tile - t0 >= X::CHAIN) t += met[ONE ? 0 : v][ch];
         float* dst = v < 9 ? p.gw + ((size_t)part * 9 + v) * C : p.sums + ((size_t)part * 2 + v - 9) * C;
-        if (last) dst[cg0 * 8 + ch] = (float)t;
-        else met[ONE ? 0 : v][ch] = (float)t;
+        if (last) dst[cg0 * 8 + ch] = t;
+        else met[ONE ? 0 : v][ch] = t;
       }
     if (!ONE) {
 #pragma unroll
@@ -1436,10 +1445,10 @@ void dw_bwd(int dt, hipStream_t st, const void* dA, const HView* own, const BnPe
   a.dIn = dIn; a.sums = sums; a.gw = gw_part;
   a.prev = DwPrev{in.z, in.scale, in.shift, in.act};
   if (a.d.PH > (g.stride == 1 ? 10 : 5) || a.d.PW > (g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::PW : DwBwd<bf16_t, 1>::PW) : 9)) { launch_plan_failed("depthwise backward patch beyond the kernel's"); return; }
-  size_t lds = g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::LDS : DwBwd<bf16_t, 1>::LDS) : (dt == 0 ? DwBwd<float, 2>::LDS : DwBwd<bf16_t, 2>::LDS);
   const dim3 grid((unsigned)P * a.d.nslab);
 #define FTP_DW_BWD1(T, S, NV, ONE)                                                                            \
   do {                                                                                                        \
+    const size_t lds = ONE ? DwBwd<T, S>::LDS_ONE : DwBwd<T, S>::LDS_MORE;                                    \
     if (own) hipLaunchKernelGGL((dw_bwd_k<T, S, true, NV, ONE>), grid, dim3(256), lds, st, a);                \
     else hipLaunchKernelGGL((dw_bwd_k<T, S, false, NV, ONE>), grid, dim3(256), lds, st, a);                   \
   } while (0)
