@@ -735,7 +735,9 @@ __global__ __launch_bounds__(64) void gap_fwd_k(View in, BnPending pend, float e
   __shared__ float red[64][8];
   __shared__ double fin[64];
   __shared__ float vec[2][8];
-  const int i = blockIdx.x, n = i / CG, cg = i % CG, lane = threadIdx.x;
+  // Neighbouring groups share the lines of an image's rows: on one XCD they are fetched once.  128 images of 7x7, 1792 channels, bfloat16 27.6 -> 17.8 us (26.3 before
+  // it left anything for the backward).
+  const int i = xcd_logical_block(), n = i / CG, cg = i % CG, lane = threadIdx.x;
   const T* src = reinterpret_cast<const T*>(in.z) + (size_t)n * HW * CG * 8 + cg * 8;
   float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0}, open_n[8] = {0, 0, 0, 0, 0, 0, 0, 0};
   typename std::conditional<(U > 1), double, float>::type open_z[8] = {0, 0, 0, 0, 0, 0, 0, 0};
