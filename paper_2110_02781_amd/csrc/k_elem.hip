@@ -593,11 +593,13 @@ __global__ __launch_bounds__(256) void bn_bwd_finish_apply_k(const T* __restrict
   }
 }
 
-// Every block reads 512 bytes for each partial: up to 200 of them, and tensors whose blocks run in one turn.  Steps, ms, finalize launches / this rule:
-// units 15-18 at 224x224 bfloat16 batch 64 (12 steps) 4.81 / 4.60, 32x32 fp32 (10) 9.58 / 9.47, 161x193 width 0.5 bfloat16 (8) 8.91 / 8.79, 224x224
-// bfloat16 recomputing (4) 12.46 / 12.26, 224x224 fp32 (3) 10.61 / 10.54.  With up to 512 partials 10.72 there and 12.41 recomputing, width 1.4
-// batch 128 (4) 29.14 / 29.17 / 29.55; with tensors of up to 64 M values too 30.0.  (The depthwise forward doing the same for its input's
-// BatchNorm took as long as the launch it saved.)
+// Every block reads 512 bytes for each partial: up to 256 of them, and tensors whose blocks run in one turn.  Steps, ms, finalize launches for all / where there are more than
+// 200 partials or more values (when the depthwise backward was passes of its own): units 15-18 at 224x224 bfloat16 batch 64 (12 steps) 4.81 / 4.60, 32x32 fp32 (10) 9.58 / 9.47,
+// 161x193 width 0.5 bfloat16 (8) 8.91 / 8.79, 224x224 bfloat16 recomputing (4) 12.46 / 12.26, 224x224 fp32 (3) 10.61 / 10.54; with up to 512 partials 10.72 there and 12.41 recomputing,
+// width 1.4 batch 128 (4) 29.14 / 29.17 / 29.55, with tensors of up to 64 M values too 30.0.  (The depthwise forward doing the same for its input's BatchNorm took as long as the launch
+// it saved.)  With the kernels that stand here, up to 128 / 200 / 256 partials: 32x32 8.89 / 8.98 / 8.82, 97x75 fp32 6.96 / 7.00 / 6.88, 161x193 8.21 / 8.39 / 8.12, recomputing 11.56 /
+// 11.55 / 11.47, the others within 0.5 % of each other.  More would need a larger buffer: a layer that leaves sums while it reads others has half of 512.
+// Blocks at most (kFinishBlocks) 512 / 1024 / 2048: 32x32 8.78 / 8.82 / 9.01, 97x75 6.88 / 6.88 / 6.98, 224x224 fp32 9.38 / 9.39 / 9.44, 161x193 8.11 / 8.12 / 8.24, the others even.
 int bn_finish_ok(size_t M, int C, int P) {
   return P <= 256 && M * (size_t)C <= ((size_t)16 << 20);
 }
@@ -1017,10 +1019,10 @@ struct CeRow {
 // Wavefront = row.  Bound by memory: 4096 x 1000 bfloat16 moves 16 MB; a block per row, which goes over its row three
 // times with six block-wide reductions between, took 14 us.
 // The mean: a block's rows are one partial, and the last block to arrive adds all of them, in order; a launch for it cost as much as the rows where
-// they are few (64 x 1000 bfloat16 7.5 us a call, 5.0 so; 4096 x 1000 8.4 / 7.6, 16384 x 1000 18.5 / 16.6, 9000 x 100 fp32 7.2 / 7.25).  partial and arrived go past the L2s (each
+// they are few (64 x 1000 bfloat16 7.2 us a call, 4.7 so; softmax_ce_arrives has more).  partial and arrived go past the L2s (each
 // XCD has its own) one by one: a fence would write a whole L2 back.  Additions to one counter take some 12 ns each, so the blocks arrive in
 // kCeGroups groups and the groups at the first counter (563 blocks at one: 3.5 us more).  Whoever arrives last leaves zeros.
-// 8 rows a block: with 16 the few rows take 0.6 us more, with 4 the 4096 x 1000 0.5.  arrived == nullptr: the partials only.
+// 8 rows a block: with 16 the few rows take 0.6 us more, with 4 the 4096 x 1000 0.5.
 template <typename T, int E, int VEC, bool AL>
 __global__ __launch_bounds__(kCeRows * 64) void softmax_ce_wave_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B, int classes,
                                                                   float* partial, unsigned* arrived, T* __restrict__ dlogits, float* __restrict__ loss) {
@@ -1043,11 +1045,11 @@ __global__ __launch_bounds__(kCeRows * 64) void softmax_ce_wave_k(const T* __res
     if (l == 0) {
       __hip_atomic_store(partial + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");            // it is there before this block counts as arrived
-      if (arrived) before = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      before = __hip_atomic_fetch_add(mine, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
   if (b < B) r.template store<WHOLE>(dlogits + (size_t)b * classes, classes, l, 1.f / (float)B);
-  if (wave != 0 || !arrived || __builtin_amdgcn_readfirstlane(before) + 1 != members) return;
+  if (wave != 0 || __builtin_amdgcn_readfirstlane(before) + 1 != members) return;
   if (l == 0) {
     __hip_atomic_store(mine, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     before = __hip_atomic_fetch_add(arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -1066,6 +1068,28 @@ __global__ __launch_bounds__(kCeRows * 64) void softmax_ce_wave_k(const T* __res
     *loss = s / (float)B;
     __hip_atomic_store(arrived, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// The rows alone, for a mean in a launch behind.  Four rows a block and nothing between its wavefronts; many long rows in bfloat16 eight, which are read by all before the first is
+// written: 16384 x 1000 19.4 -> 18.5 us, 60000 x 1000 52 -> 49.
+template <typename T, int E, int VEC, bool AL, int RPB>
+__global__ __launch_bounds__(RPB * 64) void softmax_ce_rows_k(const T* __restrict__ logits, const int32_t* __restrict__ labels, int B, int classes,
+                                                         float* __restrict__ row_loss, T* __restrict__ dlogits) {
+  constexpr bool WHOLE = VEC > 1;
+  const int l = threadIdx.x & 63, b = blockIdx.x * RPB + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (RPB == 4 && b >= B) return;
+  CeRow<T, 64, E, VEC, AL> r;
+  float t = 0.f;
+  if (RPB == 4 || b < B) {
+    r.fetch(logits + (size_t)b * classes, labels + b, classes, l);
+    t = r.template sums<WHOLE>(classes, l);
+  }
+  if (RPB > 4) {
+    __syncthreads();
+    if (b >= B) return;
+  }
+  r.template store<WHOLE>(dlogits + (size_t)b * classes, classes, l, 1.f / (float)B);
+  if (l == 0) row_loss[b] = t;
 }
 
 // Few elements: one block does all rows and their mean.  Latency only, and a second dependent launch is half of it.
@@ -1099,17 +1123,16 @@ __global__ __launch_bounds__(1024) void softmax_ce_one_k(const T* __restrict__ l
   }
 }
 
-// the sum of n partial sums over B rows
-__global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ row_loss, int n, int B, float* __restrict__ loss) {
+__global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ row_loss, int B, float* __restrict__ loss) {
   __shared__ float part[16];
   const int nt = blockDim.x;
   float s = 0.f;
-  for (int i0 = threadIdx.x; i0 < n; i0 += 8 * nt) {        // eight loads per trip to memory
+  for (int i0 = threadIdx.x; i0 < B; i0 += 8 * nt) {        // eight loads per trip to memory
     float x[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) x[u] = row_loss[i0 + nt * u < n ? i0 + nt * u : 0];
+    for (int u = 0; u < 8; ++u) x[u] = row_loss[i0 + nt * u < B ? i0 + nt * u : 0];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) s += i0 + nt * u < n ? x[u] : 0.f;
+    for (int u = 0; u < 8; ++u) s += i0 + nt * u < B ? x[u] : 0.f;
   }
   s = wave_sum(s);
   if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = s;
@@ -1121,13 +1144,50 @@ __global__ __launch_bounds__(1024) void mean_rows_k(const float* __restrict__ ro
   }
 }
 
+// The same in the order in which blocks that arrive add: eight rows two by two, a chain over every 64th eight, lanes.  row_loss has a multiple of eight places.
+// 64 * U eights at a time.
+template <int U>
+__global__ __launch_bounds__(1024) void mean_arrived_k(const float* __restrict__ row_loss, int B, float* __restrict__ loss) {
+  static_assert(kCeRows == 8, "load8");
+  __shared__ float part[64 * U];
+  const int tid = threadIdx.x, n = (B + kCeRows - 1) / kCeRows;
+  float s = 0.f;
+  for (int p0 = 0; p0 < n; p0 += 64 * U) {
+    if (p0 > 0) __syncthreads();                                // the eights before have been added
+    for (int p = tid; p < 64 * U && p0 + p < n; p += blockDim.x) {
+      float r[kCeRows];
+      load8(row_loss + (size_t)(p0 + p) * kCeRows, r);
+#pragma unroll
+      for (int u = 0; u < kCeRows; ++u) r[u] = (p0 + p) * kCeRows + u < B ? r[u] : 0.f;
+      part[p] = ((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7]));
+    }
+    __syncthreads();
+    if (tid < 64) {
+      float x[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) x[u] = part[tid + 64 * u];    // beyond n: not used
+#pragma unroll
+      for (int u = 0; u < U; ++u) s += p0 + tid + 64 * u < n ? x[u] : 0.f;
+    }
+  }
+  if (tid >= 64) return;
+  s = wave_sum(s);
+  if (tid == 0) *loss = s / (float)B;
+}
+
 // One block for everything where its lane groups need at most two rounds of short rows (or one of longer ones), else a wavefront per row and the
 // mean by the last block.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean kernel; the last without that
 // launch, above): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4, 4096 x 10 11.4 / 24 / 6.4, 4096 x
 // 1000 bfloat16 16.8 / - / 7.8 (on logits that no cache holds 21.8 / - / 9.1), 16384 x 1000 bfloat16 62 / - / 19.
 static int ce_lanes(int classes) { return classes <= 16 ? 8 : classes <= 64 ? 16 : classes <= 128 ? 32 : 64; }       // of a row in the one-block kernel
 static bool ce_one_block(int B, int classes) { return classes <= 1024 && B <= (classes <= 256 ? 2 : 1) * (1024 / ce_lanes(classes)); }
-int softmax_ce_arrives(int B, int classes) { return !ce_one_block(B, classes) && classes <= 1024; }
+// Arriving costs a block its wait for the partial and the counters, a launch behind the rows 2 us of the host's time and one of the GPU's.  us a call, arriving / two launches (bound by the host
+// up to 6.4 or 7.2, from machine to machine): bfloat16 4096 rows of 40 classes 4.7 / 6.4, 300 6.0 / 6.4, 8192 of 40 5.9 / 6.4, 200 6.9 / 6.5, 300 8.1 / 7.6, 16384 of 40 8.4 / 7.3, 200
+// 10.5 / 9.2, 300 12.5 / 11.4; long rows hide it: 1000 classes 4096 rows 7.2 / 7.2, 9000 11.8 / 12.6, 16384 16.2 / 18.5, 60000 45 / 49, fp32 even.  In captured calls, which have no counters,
+// two launches take 4.0 (600 x 40), 4.5 (4096 x 40), 5.7 (4096 x 300) and 10.6 (7000 x 1000).
+int softmax_ce_arrives(int B, int classes) {
+  return !ce_one_block(B, classes) && classes <= 1024 && (classes > 512 || B <= 4096 || (classes <= 256 && B <= 8192));
+}
 
 template <typename T>
 static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* labels, int B, int classes, float* row_loss, T* dlogits,
@@ -1144,15 +1204,23 @@ static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* la
 #undef FTP_CE_ONE
     return;
   }
-  const dim3 rows((unsigned)((B + kCeRows - 1) / kCeRows));
   const bool al = ((uintptr_t)logits | (uintptr_t)dlogits) % 16 == 0;      // the buffers are the caller's
-#define FTP_CE_WAVE(E, VEC, AL)   hipLaunchKernelGGL((softmax_ce_wave_k<T, E, VEC, AL>), rows, dim3(kCeRows * 64), 0, st, logits, labels, B, classes, row_loss, arrived, dlogits, loss)
-#define FTP_CE_WAVE8(E) do { if (al) FTP_CE_WAVE(E, 8, true); else FTP_CE_WAVE(E, 8, false); } while (0)
+  const int mean_threads = B <= 2048 ? 256 : 1024;
   if (classes > 1024) {
     hipLaunchKernelGGL(softmax_ce_k<T>, dim3(B), dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits);
-    hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(B <= 2048 ? 256 : 1024), 0, st, row_loss, B, B, loss);
+    hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(mean_threads), 0, st, row_loss, B, loss);
     return;
   }
+  const bool may = softmax_ce_arrives(B, classes), arrives = may && arrived;
+  const bool wide = sizeof(T) == 2 && classes > 256 && B > 4096;             // eight rows a block, see softmax_ce_rows_k
+#define FTP_CE_WAVE(E, VEC, AL)                                                                                                                                  \
+  do {                                                                                                                                                           \
+    if (arrives) hipLaunchKernelGGL((softmax_ce_wave_k<T, E, VEC, AL>), dim3((B + kCeRows - 1) / kCeRows), dim3(kCeRows * 64), 0, st, logits, labels, B, classes, \
+                                    row_loss, arrived, dlogits, loss);                                                                                           \
+    else if (wide) hipLaunchKernelGGL((softmax_ce_rows_k<T, E, VEC, AL, 8>), dim3((B + 7) / 8), dim3(512), 0, st, logits, labels, B, classes, row_loss, dlogits);  \
+    else hipLaunchKernelGGL((softmax_ce_rows_k<T, E, VEC, AL, 4>), dim3((B + 3) / 4), dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits);          \
+  } while (0)
+#define FTP_CE_WAVE8(E) do { if (al) FTP_CE_WAVE(E, 8, true); else FTP_CE_WAVE(E, 8, false); } while (0)
   if (classes % 8 == 0 && classes > 256) { if (classes <= 512) FTP_CE_WAVE8(8); else FTP_CE_WAVE8(16); }
   else if (classes <= 64) FTP_CE_WAVE(1, 1, false);
   else if (classes <= 128) FTP_CE_WAVE(2, 1, false);
@@ -1161,7 +1229,10 @@ static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* la
   else FTP_CE_WAVE(16, 1, false);
 #undef FTP_CE_WAVE8
 #undef FTP_CE_WAVE
-  if (!arrived) hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(64), 0, st, row_loss, (int)rows.x, B, loss);      // in the same order
+  if (arrives) return;
+  if (may && B <= 1024) hipLaunchKernelGGL(mean_arrived_k<2>, dim3(1), dim3((B + 511) / 512 * 64), 0, st, row_loss, B, loss);        // no counters: bit for bit the same
+  else if (may) hipLaunchKernelGGL(mean_arrived_k<16>, dim3(1), dim3(B > 7680 ? 1024 : (B + 511) / 512 * 64), 0, st, row_loss, B, loss);
+  else hipLaunchKernelGGL(mean_rows_k, dim3(1), dim3(mean_threads), 0, st, row_loss, B, loss);
 }
 
 void softmax_ce(int dt, hipStream_t st, const void* logits, const int32_t* labels, int B, int classes,

@@ -481,7 +481,8 @@ static bool deep_plan(int dt, size_t M, int R, int NC, bool dgrad, DeepPlan* d, 
   // 960 -> 160 forward 15.7 (2 x 5, 49 blocks), 12.3 (2 x 2, 147), 11.8 (1 x 3, 196), 10.4 (1 x 1, 490); its mirror, with residual, 13.5, 8.7, 8.5, 7.3;
   // 1280 -> 320 data gradient 16.1 (2 x 5, 98), 13.0 (2 x 3, 196), 11.3 (2 x 2, 245), 13.8 (1 x 1, 980); 320 -> 960 11.6 (2 x 5, 294), 8.9 (4 x 3, 250).
   // With sums, bfloat16: up to two.  What such a layer waits for is z, and of the larger tiles two blocks at most share a CU: width 1.4, batch 128, 4 steps
-  // 26.98 ms with 4 x 3 and 4 x 4, 26.85 without; 4 x 5 (one block) 25088 rows 136 -> 816 67 us, 4 x 4 51, without sums 33.
+  // 26.92 ms with tiles of four, 26.85 without, recomputing at 224x224 11.48 / 11.47, units 15-18 batch 64 4.278 / 4.273, 161x193 8.12 / 8.12; 4 x 5 (one block) 25088 rows
+  // 136 -> 816 67 us, 4 x 4 51, without sums 33.
   static const int kTiles[][2] = {{4, 5}, {4, 4}, {4, 3}, {4, 2}, {2, 3}, {2, 2}, {2, 1}, {1, 1}};
   int best = 0;
   for (const auto& st : kTiles) {

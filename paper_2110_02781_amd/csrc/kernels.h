@@ -126,7 +126,7 @@ void gap_fwd(int dt, hipStream_t st, HView in, const BnPending& pend, float eps,
 // sums != nullptr: also the partial sums [*P_out][2][C] that bn_bwd_reduce would compute for that BatchNorm + activation
 void gap_bwd(int dt, hipStream_t st, const void* dOut, int N, int HW, int C, void* dIn, const float* open = nullptr, float* sums = nullptr,
              int* P_out = nullptr);
-// dlogits[B][classes] = (softmax - onehot)/B, mean loss into *loss; row_loss: B floats of scratch.  arrived: kCeCounters zeros, zeros again afterwards,
+// dlogits[B][classes] = (softmax - onehot)/B, mean loss into *loss; row_loss: B floats of scratch, rounded up to a multiple of 8.  arrived: kCeCounters zeros, zeros again afterwards,
 // for one call at a time; without them what softmax_ce_arrives takes a launch more
 int softmax_ce_arrives(int B, int classes);
 enum { kCeRows = 8, kCeGroups = 32, kCeLine = 16, kCeCounters = (kCeGroups + 1) * kCeLine };     // rows of a block, groups of blocks

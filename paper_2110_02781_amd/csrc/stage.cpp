@@ -565,7 +565,7 @@ extern "C" int ftp_stage_create_ex(const ftp_model* m, int a, int b, int batch, 
       if ((rc = dev_alloc(&s->dzring[i], s->dzring_bytes))) { stage_free(s); return rc; }
   }
   if ((rc = dev_alloc(&s->bn_part, (size_t)kBnPartials * 2 * max_c * 4)) || (rc = dev_alloc(&s->coef, (size_t)3 * max_c * 4)) ||
-      (rc = dev_alloc(&s->ws, ws_floats * 4)) || (rc = dev_alloc(&s->row_loss, (size_t)batch * 4)) || (s->has_loss && (rc = dev_alloc(&s->arrived, kCeCounters * 4)))) { stage_free(s); return rc; }
+      (rc = dev_alloc(&s->ws, ws_floats * 4)) || (rc = dev_alloc(&s->row_loss, align_up((size_t)batch, 8) * 4)) || (s->has_loss && (rc = dev_alloc(&s->arrived, kCeCounters * 4)))) { stage_free(s); return rc; }
   if (s->im2col_elems && (rc = dev_alloc(&s->im2col, s->im2col_elems * s->es))) { stage_free(s); return rc; }
   if (s->defers && ((rc = dev_alloc(&s->dz_store, s->dz_cap)) || (rc = dev_alloc(&s->parts, s->part_cap * 4)))) { stage_free(s); return rc; }
   if (!s->defers && s->ws_fused_floats && (rc = dev_alloc(&s->ws_fused, s->ws_fused_floats * 4))) { stage_free(s); return rc; }
@@ -1618,7 +1618,7 @@ extern "C" int ftp_stage_update(ftp_stage* s, const ftp_sgd* opt, void* stream) 
 }
 
 // ------------------------------------------------------------ loss without a stage, without allocation
-// Sums of row losses of ftp_softmax_ce_static: partial results inside the call.  One copy per GPU, held until the
+// Row losses of ftp_softmax_ce_static, or sums of eight: partial results inside the call.  One copy per GPU, held until the
 // process ends; in host code the name is only a handle for hipGetSymbolAddress, the kernels get the address.
 enum { kStaticLossMaxBatch = FTP_STATIC_LOSS_MAX_BATCH, kStaticMaxDevices = 64, kStaticStreams = 64 };
 static __device__ __align__(256) float scratch[kStaticLossMaxBatch + kStaticStreams * kCeCounters];

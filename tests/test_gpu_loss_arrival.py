@@ -7,8 +7,10 @@ import synth
 
 pytestmark = pytest.mark.gpu
 
-# one block and a few rows, 31, 32 and 33 blocks (the groups), a last block of one row, 513 and more blocks
-SIZES = [(17, 1000), (248, 300), (256, 1000), (257, 300), (600, 33), (1025, 65), (4097, 264), (4096, 9), (16390, 9)]
+# one block and a few rows, 31, 32 and 33 blocks (the groups), a last block of one row, 513 and more blocks, more than 1024 (a captured call's mean takes them 1024 at a time); rows
+# whose mean is a launch of its own on every stream: short ones beyond 8192 and 256 classes beyond 4096, four and eight rows a block
+SIZES = [(17, 1000), (248, 300), (256, 1000), (257, 300), (600, 33), (1024, 40), (1025, 65), (4097, 250), (4096, 9), (8191, 200), (16390, 520),
+         (4097, 264), (4099, 300), (16390, 9)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
