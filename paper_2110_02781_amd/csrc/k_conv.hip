@@ -1112,7 +1112,8 @@ void dw_bwd_small(int dt, hipStream_t st, const BnBwdIn& bo, const void* w, HVie
 // some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.79 ms a step (of kernels that run beside weight
 // gradients); their data and weight gradients were 1.80 and the passes for dz and the sums another 0.9, on two streams (a step 7.27 -> 6.79 ms; 224x224 fp32 3.51 -> 3.21).
 // bfloat16 tiles of 8 x 16 at stride 1: 207 registers, two blocks to a CU, or scratch with three: 1.12 and 1.24 ms for the stride-1 layers, 1.03 so.
-// ONE: a block of a single tile requests the tile together with the weights and the partial sums.  The eleven sums of a block leave in one round
+// LEN: 0 blocks of a single tile, 1 of up to CHAIN, 2 of more (its own code, with the weights out of the way of the sums that meet inside the loop: for all, block 2 at 112x112 took 1 % longer).
+// A block of a single tile requests the tile together with the weights and the partial sums.  The eleven sums of a block leave in one round
 // through LDS, a wavefront to each in turn.  Both against a request after the prologue and four rounds of twelve numbers: the width-1.4 step
 // 6.82 -> 6.77 ms, a 13-image step of width 0.5 at 161x193 1.070 -> 1.061.
 struct DwBwdArgs {
@@ -1144,19 +1145,20 @@ template <typename T, int S> struct DwBwd {
   // Width 1.4, batch 128: 105.2 us a launch, one chain a block 103.9; with chains of 12 and 8 tiles a step takes 1 % longer.
   enum { CHAIN = S == 1 ? 17 : 25 };
 };
-template <typename T, int S, bool FORM, int NV, bool ONE>
+template <typename T, int S, bool FORM, int NV, int LEN>
 __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // three blocks to a CU: 168 registers
   typedef DwBwd<T, S> X;
   typedef typename X::P PT;
   constexpr int NR = X::NR, VS = X::VS, PW = X::PW;
+  constexpr bool ONE = LEN == 0;
   extern __shared__ __attribute__((aligned(16))) char smem_raw[];
   __shared__ __attribute__((aligned(16))) float vec[FORM ? 5 : 1][64], prv[2][64];
-  __shared__ float met[ONE ? 1 : 11][64];             // sums of the chains that have met
+  __shared__ float met[LEN == 2 ? 11 : 1][64];        // sums of the chains that have met
   __builtin_amdgcn_s_setprio(3);                      // data-gradient chain: ahead of the weight-gradient stream's waves
   const DwPlan& d = p.d;
   const int C = p.C, Hin = p.Hin, Win = p.Win;
   PT* const patch = reinterpret_cast<PT*>(smem_raw);
-  float* const wl = reinterpret_cast<float*>(smem_raw + (ONE ? X::PATCH : X::WEIGHTS));       // [9][VS]
+  float* const wl = reinterpret_cast<float*>(smem_raw + (LEN == 2 ? X::WEIGHTS : X::PATCH));       // [9][VS]
   const int lb = xcd_logical_block();
   const int slab = lb % d.nslab, part = lb / d.nslab, cg0 = slab * d.CGB, t0 = part * p.per, t1 = min(t0 + p.per, d.ntiles);
   const int QB = 2 * d.CGB, seg0 = dw_div(threadIdx.x, d.m_qb), cq = threadIdx.x - seg0 * QB, c4 = cq * 4, gc = cg0 * 8 + c4;
@@ -1266,6 +1268,36 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
   float4 aw[9], s1 = make_float4(0.f, 0.f, 0.f, 0.f), s2 = s1;
 #pragma unroll
   for (int t = 0; t < 9; ++t) aw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
+  // The sums of a chain of tiles meet: the runs of a channel quad are spread over spp threads, eleven vectors of each go through LDS and are summed in a fixed order, a
+  // wavefront to each vector in turn.
+  auto meet = [&](const bool first, const bool last) __attribute__((always_inline)) {
+    float4* const red = reinterpret_cast<float4*>(smem_raw);         // [11][256]
+    const int tid = threadIdx.x, wave = tid >> 6, ch = tid & 63;
+    __syncthreads();
+#pragma unroll
+    for (int t = 0; t < 9; ++t) red[t * 256 + tid] = aw[t];
+    red[9 * 256 + tid] = s1;
+    red[10 * 256 + tid] = s2;
+    __syncthreads();
+    if (ch >= nc) return;
+    for (int v = wave; v < (p.sums ? 11 : 9); v += 4) {
+      const float* src = reinterpret_cast<const float*>(red + v * 256) + ch;
+      // four chains, 6 to 10 additions one behind the other in most layers.  In float64 the blocks of one tile took 4 to 10 % longer; as one chain in fp32 of 16 or 32 the error of fp32
+      // layers with few rows was 2.0 where a pass has 1.7 (25088 x 96), so it is 1.4.
+      float q[4] = {0.f, 0.f, 0.f, 0.f};
+      int sgi = 0;
+#pragma unroll 2
+      for (; sgi + 3 < d.spp; sgi += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) q[u] += src[(sgi + u) * QB * 4];
+      for (; sgi < d.spp; ++sgi) q[0] += src[sgi * QB * 4];
+      float t = (q[0] + q[1]) + (q[2] + q[3]);
+      if (!first) t += met[LEN == 2 ? v : 0][ch];
+      float* dst = v < 9 ? p.gw + ((size_t)part * 9 + v) * C : p.sums + ((size_t)part * 2 + v - 9) * C;
+      if (last) dst[cg0 * 8 + ch] = t;
+      else met[LEN == 2 ? v : 0][ch] = t;
+    }
+  };
   for (int tile = t0; tile < (ONE ? t0 + 1 : t1); ++tile) {
     if (!ONE) request();
     if (!ONE && tile > t0) __syncthreads();           // the tile before has been read
@@ -1360,42 +1392,16 @@ __global__ __launch_bounds__(256, 3) void dw_bwd_k(DwBwdArgs p) {        // thre
         }
       }
     }
-    // The sums of CHAIN tiles (or of the block's last) meet: the runs of a channel quad are spread over spp threads, eleven vectors of each go through LDS and are
-    // summed in a fixed order, a wavefront to each vector in turn.
-    const bool last = ONE || tile + 1 == t1;
-    if (!last && (tile + 1 - t0) % X::CHAIN != 0) continue;
-    float4* const red = reinterpret_cast<float4*>(smem_raw);         // [11][256]
-    const int tid = threadIdx.x, wave = tid >> 6, ch = tid & 63;
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < 9; ++t) red[t * 256 + tid] = aw[t];
-    red[9 * 256 + tid] = s1;
-    red[10 * 256 + tid] = s2;
-    __syncthreads();
-    if (ch < nc)
-      for (int v = wave; v < (p.sums ? 11 : 9); v += 4) {
-        const float* src = reinterpret_cast<const float*>(red + v * 256) + ch;
-        // four chains, 6 to 10 additions one behind the other in most layers.  In float64 the blocks of one tile took 4 to 10 % longer; as one chain in fp32 of 16 or 32 the error of fp32
-        // layers with few rows was 2.0 where a pass has 1.7 (25088 x 96), so it is 1.4.
-        float q[4] = {0.f, 0.f, 0.f, 0.f};
-        int sgi = 0;
-#pragma unroll 2
-        for (; sgi + 3 < d.spp; sgi += 4)
-#pragma unroll
-          for (int u = 0; u < 4; ++u) q[u] += src[(sgi + u) * QB * 4];
-        for (; sgi < d.spp; ++sgi) q[0] += src[sgi * QB * 4];
-        float t = (q[0] + q[1]) + (q[2] + q[3]);
-        if (!ONE && tile - t0 >= X::CHAIN) t += met[ONE ? 0 : v][ch];
-        float* dst = v < 9 ? p.gw + ((size_t)part * 9 + v) * C : p.sums + ((size_t)part * 2 + v - 9) * C;
-        if (last) dst[cg0 * 8 + ch] = t;
-        else met[ONE ? 0 : v][ch] = t;
-      }
-    if (!ONE) {
+    if constexpr (LEN == 2) {
+      const bool last = tile + 1 == t1;
+      if (!last && (tile + 1 - t0) % X::CHAIN != 0) continue;
+      meet(tile - t0 < X::CHAIN, last);
 #pragma unroll
       for (int t = 0; t < 9; ++t) aw[t] = make_float4(0.f, 0.f, 0.f, 0.f);
       s1 = s2 = aw[0];
     }
   }
+  if constexpr (LEN < 2) meet(true, true);
 }
 
 static DwPlan dw_bwd_plan(int dt, const ConvGeom& g, int* per, int* P) {
@@ -1446,13 +1452,18 @@ void dw_bwd(int dt, hipStream_t st, const void* dA, const HView* own, const BnPe
   a.prev = DwPrev{in.z, in.scale, in.shift, in.act};
   if (a.d.PH > (g.stride == 1 ? 10 : 5) || a.d.PW > (g.stride == 1 ? (dt == 0 ? DwBwd<float, 1>::PW : DwBwd<bf16_t, 1>::PW) : 9)) { launch_plan_failed("depthwise backward patch beyond the kernel's"); return; }
   const dim3 grid((unsigned)P * a.d.nslab);
-#define FTP_DW_BWD1(T, S, NV, ONE)                                                                            \
+#define FTP_DW_BWD1(T, S, NV, LEN)                                                                            \
   do {                                                                                                        \
-    const size_t lds = ONE ? DwBwd<T, S>::LDS_ONE : DwBwd<T, S>::LDS_MORE;                                    \
-    if (own) hipLaunchKernelGGL((dw_bwd_k<T, S, true, NV, ONE>), grid, dim3(256), lds, st, a);                \
-    else hipLaunchKernelGGL((dw_bwd_k<T, S, false, NV, ONE>), grid, dim3(256), lds, st, a);                   \
+    const size_t lds = LEN == 2 ? DwBwd<T, S>::LDS_MORE : DwBwd<T, S>::LDS_ONE;                               \
+    if (own) hipLaunchKernelGGL((dw_bwd_k<T, S, true, NV, LEN>), grid, dim3(256), lds, st, a);                \
+    else hipLaunchKernelGGL((dw_bwd_k<T, S, false, NV, LEN>), grid, dim3(256), lds, st, a);                   \
   } while (0)
-#define FTP_DW_BWD(T, S, NV) do { if (a.per == 1) FTP_DW_BWD1(T, S, NV, true); else FTP_DW_BWD1(T, S, NV, false); } while (0)
+#define FTP_DW_BWD(T, S, NV)                                                                                  \
+  do {                                                                                                        \
+    if (a.per == 1) FTP_DW_BWD1(T, S, NV, 0);                                                                 \
+    else if (a.per <= DwBwd<T, S>::CHAIN) FTP_DW_BWD1(T, S, NV, 1);                                           \
+    else FTP_DW_BWD1(T, S, NV, 2);                                                                            \
+  } while (0)
   if (g.stride == 2) { if (dt == 0) FTP_DW_BWD(float, 2, 1); else FTP_DW_BWD(bf16_t, 2, 2); }
   else if (dt == 0) FTP_DW_BWD(float, 1, 3);
   else if (fill == 3) FTP_DW_BWD(bf16_t, 1, 3);

@@ -10,12 +10,12 @@ from oracle import models as OM
 pytestmark = pytest.mark.gpu
 
 # (stride, cin, cout, expand, h, w, batch, copies in the batch).  Fewer tiles than partials, one more than as many, two and three to a block with a
-# last block of fewer; odd sizes, a tile of one row and of one column; slabs of 1, 3, 6 and 8 column groups, a last slab of fewer; images of 7, 14 and 28
+# last block of fewer, more than go through one chain of additions; odd sizes, a tile of one row and of one column; slabs of 1, 3, 6 and 8 column groups, a last slab of fewer; images of 7, 14 and 28
 # rows (tiles of 7 in bfloat16) and one row more; an output of up to 2048 rows (its BatchNorm backward is a launch of its own)
 CASES = [(2, 8, 16, 3, 41, 51, 1, 1), (2, 16, 24, 6, 9, 17, 19, 1), (2, 8, 8, 3, 8, 16, 513, 27), (2, 24, 16, 6, 33, 35, 60, 6), (2, 16, 32, 4, 45, 50, 48, 4),
-         (2, 8, 16, 6, 2, 1030, 8, 1), (2, 16, 16, 6, 7, 1, 700, 35),
+         (2, 8, 16, 6, 2, 1030, 8, 1), (2, 16, 16, 6, 7, 1, 700, 35), (2, 8, 8, 3, 8, 16, 13311, 459),
          (1, 8, 16, 3, 41, 51, 1, 1), (1, 16, 24, 6, 14, 14, 32, 4), (1, 16, 16, 5, 15, 14, 33, 3), (1, 24, 24, 6, 28, 30, 4, 1), (1, 8, 8, 3, 8, 16, 513, 27),
-         (1, 24, 16, 6, 33, 35, 60, 6), (1, 88, 40, 6, 7, 7, 64, 8), (1, 8, 16, 6, 2, 1030, 3, 1), (1, 16, 8, 6, 2051, 1, 1, 1)]
+         (1, 24, 16, 6, 33, 35, 60, 6), (1, 88, 40, 6, 7, 7, 64, 8), (1, 8, 16, 6, 2, 1030, 3, 1), (1, 16, 8, 6, 2051, 1, 1, 1), (1, 8, 8, 3, 8, 16, 8721, 459)]
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
