@@ -1109,7 +1109,7 @@ void dw_bwd_small(int dt, hipStream_t st, const BnBwdIn& bo, const void* w, HVie
 // with the six dz under each row of taps, in LDS in fp32 (converted once instead of for up to nine taps); stride 2: quads of 2 x 2 pixels, which
 // four dz values reach (nine products, no parity to branch on).  The weights stay in LDS: in registers, one block less would fit a CU.
 // Bound by memory at stride 2 (112x112x144, batch 64, bfloat16: 126 us, 4.7 TB/s; its passes were 18 + 48 + 106 + 70) and by vector instructions at stride 1,
-// some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.79 ms a step (of kernels that run beside weight
+// some 60 an output value in bfloat16, a third of them for the patch.  MobileNetV2 of width 1.4 at 224x224, batch 128: the 17 layers 1.8 ms a step (of kernels that run beside weight
 // gradients); their data and weight gradients were 1.80 and the passes for dz and the sums another 0.9, on two streams (a step 7.27 -> 6.79 ms; 224x224 fp32 3.51 -> 3.21).
 // bfloat16 tiles of 8 x 16 at stride 1: 207 registers, two blocks to a CU, or scratch with three: 1.12 and 1.24 ms for the stride-1 layers, 1.03 so.
 // LEN: 0 blocks of a single tile, 1 of up to CHAIN, 2 of more (its own code, with the weights out of the way of the sums that meet inside the loop: for all, block 2 at 112x112 took 1 % longer).
