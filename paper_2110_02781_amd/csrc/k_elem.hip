@@ -1176,7 +1176,7 @@ __global__ __launch_bounds__(1024) void mean_arrived_k(const float* __restrict__
 }
 
 // One block for everything where its lane groups need at most two rounds of short rows (or one of longer ones), else a wavefront per row and the
-// mean by the last block.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean kernel; the last without that
+// mean by the last block or a launch behind.  Measured, us a call (block per row and a mean kernel / one block / wavefront per row and a mean kernel; the last without that
 // launch, above): 64 x 100 6.3 / 4.1 / 6.4, 128 x 100 6.3 / 6.4 / 6.4, 16 x 1000 6.4 / 5.3 / 6.4, 32 x 1000 6.4 / 9.0 / 6.4, 4096 x 10 11.4 / 24 / 6.4, 4096 x
 // 1000 bfloat16 16.8 / - / 7.8 (on logits that no cache holds 21.8 / - / 9.1), 16384 x 1000 bfloat16 62 / - / 19.
 static int ce_lanes(int classes) { return classes <= 16 ? 8 : classes <= 64 ? 16 : classes <= 128 ? 32 : 64; }       // of a row in the one-block kernel
@@ -1217,7 +1217,8 @@ static void softmax_ce_launch(hipStream_t st, const T* logits, const int32_t* la
   do {                                                                                                                                                           \
     if (arrives) hipLaunchKernelGGL((softmax_ce_wave_k<T, E, VEC, AL>), dim3((B + kCeRows - 1) / kCeRows), dim3(kCeRows * 64), 0, st, logits, labels, B, classes, \
                                     row_loss, arrived, dlogits, loss);                                                                                           \
-    else if (wide) hipLaunchKernelGGL((softmax_ce_rows_k<T, E, VEC, AL, 8>), dim3((B + 7) / 8), dim3(512), 0, st, logits, labels, B, classes, row_loss, dlogits);  \
+    else if (wide) hipLaunchKernelGGL((softmax_ce_rows_k<T, E, VEC, AL, (sizeof(T) == 2 && E > 4 ? 8 : 4)>), dim3((B + 7) / 8), dim3(512), 0, st, logits, labels, B, \
+                                      classes, row_loss, dlogits);                                                                                               \
     else hipLaunchKernelGGL((softmax_ce_rows_k<T, E, VEC, AL, 4>), dim3((B + 3) / 4), dim3(256), 0, st, logits, labels, B, classes, row_loss, dlogits);          \
   } while (0)
 #define FTP_CE_WAVE8(E) do { if (al) FTP_CE_WAVE(E, 8, true); else FTP_CE_WAVE(E, 8, false); } while (0)
